@@ -101,7 +101,8 @@ kb_status_t kb_normalize(kb_t *kb, void *hip_stream);
  * kb_query_plan_bytes is the host-side planner behind it: the bytes a query of `kind` (0: kb_query, 1:
  * kb_query_sampled, 2: kb_query with KB_FP8_E4M3 queries, 3: kb_query_sampled with them) needs when the knowledge base holds n rows; 0 when the
  * arguments are invalid or the handle does not take that kind of query.  For every n <= capacity it is at most
- * kb_query_workspace_bytes(kb, Q, k).  No device work.
+ * kb_query_workspace_bytes(kb, Q, k).  (A store that is scored whole runs the scan pipeline when given less than this
+ * but enough for that.)  No device work.
  */
 size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k);
 size_t kb_query_plan_bytes(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32_t kind);
@@ -264,9 +265,9 @@ kb_status_t kb_query_counters(const kb_t *kb, const void *workspace_dev, int64_t
  *   "sample_keys"   keys scored by the sampling pass (0 = automatic)
  *   "scan_config"   tile configuration of the scan kernel (0 = automatic)
  *   "wg_per_cu"     resident scan workgroups per compute unit (0 = automatic)
- *   "small_path"    1 (default): a knowledge base of at most 16384 rows, queried with a small batch and no other knob
- *                   set, is scored whole by two launches (no sampling pass, no candidate lists); 0: always the
- *                   scan pipeline.  Both produce the same bits.
+ *   "small_path"    1 (default): a knowledge base of up to some hundred thousand rows, queried with up to 128 queries and
+ *                   no other knob set, is scored whole by two launches (no sampling pass, no candidate lists); 0: always
+ *                   the scan pipeline.  Both produce the same bits.
  *   "profile_stride" of a kb_profile_begin session, every value-th scan launch is timed: launch value/2 of each run of
  *                   `value` launches (0 or 1: every one).  A timed
  *                   launch costs the stream about 12 us of idle time around it; a stride spreads the timed launches

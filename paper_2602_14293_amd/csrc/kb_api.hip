@@ -33,7 +33,13 @@ bool scan_config_info(int key_dtype, int config, ConfigInfo *out)
     KB_SCAN_CONFIGS_BF16(X)
     KB_SCAN_CONFIGS_F32(X)
     KB_SCAN_CONFIGS_FP8(X)
+    KB_SCAN_WHOLE_CONFIGS_BF16(X)
+    KB_SCAN_WHOLE_CONFIGS_FP8(X)
 #undef X
+    if (key_dtype == KB_F32 && config == SMALL_F32_CONFIG) {
+        *out = ConfigInfo{16, 32, 64, 2, 4, 128, 0};
+        return true;
+    }
 #define X(ID, KT, TK, TQ, WM, WN, RBA, NSTAGE, WGPC)                          \
     if (key_dtype == KB_FP8_E4M3 && config == ID) {                           \
         *out = ConfigInfo{TK, TQ, 64 * WM * WN, WM * 2, WGPC, RBA, 0};    \
@@ -95,6 +101,8 @@ bool is_fp8_query_config(int config)
 {
     return config == FP8_QUERY_CONFIG || config == FP8_QUERY_WIDE_CONFIG || (config >= FP8_QUERY_TILED_CONFIG && config <= FP8_QUERY_TILED_CONFIG + 2);
 }
+
+bool is_whole_config(int config) { return config >= 13 && config <= 15; }      // no pipeline with a sampling pass runs them
 
 int key_bytes(kb_dtype_t t) { return t == KB_F32 ? 4 : t == KB_BF16 ? 2 : 1; }
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -299,6 +307,49 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
     lay_out(z, &p);
     *out = p;
     if (sizes) *sizes = z;
+}
+
+// The whole-store plan, where it applies (the knobs ask for a particular scan pipeline).  It saves the latency of a
+// sampling pass, a threshold kernel and the candidate lists, 10 to 20 us per call, and pays for it in the scan's epilogue,
+// which keeps the best three of every group where the pipeline's only tests a bound: about 1.3 us per tile and
+// workgroup.  Measured against the pipeline on stores of 256 and 1024 elements a row, masked and not: up to three tiles
+// for every resident workgroup 1.05 to 1.8 times as fast, with up to 32 queries still 1.0 to 1.3 times at five, with more
+// 0.9 to 1.05 times at four; at ten it loses (0.85 to 1.05).
+constexpr int64_t WHOLE_FINE_GROUPS = 4096;
+constexpr int64_t WHOLE_MAX_ROWS_FEW = 5 * 128 * 2 * DEVICE_CUS, WHOLE_MAX_ROWS = 3 * 128 * 2 * DEVICE_CUS;     // up to 32 queries; up to 128
+bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, WholePlan *out)
+{
+    if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
+    if (n < 1 || Q > 128 || n > (Q > 32 ? WHOLE_MAX_ROWS : WHOLE_MAX_ROWS_FEW) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
+    WholePlan p;
+    if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
+    else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : 16;    // (14: once every resident workgroup gets a tile)
+    else p.config = Q <= 32 ? 1 : 2;
+    // tiles of 32 rows while those of 128 would leave compute units without one
+    if (p.config == 1 && n <= 128 * DEVICE_CUS / 2) p.config = h->dtype == KB_F32 ? SMALL_F32_CONFIG : 13;
+    ConfigInfo ci;
+    if (!scan_config_info(h->dtype, p.config, &ci)) return false;
+    p.tk = ci.tk;
+    p.tq = ci.tq;
+    p.nqb = (int32_t)ceil_div(Q, ci.tq);
+    const int64_t tiles = ceil_div(n, ci.tk);
+    // a group is the rows of one wave while there are few of them (groups_per_tile counts both lane halves of its waves)
+    const int fine_rows = 2 * ci.tk / ci.groups_per_tile;
+    p.fine = tiles * (ci.tk / fine_rows) <= WHOLE_FINE_GROUPS;
+    p.group_rows = p.fine ? fine_rows : ci.tk;
+    p.run_shift = ci.tk >= 64 ? 2 : 0;
+    if (tiles * (ci.tk / p.group_rows) > WHOLE_MAX_GROUPS) return false;
+    p.groups = (int32_t)(tiles * (ci.tk / p.group_rows));
+    // Groups with three of a query's k best are scored again, which costs a call some 5 us: k^3 / 6 / groups^2 of them if
+    // rows come in no order.  One in fifty queries is the limit.
+    if ((double)k * k * k > 0.12 * (double)p.groups * p.groups) return false;
+    const int64_t items = tiles * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
+    p.grid = (int32_t)(items < most ? items : most);
+    p.off_best = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));       // the diagnostics come first, as always
+    p.off_pair = p.off_best + align_up(sizeof(float) * (size_t)Q * p.groups);
+    p.total = p.off_pair + align_up(sizeof(u32x4) * (size_t)Q * p.groups);
+    *out = p;
+    return true;
 }
 
 // Pure function of (handle settings, row count n, Q, k): which kernels run on what, and where everything lives
@@ -520,6 +571,19 @@ __device__ inline uint32_t wave_scan_or(uint32_t x)
     x |= dpp_or<0x143, 0xc>(0u, x);
     return x;
 }
+
+__device__ inline float wave_scan_min(float x)
+{
+    constexpr uint32_t IDLE = 0x7f800000u;      // +inf
+    x = __builtin_fminf(x, as_f32(dpp_or<0x111, 0xf>(IDLE, as_u32(x))));
+    x = __builtin_fminf(x, as_f32(dpp_or<0x112, 0xf>(IDLE, as_u32(x))));
+    x = __builtin_fminf(x, as_f32(dpp_or<0x114, 0xf>(IDLE, as_u32(x))));
+    x = __builtin_fminf(x, as_f32(dpp_or<0x118, 0xf>(IDLE, as_u32(x))));
+    x = __builtin_fminf(x, as_f32(dpp_or<0x142, 0xa>(IDLE, as_u32(x))));
+    x = __builtin_fminf(x, as_f32(dpp_or<0x143, 0xc>(IDLE, as_u32(x))));
+    return x;
+}
+__device__ inline float wave_scan_max(float x) { return -wave_scan_min(-x); }
 
 // buf[0..n) in, buf[0..k) out (the rest of buf is left as it was).  All threads of the workgroup call it (at most 16
 // wavefronts), converged.
@@ -772,20 +836,83 @@ struct FinalArgs {
 // KT = KT_FP8_Q8 stands for fp8 keys with fp8 queries (one fp8 matrix instruction per 64-byte chunk, as in the scan).
 constexpr int KT_FP8_Q8 = 3;
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, uint64_t *buf, uint32_t *ctl, SelectScratch *sc, int64_t row_begin,
-                                                   int64_t row_end, const float *inv_q = nullptr)
+// 32 dot products of one query by one wavefront, accumulated exactly as the scan kernels do: lane (lrow, half) supplies
+// row my_row for lrow and gets, in element i, the product of the row that lane 8 (i / 4) + 4 half + i % 4 supplied
+// (every column holds the same query).
+template <int KT, int UNR> __device__ inline f32x16 score_rows(const void *keys, const void *queries, int d, int64_t my_row, int q)
 {
     constexpr bool Q8 = KT == KT_FP8_Q8;
     constexpr int KTT = Q8 ? (int)KB_FP8_E4M3 : KT;
     constexpr int KEY_BYTES = KeyTraits<KTT>::KEY_BYTES, QRY_BYTES = Q8 ? 1 : KeyTraits<KTT>::QRY_BYTES, BMUL = QRY_BYTES / KEY_BYTES;
+    const int half = (threadIdx.x & 63) >> 5;
+    const size_t key_row_bytes = (size_t)d * KEY_BYTES;
+    const unsigned char *qrow = static_cast<const unsigned char *>(queries) + (size_t)q * d * QRY_BYTES;
+    const int n_groups = (int)(key_row_bytes / (Q8 ? 64 : 32));
+    const unsigned char *krow = static_cast<const unsigned char *>(keys) + (size_t)my_row * key_row_bytes + half * 16;
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    // The loads of UNR groups go out before their matrix instructions (the order of the accumulation does not
+    // change): one memory round trip per UNR groups instead of one per group.
+    if constexpr (Q8) {
+        // one fp8 matrix instruction per 64-byte chunk: lane half h supplies bytes [32h, 32h+32) of its key row
+        // and of the query row, the operand layout the scan uses, so both paths give the same bits
+        const unsigned char *kp = krow + half * 16;
+        auto step = [&](const u32x4 &a0, const u32x4 &a1, const u32x4 &b0, const u32x4 &b1) {
+            const i32x8 av = {(int)a0[0], (int)a0[1], (int)a0[2], (int)a0[3], (int)a1[0], (int)a1[1], (int)a1[2], (int)a1[3]};
+            const i32x8 bv = {(int)b0[0], (int)b0[1], (int)b0[2], (int)b0[3], (int)b1[0], (int)b1[1], (int)b1[2], (int)b1[3]};
+            acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc, 0, 0, 0, 0, 0, 0);
+        };
+        int g = 0;
+        for (; g + UNR <= n_groups; g += UNR) {
+            u32x4 a0[UNR], a1[UNR], b0[UNR], b1[UNR];
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                a0[u] = *reinterpret_cast<const u32x4 *>(kp + (size_t)(g + u) * 64);
+                a1[u] = *reinterpret_cast<const u32x4 *>(kp + (size_t)(g + u) * 64 + 16);
+                b0[u] = *reinterpret_cast<const u32x4 *>(qrow + (size_t)(g + u) * 64 + half * 32);
+                b1[u] = *reinterpret_cast<const u32x4 *>(qrow + (size_t)(g + u) * 64 + half * 32 + 16);
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) step(a0[u], a1[u], b0[u], b1[u]);
+        }
+        for (; g < n_groups; ++g)
+            step(*reinterpret_cast<const u32x4 *>(kp + (size_t)g * 64), *reinterpret_cast<const u32x4 *>(kp + (size_t)g * 64 + 16),
+                 *reinterpret_cast<const u32x4 *>(qrow + (size_t)g * 64 + half * 32), *reinterpret_cast<const u32x4 *>(qrow + (size_t)g * 64 + half * 32 + 16));
+    } else {
+        const unsigned char *qbase = qrow + half * 16 * BMUL;
+        int g = 0;
+        for (; g + UNR <= n_groups; g += UNR) {
+            u32x4 av[UNR], b0[UNR], b1[UNR];
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                av[u] = *reinterpret_cast<const u32x4 *>(krow + (size_t)(g + u) * 32);
+                const unsigned char *qp = qbase + (size_t)(g + u) * 32 * BMUL;
+                b0[u] = *reinterpret_cast<const u32x4 *>(qp);
+                b1[u] = BMUL == 2 ? *reinterpret_cast<const u32x4 *>(qp + 16) : b0[u];
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) Mma<KTT>::run(acc, Mma<KTT>::prepare(av[u]), b0[u], b1[u]);
+        }
+        for (; g < n_groups; ++g) {
+            const u32x4 av = *reinterpret_cast<const u32x4 *>(krow + (size_t)g * 32);
+            const unsigned char *qp = qbase + (size_t)g * 32 * BMUL;
+            const u32x4 b0 = *reinterpret_cast<const u32x4 *>(qp);
+            const u32x4 b1 = BMUL == 2 ? *reinterpret_cast<const u32x4 *>(qp + 16) : b0;
+            Mma<KTT>::run(acc, Mma<KTT>::prepare(av), b0, b1);
+        }
+    }
+    return acc;
+}
+
+template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, uint64_t *buf, uint32_t *ctl, SelectScratch *sc, int64_t row_begin,
+                                                   int64_t row_end, const float *inv_q = nullptr)
+{
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lrow = lane & 31, half = lane >> 5;
     const int cap = a.cand_cap;
     const bool filter = a.qmask != nullptr;
     const uint64_t qm = filter ? a.qmask[q] : 0;
     const float iq = inv_q ? *inv_q : a.invq[q];
-    const size_t key_row_bytes = (size_t)a.d * KEY_BYTES;
-    const unsigned char *qrow = static_cast<const unsigned char *>(a.queries) + (size_t)q * a.d * QRY_BYTES;
-    const int n_groups = (int)(key_row_bytes / (Q8 ? 64 : 32));
     uint64_t *thr_local = reinterpret_cast<uint64_t *>(ctl + 2);   // ctl[0] = count, ctl[2..3] = threshold word
     if (tid == 0) {
         ctl[0] = 0;
@@ -795,62 +922,7 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
     for (int64_t row0 = row_begin; row0 < row_end; row0 += 128) {
         int64_t my_row = row0 + wave * 32 + lrow;
         if (my_row >= row_end) my_row = row_end - 1;
-        const unsigned char *krow = static_cast<const unsigned char *>(a.keys) + (size_t)my_row * key_row_bytes + half * 16;
-        f32x16 acc;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-        // The loads of UNR groups go out before their matrix instructions (the order of the accumulation does not
-        // change): one memory round trip per UNR groups instead of one per group (16 where a group is two registers
-        // quadruples, 8 where it is three or four).
-        constexpr int UNR = (Q8 || BMUL == 2) ? 8 : 16;
-        if constexpr (Q8) {
-            // one fp8 matrix instruction per 64-byte chunk: lane half h supplies bytes [32h, 32h+32) of its key row
-            // and of the query row, the operand layout the scan uses, so both paths give the same bits
-            const unsigned char *kp = krow + half * 16;
-            auto step = [&](const u32x4 &a0, const u32x4 &a1, const u32x4 &b0, const u32x4 &b1) {
-                const i32x8 av = {(int)a0[0], (int)a0[1], (int)a0[2], (int)a0[3], (int)a1[0], (int)a1[1], (int)a1[2], (int)a1[3]};
-                const i32x8 bv = {(int)b0[0], (int)b0[1], (int)b0[2], (int)b0[3], (int)b1[0], (int)b1[1], (int)b1[2], (int)b1[3]};
-                acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc, 0, 0, 0, 0, 0, 0);
-            };
-            int g = 0;
-            for (; g + UNR <= n_groups; g += UNR) {
-                u32x4 a0[UNR], a1[UNR], b0[UNR], b1[UNR];
-#pragma unroll
-                for (int u = 0; u < UNR; ++u) {
-                    a0[u] = *reinterpret_cast<const u32x4 *>(kp + (size_t)(g + u) * 64);
-                    a1[u] = *reinterpret_cast<const u32x4 *>(kp + (size_t)(g + u) * 64 + 16);
-                    b0[u] = *reinterpret_cast<const u32x4 *>(qrow + (size_t)(g + u) * 64 + half * 32);
-                    b1[u] = *reinterpret_cast<const u32x4 *>(qrow + (size_t)(g + u) * 64 + half * 32 + 16);
-                }
-#pragma unroll
-                for (int u = 0; u < UNR; ++u) step(a0[u], a1[u], b0[u], b1[u]);
-            }
-            for (; g < n_groups; ++g)
-                step(*reinterpret_cast<const u32x4 *>(kp + (size_t)g * 64), *reinterpret_cast<const u32x4 *>(kp + (size_t)g * 64 + 16),
-                     *reinterpret_cast<const u32x4 *>(qrow + (size_t)g * 64 + half * 32), *reinterpret_cast<const u32x4 *>(qrow + (size_t)g * 64 + half * 32 + 16));
-        } else {
-            const unsigned char *qbase = qrow + half * 16 * BMUL;
-            int g = 0;
-            for (; g + UNR <= n_groups; g += UNR) {
-                u32x4 av[UNR], b0[UNR], b1[UNR];
-#pragma unroll
-                for (int u = 0; u < UNR; ++u) {
-                    av[u] = *reinterpret_cast<const u32x4 *>(krow + (size_t)(g + u) * 32);
-                    const unsigned char *qp = qbase + (size_t)(g + u) * 32 * BMUL;
-                    b0[u] = *reinterpret_cast<const u32x4 *>(qp);
-                    b1[u] = BMUL == 2 ? *reinterpret_cast<const u32x4 *>(qp + 16) : b0[u];
-                }
-#pragma unroll
-                for (int u = 0; u < UNR; ++u) Mma<KTT>::run(acc, Mma<KTT>::prepare(av[u]), b0[u], b1[u]);
-            }
-            for (; g < n_groups; ++g) {
-                const u32x4 av = *reinterpret_cast<const u32x4 *>(krow + (size_t)g * 32);
-                const unsigned char *qp = qbase + (size_t)g * 32 * BMUL;
-                const u32x4 b0 = *reinterpret_cast<const u32x4 *>(qp);
-                const u32x4 b1 = BMUL == 2 ? *reinterpret_cast<const u32x4 *>(qp + 16) : b0;
-                Mma<KTT>::run(acc, Mma<KTT>::prepare(av), b0, b1);
-            }
-        }
+        const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, my_row, q);    // (16 where a group is two register quadruples, 8 where it is three or four)
         // every column holds the same query; lanes 0..15 of each half own one row each
         float v = acc[0];
 #pragma unroll
@@ -879,6 +951,274 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
         }
     }
     select_topk_desc(buf, (int)ctl[0], a.k, sc, tid, 256);      // buf[0..k): the result in order, zero words where there is none
+}
+
+// ------------------------------------------------------------------------------------------------
+// Whole-store plan, second launch: one workgroup per query selects from what the scan left of every group of rows.
+//
+// The k-th largest of the groups' best scores bounds the k-th best score from below (k distinct rows reach it).  It is
+// found by counting the best scores in equal bins between the smallest and the largest: scores near the top of a store
+// are sparse, so one pass of the counting leaves a handful of groups beyond the k wanted ones; only when many groups
+// share the deciding bin is that bin divided again.  Of the groups that reach the bound the two best rows are known; one
+// in which a third row might reach it as well is scored again, with the instruction sequence of the scan.  Everything
+// that decides is a comparison of final scores, a non-decreasing function of the products, so rows whose scores tie
+// after rounding are never told apart here; the candidate words order them by index.
+// ------------------------------------------------------------------------------------------------
+struct WholeSelectArgs {
+    const void *keys, *queries;
+    const float *inv_norm;
+    const uint64_t *tags, *qmask;       // nullptr when no filter is applied
+    const float *best;                  // ScanArgs::whole_best, whole_pair
+    const u32x4 *pair;
+    int32_t *out_index;
+    float *out_score;
+    uint64_t *stats;
+    int64_t n_keys;
+    int32_t k, d, groups, group_rows, tile_rows, tiles, run_shift, grid;
+};
+constexpr int WHOLE_BINS = 256;          // four a lane of the wavefront that adds them up
+constexpr int WHOLE_CAP = 4096;         // words gathered before they are cut down to the best k: two steps of 1024 threads and more
+constexpr int WHOLE_LIST = 2048;        // groups listed at a time
+constexpr int WHOLE_PER_THREAD = WHOLE_MAX_GROUPS / 1024;
+
+template <int KT> __global__ __launch_bounds__(1024) void whole_select_kernel(WholeSelectArgs a)
+{
+    constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
+    __shared__ __attribute__((aligned(16))) uint64_t buf[WHOLE_CAP];
+    __shared__ __attribute__((aligned(16))) uint32_t hist[WHOLE_BINS];
+    __shared__ uint16_t list[WHOLE_LIST], again[WHOLE_LIST];            // groups that reach the bound; groups to score again
+    __shared__ SelectScratch sc;
+    __shared__ float sh_iq, sh_lo[2][16], sh_hi[2][16];
+    __shared__ uint32_t sh_cnt, sh_bin, sh_above, sh_ge, sh_listed, sh_again;
+    __shared__ uint64_t sh_thr;
+    const int q = blockIdx.x, tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = nt >> 6, k = a.k, groups = a.groups;
+    constexpr float NONE = -__builtin_inff();
+    const float *best = a.best + (size_t)q * groups;
+    const u32x4 *pair = a.pair + (size_t)q * groups;
+    // this thread's groups: tid, tid + nt, ... (at most WHOLE_PER_THREAD: the host picks nt); their loads go out first
+    const int rounds = (groups + nt - 1) / nt;
+    float v[WHOLE_PER_THREAD];
+#pragma unroll
+    for (int u = 0; u < WHOLE_PER_THREAD; ++u)
+        v[u] = u < rounds && tid + u * nt < groups ? best[tid + u * nt] : NONE;
+    const uint64_t qm = a.qmask ? a.qmask[q] : 0ull;
+    if (q == 0 && tid < STAT_WORDS + STAT_PARTIALS) a.stats[tid] = tid == 3 ? (uint64_t)a.grid : 0ull;
+    if (tid < 64) {
+        const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid);
+        if (tid == 0) {
+            sh_iq = inv;
+            sh_cnt = sh_listed = sh_again = 0;
+            sh_thr = 0;
+        }
+    }
+    for (int i = tid; i < WHOLE_BINS; i += nt) hist[i] = 0u;
+    __syncthreads();
+    const float iq = sh_iq;
+    // smallest and largest over the workgroup of what each thread has found (called converged, `turn` alternating)
+    auto reduce_range = [&](float &lo, float &hi, int turn) {
+        lo = wave_scan_min(lo);
+        hi = wave_scan_max(hi);
+        if (lane == 63) {
+            sh_lo[turn][wave] = lo;
+            sh_hi[turn][wave] = hi;
+        }
+        __syncthreads();
+        lo = sh_lo[turn][0];
+        hi = sh_hi[turn][0];
+        for (int w = 1; w < nw; ++w) {
+            lo = __builtin_fminf(lo, sh_lo[turn][w]);
+            hi = __builtin_fmaxf(hi, sh_hi[turn][w]);
+        }
+    };
+    float lo = __builtin_inff(), hi = NONE;
+#pragma unroll
+    for (int u = 0; u < WHOLE_PER_THREAD; ++u) {
+        if (v[u] > NONE) {
+            v[u] = v[u] * iq + 0.0f;
+            lo = __builtin_fminf(lo, v[u]);
+            hi = __builtin_fmaxf(hi, v[u]);
+        }
+    }
+    reduce_range(lo, hi, 0);
+    float scale = 0.f;
+    int bin_min = 0;
+    uint32_t need = (uint32_t)k;
+    bool all = false;           // fewer than k groups have an entry: no bound, every entry counts
+    auto bin_of = [&](float f) {        // (never falls as f grows)
+        const int b = (int)((f - lo) * scale);
+        return b < 0 ? 0 : b < WHOLE_BINS - 1 ? b : WHOLE_BINS - 1;
+    };
+    auto passes = [&](float f) { return all || f > hi || (f >= lo && bin_of(f) >= bin_min); };
+    for (int round = 0; round < 4 && hi >= lo; ++round) {
+        scale = hi > lo ? (float)WHOLE_BINS / (hi - lo) : 0.f;
+        if (!(scale < __builtin_inff())) scale = 0.f;
+#pragma unroll
+        for (int u = 0; u < WHOLE_PER_THREAD; ++u)
+            if (u < rounds && v[u] >= lo && v[u] <= hi) atomicAdd(&hist[bin_of(v[u])], 1u);
+        __syncthreads();
+        if (tid < 64) {         // lane l owns bins 4 (63 - l) .. + 3: the scan over the lanes counts the higher bins
+            u32x4 *h = reinterpret_cast<u32x4 *>(hist) + (63 - lane);
+            const u32x4 c = *h;
+            *h = u32x4{0u, 0u, 0u, 0u};     // (for the next round)
+            const uint32_t mine = c[0] + c[1] + c[2] + c[3];
+            const uint32_t incl = wave_scan_add(mine);
+            uint32_t above = incl - mine;
+            if ((above < need && incl >= need) || (lane == 63 && incl < need)) {
+                int b = 0;
+                bool found = false;
+                uint32_t ge = incl;
+#pragma unroll
+                for (int j = 3; j >= 0; --j) {
+                    if (!found && above + c[j] >= need) {
+                        found = true;
+                        b = 4 * (63 - lane) + j;
+                        ge = above + c[j];
+                    } else if (!found) {
+                        above += c[j];
+                    }
+                }
+                sh_bin = (uint32_t)b;
+                sh_above = above;
+                sh_ge = ge;
+            }
+        }
+        __syncthreads();
+        bin_min = (int)sh_bin;
+        all = sh_ge < need;
+        if (sh_ge <= 256u + need || scale == 0.f) break;
+        // many groups share the deciding bin: its own range next
+        need -= sh_above;
+        float lo2 = __builtin_inff(), hi2 = NONE;
+#pragma unroll
+        for (int u = 0; u < WHOLE_PER_THREAD; ++u) {
+            if (v[u] >= lo && v[u] <= hi && bin_of(v[u]) == bin_min) {
+                lo2 = __builtin_fminf(lo2, v[u]);
+                hi2 = __builtin_fmaxf(hi2, v[u]);
+            }
+        }
+        reduce_range(lo2, hi2, (round + 1) & 1);
+        lo = lo2;
+        hi = hi2;
+        scale = 0.f;
+        bin_min = 0;
+    }
+
+    // row at place `rel` of group g (the groups of a tile follow each other)
+    auto row_of = [&](uint32_t g, uint32_t rel) {
+        const uint32_t per_tile = (uint32_t)a.tile_rows / (uint32_t)a.group_rows, tile = g / per_tile;
+        return (uint32_t)whole_row((int32_t)tile, a.tiles, a.tile_rows, a.run_shift, (int)((g - tile * per_tile) * (uint32_t)a.group_rows + rel));
+    };
+    auto append = [&](float product, uint32_t row) {
+        const float f = product * iq + 0.0f;
+        const uint64_t cw = pack_candidate(f, row);
+        if (product > NONE && passes(f) && cw > sh_thr) buf[atomicAdd(&sh_cnt, 1u)] = cw;
+    };
+    // Room for a step that appends up to `most` words; `have`: no more than that are in the buffer (called converged,
+    // nobody appending).
+    auto make_room = [&](uint32_t have, uint32_t most) {
+        if (have + most <= (uint32_t)WHOLE_CAP) return;         // (uniform)
+        select_topk_desc(buf, (int)have, k, &sc, tid, nt);      // cut down to the best k
+        if (tid == 0) {
+            sh_cnt = have < (uint32_t)k ? have : (uint32_t)k;
+            sh_thr = have >= (uint32_t)k ? buf[k - 1] : 0ull;
+        }
+        __syncthreads();
+    };
+    // The listed groups, one a thread: the two best rows, or a place on the list of those to be scored again.
+    auto look_into = [&](uint32_t n, uint32_t have) {
+        for (uint32_t j0 = 0; j0 < n; j0 += (uint32_t)nt) {
+            make_room(have, 2 * (uint32_t)nt);
+            const uint32_t j = j0 + (uint32_t)tid;
+            if (j < n) {
+                const uint32_t g = list[j], row0 = row_of(g, 0);
+                const u32x4 x = pair[g];
+                const float first = best[g], bound = as_f32(x[1]) * iq + 0.0f;
+                // (row0 is the group's lowest row: a bound that ties with the k-th word's score can still lose)
+                if (as_f32(x[1]) > NONE && passes(bound) && pack_candidate(bound, row0) > sh_thr) {
+                    again[atomicAdd(&sh_again, 1u)] = (uint16_t)g;
+                } else {
+                    append(first, row_of(g, x[2] & 255u));
+                    append(as_f32(x[0]), row_of(g, x[2] >> 8 & 255u));
+                }
+            }
+            __syncthreads();
+            have = sh_cnt;
+            if (j0 + (uint32_t)nt < n) __syncthreads();         // (everyone has the count that the next step moves on)
+        }
+        const uint32_t per = ((uint32_t)a.group_rows + 31) / 32, tasks = n > 0 ? sh_again * per : 0u;
+        for (uint32_t t0 = 0; t0 < tasks; t0 += (uint32_t)nw) {     // 32 rows a wavefront
+            __syncthreads();
+            make_room(have, 32 * (uint32_t)nw);
+            const uint32_t t = t0 + (uint32_t)wave;
+            if (t < tasks) {
+                const uint32_t g = again[t / per], place = t % per * 32;
+                const int lrow = lane & 31, half = lane >> 5;
+                const int64_t at = row_of(g, place + lrow), mine = at < a.n_keys ? at : a.n_keys - 1;      // (a place past a group of 16 is some other row)
+                const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 8 : 4>(a.keys, a.queries, a.d, mine, q);      // (128 registers with 1024 threads)
+                const float dot = select16(acc, lrow & 15);
+                const uint32_t rel = place + 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3);
+                const int64_t row = row_of(g, rel);
+                if (lrow < 16 && rel < (uint32_t)a.group_rows && row < a.n_keys) {
+                    const float ik = a.inv_norm[row];
+                    if (!row_removed(ik) && (!a.qmask || (a.tags[row] & qm) != 0)) append(dot * ik, (uint32_t)row);
+                }
+            }
+            __syncthreads();
+            have = sh_cnt;
+        }
+        return have;
+    };
+    // (the bound of a group is at most 2^-16 relative above its best; this only matters for the third row of a group
+    // whose best three all but tie)
+    auto lists = [&](float f) { return f > NONE && passes(f + __builtin_fabsf(f) * 0x1p-15f + 1e-30f); };
+#pragma unroll
+    for (int u = 0; u < WHOLE_PER_THREAD; ++u) {
+        if (u < rounds && lists(v[u])) {
+            const uint32_t at = atomicAdd(&sh_listed, 1u);
+            if (at < (uint32_t)WHOLE_LIST) list[at] = (uint16_t)(tid + u * nt);
+        }
+    }
+    __syncthreads();
+    uint32_t have = 0;
+    if (sh_listed <= (uint32_t)WHOLE_LIST) {
+        have = look_into(sh_listed, 0u);
+    } else {                    // thousands of equal scores: nt groups at a time, the threshold word rises as it goes
+#pragma unroll 1
+        for (int u = 0; u < rounds; ++u) {
+            __syncthreads();
+            if (tid == 0) sh_listed = sh_again = 0;
+            __syncthreads();
+            const float f = tid + u * nt < groups ? best[tid + u * nt] : NONE;
+            if (f > NONE && lists(f * iq + 0.0f)) list[atomicAdd(&sh_listed, 1u)] = (uint16_t)(tid + u * nt);
+            __syncthreads();
+            have = look_into(sh_listed, have);
+        }
+    }
+    // the result in order: few words place themselves by counting the larger ones, many are cut down first
+    const int m = (int)have < k ? (int)have : k;
+    if (have <= 128u) {
+        if (tid < (int)have) {
+            const uint64_t e = buf[tid];
+            int rank = 0;
+#pragma unroll 8
+            for (int j = 0; j < (int)have; ++j) rank += buf[j] > e;
+            if (rank < k) {
+                a.out_index[(size_t)q * k + rank] = (int32_t)candidate_index(e);
+                a.out_score[(size_t)q * k + rank] = candidate_score(e);
+            }
+        }
+    } else {
+        __syncthreads();
+        select_topk_desc(buf, (int)have, k, &sc, tid, nt);
+        if (tid < m) {
+            a.out_index[(size_t)q * k + tid] = (int32_t)candidate_index(buf[tid]);
+            a.out_score[(size_t)q * k + tid] = candidate_score(buf[tid]);
+        }
+    }
+    if (tid >= m && tid < k) {          // fewer than k qualify
+        a.out_index[(size_t)q * k + tid] = -1;
+        a.out_score[(size_t)q * k + tid] = NONE;
+    }
 }
 
 template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalArgs a)
@@ -1243,6 +1583,69 @@ SmallPlan make_small_plan(int32_t Q, int32_t k, int parts)
     return p;
 }
 
+// kb_query by the whole-store plan: two launches.
+kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k,
+                         int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
+{
+    ScanArgs a;
+    memset(&a, 0, sizeof a);
+    a.keys = h->keys;
+    a.inv_norm = h->inv_norm;
+    a.tags = qmask_dev ? h->tags : nullptr;
+    a.queries = queries_dev;
+    a.qmask = qmask_dev;
+    a.n_keys = h->n;
+    a.n_tiles = ceil_div(h->n, p.tk);
+    a.tile_stride = 1;
+    a.d = h->d;
+    a.Q = Q;
+    a.nqb = p.nqb;
+    a.qpad = p.nqb * p.tq;
+    a.whole_best = reinterpret_cast<float *>(ws + p.off_best);
+    a.whole_pair = reinterpret_cast<u32x4 *>(ws + p.off_pair);
+    a.whole_groups = p.groups;
+    a.whole_fine = p.fine;
+    a.whole_run_shift = p.run_shift;
+    const bool timed = h->prof_events && h->prof_used < h->prof_max && h->prof_seen++ % h->prof_stride == h->prof_stride / 2;
+    if (timed) {
+        scan_timing.start = h->prof_events[2 * h->prof_used];
+        scan_timing.stop = h->prof_events[2 * h->prof_used + 1];
+    }
+    const hipError_t launched = launch_scan(h->dtype, p.config, 0, false, p.grid, a, s);
+    scan_timing = ScanTiming();
+    if (launched != hipSuccess) return KB_ERR_DEVICE;
+    if (timed) ++h->prof_used;
+
+    WholeSelectArgs t;
+    t.keys = a.keys;
+    t.queries = queries_dev;
+    t.inv_norm = a.inv_norm;
+    t.tags = a.tags;
+    t.qmask = qmask_dev;
+    t.best = a.whole_best;
+    t.pair = a.whole_pair;
+    t.out_index = indices_out_dev;
+    t.out_score = scores_out_dev;
+    t.stats = reinterpret_cast<uint64_t *>(ws);
+    t.n_keys = h->n;
+    t.k = k;
+    t.d = h->d;
+    t.groups = p.groups;
+    t.group_rows = p.group_rows;
+    t.tile_rows = p.tk;
+    t.tiles = (int32_t)a.n_tiles;
+    t.run_shift = p.run_shift;
+    t.grid = p.grid;
+    const int kt = q8 ? KT_FP8_Q8 : (int)h->dtype;
+    void (*fn)(WholeSelectArgs) = kt == KB_F32 ? &whole_select_kernel<KB_F32> : kt == KB_BF16 ? &whole_select_kernel<KB_BF16>
+                                : kt == KB_FP8_E4M3 ? &whole_select_kernel<KB_FP8_E4M3> : &whole_select_kernel<KT_FP8_Q8>;
+    // as few threads as hold the groups: its length is a dozen barriers, which more wavefronts only make longer (64 queries
+    // x 2048 groups: 7.6 us with 256 threads, 8.2 with 1024)
+    const int threads = p.groups > 8 * 1024 ? 1024 : p.groups > 4 * 1024 ? 512 : 256;
+    hipLaunchKernelGGL(fn, dim3(Q), dim3(threads), 0, s, t);
+    return hipGetLastError() == hipSuccess ? KB_OK : KB_ERR_DEVICE;
+}
+
 }  // namespace
 
 size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
@@ -1264,14 +1667,21 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     if (!any) return 0;
     Plan p;
     lay_out(m, &p);
-    const size_t small = make_small_plan(Q, k, PROBE_MAX_LISTS).total;      // the path of small knowledge bases
-    return p.total > small ? p.total : small;
+    // the whole-store plan: grows with its groups, so with the rows up to where the groups get coarser and to the most it takes
+    size_t total = p.total;
+    const int64_t most[] = {WHOLE_FINE_GROUPS * 32, WHOLE_FINE_GROUPS * 64, WHOLE_MAX_ROWS, WHOLE_MAX_ROWS_FEW};       // the most rows by group height and by rule
+    for (int64_t n : most)
+        for (int q8 = 0; q8 < 2; ++q8) {
+            WholePlan wp;
+            if (make_whole_plan(kb, n < kb->capacity ? n : kb->capacity, Q, k, false, q8 != 0, &wp) && wp.total > total) total = wp.total;
+        }
+    return total;
 }
 
 size_t kb_query_plan_bytes(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32_t kind)
 {
     if (!kb || n < 0 || n > kb->capacity || Q < 1 || k < 1 || k > KB_K_MAX || kind < 0 || kind > 3) return 0;
-    if (const int parts = small_path_parts(kb, n, Q, (kind & 1) != 0)) return make_small_plan(Q, k, parts).total;
+    if (WholePlan wp; make_whole_plan(kb, n, Q, k, (kind & 1) != 0, (kind & 2) != 0, &wp)) return wp.total;
     Plan p;
     return make_plan(kb, n, Q, k, (kind & 1) != 0, (kind & 2) != 0, &p) ? p.total : 0;
 }
@@ -1293,6 +1703,10 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     if (qmask_dev && !kb->tags) return KB_ERR_NO_TAGS;
     if (kb->n_normalized != kb->n) return KB_ERR_NOT_NORMALIZED;
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & (WS_ALIGN - 1)) != 0) return KB_ERR_WORKSPACE;
+    // (given less memory than the whole-store plan wants, the call runs the pipeline)
+    if (WholePlan wp; make_whole_plan(kb, kb->n, Q, k, draw, q8, &wp) && wp.total <= workspace_bytes)
+        return launch_whole(kb, wp, queries_dev, q8, Q, qmask_dev, k, indices_out_dev, scores_out_dev, static_cast<unsigned char *>(workspace_dev),
+                            static_cast<hipStream_t>(hip_stream));
     if (const int parts = small_path_parts(kb, kb->n, Q, draw)) {
         const SmallPlan sp = make_small_plan(Q, k, parts);
         if (workspace_bytes < sp.total) return KB_ERR_WORKSPACE;
@@ -1378,6 +1792,9 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         while (p.sample_tiles > 0 && ((int64_t)p.sample_tiles << (a.sample_group_shift + 1)) <= p.sample_slots) ++a.sample_group_shift;
         a.region_cap = p.region_cap;
         a.draw = dr;
+        a.whole_best = nullptr;
+        a.whole_pair = nullptr;
+        a.whole_groups = a.whole_fine = a.whole_run_shift = 0;
         a.tile_stride = 1;
         a.row_mul = 0;
         a.row_run_shift = 0;
@@ -1609,7 +2026,7 @@ kb_status_t kb_set_tuning(kb_t *kb, const char *name, int64_t value)
     if (!strcmp(name, "sample_keys")) kb->tune_sample_keys = value;
     else if (!strcmp(name, "scan_config")) {
         ConfigInfo ci;
-        if (value != 0 && !scan_config_info(kb->dtype, (int)value, &ci)) return KB_ERR_INVALID_ARG;
+        if (value != 0 && (!scan_config_info(kb->dtype, (int)value, &ci) || is_whole_config((int)value))) return KB_ERR_INVALID_ARG;
         kb->tune_config = value;
     } else if (!strcmp(name, "small_path")) {
         if (value > 1) return KB_ERR_INVALID_ARG;

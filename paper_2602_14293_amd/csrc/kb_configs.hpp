@@ -25,6 +25,17 @@
     X(7, KB_FP8_Q8, 128, 128, 2, 2, 64, 3, 2)    \
     X(8, KB_FP8_Q8, 128, 256, 2, 2, 64, 3, 1)
 
+// ... of the whole-store plan only (it also takes those above with query blocks of up to 128).  13: the shortest scans, one wavefront
+// per workgroup with nearly a whole row of each of its 32 keys in flight at once.  14: some ten thousand rows and
+// up to 64 queries, one tile per resident workgroup (65,536 x 768 keys: 23.7 us, 25.1 with config 12).
+#define KB_SCAN_WHOLE_CONFIGS_BF16(X)            \
+    X(13, KB_BF16, 32, 32, 1, 1, 128, 9, 2)      \
+    X(14, KB_BF16, 128, 64, 4, 1, 128, 3, 2)
+#define KB_SCAN_WHOLE_CONFIGS_FP8(X)             \
+    X(13, KB_FP8_E4M3, 32, 32, 1, 1, 64, 12, 2)
+// ... and of a kernel of its own, for f32 rows (kb_scan_f32.hip): tiles of 16 rows
+constexpr int SMALL_F32_CONFIG = 15;
+
 // Software-pipelined configurations (kb_scan_sp.hpp): XS(id, key dtype, TQ, NSA, NSB); 256-row tiles, 512 threads,
 // NSA / NSB = ring depth of key / query chunks in LDS.
 // bf16: the loads are issued between the MFMAs (IL mode)

@@ -269,6 +269,132 @@ __device__ inline void sample_epilogue(const f32x16 (&acc)[IB][JB], const EpiSid
 }
 
 // ------------------------------------------------------------------------------------------------
+// Whole-store plan: per query and group of rows (the rows of the tile) the two best qualifying products, exact, and an
+// upper bound on every other one.
+// ------------------------------------------------------------------------------------------------
+struct TopTwo {
+    float first, second;       // products; -inf where there is none
+    float bound;               // no other row of the group has a larger product
+    uint32_t rows;             // tile-local rows: first | second << 8
+};
+// The same of the rows of both arguments.
+__device__ inline TopTwo join(const TopTwo &a, const TopTwo &b)
+{
+    const bool swap = b.first > a.first;
+    const TopTwo x = swap ? b : a, y = swap ? a : b;
+    const bool keep = x.second >= y.first;
+    TopTwo r;
+    r.first = x.first;
+    r.second = keep ? x.second : y.first;
+    r.rows = keep ? x.rows : (x.rows & 255u) | (y.rows << 8 & 0xff00u);
+    r.bound = __builtin_fmaxf(__builtin_fmaxf(x.bound, y.bound), keep ? y.first : __builtin_fmaxf(x.second, y.second));
+    return r;
+}
+
+// One wave column: the lane's 16 * IB elements.  As in the sampling search the element's number replaces the product's
+// low five bits, here with the product left a float: one maximum and two medians per element keep the largest three
+// in order.  The first two are then recomputed exactly; the third bounds the rest once its low bits are allowed
+// for (2^-17 relative).  dead: bit r set = row r of the wave's 32 * IB does not count (removed, or past the end).
+template <int IB, int JB>
+__device__ inline TopTwo whole_column(const f32x16 (&acc)[IB][JB], int jb, const EpiSide &sd, bool filter, uint64_t qm, int wave_row0, int half,
+                                      uint64_t dead)
+{
+    const float none = as_f32(0xff7fffe0u);        // the lowest finite value but for its low bits
+    float m1 = none, m2 = none, m3 = none;
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib) {
+        float v[16];
+#pragma unroll
+        for (int run = 0; run < 4; ++run) {
+            const int rl = wave_row0 + ib * 32 + 8 * run + 4 * half;
+            const f32x4 ik4 = *reinterpret_cast<const f32x4 *>(sd.invk + rl);
+            const float ik[4] = {ik4.x, ik4.y, ik4.z, ik4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * run + e] = as_f32((as_u32(acc[ib][jb][4 * run + e] * ik[e]) & ~31u) | (uint32_t)(ib * 16 + 4 * run + e));
+            if (filter) {
+                const u32x4 t0 = *reinterpret_cast<const u32x4 *>(sd.tag + rl), t1 = *reinterpret_cast<const u32x4 *>(sd.tag + rl + 2);
+                const uint32_t lo[4] = {t0.x, t0.z, t1.x, t1.z}, hi[4] = {t0.y, t0.w, t1.y, t1.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * run + e] = ((lo[e] & (uint32_t)qm) | (hi[e] & (uint32_t)(qm >> 32))) != 0 ? v[4 * run + e] : none;
+            }
+        }
+        const uint32_t dead32 = (uint32_t)(dead >> (32 * ib)) >> (4 * half);
+        if (dead != 0) {            // (uniform)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = (dead32 >> (8 * (i >> 2) + (i & 3)) & 1u) ? none : v[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            m3 = __builtin_amdgcn_fmed3f(m2, m3, v[i]);
+            m2 = __builtin_amdgcn_fmed3f(m1, m2, v[i]);
+            m1 = __builtin_fmaxf(m1, v[i]);
+        }
+    }
+    TopTwo t;
+    t.bound = m3 > none ? __builtin_fmaf(__builtin_fabsf(m3), 0x1p-17f, m3) + 0x1p-120f : -__builtin_inff();
+    t.rows = 0;
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const float m = w == 0 ? m1 : m2;
+        const int e = (int)(as_u32(m) & 31u), ib = e >> 4, i = e & 15;
+        const int rl = wave_row0 + (IB > 1 ? ib * 32 : 0) + 4 * half + 8 * (i >> 2) + (i & 3);
+        float dot = select16(acc[0][jb], i);
+        if (IB > 1 && ib == 1) dot = select16(acc[IB - 1][jb], i);
+        const float exact = m > none ? dot * sd.invk[rl] : -__builtin_inff();
+        (w == 0 ? t.first : t.second) = exact;
+        t.rows |= (uint32_t)rl << (8 * w);
+    }
+    if (t.second > t.first) {       // (equal but for the bits that held the numbers)
+        const float f = t.first;
+        t.first = t.second;
+        t.second = f;
+        t.rows = (t.rows >> 8) | (t.rows & 255u) << 8;
+    }
+    return t;
+}
+
+// All waves of the workgroup call this, converged.  `exchange`: (WM - 1) * TQ entries in LDS.
+template <int IB, int JB, int WM, int TQ>
+__device__ inline void whole_epilogue(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wm, int ql0, int half, int64_t tile,
+                                      int q0, const ScanArgs &p, uint64_t dead, u32x4 *exchange)
+{
+    TopTwo t[JB];
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) {
+        t[jb] = whole_column<IB, JB>(acc, jb, sd, filter, filter ? sd.qmask[ql0 + jb * 32] : 0ull, wm * IB * 32, half, dead);
+        TopTwo o;                   // the other half of the rows
+        o.first = __shfl_xor(t[jb].first, 32, 64);
+        o.second = __shfl_xor(t[jb].second, 32, 64);
+        o.bound = __shfl_xor(t[jb].bound, 32, 64);
+        o.rows = (uint32_t)__shfl_xor((int)t[jb].rows, 32, 64);
+        t[jb] = join(t[jb], o);
+        if (!p.whole_fine && wm > 0 && half == 0) exchange[(wm - 1) * TQ + ql0 + jb * 32] = u32x4{as_u32(t[jb].first), as_u32(t[jb].second), as_u32(t[jb].bound), t[jb].rows};
+    }
+    const int64_t group = p.whole_fine ? tile * WM + wm : tile;
+    if (!p.whole_fine) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (wm != 0) return;
+    }
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) {
+        const int ql = ql0 + jb * 32, q = q0 + ql;
+        for (int w = 0; w < (p.whole_fine ? 0 : WM - 1); ++w) {
+            const u32x4 x = exchange[w * TQ + ql];
+            t[jb] = join(t[jb], TopTwo{as_f32(x[0]), as_f32(x[1]), as_f32(x[2]), x[3]});
+        }
+        if (half == 0 && q < p.Q) {
+            const size_t at = (size_t)q * p.whole_groups + group;
+            const uint32_t first_row = p.whole_fine ? (uint32_t)(wm * IB * 32) * 0x0101u : 0u;
+            p.whole_best[at] = t[jb].first;
+            p.whole_pair[at] = u32x4{as_u32(t[jb].second), as_u32(t[jb].bound), t[jb].rows - first_row, 0u};
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
 // Weighted random selection: the same two epilogues on keys = score / T + ln(gain) + Gumbel noise.
 // ------------------------------------------------------------------------------------------------
 

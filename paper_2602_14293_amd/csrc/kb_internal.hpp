@@ -118,6 +118,19 @@ struct Plan {
         off_cand, off_lgain, total;
 };
 
+// The whole-store plan: a small or middling store, or a handful of queries, where the sampling pass, the thresholds
+// and the candidate lists cost more than they save.  Two launches: the tiled scan leaves, per query and group of rows
+// (the rows of a key tile), the best two products and a bound on all others; one workgroup per query finds the k-th
+// best of the groups' best and takes what reaches it, scoring a group again only when a third row of it might.
+// GroupPair as four words: bits of the second best product, bits of the bound, row of the best | row of the second
+// << 8 (within the group), 0.  A group without a (second) entry has -inf there.
+constexpr int WHOLE_MAX_GROUPS = 16384;     // a thread of the selecting workgroup (1024) keeps 16 of them
+struct WholePlan {
+    int32_t config, tk, tq, nqb, grid;
+    int32_t groups, group_rows, fine, run_shift;
+    size_t off_best, off_pair, total;
+};
+
 // Weighted random selection (Section 3, Optimization Selector: its top-k is a random draw whose weights are the
 // entries' predicted gains): entries are ranked by key = score / T + ln(gain) + Gumbel noise instead of by
 // score, which draws k entries without replacement with probability proportional to gain * exp(score / T).
@@ -154,6 +167,11 @@ struct ScanArgs {
     int32_t row_run_shift;
     int32_t d, Q, nqb, qpad, sample_slots, sample_group_shift, region_cap, cand_cap;
     DrawArgs draw;
+    // Whole-store plan (see WholePlan): the best two of every group of rows, nothing is filtered.  nullptr otherwise.
+    float *whole_best;        // [Q][groups]: product of the best row of the group
+    u32x4 *whole_pair;        // [Q][groups]: see GroupPair
+    int32_t whole_groups, whole_fine;       // fine: a group is the rows of one wave, not of the tile
+    int32_t whole_run_shift;                // see whole_row
 };
 
 // Key row behind row r of logical tile `tile` in a sampling pass.  With row_mul the sample is scattered in runs of
@@ -204,6 +222,21 @@ __device__ inline int64_t sample_row0(const ScanArgs &p, int64_t tile, int tk) {
 __device__ inline uint32_t sample_index(const ScanArgs &p, int64_t tile_run, int64_t row0, int tk, int rl)
 {
     return (uint32_t)(p.row_mul ? sample_row(p, tile_run, 0, tk, rl) : row0 + rl);
+}
+
+// Knowledge-base row at place `pos` of a tile of the whole-store plan (>= n_keys: none).  The rows of a tile are not
+// neighbours: where rows are grouped by cluster, a query's best entries are, and a group of neighbours would hold more
+// of them than the two it can name.  The store is cut into runs of R = 2^shift rows; every tile takes one run of each
+// `tiles` consecutive ones, and the rows of a run are a quarter (R = 4) of the tile apart.  Which one moves on by one or
+// two from place to place, so that the distance between a tile's runs is an odd number of them: at 2048 tiles of 128
+// rows a fixed place made it a power of two, and the scan took 120 us where 115 % of the rows took 131 (bf16, d = 1024).
+__host__ __device__ inline int64_t whole_row(int32_t tile, int32_t tiles, int tk, int shift, int pos)
+{
+    const int per = tk >> shift, j = pos & (per - 1);        // runs in a tile, which of them
+    int32_t t = tile + j * (2 - (tiles & 1 ? 0 : 1));
+    if (tiles > 2 * 128) t -= t >= tiles ? tiles : 0;        // (j < 128)
+    else t %= tiles;
+    return (((int64_t)j * tiles + t) << shift) + (shift ? pos / per : 0);
 }
 
 // Where sample `slot` (= tile * groups + group) of query q lives.  The groups of one tile are adjacent (64 bytes per

@@ -22,6 +22,10 @@
 // and only in blocks in which some lane passes do the passing lanes apply the tag predicate and append
 // (raw dot product, row, query) to their wave's private record region (slot = the wave's running count +
 // the lane's rank, plain global store); the wave moves its records to the per-query lists itself.
+//
+// WHOLE (the whole-store plan, see WholePlan): one pass over everything, no filter; per query and group of rows the
+// best two products and a bound on the rest.  65,536 x 768 bf16 rows, 64 queries: 23.7 us, where the sampling pass,
+// the thresholds and the filtered scan took 8.6 + 6.0 + 23.1; writing all products instead took 29.6.
 #pragma once
 #include <type_traits>
 #include "kb_epilogue.hpp"
@@ -141,6 +145,10 @@ struct ScanCfg {
     static constexpr int OFF_THRP = OFF_INVQ + TQ * 4;
     static constexpr int OFF_LGAIN = OFF_THRP + TQ * 4;
     static constexpr int SMEM_BYTES = OFF_LGAIN + TK * 4;
+    // whole-store plan: the bit map of the tile's dead rows and the waves' exchange take the place of what it does not use
+    static constexpr int OFF_DEAD = OFF_INVQ;
+    static constexpr int OFF_EXCHANGE = OFF_DEAD + 16;
+    static constexpr int SMEM_BYTES_WHOLE = OFF_EXCHANGE + (WM - 1) * TQ * 16;
     static constexpr int GROUPS_PER_TILE = WM * 2;
     static_assert(TK % (WM * 32) == 0 && TQ % (WN * 32) == 0, "wave tiles are made of 32x32 blocks");
     static_assert(A_BYTES % 1024 == 0 && B_BYTES % 1024 == 0, "chunk buffers are filled 1 KiB per wave instruction");
@@ -172,14 +180,15 @@ __device__ inline void bare_barrier()
     asm volatile("" ::: "memory");
 }
 
-template <class C, bool SAMPLE, bool DRAW>
+template <class C, bool SAMPLE, bool DRAW, bool WHOLE = false>
 __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p)
 {
     constexpr int TK = C::TK, TQ = C::TQ, RBA = C::RBA, RBB = C::RBB, IB = C::IB, JB = C::JB, NW = C::NW;
     constexpr int LA = C::NIA / NW, LB = C::NIB / NW;           // load instructions per wave per chunk
     constexpr int RSTEP_A = NW * 64 / C::PPRA, RSTEP_B = NW * 64 / C::PPRB;   // rows between a wave's instructions
     static_assert(C::NIA % NW == 0 && C::NIB % NW == 0, "every wave issues the same number of loads");
-    static_assert(RSTEP_A % 32 == 0 && RSTEP_B % 32 == 0, "the swizzle must not change between instructions");
+    constexpr bool SAME_SWZ_A = RSTEP_A % 16 == 0, SAME_SWZ_B = RSTEP_B % 16 == 0;      // the swizzle repeats every 16 rows
+    static_assert(WHOLE || SAME_SWZ_A, "only the whole-store plan takes tiles whose load instructions differ in the swizzle");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void *lds_ptr;
 
@@ -217,7 +226,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
     const uint32_t ldB_piece = (uint32_t)((((wave * 64 + lane) % C::PPRB) ^ swizzle<C::PPRB>(ldB_row)) * 16);
     int ld_tile = vb / nqb, ld_qb = vb % nqb;
     int ld_c = 0, ld_stage = 0;
-    typedef typename std::conditional<SAMPLE, uint64_t, uint32_t>::type OffA;   // a sampling pass addresses rows anywhere
+    typedef typename std::conditional<SAMPLE || WHOLE, uint64_t, uint32_t>::type OffA;   // a sampling pass and the whole-store plan address rows anywhere
     OffA offA[LA];
     uint32_t offB[LB];
     auto ld_setup = [&]() {
@@ -231,19 +240,22 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
             // per lane and load across the items, in registers that end up spilled)
             if constexpr (SAMPLE) asm volatile("" : "+v"(r));
             if constexpr (SAMPLE) offA[j] = (uint64_t)sample_row(p, tile_run, ld_tile, TK, r) * key_row_bytes + ldA_piece;
-            else offA[j] = (uint32_t)(r < last ? r : last) * key_row_bytes + ldA_piece;
+            else if constexpr (WHOLE) {
+                const int64_t row = whole_row(ld_tile, (int32_t)p.n_tiles, TK, p.whole_run_shift, r);
+                offA[j] = (uint64_t)(row < p.n_keys ? row : p.n_keys - 1) * key_row_bytes + (SAME_SWZ_A ? ldA_piece : (uint32_t)((((wave * 64 + lane) % C::PPRA) ^ swizzle<C::PPRA>(r)) * 16));
+            } else offA[j] = (uint32_t)(r < last ? r : last) * key_row_bytes + ldA_piece;
         }
         const int qlast = p.Q - 1 - ld_qb * TQ;
 #pragma unroll
         for (int j = 0; j < LB; ++j) {
             const int r = ldB_row + j * RSTEP_B;
-            offB[j] = (uint32_t)(ld_qb * TQ + (r < qlast ? r : qlast)) * qry_row_bytes + ldB_piece;
+            offB[j] = (uint32_t)(ld_qb * TQ + (r < qlast ? r : qlast)) * qry_row_bytes + (SAME_SWZ_B ? ldB_piece : (uint32_t)((((wave * 64 + lane) % C::PPRB) ^ swizzle<C::PPRB>(r)) * 16));
         }
     };
     auto issue_next = [&]() {
         unsigned char *sA = smem + ld_stage * C::STAGE_BYTES + wave * 1024;
         unsigned char *sB = sA + C::A_BYTES;
-        const unsigned char *gA = static_cast<const unsigned char *>(p.keys) + (SAMPLE ? 0 : (size_t)(ld_tile * tstride) * TK * key_row_bytes) + (size_t)ld_c * RBA;
+        const unsigned char *gA = static_cast<const unsigned char *>(p.keys) + (SAMPLE || WHOLE ? 0 : (size_t)(ld_tile * tstride) * TK * key_row_bytes) + (size_t)ld_c * RBA;
         const unsigned char *gB = static_cast<const unsigned char *>(p.queries) + (size_t)ld_c * RBB;
 #pragma unroll
         for (int j = 0; j < LA; ++j)
@@ -312,14 +324,18 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                     asm volatile("" : "+v"(rl));
                     r = sample_row(p, sample_tile_run(p, tile, TK), tile, TK, rl);
                 }
+                if constexpr (WHOLE) {
+                    r = whole_row(tile, (int32_t)p.n_tiles, TK, p.whole_run_shift, tid);
+                    r = r < p.n_keys ? r : p.n_keys - 1;
+                }
                 my_invk = p.inv_norm[r];
                 if (filter) my_tag = p.tags[r];
                 if constexpr (DRAW) my_lgain = p.draw.log_gain[r];
             }
             if (tid < TQ) {
                 const int q = qb * TQ + tid;            // < qpad: invq, thr64 and thrp are padded arrays
-                if (!SAMPLE || DRAW) my_invq = p.invq[q];      // (a sampling pass on scores runs before 1/|q| exists)
-                if (!SAMPLE) {
+                if ((!SAMPLE && !WHOLE) || DRAW) my_invq = p.invq[q];      // (a sampling pass on scores runs before 1/|q| exists)
+                if (!SAMPLE && !WHOLE) {
                     my_thr64 = p.thr64[q];
                     my_thrp = p.thrp[q];
                 }
@@ -366,16 +382,24 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
         if (++c == NC) {
             // ---- epilogue of the item -----------------------------------------------------------
             // (the side-data buffers were last read in the previous epilogue, at least one barrier ago)
+            if constexpr (WHOLE) {          // (TK is a multiple of 64: whole waves)
+                if (tid < TK) {
+                    const uint64_t dead = __builtin_amdgcn_ballot_w64(row_removed(my_invk) || whole_row(tile, (int32_t)p.n_tiles, TK, p.whole_run_shift, tid) >= p.n_keys);
+                    if (lane == 0) reinterpret_cast<uint64_t *>(smem + C::OFF_DEAD)[wave] = dead;
+                }
+            }
             if (tid < TK) {
                 aux_invk[tid] = my_invk;
                 aux_tag[tid] = my_tag;
                 if constexpr (DRAW) aux_lgain[tid] = my_lgain;
             }
             if (tid < TQ) {
-                aux_invq[tid] = my_invq;
                 aux_qmask[tid] = my_qmask;
-                aux_thr64[tid] = my_thr64;
-                reinterpret_cast<float *>(smem + C::OFF_THRP)[tid] = my_thrp;
+                if constexpr (!WHOLE) {
+                    aux_invq[tid] = my_invq;
+                    aux_thr64[tid] = my_thr64;
+                    reinterpret_cast<float *>(smem + C::OFF_THRP)[tid] = my_thrp;
+                }
             }
             __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0());
             bare_barrier();
@@ -387,6 +411,14 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
             else if (SAMPLE)
                 sample_epilogue<IB, JB, (IB * JB >= 8)>(acc, sd, filter, rowA - lrow, rowB, half, row0, qb * TQ, p,      // (128 accumulators: the search that needs few registers)
                                         (int64_t)tile * C::GROUPS_PER_TILE + wm * 2 + half, sample_tile_run(p, tile, TK), TK);
+            else if constexpr (WHOLE) {
+                const uint64_t *dead_map = reinterpret_cast<const uint64_t *>(smem + C::OFF_DEAD);
+                uint64_t dead = dead_map[wm * IB / 2];              // 64 rows a word
+                dead = IB == 1 ? (uint64_t)(uint32_t)(dead >> (32 * (wm & 1))) : dead;
+                const uint32_t dead_lo = __builtin_amdgcn_readfirstlane((uint32_t)dead), dead_hi = __builtin_amdgcn_readfirstlane((uint32_t)(dead >> 32));
+                whole_epilogue<IB, JB, C::WM, TQ>(acc, sd, filter, wm, rowB, half, tile, qb * TQ, p, (uint64_t)dead_hi << 32 | dead_lo,
+                                                  reinterpret_cast<u32x4 *>(smem + C::OFF_EXCHANGE));
+            }
             else if (DRAW)
                 main_epilogue_draw<IB, JB>(acc, sd, filter, rowA - lrow, rowB, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
             else
@@ -407,11 +439,26 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
         }
     }
 
-    if (!SAMPLE) flush_records(p, my_region, wave_cnt, blockIdx.x * NW + wave);      // what is left in the region
+    if (!SAMPLE && !WHOLE) flush_records(p, my_region, wave_cnt, blockIdx.x * NW + wave);      // what is left in the region
+}
+
+// the first launch of the whole-store plan
+template <class C> hipError_t launch_whole_cfg(int grid, const ScanArgs &a, hipStream_t s)
+{
+    static_assert(C::TQ <= 128 && C::TK <= 128 && C::IB <= 2 && C::SMEM_BYTES_WHOLE * C::WGPC <= 160 * 1024);
+    static LdsAllowed allowed;
+    auto *fn = &kb_scan_kernel<C, false, false, true>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed, C::SMEM_BYTES_WHOLE); e != hipSuccess) return e;
+    hipExtLaunchKernelGGL(fn, dim3(grid), dim3(C::THREADS), C::SMEM_BYTES_WHOLE, s, scan_timing.start, scan_timing.stop, 0, a);
+    return hipGetLastError();
 }
 
 template <class C> hipError_t launch_scan_cfg(bool sample, int grid, const ScanArgs &a, hipStream_t s)
 {
+    if (a.whole_best) {
+        if constexpr (C::TQ <= 128) return launch_whole_cfg<C>(grid, a, s);
+        return hipErrorInvalidValue;
+    }
     // more than 64 KiB of dynamic LDS has to be requested explicitly, once per kernel
     static LdsAllowed allowed[4];
     const bool draw = a.draw.enabled != 0;

@@ -1,0 +1,92 @@
+"""The whole-store plan of kb_query (two launches, no sampling pass) at the sizes where it changes its tiles, its groups
+and its selection: against the oracle and, bit for bit, against the scan pipeline (run_and_check runs both)."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2602_14293_amd import kb as kbmod
+from paper_2602_14293_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def T():
+    import kb_testlib
+
+    return kb_testlib
+
+
+# one wavefront per workgroup up to 16,384 rows, tiles of 64 / 128 rows; groups of a wave up to 4096 of them, of a tile
+# beyond; odd and even numbers of tiles; the fewest rows; query counts at the edges of the blocks of 32, 64 and 128
+@pytest.mark.parametrize("kind,N,d,Q,k", [
+    ("f32", 1, 32, 1, 1), ("f32", 33, 32, 3, 1), ("f32", 4096, 96, 32, 12), ("f32", 16384, 32, 7, 8), ("f32", 16385, 32, 33, 5),
+    ("f32", 131072 + 129, 32, 5, 20), ("bf16", 31, 64, 2, 1), ("bf16", 5000, 128, 32, 10), ("bf16", 16385, 64, 31, 16),
+    ("bf16", 65535, 64, 64, 9), ("bf16", 65537, 128, 40, 32), ("bf16", 20000, 64, 65, 16), ("bf16", 40001, 64, 128, 24),
+    ("bf16", 140001, 64, 11, 64), ("bf16m", 30001, 64, 20, 12), ("bf16m", 70001, 64, 60, 20), ("bf16m", 33333, 64, 100, 16),
+    ("fp8", 12000, 64, 9, 8), ("fp8", 50001, 128, 70, 16), ("q8", 9001, 64, 64, 8), ("q8", 30001, 192, 100, 16)])
+def test_shapes(T, kind, N, d, Q, k):
+    if kind == "f32":
+        w = W.tiny(seed=N, N=N, d=d, Q=Q, k=k)
+    elif kind == "bf16":
+        w = W.clustered(seed=N, N=N, d=d, Q=Q, k=k, centers=max(1, min(64, N // 4)))
+    elif kind == "bf16m":
+        w = W.filtered(seed=N, N=N, d=d, Q=Q, k=k, centers=32, p_tag=0.02, single_bit_qmask=True)
+    else:
+        w = W.compressed(seed=N, N=N, d=d, Q=Q, k=k, centers=32, fp8_queries=kind == "q8")
+    T.run_and_check(w, label=f"{kind} N={N} d={d} Q={Q} k={k}")
+
+
+@pytest.mark.parametrize("dtype,C,mean,d,Q,k", [(torch.float32, 20, 500, 64, 8, 10), (torch.bfloat16, 100, 600, 128, 64, 32),
+                                                (torch.float8_e4m3fn, 60, 500, 128, 20, 24)])
+def test_rows_grouped_by_cluster(T, dtype, C, mean, d, Q, k):
+    """Neighbouring rows resemble each other, some in equal copies: groups are scored again, ties go to the lower index."""
+    w, _, _ = W.grouped(seed=C, C=C, mean_size=mean, d=d, spread=0.002, Q=Q, k=k, dtype=dtype, p_tag=0.4)
+    w.keys[200:400:3] = w.keys[200].clone()
+    w.queries[0] = (w.keys[200].float() * (1.0 if w.scale is None else w.scale[200])).to(w.queries.dtype)
+    T.run_and_check(w, label=f"grouped {dtype}")
+
+
+def test_all_rows_alike_and_removed(T):
+    """Every group's best ties: the groups are gone through a thousand at a time and the lowest live rows win."""
+    w = W.clustered(seed=3, N=90000, d=64, Q=5, k=20, centers=2)
+    w.keys[:] = w.keys[0].clone()
+    kb = T.build_kb(w)
+    gone = torch.arange(0, 60, 2, dtype=torch.int32)
+    kb.remove(gone.cuda())
+    gi, gs = T.gpu_query(kb, w)
+    assert gi.tolist() == [[i for i in range(100) if i >= 60 or i % 2][:20]] * 5 and len(set(gs.ravel().tolist())) == 5
+    kb.close()
+
+
+def test_replays_from_a_graph_and_less_memory(T):
+    w = W.filtered(seed=8, N=50001, d=128, Q=24, k=10, centers=32)
+    kb = T.build_kb(w)
+    L = kbmod.lib()
+    q, qm = w.queries.cuda().contiguous(), w.qmask.cuda()
+    oi, os_ = torch.empty((w.Q, w.k), dtype=torch.int32, device="cuda"), torch.empty((w.Q, w.k), device="cuda")
+    want = kb.query(q, w.k, qm)
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        kb.query(q, w.k, qm, oi, os_)
+    for rep in range(3):
+        oi.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(oi, want[0]) and torch.equal(os_, want[1]), f"replay {rep}"
+    # a workspace that only the pipeline fits into
+    whole = L.kb_query_plan_bytes(kb._h, kb.size, w.Q, w.k, 0)
+    kb.set_tuning("small_path", 0)
+    pipeline = L.kb_query_plan_bytes(kb._h, kb.size, w.Q, w.k, 0)
+    kb.set_tuning("small_path", 1)
+    for have in sorted((whole, pipeline)):
+        ws = torch.empty(have, dtype=torch.uint8, device="cuda")
+        oi.fill_(-7)
+        assert L.kb_query(kb._h, ctypes.c_void_p(q.data_ptr()), 1, w.Q, ctypes.c_void_p(qm.data_ptr()), w.k, ctypes.c_void_p(oi.data_ptr()),
+                          ctypes.c_void_p(os_.data_ptr()), ctypes.c_void_p(ws.data_ptr()), have, None) == (0 if have >= min(whole, pipeline) else 7)
+        torch.cuda.synchronize()
+        assert torch.equal(oi, want[0]) and torch.equal(os_, want[1])
+    kb.close()
