@@ -1325,36 +1325,180 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
 constexpr int PROBE_CAP = 1024;        // LDS candidate buffer of a partial scan (words); k <= 128 fits eight times
 constexpr int PROBE_MAX_LISTS = 64;    // partial lists per query that the merge can take: 64 x 128 = MAX_CAND_CAP words
 
+// A wavefront's stream of 32 key rows and the query row through its own ring of chunks in LDS: every chunk is RB bytes of
+// each row, loaded directly to LDS whole cache lines at a time (fp8: half lines, rows are multiples of 64 bytes), swizzled
+// as in the tiled scan.  No wavefront waits for another.
+template <int KT> struct ProbeRing {
+    static constexpr bool Q8 = KT == KT_FP8_Q8;
+    static constexpr int KTT = Q8 ? (int)KB_FP8_E4M3 : KT;
+    static constexpr int KEY_BYTES = KeyTraits<KTT>::KEY_BYTES, QRY_BYTES = Q8 ? 1 : KeyTraits<KTT>::QRY_BYTES, BMUL = QRY_BYTES / KEY_BYTES;
+    static constexpr int RB = KEY_BYTES == 1 ? 64 : 128, PPR = RB / 16;
+    static constexpr int LOADS = 32 * RB / 1024;                        // load instructions for the keys of a chunk; one more for the query
+    static constexpr int CHUNK = 32 * RB + 256;                         // ... whose bytes follow the keys' (RB * BMUL of 256)
+    static constexpr int DEPTH = KEY_BYTES == 1 ? 14 : 8;
+    static constexpr int BYTES = DEPTH * CHUNK;
+    static_assert((LOADS + 1) * (DEPTH - 2) < 64 && RB * BMUL <= 256, "vmcnt is a 6-bit counter");
+};
+
+// score_rows with the rows taken through the ring (the same instruction sequence per element).
+template <int KT> __device__ inline f32x16 score_rows_ring(const void *keys, const void *queries, int d, int64_t row_begin, int64_t row_end, int q,
+                                                           unsigned char *ring)
+{
+    typedef ProbeRing<KT> R;
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const int lane = threadIdx.x & 63, lrow = lane & 31, half = lane >> 5;
+    const size_t row_bytes = (size_t)d * R::KEY_BYTES;
+    const int NC = (int)(row_bytes / R::RB);
+    const unsigned char *src[R::LOADS];
+#pragma unroll
+    for (int j = 0; j < R::LOADS; ++j) {
+        const int r = j * (64 / R::PPR) + lane / R::PPR;
+        const int64_t row = row_begin + r < row_end ? row_begin + r : row_end - 1;
+        src[j] = static_cast<const unsigned char *>(keys) + (size_t)row * row_bytes + (((lane % R::PPR) ^ swizzle<R::PPR>(r)) * 16);
+    }
+    const unsigned char *qsrc = static_cast<const unsigned char *>(queries) + (size_t)q * d * R::QRY_BYTES + lane * 16;
+    int issued = 0, slot = 0;
+    auto issue = [&]() {
+        unsigned char *dst = ring + slot * R::CHUNK;
+#pragma unroll
+        for (int j = 0; j < R::LOADS; ++j)
+            __builtin_amdgcn_global_load_lds((const void *)(src[j] + (size_t)issued * R::RB), (lds_ptr)(dst + j * 1024), 16, 0, 0);
+        if (lane < R::RB * R::BMUL / 16)
+            __builtin_amdgcn_global_load_lds((const void *)(qsrc + (size_t)issued * R::RB * R::BMUL), (lds_ptr)(dst + 32 * R::RB), 16, 0, 0);
+        ++issued;
+        slot = slot + 1 == R::DEPTH ? 0 : slot + 1;
+    };
+    __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0());        // (the ring's last readers: an earlier call of this wavefront)
+    asm volatile("" ::: "memory");
+    for (int s = 0; s < R::DEPTH - 1 && s < NC; ++s) issue();
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    int stage = 0;
+    const int sw = swizzle<R::PPR>(lrow);
+    for (int c = 0; c < NC; ++c) {
+        if (c + (R::DEPTH - 2) < NC) __builtin_amdgcn_s_waitcnt(waitcnt_vm((R::LOADS + 1) * (R::DEPTH - 2)));
+        else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+        asm volatile("" ::: "memory");
+        const unsigned char *sA = ring + stage * R::CHUNK + lrow * R::RB, *sB = ring + stage * R::CHUNK + 32 * R::RB;
+        if constexpr (R::Q8) {
+            const u32x4 a0 = *reinterpret_cast<const u32x4 *>(sA + (((2 * half) ^ sw) << 4)), a1 = *reinterpret_cast<const u32x4 *>(sA + (((2 * half + 1) ^ sw) << 4));
+            const u32x4 b0 = *reinterpret_cast<const u32x4 *>(sB + half * 32), b1 = *reinterpret_cast<const u32x4 *>(sB + half * 32 + 16);
+            typename Mma<KB_FP8_Q8>::PrepA a;
+            a.lo = a0;
+            a.hi = a1;
+            Mma<KB_FP8_Q8>::run(acc, a, b0, b1);
+        } else {
+#pragma unroll
+            for (int g = 0; g < R::RB / 32; ++g) {
+                const u32x4 a = *reinterpret_cast<const u32x4 *>(sA + (((2 * g + half) ^ sw) << 4));
+                const u32x4 b0 = *reinterpret_cast<const u32x4 *>(sB + (g * 2 + half) * 16 * R::BMUL);
+                const u32x4 b1 = R::BMUL == 2 ? *reinterpret_cast<const u32x4 *>(sB + (g * 2 + half) * 32 + 16) : b0;
+                Mma<R::KTT>::run(acc, Mma<R::KTT>::prepare(a), b0, b1);
+            }
+        }
+        stage = stage + 1 == R::DEPTH ? 0 : stage + 1;
+        asm volatile("" ::: "memory");      // (the slot of the chunk before: its fragments went into matrix instructions issued by now)
+        if (c + (R::DEPTH - 1) < NC) issue();
+    }
+    return acc;
+}
+
+constexpr int PROBE_WAVES = 2;              // scoring wavefronts of a block, 32 rows each at a time; one more forms 1/|q| meanwhile
+constexpr int PROBE_THREADS = 64 * (PROBE_WAVES + 1);
+template <int KT> size_t probe_scan_lds() { return (size_t)PROBE_WAVES * ProbeRing<KT>::BYTES + PROBE_CAP * 8 + sizeof(SelectScratch); }
+
 // Block (p, s, q): part s of `splits` of the rows of cluster probe[q][p], scored exactly as the scan kernels score
 // (same MFMA sequence per element), best k written as a sorted list of candidate words (zero = no entry).
-// Without cluster_offsets the one "cluster" is the whole knowledge base (the path of small knowledge bases).
 // Every block computes 1/|q| of its query itself (one wavefront, the row-norm routine every path uses: the same bits),
-// which saves the launch that would do it once per query: these calls are bound by the latency of their launches.
-// stats (optional): the diagnostics of a query that took this path: no candidates, no sampling, one workgroup per block.
-template <int KT> __global__ __launch_bounds__(256) void probe_scan_kernel(FinalArgs a, const int64_t *cluster_offsets, int n_clusters,
-                                                                         const int32_t *probe, int nprobe, int splits, uint64_t *lists, uint64_t *stats)
+// which saves the launch that would do it once per query.  Such a call is bound by the latency of its loads: nearly a whole
+// row of each of the 32 keys of a wavefront is in flight at once.  8 queries, four clusters of about 1000 rows of 1024
+// bf16 values each (65 MB): 21.3 us, 32.7 us with fragments loaded to registers, a quarter of a row at a time and each
+// lane from a row of its own.
+template <int KT> __global__ __launch_bounds__(PROBE_THREADS) void probe_scan_kernel(FinalArgs a, const int64_t *cluster_offsets, int n_clusters,
+                                                                                        const int32_t *probe, int nprobe, int splits, uint64_t *lists)
+{
+    constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
+    constexpr int THREADS = PROBE_THREADS, STEP = 32 * PROBE_WAVES;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    uint64_t *buf = reinterpret_cast<uint64_t *>(smem_raw + PROBE_WAVES * ProbeRing<KT>::BYTES);
+    SelectScratch *sc = reinterpret_cast<SelectScratch *>(smem_raw + PROBE_WAVES * ProbeRing<KT>::BYTES + PROBE_CAP * 8);
+    __shared__ uint32_t count;
+    __shared__ uint64_t thr_local;
+    __shared__ float inv_q;
+    const int p = blockIdx.x, s = blockIdx.y, q = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lrow = lane & 31, half = lane >> 5;
+    uint64_t *out = lists + ((size_t)q * nprobe * splits + (size_t)p * splits + s) * a.k;
+    const int c = probe[(size_t)q * nprobe + p];
+    bool first = true;          // a cluster named twice is scanned once (the merge takes distinct entries)
+    for (int e = 0; e < p; ++e) first = first && probe[(size_t)q * nprobe + e] != c;
+    int64_t begin = 0, end = 0;
+    if (first && c >= 0 && c < n_clusters) {
+        const int64_t cb = cluster_offsets[c], ce = cluster_offsets[c + 1];
+        if (cb >= 0 && ce <= a.n_keys && cb < ce) {
+            const int64_t len = ((ce - cb + splits - 1) / splits + STEP - 1) / STEP * STEP;    // whole steps
+            begin = cb + (int64_t)s * len;
+            end = begin + len < ce ? begin + len : ce;
+        }
+    }
+    if (begin >= end) {         // workgroup-uniform
+        for (int i = tid; i < a.k; i += THREADS) out[i] = 0ull;
+        return;
+    }
+    if (tid == 0) {
+        count = 0;
+        thr_local = 0;
+    }
+    const uint64_t qm = a.qmask ? a.qmask[q] : 0;
+    for (int64_t row0 = begin; row0 < end; row0 += STEP) {
+        const int64_t base = row0 + wave * 32;
+        const int64_t row = base + 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3);      // lanes 0..15 of each half own one row each
+        const int64_t at = row < end ? row : end - 1;
+        const float ik = a.inv_norm[at];
+        const uint64_t tag = a.qmask ? a.tags[at] : 0;
+        float dot = 0.f;
+        if (wave < PROBE_WAVES && base < end) dot = select16(score_rows_ring<KT>(a.keys, a.queries, a.d, base, end, q, smem_raw + wave * ProbeRing<KT>::BYTES), lrow & 15);
+        if (row0 == begin) {
+            if (wave == PROBE_WAVES) {
+                const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), lane);
+                if (lane == 0) inv_q = inv;
+            }
+            __syncthreads();
+        }
+        if (wave < PROBE_WAVES && lrow < 16 && row < end && !row_removed(ik) && (!a.qmask || (tag & qm) != 0)) {
+            const float value = final_score(dot, ik, inv_q);
+            const uint64_t cw = pack_candidate(value, (uint32_t)row);
+            if (cw > thr_local && value > -__builtin_inff()) buf[atomicAdd(&count, 1u)] = cw;      // < PROBE_CAP: at most STEP appends between compactions
+        }
+        __syncthreads();
+        const uint32_t n = count;
+        if (n + STEP > (uint32_t)PROBE_CAP) {      // uniform: compact to the best k (sorted into buf[0..k))
+            select_topk_desc(buf, (int)n, a.k, sc, tid, THREADS);
+            if (tid == 0) {
+                count = n < (uint32_t)a.k ? n : (uint32_t)a.k;
+                thr_local = n >= (uint32_t)a.k ? buf[a.k - 1] : 0ull;
+            }
+        }
+        __syncthreads();        // (everyone has read the count that the next step moves on)
+    }
+    select_topk_desc(buf, (int)count, a.k, sc, tid, THREADS);
+    for (int i = tid; i < a.k; i += THREADS) out[i] = buf[i];
+}
+
+// A small knowledge base, block (s, q): part s of the rows, as above but with fragments loaded to registers.  It takes the
+// calls whose k is large for the number of rows, which the whole-store plan leaves.
+// stats: the diagnostics of a query that took this path: no candidates, no sampling, one workgroup per block.
+template <int KT> __global__ __launch_bounds__(256) void small_scan_kernel(FinalArgs a, uint64_t *lists, uint64_t *stats)
 {
     constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
     __shared__ __attribute__((aligned(16))) uint64_t buf[PROBE_CAP];
     __shared__ uint32_t ctl[4];
     __shared__ SelectScratch sc;
     __shared__ float inv_q;
-    const int p = blockIdx.x, s = blockIdx.y, q = blockIdx.z, tid = threadIdx.x;
-    if (stats && p == 0 && s == 0 && q == 0 && tid < STAT_WORDS + STAT_PARTIALS)
-        stats[tid] = tid == 3 ? (uint64_t)gridDim.x * gridDim.y * gridDim.z : 0ull;
-    uint64_t *out = lists + ((size_t)q * nprobe * splits + (size_t)p * splits + s) * a.k;
-    const int c = cluster_offsets ? probe[(size_t)q * nprobe + p] : 0;
-    bool first = true;          // a cluster named twice is scanned once (the merge takes distinct entries)
-    for (int e = 0; cluster_offsets && e < p; ++e) first = first && probe[(size_t)q * nprobe + e] != c;
-    int64_t begin = 0, end = 0;
-    if (first && c >= 0 && c < n_clusters) {
-        const int64_t cb = cluster_offsets ? cluster_offsets[c] : 0, ce = cluster_offsets ? cluster_offsets[c + 1] : a.n_keys;
-        if (cb >= 0 && ce <= a.n_keys && cb < ce) {
-            const int64_t len = ((ce - cb + splits - 1) / splits + 127) / 128 * 128;    // whole steps of the scorer
-            begin = cb + (int64_t)s * len;
-            end = begin + len < ce ? begin + len : ce;
-        }
-    }
+    const int s = blockIdx.x, parts = gridDim.x, q = blockIdx.y, tid = threadIdx.x;
+    if (s == 0 && q == 0 && tid < STAT_WORDS + STAT_PARTIALS) stats[tid] = tid == 3 ? (uint64_t)gridDim.x * gridDim.y : 0ull;
+    uint64_t *out = lists + ((size_t)q * parts + s) * a.k;
+    const int64_t len = ((a.n_keys + parts - 1) / parts + 127) / 128 * 128;    // whole steps of the scorer
+    const int64_t begin = (int64_t)s * len, end = begin + len < a.n_keys ? begin + len : a.n_keys;
     if (begin >= end) {         // workgroup-uniform
         if (tid < a.k) out[tid] = 0ull;
         return;
@@ -1368,20 +1512,30 @@ template <int KT> __global__ __launch_bounds__(256) void probe_scan_kernel(Final
     if (tid < a.k) out[tid] = buf[tid];
 }
 
-__global__ __launch_bounds__(256) void probe_merge_kernel(const uint64_t *lists, int n_lists, int k, int32_t *out_index, float *out_score)
+__global__ __launch_bounds__(1024) void probe_merge_kernel(const uint64_t *lists, int n_lists, int k, int32_t *out_index, float *out_score)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     uint64_t *buf = reinterpret_cast<uint64_t *>(smem_raw);
-    const int n = n_lists * k, q = blockIdx.x, tid = threadIdx.x;
+    const int n = n_lists * k, q = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
     SelectScratch *sc = reinterpret_cast<SelectScratch *>(smem_raw + sizeof(uint64_t) * (size_t)(n > k ? n : k) + 16);
-    for (int i = tid; i < n; i += 256) buf[i] = lists[(size_t)q * n + i];
+    for (int i = tid; i < n; i += nt) buf[i] = lists[(size_t)q * n + i];
     __syncthreads();
-    select_topk_desc(buf, n, k, sc, tid, 256);
+    select_topk_desc(buf, n, k, sc, tid, nt);
     if (tid < k) {
         const uint64_t cw = buf[tid];
         out_index[(size_t)q * k + tid] = cw ? (int32_t)candidate_index(cw) : -1;
         out_score[(size_t)q * k + tid] = cw ? candidate_score(cw) : -__builtin_inff();
     }
+}
+
+template <int KT> hipError_t launch_probe_scan(const dim3 &grid, const FinalArgs &f, const int64_t *cluster_offsets_dev, int32_t n_clusters,
+                                               const int32_t *probe_dev, int32_t nprobe, int splits, uint64_t *lists, hipStream_t s)
+{
+    static_assert(2 * (PROBE_WAVES * ProbeRing<KT>::BYTES + PROBE_CAP * 8 + sizeof(SelectScratch) + 64) <= 160 * 1024, "two blocks share a compute unit");
+    static LdsAllowed allowed;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&probe_scan_kernel<KT>), allowed, probe_scan_lds<KT>()); e != hipSuccess) return e;
+    hipLaunchKernelGGL(probe_scan_kernel<KT>, grid, dim3(PROBE_THREADS), probe_scan_lds<KT>(), s, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists);
+    return hipGetLastError();
 }
 
 hipError_t launch_scan(kb_dtype_t dt, int config, int family, bool sample, int grid, const ScanArgs &a, hipStream_t s)
@@ -1502,7 +1656,7 @@ int probe_splits(int Q, int nprobe)
 
 struct ProbePlan {
     int splits;
-    size_t off_invq, off_lists, total;
+    size_t off_lists, total;
 };
 
 bool make_probe_plan(int32_t Q, int32_t k, int32_t nprobe, ProbePlan *out)
@@ -1510,19 +1664,26 @@ bool make_probe_plan(int32_t Q, int32_t k, int32_t nprobe, ProbePlan *out)
     if (Q < 1 || Q > 65535 || k < 1 || k > KB_K_MAX || nprobe < 1 || nprobe > PROBE_MAX_LISTS) return false;
     ProbePlan p;
     p.splits = probe_splits(Q, nprobe);
-    p.off_invq = 0;
-    p.off_lists = align_up((size_t)Q * 4);
+    p.off_lists = 0;
     p.total = p.off_lists + align_up((size_t)Q * nprobe * p.splits * k * 8);
     *out = p;
     return true;
 }
 
 
-// The two launches behind kb_query_probe; also the whole pipeline of kb_query on a small knowledge base
-// (cluster_offsets == nullptr: one "cluster" = every row, nprobe = 1, `stats` zeroed for kb_query_counters).
-kb_status_t launch_probe(kb *h, bool timed_scan, const void *queries_dev, kb_dtype_t q_dtype, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k,
-                         const int64_t *cluster_offsets_dev, int32_t n_clusters, const int32_t *probe_dev, int32_t nprobe, int splits, float *invq,
-                         uint64_t *lists, uint64_t *stats, int32_t *indices_out_dev, float *scores_out_dev, hipStream_t s)
+// The merge of a query's sorted lists, the second launch of the two paths below.
+kb_status_t launch_merge(const uint64_t *lists, int n_lists, int32_t Q, int32_t k, int32_t *indices_out_dev, float *scores_out_dev, hipStream_t s)
+{
+    const int n = n_lists * k, threads = n > 1024 ? 1024 : n > 512 ? 512 : 256;
+    const size_t merge_lds = sizeof(uint64_t) * (size_t)(n > k ? n : k) + 16 + sizeof(SelectScratch);
+    static LdsAllowed merge_allowed;
+    if (allow_dynamic_lds(reinterpret_cast<const void *>(&probe_merge_kernel), merge_allowed, MAX_CAND_CAP * 8 + 16 + sizeof(SelectScratch)) != hipSuccess)
+        return KB_ERR_DEVICE;
+    hipLaunchKernelGGL(probe_merge_kernel, dim3(Q), dim3(threads), merge_lds, s, lists, n_lists, k, indices_out_dev, scores_out_dev);
+    return hipGetLastError() == hipSuccess ? KB_OK : KB_ERR_DEVICE;
+}
+
+FinalArgs list_scan_args(const kb *h, const void *queries_dev, const uint64_t *qmask_dev, int32_t k)
 {
     FinalArgs f;
     memset(&f, 0, sizeof f);
@@ -1531,34 +1692,52 @@ kb_status_t launch_probe(kb *h, bool timed_scan, const void *queries_dev, kb_dty
     f.tags = h->tags;
     f.queries = queries_dev;
     f.qmask = qmask_dev;
-    f.invq = invq;
     f.n_keys = h->n;
     f.d = h->d;
     f.k = k;
     f.cand_cap = PROBE_CAP;
+    return f;
+}
+
+// The two launches behind kb_query_probe.
+kb_status_t launch_probe(kb *h, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k,
+                         const int64_t *cluster_offsets_dev, int32_t n_clusters, const int32_t *probe_dev, int32_t nprobe, int splits,
+                         uint64_t *lists, int32_t *indices_out_dev, float *scores_out_dev, hipStream_t s)
+{
+    const FinalArgs f = list_scan_args(h, queries_dev, qmask_dev, k);
     const dim3 grid(nprobe, splits, Q);
-    const bool timed = timed_scan && h->prof_events && h->prof_used < h->prof_max && h->prof_seen++ % h->prof_stride == h->prof_stride / 2;     // the scoring kernel stands for the scan
+    hipError_t e;
+    switch (q8 ? KT_FP8_Q8 : (int)h->dtype) {
+    case KB_F32: e = launch_probe_scan<KB_F32>(grid, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists, s); break;
+    case KB_BF16: e = launch_probe_scan<KB_BF16>(grid, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists, s); break;
+    case KB_FP8_E4M3: e = launch_probe_scan<KB_FP8_E4M3>(grid, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists, s); break;
+    default: e = launch_probe_scan<KT_FP8_Q8>(grid, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists, s); break;
+    }
+    return e == hipSuccess ? launch_merge(lists, nprobe * splits, Q, k, indices_out_dev, scores_out_dev, s) : KB_ERR_DEVICE;
+}
+
+// kb_query on a small knowledge base that the whole-store plan leaves (k large for the number of rows): two launches.
+kb_status_t launch_small(kb *h, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k, int parts, uint64_t *lists,
+                         uint64_t *stats, int32_t *indices_out_dev, float *scores_out_dev, hipStream_t s)
+{
+    const FinalArgs f = list_scan_args(h, queries_dev, qmask_dev, k);
+    const dim3 grid(parts, Q);
+    const bool timed = h->prof_events && h->prof_used < h->prof_max && h->prof_seen++ % h->prof_stride == h->prof_stride / 2;     // the scoring kernel stands for the scan
     if (timed && hipEventRecord(h->prof_events[2 * h->prof_used], s) != hipSuccess) return KB_ERR_DEVICE;
     switch (q8 ? KT_FP8_Q8 : (int)h->dtype) {
-    case KB_F32: hipLaunchKernelGGL(probe_scan_kernel<KB_F32>, grid, dim3(256), 0, s, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists, stats); break;
-    case KB_BF16: hipLaunchKernelGGL(probe_scan_kernel<KB_BF16>, grid, dim3(256), 0, s, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists, stats); break;
-    case KB_FP8_E4M3: hipLaunchKernelGGL(probe_scan_kernel<KB_FP8_E4M3>, grid, dim3(256), 0, s, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists, stats); break;
-    default: hipLaunchKernelGGL(probe_scan_kernel<KT_FP8_Q8>, grid, dim3(256), 0, s, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists, stats); break;
+    case KB_F32: hipLaunchKernelGGL(small_scan_kernel<KB_F32>, grid, dim3(256), 0, s, f, lists, stats); break;
+    case KB_BF16: hipLaunchKernelGGL(small_scan_kernel<KB_BF16>, grid, dim3(256), 0, s, f, lists, stats); break;
+    case KB_FP8_E4M3: hipLaunchKernelGGL(small_scan_kernel<KB_FP8_E4M3>, grid, dim3(256), 0, s, f, lists, stats); break;
+    default: hipLaunchKernelGGL(small_scan_kernel<KT_FP8_Q8>, grid, dim3(256), 0, s, f, lists, stats); break;
     }
     if (timed) {
         if (hipEventRecord(h->prof_events[2 * h->prof_used + 1], s) != hipSuccess) return KB_ERR_DEVICE;
         ++h->prof_used;
     }
-    const int n_lists = nprobe * splits;
-    const size_t merge_lds = sizeof(uint64_t) * (size_t)(n_lists * k > k ? n_lists * k : k) + 16 + sizeof(SelectScratch);
-    static LdsAllowed merge_allowed;
-    if (allow_dynamic_lds(reinterpret_cast<const void *>(&probe_merge_kernel), merge_allowed, MAX_CAND_CAP * 8 + 16 + sizeof(SelectScratch)) != hipSuccess)
-        return KB_ERR_DEVICE;
-    hipLaunchKernelGGL(probe_merge_kernel, dim3(Q), dim3(256), merge_lds, s, lists, n_lists, k, indices_out_dev, scores_out_dev);
-    return hipGetLastError() == hipSuccess ? KB_OK : KB_ERR_DEVICE;
+    return hipGetLastError() == hipSuccess ? launch_merge(lists, parts, Q, k, indices_out_dev, scores_out_dev, s) : KB_ERR_DEVICE;
 }
 
-// A small knowledge base is scored whole by the same two launches: parts of 128 or 256 rows (one or two steps of the scorer), no
+// A small knowledge base in parts of 128 or 256 rows (one or two steps of the scorer): no
 // sampling pass, no candidate lists.  Same scores, same order: results do not depend on which path ran.
 constexpr int64_t SMALL_ROWS = 16384;
 constexpr int SMALL_BLOCKS = 1024;
@@ -1572,13 +1751,12 @@ int small_path_parts(const kb *h, int64_t n, int32_t Q, bool draw)
 }
 
 struct SmallPlan {
-    size_t off_invq, off_lists, total;
+    size_t off_lists, total;
 };
 SmallPlan make_small_plan(int32_t Q, int32_t k, int parts)
 {
     SmallPlan p;
-    p.off_invq = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));      // the diagnostics come first, as always
-    p.off_lists = p.off_invq + align_up((size_t)Q * 4);
+    p.off_lists = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));      // the diagnostics come first, as always
     p.total = p.off_lists + align_up((size_t)Q * parts * k * 8);
     return p;
 }
@@ -1711,9 +1889,8 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         const SmallPlan sp = make_small_plan(Q, k, parts);
         if (workspace_bytes < sp.total) return KB_ERR_WORKSPACE;
         unsigned char *w = static_cast<unsigned char *>(workspace_dev);
-        return launch_probe(kb, true, queries_dev, q_dtype, q8, Q, qmask_dev, k, nullptr, 1, nullptr, 1, parts, reinterpret_cast<float *>(w + sp.off_invq),
-                            reinterpret_cast<uint64_t *>(w + sp.off_lists), reinterpret_cast<uint64_t *>(w), indices_out_dev, scores_out_dev,
-                            static_cast<hipStream_t>(hip_stream));
+        return launch_small(kb, queries_dev, q8, Q, qmask_dev, k, parts, reinterpret_cast<uint64_t *>(w + sp.off_lists), reinterpret_cast<uint64_t *>(w),
+                            indices_out_dev, scores_out_dev, static_cast<hipStream_t>(hip_stream));
     }
     Plan p;
     if (!make_plan(kb, kb->n, Q, k, draw, q8, &p)) return KB_ERR_INVALID_ARG;
@@ -1973,10 +2150,9 @@ kb_status_t kb_query_probe(kb_t *kb, const void *queries_dev, kb_dtype_t q_dtype
 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     unsigned char *ws = static_cast<unsigned char *>(workspace_dev);
-    float *invq = reinterpret_cast<float *>(ws + p.off_invq);
     uint64_t *lists = reinterpret_cast<uint64_t *>(ws + p.off_lists);
-    return launch_probe(kb, false, queries_dev, q_dtype, q8, Q, qmask_dev, k, cluster_offsets_dev, n_clusters, probe_dev, nprobe, p.splits, invq, lists, nullptr,
-                        indices_out_dev, scores_out_dev, s);
+    return launch_probe(kb, queries_dev, q8, Q, qmask_dev, k, cluster_offsets_dev, n_clusters, probe_dev, nprobe, p.splits, lists, indices_out_dev,
+                        scores_out_dev, s);
 }
 
 kb_status_t kb_query_counters(const kb_t *kb, const void *workspace_dev, int64_t *out, void *hip_stream)
