@@ -125,11 +125,12 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a)
     };
     uint32_t x = tid;
     for (; x + 768 < total; x += 1024) {
-        const u32x4 v0 = *source(x), v1 = *source(x + 256), v2 = *source(x + 512), v3 = *source(x + 768);
-        dst[x] = v0;
-        dst[x + 256] = v1;
-        dst[x + 512] = v2;
-        dst[x + 768] = v3;
+        const u32x4 v0 = __builtin_nontemporal_load(source(x)), v1 = __builtin_nontemporal_load(source(x + 256)),
+                    v2 = __builtin_nontemporal_load(source(x + 512)), v3 = __builtin_nontemporal_load(source(x + 768));
+        __builtin_nontemporal_store(v0, dst + x);
+        __builtin_nontemporal_store(v1, dst + x + 256);
+        __builtin_nontemporal_store(v2, dst + x + 512);
+        __builtin_nontemporal_store(v3, dst + x + 768);
     }
     for (; x < total; x += 256) dst[x] = *source(x);
 }
