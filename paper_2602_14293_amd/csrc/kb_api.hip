@@ -102,7 +102,7 @@ bool is_fp8_query_config(int config)
     return config == FP8_QUERY_CONFIG || config == FP8_QUERY_WIDE_CONFIG || (config >= FP8_QUERY_TILED_CONFIG && config <= FP8_QUERY_TILED_CONFIG + 2);
 }
 
-bool is_whole_config(int config) { return config >= 13 && config <= 15; }      // no pipeline with a sampling pass runs them
+bool is_whole_config(int config) { return (config >= 13 && config <= 15) || config == 21; }      // no pipeline with a sampling pass runs them
 
 int key_bytes(kb_dtype_t t) { return t == KB_F32 ? 4 : t == KB_BF16 ? 2 : 1; }
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -323,7 +323,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     if (n < 1 || Q > 128 || n > (Q > 32 ? WHOLE_MAX_ROWS : WHOLE_MAX_ROWS_FEW) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
     WholePlan p;
     if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
-    else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : 16;    // (14: once every resident workgroup gets a tile)
+    else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : n >= 128 * 2 * DEVICE_CUS && h->d >= 512 ? 21 : 16;    // (14: once every resident workgroup gets a tile)
     else p.config = Q <= 32 ? 1 : 2;
     // tiles of 32 rows while those of 128 would leave compute units without one
     if (p.config == 1 && n <= 128 * DEVICE_CUS / 2) p.config = h->dtype == KB_F32 ? SMALL_F32_CONFIG : 13;

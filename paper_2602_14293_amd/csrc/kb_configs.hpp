@@ -27,10 +27,14 @@
 
 // ... of the whole-store plan only (it also takes those above with query blocks of up to 128).  13: the shortest scans, one wavefront
 // per workgroup with nearly a whole row of each of its 32 keys in flight at once.  14: some ten thousand rows and
-// up to 64 queries, one tile per resident workgroup (65,536 x 768 keys: 23.7 us, 25.1 with config 12).
+// up to 64 queries, one tile per resident workgroup (65,536 x 768 keys: 23.7 us, 25.1 with config 12).  21: up to 128
+// queries, two tiles of 128 rows per compute unit and more (65,536 x 1024 keys, 128 queries: 39.6 us, 44.4 with config 16,
+// whose 64 rows meet twice as many query bytes; 196,000 rows 110 against 120; 16,384 rows 15.8 against 14.1, and with rows
+// of 512 bytes 30.6 against 28.1).
 #define KB_SCAN_WHOLE_CONFIGS_BF16(X)            \
     X(13, KB_BF16, 32, 32, 1, 1, 128, 9, 2)      \
-    X(14, KB_BF16, 128, 64, 4, 1, 128, 3, 2)
+    X(14, KB_BF16, 128, 64, 4, 1, 128, 3, 2)     \
+    X(21, KB_BF16, 128, 128, 4, 2, 128, 4, 1)
 #define KB_SCAN_WHOLE_CONFIGS_FP8(X)             \
     X(13, KB_FP8_E4M3, 32, 32, 1, 1, 64, 12, 2)
 // ... and of a kernel of its own, for f32 rows (kb_scan_f32.hip): tiles of 16 rows

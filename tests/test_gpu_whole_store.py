@@ -19,12 +19,12 @@ def T():
 
 
 # one wavefront per workgroup up to 16,384 rows, tiles of 64 / 128 rows; groups of a wave up to 4096 of them, of a tile
-# beyond; odd and even numbers of tiles; the fewest rows; query counts at the edges of the blocks of 32, 64 and 128
+# beyond; odd and even numbers of tiles; the fewest rows; query counts at the edges of the blocks of 32, 64 and 128; the eight-wave tiles of longer rows
 @pytest.mark.parametrize("kind,N,d,Q,k", [
     ("f32", 1, 32, 1, 1), ("f32", 33, 32, 3, 1), ("f32", 4096, 96, 32, 12), ("f32", 16384, 32, 7, 8), ("f32", 16385, 32, 33, 5),
     ("f32", 131072 + 129, 32, 5, 20), ("bf16", 31, 64, 2, 1), ("bf16", 5000, 128, 32, 10), ("bf16", 16385, 64, 31, 16),
     ("bf16", 65535, 64, 64, 9), ("bf16", 65537, 128, 40, 32), ("bf16", 20000, 64, 65, 16), ("bf16", 40001, 64, 128, 24),
-    ("bf16", 140001, 64, 11, 64), ("bf16m", 30001, 64, 20, 12), ("bf16m", 70001, 64, 60, 20), ("bf16m", 33333, 64, 100, 16),
+    ("bf16", 140001, 64, 11, 64), ("bf16m", 30001, 64, 20, 12), ("bf16m", 70001, 64, 60, 20), ("bf16m", 33333, 64, 100, 16), ("bf16m", 65537, 512, 90, 20),
     ("fp8", 12000, 64, 9, 8), ("fp8", 50001, 128, 70, 16), ("q8", 9001, 64, 64, 8), ("q8", 30001, 192, 100, 16)])
 def test_shapes(T, kind, N, d, Q, k):
     if kind == "f32":
