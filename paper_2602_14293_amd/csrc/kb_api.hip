@@ -97,9 +97,11 @@ constexpr size_t WS_ALIGN = 256;
 constexpr int FP8_QUERY_CONFIG = 5;    // scan configuration of fp8 keys with fp8 queries (kb_configs.hpp)
 constexpr int FP8_QUERY_WIDE_CONFIG = 20;     // ... with 128-byte row pieces: rows of a multiple of 128 bytes, 512 at least
 constexpr int FP8_QUERY_TILED_CONFIG = 6;     // ... the tiled kernel: 6, 7, 8 for query blocks of 64, 128, 256; every row length
+constexpr int FP8_STREAM_CONFIG = 23;         // fp8 keys with bf16 queries: the tiled kernel with whole lines, up to 32 queries
+constexpr int FP8_QUERY_STREAM_CONFIG = 24;   // ... the tiled kernel with whole lines, up to 32 queries
 bool is_fp8_query_config(int config)
 {
-    return config == FP8_QUERY_CONFIG || config == FP8_QUERY_WIDE_CONFIG || (config >= FP8_QUERY_TILED_CONFIG && config <= FP8_QUERY_TILED_CONFIG + 2);
+    return config == FP8_QUERY_CONFIG || config == FP8_QUERY_STREAM_CONFIG || config == FP8_QUERY_WIDE_CONFIG || (config >= FP8_QUERY_TILED_CONFIG && config <= FP8_QUERY_TILED_CONFIG + 2);
 }
 
 bool is_whole_config(int config) { return (config >= 13 && config <= 15) || config == 21; }      // no pipeline with a sampling pass runs them
@@ -132,6 +134,14 @@ uint64_t scatter_multiplier(int64_t n)
     }
 }
 
+// Whether a scan's key loads carry the non-temporal policy: the store does not fit the Infinity Cache (256 MiB), so the next
+// call will not find its rows there, and no second query block of this launch reads them.  A stream that leaves the
+// caches alone is the faster one: 1,000,003 x 1024 bf16 rows and one query 358 -> 321 us, 2^20 rows and 128 queries 425 ->
+// 396, 256 queries 588 -> 570.  With a store that fits and is asked again it loses (100 MB and 64 queries 28.1 -> 29.2 us),
+// with two query blocks too (2,500,001 x 512 fp8 rows, 500 queries: 684 -> 708 us), and with half lines by a tenth.
+constexpr int64_t INFINITY_CACHE_BYTES = 256 << 20;
+bool stream_keys(const kb *h, int64_t n, int nqb) { return nqb == 1 && n * h->d * key_bytes(h->dtype) > INFINITY_CACHE_BYTES; }
+
 // ------------------------------------------------------------------------------------------------
 // Planning: which kernels a query runs, how large its buffers are, where they live in the workspace.
 // ------------------------------------------------------------------------------------------------
@@ -147,26 +157,32 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
     Choice c;
     const int generic = Q <= 32 ? 1 : Q <= 128 ? 2 : 3;        // the tiled kernel: every dtype, every row length
     const size_t row_bytes = (size_t)h->d * key_bytes(h->dtype);
+    // fp8 rows beyond the caches, few queries: the tiled kernel with 128-byte row pieces (the others take 64 bytes, half a
+    // cache line, of an fp8 row at a time).  1,000,000 x 512 rows: one query 119.5 -> 100.9 us, 20 queries 121 -> 108.6
+    const bool whole_line_rows = row_bytes % 128 == 0;
     if (q8) {       // fp8 queries: only the kernels built on the fp8 matrix instruction take them
         if (h->dtype != KB_FP8_E4M3) return false;
         const int generic8 = Q <= 64 ? FP8_QUERY_TILED_CONFIG : Q <= 128 ? FP8_QUERY_TILED_CONFIG + 1 : FP8_QUERY_TILED_CONFIG + 2;
         // large batches: the pipelined kernels (256-query blocks); smaller ones would pad their query columns there
         c.config = Q <= 128 ? generic8 : (row_bytes % 128 == 0 && row_bytes >= 512) ? FP8_QUERY_WIDE_CONFIG : FP8_QUERY_CONFIG;
+        if (Q <= 32 && whole_line_rows && stream_keys(h, n, 1)) c.config = FP8_QUERY_STREAM_CONFIG;
         if (is_fp8_query_config((int)h->tune_config)) c.config = (int)h->tune_config;         // another one can be asked for
         if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;
         // the weighted random selection exists in the tiled kernel only, and rows may be too short for a pipelined kernel
-        if ((draw && c.ci.family != 0) || row_bytes < (size_t)c.ci.min_row_bytes) {
+        if ((draw && c.ci.family != 0) || row_bytes < (size_t)c.ci.min_row_bytes ||
+            (!whole_line_rows && (c.config == FP8_QUERY_STREAM_CONFIG || c.config == FP8_QUERY_WIDE_CONFIG))) {
             c.config = generic8;
             if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;
         }
     } else {
         c.config = h->tune_config > 0 ? (int)h->tune_config : scan_config_for(h->dtype, Q, h->d, n);
+        if (h->tune_config == 0 && h->dtype == KB_FP8_E4M3 && Q <= 32 && whole_line_rows && stream_keys(h, n, 1)) c.config = FP8_STREAM_CONFIG;
         if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;
         // fall back where a (forced) configuration does not apply: the weighted random selection exists in the
         // tiled kernel and in the main pass of the bf16 full-line kernel, rows may be too short for a pipelined kernel,
         // and the fp8-query kernels read fp8 queries
         const bool draws = c.ci.family == 0 || (c.ci.family == 4 && h->dtype == KB_BF16);
-        if ((draw && !draws) || row_bytes < (size_t)c.ci.min_row_bytes || (h->dtype == KB_FP8_E4M3 && is_fp8_query_config(c.config))) {
+        if ((draw && !draws) || row_bytes < (size_t)c.ci.min_row_bytes || (!whole_line_rows && c.config == FP8_STREAM_CONFIG) || (h->dtype == KB_FP8_E4M3 && is_fp8_query_config(c.config))) {
             c.config = generic;
             if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;
         }
@@ -325,6 +341,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
     else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : n >= 128 * 2 * DEVICE_CUS && h->d >= 512 ? 21 : 16;    // (14: once every resident workgroup gets a tile)
     else p.config = Q <= 32 ? 1 : 2;
+    if (h->dtype == KB_FP8_E4M3 && Q <= 32 && h->d % 128 == 0 && stream_keys(h, n, 1)) p.config = q8 ? FP8_QUERY_STREAM_CONFIG : FP8_STREAM_CONFIG;
     // tiles of 32 rows while those of 128 would leave compute units without one
     if (p.config == 1 && n <= 128 * DEVICE_CUS / 2) p.config = h->dtype == KB_F32 ? SMALL_F32_CONFIG : 13;
     ConfigInfo ci;
@@ -1537,7 +1554,6 @@ template <int KT> hipError_t launch_probe_scan(const dim3 &grid, const FinalArgs
     hipLaunchKernelGGL(probe_scan_kernel<KT>, grid, dim3(PROBE_THREADS), probe_scan_lds<KT>(), s, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists);
     return hipGetLastError();
 }
-
 hipError_t launch_scan(kb_dtype_t dt, int config, int family, bool sample, int grid, const ScanArgs &a, hipStream_t s)
 {
     if (family == 4)
@@ -1779,6 +1795,7 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     a.Q = Q;
     a.nqb = p.nqb;
     a.qpad = p.nqb * p.tq;
+    a.keys_once = stream_keys(h, h->n, p.nqb);
     a.whole_best = reinterpret_cast<float *>(ws + p.off_best);
     a.whole_pair = reinterpret_cast<u32x4 *>(ws + p.off_pair);
     a.whole_groups = p.groups;
@@ -1969,6 +1986,7 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         while (p.sample_tiles > 0 && ((int64_t)p.sample_tiles << (a.sample_group_shift + 1)) <= p.sample_slots) ++a.sample_group_shift;
         a.region_cap = p.region_cap;
         a.draw = dr;
+        a.keys_once = stream_keys(kb, kb->n, p.nqb);
         a.whole_best = nullptr;
         a.whole_pair = nullptr;
         a.whole_groups = a.whole_fine = a.whole_run_shift = 0;

@@ -3,7 +3,7 @@
 //   RBA          bytes of each key row per d-chunk    NSTAGE   chunk buffers in LDS
 //   WGPC         workgroups resident per compute unit (LDS and registers are budgeted for it)
 // (12, 16: small tiles for knowledge bases of some ten thousand rows, where a query is bound by the latency of its
-//  launches and more, shorter work items finish sooner)
+//  launches and more, shorter work items finish sooner; 23, 24: whole cache lines of fp8 rows of a multiple of 128 bytes)
 #pragma once
 #define KB_SCAN_CONFIGS_BF16(X)                  \
     X(1, KB_BF16, 128, 32, 4, 1, 128, 3, 2)      \
@@ -18,12 +18,14 @@
 #define KB_SCAN_CONFIGS_FP8(X)                   \
     X(1, KB_FP8_E4M3, 128, 32, 4, 1, 64, 3, 2)   \
     X(2, KB_FP8_E4M3, 128, 128, 2, 2, 64, 3, 2)  \
-    X(3, KB_FP8_E4M3, 128, 256, 2, 2, 64, 3, 1)
+    X(3, KB_FP8_E4M3, 128, 256, 2, 2, 64, 3, 1)  \
+    X(23, KB_FP8_E4M3, 128, 32, 4, 1, 128, 3, 2)
 // ... with fp8 queries as well (key type KB_FP8_Q8 inside the kernels): every row length, every batch size
 #define KB_SCAN_CONFIGS_FP8_Q8(X)                \
     X(6, KB_FP8_Q8, 128, 64, 2, 2, 64, 3, 2)     \
     X(7, KB_FP8_Q8, 128, 128, 2, 2, 64, 3, 2)    \
-    X(8, KB_FP8_Q8, 128, 256, 2, 2, 64, 3, 1)
+    X(8, KB_FP8_Q8, 128, 256, 2, 2, 64, 3, 1)    \
+    X(24, KB_FP8_Q8, 128, 32, 4, 1, 128, 3, 2)
 
 // ... of the whole-store plan only (it also takes those above with query blocks of up to 128).  13: the shortest scans, one wavefront
 // per workgroup with nearly a whole row of each of its 32 keys in flight at once.  14: some ten thousand rows and

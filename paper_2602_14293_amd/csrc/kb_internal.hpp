@@ -142,6 +142,9 @@ struct DrawArgs {
     int32_t enabled;
 };
 
+// Load policy of key rows that are read once, as the last operand of a direct-to-LDS load: non-temporal.
+constexpr int LOAD_NT = 2;
+
 struct ScanArgs {
     const void *keys;
     const float *inv_norm;
@@ -167,6 +170,7 @@ struct ScanArgs {
     int32_t row_run_shift;
     int32_t d, Q, nqb, qpad, sample_slots, sample_group_shift, region_cap, cand_cap;
     DrawArgs draw;
+    int32_t keys_once;        // the launch reads keys that no cache holds and nobody reads again: see stream_keys
     // Whole-store plan (see WholePlan): the best two of every group of rows, nothing is filtered.  nullptr otherwise.
     float *whole_best;        // [Q][groups]: product of the best row of the group
     u32x4 *whole_pair;        // [Q][groups]: see GroupPair

@@ -180,7 +180,7 @@ __device__ inline void bare_barrier()
     asm volatile("" ::: "memory");
 }
 
-template <class C, bool SAMPLE, bool DRAW, bool WHOLE = false>
+template <class C, bool SAMPLE, bool DRAW, bool WHOLE = false, bool NT = false>
 __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p)
 {
     constexpr int TK = C::TK, TQ = C::TQ, RBA = C::RBA, RBB = C::RBB, IB = C::IB, JB = C::JB, NW = C::NW;
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
         const unsigned char *gB = static_cast<const unsigned char *>(p.queries) + (size_t)ld_c * RBB;
 #pragma unroll
         for (int j = 0; j < LA; ++j)
-            __builtin_amdgcn_global_load_lds((const void *)(gA + offA[j]), (lds_ptr)(sA + j * NW * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const void *)(gA + offA[j]), (lds_ptr)(sA + j * NW * 1024), 16, 0, NT ? LOAD_NT : 0);
 #pragma unroll
         for (int j = 0; j < LB; ++j)
             __builtin_amdgcn_global_load_lds((const void *)(gB + offB[j]), (lds_ptr)(sB + j * NW * 1024), 16, 0, 0);
@@ -442,15 +442,32 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
     if (!SAMPLE && !WHOLE) flush_records(p, my_region, wave_cnt, blockIdx.x * NW + wave);      // what is left in the region
 }
 
+// Variants of a configuration with the non-temporal policy: where query blocks of 32 make the scan a stream of keys, in whole
+// lines (half lines would be fetched twice).
+template <class C> constexpr bool HAS_NT = C::TQ == 32 && C::TK == 128 && C::RBA == 128;
+
+template <class C, bool SAMPLE, bool DRAW, bool WHOLE, bool NT> hipError_t launch_scan_variant(int grid, const ScanArgs &a, hipStream_t s)
+{
+    // more than 64 KiB of dynamic LDS has to be requested explicitly, once per kernel
+    constexpr int SMEM = WHOLE ? C::SMEM_BYTES_WHOLE : C::SMEM_BYTES;
+    static LdsAllowed allowed;
+    auto *fn = &kb_scan_kernel<C, SAMPLE, DRAW, WHOLE, NT>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed, SMEM); e != hipSuccess) return e;
+    hipExtLaunchKernelGGL(fn, dim3(grid), dim3(C::THREADS), SMEM, s, scan_timing.start, scan_timing.stop, 0, a);
+    return hipGetLastError();
+}
+template <class C, bool SAMPLE, bool DRAW, bool WHOLE> hipError_t launch_scan_policy(int grid, const ScanArgs &a, hipStream_t s)
+{
+    if constexpr (HAS_NT<C>)
+        if (a.keys_once) return launch_scan_variant<C, SAMPLE, DRAW, WHOLE, true>(grid, a, s);
+    return launch_scan_variant<C, SAMPLE, DRAW, WHOLE, false>(grid, a, s);
+}
+
 // the first launch of the whole-store plan
 template <class C> hipError_t launch_whole_cfg(int grid, const ScanArgs &a, hipStream_t s)
 {
     static_assert(C::TQ <= 128 && C::TK <= 128 && C::IB <= 2 && C::SMEM_BYTES_WHOLE * C::WGPC <= 160 * 1024);
-    static LdsAllowed allowed;
-    auto *fn = &kb_scan_kernel<C, false, false, true>;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed, C::SMEM_BYTES_WHOLE); e != hipSuccess) return e;
-    hipExtLaunchKernelGGL(fn, dim3(grid), dim3(C::THREADS), C::SMEM_BYTES_WHOLE, s, scan_timing.start, scan_timing.stop, 0, a);
-    return hipGetLastError();
+    return launch_scan_policy<C, false, false, true>(grid, a, s);
 }
 
 template <class C> hipError_t launch_scan_cfg(bool sample, int grid, const ScanArgs &a, hipStream_t s)
@@ -459,15 +476,8 @@ template <class C> hipError_t launch_scan_cfg(bool sample, int grid, const ScanA
         if constexpr (C::TQ <= 128) return launch_whole_cfg<C>(grid, a, s);
         return hipErrorInvalidValue;
     }
-    // more than 64 KiB of dynamic LDS has to be requested explicitly, once per kernel
-    static LdsAllowed allowed[4];
-    const bool draw = a.draw.enabled != 0;
-    auto *fn = draw ? (sample ? &kb_scan_kernel<C, true, true> : &kb_scan_kernel<C, false, true>)
-                    : (sample ? &kb_scan_kernel<C, true, false> : &kb_scan_kernel<C, false, false>);
-    const int which = (draw ? 2 : 0) + (sample ? 1 : 0);
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed[which], C::SMEM_BYTES); e != hipSuccess) return e;
-    hipExtLaunchKernelGGL(fn, dim3(grid), dim3(C::THREADS), C::SMEM_BYTES, s, scan_timing.start, scan_timing.stop, 0, a);
-    return hipGetLastError();
+    if (a.draw.enabled) return sample ? launch_scan_policy<C, true, true, false>(grid, a, s) : launch_scan_policy<C, false, true, false>(grid, a, s);
+    return sample ? launch_scan_policy<C, true, false, false>(grid, a, s) : launch_scan_policy<C, false, false, false>(grid, a, s);
 }
 
 }  // namespace kbi

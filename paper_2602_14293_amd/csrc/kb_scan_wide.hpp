@@ -84,7 +84,7 @@ template <int KT_, int TQ_, bool QF8_ = false> struct WideCfg {
     static_assert(SMEM_BYTES <= 160 * 1024, "LDS budget");
 };
 
-template <class C, bool SAMPLE, bool DRAW = false>
+template <class C, bool SAMPLE, bool DRAW = false, bool NT = false>
 __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
 {
     static_assert(!DRAW || (!SAMPLE && !C::QF8), "keys of the weighted random selection: main pass, bf16");
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
     };
     // role 0: load j (0..3) of the key piece at the cursor, half h of its chunk; key_next(h) moves the cursor on
     auto key_issue = [&](int h, int j) {
-        __builtin_amdgcn_global_load_lds((const void *)(ld_src + ((uint64_t)off[h][j] << OSH)), (lds_ptr)(ld_dst + j * 4096), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((const void *)(ld_src + ((uint64_t)off[h][j] << OSH)), (lds_ptr)(ld_dst + j * 4096), 16, 0, NT ? LOAD_NT : 0);
     };
     auto item_next = [&]() {
         if constexpr (SAMPLE) return;       // one item per workgroup: the stream ends with it
@@ -567,17 +567,29 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
     if (!SAMPLE) flush_records(p, my_region, wave_cnt, blockIdx.x * NW + wave);      // what is left in the region
 }
 
-template <class C> hipError_t launch_scan_wide_cfg(bool sample, int grid, const ScanArgs &a, hipStream_t s)
+template <class C, bool SAMPLE, bool DRAW, bool NT> hipError_t launch_scan_wide_variant(int grid, const ScanArgs &a, hipStream_t s)
 {
-    static LdsAllowed allowed[3];
-    const bool draw = a.draw.enabled != 0;
-    if (C::QF8 && (sample || draw)) return hipErrorInvalidValue;     // fp8: the sampling pass runs the 64-byte-piece kernel (fewer registers)
-    if (draw && sample) return hipErrorInvalidValue;                 // keys of the weighted random selection: main pass only
-    auto *fn = (sample && !C::QF8) ? &kb_scan_wide_kernel<C, C::QF8 ? false : true>
-               : (draw && !C::QF8) ? &kb_scan_wide_kernel<C, false, C::QF8 ? false : true> : &kb_scan_wide_kernel<C, false>;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed[draw ? 2 : sample], C::SMEM_BYTES); e != hipSuccess) return e;
+    static LdsAllowed allowed;
+    auto *fn = &kb_scan_wide_kernel<C, SAMPLE, DRAW, NT>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed, C::SMEM_BYTES); e != hipSuccess) return e;
     hipExtLaunchKernelGGL(fn, dim3(grid), dim3(C::THREADS), C::SMEM_BYTES, s, scan_timing.start, scan_timing.stop, 0, a);
     return hipGetLastError();
+}
+template <class C, bool SAMPLE, bool DRAW> hipError_t launch_scan_wide_policy(int grid, const ScanArgs &a, hipStream_t s)
+{
+    return a.keys_once ? launch_scan_wide_variant<C, SAMPLE, DRAW, true>(grid, a, s) : launch_scan_wide_variant<C, SAMPLE, DRAW, false>(grid, a, s);
+}
+
+template <class C> hipError_t launch_scan_wide_cfg(bool sample, int grid, const ScanArgs &a, hipStream_t s)
+{
+    const bool draw = a.draw.enabled != 0;
+    if (draw && sample) return hipErrorInvalidValue;                 // keys of the weighted random selection: main pass only
+    if constexpr (C::QF8) {      // fp8: the sampling pass runs the 64-byte-piece kernel (fewer registers)
+        return sample || draw ? hipErrorInvalidValue : launch_scan_wide_policy<C, false, false>(grid, a, s);
+    } else {
+        return sample ? launch_scan_wide_policy<C, true, false>(grid, a, s)
+               : draw ? launch_scan_wide_policy<C, false, true>(grid, a, s) : launch_scan_wide_policy<C, false, false>(grid, a, s);
+    }
 }
 
 }  // namespace kbi

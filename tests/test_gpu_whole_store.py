@@ -90,3 +90,34 @@ def test_replays_from_a_graph_and_less_memory(T):
         torch.cuda.synchronize()
         assert torch.equal(oi, want[0]) and torch.equal(os_, want[1])
     kb.close()
+
+
+@pytest.mark.parametrize("kind,d,Q", [("bf16", 1024, 5), ("bf16", 1024, 70), ("bf16", 1024, 200), ("f32", 512, 3), ("fp8", 1024, 7),
+                                      ("q8", 1024, 30), ("fp8", 1088, 2)])
+def test_stores_beyond_the_infinity_cache(T, kind, d, Q):
+    """Just over 256 MiB of keys: the loads' policy changes and fp8 rows of a multiple of 128 bytes go a line at a time.  Checked
+    against a plain product in double precision."""
+    N = (256 << 20) // (d * {"bf16": 2, "f32": 4}.get(kind, 1)) + 77
+    g = torch.Generator(device="cuda").manual_seed(d + Q)
+    rows = torch.randn((N, d), generator=g, device="cuda")
+    scale = None
+    if kind in ("fp8", "q8"):
+        rows, scale = kbmod.quantize_rows(rows)
+    rows = rows.to({"bf16": torch.bfloat16, "f32": torch.float32}.get(kind, torch.float8_e4m3fn))
+    queries = torch.randn((Q, d), generator=g, device="cuda")
+    queries = queries if kind == "f32" else kbmod.quantize_rows(queries)[0] if kind == "q8" else queries.to(torch.bfloat16)
+    kb = kbmod.KnowledgeBase(d, {"bf16": kbmod.KB_BF16, "f32": kbmod.KB_F32}.get(kind, kbmod.KB_FP8_E4M3), N)
+    kb.append(rows, scale)
+    kb.normalize()
+    gi, gs = kb.query(queries, 6)
+    kb.set_tuning("small_path", 0)
+    pi, ps = kb.query(queries, 6)
+    q = torch.nn.functional.normalize(queries.float().double(), dim=1)
+    best = torch.cat([torch.nn.functional.normalize(rows[s:s + 65536].float().double(), dim=1) @ q.T for s in range(0, N, 65536)])
+    want = best.topk(6, dim=0)
+    torch.cuda.synchronize()
+    assert torch.equal(gi, pi) and torch.equal(gs, ps)
+    assert (gs.double() - want.values.T).abs().max() < (1e-4 if kind == "q8" else 1e-5)       # the tolerances of kb_testlib
+    got = best.gather(0, gi.T.long())
+    assert (got - want.values).abs().max() < (1e-4 if kind == "q8" else 1e-5)
+    kb.close()
