@@ -1340,7 +1340,7 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
 // Two-stage retrieval, second stage: exact top-k of one query over the rows of the clusters it probes.
 // ------------------------------------------------------------------------------------------------
 constexpr int PROBE_CAP = 1024;        // LDS candidate buffer of a partial scan (words); k <= 128 fits eight times
-constexpr int PROBE_MAX_LISTS = 64;    // partial lists per query that the merge can take: 64 x 128 = MAX_CAND_CAP words
+constexpr int PROBE_MAX = 64;          // clusters a query can probe: one list of 128 words each is MAX_CAND_CAP words, what the merge takes
 
 // A wavefront's stream of 32 key rows and the query row through its own ring of chunks in LDS: every chunk is RB bytes of
 // each row, loaded directly to LDS whole cache lines at a time (fp8: half lines, rows are multiples of 64 bytes), swizzled
@@ -1430,7 +1430,7 @@ template <int KT> size_t probe_scan_lds() { return (size_t)PROBE_WAVES * ProbeRi
 // Every block computes 1/|q| of its query itself (one wavefront, the row-norm routine every path uses: the same bits),
 // which saves the launch that would do it once per query.  Such a call is bound by the latency of its loads: nearly a whole
 // row of each of the 32 keys of a wavefront is in flight at once.  8 queries, four clusters of about 1000 rows of 1024
-// bf16 values each (65 MB): 21.3 us, 32.7 us with fragments loaded to registers, a quarter of a row at a time and each
+// bf16 values each (65 MB): 20.7 us, 32.7 us with fragments loaded to registers, a quarter of a row at a time and each
 // lane from a row of its own.
 template <int KT> __global__ __launch_bounds__(PROBE_THREADS) void probe_scan_kernel(FinalArgs a, const int64_t *cluster_offsets, int n_clusters,
                                                                                         const int32_t *probe, int nprobe, int splits, uint64_t *lists)
@@ -1497,7 +1497,19 @@ template <int KT> __global__ __launch_bounds__(PROBE_THREADS) void probe_scan_ke
         }
         __syncthreads();        // (everyone has read the count that the next step moves on)
     }
-    select_topk_desc(buf, (int)count, a.k, sc, tid, THREADS);
+    const int n = (int)count;
+    if (n <= THREADS) {         // a block of one or two steps: every word finds its place by counting the larger ones
+        if (tid < n) {
+            const uint64_t e = buf[tid];
+            int rank = 0;
+#pragma unroll 8
+            for (int j = 0; j < n; ++j) rank += buf[j] > e;
+            if (rank < a.k) out[rank] = e;
+        }
+        for (int i = n + tid; i < a.k; i += THREADS) out[i] = 0ull;
+        return;
+    }
+    select_topk_desc(buf, n, a.k, sc, tid, THREADS);
     for (int i = tid; i < a.k; i += THREADS) out[i] = buf[i];
 }
 
@@ -1661,12 +1673,13 @@ kb_status_t kb_normalize(kb_t *kb, void *hip_stream)
 // ------------------------------------------------------------------------------------------------
 namespace {
 
-// Parts a cluster's rows are split into, so that a small batch still fills the device: a function of (Q, nprobe) only.
-int probe_splits(int Q, int nprobe)
+// Parts a cluster's rows are split into, so that a small batch still fills the device, as far as the merge can take the
+// partial lists: a function of (Q, nprobe, k) only.
+int probe_splits(int Q, int k, int nprobe)
 {
     int64_t s = (4 * (int64_t)DEVICE_CUS + (int64_t)Q * nprobe - 1) / ((int64_t)Q * nprobe);
     if (s > 16) s = 16;
-    if (s > PROBE_MAX_LISTS / nprobe) s = PROBE_MAX_LISTS / nprobe;
+    if (s > MAX_CAND_CAP / k / nprobe) s = MAX_CAND_CAP / k / nprobe;
     return s < 1 ? 1 : (int)s;
 }
 
@@ -1677,9 +1690,9 @@ struct ProbePlan {
 
 bool make_probe_plan(int32_t Q, int32_t k, int32_t nprobe, ProbePlan *out)
 {
-    if (Q < 1 || Q > 65535 || k < 1 || k > KB_K_MAX || nprobe < 1 || nprobe > PROBE_MAX_LISTS) return false;
+    if (Q < 1 || Q > 65535 || k < 1 || k > KB_K_MAX || nprobe < 1 || nprobe > PROBE_MAX) return false;
     ProbePlan p;
-    p.splits = probe_splits(Q, nprobe);
+    p.splits = probe_splits(Q, k, nprobe);
     p.off_lists = 0;
     p.total = p.off_lists + align_up((size_t)Q * nprobe * p.splits * k * 8);
     *out = p;
@@ -1762,7 +1775,7 @@ int small_path_parts(const kb *h, int64_t n, int32_t Q, bool draw)
     if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return 0;
     if (n < 1 || n > SMALL_ROWS || Q > 65535) return 0;
     int64_t parts = (n + 127) / 128;       // one step of the scorer per part up to 8192 rows, two beyond
-    if (parts > PROBE_MAX_LISTS) parts = PROBE_MAX_LISTS;
+    if (parts > PROBE_MAX) parts = PROBE_MAX;
     return parts * Q <= SMALL_BLOCKS ? (int)parts : 0;
 }
 
