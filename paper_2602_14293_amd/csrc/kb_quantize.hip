@@ -11,6 +11,7 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int THREADS = 256;
+constexpr int64_t STREAM_BYTES = 64 << 20;
 constexpr int CACHED = 4;           // 16-byte pieces of the row a lane keeps in registers between the two passes
 constexpr float E4M3_MAX = 448.0f;
 
@@ -56,7 +57,7 @@ template <bool EXACT> __device__ inline float quotient(float x, float scale, flo
     return __builtin_copysignf(q, x);       // (the corrections turn a -0 into a +0)
 }
 
-template <int DT, bool EXACT> __device__ inline void piece_store(const u32x4 &v, float scale, float recip, unsigned char *dst)
+template <int DT, bool EXACT, bool STREAM> __device__ inline void piece_store(const u32x4 &v, float scale, float recip, unsigned char *dst)
 {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     uint32_t w[Piece<DT>::ELEMS / 4];
@@ -65,16 +66,19 @@ template <int DT, bool EXACT> __device__ inline void piece_store(const u32x4 &v,
         w[j] = encode_e4m3_x4(quotient<EXACT>(Piece<DT>::value(v, 4 * j), scale, recip), quotient<EXACT>(Piece<DT>::value(v, 4 * j + 1), scale, recip),
                               quotient<EXACT>(Piece<DT>::value(v, 4 * j + 2), scale, recip), quotient<EXACT>(Piece<DT>::value(v, 4 * j + 3), scale, recip));
     }
-    if constexpr (Piece<DT>::ELEMS == 8)
-        __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<u32x2 *>(dst));
-    else
-        __builtin_nontemporal_store(w[0], reinterpret_cast<uint32_t *>(dst));
+    if constexpr (Piece<DT>::ELEMS == 8) {
+        if constexpr (STREAM) __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<u32x2 *>(dst));
+        else *reinterpret_cast<u32x2 *>(dst) = u32x2{w[0], w[1]};
+    } else {
+        if constexpr (STREAM) __builtin_nontemporal_store(w[0], reinterpret_cast<uint32_t *>(dst));
+        else *reinterpret_cast<uint32_t *>(dst) = w[0];
+    }
 }
 
 // LANES lanes (32 or 64) take a row: with rows of up to 128 pieces two rows share a wavefront, so that 96 pieces (768 bf16
 // values) leave no lane idle and a wavefront has twice the bytes in flight.  500,000 x 768
 // bf16 rows (1.15 GB): 0.198 ms = 5.8 TB/s, 0.264 ms with a wavefront per row, general divisions and cached loads and stores.
-template <int DT, int LANES> __global__ __launch_bounds__(THREADS) void quantize_rows_kernel(const unsigned char *rows, int64_t n, int d, unsigned char *codes, float *scale_out)
+template <int DT, int LANES, bool STREAM> __global__ __launch_bounds__(THREADS) void quantize_rows_kernel(const unsigned char *rows, int64_t n, int d, unsigned char *codes, float *scale_out)
 {
     constexpr int ELEMS = Piece<DT>::ELEMS, ROWS = THREADS / LANES;
     const int lane = threadIdx.x % LANES;
@@ -86,7 +90,7 @@ template <int DT, int LANES> __global__ __launch_bounds__(THREADS) void quantize
 #pragma unroll
         for (int c = 0; c < CACHED; ++c) {
             const int p = lane + LANES * c;
-            keep[c] = p < pieces ? __builtin_nontemporal_load(src + p) : u32x4{0, 0, 0, 0};
+            keep[c] = p < pieces ? (STREAM ? __builtin_nontemporal_load(src + p) : src[p]) : u32x4{0, 0, 0, 0};
         }
 #pragma unroll
         for (int c = 0; c < CACHED; ++c) m = fmaxf(m, piece_amax<DT>(keep[c]));
@@ -100,11 +104,11 @@ template <int DT, int LANES> __global__ __launch_bounds__(THREADS) void quantize
 #pragma unroll
             for (int c = 0; c < CACHED; ++c) {
                 const int p = lane + LANES * c;
-                if (p < pieces) piece_store<DT, false>(keep[c], scale, recip, dst + (size_t)p * ELEMS);
+                if (p < pieces) piece_store<DT, false, STREAM>(keep[c], scale, recip, dst + (size_t)p * ELEMS);
             }
-            for (int p = lane + LANES * CACHED; p < pieces; p += LANES) piece_store<DT, false>(src[p], scale, recip, dst + (size_t)p * ELEMS);
+            for (int p = lane + LANES * CACHED; p < pieces; p += LANES) piece_store<DT, false, STREAM>(src[p], scale, recip, dst + (size_t)p * ELEMS);
         } else {
-            for (int p = lane; p < pieces; p += LANES) piece_store<DT, true>(src[p], scale, recip, dst + (size_t)p * ELEMS);
+            for (int p = lane; p < pieces; p += LANES) piece_store<DT, true, STREAM>(src[p], scale, recip, dst + (size_t)p * ELEMS);
         }
     }
 }
@@ -114,8 +118,11 @@ template <int DT> void launch_quantize(const unsigned char *rows, int64_t n, int
     const int lanes = d / Piece<DT>::ELEMS <= 32 * CACHED ? 32 : 64, per_block = THREADS / lanes;
     const int64_t want = (n + per_block - 1) / per_block;
     const int grid = (int)(want < 256 * 32 ? want : 256 * 32);      // 32 workgroups per compute unit keep HBM busy; the rest loops
-    if (lanes == 32) hipLaunchKernelGGL((quantize_rows_kernel<DT, 32>), dim3(grid), dim3(THREADS), 0, s, rows, n, d, codes, scale);
-    else hipLaunchKernelGGL((quantize_rows_kernel<DT, 64>), dim3(grid), dim3(THREADS), 0, s, rows, n, d, codes, scale);
+    // past the caches when the rows are more than they keep: a batch of queries is read and written where it is used
+    const bool stream = n * (int64_t)d * (16 / Piece<DT>::ELEMS) > STREAM_BYTES;
+    auto *fn = lanes == 32 ? (stream ? &quantize_rows_kernel<DT, 32, true> : &quantize_rows_kernel<DT, 32, false>)
+                           : (stream ? &quantize_rows_kernel<DT, 64, true> : &quantize_rows_kernel<DT, 64, false>);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(THREADS), 0, s, rows, n, d, codes, scale);
 }
 
 }  // namespace
