@@ -495,25 +495,37 @@ template <int DT> __global__ __launch_bounds__(256) void row_norm_kernel(const v
 // ------------------------------------------------------------------------------------------------
 // weighted random selection: ln(gain) per entry, -inf for entries without weight and for the padding
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void log_gain_kernel(const float *gain, int64_t n, int64_t n_padded, float *log_gain)
+struct GainArgs {
+    const float *gain;          // nullptr: no weighted selection
+    float *log_gain;
+    int64_t n, n_padded;
+    int blocks;                 // workgroups of 256 entries
+};
+__device__ inline void log_gain_block(const GainArgs &g, int block)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n_padded) return;
+    const int64_t i = (int64_t)block * 256 + threadIdx.x;
+    if (i >= g.n_padded) return;
     float v = -__builtin_inff();
-    if (i < n) {
-        const float g = gain[i];
-        if (g > 0.f) v = logf(g);
+    if (i < g.n) {
+        const float x = g.gain[i];
+        if (x > 0.f) v = logf(x);
     }
-    log_gain[i] = v;
+    g.log_gain[i] = v;
 }
 
 // ------------------------------------------------------------------------------------------------
-// prep: query norms + reset of the per-call counters
+// prep: query norms + reset of the per-call counters; for the weighted selection its last workgroups form ln(gain), which
+// as a launch of its own cost a call 5 us
 // ------------------------------------------------------------------------------------------------
 template <int QT> __global__ __launch_bounds__(256) void prep_kernel(const void *queries, int Q, int qpad, int d, float *invq, uint64_t *thr64, float *thrp,
                                                                        uint32_t *cnt, uint32_t *flag, uint64_t *stats, uint64_t sample_keys,
-                                                                       const uint64_t *qmask, uint64_t *qmask_pad, int grid, uint32_t *fb_done)
+                                                                       const uint64_t *qmask, uint64_t *qmask_pad, int grid, uint32_t *fb_done, GainArgs g)
 {
+    const int prep_blocks = (int)gridDim.x - g.blocks;
+    if ((int)blockIdx.x >= prep_blocks) {
+        log_gain_block(g, (int)blockIdx.x - prep_blocks);
+        return;
+    }
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t < qpad) fb_done[t] = 0;
     if (t < qpad) {     // padding queries (t >= Q) can never pass the filter of the scan
@@ -1943,6 +1955,8 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
 
     DrawArgs dr;
     memset(&dr, 0, sizeof dr);
+    GainArgs ga;
+    memset(&ga, 0, sizeof ga);
     if (draw) {
         dr.log_gain = log_gain;
         dr.inv_t = 1.0f / temperature;
@@ -1950,9 +1964,11 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         dr.seed_hi = (uint32_t)(seed >> 32);
         dr.first_query = (uint32_t)first_query;
         dr.enabled = 1;
-        const int64_t n_padded = ceil_div(kb->n > 0 ? kb->n : 1, 256) * 256 + 256;
-        hipLaunchKernelGGL(log_gain_kernel, dim3((unsigned)ceil_div(n_padded, 256)), dim3(256), 0, s, gain_dev, kb->n, n_padded, log_gain);
-        if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
+        ga.gain = gain_dev;
+        ga.log_gain = log_gain;
+        ga.n = kb->n;
+        ga.n_padded = ceil_div(kb->n > 0 ? kb->n : 1, 256) * 256 + 256;
+        ga.blocks = (int)ceil_div(ga.n_padded, 256);
     }
 
     // Query norms and per-call counters: the threshold kernel sets them when there is a sampling pass on scores;
@@ -1961,13 +1977,13 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     if (!sampled || draw) {
         const int n_init = p.qpad > STAT_WORDS + STAT_PARTIALS ? p.qpad : STAT_WORDS + STAT_PARTIALS;
         const int blocks_rows = (int)ceil_div(p.qpad, 4), blocks_init = (int)ceil_div(n_init, 256);
-        const unsigned grid = blocks_rows > blocks_init ? blocks_rows : blocks_init;
+        const unsigned grid = (blocks_rows > blocks_init ? blocks_rows : blocks_init) + ga.blocks;
         if (q_dtype == KB_F32)
-            hipLaunchKernelGGL(prep_kernel<KB_F32>, dim3(grid), dim3(256), 0, s, queries_dev, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done);
+            hipLaunchKernelGGL(prep_kernel<KB_F32>, dim3(grid), dim3(256), 0, s, queries_dev, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done, ga);
         else if (q_dtype == KB_FP8_E4M3)
-            hipLaunchKernelGGL(prep_kernel<KB_FP8_E4M3>, dim3(grid), dim3(256), 0, s, queries_dev, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done);
+            hipLaunchKernelGGL(prep_kernel<KB_FP8_E4M3>, dim3(grid), dim3(256), 0, s, queries_dev, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done, ga);
         else
-            hipLaunchKernelGGL(prep_kernel<KB_BF16>, dim3(grid), dim3(256), 0, s, queries_dev, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done);
+            hipLaunchKernelGGL(prep_kernel<KB_BF16>, dim3(grid), dim3(256), 0, s, queries_dev, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done, ga);
         if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
     }
 
