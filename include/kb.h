@@ -193,6 +193,7 @@ kb_status_t kb_quantize_rows(const void *rows_dev, kb_dtype_t dtype, int64_t n, 
  *   queries, q_dtype, qmask, k, outputs, stream: as kb_query (fp8 queries are accepted for any d here); removed
  *   entries are never returned
  *   workspace_dev  256-byte aligned, at least kb_query_probe_workspace_bytes(kb, Q, k, nprobe) (0 on invalid arguments)
+ *                  (a workspace for 64 lists of k words per query is enough, at a lower speed where k < 128)
  * Cost is proportional to the rows of the probed clusters, not to kb_size: meant for small batches.
  * Errors: as kb_query.
  */

@@ -1700,11 +1700,13 @@ struct ProbePlan {
     size_t off_lists, total;
 };
 
-bool make_probe_plan(int32_t Q, int32_t k, int32_t nprobe, ProbePlan *out)
+// `few`: no more than 64 lists per query.  Enough for the same results, in less memory where k is small; a call that brings
+// only that much runs so.
+bool make_probe_plan(int32_t Q, int32_t k, int32_t nprobe, ProbePlan *out, bool few = false)
 {
     if (Q < 1 || Q > 65535 || k < 1 || k > KB_K_MAX || nprobe < 1 || nprobe > PROBE_MAX) return false;
     ProbePlan p;
-    p.splits = probe_splits(Q, k, nprobe);
+    p.splits = probe_splits(Q, few ? KB_K_MAX : k, nprobe);
     p.off_lists = 0;
     p.total = p.off_lists + align_up((size_t)Q * nprobe * p.splits * k * 8);
     *out = p;
@@ -2193,6 +2195,7 @@ kb_status_t kb_query_probe(kb_t *kb, const void *queries_dev, kb_dtype_t q_dtype
         return KB_ERR_INVALID_ARG;
     if (qmask_dev && !kb->tags) return KB_ERR_NO_TAGS;
     if (kb->n_normalized != kb->n) return KB_ERR_NOT_NORMALIZED;
+    if (workspace_bytes < p.total) make_probe_plan(Q, k, nprobe, &p, true);
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & (WS_ALIGN - 1)) != 0 || workspace_bytes < p.total) return KB_ERR_WORKSPACE;
 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);

@@ -128,3 +128,27 @@ def test_rows_grouped_by_cluster_stay_on_the_fast_path(T, Q, k):
     w, cent, off = W.grouped(seed=Q, C=64, mean_size=1000, d=256, spread=0.03, Q=Q, k=k, dtype=torch.bfloat16)
     rep, cnt, _ = T.run_and_check(w, label=f"grouped rows Q={Q}")
     assert rep.queries == Q and cnt["exhaustive_queries"] == 0
+
+
+@pytest.mark.parametrize("Q,k,nprobe", [(1, 5, 16), (3, 10, 64), (8, 127, 3)])
+def test_a_workspace_for_64_lists_gives_the_same_result(T, Q, k, nprobe):
+    # 64 lists of k words per query, in as many equal parts per cluster as fit (at most 16): less than the planner asks for
+    w, cent, off = W.grouped(seed=11, C=64, mean_size=200, d=128, Q=Q, k=k, dtype=torch.bfloat16)
+    kb = T.build_kb(w)
+    probe = torch.from_numpy(_random_probe(np.random.default_rng(Q), Q, 64, nprobe)).cuda()
+    q, o = w.queries.cuda(), off.cuda()
+    want_i, want_s = kb.query_probe(q, k, o, probe)
+    parts = min(16, 64 // nprobe, -(-1024 // (Q * nprobe)))
+    small = torch.empty(-(-(Q * nprobe * parts * k * 8) // 256) * 256, dtype=torch.uint8, device="cuda")
+    L = kbmod.lib()
+    assert small.numel() <= L.kb_query_probe_workspace_bytes(kb._h, Q, k, nprobe)
+    index, score = torch.empty_like(want_i), torch.empty_like(want_s)
+
+    def call(size):
+        return L.kb_query_probe(kb._h, kbmod._ptr(q), kbmod.KB_BF16, Q, None, k, kbmod._ptr(o), o.numel() - 1, kbmod._ptr(probe), nprobe,
+                                kbmod._ptr(index), kbmod._ptr(score), kbmod._ptr(small), size, kbmod._stream())
+
+    assert call(small.numel() - 1) == 7 and call(small.numel()) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(index, want_i) and torch.equal(score, want_s)
+    kb.close()
