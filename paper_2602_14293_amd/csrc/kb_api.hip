@@ -1904,6 +1904,8 @@ size_t kb_query_plan_bytes(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int3
 {
     if (!kb || n < 0 || n > kb->capacity || Q < 1 || k < 1 || k > KB_K_MAX || kind < 0 || kind > 3) return 0;
     if (WholePlan wp; make_whole_plan(kb, n, Q, k, (kind & 1) != 0, (kind & 2) != 0, &wp)) return wp.total;
+    if (const int parts = small_path_parts(kb, n, Q, (kind & 1) != 0); parts && ((kind & 2) == 0 || kb->dtype == KB_FP8_E4M3))
+        return make_small_plan(Q, k, parts).total;
     Plan p;
     return make_plan(kb, n, Q, k, (kind & 1) != 0, (kind & 2) != 0, &p) ? p.total : 0;
 }

@@ -245,6 +245,23 @@ def test_workspace_size_bounds_the_plan_of_every_row_count(L, dtype, d, cap, Q, 
     L.kb_destroy(h)
 
 
+@pytest.mark.parametrize("dtype,d,n,Q,k", [(kbmod.KB_F32, 64, 128, 1000, 128), (kbmod.KB_BF16, 64, 1, 1, 1), (kbmod.KB_BF16, 128, 500, 200, 16),
+                                           (kbmod.KB_FP8_E4M3, 64, 16384, 16, 128), (kbmod.KB_BF16, 256, 8193, 4, 100)])
+def test_plan_bytes_of_a_small_store_are_its_lists(L, dtype, d, n, Q, k):
+    # too many queries, or k too large for the number of rows, to be selected from groups of rows: one sorted list of k
+    # words per query and part of the rows is all the call keeps, besides the diagnostics
+    st, h = _create(L, d=d, dtype=dtype, cap=n, scale=FAKE if dtype == kbmod.KB_FP8_E4M3 else None)
+    assert st == 0
+    lists = Q * min(64, -(-n // 128)) * k * 8
+    for kind in (0, 2):
+        got = L.kb_query_plan_bytes(h, n, Q, k, kind)
+        if kind == 2 and dtype != kbmod.KB_FP8_E4M3:
+            assert got == 0                                  # fp8 queries on other keys: not a call the handle takes
+            continue
+        assert lists <= got <= lists + 2048 and got <= L.kb_query_workspace_bytes(h, Q, k)
+    L.kb_destroy(h)
+
+
 def test_workspace_size_follows_the_tuning_knobs(L):
     st, h = _create(L, d=1024, cap=1 << 20)
     for name, value in ((b"sample_keys", 4096), (b"scan_config", 3), (b"wg_per_cu", 2), (b"small_path", 0)):
