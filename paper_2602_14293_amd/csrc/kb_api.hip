@@ -10,6 +10,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 
 #include "kb_configs.hpp"
@@ -333,6 +334,7 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
 // 0.9 to 1.05 times at four; at ten it loses (0.85 to 1.05).
 constexpr int64_t WHOLE_FINE_GROUPS = 4096;
 constexpr int64_t WHOLE_MAX_ROWS_FEW = 5 * 128 * 2 * DEVICE_CUS, WHOLE_MAX_ROWS = 3 * 128 * 2 * DEVICE_CUS;     // up to 32 queries; up to 128
+constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
 bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, WholePlan *out)
 {
     if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
@@ -343,7 +345,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     else p.config = Q <= 32 ? 1 : 2;
     if (h->dtype == KB_FP8_E4M3 && Q <= 32 && h->d % 128 == 0 && stream_keys(h, n, 1)) p.config = q8 ? FP8_QUERY_STREAM_CONFIG : FP8_STREAM_CONFIG;
     // tiles of 32 rows while those of 128 would leave compute units without one
-    if (p.config == 1 && n <= 128 * DEVICE_CUS / 2) p.config = h->dtype == KB_F32 ? SMALL_F32_CONFIG : 13;
+    if (p.config == 1 && n <= WHOLE_SMALL_TILE_ROWS) p.config = h->dtype == KB_F32 ? SMALL_F32_CONFIG : 13;
     ConfigInfo ci;
     if (!scan_config_info(h->dtype, p.config, &ci)) return false;
     p.tk = ci.tk;
@@ -1873,8 +1875,9 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
 size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
 {
     if (!kb || Q < 1 || k < 1 || k > KB_K_MAX) return 0;
-    // Every combination of kernels a query on this handle can run (the choice depends on the row count only through
-    // the two sides of WIDE128_MIN_ROWS, and on the kind of query), each bounded over all row counts.
+    // Every combination of kernels a query on this handle can run, each bounded over all row counts.  The choice depends on
+    // the kind of query and, through two limits of which a handle's type and batch meet at most one, on the row count
+    // (WIDE128_MIN_ROWS for bf16 rows, the size of the Infinity Cache for fp8 rows): its two sides are those of 1 and of the capacity.
     Sizes m;
     memset(&m, 0, sizeof m);
     bool any = false;
@@ -1889,13 +1892,16 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     if (!any) return 0;
     Plan p;
     lay_out(m, &p);
-    // the whole-store plan: grows with its groups, so with the rows up to where the groups get coarser and to the most it takes
     size_t total = p.total;
-    const int64_t most[] = {WHOLE_FINE_GROUPS * 32, WHOLE_FINE_GROUPS * 64, WHOLE_MAX_ROWS, WHOLE_MAX_ROWS_FEW};       // the most rows by group height and by rule
+    // a store scored in parts: the most parts that its rows and the limit on workgroups allow
+    const int64_t parts = std::min<int64_t>({PROBE_MAX, SMALL_BLOCKS / Q, ceil_div(kb->capacity, 128)});
+    if (parts > 0) total = std::max(total, make_small_plan(Q, k, (int)parts).total);
+    // the whole-store plan: grows with its groups, so with the rows up to where the groups get coarser and to the most it takes
+    const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, WHOLE_FINE_GROUPS * 32, WHOLE_FINE_GROUPS * 64, WHOLE_MAX_ROWS, WHOLE_MAX_ROWS_FEW};
     for (int64_t n : most)
         for (int q8 = 0; q8 < 2; ++q8) {
             WholePlan wp;
-            if (make_whole_plan(kb, n < kb->capacity ? n : kb->capacity, Q, k, false, q8 != 0, &wp) && wp.total > total) total = wp.total;
+            if (make_whole_plan(kb, std::min(n, kb->capacity), Q, k, false, q8 != 0, &wp)) total = std::max(total, wp.total);
         }
     return total;
 }

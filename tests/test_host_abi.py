@@ -262,6 +262,24 @@ def test_plan_bytes_of_a_small_store_are_its_lists(L, dtype, d, n, Q, k):
     L.kb_destroy(h)
 
 
+def test_workspace_size_covers_small_stores_on_any_knob_free_path(L):
+    # capacities just above 16,384 rows: f32 stores are cut into the most groups (16 rows each) at 16,384, not at the
+    # capacity; 20 bytes per group and query, and the diagnostics.  Up to that many rows a store may also be scored in
+    # parts, whose lists are bounded by 1024 workgroups of k words.
+    for cap in (16384, 16385, 17000, 20000, 32768, 40000):
+        for dtype, d in ((kbmod.KB_F32, 32), (kbmod.KB_F32, 256), (kbmod.KB_BF16, 64)):
+            st, h = _create(L, d=d, dtype=dtype, cap=cap)
+            for Q in (1, 8, 31, 32, 33, 128):
+                for k in (1, 5, 50, 128):
+                    need = L.kb_query_workspace_bytes(h, Q, k)
+                    whole = max(L.kb_query_plan_bytes(h, n, Q, k, 0) for n in (16384, 16383, 16000, 12000, cap))
+                    parts = min(64, 1024 // Q)
+                    assert need >= whole and need >= Q * parts * k * 8
+                    if dtype == kbmod.KB_F32 and Q <= 32 and k <= 5:
+                        assert need >= 20 * 1024 * Q
+            L.kb_destroy(h)
+
+
 def test_workspace_size_follows_the_tuning_knobs(L):
     st, h = _create(L, d=1024, cap=1 << 20)
     for name, value in ((b"sample_keys", 4096), (b"scan_config", 3), (b"wg_per_cu", 2), (b"small_path", 0)):
