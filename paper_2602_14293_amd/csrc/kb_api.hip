@@ -332,7 +332,6 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
 // workgroup.  Measured against the pipeline on stores of 256 and 1024 elements a row, masked and not: up to three tiles
 // for every resident workgroup 1.05 to 1.8 times as fast, with up to 32 queries still 1.0 to 1.3 times at five, with more
 // 0.9 to 1.05 times at four; at ten it loses (0.85 to 1.05).
-constexpr int64_t WHOLE_FINE_GROUPS = 4096;
 constexpr int64_t WHOLE_MAX_ROWS_FEW = 5 * 128 * 2 * DEVICE_CUS, WHOLE_MAX_ROWS = 3 * 128 * 2 * DEVICE_CUS;     // up to 32 queries; up to 128
 constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
 bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, WholePlan *out)
@@ -354,10 +353,10 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     const int64_t tiles = ceil_div(n, ci.tk);
     // a group is the rows of one wave while there are few of them (groups_per_tile counts both lane halves of its waves)
     const int fine_rows = 2 * ci.tk / ci.groups_per_tile;
-    p.fine = tiles * (ci.tk / fine_rows) <= WHOLE_FINE_GROUPS;
+    p.fine = tiles * (ci.tk / fine_rows) <= WHOLE_MAX_GROUPS;
     p.group_rows = p.fine ? fine_rows : ci.tk;
     p.run_shift = ci.tk >= 64 ? 2 : 0;
-    if (tiles * (ci.tk / p.group_rows) > WHOLE_MAX_GROUPS) return false;
+    static_assert(WHOLE_MAX_ROWS_FEW / 128 <= WHOLE_MAX_GROUPS && WHOLE_MAX_ROWS / 64 <= WHOLE_MAX_GROUPS, "whole tiles: 128 rows, or 64 with more than 32 queries");
     p.groups = (int32_t)(tiles * (ci.tk / p.group_rows));
     // Groups with three of a query's k best are scored again, which costs a call some 5 us: k^3 / 6 / groups^2 of them if
     // rows come in no order.  One in fifty queries is the limit.
@@ -1007,26 +1006,30 @@ struct WholeSelectArgs {
     int64_t n_keys;
     int32_t k, d, groups, group_rows, tile_rows, tiles, run_shift, grid;
 };
+// 256 threads hold the groups: the kernel's length is a dozen barriers, which more wavefronts only make longer (64 queries
+// x 2048 groups: 7.6 us with 256 threads, 8.2 with 1024)
+constexpr int WHOLE_THREADS = 256;
 constexpr int WHOLE_BINS = 256;          // four a lane of the wavefront that adds them up
-constexpr int WHOLE_CAP = 4096;         // words gathered before they are cut down to the best k: two steps of 1024 threads and more
+constexpr int WHOLE_CAP = 4096;         // words gathered before they are cut down to the best k
 constexpr int WHOLE_LIST = 2048;        // groups listed at a time
-constexpr int WHOLE_PER_THREAD = WHOLE_MAX_GROUPS / 1024;
+constexpr int WHOLE_PER_THREAD = WHOLE_MAX_GROUPS / WHOLE_THREADS;
 
-template <int KT> __global__ __launch_bounds__(1024) void whole_select_kernel(WholeSelectArgs a)
+template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_kernel(WholeSelectArgs a)
 {
     constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
     __shared__ __attribute__((aligned(16))) uint64_t buf[WHOLE_CAP];
     __shared__ __attribute__((aligned(16))) uint32_t hist[WHOLE_BINS];
     __shared__ uint16_t list[WHOLE_LIST], again[WHOLE_LIST];            // groups that reach the bound; groups to score again
     __shared__ SelectScratch sc;
-    __shared__ float sh_iq, sh_lo[2][16], sh_hi[2][16];
+    __shared__ float sh_iq, sh_lo[2][WHOLE_THREADS / 64], sh_hi[2][WHOLE_THREADS / 64];
     __shared__ uint32_t sh_cnt, sh_bin, sh_above, sh_ge, sh_listed, sh_again;
     __shared__ uint64_t sh_thr;
-    const int q = blockIdx.x, tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = nt >> 6, k = a.k, groups = a.groups;
+    constexpr int nt = WHOLE_THREADS, nw = nt / 64;
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k = a.k, groups = a.groups;
     constexpr float NONE = -__builtin_inff();
     const float *best = a.best + (size_t)q * groups;
     const u32x4 *pair = a.pair + (size_t)q * groups;
-    // this thread's groups: tid, tid + nt, ... (at most WHOLE_PER_THREAD: the host picks nt); their loads go out first
+    // this thread's groups: tid, tid + nt, ...; their loads go out first
     const int rounds = (groups + nt - 1) / nt;
     float v[WHOLE_PER_THREAD];
 #pragma unroll
@@ -1185,7 +1188,7 @@ template <int KT> __global__ __launch_bounds__(1024) void whole_select_kernel(Wh
                 const uint32_t g = again[t / per], place = t % per * 32;
                 const int lrow = lane & 31, half = lane >> 5;
                 const int64_t at = row_of(g, place + lrow), mine = at < a.n_keys ? at : a.n_keys - 1;      // (a place past a group of 16 is some other row)
-                const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 8 : 4>(a.keys, a.queries, a.d, mine, q);      // (128 registers with 1024 threads)
+                const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, mine, q);
                 const float dot = select16(acc, lrow & 15);
                 const uint32_t rel = place + 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3);
                 const int64_t row = row_of(g, rel);
@@ -1863,10 +1866,7 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     const int kt = q8 ? KT_FP8_Q8 : (int)h->dtype;
     void (*fn)(WholeSelectArgs) = kt == KB_F32 ? &whole_select_kernel<KB_F32> : kt == KB_BF16 ? &whole_select_kernel<KB_BF16>
                                 : kt == KB_FP8_E4M3 ? &whole_select_kernel<KB_FP8_E4M3> : &whole_select_kernel<KT_FP8_Q8>;
-    // as few threads as hold the groups: its length is a dozen barriers, which more wavefronts only make longer (64 queries
-    // x 2048 groups: 7.6 us with 256 threads, 8.2 with 1024)
-    const int threads = p.groups > 8 * 1024 ? 1024 : p.groups > 4 * 1024 ? 512 : 256;
-    hipLaunchKernelGGL(fn, dim3(Q), dim3(threads), 0, s, t);
+    hipLaunchKernelGGL(fn, dim3(Q), dim3(WHOLE_THREADS), 0, s, t);
     return hipGetLastError() == hipSuccess ? KB_OK : KB_ERR_DEVICE;
 }
 
@@ -1897,7 +1897,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     const int64_t parts = std::min<int64_t>({PROBE_MAX, SMALL_BLOCKS / Q, ceil_div(kb->capacity, 128)});
     if (parts > 0) total = std::max(total, make_small_plan(Q, k, (int)parts).total);
     // the whole-store plan: grows with its groups, so with the rows up to where the groups get coarser and to the most it takes
-    const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, WHOLE_FINE_GROUPS * 32, WHOLE_FINE_GROUPS * 64, WHOLE_MAX_ROWS, WHOLE_MAX_ROWS_FEW};
+    const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, WHOLE_MAX_GROUPS * 32, WHOLE_MAX_GROUPS * 64, WHOLE_MAX_ROWS, WHOLE_MAX_ROWS_FEW};
     for (int64_t n : most)
         for (int q8 = 0; q8 < 2; ++q8) {
             WholePlan wp;

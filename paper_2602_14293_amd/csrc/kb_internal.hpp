@@ -124,7 +124,7 @@ struct Plan {
 // best of the groups' best and takes what reaches it, scoring a group again only when a third row of it might.
 // GroupPair as four words: bits of the second best product, bits of the bound, row of the best | row of the second
 // << 8 (within the group), 0.  A group without a (second) entry has -inf there.
-constexpr int WHOLE_MAX_GROUPS = 16384;     // a thread of the selecting workgroup (1024) keeps 16 of them
+constexpr int WHOLE_MAX_GROUPS = 4096;      // a thread of the selecting workgroup (256) keeps 16 of them
 struct WholePlan {
     int32_t config, tk, tq, nqb, grid;
     int32_t groups, group_rows, fine, run_shift;

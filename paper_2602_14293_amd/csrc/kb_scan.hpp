@@ -473,7 +473,8 @@ template <class C> hipError_t launch_whole_cfg(int grid, const ScanArgs &a, hipS
 template <class C> hipError_t launch_scan_cfg(bool sample, int grid, const ScanArgs &a, hipStream_t s)
 {
     if (a.whole_best) {
-        if constexpr (C::TQ <= 128) return launch_whole_cfg<C>(grid, a, s);
+        // (bf16 rows and 65 to 128 queries: tiles of 64 rows, or of 128 on eight wavefronts)
+        if constexpr (C::TQ <= 128 && !(C::KT == KB_BF16 && C::TQ == 128 && C::TK == 128)) return launch_whole_cfg<C>(grid, a, s);
         return hipErrorInvalidValue;
     }
     if (a.draw.enabled) return sample ? launch_scan_policy<C, true, true, false>(grid, a, s) : launch_scan_policy<C, false, true, false>(grid, a, s);
