@@ -355,7 +355,6 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     const int fine_rows = 2 * ci.tk / ci.groups_per_tile;
     p.fine = tiles * (ci.tk / fine_rows) <= WHOLE_MAX_GROUPS;
     p.group_rows = p.fine ? fine_rows : ci.tk;
-    p.run_shift = ci.tk >= 64 ? 2 : 0;
     static_assert(WHOLE_MAX_ROWS_FEW / 128 <= WHOLE_MAX_GROUPS && WHOLE_MAX_ROWS / 64 <= WHOLE_MAX_GROUPS, "whole tiles: 128 rows, or 64 with more than 32 queries");
     p.groups = (int32_t)(tiles * (ci.tk / p.group_rows));
     // Groups with three of a query's k best are scored again, which costs a call some 5 us: k^3 / 6 / groups^2 of them if
@@ -669,9 +668,33 @@ __device__ inline void select_topk_desc(uint64_t *buf, int n, int k, SelectScrat
     int shift = 0;
     uint64_t pref = 1;
     if ((int)nz > k) {
-        const uint32_t diff = all_and ^ all_or;              // (the lower halves, row numbers, differ anyway)
+        const uint32_t diff = all_and ^ all_or;
         int hi = diff ? 64 - __builtin_clz(diff) : 32;       // bits [hi, 64) are decided and equal pref
         pref = hi >= 64 ? 0ull : (uint64_t)(all_or >> (hi - 32));
+        if (diff == 0) {        // equal scores: what the row numbers share would be counted into one bin each, one word after the other
+            uint32_t alo = ~0u, olo = 0u;
+            for (int i = tid; i < n; i += nthreads) {
+                const uint64_t e = buf[i];
+                alo &= e != 0 ? (uint32_t)e : ~0u;
+                olo |= (uint32_t)e;
+            }
+            alo = wave_scan_and(alo);
+            olo = wave_scan_or(olo);
+            __syncthreads();            // (the parts above have been read)
+            if (lane == 63) {
+                sc->part[wave][1] = alo;
+                sc->part[wave][2] = olo;
+            }
+            __syncthreads();
+            for (int w = 0; w < nwaves; ++w) {
+                alo &= sc->part[w][1];
+                olo |= sc->part[w][2];
+            }
+            alo = (uint32_t)__builtin_amdgcn_readlane((int)alo, 63);
+            olo = (uint32_t)__builtin_amdgcn_readlane((int)olo, 63);
+            hi = alo != olo ? 32 - __builtin_clz(alo ^ olo) : 0;
+            pref = ((uint64_t)all_or << 32 | olo) >> hi;
+        }
         uint32_t need = (uint32_t)k;
         for (int pass = 0; pass < 9 && hi > 0; ++pass) {
             const int width = hi < 8 ? hi : 8, lo = hi - width;
@@ -989,10 +1012,12 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
 // The k-th largest of the groups' best scores bounds the k-th best score from below (k distinct rows reach it).  It is
 // found by counting the best scores in equal bins between the smallest and the largest: scores near the top of a store
 // are sparse, so one pass of the counting leaves a handful of groups beyond the k wanted ones; only when many groups
-// share the deciding bin is that bin divided again.  Of the groups that reach the bound the two best rows are known; one
-// in which a third row might reach it as well is scored again, with the instruction sequence of the scan.  Everything
-// that decides is a comparison of final scores, a non-decreasing function of the products, so rows whose scores tie
-// after rounding are never told apart here; the candidate words order them by index.
+// share the deciding bin is that bin divided again.  Of the groups that reach the bound two or three rows are known.  If
+// a row that is not could reach it as well, the k-th best of all that are known is found, and groups where such a row
+// might come before that are scored again, with the instruction sequence of the scan: at most about k / 2 (see WholePlan).
+// 16,384 equal bf16 rows of 1024 elements and 8 queries, where every group ties: 24 us a call; when every group whose third
+// row ties was scored again, 1502.  Everything that decides is a comparison of final scores, a non-decreasing function
+// of the products, or of candidate words, which order equal scores by index.
 // ------------------------------------------------------------------------------------------------
 struct WholeSelectArgs {
     const void *keys, *queries;
@@ -1004,14 +1029,13 @@ struct WholeSelectArgs {
     float *out_score;
     uint64_t *stats;
     int64_t n_keys;
-    int32_t k, d, groups, group_rows, tile_rows, tiles, run_shift, grid;
+    int32_t k, d, groups, group_rows, tile_rows, tiles, grid;
 };
 // 256 threads hold the groups: the kernel's length is a dozen barriers, which more wavefronts only make longer (64 queries
 // x 2048 groups: 7.6 us with 256 threads, 8.2 with 1024)
 constexpr int WHOLE_THREADS = 256;
 constexpr int WHOLE_BINS = 256;          // four a lane of the wavefront that adds them up
 constexpr int WHOLE_CAP = 4096;         // words gathered before they are cut down to the best k
-constexpr int WHOLE_LIST = 2048;        // groups listed at a time
 constexpr int WHOLE_PER_THREAD = WHOLE_MAX_GROUPS / WHOLE_THREADS;
 
 template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_kernel(WholeSelectArgs a)
@@ -1019,7 +1043,7 @@ template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_
     constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
     __shared__ __attribute__((aligned(16))) uint64_t buf[WHOLE_CAP];
     __shared__ __attribute__((aligned(16))) uint32_t hist[WHOLE_BINS];
-    __shared__ uint16_t list[WHOLE_LIST], again[WHOLE_LIST];            // groups that reach the bound; groups to score again
+    __shared__ uint16_t list[WHOLE_MAX_GROUPS], again[WHOLE_MAX_GROUPS];        // groups that reach the bound; with what is not known of them
     __shared__ SelectScratch sc;
     __shared__ float sh_iq, sh_lo[2][WHOLE_THREADS / 64], sh_hi[2][WHOLE_THREADS / 64];
     __shared__ uint32_t sh_cnt, sh_bin, sh_above, sh_ge, sh_listed, sh_again;
@@ -1137,95 +1161,88 @@ template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_
         bin_min = 0;
     }
 
-    // row at place `rel` of group g (the groups of a tile follow each other)
-    auto row_of = [&](uint32_t g, uint32_t rel) {
-        const uint32_t per_tile = (uint32_t)a.tile_rows / (uint32_t)a.group_rows, tile = g / per_tile;
-        return (uint32_t)whole_row((int32_t)tile, a.tiles, a.tile_rows, a.run_shift, (int)((g - tile * per_tile) * (uint32_t)a.group_rows + rel));
-    };
+    // row at a place of the tile of group g (the groups of a tile follow each other)
+    const uint32_t per_tile = (uint32_t)a.tile_rows / (uint32_t)a.group_rows;
+    auto row_at = [&](uint32_t g, uint32_t place) { return (uint32_t)whole_row((int32_t)(g / per_tile), a.tiles, a.tile_rows, (int)place); };
+    auto first_place = [&](uint32_t g) { return g % per_tile * (uint32_t)a.group_rows; };
     auto append = [&](float product, uint32_t row) {
         const float f = product * iq + 0.0f;
         const uint64_t cw = pack_candidate(f, row);
         if (product > NONE && passes(f) && cw > sh_thr) buf[atomicAdd(&sh_cnt, 1u)] = cw;
     };
-    // Room for a step that appends up to `most` words; `have`: no more than that are in the buffer (called converged,
-    // nobody appending).
-    auto make_room = [&](uint32_t have, uint32_t most) {
-        if (have + most <= (uint32_t)WHOLE_CAP) return;         // (uniform)
-        select_topk_desc(buf, (int)have, k, &sc, tid, nt);      // cut down to the best k
+    // Cuts the `have` words gathered down to the best k and takes the k-th as the threshold (called converged, nobody
+    // appending).
+    auto cut = [&](uint32_t have) {
+        select_topk_desc(buf, (int)have, k, &sc, tid, nt);
         if (tid == 0) {
             sh_cnt = have < (uint32_t)k ? have : (uint32_t)k;
             sh_thr = have >= (uint32_t)k ? buf[k - 1] : 0ull;
         }
         __syncthreads();
     };
-    // The listed groups, one a thread: the two best rows, or a place on the list of those to be scored again.
-    auto look_into = [&](uint32_t n, uint32_t have) {
-        for (uint32_t j0 = 0; j0 < n; j0 += (uint32_t)nt) {
-            make_room(have, 2 * (uint32_t)nt);
-            const uint32_t j = j0 + (uint32_t)tid;
-            if (j < n) {
-                const uint32_t g = list[j], row0 = row_of(g, 0);
-                const u32x4 x = pair[g];
-                const float first = best[g], bound = as_f32(x[1]) * iq + 0.0f;
-                // (row0 is the group's lowest row: a bound that ties with the k-th word's score can still lose)
-                if (as_f32(x[1]) > NONE && passes(bound) && pack_candidate(bound, row0) > sh_thr) {
-                    again[atomicAdd(&sh_again, 1u)] = (uint16_t)g;
-                } else {
-                    append(first, row_of(g, x[2] & 255u));
-                    append(as_f32(x[0]), row_of(g, x[2] >> 8 & 255u));
-                }
-            }
-            __syncthreads();
-            have = sh_cnt;
-            if (j0 + (uint32_t)nt < n) __syncthreads();         // (everyone has the count that the next step moves on)
+#pragma unroll
+    for (int u = 0; u < WHOLE_PER_THREAD; ++u)
+        if (u < rounds && v[u] > NONE && passes(v[u])) list[atomicAdd(&sh_listed, 1u)] = (uint16_t)(tid + u * nt);
+    __syncthreads();
+    const uint32_t listed = sh_listed;
+    uint32_t have = 0;
+    for (uint32_t j0 = 0; j0 < listed; j0 += (uint32_t)nt) {        // one group a thread: the rows known
+        if (have + 3 * (uint32_t)nt > (uint32_t)WHOLE_CAP) cut(have);
+        const uint32_t j = j0 + (uint32_t)tid;
+        if (j < listed) {
+            const uint32_t g = list[j];
+            const u32x4 x = pair[g];
+            append(best[g], row_at(g, x[2] & 255u));
+            append(as_f32(x[0]), row_at(g, x[2] >> 8 & 255u));
+            const uint32_t third = x[2] >> 16 & 255u;
+            if (third != 0u) append(as_f32(x[1]), row_at(g, third - 1u));
+            if (as_f32(x[1]) > NONE && passes(as_f32(x[1]) * iq + 0.0f)) again[atomicAdd(&sh_again, 1u)] = (uint16_t)g;
         }
-        const uint32_t per = ((uint32_t)a.group_rows + 31) / 32, tasks = n > 0 ? sh_again * per : 0u;
+        __syncthreads();
+        have = sh_cnt;
+        if (j0 + (uint32_t)nt < listed) __syncthreads();         // (everyone has the count that the next step moves on)
+    }
+    const uint32_t asked = listed > 0 ? sh_again : 0u;
+    if (asked > 0) {
+        __syncthreads();
+        if (tid == 0) sh_listed = 0;
+        cut(have);
+        // those of which a row that is not known could come before the k-th of those that are
+        for (uint32_t j = (uint32_t)tid; j < asked; j += (uint32_t)nt) {
+            const uint32_t g = again[j];
+            const u32x4 x = pair[g];
+            const float third = as_f32(x[1]), f = third * iq + 0.0f;
+            const uint32_t place = x[2] >> 16 & 255u;
+            uint64_t most = pack_candidate(f, row_at(g, first_place(g)));       // (the group's lowest row)
+            if (place != 0u) {          // known: the others' scores are lower, or equal at higher rows unless the rounding hides a difference
+                const float below = ordered_to_score(score_to_ordered(third + 0.0f) - ((x[2] & WHOLE_NEAR) != 0u ? 1u : 3u));
+                if (below * iq + 0.0f < f) most = pack_candidate(f, row_at(g, place - 1u));
+            }
+            if (most > sh_thr) list[atomicAdd(&sh_listed, 1u)] = (uint16_t)g;
+        }
+        __syncthreads();
+        have = sh_cnt;
+        const uint32_t per = ((uint32_t)a.group_rows + 31) / 32, tasks = sh_listed * per;
         for (uint32_t t0 = 0; t0 < tasks; t0 += (uint32_t)nw) {     // 32 rows a wavefront
             __syncthreads();
-            make_room(have, 32 * (uint32_t)nw);
+            if (have + 32 * (uint32_t)nw > (uint32_t)WHOLE_CAP) cut(have);
             const uint32_t t = t0 + (uint32_t)wave;
             if (t < tasks) {
-                const uint32_t g = again[t / per], place = t % per * 32;
+                const uint32_t g = list[t / per], in_group = t % per * 32, place0 = first_place(g) + in_group, known = pair[g][2];
                 const int lrow = lane & 31, half = lane >> 5;
-                const int64_t at = row_of(g, place + lrow), mine = at < a.n_keys ? at : a.n_keys - 1;      // (a place past a group of 16 is some other row)
+                const int64_t at = row_at(g, place0 + lrow), mine = at < a.n_keys ? at : a.n_keys - 1;      // (a place past a group of 16 is some other row)
                 const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, mine, q);
                 const float dot = select16(acc, lrow & 15);
-                const uint32_t rel = place + 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3);
-                const int64_t row = row_of(g, rel);
-                if (lrow < 16 && rel < (uint32_t)a.group_rows && row < a.n_keys) {
+                const uint32_t rel = 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3), place = place0 + rel;
+                const int64_t row = row_at(g, place);
+                const bool listed_before = place == (known & 255u) || place == (known >> 8 & 255u) || place + 1u == (known >> 16 & 255u);
+                if (lrow < 16 && in_group + rel < (uint32_t)a.group_rows && row < a.n_keys && !listed_before) {
                     const float ik = a.inv_norm[row];
                     if (!row_removed(ik) && (!a.qmask || (a.tags[row] & qm) != 0)) append(dot * ik, (uint32_t)row);
                 }
             }
             __syncthreads();
             have = sh_cnt;
-        }
-        return have;
-    };
-    // (the bound of a group is at most 2^-16 relative above its best; this only matters for the third row of a group
-    // whose best three all but tie)
-    auto lists = [&](float f) { return f > NONE && passes(f + __builtin_fabsf(f) * 0x1p-15f + 1e-30f); };
-#pragma unroll
-    for (int u = 0; u < WHOLE_PER_THREAD; ++u) {
-        if (u < rounds && lists(v[u])) {
-            const uint32_t at = atomicAdd(&sh_listed, 1u);
-            if (at < (uint32_t)WHOLE_LIST) list[at] = (uint16_t)(tid + u * nt);
-        }
-    }
-    __syncthreads();
-    uint32_t have = 0;
-    if (sh_listed <= (uint32_t)WHOLE_LIST) {
-        have = look_into(sh_listed, 0u);
-    } else {                    // thousands of equal scores: nt groups at a time, the threshold word rises as it goes
-#pragma unroll 1
-        for (int u = 0; u < rounds; ++u) {
-            __syncthreads();
-            if (tid == 0) sh_listed = sh_again = 0;
-            __syncthreads();
-            const float f = tid + u * nt < groups ? best[tid + u * nt] : NONE;
-            if (f > NONE && lists(f * iq + 0.0f)) list[atomicAdd(&sh_listed, 1u)] = (uint16_t)(tid + u * nt);
-            __syncthreads();
-            have = look_into(sh_listed, have);
         }
     }
     // the result in order: few words place themselves by counting the larger ones, many are cut down first
@@ -1832,7 +1849,6 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     a.whole_pair = reinterpret_cast<u32x4 *>(ws + p.off_pair);
     a.whole_groups = p.groups;
     a.whole_fine = p.fine;
-    a.whole_run_shift = p.run_shift;
     const bool timed = h->prof_events && h->prof_used < h->prof_max && h->prof_seen++ % h->prof_stride == h->prof_stride / 2;
     if (timed) {
         scan_timing.start = h->prof_events[2 * h->prof_used];
@@ -1861,7 +1877,6 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     t.group_rows = p.group_rows;
     t.tile_rows = p.tk;
     t.tiles = (int32_t)a.n_tiles;
-    t.run_shift = p.run_shift;
     t.grid = p.grid;
     const int kt = q8 ? KT_FP8_Q8 : (int)h->dtype;
     void (*fn)(WholeSelectArgs) = kt == KB_F32 ? &whole_select_kernel<KB_F32> : kt == KB_BF16 ? &whole_select_kernel<KB_BF16>
@@ -2028,7 +2043,7 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         a.keys_once = stream_keys(kb, kb->n, p.nqb);
         a.whole_best = nullptr;
         a.whole_pair = nullptr;
-        a.whole_groups = a.whole_fine = a.whole_run_shift = 0;
+        a.whole_groups = a.whole_fine = 0;
         a.tile_stride = 1;
         a.row_mul = 0;
         a.row_run_shift = 0;

@@ -269,69 +269,134 @@ __device__ inline void sample_epilogue(const f32x16 (&acc)[IB][JB], const EpiSid
 }
 
 // ------------------------------------------------------------------------------------------------
-// Whole-store plan: per query and group of rows (the rows of the tile) the two best qualifying products, exact, and an
-// upper bound on every other one.
+// Whole-store plan: per query and group of rows the two best qualifying products, exact, and the third or a bound on it.
 // ------------------------------------------------------------------------------------------------
-struct TopTwo {
-    float first, second;       // products; -inf where there is none
-    float bound;               // no other row of the group has a larger product
-    uint32_t rows;             // tile-local rows: first | second << 8
+struct TopThree {
+    float first, second;       // products of the two best rows; -inf where there is none
+    float third;               // no other row of the group has a larger product
+    uint32_t rows;             // places in the tile, as in the group's entry (see WholePlan)
 };
-// The same of the rows of both arguments.
-__device__ inline TopTwo join(const TopTwo &a, const TopTwo &b)
+// The same of the rows of both arguments; the third is a bound.
+__device__ inline TopThree join(const TopThree &a, const TopThree &b)
 {
     const bool swap = b.first > a.first;
-    const TopTwo x = swap ? b : a, y = swap ? a : b;
+    const TopThree x = swap ? b : a, y = swap ? a : b;
     const bool keep = x.second >= y.first;
-    TopTwo r;
+    TopThree r;
     r.first = x.first;
     r.second = keep ? x.second : y.first;
-    r.rows = keep ? x.rows : (x.rows & 255u) | (y.rows << 8 & 0xff00u);
-    r.bound = __builtin_fmaxf(__builtin_fmaxf(x.bound, y.bound), keep ? y.first : __builtin_fmaxf(x.second, y.second));
+    r.rows = keep ? x.rows & 0xffffu : (x.rows & 255u) | (y.rows << 8 & 0xff00u);
+    r.third = __builtin_fmaxf(__builtin_fmaxf(x.third, y.third), keep ? y.first : __builtin_fmaxf(x.second, y.second));
     return r;
+}
+__device__ inline TopThree other_half(const TopThree &t, int lanes)
+{
+    TopThree o;
+    o.first = __shfl_xor(t.first, lanes, 64);
+    o.second = __shfl_xor(t.second, lanes, 64);
+    o.third = __shfl_xor(t.third, lanes, 64);
+    o.rows = (uint32_t)__shfl_xor((int)t.rows, lanes, 64);
+    return o;
+}
+// Whether, in some lane, what is not named could be as good as the second row (uniform).
+__device__ inline bool unclear(const TopThree &t)
+{
+    return __builtin_amdgcn_ballot_w64(t.third >= t.second && t.third > -__builtin_inff()) != 0;
+}
+
+// Does product a at order number oa come before b at ob?
+__device__ inline bool comes_before(float a, uint32_t oa, float b, uint32_t ob) { return a > b || (a == b && oa < ob); }
+// Units in the last place by which x is below `top`, less one (a large number where it is not); a row is near below 2.
+__device__ inline uint32_t gap_below(float top, float x)
+{
+    auto ordered = [](uint32_t u) { return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u); };      // (score_to_ordered without a condition)
+    return ordered(as_u32(top + 0.0f)) - ordered(as_u32(x + 0.0f)) - 1u;       // (one zero)
+}
+__device__ inline uint32_t least(uint32_t a, uint32_t b) { return a < b ? a : b; }
+
+// join for rows in the order of the result.  Each argument names its first three, or its first two and a bound below the
+// second; so does the result, as a bound that reaches the third place belongs to an argument whose two rows are the first
+// two.  (A bound wins against an equal product: the row behind it may have the lower index.)
+template <int TK> __device__ inline TopThree join_in_order(TopThree a, TopThree b)
+{
+    auto sorted = [](TopThree t) {        // two equal products that a join without order left as they came
+        const uint32_t p = t.rows & 255u, q = t.rows >> 8 & 255u;
+        if (t.first == t.second && whole_order<TK>(p) > whole_order<TK>(q)) t.rows = (t.rows & ~0xffffu) | q | p << 8;
+        return t;
+    };
+    a = sorted(a);
+    b = sorted(b);
+    auto order = [](const TopThree &t, int w) { return whole_order<TK>(t.rows >> (8 * w) & 255u); };
+    const bool swap = comes_before(b.first, order(b, 0), a.first, order(a, 0));
+    const TopThree x = swap ? b : a, y = swap ? a : b;
+    const bool keep = comes_before(x.second, order(x, 1), y.first, order(y, 0));
+    const uint32_t x3 = x.rows >> 16 & 255u;
+    const bool bound = keep && x3 == 0u && x.third >= y.first;
+    const bool third_x = keep ? bound || (x3 != 0u && comes_before(x.third, whole_order<TK>(x3 - 1u), y.first, order(y, 0)))
+                              : comes_before(x.second, order(x, 1), y.second, order(y, 1));
+    TopThree r;
+    r.first = x.first;
+    r.second = keep ? x.second : y.first;
+    r.third = keep ? (third_x ? x.third : y.first) : (third_x ? x.second : y.second);
+    const uint32_t place = keep ? (third_x ? x3 - 1u : y.rows & 255u) : ((third_x ? x.rows : y.rows) >> 8 & 255u);
+    r.rows = (keep ? x.rows & 0xffffu : (x.rows & 255u) | (y.rows << 8 & 0xff00u)) | (bound ? 0u : (place + 1u) << 16);
+    const float third = r.third;
+    auto gap = [third](const TopThree &t) { return least(least(gap_below(third, t.first), gap_below(third, t.second)), gap_below(third, t.third)); };
+    auto near = [third](const TopThree &t) { return t.third == third ? t.rows & WHOLE_NEAR : 0u; };
+    r.rows |= near(x) | near(y) | (least(gap(x), gap(y)) < 2u ? WHOLE_NEAR : 0u);
+    return r;
+}
+
+// The products of the lane's 16 elements of block (ib, jb), `none` in the place of rows that do not count.  rl0: tile-local
+// row of the first; dead: bit r set = row r of the wave's 32 * IB is removed or past the end.
+__device__ inline void whole_products(const f32x16 &a, const EpiSide &sd, bool filter, uint64_t qm, int rl0, int half, int ib, uint64_t dead, float none,
+                                      float (&v)[16])
+{
+#pragma unroll
+    for (int run = 0; run < 4; ++run) {
+        const int rl = rl0 + 8 * run;
+        const f32x4 ik4 = *reinterpret_cast<const f32x4 *>(sd.invk + rl);
+        const float ik[4] = {ik4.x, ik4.y, ik4.z, ik4.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * run + e] = a[4 * run + e] * ik[e];
+        if (filter) {
+            const u32x4 t0 = *reinterpret_cast<const u32x4 *>(sd.tag + rl), t1 = *reinterpret_cast<const u32x4 *>(sd.tag + rl + 2);
+            const uint32_t lo[4] = {t0.x, t0.z, t1.x, t1.z}, hi[4] = {t0.y, t0.w, t1.y, t1.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * run + e] = ((lo[e] & (uint32_t)qm) | (hi[e] & (uint32_t)(qm >> 32))) != 0 ? v[4 * run + e] : none;
+        }
+    }
+    if (dead != 0) {            // (uniform)
+        const uint32_t dead32 = (uint32_t)(dead >> (32 * ib)) >> (4 * half);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = (dead32 >> (8 * (i >> 2) + (i & 3)) & 1u) ? none : v[i];
+    }
 }
 
 // One wave column: the lane's 16 * IB elements.  As in the sampling search the element's number replaces the product's
 // low five bits, here with the product left a float: one maximum and two medians per element keep the largest three
-// in order.  The first two are then recomputed exactly; the third bounds the rest once its low bits are allowed
-// for (2^-17 relative).  dead: bit r set = row r of the wave's 32 * IB does not count (removed, or past the end).
+// in order.  The first two are then recomputed exactly; the third, its low bits at their largest, bounds the rest.
 template <int IB, int JB>
-__device__ inline TopTwo whole_column(const f32x16 (&acc)[IB][JB], int jb, const EpiSide &sd, bool filter, uint64_t qm, int wave_row0, int half,
-                                      uint64_t dead)
+__device__ inline TopThree whole_column(const f32x16 (&acc)[IB][JB], int jb, const EpiSide &sd, bool filter, uint64_t qm, int wave_row0, int half,
+                                        uint64_t dead)
 {
     const float none = as_f32(0xff7fffe0u);        // the lowest finite value but for its low bits
     float m1 = none, m2 = none, m3 = none;
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib) {
         float v[16];
-#pragma unroll
-        for (int run = 0; run < 4; ++run) {
-            const int rl = wave_row0 + ib * 32 + 8 * run + 4 * half;
-            const f32x4 ik4 = *reinterpret_cast<const f32x4 *>(sd.invk + rl);
-            const float ik[4] = {ik4.x, ik4.y, ik4.z, ik4.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * run + e] = as_f32((as_u32(acc[ib][jb][4 * run + e] * ik[e]) & ~31u) | (uint32_t)(ib * 16 + 4 * run + e));
-            if (filter) {
-                const u32x4 t0 = *reinterpret_cast<const u32x4 *>(sd.tag + rl), t1 = *reinterpret_cast<const u32x4 *>(sd.tag + rl + 2);
-                const uint32_t lo[4] = {t0.x, t0.z, t1.x, t1.z}, hi[4] = {t0.y, t0.w, t1.y, t1.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[4 * run + e] = ((lo[e] & (uint32_t)qm) | (hi[e] & (uint32_t)(qm >> 32))) != 0 ? v[4 * run + e] : none;
-            }
-        }
-        const uint32_t dead32 = (uint32_t)(dead >> (32 * ib)) >> (4 * half);
-        if (dead != 0) {            // (uniform)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = (dead32 >> (8 * (i >> 2) + (i & 3)) & 1u) ? none : v[i];
-        }
+        whole_products(acc[ib][jb], sd, filter, qm, wave_row0 + ib * 32 + 4 * half, half, ib, dead, none, v);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            m3 = __builtin_amdgcn_fmed3f(m2, m3, v[i]);
-            m2 = __builtin_amdgcn_fmed3f(m1, m2, v[i]);
-            m1 = __builtin_fmaxf(m1, v[i]);
+            const float f = as_f32((as_u32(v[i]) & ~31u) | (uint32_t)(ib * 16 + i));       // (never above `none` where v is)
+            m3 = __builtin_amdgcn_fmed3f(m2, m3, f);
+            m2 = __builtin_amdgcn_fmed3f(m1, m2, f);
+            m1 = __builtin_fmaxf(m1, f);
         }
     }
-    TopTwo t;
-    t.bound = m3 > none ? __builtin_fmaf(__builtin_fabsf(m3), 0x1p-17f, m3) + 0x1p-120f : -__builtin_inff();
+    TopThree t;
+    const uint32_t b3 = as_u32(m3);
+    t.third = m3 > none ? as_f32((int32_t)b3 < 0 ? b3 & ~31u : b3 | 31u) : -__builtin_inff();
     t.rows = 0;
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
@@ -353,22 +418,59 @@ __device__ inline TopTwo whole_column(const f32x16 (&acc)[IB][JB], int jb, const
     return t;
 }
 
+// The same with the first three in the order of the result: the elements are taken by rising row, one that is larger than
+// a place's moves in.  About 20 instructions an element, for the few columns where the search above leaves the third
+// unclear: one in ten thousand of a store without equal rows.
+template <int TK, int IB, int JB>
+__device__ inline TopThree whole_column_in_order(const f32x16 (&acc)[IB][JB], int jb, const EpiSide &sd, bool filter, uint64_t qm, int wave_row0, int half,
+                                                 uint64_t dead)
+{
+    static_assert(TK == 128 || IB == 1, "order of the elements");
+    constexpr float NONE = -__builtin_inff();
+    float v[IB][16];
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib) whole_products(acc[ib][jb], sd, filter, qm, wave_row0 + ib * 32 + 4 * half, half, ib, dead, NONE, v[ib]);
+    TopThree t = {NONE, NONE, NONE, 0u};
+    uint32_t p1 = 0, p2 = 0, p3 = 0;
+#pragma unroll
+    for (int n = 0; n < 16 * IB; ++n) {
+        // by rising whole_order: rows 32 places apart follow each other in a tile of 128, 16 places apart in one of 64
+        const int ib = TK == 64 ? 0 : n % IB, i = TK == 64 ? (n >> 1) | (n & 1) << 3 : n / IB;
+        const float f = v[ib][i];
+        const uint32_t place = (uint32_t)(wave_row0 + ib * 32 + 4 * half + 8 * (i >> 2) + (i & 3));
+        const bool g1 = f > t.first, g2 = f > t.second, g3 = f > t.third;
+        t.third = g2 ? t.second : g3 ? f : t.third;
+        p3 = g2 ? p2 : g3 ? place : p3;
+        t.second = g1 ? t.first : g2 ? f : t.second;
+        p2 = g1 ? p1 : g2 ? place : p2;
+        t.first = g1 ? f : t.first;
+        p1 = g1 ? place : p1;
+    }
+    uint32_t gap = ~0u;
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) gap = least(gap, gap_below(t.third, v[ib][i]));
+    t.rows = p1 | p2 << 8 | (p3 + 1u) << 16 | (gap < 2u ? WHOLE_NEAR : 0u);
+    return t;
+}
+
 // All waves of the workgroup call this, converged.  `exchange`: (WM - 1) * TQ entries in LDS.
-template <int IB, int JB, int WM, int TQ>
+template <int TK, int IB, int JB, int WM, int TQ>
 __device__ inline void whole_epilogue(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wm, int ql0, int half, int64_t tile,
                                       int q0, const ScanArgs &p, uint64_t dead, u32x4 *exchange)
 {
-    TopTwo t[JB];
+    TopThree t[JB];
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb) {
-        t[jb] = whole_column<IB, JB>(acc, jb, sd, filter, filter ? sd.qmask[ql0 + jb * 32] : 0ull, wm * IB * 32, half, dead);
-        TopTwo o;                   // the other half of the rows
-        o.first = __shfl_xor(t[jb].first, 32, 64);
-        o.second = __shfl_xor(t[jb].second, 32, 64);
-        o.bound = __shfl_xor(t[jb].bound, 32, 64);
-        o.rows = (uint32_t)__shfl_xor((int)t[jb].rows, 32, 64);
-        t[jb] = join(t[jb], o);
-        if (!p.whole_fine && wm > 0 && half == 0) exchange[(wm - 1) * TQ + ql0 + jb * 32] = u32x4{as_u32(t[jb].first), as_u32(t[jb].second), as_u32(t[jb].bound), t[jb].rows};
+        const uint64_t qm = filter ? sd.qmask[ql0 + jb * 32] : 0ull;
+        const TopThree own = whole_column<IB, JB>(acc, jb, sd, filter, qm, wm * IB * 32, half, dead);
+        t[jb] = join(own, other_half(own, 32));
+        if (__builtin_expect(unclear(t[jb]), 0)) {
+            const TopThree o = whole_column_in_order<TK, IB, JB>(acc, jb, sd, filter, qm, wm * IB * 32, half, dead);
+            t[jb] = join_in_order<TK>(o, other_half(o, 32));
+        }
+        if (!p.whole_fine && wm > 0 && half == 0) exchange[(wm - 1) * TQ + ql0 + jb * 32] = u32x4{as_u32(t[jb].first), as_u32(t[jb].second), as_u32(t[jb].third), t[jb].rows};
     }
     const int64_t group = p.whole_fine ? tile * WM + wm : tile;
     if (!p.whole_fine) {
@@ -381,15 +483,22 @@ __device__ inline void whole_epilogue(const f32x16 (&acc)[IB][JB], const EpiSide
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb) {
         const int ql = ql0 + jb * 32, q = q0 + ql;
-        for (int w = 0; w < (p.whole_fine ? 0 : WM - 1); ++w) {
-            const u32x4 x = exchange[w * TQ + ql];
-            t[jb] = join(t[jb], TopTwo{as_f32(x[0]), as_f32(x[1]), as_f32(x[2]), x[3]});
+        if (!p.whole_fine) {
+            auto of_wave = [&](int w) {
+                const u32x4 x = exchange[w * TQ + ql];
+                return TopThree{as_f32(x[0]), as_f32(x[1]), as_f32(x[2]), x[3]};
+            };
+            const TopThree own = t[jb];
+            for (int w = 0; w < WM - 1; ++w) t[jb] = join(t[jb], of_wave(w));
+            if (__builtin_expect(unclear(t[jb]), 0)) {
+                t[jb] = own;
+                for (int w = 0; w < WM - 1; ++w) t[jb] = join_in_order<TK>(t[jb], of_wave(w));
+            }
         }
         if (half == 0 && q < p.Q) {
             const size_t at = (size_t)q * p.whole_groups + group;
-            const uint32_t first_row = p.whole_fine ? (uint32_t)(wm * IB * 32) * 0x0101u : 0u;
             p.whole_best[at] = t[jb].first;
-            p.whole_pair[at] = u32x4{as_u32(t[jb].second), as_u32(t[jb].bound), t[jb].rows - first_row, 0u};
+            p.whole_pair[at] = u32x4{as_u32(t[jb].second), as_u32(t[jb].third), t[jb].rows, 0u};
         }
     }
 }

@@ -120,14 +120,21 @@ struct Plan {
 
 // The whole-store plan: a small or middling store, or a handful of queries, where the sampling pass, the thresholds
 // and the candidate lists cost more than they save.  Two launches: the tiled scan leaves, per query and group of rows
-// (the rows of a key tile), the best two products and a bound on all others; one workgroup per query finds the k-th
-// best of the groups' best and takes what reaches it, scoring a group again only when a third row of it might.
-// GroupPair as four words: bits of the second best product, bits of the bound, row of the best | row of the second
-// << 8 (within the group), 0.  A group without a (second) entry has -inf there.
+// (the rows of a wave, or of a key tile), the two best products and a bound on all others; one workgroup per query finds the
+// k-th best of the groups' best and takes what reaches it, scoring a group again only when a further row of it might.
+// A group's entry is four words: the second best product; the third best one or a bound on it; the places of these rows
+// in the tile, first | second << 8 | (third + 1) << 16, where 0 means that the third is only a bound; 0.  -inf where there is no row.
+//
+// What is not named is strictly worse than the second row if the third is a bound.  Where it could not be told from the
+// second (equal rows, most of all), the scan names the third as well, the rows taken in the order of the result: by
+// product, then by index.  So a group is scored again only if two rows of it are better than the k-th result, which is
+// at most k / 2 groups, however many rows are alike.  One thing is left: products a unit or two in the last place apart
+// can round to equal scores, and then the lower index wins.  WHOLE_NEAR says that such a row may be among those not named.
+constexpr uint32_t WHOLE_NEAR = 1u << 24;
 constexpr int WHOLE_MAX_GROUPS = 4096;      // a thread of the selecting workgroup (256) keeps 16 of them
 struct WholePlan {
     int32_t config, tk, tq, nqb, grid;
-    int32_t groups, group_rows, fine, run_shift;
+    int32_t groups, group_rows, fine;
     size_t off_best, off_pair, total;
 };
 
@@ -173,9 +180,8 @@ struct ScanArgs {
     int32_t keys_once;        // the launch reads keys that no cache holds and nobody reads again: see stream_keys
     // Whole-store plan (see WholePlan): the best two of every group of rows, nothing is filtered.  nullptr otherwise.
     float *whole_best;        // [Q][groups]: product of the best row of the group
-    u32x4 *whole_pair;        // [Q][groups]: see GroupPair
+    u32x4 *whole_pair;        // [Q][groups]: the rest of the group's entry
     int32_t whole_groups, whole_fine;       // fine: a group is the rows of one wave, not of the tile
-    int32_t whole_run_shift;                // see whole_row
 };
 
 // Key row behind row r of logical tile `tile` in a sampling pass.  With row_mul the sample is scattered in runs of
@@ -234,13 +240,20 @@ __device__ inline uint32_t sample_index(const ScanArgs &p, int64_t tile_run, int
 // `tiles` consecutive ones, and the rows of a run are a quarter (R = 4) of the tile apart.  Which one moves on by one or
 // two from place to place, so that the distance between a tile's runs is an odd number of them: at 2048 tiles of 128
 // rows a fixed place made it a power of two, and the scan took 120 us where 115 % of the rows took 131 (bf16, d = 1024).
-__host__ __device__ inline int64_t whole_row(int32_t tile, int32_t tiles, int tk, int shift, int pos)
+__host__ __device__ constexpr int whole_run_shift(int tk) { return tk >= 64 ? 2 : 0; }
+__host__ __device__ inline int64_t whole_row(int32_t tile, int32_t tiles, int tk, int pos)
 {
-    const int per = tk >> shift, j = pos & (per - 1);        // runs in a tile, which of them
+    const int shift = whole_run_shift(tk), per = tk >> shift, j = pos & (per - 1);        // runs in a tile, which of them
     int32_t t = tile + j * (2 - (tiles & 1 ? 0 : 1));
     if (tiles > 2 * 128) t -= t >= tiles ? tiles : 0;        // (j < 128)
     else t %= tiles;
     return (((int64_t)j * tiles + t) << shift) + (shift ? pos / per : 0);
+}
+// A number below tk that rises with the row at a place.
+template <int TK> __host__ __device__ inline uint32_t whole_order(uint32_t place)
+{
+    constexpr int SHIFT = whole_run_shift(TK);
+    return ((place << SHIFT) | (place / (uint32_t)(TK >> SHIFT))) & (uint32_t)(TK - 1);
 }
 
 // Where sample `slot` (= tile * groups + group) of query q lives.  The groups of one tile are adjacent (64 bytes per

@@ -24,7 +24,7 @@
 // the lane's rank, plain global store); the wave moves its records to the per-query lists itself.
 //
 // WHOLE (the whole-store plan, see WholePlan): one pass over everything, no filter; per query and group of rows the
-// best two products and a bound on the rest.  65,536 x 768 bf16 rows, 64 queries: 23.7 us, where the sampling pass,
+// two best products and the third or a bound on it.  65,536 x 768 bf16 rows, 64 queries: 23.7 us, where the sampling pass,
 // the thresholds and the filtered scan took 8.6 + 6.0 + 23.1; writing all products instead took 29.6.
 #pragma once
 #include <type_traits>
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
             if constexpr (SAMPLE) asm volatile("" : "+v"(r));
             if constexpr (SAMPLE) offA[j] = (uint64_t)sample_row(p, tile_run, ld_tile, TK, r) * key_row_bytes + ldA_piece;
             else if constexpr (WHOLE) {
-                const int64_t row = whole_row(ld_tile, (int32_t)p.n_tiles, TK, p.whole_run_shift, r);
+                const int64_t row = whole_row(ld_tile, (int32_t)p.n_tiles, TK, r);
                 offA[j] = (uint64_t)(row < p.n_keys ? row : p.n_keys - 1) * key_row_bytes + (SAME_SWZ_A ? ldA_piece : (uint32_t)((((wave * 64 + lane) % C::PPRA) ^ swizzle<C::PPRA>(r)) * 16));
             } else offA[j] = (uint32_t)(r < last ? r : last) * key_row_bytes + ldA_piece;
         }
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                     r = sample_row(p, sample_tile_run(p, tile, TK), tile, TK, rl);
                 }
                 if constexpr (WHOLE) {
-                    r = whole_row(tile, (int32_t)p.n_tiles, TK, p.whole_run_shift, tid);
+                    r = whole_row(tile, (int32_t)p.n_tiles, TK, tid);
                     r = r < p.n_keys ? r : p.n_keys - 1;
                 }
                 my_invk = p.inv_norm[r];
@@ -382,9 +382,9 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
         if (++c == NC) {
             // ---- epilogue of the item -----------------------------------------------------------
             // (the side-data buffers were last read in the previous epilogue, at least one barrier ago)
-            if constexpr (WHOLE) {          // (TK is a multiple of 64: whole waves)
+            if constexpr (WHOLE) {          // (a tile of 32 rows leaves the upper half of its one word zero)
                 if (tid < TK) {
-                    const uint64_t dead = __builtin_amdgcn_ballot_w64(row_removed(my_invk) || whole_row(tile, (int32_t)p.n_tiles, TK, p.whole_run_shift, tid) >= p.n_keys);
+                    const uint64_t dead = __builtin_amdgcn_ballot_w64(row_removed(my_invk) || whole_row(tile, (int32_t)p.n_tiles, TK, tid) >= p.n_keys);
                     if (lane == 0) reinterpret_cast<uint64_t *>(smem + C::OFF_DEAD)[wave] = dead;
                 }
             }
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 uint64_t dead = dead_map[wm * IB / 2];              // 64 rows a word
                 dead = IB == 1 ? (uint64_t)(uint32_t)(dead >> (32 * (wm & 1))) : dead;
                 const uint32_t dead_lo = __builtin_amdgcn_readfirstlane((uint32_t)dead), dead_hi = __builtin_amdgcn_readfirstlane((uint32_t)(dead >> 32));
-                whole_epilogue<IB, JB, C::WM, TQ>(acc, sd, filter, wm, rowB, half, tile, qb * TQ, p, (uint64_t)dead_hi << 32 | dead_lo,
+                whole_epilogue<TK, IB, JB, C::WM, TQ>(acc, sd, filter, wm, rowB, half, tile, qb * TQ, p, (uint64_t)dead_hi << 32 | dead_lo,
                                                   reinterpret_cast<u32x4 *>(smem + C::OFF_EXCHANGE));
             }
             else if (DRAW)

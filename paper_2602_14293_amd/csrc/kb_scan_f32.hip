@@ -33,7 +33,7 @@ template <int CB> __global__ __launch_bounds__(64) void kb_small_f32_kernel(Scan
         const int r = j * 8 + (lane >> 3), place = j < 2 ? r : r - 16;
         const uint32_t piece = (uint32_t)(((lane & 7) ^ swizzle<8>(place)) * 16);
         if (j < 2) {
-            const int64_t row = whole_row(tile, (int32_t)p.n_tiles, 16, 0, place);
+            const int64_t row = whole_row(tile, (int32_t)p.n_tiles, 16, place);
             src[j] = static_cast<const unsigned char *>(p.keys) + (size_t)(row < p.n_keys ? row : p.n_keys - 1) * row_bytes + piece;
         } else {
             src[j] = static_cast<const unsigned char *>(p.queries) + (size_t)(place < p.Q ? place : p.Q - 1) * row_bytes + piece;
@@ -54,7 +54,7 @@ template <int CB> __global__ __launch_bounds__(64) void kb_small_f32_kernel(Scan
     const bool filter = p.qmask != nullptr;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int64_t row = whole_row(tile, (int32_t)p.n_tiles, 16, 0, 4 * h + i);
+        const int64_t row = whole_row(tile, (int32_t)p.n_tiles, 16, 4 * h + i);
         live[i] = row < p.n_keys;
         const int64_t r = live[i] ? row : p.n_keys - 1;
         ik[i] = p.inv_norm[r];
@@ -92,26 +92,27 @@ template <int CB> __global__ __launch_bounds__(64) void kb_small_f32_kernel(Scan
     // lane (col, h) holds rows 4 h .. 4 h + 3 of query 16 b + col
 #pragma unroll
     for (int b = 0; b < CB; ++b) {
-        TopTwo t = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), 0u};
+        TopThree one[4], t = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), 0u};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const bool ok = live[i] && !row_removed(ik[i]) && (!filter || (tg[i] & qm[b]) != 0);
-            t = join(t, TopTwo{ok ? acc[b][i] * ik[i] : -__builtin_inff(), -__builtin_inff(), -__builtin_inff(), (uint32_t)(4 * h + i)});
+            one[i] = TopThree{ok ? acc[b][i] * ik[i] : -__builtin_inff(), -__builtin_inff(), -__builtin_inff(), (uint32_t)(4 * h + i)};
+            t = join(t, one[i]);
         }
 #pragma unroll
-        for (int o = 16; o < 64; o <<= 1) {
-            TopTwo x;
-            x.first = __shfl_xor(t.first, o, 64);
-            x.second = __shfl_xor(t.second, o, 64);
-            x.bound = __shfl_xor(t.bound, o, 64);
-            x.rows = (uint32_t)__shfl_xor((int)t.rows, o, 64);
-            t = join(t, x);
+        for (int o = 16; o < 64; o <<= 1) t = join(t, other_half(t, o));
+        if (__builtin_expect(unclear(t), 0)) {
+            t = one[0];
+#pragma unroll
+            for (int i = 1; i < 4; ++i) t = join_in_order<C::TK>(t, one[i]);
+#pragma unroll
+            for (int o = 16; o < 64; o <<= 1) t = join_in_order<C::TK>(t, other_half(t, o));
         }
         const int q = 16 * b + col;
         if (h == 0 && q < p.Q) {
             const size_t at = (size_t)q * p.whole_groups + tile;
             p.whole_best[at] = t.first;
-            p.whole_pair[at] = u32x4{as_u32(t.second), as_u32(t.bound), t.rows, 0u};
+            p.whole_pair[at] = u32x4{as_u32(t.second), as_u32(t.third), t.rows, 0u};
         }
     }
 }
