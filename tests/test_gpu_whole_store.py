@@ -113,10 +113,73 @@ def test_rows_that_tie_cost_no_more_than_the_pipeline(T, kind, dtype, N, d, Q, k
     kb.close()
 
 
-def test_replays_from_a_graph_and_less_memory(T):
+@pytest.mark.parametrize("dtype,N", [(torch.float32, 90000), (torch.bfloat16, 120001)])
+@pytest.mark.parametrize("spread,outliers", [(1e-2, (1.0,)), (1e-4, (-1.0,)), (1e-4, (1.0, 0.7)), (3e-6, (1.0, 0.601, -0.5)), (3e-6, (0.999,) * 9)])
+def test_scores_in_a_narrow_band(T, dtype, N, spread, outliers):
+    """Nearly all scores share a bin of the counting between the lowest and the highest, so the deciding bin is divided again,
+    up to three times (an outlier at 1, one just above the band, the band itself).  Its negative gives the lowest of all."""
+    g = torch.Generator().manual_seed(N + int(1e7 * spread) + len(outliers))
+    q = torch.nn.functional.normalize(torch.randn(64, generator=g, dtype=torch.float64), dim=0)
+    cosine = 0.6 + spread * torch.rand(N, generator=g, dtype=torch.float64)
+    cosine[torch.randperm(N, generator=g)[: len(outliers)]] = torch.tensor(outliers, dtype=torch.float64)
+    other = torch.randn((N, 64), generator=g, dtype=torch.float64)
+    other = torch.nn.functional.normalize(other - (other @ q)[:, None] * q, dim=1)
+    rows = (cosine[:, None] * q + (1 - cosine**2).clamp(min=0).sqrt()[:, None] * other).to(dtype)
+    w = W.Workload("band", rows, torch.stack([q, -q, 3 * q]).to(dtype), 10)
+    T.run_and_check(w, label=f"band {dtype} {spread} {outliers}")
+
+
+def _row_at(tile, tiles, tk, place):
+    """Row at a place of a tile: runs of four rows, dealt to the tiles in turn, the tile's run moving on from place to place."""
+    per = tk // 4
+    j = place % per
+    return ((j * tiles + (tile + j * (2 if tiles % 2 else 1)) % tiles) * 4) + place // per
+
+
+@pytest.mark.parametrize("kind,N,d,Q,tk", [("f32", 140000, 32, 5, 128), ("f32", 140100, 32, 5, 128), ("bf16", 140100, 64, 7, 128), ("bf16", 190001, 64, 70, 64),
+                                           ("bf16", 150000, 512, 66, 128), ("fp8", 200001, 64, 9, 128), ("f32", 60000, 32, 5, 128), ("bf16", 60001, 64, 40, 64)])
+@pytest.mark.parametrize("alike", ["falling", "equal", "rounding"])
+def test_best_rows_in_one_group(T, kind, N, d, Q, tk, alike):
+    """Seven of each query's best ten rows in one tile, in all four of its parts of 32 places where a group is a tile (more than 4096
+    groups of a wave's rows), else in one part: what the scan cannot name is found by scoring the group again.  Their scores fall,
+    are equal, or differ by the rounding of a factor only; some are removed, some do not pass the filter."""
+    tiles = -(-N // tk)
+    coarse = tiles * (tk // 32) > 4096
+    g = torch.Generator().manual_seed(N + Q)
+    unit = torch.nn.functional.normalize
+    rows, queries = unit(torch.randn((N, d), generator=g), dim=1), unit(torch.randn((Q, d), generator=g), dim=1)
+    tags = torch.ones(N, dtype=torch.int64)
+    removed = torch.zeros(N, dtype=torch.bool)
+    for r in range(Q):
+        places = [3, tk - 1, 40, tk // 2 + 5, 31, tk - 30, 17] if coarse else [3, 31, 17, 0, 9, 22, 14]
+        at = [_row_at(11 + 13 * r, tiles, tk, place) for place in places]
+        for i, row in enumerate(at):
+            if alike == "falling":
+                rows[row] = queries[r] + 0.05 * (i + 1) * rows[row]
+            else:
+                rows[row] = queries[r] * (1.0 if alike == "equal" else 1.0 + 0.37 * i)
+        if r % 2:
+            removed[at[r % 7]] = True
+        if r % 3 == 0:
+            tags[at[(r + 2) % 7]] = 2
+    rows, scale = kbmod.quantize_rows(rows.cuda()) if kind == "fp8" else (rows, None)
+    w = W.Workload("one group", rows.to({"f32": torch.float32, "bf16": torch.bfloat16}.get(kind, torch.float8_e4m3fn)).cpu(),
+                   queries.to(torch.float32 if kind == "f32" else torch.bfloat16), 10, scale=None if scale is None else scale.cpu(), tags=tags,
+                   qmask=torch.ones(Q, dtype=torch.int64))
+    kb = T.build_kb(w)
+    kb.remove(removed.nonzero()[:, 0].to(torch.int32).cuda())
+    gi, gs = T.gpu_query(kb, w)
+    assert kb.counters()["sample_keys"] == 0
+    T.check_against_oracle(w, gi, gs, label=f"{kind} {alike}", removed=removed.numpy(), min_strict=0.8 if alike == "falling" else None)
+    kb.set_tuning("small_path", 0)
+    pi, ps = T.gpu_query(kb, w)
+    assert (gi == pi).all() and (gs.view("int32") == ps.view("int32")).all()
+    kb.close()
+
+
+def test_replays_from_a_graph(T):
     w = W.filtered(seed=8, N=50001, d=128, Q=24, k=10, centers=32)
     kb = T.build_kb(w)
-    L = kbmod.lib()
     q, qm = w.queries.cuda().contiguous(), w.qmask.cuda()
     oi, os_ = torch.empty((w.Q, w.k), dtype=torch.int32, device="cuda"), torch.empty((w.Q, w.k), device="cuda")
     want = kb.query(q, w.k, qm)
@@ -130,18 +193,51 @@ def test_replays_from_a_graph_and_less_memory(T):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(oi, want[0]) and torch.equal(os_, want[1]), f"replay {rep}"
-    # a workspace that only the pipeline fits into
+    kb.close()
+
+
+def test_a_workspace_that_only_the_pipeline_fits_into(T):
+    w = W.clustered(seed=5, N=100000, d=128, Q=128, k=10, centers=64)
+    kb = T.build_kb(w)
+    L = kbmod.lib()
+    q = w.queries.cuda().contiguous()
+    want = kb.query(q, w.k)
     whole = L.kb_query_plan_bytes(kb._h, kb.size, w.Q, w.k, 0)
     kb.set_tuning("small_path", 0)
     pipeline = L.kb_query_plan_bytes(kb._h, kb.size, w.Q, w.k, 0)
     kb.set_tuning("small_path", 1)
-    for have in sorted((whole, pipeline)):
-        ws = torch.empty(have, dtype=torch.uint8, device="cuda")
+    assert pipeline < whole                          # or the sizes below say nothing
+    ws = torch.empty(whole, dtype=torch.uint8, device="cuda")
+    oi, os_ = torch.empty((w.Q, w.k), dtype=torch.int32, device="cuda"), torch.empty((w.Q, w.k), device="cuda")
+    counters = (ctypes.c_int64 * 4)()
+    for have, sampled in ((whole, False), (whole - 256, True), (pipeline, True)):
         oi.fill_(-7)
-        assert L.kb_query(kb._h, ctypes.c_void_p(q.data_ptr()), 1, w.Q, ctypes.c_void_p(qm.data_ptr()), w.k, ctypes.c_void_p(oi.data_ptr()),
-                          ctypes.c_void_p(os_.data_ptr()), ctypes.c_void_p(ws.data_ptr()), have, None) == (0 if have >= min(whole, pipeline) else 7)
-        torch.cuda.synchronize()
+        assert L.kb_query(kb._h, kbmod._ptr(q), kbmod.KB_BF16, w.Q, None, w.k, kbmod._ptr(oi), kbmod._ptr(os_), kbmod._ptr(ws), have, kbmod._stream()) == 0
+        assert L.kb_query_counters(kb._h, kbmod._ptr(ws), counters, kbmod._stream()) == 0        # (synchronises)
+        assert (counters[2] > 0) == sampled, have
         assert torch.equal(oi, want[0]) and torch.equal(os_, want[1])
+    oi.fill_(-7)
+    for have in (pipeline - 256, 256):
+        assert L.kb_query(kb._h, kbmod._ptr(q), kbmod.KB_BF16, w.Q, None, w.k, kbmod._ptr(oi), kbmod._ptr(os_), kbmod._ptr(ws), have, kbmod._stream()) == 7
+    torch.cuda.synchronize()
+    assert (oi == -7).all()
+    kb.close()
+
+
+def test_a_store_scored_in_parts_takes_the_lists_it_was_told(T):
+    w = W.tiny(seed=6, N=128, d=64, Q=1000, k=128)
+    kb = T.build_kb(w)
+    L = kbmod.lib()
+    q = w.queries.cuda().contiguous()
+    want = kb.query(q, w.k)
+    need = L.kb_query_plan_bytes(kb._h, kb.size, w.Q, w.k, 0)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    oi, os_ = torch.empty((w.Q, w.k), dtype=torch.int32, device="cuda"), torch.empty((w.Q, w.k), device="cuda")
+    for have, status in ((need - 256, 7), (need, 0)):
+        assert L.kb_query(kb._h, kbmod._ptr(q), kbmod.KB_F32, w.Q, None, w.k, kbmod._ptr(oi), kbmod._ptr(os_), kbmod._ptr(ws), have, kbmod._stream()) == status
+    torch.cuda.synchronize()
+    assert torch.equal(oi, want[0]) and torch.equal(os_, want[1])
+    T.check_against_oracle(w, oi.cpu().numpy(), os_.cpu().numpy(), label="parts")
     kb.close()
 
 
