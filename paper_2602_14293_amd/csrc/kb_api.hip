@@ -136,12 +136,19 @@ uint64_t scatter_multiplier(int64_t n)
 }
 
 // Whether a scan's key loads carry the non-temporal policy: the store does not fit the Infinity Cache (256 MiB), so the next
-// call will not find its rows there, and no second query block of this launch reads them.  A stream that leaves the
-// caches alone is the faster one: 1,000,003 x 1024 bf16 rows and one query 358 -> 321 us, 2^20 rows and 128 queries 425 ->
+// call will find too little of it there, and no second query block of this launch reads the rows again.  A stream that leaves
+// the caches alone is the faster one: 1,000,003 x 1024 bf16 rows and one query 358 -> 321 us, 2^20 rows and 128 queries 425 ->
 // 396, 256 queries 588 -> 570.  With a store that fits and is asked again it loses (100 MB and 64 queries 28.1 -> 29.2 us),
 // with two query blocks too (2,500,001 x 512 fp8 rows, 500 queries: 684 -> 708 us), and with half lines by a tenth.
-constexpr int64_t INFINITY_CACHE_BYTES = 256 << 20;
-bool stream_keys(const kb *h, int64_t n, int nqb) { return nqb == 1 && n * h->d * key_bytes(h->dtype) > INFINITY_CACHE_BYTES; }
+// Where the line lies, against cached loads, on one store asked again and again | on three in turn (bf16, 1024 elements):
+//   20 queries   260 MiB 1.06 | 0.91    288 MiB 1.00 | 0.93    320 MiB 0.91 | 0.92
+//   256 queries  260 MiB 1.07 | 0.98    288 MiB 1.00 | 0.98    320 MiB 0.99 | 0.97    (100, rows of 512: 1.07, 1.05, 1.00 | 1.00, 0.98, 0.98)
+// fp8 rows and few queries, where whole lines come with it: 0.96 | 0.82 at 260 MiB already.
+bool stream_keys(const kb *h, int64_t n, int32_t Q, int nqb)
+{
+    const int64_t limit = (int64_t)(Q > 32 ? 320 : h->dtype == KB_FP8_E4M3 ? 256 : 288) << 20;
+    return nqb == 1 && n * h->d * key_bytes(h->dtype) > limit;
+}
 
 // ------------------------------------------------------------------------------------------------
 // Planning: which kernels a query runs, how large its buffers are, where they live in the workspace.
@@ -166,7 +173,7 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
         const int generic8 = Q <= 64 ? FP8_QUERY_TILED_CONFIG : Q <= 128 ? FP8_QUERY_TILED_CONFIG + 1 : FP8_QUERY_TILED_CONFIG + 2;
         // large batches: the pipelined kernels (256-query blocks); smaller ones would pad their query columns there
         c.config = Q <= 128 ? generic8 : (row_bytes % 128 == 0 && row_bytes >= 512) ? FP8_QUERY_WIDE_CONFIG : FP8_QUERY_CONFIG;
-        if (Q <= 32 && whole_line_rows && stream_keys(h, n, 1)) c.config = FP8_QUERY_STREAM_CONFIG;
+        if (Q <= 32 && whole_line_rows && stream_keys(h, n, Q, 1)) c.config = FP8_QUERY_STREAM_CONFIG;
         if (is_fp8_query_config((int)h->tune_config)) c.config = (int)h->tune_config;         // another one can be asked for
         if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;
         // the weighted random selection exists in the tiled kernel only, and rows may be too short for a pipelined kernel
@@ -177,7 +184,7 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
         }
     } else {
         c.config = h->tune_config > 0 ? (int)h->tune_config : scan_config_for(h->dtype, Q, h->d, n);
-        if (h->tune_config == 0 && h->dtype == KB_FP8_E4M3 && Q <= 32 && whole_line_rows && stream_keys(h, n, 1)) c.config = FP8_STREAM_CONFIG;
+        if (h->tune_config == 0 && h->dtype == KB_FP8_E4M3 && Q <= 32 && whole_line_rows && stream_keys(h, n, Q, 1)) c.config = FP8_STREAM_CONFIG;
         if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;
         // fall back where a (forced) configuration does not apply: the weighted random selection exists in the
         // tiled kernel and in the main pass of the bf16 full-line kernel, rows may be too short for a pipelined kernel,
@@ -342,7 +349,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
     else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : n >= 128 * 2 * DEVICE_CUS && h->d >= 512 ? 21 : 16;    // (14: once every resident workgroup gets a tile)
     else p.config = Q <= 32 ? 1 : 2;
-    if (h->dtype == KB_FP8_E4M3 && Q <= 32 && h->d % 128 == 0 && stream_keys(h, n, 1)) p.config = q8 ? FP8_QUERY_STREAM_CONFIG : FP8_STREAM_CONFIG;
+    if (h->dtype == KB_FP8_E4M3 && Q <= 32 && h->d % 128 == 0 && stream_keys(h, n, Q, 1)) p.config = q8 ? FP8_QUERY_STREAM_CONFIG : FP8_STREAM_CONFIG;
     // tiles of 32 rows while those of 128 would leave compute units without one
     if (p.config == 1 && n <= WHOLE_SMALL_TILE_ROWS) p.config = h->dtype == KB_F32 ? SMALL_F32_CONFIG : 13;
     ConfigInfo ci;
@@ -1844,7 +1851,7 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     a.Q = Q;
     a.nqb = p.nqb;
     a.qpad = p.nqb * p.tq;
-    a.keys_once = stream_keys(h, h->n, p.nqb);
+    a.keys_once = stream_keys(h, h->n, Q, p.nqb);
     a.whole_best = reinterpret_cast<float *>(ws + p.off_best);
     a.whole_pair = reinterpret_cast<u32x4 *>(ws + p.off_pair);
     a.whole_groups = p.groups;
@@ -1892,7 +1899,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     if (!kb || Q < 1 || k < 1 || k > KB_K_MAX) return 0;
     // Every combination of kernels a query on this handle can run, each bounded over all row counts.  The choice depends on
     // the kind of query and, through two limits of which a handle's type and batch meet at most one, on the row count
-    // (WIDE128_MIN_ROWS for bf16 rows, the size of the Infinity Cache for fp8 rows): its two sides are those of 1 and of the capacity.
+    // (WIDE128_MIN_ROWS for bf16 rows, stream_keys for fp8 rows): its two sides are those of 1 and of the capacity.
     Sizes m;
     memset(&m, 0, sizeof m);
     bool any = false;
@@ -2040,7 +2047,7 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         while (p.sample_tiles > 0 && ((int64_t)p.sample_tiles << (a.sample_group_shift + 1)) <= p.sample_slots) ++a.sample_group_shift;
         a.region_cap = p.region_cap;
         a.draw = dr;
-        a.keys_once = stream_keys(kb, kb->n, p.nqb);
+        a.keys_once = stream_keys(kb, kb->n, Q, p.nqb);
         a.whole_best = nullptr;
         a.whole_pair = nullptr;
         a.whole_groups = a.whole_fine = 0;

@@ -244,9 +244,9 @@ def test_a_store_scored_in_parts_takes_the_lists_it_was_told(T):
 @pytest.mark.parametrize("kind,d,Q", [("bf16", 1024, 5), ("bf16", 1024, 70), ("bf16", 1024, 200), ("f32", 512, 3), ("fp8", 1024, 7),
                                       ("q8", 1024, 30), ("fp8", 1088, 2)])
 def test_stores_beyond_the_infinity_cache(T, kind, d, Q):
-    """Just over 256 MiB of keys: the loads' policy changes and fp8 rows of a multiple of 128 bytes go a line at a time.  Checked
-    against a plain product in double precision."""
-    N = (256 << 20) // (d * {"bf16": 2, "f32": 4}.get(kind, 1)) + 77
+    """Just over 320 MiB of keys: the loads' policy has changed for every batch and fp8 rows of a multiple of 128 bytes go a line at
+    a time.  Checked against a plain product in double precision."""
+    N = (320 << 20) // (d * {"bf16": 2, "f32": 4}.get(kind, 1)) + 77
     g = torch.Generator(device="cuda").manual_seed(d + Q)
     rows = torch.randn((N, d), generator=g, device="cuda")
     scale = None
