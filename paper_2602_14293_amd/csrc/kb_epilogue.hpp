@@ -419,39 +419,53 @@ __device__ inline TopThree whole_column(const f32x16 (&acc)[IB][JB], int jb, con
 }
 
 // The same with the first three in the order of the result: the elements are taken by rising row, one that is larger than
-// a place's moves in.  About 20 instructions an element, for the few columns where the search above leaves the third
-// unclear: one in ten thousand of a store without equal rows.
+// a place's moves in.  For the few columns where the search above leaves the third unclear, one in ten thousand of a store
+// without equal rows; so it is written for few registers (with those of a search over arrays, eight more to 64, calls of
+// 65 to 128 queries and of fp8 queries were 3 to 5 % slower).
 template <int TK, int IB, int JB>
 __device__ inline TopThree whole_column_in_order(const f32x16 (&acc)[IB][JB], int jb, const EpiSide &sd, bool filter, uint64_t qm, int wave_row0, int half,
                                                  uint64_t dead)
 {
     static_assert(TK == 128 || IB == 1, "order of the elements");
     constexpr float NONE = -__builtin_inff();
-    float v[IB][16];
-#pragma unroll
-    for (int ib = 0; ib < IB; ++ib) whole_products(acc[ib][jb], sd, filter, qm, wave_row0 + ib * 32 + 4 * half, half, ib, dead, NONE, v[ib]);
     TopThree t = {NONE, NONE, NONE, 0u};
-    uint32_t p1 = 0, p2 = 0, p3 = 0;
+    float below = NONE;         // the largest product below the third
+    int p1 = 0, p2 = 0, p3 = 0;
+    int rl0 = wave_row0 + 4 * half;
+    asm volatile("" : "+v"(rl0));       // (the products are formed again: kept from the search they would cost it registers)
+    uint32_t out_of_it = 0;     // bit ib * 16 + i: element i of block ib does not count
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib) {
+        const uint32_t d = (uint32_t)(dead >> (32 * ib)) >> (4 * half);
+        out_of_it |= ((d & 15u) | (d >> 4 & 0xf0u) | (d >> 8 & 0xf00u) | (d >> 12 & 0xf000u)) << (16 * ib);
+    }
+    if (filter) {
+#pragma unroll
+        for (int e = 0; e < 16 * IB; ++e) {
+            const uint64_t hit = sd.tag[rl0 + (e >> 4) * 32 + 8 * (e >> 2 & 3) + (e & 3)] & qm;
+            out_of_it |= hit != 0 ? 0u : 1u << e;
+            if (e % 4 == 3) asm volatile("" : "+v"(out_of_it));
+        }
+    }
 #pragma unroll
     for (int n = 0; n < 16 * IB; ++n) {
         // by rising whole_order: rows 32 places apart follow each other in a tile of 128, 16 places apart in one of 64
-        const int ib = TK == 64 ? 0 : n % IB, i = TK == 64 ? (n >> 1) | (n & 1) << 3 : n / IB;
-        const float f = v[ib][i];
-        const uint32_t place = (uint32_t)(wave_row0 + ib * 32 + 4 * half + 8 * (i >> 2) + (i & 3));
+        const int ib = TK == 64 ? 0 : n % IB, i = TK == 64 ? (n >> 1) | (n & 1) << 3 : n / IB, at = ib * 32 + 8 * (i >> 2) + (i & 3);
+        float f = acc[ib][jb][i] * sd.invk[rl0 + at];
+        f = (out_of_it >> (ib * 16 + i) & 1u) != 0 ? NONE : f;
         const bool g1 = f > t.first, g2 = f > t.second, g3 = f > t.third;
+        const float out = g3 ? t.third : f;
         t.third = g2 ? t.second : g3 ? f : t.third;
-        p3 = g2 ? p2 : g3 ? place : p3;
+        p3 = g2 ? p2 : g3 ? rl0 + at : p3;
         t.second = g1 ? t.first : g2 ? f : t.second;
-        p2 = g1 ? p1 : g2 ? place : p2;
+        p2 = g1 ? p1 : g2 ? rl0 + at : p2;
         t.first = g1 ? f : t.first;
-        p1 = g1 ? place : p1;
+        p1 = g1 ? rl0 + at : p1;
+        below = out < t.third ? __builtin_fmaxf(below, out) : below;
+        // (here and now: moved to the end, the places would keep the conditions of all elements, which spill)
+        if (n % 2 == 1) asm volatile("" : "+v"(p1), "+v"(p2), "+v"(p3), "+v"(below));
     }
-    uint32_t gap = ~0u;
-#pragma unroll
-    for (int ib = 0; ib < IB; ++ib)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) gap = least(gap, gap_below(t.third, v[ib][i]));
-    t.rows = p1 | p2 << 8 | (p3 + 1u) << 16 | (gap < 2u ? WHOLE_NEAR : 0u);
+    t.rows = (uint32_t)p1 | (uint32_t)p2 << 8 | (uint32_t)(p3 + 1) << 16 | (gap_below(t.third, below) < 2u ? WHOLE_NEAR : 0u);
     return t;
 }
 
