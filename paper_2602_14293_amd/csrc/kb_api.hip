@@ -1019,9 +1019,10 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
 // The k-th largest of the groups' best scores bounds the k-th best score from below (k distinct rows reach it).  It is
 // found by counting the best scores in equal bins between the smallest and the largest: scores near the top of a store
 // are sparse, so one pass of the counting leaves a handful of groups beyond the k wanted ones; only when many groups
-// share the deciding bin is that bin divided again.  Of the groups that reach the bound two or three rows are known.  If
-// a row that is not could reach it as well, the k-th best of all that are known is found, and groups where such a row
-// might come before that are scored again, with the instruction sequence of the scan: at most about k / 2 (see WholePlan).
+// share the deciding bin is that bin divided again.  Of the groups that reach the bound two or three rows are known.
+// Where a row that is not could reach it as well, the group is scored again, with the instruction sequence of the scan.  If
+// that is more than one step of the workgroup, the k-th best of all known rows is found first, and only groups
+// where such a row might come before that stay: at most about k / 2 (see WholePlan).
 // 16,384 equal bf16 rows of 1024 elements and 8 queries, where every group ties: 24 us a call; when every group whose third
 // row ties was scored again, 1502.  Everything that decides is a comparison of final scores, a non-decreasing function
 // of the products, or of candidate words, which order equal scores by index.
@@ -1210,10 +1211,22 @@ template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_
         if (j0 + (uint32_t)nt < listed) __syncthreads();         // (everyone has the count that the next step moves on)
     }
     const uint32_t asked = listed > 0 ? sh_again : 0u;
-    if (asked > 0) {
+    const uint32_t per = ((uint32_t)a.group_rows + 31) / 32;            // pieces of 32 rows, one a wavefront at a time
+    uint32_t tasks = asked * per;
+    const uint16_t *to_score = again;
+    if (tasks > (uint32_t)nw) {         // more than one step of the workgroup: it pays to look again (a single one takes as long)
         __syncthreads();
         if (tid == 0) sh_listed = 0;
-        cut(have);
+        if (have > (uint32_t)nt) {
+            cut(have);
+        } else {                    // few words: the one with k - 1 larger ones is the k-th
+            const uint64_t e = tid < (int)have ? buf[tid] : 0ull;
+            int rank = 0;
+#pragma unroll 8
+            for (int j = 0; j < (int)have; ++j) rank += buf[j] > e;
+            if (tid < (int)have && rank == k - 1) sh_thr = e;
+            __syncthreads();
+        }
         // those of which a row that is not known could come before the k-th of those that are
         for (uint32_t j = (uint32_t)tid; j < asked; j += (uint32_t)nt) {
             const uint32_t g = again[j];
@@ -1229,28 +1242,29 @@ template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_
         }
         __syncthreads();
         have = sh_cnt;
-        const uint32_t per = ((uint32_t)a.group_rows + 31) / 32, tasks = sh_listed * per;
-        for (uint32_t t0 = 0; t0 < tasks; t0 += (uint32_t)nw) {     // 32 rows a wavefront
-            __syncthreads();
-            if (have + 32 * (uint32_t)nw > (uint32_t)WHOLE_CAP) cut(have);
-            const uint32_t t = t0 + (uint32_t)wave;
-            if (t < tasks) {
-                const uint32_t g = list[t / per], in_group = t % per * 32, place0 = first_place(g) + in_group, known = pair[g][2];
-                const int lrow = lane & 31, half = lane >> 5;
-                const int64_t at = row_at(g, place0 + lrow), mine = at < a.n_keys ? at : a.n_keys - 1;      // (a place past a group of 16 is some other row)
-                const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, mine, q);
-                const float dot = select16(acc, lrow & 15);
-                const uint32_t rel = 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3), place = place0 + rel;
-                const int64_t row = row_at(g, place);
-                const bool listed_before = place == (known & 255u) || place == (known >> 8 & 255u) || place + 1u == (known >> 16 & 255u);
-                if (lrow < 16 && in_group + rel < (uint32_t)a.group_rows && row < a.n_keys && !listed_before) {
-                    const float ik = a.inv_norm[row];
-                    if (!row_removed(ik) && (!a.qmask || (a.tags[row] & qm) != 0)) append(dot * ik, (uint32_t)row);
-                }
+        tasks = sh_listed * per;
+        to_score = list;
+    }
+    for (uint32_t t0 = 0; t0 < tasks; t0 += (uint32_t)nw) {
+        __syncthreads();
+        if (have + 32 * (uint32_t)nw > (uint32_t)WHOLE_CAP) cut(have);
+        const uint32_t t = t0 + (uint32_t)wave;
+        if (t < tasks) {
+            const uint32_t g = to_score[t / per], in_group = t % per * 32, place0 = first_place(g) + in_group, known = pair[g][2];
+            const int lrow = lane & 31, half = lane >> 5;
+            const int64_t at = row_at(g, place0 + lrow), mine = at < a.n_keys ? at : a.n_keys - 1;      // (a place past a group of 16 is some other row)
+            const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, mine, q);
+            const float dot = select16(acc, lrow & 15);
+            const uint32_t rel = 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3), place = place0 + rel;
+            const int64_t row = row_at(g, place);
+            const bool listed_before = place == (known & 255u) || place == (known >> 8 & 255u) || place + 1u == (known >> 16 & 255u);
+            if (lrow < 16 && in_group + rel < (uint32_t)a.group_rows && row < a.n_keys && !listed_before) {
+                const float ik = a.inv_norm[row];
+                if (!row_removed(ik) && (!a.qmask || (a.tags[row] & qm) != 0)) append(dot * ik, (uint32_t)row);
             }
-            __syncthreads();
-            have = sh_cnt;
         }
+        __syncthreads();
+        have = sh_cnt;
     }
     // the result in order: few words place themselves by counting the larger ones, many are cut down first
     const int m = (int)have < k ? (int)have : k;

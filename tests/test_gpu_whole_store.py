@@ -139,10 +139,12 @@ def _row_at(tile, tiles, tk, place):
 @pytest.mark.parametrize("kind,N,d,Q,tk", [("f32", 140000, 32, 5, 128), ("f32", 140100, 32, 5, 128), ("bf16", 140100, 64, 7, 128), ("bf16", 190001, 64, 70, 64),
                                            ("bf16", 150000, 512, 66, 128), ("fp8", 200001, 64, 9, 128), ("f32", 60000, 32, 5, 128), ("bf16", 60001, 64, 40, 64)])
 @pytest.mark.parametrize("alike", ["falling", "equal", "rounding"])
-def test_best_rows_in_one_group(T, kind, N, d, Q, tk, alike):
+@pytest.mark.parametrize("groups,k", [(1, 10), (5, 40)])
+def test_best_rows_in_one_group(T, kind, N, d, Q, tk, alike, groups, k):
     """Seven of each query's best ten rows in one tile, in all four of its parts of 32 places where a group is a tile (more than 4096
     groups of a wave's rows), else in one part: what the scan cannot name is found by scoring the group again.  Their scores fall,
-    are equal, or differ by the rounding of a factor only; some are removed, some do not pass the filter."""
+    are equal, or differ by the rounding of a factor only; some are removed, some do not pass the filter.  Five such groups are
+    more than a step of the selecting workgroup: it first sees which of them it needs."""
     tiles = -(-N // tk)
     coarse = tiles * (tk // 32) > 4096
     g = torch.Generator().manual_seed(N + Q)
@@ -152,19 +154,20 @@ def test_best_rows_in_one_group(T, kind, N, d, Q, tk, alike):
     removed = torch.zeros(N, dtype=torch.bool)
     for r in range(Q):
         places = [3, tk - 1, 40, tk // 2 + 5, 31, tk - 30, 17] if coarse else [3, 31, 17, 0, 9, 22, 14]
-        at = [_row_at(11 + 13 * r, tiles, tk, place) for place in places]
+        at = [_row_at((11 + 13 * r + 1000 * j) % tiles, tiles, tk, place) for j in range(groups) for place in places]
+        at = [row for row in at if row < N]             # (a place of the last rows' runs can be past the end)
         for i, row in enumerate(at):
             if alike == "falling":
-                rows[row] = queries[r] + 0.05 * (i + 1) * rows[row]
+                rows[row] = queries[r] + 0.05 * (i % 7 + 1) * rows[row]
             else:
-                rows[row] = queries[r] * (1.0 if alike == "equal" else 1.0 + 0.37 * i)
+                rows[row] = queries[r] * (1.0 if alike == "equal" else 1.0 + 0.37 * i)       # (f32 and bf16 products that differ in the last places, if at all)
         if r % 2:
             removed[at[r % 7]] = True
         if r % 3 == 0:
             tags[at[(r + 2) % 7]] = 2
     rows, scale = kbmod.quantize_rows(rows.cuda()) if kind == "fp8" else (rows, None)
     w = W.Workload("one group", rows.to({"f32": torch.float32, "bf16": torch.bfloat16}.get(kind, torch.float8_e4m3fn)).cpu(),
-                   queries.to(torch.float32 if kind == "f32" else torch.bfloat16), 10, scale=None if scale is None else scale.cpu(), tags=tags,
+                   queries.to(torch.float32 if kind == "f32" else torch.bfloat16), k, scale=None if scale is None else scale.cpu(), tags=tags,
                    qmask=torch.ones(Q, dtype=torch.int64))
     kb = T.build_kb(w)
     kb.remove(removed.nonzero()[:, 0].to(torch.int32).cuda())
