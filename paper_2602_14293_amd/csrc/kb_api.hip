@@ -1483,8 +1483,8 @@ template <int KT> size_t probe_scan_lds() { return (size_t)PROBE_WAVES * ProbeRi
 // Block (p, s, q): part s of `splits` of the rows of cluster probe[q][p], scored exactly as the scan kernels score
 // (same MFMA sequence per element), best k written as a sorted list of candidate words (zero = no entry).
 // Every block computes 1/|q| of its query itself (one wavefront, the row-norm routine every path uses: the same bits),
-// which saves the launch that would do it once per query.  Such a call is bound by the latency of its loads: nearly a whole
-// row of each of the 32 keys of a wavefront is in flight at once.  8 queries, four clusters of about 1000 rows of 1024
+// which saves the launch that would do it once per query.  Such a call is bound by the latency of its loads: seven chunks
+// of 128 bytes of each of a wavefront's 32 rows are in flight at once (fp8: thirteen of 64).  8 queries, four clusters of about 1000 rows of 1024
 // bf16 values each (65 MB): 20.7 us, 32.7 us with fragments loaded to registers, a quarter of a row at a time and each
 // lane from a row of its own.
 template <int KT> __global__ __launch_bounds__(PROBE_THREADS) void probe_scan_kernel(FinalArgs a, const int64_t *cluster_offsets, int n_clusters,
