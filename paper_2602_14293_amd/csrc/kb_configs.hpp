@@ -28,7 +28,7 @@
     X(24, KB_FP8_Q8, 128, 32, 4, 1, 128, 3, 2)
 
 // ... of the whole-store plan only (it also takes those above with query blocks of up to 128, but for 2 of bf16).  13: the shortest scans, one wavefront
-// per workgroup with nearly a whole row of each of its 32 keys in flight at once.  14: some ten thousand rows and
+// per workgroup with eight chunks of 128 bytes of each of its 32 keys in flight at once (fp8: eleven of 64).  14: some ten thousand rows and
 // up to 64 queries, one tile per resident workgroup (65,536 x 768 keys: 23.7 us, 25.1 with config 12).  21: up to 128
 // queries, two tiles of 128 rows per compute unit and more (65,536 x 1024 keys, 128 queries: 39.6 us, 44.4 with config 16,
 // whose 64 rows meet twice as many query bytes; 196,000 rows 110 against 120; 16,384 rows 15.8 against 14.1, and with rows
