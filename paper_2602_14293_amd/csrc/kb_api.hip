@@ -65,9 +65,17 @@ bool scan_config_info(int key_dtype, int config, ConfigInfo *out)
     KB_SCAN_WIDE_CONFIGS_BF16(XW)
     KB_SCAN_WIDE_CONFIGS_FP8_Q8(XW)
 #undef XW
+#define XW(ID, KT, TQ)                                                        \
+    if (key_dtype == KT && config == ID) {                                    \
+        *out = ConfigInfo{256, TQ, 512, 8, 1, 256, 4};                        \
+        return true;                                                          \
+    }
+    KB_SCAN_WIDE_CONFIGS_FP8(XW)
+#undef XW
     return false;
 }
 
+constexpr int FP8_WIDE_CONFIG = 22;    // fp8 keys with bf16 queries: the full-line kernel (rows of a multiple of 128 bytes, 256 at least)
 constexpr int64_t WIDE128_MIN_ROWS = 4 * 65536;     // rows from which the 128-query full-line kernel is the faster one (measured: 2^18)
 
 int scan_config_for(int key_dtype, int Q, int d, int64_t n)
@@ -76,7 +84,7 @@ int scan_config_for(int key_dtype, int Q, int d, int64_t n)
     // 33 to 128 queries: the full-line kernel once a workgroup has several tiles to stream (its ring takes longer to fill)
     if (key_dtype == KB_BF16 && Q > 32 && d * 2 >= 512 && n >= WIDE128_MIN_ROWS) return 19;
     if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= 384) return 17;
-    if (key_dtype == KB_FP8_E4M3 && Q > 128 && d >= 256) return 4;
+    if (key_dtype == KB_FP8_E4M3 && Q > 128 && d >= 256) return d % 128 == 0 ? FP8_WIDE_CONFIG : 4;
     // below that size a query is bound by the latency of its launches: tiles of 64 rows (twice the workgroups, half the
     // chunks each) finish sooner: 62 against 71 us per call on 65,536 rows of 768 bf16 values with 64 queries
     // (and 64 against 70 us with 128 queries)
@@ -95,6 +103,7 @@ constexpr int MAX_CAND_CAP = 8192;     // finalize_kernel likewise
 constexpr int MIN_CAND_CAP = 1024;
 constexpr int FALLBACK_PARTS = 32;    // workgroups that share the rows of a query on the exhaustive path
 constexpr size_t WS_ALIGN = 256;
+constexpr int FP8_PIPELINED_CONFIG = 4;       // fp8 keys with bf16 queries, 64-byte row pieces
 constexpr int FP8_QUERY_CONFIG = 5;    // scan configuration of fp8 keys with fp8 queries (kb_configs.hpp)
 constexpr int FP8_QUERY_WIDE_CONFIG = 20;     // ... with 128-byte row pieces: rows of a multiple of 128 bytes, 512 at least
 constexpr int FP8_QUERY_TILED_CONFIG = 6;     // ... the tiled kernel: 6, 7, 8 for query blocks of 64, 128, 256; every row length
@@ -190,7 +199,7 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
         // tiled kernel and in the main pass of the bf16 full-line kernel, rows may be too short for a pipelined kernel,
         // and the fp8-query kernels read fp8 queries
         const bool draws = c.ci.family == 0 || (c.ci.family == 4 && h->dtype == KB_BF16);
-        if ((draw && !draws) || row_bytes < (size_t)c.ci.min_row_bytes || (!whole_line_rows && c.config == FP8_STREAM_CONFIG) || (h->dtype == KB_FP8_E4M3 && is_fp8_query_config(c.config))) {
+        if ((draw && !draws) || row_bytes < (size_t)c.ci.min_row_bytes || (!whole_line_rows && (c.config == FP8_STREAM_CONFIG || c.config == FP8_WIDE_CONFIG)) || (h->dtype == KB_FP8_E4M3 && is_fp8_query_config(c.config))) {
             c.config = generic;
             if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;
         }
@@ -198,7 +207,7 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
     c.sci = c.ci;
     c.sample_config = c.config;
     if (c.ci.family == 4 && h->dtype == KB_FP8_E4M3) {       // the fp8 full-line kernel is a main pass only
-        c.sample_config = FP8_QUERY_CONFIG;
+        c.sample_config = q8 ? FP8_QUERY_CONFIG : FP8_PIPELINED_CONFIG;
         if (!scan_config_info(h->dtype, c.sample_config, &c.sci) || c.sci.tq != c.ci.tq || c.sci.tk != c.ci.tk) return false;
     }
     if (draw && c.ci.family == 4) {     // so is the full-line kernel on keys: the tiled kernel with the same query blocks samples

@@ -60,3 +60,6 @@ constexpr int SMALL_F32_CONFIG = 15;
 // ... for fp8 keys with fp8 queries
 #define KB_SCAN_WIDE_CONFIGS_FP8_Q8(XW) \
     XW(20, KB_FP8_E4M3, 256)
+// ... for fp8 keys with bf16 queries: rows of a multiple of 128 elements, 256 at least
+#define KB_SCAN_WIDE_CONFIGS_FP8(XW) \
+    XW(22, KB_FP8_E4M3, 256)

@@ -78,6 +78,16 @@ __device__ inline uint32_t e4m3_pair_to_bf16(uint32_t word, bool upper)
     return __builtin_bit_cast(uint32_t, v);
 }
 
+// bytes 0-7 / 8-15 of a 16-byte run of e4m3 codes as eight bf16 values (exact: see e4m3_pair_to_bf16)
+__device__ inline u32x4 widen_e4m3_lo(u32x4 a)
+{
+    return u32x4{e4m3_pair_to_bf16(a.x, false), e4m3_pair_to_bf16(a.x, true), e4m3_pair_to_bf16(a.y, false), e4m3_pair_to_bf16(a.y, true)};
+}
+__device__ inline u32x4 widen_e4m3_hi(u32x4 a)
+{
+    return u32x4{e4m3_pair_to_bf16(a.z, false), e4m3_pair_to_bf16(a.z, true), e4m3_pair_to_bf16(a.w, false), e4m3_pair_to_bf16(a.w, true)};
+}
+
 template <> struct Mma<KB_FP8_E4M3> {
     struct PrepA {
         u32x4 lo, hi;
@@ -85,10 +95,8 @@ template <> struct Mma<KB_FP8_E4M3> {
     static __device__ inline PrepA prepare(u32x4 a)
     {
         PrepA p;
-        p.lo = u32x4{e4m3_pair_to_bf16(a.x, false), e4m3_pair_to_bf16(a.x, true), e4m3_pair_to_bf16(a.y, false),
-                     e4m3_pair_to_bf16(a.y, true)};
-        p.hi = u32x4{e4m3_pair_to_bf16(a.z, false), e4m3_pair_to_bf16(a.z, true), e4m3_pair_to_bf16(a.w, false),
-                     e4m3_pair_to_bf16(a.w, true)};
+        p.lo = widen_e4m3_lo(a);
+        p.hi = widen_e4m3_hi(a);
         return p;
     }
     static __device__ inline void run(f32x16 &acc, const PrepA &a, u32x4 b0, u32x4 b1)

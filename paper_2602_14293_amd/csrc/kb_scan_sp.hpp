@@ -37,16 +37,6 @@
 
 namespace kbi {
 
-// bytes 0-7 / 8-15 of a 16-byte run of e4m3 codes as eight bf16 values (exact: see e4m3_pair_to_bf16)
-__device__ inline u32x4 widen_e4m3_lo(u32x4 a)
-{
-    return u32x4{e4m3_pair_to_bf16(a.x, false), e4m3_pair_to_bf16(a.x, true), e4m3_pair_to_bf16(a.y, false), e4m3_pair_to_bf16(a.y, true)};
-}
-__device__ inline u32x4 widen_e4m3_hi(u32x4 a)
-{
-    return u32x4{e4m3_pair_to_bf16(a.z, false), e4m3_pair_to_bf16(a.z, true), e4m3_pair_to_bf16(a.w, false), e4m3_pair_to_bf16(a.w, true)};
-}
-
 template <int KT_, int TQ_, int NSA_, int NSB_, bool QF8_ = false, bool IL_ = false> struct SPCfg {
     static constexpr int KT = KT_, TQ = TQ_, NSA = NSA_, NSB = NSB_;       // query block; ring depths in chunks: keys, queries
     static constexpr bool QF8 = QF8_;                                      // fp8 keys AND fp8 queries: the fp8 matrix instruction

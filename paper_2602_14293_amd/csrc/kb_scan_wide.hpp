@@ -54,7 +54,8 @@ template <int KT_, int TQ_, bool QF8_ = false> struct WideCfg {
     static constexpr bool QF8 = QF8_;                                // fp8 keys AND fp8 queries: the fp8 matrix instruction
     static constexpr int TK = 256, TQ = TQ_, THREADS = 512, NW = 8;
     static constexpr int KEY_BYTES = KeyTraits<KT>::KEY_BYTES, QRY_BYTES = QF8 ? 1 : KeyTraits<KT>::QRY_BYTES;
-    static constexpr int RB = 128;                                   // bytes of a key / query row per d-chunk
+    static constexpr bool MIX = QRY_BYTES != KEY_BYTES;              // fp8 keys with bf16 queries: a key piece serves two query chunks
+    static constexpr int RB = 128;                                   // bytes of a query row per d-chunk, and of a key row per piece
     static constexpr int PIECE_ROWS = 128, PIECE_BYTES = PIECE_ROWS * RB;
     static constexpr int NB = TQ / PIECE_ROWS;                       // pieces of a query chunk
     static constexpr int NPB = 2 * NB, NPA = 9 - NPB;                // ring depth in pieces: queries (two chunks), keys (the rest)
@@ -77,8 +78,7 @@ template <int KT_, int TQ_, bool QF8_ = false> struct WideCfg {
     static constexpr int GROUPS_PER_TILE = 8;                // sampling groups: 2 pieces x 2 wave rows x 2 lane halves
     static constexpr int MIN_ROW_BYTES = 4 * RB;             // the key stream runs five pieces ahead of the MFMAs
     static constexpr int KS = QF8 ? 2 : 4;                           // k-steps per chunk: 32 bytes per lane and MFMA for fp8, 16 for bf16
-    static_assert(((KT == KB_BF16 && !QF8) || (KT == KB_FP8_E4M3 && QF8 && TQ == 256)) && KEY_BYTES == QRY_BYTES,
-                  "written for bf16 keys and queries, and for fp8 keys with fp8 queries in 256-query blocks");
+    static_assert((KT == KB_BF16 && !QF8) || (KT == KB_FP8_E4M3 && TQ == 256), "written for bf16 keys, and for fp8 keys in 256-query blocks");
     static_assert(TQ == 256 || TQ == 128, "query blocks of 256 or 128");
     static_assert(NPA % 2 == 1, "the parity of the piece a phase issues is fixed in the code");
     static_assert(SMEM_BYTES <= 160 * 1024, "LDS budget");
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
     // which looks at every element and needs the registers (a spilled register costs this kernel dearly: its
     // reload queues behind the stream loads in flight).
     const int my_items = SAMPLE ? ((int64_t)vb < n_items ? 1 : 0) : ((int64_t)vb < n_items ? (int)((n_items - vb + gridDim.x - 1) / gridDim.x) : 0);
-    const int NC = p.d * C::KEY_BYTES / RB;                    // chunks per item
+    const int NC = p.d * C::QRY_BYTES / RB;                    // chunks per item
     const int total = my_items * NC;                           // chunks of this workgroup
     const int phases = 2 * total;
     const uint32_t key_row_bytes = (uint32_t)p.d * C::KEY_BYTES, qry_row_bytes = (uint32_t)p.d * C::QRY_BYTES;
@@ -133,6 +133,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
     lds_u8 *const ld_ring0 = lds + (role == 0 ? 0 : C::OFF_B) + ridx * 1024;
     lds_u8 *ld_dst = ld_ring0;
     int ld_ring = 0;
+    const int ld_nc = C::MIX && role == 0 ? NC / 2 : NC;               // columns of pieces that an item has
     // [piece of the chunk][instruction]: bytes from the tile's (the query block's) first row; a sampling pass gathers
     // key rows from anywhere and counts in units of 16 bytes from the first key (the host scatters the sample only
     // when that fits 32 bits)
@@ -272,7 +273,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
         ld_dst = ld_ring0 + ld_ring * PB;
         if (more && h == 1) {
             ld_src += RB;
-            if (++ld_c == NC) item_next();
+            if (++ld_c == ld_nc) item_next();
         }
     };
     // role 1: load j (0..7) of the query chunk at the cursor: piece j / 4, instruction j % 4
@@ -285,18 +286,20 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
         ld_dst = ld_ring0 + ld_ring * PB;
         if (more) {
             ld_src += RB;
-            if (++ld_c == NC) item_next();
+            if (++ld_c == ld_nc) item_next();
         }
     };
 
     // ---- fragment addresses -------------------------------------------------------------------------------
     // piece-local row = 64 * (wave's half of the piece) + 32 * block + lrow; logical 16-byte slot of k-step kk = 2 kk + half
     // (kk << 5 only touches bits 5 and 6, a ring slot is a multiple of 16 KiB: the XOR can follow the addition)
-    constexpr bool F8 = C::QF8;
+    // MIX: the 16 key bytes of slot 4 (chunk & 1) + 2 kg + half widen to the operands of k-steps 2 kg and 2 kg + 1, whose queries are
+    // in slots 4 kg + 2 half and the next one
+    constexpr bool F8 = C::QF8, MIX = C::MIX;
     const int hslot = F8 ? 2 * half : half;                            // a lane's first 16-byte slot within a k-step
     const int baseA = (wm * 64 + lrow) * RB | ((hslot ^ swizzle<8>(lrow)) << 4);
     const int qrow = wn * (32 * JB) + lrow;                            // this lane's query in block 0 of the wave
-    const int baseB = C::OFF_B + (qrow / C::PIECE_ROWS) * PB + ((qrow % C::PIECE_ROWS) * RB | ((hslot ^ swizzle<8>(lrow)) << 4));
+    const int baseB = C::OFF_B + (qrow / C::PIECE_ROWS) * PB + ((qrow % C::PIECE_ROWS) * RB | (((MIX ? 2 * half : hslot) ^ swizzle<8>(lrow)) << 4));
     // bf16: 16 bytes of the row per lane and k-step (slot 2 kk + half); fp8: 32 bytes (slots 4 kk + 2 half, + 1)
     typedef int i32x8 __attribute__((ext_vector_type(8)));
     typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -307,9 +310,16 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
             v.lo = __builtin_bit_cast(i32x4, *(lds_u32x4 *)(lds + ((addr ^ (kk << 6)) + blk * 32 * RB)));
             v.hi = __builtin_bit_cast(i32x4, *(lds_u32x4 *)(lds + (((addr ^ (kk << 6)) ^ 16) + blk * 32 * RB)));
             return v;
+        } else if constexpr (MIX) {     // (queries)
+            return *(lds_u32x4 *)(lds + ((addr ^ ((kk & 2) << 5) ^ ((kk & 1) << 4)) + blk * 32 * RB));
         } else {
             return *(lds_u32x4 *)(lds + ((addr ^ (kk << 5)) + blk * 32 * RB));
         }
+    };
+    auto lo_half = [&](const u32x4 &codes) { Frag v{}; if constexpr (MIX) v = widen_e4m3_lo(codes); return v; };
+    auto hi_half = [&](const u32x4 &codes) { Frag v{}; if constexpr (MIX) v = widen_e4m3_hi(codes); return v; };
+    auto read_codes = [&](int addr, int odd_chunk, int kg, int blk) {        // MIX: the keys' codes of 32 elements
+        return *(lds_u32x4 *)(lds + ((addr ^ (odd_chunk << 6) ^ (kg << 5)) + blk * 32 * RB));
     };
 
     f32x16 acc[2][IB][JB];      // (never cleared: every item's first MFMAs start from zero)
@@ -330,7 +340,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
             else if constexpr (DRAW)
                 main_epilogue_draw<IB, JB>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
             else
-                main_epilogue<IB, JB, F8>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
+                main_epilogue<IB, JB, C::KEY_BYTES == 1>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
         }
     };
 
@@ -343,14 +353,20 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
         if (role == 0) {
             issue_tile_aux();
 #pragma unroll
-            for (int s = 0; s < C::NPA - 1; ++s) {
+            for (int s = 0; s < (MIX ? 3 : C::NPA - 1); ++s) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) key_issue(s & 1, j);
                 key_next(s & 1, true);
             }
-            key_issue(0, 0);
-            if (F8) key_issue(0, 1);                                   // (two loads per k-step there: two k-steps per phase)
-            __builtin_amdgcn_s_waitcnt(waitcnt_vm(4 * (C::NPA - 2) + (F8 ? 2 : 1)));   // piece 0 (and the side data before it) has landed
+            if constexpr (MIX) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j) key_issue(1, j);
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm(4 * 2 + 3));     // piece 0 (and the side data before it) has landed
+            } else {
+                key_issue(0, 0);
+                if (F8) key_issue(0, 1);                                   // (two loads per k-step there: two k-steps per phase)
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm(4 * (C::NPA - 2) + (F8 ? 2 : 1)));   // piece 0 (and the side data before it) has landed
+            }
         } else {
             issue_query_aux(vb % nqb);
 #pragma unroll
@@ -369,8 +385,16 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
         // key fragments of one k-step in two sets (one in use, one being refilled); the query fragments of all four
         // k-steps of the chunk stay in registers for its second phase
         Frag xa[IB], ya[IB], fb[C::KS][JB];
+        u32x4 codes[IB];                                       // MIX: of one k-group
 #pragma unroll
-        for (int ib = 0; ib < IB; ++ib) xa[ib] = read_f(baseA, 0, ib);
+        for (int ib = 0; ib < IB; ++ib) {
+            if constexpr (MIX) {
+                codes[ib] = read_codes(baseA, 0, 0, ib);
+                xa[ib] = widen_e4m3_lo(codes[ib]);
+            } else {
+                xa[ib] = read_f(baseA, 0, ib);
+            }
+        }
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb) fb[0][jb] = read_f(baseB, 0, jb);
 
@@ -530,8 +554,89 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
                     ++f;
                 }
             };
-            chunk(std::true_type{}, 0);
-            for (int c = 1; c < NC; ++c) chunk(std::false_type{}, c);
+            // MIX: two chunks on two key pieces, four phases (chunk, piece).  A phase's codes are in registers by its barrier; the second
+            // chunk's phases are the pieces' last.  Key waves issue two loads a phase: piece q + 5 into the slot that the barrier of
+            // piece q's last phase retires.
+            auto two_chunks = [&](auto first_c, int c) {
+                const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                const int rn1 = ra + 1 >= C::NPA ? ra + 1 - C::NPA : ra + 1, rn2 = ra + 2 >= C::NPA ? ra + 2 - C::NPA : ra + 2;
+                auto phase = [&](auto odd_c, auto rh_c) {
+                    constexpr int ODD = decltype(odd_c)::value, RH = decltype(rh_c)::value, PH = 2 * ODD + RH;
+                    constexpr bool FIRST = decltype(first_c)::value && ODD == 0;
+                    const int g = g0 + c + ODD;
+                    const bool more = g + 1 < total;
+                    int base_a = baseA, base_b = baseB;
+                    asm volatile("" : "+v"(base_a), "+v"(base_b));
+                    const int aa = base_a + (RH ? rn1 : ra) * PB, ab = base_b + rb * PB, abn = base_b + (more ? rb ^ C::NB : rb) * PB;
+                    // the next phase's piece (past the last one: the current one again, values unused)
+                    const int aan = base_a + (PH == 3 ? (more ? rn2 : ra) : RH ? ra : rn1) * PB;
+                    constexpr int ODDN = RH ? ODD ^ 1 : ODD;
+                    __builtin_amdgcn_s_setprio(1);
+#define KBW_MIX_KSTEP(KU, W, R0, R1, RC)               \
+    KBW_MFMA(RH, xa, KU, 0, 0);                        \
+    R0;                                                \
+    __builtin_amdgcn_sched_barrier(0);                 \
+    KBW_MFMA(RH, xa, KU, 0, 1);                        \
+    xa[0] = W(codes[0]);                               \
+    RC(0);                                             \
+    __builtin_amdgcn_sched_barrier(0);                 \
+    KBW_MFMA(RH, xa, KU, 1, 0);                        \
+    R1;                                                \
+    __builtin_amdgcn_sched_barrier(0);                 \
+    KBW_MFMA(RH, xa, KU, 1, 1);                        \
+    xa[1] = W(codes[1]);                               \
+    RC(1);                                             \
+    __builtin_amdgcn_sched_barrier(0)
+#define KBW_MIX_QUERIES(KR, AB) (fb[KR][0] = read_f(AB, KR, 0), fb[KR][1] = read_f(AB, KR, 1))
+#define KBW_MIX_GROUP1(IBLK) codes[IBLK] = read_codes(aa, ODD, 1, IBLK)
+#define KBW_MIX_GROUP0(IBLK) codes[IBLK] = read_codes(aan, ODDN, 0, IBLK)
+#define KBW_MIX_KEEP(IBLK) (void)0
+                    KBW_MIX_KSTEP(0, hi_half, if (RH == 0) KBW_MIX_QUERIES(1, ab), if (RH == 0) KBW_MIX_QUERIES(2, ab);
+                                  if (ROLE == 1) qry_issue(RH == 0 ? 5 : 1), KBW_MIX_GROUP1);
+                    KBW_MIX_KSTEP(1, lo_half, if (RH == 0) KBW_MIX_QUERIES(3, ab),
+                                  if (ROLE == 1) qry_issue(RH == 0 ? 6 : 2);
+                                  else {
+                                      key_issue(PH == 0 || PH == 3 ? 1 : 0, PH == 0 || PH == 2 ? 3 : 1);
+                                      if (PH == 0) key_next(1, g0 + c + 4 < total);
+                                      if (PH == 2) key_next(0, true);
+                                  }, KBW_MIX_KEEP);
+                    __builtin_amdgcn_s_setprio(0);
+                    if (ROLE == 0 && PH == 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm(8));
+                    if (ROLE == 0 && PH == 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm(10));
+                    if (ROLE == 1 && RH == 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(3));
+                    __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0());
+                    __builtin_amdgcn_sched_barrier(0);
+                    bare_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (ROLE == 1 && PH == 0 && nqb > 1 && c == 0 && g > 0) issue_query_aux(qb);
+                    if (ROLE == 0 && PH == 0 && ld_c == 0 && g0 + c + 4 < total) issue_tile_aux();
+                    __builtin_amdgcn_s_setprio(1);
+                    KBW_MIX_KSTEP(2, hi_half, if (RH == 1) KBW_MIX_QUERIES(0, abn),
+                                  if (ROLE == 1) { qry_issue(RH == 0 ? 7 : 3); if (RH == 0) qry_next(g + 2 < total); }, KBW_MIX_GROUP0);
+                    KBW_MIX_KSTEP(3, lo_half, KBW_NONE,
+                                  if (ROLE == 1) qry_issue(RH == 0 ? 0 : 4); else key_issue(PH == 0 || PH == 1 ? 0 : 1, PH == 0 || PH == 2 ? 0 : 2), KBW_MIX_KEEP);
+                    __builtin_amdgcn_s_setprio(0);
+#undef KBW_MIX_GROUP0
+#undef KBW_MIX_GROUP1
+#undef KBW_MIX_KEEP
+#undef KBW_MIX_KSTEP
+#undef KBW_MIX_QUERIES
+                };
+                phase(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+                phase(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+                rb ^= C::NB;
+                phase(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
+                phase(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
+                rb ^= C::NB;
+                ra = rn2;
+            };
+            if constexpr (MIX) {
+                two_chunks(std::true_type{}, 0);
+                for (int c = 2; c < NC; c += 2) two_chunks(std::false_type{}, c);
+            } else {
+                chunk(std::true_type{}, 0);
+                for (int c = 1; c < NC; ++c) chunk(std::false_type{}, c);
+            }
         };
 
         for (int it = 0; it < my_items; ++it) {
@@ -545,6 +650,12 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
                 // and rows): kept across the chunks these cost registers that end up spilled, and a reload
                 // queues behind the stream loads in flight.
                 int tile_e = tile, qb_e = qb, par_e = par, qrow_e = qrow, half_e = half;
+                if constexpr (MIX) {        // (not even these two have a register to themselves)
+                    int lane_e = threadIdx.x & 63;
+                    asm volatile("" : "+v"(lane_e));
+                    qrow_e = wn * (32 * JB) + (lane_e & 31);
+                    half_e = lane_e >> 5;
+                }
                 asm volatile("" : "+s"(tile_e), "+s"(qb_e), "+s"(par_e), "+v"(qrow_e), "+v"(half_e));
                 epilogue(tile_e, qb_e, par_e, qrow_e, half_e);
             }
@@ -584,7 +695,7 @@ template <class C> hipError_t launch_scan_wide_cfg(bool sample, int grid, const 
 {
     const bool draw = a.draw.enabled != 0;
     if (draw && sample) return hipErrorInvalidValue;                 // keys of the weighted random selection: main pass only
-    if constexpr (C::QF8) {      // fp8: the sampling pass runs the 64-byte-piece kernel (fewer registers)
+    if constexpr (C::KEY_BYTES == 1) {      // fp8: the sampling pass runs the 64-byte-piece kernel (fewer registers)
         return sample || draw ? hipErrorInvalidValue : launch_scan_wide_policy<C, false, false>(grid, a, s);
     } else {
         return sample ? launch_scan_wide_policy<C, true, false>(grid, a, s)
