@@ -47,6 +47,7 @@ bool scan_config_info(int key_dtype, int config, ConfigInfo *out)
         return true;                                                          \
     }
     KB_SCAN_CONFIGS_FP8_Q8(X)
+    KB_SCAN_DENSE_CONFIGS_FP8_Q8(X)
 #undef X
 #define XS(ID, KT, TQ, NSA, NSB)                                              \
     if (key_dtype == KT && config == ID) {                                    \
@@ -75,6 +76,7 @@ bool scan_config_info(int key_dtype, int config, ConfigInfo *out)
     return false;
 }
 
+constexpr int F32_SQUARE_CONFIG = 26;  // f32 rows: tiles of 64 x 64
 constexpr int FP8_WIDE_CONFIG = 22;    // fp8 keys with bf16 queries: the full-line kernel (rows of a multiple of 128 bytes, 256 at least)
 constexpr int64_t WIDE128_MIN_ROWS = 4 * 65536;     // rows from which the 128-query full-line kernel is the faster one (measured: 2^18)
 
@@ -89,6 +91,7 @@ int scan_config_for(int key_dtype, int Q, int d, int64_t n)
     // chunks each) finish sooner: 62 against 71 us per call on 65,536 rows of 768 bf16 values with 64 queries
     // (and 64 against 70 us with 128 queries)
     if (key_dtype == KB_BF16 && Q > 32 && Q <= 128 && n < WIDE128_MIN_ROWS) return Q <= 64 ? 12 : 16;
+    if (key_dtype == KB_F32 && Q > 32 && Q <= 64) return F32_SQUARE_CONFIG;
     return Q <= 32 ? 1 : Q <= 128 ? 2 : 3;
 }
 
@@ -109,12 +112,13 @@ constexpr int FP8_QUERY_WIDE_CONFIG = 20;     // ... with 128-byte row pieces: r
 constexpr int FP8_QUERY_TILED_CONFIG = 6;     // ... the tiled kernel: 6, 7, 8 for query blocks of 64, 128, 256; every row length
 constexpr int FP8_STREAM_CONFIG = 23;         // fp8 keys with bf16 queries: the tiled kernel with whole lines, up to 32 queries
 constexpr int FP8_QUERY_STREAM_CONFIG = 24;   // ... the tiled kernel with whole lines, up to 32 queries
+constexpr int FP8_QUERY_SMALL_CONFIG = 25;    // ... with tiles of 32 x 32, the dense plan
 bool is_fp8_query_config(int config)
 {
     return config == FP8_QUERY_CONFIG || config == FP8_QUERY_STREAM_CONFIG || config == FP8_QUERY_WIDE_CONFIG || (config >= FP8_QUERY_TILED_CONFIG && config <= FP8_QUERY_TILED_CONFIG + 2);
 }
 
-bool is_whole_config(int config) { return (config >= 13 && config <= 15) || config == 21; }      // no pipeline with a sampling pass runs them
+bool is_whole_config(int config) { return (config >= 13 && config <= 15) || config == 21 || config == FP8_QUERY_SMALL_CONFIG; }      // no pipeline with a sampling pass runs them
 
 int key_bytes(kb_dtype_t t) { return t == KB_F32 ? 4 : t == KB_BF16 ? 2 : 1; }
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -349,18 +353,36 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
 // for every resident workgroup 1.05 to 1.8 times as fast, with up to 32 queries still 1.0 to 1.3 times at five, with more
 // 0.9 to 1.05 times at four; at ten it loses (0.85 to 1.05).
 constexpr int64_t WHOLE_MAX_ROWS_FEW = 5 * 128 * 2 * DEVICE_CUS, WHOLE_MAX_ROWS = 3 * 128 * 2 * DEVICE_CUS;     // up to 32 queries; up to 128
+// More than 128 queries: every product costs the epilogue the same, while the pipeline's scan gets better with larger query
+// blocks and pays 30 us of latencies once.  Time of the pipeline over this plan's, k = 16, rows of 256 | 768 elements:
+//            just inside                                            outside
+//   bf16     65,536 x 256: 1.37 | 1.28    16,000 x 1024: 1.23 | 1.18    65,536 x 400: 0.96 | 0.89    131,072 x 160: 0.96 | 0.97
+//   fp8      65,536 x 512: 1.43 | 1.33    32,000 x 1024: 1.33 | 1.27    131,072 x 400: 0.99 | 0.99
+//   fp8 x 8  65,536 x 512: 1.84 | 1.16    131,072 x 256: 1.73 | 1.23    65,536 x 1024: 1.71 | 0.89   (rows of 256: no pipelined kernel)
+//   f32      65,536 x 1024: 1.14 | 1.16   131,072 x 512: 1.14 | 1.06    131,072 x 1024: 1.02 | 1.05
+constexpr int WHOLE_MAX_QUERIES = 4096;
+int64_t whole_max_rows(const kb *h, int32_t Q)
+{
+    if (Q <= 32) return WHOLE_MAX_ROWS_FEW;
+    const int64_t pairs = (int64_t)1 << (h->dtype == KB_BF16 ? 24 : h->dtype == KB_F32 ? 26 : 25);
+    return Q <= 128 ? WHOLE_MAX_ROWS : std::min(WHOLE_MAX_ROWS, pairs / Q);
+}
 constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
+double cubed(int32_t k) { return (double)k * k * k; }
 bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, WholePlan *out)
 {
     if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
-    if (n < 1 || Q > 128 || n > (Q > 32 ? WHOLE_MAX_ROWS : WHOLE_MAX_ROWS_FEW) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
+    if (n < 1 || Q > WHOLE_MAX_QUERIES || n > whole_max_rows(h, Q) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
     WholePlan p;
     if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
     else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : n >= 128 * 2 * DEVICE_CUS && h->d >= 512 ? 21 : 16;    // (14: once every resident workgroup gets a tile)
+    else if (h->dtype == KB_F32 && Q > 32) p.config = Q <= 64 || ceil_div(n, 128) * ceil_div(Q, 128) <= DEVICE_CUS ? F32_SQUARE_CONFIG : 2;
     else p.config = Q <= 32 ? 1 : 2;
     if (h->dtype == KB_FP8_E4M3 && Q <= 32 && h->d % 128 == 0 && stream_keys(h, n, Q, 1)) p.config = q8 ? FP8_QUERY_STREAM_CONFIG : FP8_STREAM_CONFIG;
-    // tiles of 32 rows while those of 128 would leave compute units without one
-    if (p.config == 1 && n <= WHOLE_SMALL_TILE_ROWS) p.config = h->dtype == KB_F32 ? SMALL_F32_CONFIG : 13;
+    // tiles of 32 rows while those of 128 would leave compute units without one; f32: of 16 while they run side by side (16,000 x
+    // 768 rows, 20 queries: 40 us, 27 with tiles of 64 x 64; at 8000 rows 25 against 26)
+    if (p.config == 1 && n <= WHOLE_SMALL_TILE_ROWS)
+        p.config = h->dtype != KB_F32 ? 13 : Q <= 16 || n <= WHOLE_SMALL_TILE_ROWS / 2 ? SMALL_F32_CONFIG : F32_SQUARE_CONFIG;
     ConfigInfo ci;
     if (!scan_config_info(h->dtype, p.config, &ci)) return false;
     p.tk = ci.tk;
@@ -373,14 +395,56 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     p.group_rows = p.fine ? fine_rows : ci.tk;
     static_assert(WHOLE_MAX_ROWS_FEW / 128 <= WHOLE_MAX_GROUPS && WHOLE_MAX_ROWS / 64 <= WHOLE_MAX_GROUPS, "whole tiles: 128 rows, or 64 with more than 32 queries");
     p.groups = (int32_t)(tiles * (ci.tk / p.group_rows));
-    // Groups with three of a query's k best are scored again, which costs a call some 5 us: k^3 / 6 / groups^2 of them if
-    // rows come in no order.  One in fifty queries is the limit.
-    if ((double)k * k * k > 0.12 * (double)p.groups * p.groups) return false;
+    // Groups with three of a query's k best are scored again, k^3 / 6 / groups^2 of them if rows come in no order.  Time of the
+    // pipeline over this plan's at k^3 / groups^2 of 4 (k = 100, 16,000 rows of 512 elements), 8 to 512 queries: 1.5 to 2.0 with
+    // bf16 rows, 1.1 to 1.9 with fp8, 1.1 to 1.6 with f32; at 8.4 (k = 128) 1.4 to 1.7, 0.8 to 1.8, 0.8 to 1.6.
+    if (cubed(k) > 4.0 * (double)p.groups * p.groups) return false;
     const int64_t items = tiles * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
     p.grid = (int32_t)(items < most ? items : most);
     p.off_best = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));       // the diagnostics come first, as always
     p.off_pair = p.off_best + align_up(sizeof(float) * (size_t)Q * p.groups);
     p.total = p.off_pair + align_up(sizeof(u32x4) * (size_t)Q * p.groups);
+    *out = p;
+    return true;
+}
+
+// The dense plan, where it applies.  Time in us of this plan | the whole-store plan | neither (1000 x 768 bf16 rows unless said):
+//   256 queries, k 8      14 | 23 | 192        k 32    14 | 36 | 194       k 128   17 |  -  | 200
+//   8 queries, k 128      16 |  -  | 28        4000 rows, 128 queries, k 32    16 | 24 | 37        f32, 64 queries, k 8   21 | 40 | 126
+//   8000 rows, 128 queries, k 8    21 | 18 | 32        k 32    22 | 22 | 34        k 128   26 | 49 | 43
+//   16,000 rows, 128 queries, k 8   28 | 19 | 33       k 32    29 | 25 | 35        k 128   33 | 34 | 52
+// (the weighted selection, 256 queries, k 32: 1000 rows 18 | - | 228, 16,000 rows 38 | - | 114).  At 16,000 rows and 1024 queries
+// it is level with the pipeline.
+constexpr int64_t DENSE_MAX_PAIRS = (int64_t)1 << 23;
+constexpr int64_t DENSE_FIRST_ROWS = 4096;                 // up to here the dense plan is never the slower one
+bool dense_is_better(int64_t n, int32_t k, const WholePlan &w) { return n <= DENSE_FIRST_ROWS || cubed(k) > 0.5 * (double)w.groups * w.groups; }
+bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, DensePlan *out)
+{
+    if (h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
+    if (n < 1 || n > DENSE_MAX_ROWS || n * Q > DENSE_MAX_PAIRS || (q8 && h->dtype != KB_FP8_E4M3)) return false;
+    DensePlan p;
+    // the smallest tiles while they all run at once; then those that read the rows and queries less often
+    // (f32, tiles of 16 x 32: two of them a compute unit; 2000 x 768 rows, 256 queries 39 us, 512 queries with tiles of 64 x 64 29)
+    const int64_t tiles32 = ceil_div(n, 32) * ceil_div(Q, 32);
+    const bool small = tiles32 <= (h->dtype == KB_F32 ? DEVICE_CUS : 2 * DEVICE_CUS);
+    if (q8) p.config = small ? FP8_QUERY_SMALL_CONFIG : Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
+    else if (h->dtype == KB_F32) p.config = small && !draw ? SMALL_F32_CONFIG : F32_SQUARE_CONFIG;
+    else if (h->dtype == KB_BF16) p.config = small ? 13 : Q <= 64 ? 12 : 16;
+    else p.config = small ? 13 : Q <= 32 ? 1 : 2;
+    ConfigInfo ci;
+    if (!scan_config_info(h->dtype, p.config, &ci)) return false;
+    p.tk = ci.tk;
+    p.tq = p.config == SMALL_F32_CONFIG && Q <= 16 ? 16 : ci.tq;
+    p.nqb = (int32_t)ceil_div(Q, p.tq);
+    const int64_t items = ceil_div(n, ci.tk) * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
+    p.grid = (int32_t)(items < most || p.config == SMALL_F32_CONFIG ? items : most);
+    p.stride = (int32_t)(ceil_div(n, 128) * 128);
+    p.off_values = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));       // the diagnostics come first, as always
+    p.off_invq = p.off_values + align_up(sizeof(float) * (size_t)Q * p.stride);
+    const int64_t qpad = (int64_t)p.nqb * p.tq;
+    p.off_lgain = p.off_invq + (draw ? align_up(sizeof(float) * qpad) : 0);
+    p.off_unused = p.off_lgain + (draw ? align_up(sizeof(float) * (ceil_div(n, 256) * 256 + 256)) : 0);
+    p.total = p.off_unused + (draw ? align_up((size_t)qpad * (2 * sizeof(uint64_t) + (3 + CAND_SEGMENTS) * sizeof(uint32_t))) : 0);    // (what prep_kernel writes for the pipeline)
     *out = p;
     return true;
 }
@@ -1053,86 +1117,66 @@ struct WholeSelectArgs {
 constexpr int WHOLE_THREADS = 256;
 constexpr int WHOLE_BINS = 256;          // four a lane of the wavefront that adds them up
 constexpr int WHOLE_CAP = 4096;         // words gathered before they are cut down to the best k
-constexpr int WHOLE_PER_THREAD = WHOLE_MAX_GROUPS / WHOLE_THREADS;
 
-template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_kernel(WholeSelectArgs a)
-{
-    constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
-    __shared__ __attribute__((aligned(16))) uint64_t buf[WHOLE_CAP];
-    __shared__ __attribute__((aligned(16))) uint32_t hist[WHOLE_BINS];
-    __shared__ uint16_t list[WHOLE_MAX_GROUPS], again[WHOLE_MAX_GROUPS];        // groups that reach the bound; with what is not known of them
-    __shared__ SelectScratch sc;
-    __shared__ float sh_iq, sh_lo[2][WHOLE_THREADS / 64], sh_hi[2][WHOLE_THREADS / 64];
-    __shared__ uint32_t sh_cnt, sh_bin, sh_above, sh_ge, sh_listed, sh_again;
-    __shared__ uint64_t sh_thr;
-    constexpr int nt = WHOLE_THREADS, nw = nt / 64;
-    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k = a.k, groups = a.groups;
-    constexpr float NONE = -__builtin_inff();
-    const float *best = a.best + (size_t)q * groups;
-    const u32x4 *pair = a.pair + (size_t)q * groups;
-    // this thread's groups: tid, tid + nt, ...; their loads go out first
-    const int rounds = (groups + nt - 1) / nt;
-    float v[WHOLE_PER_THREAD];
-#pragma unroll
-    for (int u = 0; u < WHOLE_PER_THREAD; ++u)
-        v[u] = u < rounds && tid + u * nt < groups ? best[tid + u * nt] : NONE;
-    const uint64_t qm = a.qmask ? a.qmask[q] : 0ull;
-    if (q == 0 && tid < STAT_WORDS + STAT_PARTIALS) a.stats[tid] = tid == 3 ? (uint64_t)a.grid : 0ull;
-    if (tid < 64) {
-        const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid);
-        if (tid == 0) {
-            sh_iq = inv;
-            sh_cnt = sh_listed = sh_again = 0;
-            sh_thr = 0;
-        }
+// The k-th largest of the values that the threads of a workgroup of 256 hold, as a bound from below: counted in equal bins
+// between the smallest and the largest value; only when many share the deciding bin is that bin divided again.
+// -inf stands for no value.
+struct KthBound {
+    float lo, hi, scale;
+    int bin_min;
+    bool all;                   // fewer than k values: no bound, every value counts
+    uint32_t reach;             // values that reach it (where `all` is not set: k at least)
+    __device__ int bin_of(float f) const        // (never falls as f grows)
+    {
+        const int b = (int)((f - lo) * scale);
+        return b < 0 ? 0 : b < WHOLE_BINS - 1 ? b : WHOLE_BINS - 1;
     }
-    for (int i = tid; i < WHOLE_BINS; i += nt) hist[i] = 0u;
-    __syncthreads();
-    const float iq = sh_iq;
+    __device__ bool passes(float f) const { return all || f > hi || (f >= lo && bin_of(f) >= bin_min); }
+};
+struct KthScratch {
+    __attribute__((aligned(16))) uint32_t hist[WHOLE_BINS];         // zero before the call, and after it
+    float lo[2][WHOLE_THREADS / 64], hi[2][WHOLE_THREADS / 64];
+    uint32_t bin, above, ge;
+};
+// v[u], u < rounds, are this thread's values (rounds uniform), lo and hi the smallest and largest of them.  All threads call it, converged.
+template <int PER> __device__ __forceinline__ KthBound bound_kth(const float (&v)[PER], int rounds, float lo, float hi, uint32_t need, KthScratch &sh)
+{
+    constexpr float NONE = -__builtin_inff();
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    KthBound r;
+    r.lo = lo;
+    r.hi = hi;
+    r.scale = 0.f;
+    r.bin_min = 0;
+    r.all = false;
+    r.reach = 0;
     // smallest and largest over the workgroup of what each thread has found (called converged, `turn` alternating)
     auto reduce_range = [&](float &lo, float &hi, int turn) {
         lo = wave_scan_min(lo);
         hi = wave_scan_max(hi);
         if (lane == 63) {
-            sh_lo[turn][wave] = lo;
-            sh_hi[turn][wave] = hi;
+            sh.lo[turn][wave] = lo;
+            sh.hi[turn][wave] = hi;
         }
         __syncthreads();
-        lo = sh_lo[turn][0];
-        hi = sh_hi[turn][0];
-        for (int w = 1; w < nw; ++w) {
-            lo = __builtin_fminf(lo, sh_lo[turn][w]);
-            hi = __builtin_fmaxf(hi, sh_hi[turn][w]);
+        lo = sh.lo[turn][0];
+        hi = sh.hi[turn][0];
+        for (int w = 1; w < WHOLE_THREADS / 64; ++w) {
+            lo = __builtin_fminf(lo, sh.lo[turn][w]);
+            hi = __builtin_fmaxf(hi, sh.hi[turn][w]);
         }
     };
-    float lo = __builtin_inff(), hi = NONE;
+    reduce_range(r.lo, r.hi, 0);
+#pragma unroll 1
+    for (int round = 0; round < 4 && r.hi >= r.lo; ++round) {
+        r.scale = r.hi > r.lo ? (float)WHOLE_BINS / (r.hi - r.lo) : 0.f;
+        if (!(r.scale < __builtin_inff())) r.scale = 0.f;
 #pragma unroll
-    for (int u = 0; u < WHOLE_PER_THREAD; ++u) {
-        if (v[u] > NONE) {
-            v[u] = v[u] * iq + 0.0f;
-            lo = __builtin_fminf(lo, v[u]);
-            hi = __builtin_fmaxf(hi, v[u]);
-        }
-    }
-    reduce_range(lo, hi, 0);
-    float scale = 0.f;
-    int bin_min = 0;
-    uint32_t need = (uint32_t)k;
-    bool all = false;           // fewer than k groups have an entry: no bound, every entry counts
-    auto bin_of = [&](float f) {        // (never falls as f grows)
-        const int b = (int)((f - lo) * scale);
-        return b < 0 ? 0 : b < WHOLE_BINS - 1 ? b : WHOLE_BINS - 1;
-    };
-    auto passes = [&](float f) { return all || f > hi || (f >= lo && bin_of(f) >= bin_min); };
-    for (int round = 0; round < 4 && hi >= lo; ++round) {
-        scale = hi > lo ? (float)WHOLE_BINS / (hi - lo) : 0.f;
-        if (!(scale < __builtin_inff())) scale = 0.f;
-#pragma unroll
-        for (int u = 0; u < WHOLE_PER_THREAD; ++u)
-            if (u < rounds && v[u] >= lo && v[u] <= hi) atomicAdd(&hist[bin_of(v[u])], 1u);
+        for (int u = 0; u < PER; ++u)
+            if (u < rounds && v[u] >= r.lo && v[u] <= r.hi) atomicAdd(&sh.hist[r.bin_of(v[u])], 1u);
         __syncthreads();
         if (tid < 64) {         // lane l owns bins 4 (63 - l) .. + 3: the scan over the lanes counts the higher bins
-            u32x4 *h = reinterpret_cast<u32x4 *>(hist) + (63 - lane);
+            u32x4 *h = reinterpret_cast<u32x4 *>(sh.hist) + (63 - lane);
             const u32x4 c = *h;
             *h = u32x4{0u, 0u, 0u, 0u};     // (for the next round)
             const uint32_t mine = c[0] + c[1] + c[2] + c[3];
@@ -1152,31 +1196,118 @@ template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_
                         above += c[j];
                     }
                 }
-                sh_bin = (uint32_t)b;
-                sh_above = above;
-                sh_ge = ge;
+                sh.bin = (uint32_t)b;
+                sh.above = above;
+                sh.ge = ge;
             }
         }
         __syncthreads();
-        bin_min = (int)sh_bin;
-        all = sh_ge < need;
-        if (sh_ge <= 256u + need || scale == 0.f) break;
-        // many groups share the deciding bin: its own range next
-        need -= sh_above;
+        r.bin_min = (int)sh.bin;
+        const uint32_t ge = sh.ge;
+        r.all = ge < need;
+        if (ge <= 256u + need || r.scale == 0.f) {
+            r.reach += ge;
+            break;
+        }
+        // many share the deciding bin: its own range next
+        need -= sh.above;
+        r.reach += sh.above;
         float lo2 = __builtin_inff(), hi2 = NONE;
 #pragma unroll
-        for (int u = 0; u < WHOLE_PER_THREAD; ++u) {
-            if (v[u] >= lo && v[u] <= hi && bin_of(v[u]) == bin_min) {
+        for (int u = 0; u < PER; ++u) {
+            if (v[u] >= r.lo && v[u] <= r.hi && r.bin_of(v[u]) == r.bin_min) {
                 lo2 = __builtin_fminf(lo2, v[u]);
                 hi2 = __builtin_fmaxf(hi2, v[u]);
             }
         }
         reduce_range(lo2, hi2, (round + 1) & 1);
-        lo = lo2;
-        hi = hi2;
-        scale = 0.f;
-        bin_min = 0;
+        if (round == 3) r.reach += ge - sh.above;
+        r.lo = lo2;
+        r.hi = hi2;
+        r.scale = 0.f;
+        r.bin_min = 0;
     }
+    return r;
+}
+
+// The best k of the `have` words of `buf`, in order, to a query's place in the output (256 threads, converged).
+__device__ __forceinline__ void write_best(uint64_t *buf, uint32_t have, int q, int k, int32_t *out_index, float *out_score, SelectScratch *sc)
+{
+    const int tid = threadIdx.x;
+    // the result in order: few words place themselves by counting the larger ones, many are cut down first
+    const int m = (int)have < k ? (int)have : k;
+    if (have <= 128u) {
+        if (tid < (int)have) {
+            const uint64_t e = buf[tid];
+            int rank = 0;
+#pragma unroll 8
+            for (int j = 0; j < (int)have; ++j) rank += buf[j] > e;
+            if (rank < k) {
+                out_index[(size_t)q * k + rank] = (int32_t)candidate_index(e);
+                out_score[(size_t)q * k + rank] = candidate_score(e);
+            }
+        }
+    } else {
+        __syncthreads();
+        select_topk_desc(buf, (int)have, k, sc, tid, WHOLE_THREADS);
+        if (tid < m) {
+            out_index[(size_t)q * k + tid] = (int32_t)candidate_index(buf[tid]);
+            out_score[(size_t)q * k + tid] = candidate_score(buf[tid]);
+        }
+    }
+    if (tid >= m && tid < k) {          // fewer than k qualify
+        out_index[(size_t)q * k + tid] = -1;
+        out_score[(size_t)q * k + tid] = -__builtin_inff();
+    }
+}
+
+// PER: groups a thread holds.  (The kernel is a few microseconds long: instructions that a small store skips are fetched all the same.)
+template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_kernel(WholeSelectArgs a)
+{
+    static_assert(PER * WHOLE_THREADS <= WHOLE_MAX_GROUPS);
+    constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
+    __shared__ __attribute__((aligned(16))) uint64_t buf[WHOLE_CAP];
+    __shared__ KthScratch kth;
+    __shared__ uint16_t list[WHOLE_MAX_GROUPS], again[WHOLE_MAX_GROUPS];        // groups that reach the bound; with what is not known of them
+    __shared__ SelectScratch sc;
+    __shared__ float sh_iq;
+    __shared__ uint32_t sh_cnt, sh_listed, sh_again;
+    __shared__ uint64_t sh_thr;
+    constexpr int nt = WHOLE_THREADS, nw = nt / 64;
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k = a.k, groups = a.groups;
+    constexpr float NONE = -__builtin_inff();
+    const float *best = a.best + (size_t)q * groups;
+    const u32x4 *pair = a.pair + (size_t)q * groups;
+    // this thread's groups: tid, tid + nt, ...; their loads go out first
+    const int rounds = (groups + nt - 1) / nt;
+    float v[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        v[u] = u < rounds && tid + u * nt < groups ? best[tid + u * nt] : NONE;
+    const uint64_t qm = a.qmask ? a.qmask[q] : 0ull;
+    if (q == 0 && tid < STAT_WORDS + STAT_PARTIALS) a.stats[tid] = tid == 3 ? (uint64_t)a.grid : 0ull;
+    if (tid < 64) {
+        const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid);
+        if (tid == 0) {
+            sh_iq = inv;
+            sh_cnt = sh_listed = sh_again = 0;
+            sh_thr = 0;
+        }
+    }
+    for (int i = tid; i < WHOLE_BINS; i += nt) kth.hist[i] = 0u;
+    __syncthreads();
+    const float iq = sh_iq;
+    float lo = __builtin_inff(), hi = NONE;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (v[u] > NONE) {
+            v[u] = v[u] * iq + 0.0f;
+            lo = __builtin_fminf(lo, v[u]);
+            hi = __builtin_fmaxf(hi, v[u]);
+        }
+    }
+    const KthBound bound = bound_kth(v, rounds, lo, hi, (uint32_t)k, kth);
+    auto passes = [&](float f) { return bound.passes(f); };
 
     // row at a place of the tile of group g (the groups of a tile follow each other)
     const uint32_t per_tile = (uint32_t)a.tile_rows / (uint32_t)a.group_rows;
@@ -1198,7 +1329,7 @@ template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_
         __syncthreads();
     };
 #pragma unroll
-    for (int u = 0; u < WHOLE_PER_THREAD; ++u)
+    for (int u = 0; u < PER; ++u)
         if (u < rounds && v[u] > NONE && passes(v[u])) list[atomicAdd(&sh_listed, 1u)] = (uint16_t)(tid + u * nt);
     __syncthreads();
     const uint32_t listed = sh_listed;
@@ -1275,31 +1406,96 @@ template <int KT> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_
         __syncthreads();
         have = sh_cnt;
     }
-    // the result in order: few words place themselves by counting the larger ones, many are cut down first
-    const int m = (int)have < k ? (int)have : k;
-    if (have <= 128u) {
-        if (tid < (int)have) {
-            const uint64_t e = buf[tid];
-            int rank = 0;
-#pragma unroll 8
-            for (int j = 0; j < (int)have; ++j) rank += buf[j] > e;
-            if (rank < k) {
-                a.out_index[(size_t)q * k + rank] = (int32_t)candidate_index(e);
-                a.out_score[(size_t)q * k + rank] = candidate_score(e);
-            }
+    write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
+}
+
+// Dense plan, second launch: one workgroup per query selects from the products (KEYS: the keys of the weighted selection)
+// of all rows.  PIECES: four values each that a thread holds.
+struct DenseSelectArgs {
+    const float *values;        // ScanArgs::dense
+    const void *queries;
+    int32_t *out_index;
+    float *out_score;
+    uint64_t *stats;
+    int32_t k, d, n, stride, grid;
+};
+template <int QT, bool KEYS, int PIECES> __global__ __launch_bounds__(DENSE_THREADS) void dense_select_kernel(DenseSelectArgs a)
+{
+    static_assert(DENSE_THREADS == WHOLE_THREADS && PIECES * 4 * DENSE_THREADS <= DENSE_MAX_ROWS);
+    constexpr int PER = 4 * PIECES;
+    constexpr float NONE = -__builtin_inff();
+    __shared__ __attribute__((aligned(16))) uint64_t buf[WHOLE_CAP];
+    __shared__ KthScratch kth;
+    __shared__ SelectScratch sc;
+    __shared__ float sh_iq;
+    __shared__ uint32_t sh_cnt;
+    __shared__ uint64_t sh_thr;
+    const int q = blockIdx.x, tid = threadIdx.x, k = a.k;
+    const f32x4 *values = reinterpret_cast<const f32x4 *>(a.values + (size_t)q * a.stride);
+    const int pieces = (a.n + 3) / 4, rounds = (pieces + DENSE_THREADS - 1) / DENSE_THREADS;      // (rounds <= PIECES; the scan has filled the last piece)
+    float v[PER];
+#pragma unroll
+    for (int u = 0; u < PIECES; ++u) {
+        const f32x4 x = tid + u * DENSE_THREADS < pieces ? values[tid + u * DENSE_THREADS] : f32x4{NONE, NONE, NONE, NONE};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * u + e] = x[e];
+    }
+    if (q == 0 && tid < STAT_WORDS + STAT_PARTIALS) a.stats[tid] = tid == 3 ? (uint64_t)a.grid : 0ull;
+    if (!KEYS && tid < 64) {
+        const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid);
+        if (tid == 0) sh_iq = inv;
+    }
+    if (tid == 0) {
+        sh_cnt = 0;
+        sh_thr = 0;
+    }
+    for (int i = tid; i < WHOLE_BINS; i += DENSE_THREADS) kth.hist[i] = 0u;
+    __syncthreads();
+    const float iq = KEYS ? 0.f : sh_iq;
+    float lo = __builtin_inff(), hi = NONE;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (v[u] > NONE) {
+            if (!KEYS) v[u] = v[u] * iq + 0.0f;
+            lo = __builtin_fminf(lo, v[u]);
+            hi = __builtin_fmaxf(hi, v[u]);
         }
-    } else {
+    }
+    const KthBound bound = bound_kth(v, 4 * rounds, lo, hi, (uint32_t)k, kth);
+    // the rows that reach it
+    uint32_t have = 0;
+    if (bound.reach <= (uint32_t)WHOLE_CAP) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (u < 4 * rounds && v[u] > NONE && bound.passes(v[u]))
+                buf[atomicAdd(&sh_cnt, 1u)] = pack_candidate(v[u], (uint32_t)(4 * (tid + u / 4 * DENSE_THREADS) + u % 4));
         __syncthreads();
-        select_topk_desc(buf, (int)have, k, &sc, tid, nt);
-        if (tid < m) {
-            a.out_index[(size_t)q * k + tid] = (int32_t)candidate_index(buf[tid]);
-            a.out_score[(size_t)q * k + tid] = candidate_score(buf[tid]);
+        have = sh_cnt;
+    } else {        // equal values, most of all: read again, the buffer cut down to the best k whenever it is full
+        for (int u = 0; u < rounds; ++u) {
+            if (have + 4 * DENSE_THREADS > (uint32_t)WHOLE_CAP) {
+                select_topk_desc(buf, (int)have, k, &sc, tid, DENSE_THREADS);
+                if (tid == 0) {
+                    sh_cnt = have < (uint32_t)k ? have : (uint32_t)k;
+                    sh_thr = have >= (uint32_t)k ? buf[k - 1] : 0ull;
+                }
+                __syncthreads();
+            }
+            const int piece = tid + u * DENSE_THREADS;
+            const f32x4 x = piece < pieces ? values[piece] : f32x4{NONE, NONE, NONE, NONE};
+            const float val[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float w = KEYS || !(val[e] > NONE) ? val[e] : val[e] * sh_iq + 0.0f;
+                const uint64_t cw = pack_candidate(w, (uint32_t)(4 * piece + e));
+                if (w > NONE && bound.passes(w) && cw > sh_thr) buf[atomicAdd(&sh_cnt, 1u)] = cw;
+            }
+            __syncthreads();
+            have = sh_cnt;
+            __syncthreads();
         }
     }
-    if (tid >= m && tid < k) {          // fewer than k qualify
-        a.out_index[(size_t)q * k + tid] = -1;
-        a.out_score[(size_t)q * k + tid] = NONE;
-    }
+    write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
 }
 
 template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalArgs a)
@@ -1630,6 +1826,16 @@ template <int KT> hipError_t launch_probe_scan(const dim3 &grid, const FinalArgs
     hipLaunchKernelGGL(probe_scan_kernel<KT>, grid, dim3(PROBE_THREADS), probe_scan_lds<KT>(), s, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists);
     return hipGetLastError();
 }
+template <int KT> auto whole_select(int groups) -> void (*)(WholeSelectArgs)
+{
+    return groups <= 4 * WHOLE_THREADS ? &whole_select_kernel<KT, 4> : groups <= 8 * WHOLE_THREADS ? &whole_select_kernel<KT, 8> : &whole_select_kernel<KT, 16>;
+}
+template <int QT, bool KEYS> void launch_dense_select(const DenseSelectArgs &t, int32_t Q, hipStream_t s)
+{
+    void (*fn)(DenseSelectArgs) = t.n <= 4096 ? &dense_select_kernel<QT, KEYS, 4> : t.n <= 8192 ? &dense_select_kernel<QT, KEYS, 8> : &dense_select_kernel<QT, KEYS, 16>;
+    hipLaunchKernelGGL(fn, dim3(Q), dim3(DENSE_THREADS), 0, s, t);
+}
+
 hipError_t launch_scan(kb_dtype_t dt, int config, int family, bool sample, int grid, const ScanArgs &a, hipStream_t s)
 {
     if (family == 4)
@@ -1856,6 +2062,18 @@ SmallPlan make_small_plan(int32_t Q, int32_t k, int parts)
     return p;
 }
 
+// query norms, counters and (weighted random selection) ln(gain)
+void launch_prep(const void *queries_dev, kb_dtype_t q_dtype, int32_t Q, int32_t qpad, int32_t d, float *invq, uint64_t *thr64, float *thrp, uint32_t *cnt,
+                 uint32_t *flag, uint64_t *stats, uint64_t sample_keys, const uint64_t *qmask_dev, uint64_t *qmask_pad, int32_t grid, uint32_t *fb_done,
+                 const GainArgs &ga, hipStream_t s)
+{
+    const int n_init = qpad > STAT_WORDS + STAT_PARTIALS ? qpad : STAT_WORDS + STAT_PARTIALS;
+    const int blocks_rows = (int)ceil_div(qpad, 4), blocks_init = (int)ceil_div(n_init, 256);
+    const unsigned blocks = (blocks_rows > blocks_init ? blocks_rows : blocks_init) + ga.blocks;
+    auto *fn = q_dtype == KB_F32 ? &prep_kernel<KB_F32> : q_dtype == KB_FP8_E4M3 ? &prep_kernel<KB_FP8_E4M3> : &prep_kernel<KB_BF16>;
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(256), 0, s, queries_dev, Q, qpad, d, invq, thr64, thrp, cnt, flag, stats, sample_keys, qmask_dev, qmask_pad, grid, fb_done, ga);
+}
+
 // kb_query by the whole-store plan: two launches.
 kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k,
                          int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
@@ -1909,9 +2127,71 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     t.tiles = (int32_t)a.n_tiles;
     t.grid = p.grid;
     const int kt = q8 ? KT_FP8_Q8 : (int)h->dtype;
-    void (*fn)(WholeSelectArgs) = kt == KB_F32 ? &whole_select_kernel<KB_F32> : kt == KB_BF16 ? &whole_select_kernel<KB_BF16>
-                                : kt == KB_FP8_E4M3 ? &whole_select_kernel<KB_FP8_E4M3> : &whole_select_kernel<KT_FP8_Q8>;
+    auto *fn = kt == KB_F32 ? whole_select<KB_F32>(p.groups) : kt == KB_BF16 ? whole_select<KB_BF16>(p.groups)
+             : kt == KB_FP8_E4M3 ? whole_select<KB_FP8_E4M3>(p.groups) : whole_select<KT_FP8_Q8>(p.groups);
     hipLaunchKernelGGL(fn, dim3(Q), dim3(WHOLE_THREADS), 0, s, t);
+    return hipGetLastError() == hipSuccess ? KB_OK : KB_ERR_DEVICE;
+}
+
+// kb_query and kb_query_sampled by the dense plan: two launches, three with the weighted selection (its scan needs 1/|q| and ln(gain)).
+kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_dtype_t q_dtype, int32_t Q, const uint64_t *qmask_dev, int32_t k,
+                         DrawArgs dr, GainArgs ga, int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
+{
+    ScanArgs a;
+    memset(&a, 0, sizeof a);
+    a.keys = h->keys;
+    a.inv_norm = h->inv_norm;
+    a.tags = qmask_dev ? h->tags : nullptr;
+    a.queries = queries_dev;
+    a.qmask = qmask_dev;
+    a.n_keys = h->n;
+    a.n_tiles = ceil_div(h->n, p.tk);
+    a.tile_stride = 1;
+    a.d = h->d;
+    a.Q = Q;
+    a.nqb = p.nqb;
+    a.qpad = p.nqb * p.tq;
+    a.dense = reinterpret_cast<float *>(ws + p.off_values);
+    a.dense_stride = p.stride;
+    uint64_t *stats = reinterpret_cast<uint64_t *>(ws);
+    if (dr.enabled) {
+        float *invq = reinterpret_cast<float *>(ws + p.off_invq);
+        uint64_t *u64 = reinterpret_cast<uint64_t *>(ws + p.off_unused);
+        float *thrp = reinterpret_cast<float *>(u64 + 2 * (size_t)a.qpad);
+        uint32_t *u32 = reinterpret_cast<uint32_t *>(thrp + a.qpad);
+        ga.log_gain = reinterpret_cast<float *>(ws + p.off_lgain);
+        dr.log_gain = ga.log_gain;
+        a.invq = invq;
+        a.draw = dr;
+        launch_prep(queries_dev, q_dtype, Q, a.qpad, h->d, invq, u64, thrp, u32, u32 + (size_t)a.qpad * CAND_SEGMENTS, stats, 0, qmask_dev, u64 + a.qpad, p.grid,
+                    u32 + (size_t)a.qpad * (CAND_SEGMENTS + 1), ga, s);
+        if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
+    }
+    const bool timed = h->prof_events && h->prof_used < h->prof_max && h->prof_seen++ % h->prof_stride == h->prof_stride / 2;
+    if (timed) {
+        scan_timing.start = h->prof_events[2 * h->prof_used];
+        scan_timing.stop = h->prof_events[2 * h->prof_used + 1];
+    }
+    const hipError_t launched = launch_scan(h->dtype, p.config, 0, false, p.grid, a, s);
+    scan_timing = ScanTiming();
+    if (launched != hipSuccess) return KB_ERR_DEVICE;
+    if (timed) ++h->prof_used;
+
+    DenseSelectArgs t;
+    t.values = a.dense;
+    t.queries = queries_dev;
+    t.out_index = indices_out_dev;
+    t.out_score = scores_out_dev;
+    t.stats = stats;
+    t.k = k;
+    t.d = h->d;
+    t.n = (int32_t)h->n;
+    t.stride = p.stride;
+    t.grid = p.grid;
+    if (dr.enabled) launch_dense_select<KB_F32, true>(t, Q, s);        // (the keys are finished)
+    else if (q_dtype == KB_F32) launch_dense_select<KB_F32, false>(t, Q, s);
+    else if (q_dtype == KB_BF16) launch_dense_select<KB_BF16, false>(t, Q, s);
+    else launch_dense_select<KB_FP8_E4M3, false>(t, Q, s);
     return hipGetLastError() == hipSuccess ? KB_OK : KB_ERR_DEVICE;
 }
 
@@ -1942,21 +2222,32 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     const int64_t parts = std::min<int64_t>({PROBE_MAX, SMALL_BLOCKS / Q, ceil_div(kb->capacity, 128)});
     if (parts > 0) total = std::max(total, make_small_plan(Q, k, (int)parts).total);
     // the whole-store plan: grows with its groups, so with the rows up to where the groups get coarser and to the most it takes
-    const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, WHOLE_MAX_GROUPS * 32, WHOLE_MAX_GROUPS * 64, WHOLE_MAX_ROWS, WHOLE_MAX_ROWS_FEW};
+    const int64_t whole_rows = std::min(kb->capacity, whole_max_rows(kb, Q));
+    const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, WHOLE_MAX_GROUPS * 32, WHOLE_MAX_GROUPS * 64, whole_rows};
     for (int64_t n : most)
         for (int q8 = 0; q8 < 2; ++q8) {
             WholePlan wp;
-            if (make_whole_plan(kb, std::min(n, kb->capacity), Q, k, false, q8 != 0, &wp)) total = std::max(total, wp.total);
+            if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, &wp)) total = std::max(total, wp.total);
         }
+    // the dense plan: grows with the rows
+    for (int kind = 0; kind < 4; ++kind) {
+        DensePlan dp;
+        if (make_dense_plan(kb, std::min({kb->capacity, DENSE_MAX_ROWS, DENSE_MAX_PAIRS / Q}), Q, k, (kind & 1) != 0, (kind & 2) != 0, &dp))
+            total = std::max(total, dp.total);
+    }
     return total;
 }
 
 size_t kb_query_plan_bytes(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32_t kind)
 {
     if (!kb || n < 0 || n > kb->capacity || Q < 1 || k < 1 || k > KB_K_MAX || kind < 0 || kind > 3) return 0;
-    if (WholePlan wp; make_whole_plan(kb, n, Q, k, (kind & 1) != 0, (kind & 2) != 0, &wp)) return wp.total;
-    if (const int parts = small_path_parts(kb, n, Q, (kind & 1) != 0); parts && ((kind & 2) == 0 || kb->dtype == KB_FP8_E4M3))
-        return make_small_plan(Q, k, parts).total;
+    const bool draw = (kind & 1) != 0, q8 = (kind & 2) != 0;
+    WholePlan wp;
+    DensePlan dp;
+    const bool dense = make_dense_plan(kb, n, Q, k, draw, q8, &dp);
+    if (make_whole_plan(kb, n, Q, k, draw, q8, &wp)) return dense && dense_is_better(n, k, wp) ? dp.total : wp.total;
+    if (const int parts = small_path_parts(kb, n, Q, draw); parts && (!q8 || kb->dtype == KB_FP8_E4M3)) return make_small_plan(Q, k, parts).total;         // (with more than that, the call takes the dense plan)
+    if (dense) return dp.total;
     Plan p;
     return make_plan(kb, n, Q, k, (kind & 1) != 0, (kind & 2) != 0, &p) ? p.total : 0;
 }
@@ -1978,13 +2269,37 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     if (qmask_dev && !kb->tags) return KB_ERR_NO_TAGS;
     if (kb->n_normalized != kb->n) return KB_ERR_NOT_NORMALIZED;
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & (WS_ALIGN - 1)) != 0) return KB_ERR_WORKSPACE;
-    // (given less memory than the whole-store plan wants, the call runs the pipeline)
-    if (WholePlan wp; make_whole_plan(kb, kb->n, Q, k, draw, q8, &wp) && wp.total <= workspace_bytes)
+    DrawArgs dr;
+    memset(&dr, 0, sizeof dr);
+    GainArgs ga;
+    memset(&ga, 0, sizeof ga);
+    if (draw) {
+        dr.inv_t = 1.0f / temperature;
+        dr.seed_lo = (uint32_t)seed;
+        dr.seed_hi = (uint32_t)(seed >> 32);
+        dr.first_query = (uint32_t)first_query;
+        dr.enabled = 1;
+        ga.gain = gain_dev;
+        ga.n = kb->n;
+        ga.n_padded = ceil_div(kb->n > 0 ? kb->n : 1, 256) * 256 + 256;
+        ga.blocks = (int)ceil_div(ga.n_padded, 256);
+    }
+
+    // (a plan that wants more memory than the call was given is passed over, down to the parts or the pipeline)
+    WholePlan wp;
+    DensePlan dp;
+    const bool whole = make_whole_plan(kb, kb->n, Q, k, draw, q8, &wp) && wp.total <= workspace_bytes;
+    const int parts = small_path_parts(kb, kb->n, Q, draw);
+    if (!whole && parts && workspace_bytes < make_small_plan(Q, k, parts).total) return KB_ERR_WORKSPACE;
+    const bool dense = make_dense_plan(kb, kb->n, Q, k, draw, q8, &dp) && dp.total <= workspace_bytes;
+    if (dense && !(whole && !dense_is_better(kb->n, k, wp)))
+        return launch_dense(kb, dp, queries_dev, q_dtype, Q, qmask_dev, k, dr, ga, indices_out_dev, scores_out_dev, static_cast<unsigned char *>(workspace_dev),
+                            static_cast<hipStream_t>(hip_stream));
+    if (whole)
         return launch_whole(kb, wp, queries_dev, q8, Q, qmask_dev, k, indices_out_dev, scores_out_dev, static_cast<unsigned char *>(workspace_dev),
                             static_cast<hipStream_t>(hip_stream));
-    if (const int parts = small_path_parts(kb, kb->n, Q, draw)) {
+    if (parts) {
         const SmallPlan sp = make_small_plan(Q, k, parts);
-        if (workspace_bytes < sp.total) return KB_ERR_WORKSPACE;
         unsigned char *w = static_cast<unsigned char *>(workspace_dev);
         return launch_small(kb, queries_dev, q8, Q, qmask_dev, k, parts, reinterpret_cast<uint64_t *>(w + sp.off_lists), reinterpret_cast<uint64_t *>(w),
                             indices_out_dev, scores_out_dev, static_cast<hipStream_t>(hip_stream));
@@ -2008,37 +2323,13 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     uint64_t *cand = reinterpret_cast<uint64_t *>(ws + p.off_cand);
     float *log_gain = reinterpret_cast<float *>(ws + p.off_lgain);
 
-    DrawArgs dr;
-    memset(&dr, 0, sizeof dr);
-    GainArgs ga;
-    memset(&ga, 0, sizeof ga);
-    if (draw) {
-        dr.log_gain = log_gain;
-        dr.inv_t = 1.0f / temperature;
-        dr.seed_lo = (uint32_t)seed;
-        dr.seed_hi = (uint32_t)(seed >> 32);
-        dr.first_query = (uint32_t)first_query;
-        dr.enabled = 1;
-        ga.gain = gain_dev;
-        ga.log_gain = log_gain;
-        ga.n = kb->n;
-        ga.n_padded = ceil_div(kb->n > 0 ? kb->n : 1, 256) * 256 + 256;
-        ga.blocks = (int)ceil_div(ga.n_padded, 256);
-    }
+    dr.log_gain = ga.log_gain = log_gain;
 
     // Query norms and per-call counters: the threshold kernel sets them when there is a sampling pass on scores;
     // otherwise (no sampling pass, or the weighted random selection, whose sampling pass needs 1/|q|) this launch does.
     const bool sampled = kb->n > 0 && p.sample_tiles > 0;
     if (!sampled || draw) {
-        const int n_init = p.qpad > STAT_WORDS + STAT_PARTIALS ? p.qpad : STAT_WORDS + STAT_PARTIALS;
-        const int blocks_rows = (int)ceil_div(p.qpad, 4), blocks_init = (int)ceil_div(n_init, 256);
-        const unsigned grid = (blocks_rows > blocks_init ? blocks_rows : blocks_init) + ga.blocks;
-        if (q_dtype == KB_F32)
-            hipLaunchKernelGGL(prep_kernel<KB_F32>, dim3(grid), dim3(256), 0, s, queries_dev, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done, ga);
-        else if (q_dtype == KB_FP8_E4M3)
-            hipLaunchKernelGGL(prep_kernel<KB_FP8_E4M3>, dim3(grid), dim3(256), 0, s, queries_dev, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done, ga);
-        else
-            hipLaunchKernelGGL(prep_kernel<KB_BF16>, dim3(grid), dim3(256), 0, s, queries_dev, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done, ga);
+        launch_prep(queries_dev, q_dtype, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done, ga, s);
         if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
     }
 
@@ -2074,6 +2365,8 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         a.whole_best = nullptr;
         a.whole_pair = nullptr;
         a.whole_groups = a.whole_fine = 0;
+        a.dense = nullptr;
+        a.dense_stride = 0;
         a.tile_stride = 1;
         a.row_mul = 0;
         a.row_run_shift = 0;

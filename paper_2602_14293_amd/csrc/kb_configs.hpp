@@ -3,7 +3,9 @@
 //   RBA          bytes of each key row per d-chunk    NSTAGE   chunk buffers in LDS
 //   WGPC         workgroups resident per compute unit (LDS and registers are budgeted for it)
 // (12, 16: small tiles for knowledge bases of some ten thousand rows, where a query is bound by the latency of its
-//  launches and more, shorter work items finish sooner; 23, 24: whole cache lines of fp8 rows of a multiple of 128 bytes)
+//  launches and more, shorter work items finish sooner; 23, 24: whole cache lines of fp8 rows of a multiple of 128 bytes;
+//  26: f32, where the matrix units are the bound, up to 64 queries, and small stores, whose time is one dot product's chain of
+//  matrix instructions times the blocks a wave holds: 150,000 x 256 rows, 40 queries 102 -> 65 us, 8000 x 768 rows, 100 queries 82 -> 46)
 #pragma once
 #define KB_SCAN_CONFIGS_BF16(X)                  \
     X(1, KB_BF16, 128, 32, 4, 1, 128, 3, 2)      \
@@ -14,7 +16,8 @@
 #define KB_SCAN_CONFIGS_F32(X)                   \
     X(1, KB_F32, 128, 32, 4, 1, 128, 3, 2)       \
     X(2, KB_F32, 128, 128, 2, 2, 64, 4, 2)       \
-    X(3, KB_F32, 128, 256, 2, 2, 64, 3, 2)
+    X(3, KB_F32, 128, 256, 2, 2, 64, 3, 2)       \
+    X(26, KB_F32, 64, 64, 2, 2, 128, 4, 2)
 #define KB_SCAN_CONFIGS_FP8(X)                   \
     X(1, KB_FP8_E4M3, 128, 32, 4, 1, 64, 3, 2)   \
     X(2, KB_FP8_E4M3, 128, 128, 2, 2, 64, 3, 2)  \
@@ -39,6 +42,9 @@
     X(21, KB_BF16, 128, 128, 4, 2, 128, 4, 1)
 #define KB_SCAN_WHOLE_CONFIGS_FP8(X)             \
     X(13, KB_FP8_E4M3, 32, 32, 1, 1, 64, 12, 2)
+// ... with fp8 queries (the dense plan only)
+#define KB_SCAN_DENSE_CONFIGS_FP8_Q8(X)          \
+    X(25, KB_FP8_Q8, 32, 32, 1, 1, 64, 15, 2)
 // ... and of a kernel of its own, for f32 rows (kb_scan_f32.hip): tiles of 16 rows
 constexpr int SMALL_F32_CONFIG = 15;
 

@@ -517,6 +517,40 @@ __device__ inline void whole_epilogue(const f32x16 (&acc)[IB][JB], const EpiSide
     }
 }
 
+// Dense plan: every product, -inf where the row does not qualify.  A lane stores four neighbouring rows of its query at a
+// time; the rows past the last one up to the tile's end are there too.
+__device__ inline void dense_store(float (&v)[4], const float (&ik)[4], const EpiSide &sd, bool filter, uint64_t qm, int rl, int64_t row0, int q, const ScanArgs &p)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const bool ok = row0 + rl + e < p.n_keys && !row_removed(ik[e]) && (!filter || (sd.tag[rl + e] & qm) != 0);
+        v[e] = ok ? v[e] : -__builtin_inff();
+    }
+    if (q < p.Q) *reinterpret_cast<f32x4 *>(p.dense + (size_t)q * p.dense_stride + row0 + rl) = f32x4{v[0], v[1], v[2], v[3]};
+}
+template <int IB, int JB>
+__device__ inline void dense_epilogue(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0, int half, int64_t row0, int q0,
+                                      const ScanArgs &p)
+{
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) {
+        const int ql = ql0 + jb * 32;
+        const uint64_t qm = filter ? sd.qmask[ql] : 0ull;
+#pragma unroll
+        for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+            for (int run = 0; run < 4; ++run) {
+                const int rl = wave_row0 + ib * 32 + 4 * half + 8 * run;
+                const f32x4 ik4 = *reinterpret_cast<const f32x4 *>(sd.invk + rl);
+                const float ik[4] = {ik4.x, ik4.y, ik4.z, ik4.w};
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = acc[ib][jb][4 * run + e] * ik[e];
+                dense_store(v, ik, sd, filter, qm, rl, row0, q0 + ql, p);
+            }
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 // Weighted random selection: the same two epilogues on keys = score / T + ln(gain) + Gumbel noise.
 // ------------------------------------------------------------------------------------------------
@@ -708,6 +742,36 @@ __device__ inline void main_epilogue_draw(const f32x16 (&acc)[IB][JB], const Epi
             main_block_draw(acc[ib][jb], rw, sd.thrp[ql0 + jb * 32], ql0 + jb * 32, sd, filter, row0, q0, p, region, wave_cnt, region_id);
         }
     }
+}
+
+// Dense plan on keys.
+template <int IB, int JB, int JBX>
+__device__ inline void dense_column_draw(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0, int half, int64_t row0, int q0,
+                                         const ScanArgs &p)
+{
+    const int ql = ql0 + JBX * 32;
+    const uint64_t qm = filter ? sd.qmask[ql] : 0ull;
+    const float iq = sd.invq[ql];
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib) {
+        int rl0 = wave_row0 + ib * 32 + 4 * half;
+        asm volatile("" : "+v"(rl0));       // (see sample_column_draw)
+        const EpiRows rw = load_rows(sd, rl0);
+        float key[16];
+        block_keys<false>(acc[ib][JBX], rw, iq, p, p.draw.first_query + (uint32_t)(q0 + ql), row0, sd, key);
+#pragma unroll
+        for (int run = 0; run < 4; ++run) {
+            float v[4] = {key[4 * run], key[4 * run + 1], key[4 * run + 2], key[4 * run + 3]};
+            const float ik[4] = {rw.ik[4 * run], rw.ik[4 * run + 1], rw.ik[4 * run + 2], rw.ik[4 * run + 3]};
+            dense_store(v, ik, sd, filter, qm, rl0 + 8 * run, row0, q0 + ql, p);
+        }
+    }
+}
+template <int IB, int JB, int... JBX>
+__device__ inline void dense_epilogue_draw(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0, int half, int64_t row0, int q0,
+                                           const ScanArgs &p, std::integer_sequence<int, JBX...>)
+{
+    (dense_column_draw<IB, JB, JBX>(acc, sd, filter, wave_row0, ql0, half, row0, q0, p), ...);
 }
 
 // Sampling pass on keys: per lane and query column the qualifying entry with the largest key.  One function per

@@ -138,6 +138,15 @@ struct WholePlan {
     size_t off_best, off_pair, total;
 };
 
+// The dense plan: a store of some thousand rows.  The tiled scan writes the product (the key, in the weighted selection) of
+// every row and query, one workgroup per query selects from its row of them.
+constexpr int DENSE_THREADS = 256;
+constexpr int64_t DENSE_MAX_ROWS = 16384;   // a thread of the selecting workgroup keeps 64 of them
+struct DensePlan {
+    int32_t config, tk, tq, nqb, grid, stride;      // stride: values per query, a multiple of the tile's rows and of what a load of the selection takes
+    size_t off_values, off_invq, off_lgain, off_unused, total;      // (off_invq on: the weighted selection only)
+};
+
 // Weighted random selection (Section 3, Optimization Selector: its top-k is a random draw whose weights are the
 // entries' predicted gains): entries are ranked by key = score / T + ln(gain) + Gumbel noise instead of by
 // score, which draws k entries without replacement with probability proportional to gain * exp(score / T).
@@ -182,6 +191,8 @@ struct ScanArgs {
     float *whole_best;        // [Q][groups]: product of the best row of the group
     u32x4 *whole_pair;        // [Q][groups]: the rest of the group's entry
     int32_t whole_groups, whole_fine;       // fine: a group is the rows of one wave, not of the tile
+    float *dense;             // dense plan: [Q][dense_stride] products or keys, -inf in the place of what does not qualify.  nullptr otherwise
+    int32_t dense_stride;
 };
 
 // Key row behind row r of logical tile `tile` in a sampling pass.  With row_mul the sample is scattered in runs of

@@ -188,15 +188,16 @@ __device__ inline void bare_barrier()
     asm volatile("" ::: "memory");
 }
 
-template <class C, bool SAMPLE, bool DRAW, bool WHOLE = false, bool NT = false>
+template <class C, bool SAMPLE, bool DRAW, bool WHOLE = false, bool NT = false, bool DENSE = false>
 __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p)
 {
+    static_assert(!DENSE || !(SAMPLE || WHOLE), "one of the plans");
     constexpr int TK = C::TK, TQ = C::TQ, RBA = C::RBA, RBB = C::RBB, IB = C::IB, JB = C::JB, NW = C::NW;
     constexpr int LA = C::NIA / NW, LB = C::NIB / NW;           // load instructions per wave per chunk
     constexpr int RSTEP_A = NW * 64 / C::PPRA, RSTEP_B = NW * 64 / C::PPRB;   // rows between a wave's instructions
     static_assert(C::NIA % NW == 0 && C::NIB % NW == 0, "every wave issues the same number of loads");
     constexpr bool SAME_SWZ_A = RSTEP_A % 16 == 0, SAME_SWZ_B = RSTEP_B % 16 == 0;      // the swizzle repeats every 16 rows
-    static_assert(WHOLE || SAME_SWZ_A, "only the whole-store plan takes tiles whose load instructions differ in the swizzle");
+    static_assert(WHOLE || DENSE || SAME_SWZ_A, "only the whole-store and the dense plan take tiles whose load instructions differ in the swizzle");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void *lds_ptr;
 
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
             else if constexpr (WHOLE) {
                 const int64_t row = whole_row(ld_tile, (int32_t)p.n_tiles, TK, r);
                 offA[j] = (uint64_t)(row < p.n_keys ? row : p.n_keys - 1) * key_row_bytes + (SAME_SWZ_A ? ldA_piece : (uint32_t)((((wave * 64 + lane) % C::PPRA) ^ swizzle<C::PPRA>(r)) * 16));
-            } else offA[j] = (uint32_t)(r < last ? r : last) * key_row_bytes + ldA_piece;
+            } else offA[j] = (uint32_t)(r < last ? r : last) * key_row_bytes + (SAME_SWZ_A ? ldA_piece : (uint32_t)((((wave * 64 + lane) % C::PPRA) ^ swizzle<C::PPRA>(r)) * 16));
         }
         const int qlast = p.Q - 1 - ld_qb * TQ;
 #pragma unroll
@@ -342,8 +343,8 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
             }
             if (tid < TQ) {
                 const int q = qb * TQ + tid;            // < qpad: invq, thr64 and thrp are padded arrays
-                if ((!SAMPLE && !WHOLE) || DRAW) my_invq = p.invq[q];      // (a sampling pass on scores runs before 1/|q| exists)
-                if (!SAMPLE && !WHOLE) {
+                if ((!SAMPLE && !WHOLE && !DENSE) || DRAW) my_invq = p.invq[q];      // (a sampling pass on scores runs before 1/|q| exists)
+                if (!SAMPLE && !WHOLE && !DENSE) {
                     my_thr64 = p.thr64[q];
                     my_thrp = p.thrp[q];
                 }
@@ -427,6 +428,10 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 whole_epilogue<TK, IB, JB, C::WM, TQ>(acc, sd, filter, wm, rowB, half, tile, qb * TQ, p, (uint64_t)dead_hi << 32 | dead_lo,
                                                   reinterpret_cast<u32x4 *>(smem + C::OFF_EXCHANGE));
             }
+            else if constexpr (DENSE && DRAW)
+                dense_epilogue_draw<IB, JB>(acc, sd, filter, rowA - lrow, rowB, half, row0, qb * TQ, p, std::make_integer_sequence<int, JB>{});
+            else if constexpr (DENSE)
+                dense_epilogue<IB, JB>(acc, sd, filter, rowA - lrow, rowB, half, row0, qb * TQ, p);
             else if (DRAW)
                 main_epilogue_draw<IB, JB>(acc, sd, filter, rowA - lrow, rowB, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
             else
@@ -447,19 +452,19 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
         }
     }
 
-    if (!SAMPLE && !WHOLE) flush_records(p, my_region, wave_cnt, blockIdx.x * NW + wave);      // what is left in the region
+    if (!SAMPLE && !WHOLE && !DENSE) flush_records(p, my_region, wave_cnt, blockIdx.x * NW + wave);      // what is left in the region
 }
 
 // Variants of a configuration with the non-temporal policy: where query blocks of 32 make the scan a stream of keys, in whole
 // lines (half lines would be fetched twice).
 template <class C> constexpr bool HAS_NT = C::TQ == 32 && C::TK == 128 && C::RBA == 128;
 
-template <class C, bool SAMPLE, bool DRAW, bool WHOLE, bool NT> hipError_t launch_scan_variant(int grid, const ScanArgs &a, hipStream_t s)
+template <class C, bool SAMPLE, bool DRAW, bool WHOLE, bool NT, bool DENSE = false> hipError_t launch_scan_variant(int grid, const ScanArgs &a, hipStream_t s)
 {
     // more than 64 KiB of dynamic LDS has to be requested explicitly, once per kernel
     constexpr int SMEM = WHOLE ? C::SMEM_BYTES_WHOLE : C::SMEM_BYTES;
     static LdsAllowed allowed;
-    auto *fn = &kb_scan_kernel<C, SAMPLE, DRAW, WHOLE, NT>;
+    auto *fn = &kb_scan_kernel<C, SAMPLE, DRAW, WHOLE, NT, DENSE>;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed, SMEM); e != hipSuccess) return e;
     hipExtLaunchKernelGGL(fn, dim3(grid), dim3(C::THREADS), SMEM, s, scan_timing.start, scan_timing.stop, 0, a);
     return hipGetLastError();
@@ -478,8 +483,29 @@ template <class C> hipError_t launch_whole_cfg(int grid, const ScanArgs &a, hipS
     return launch_scan_policy<C, false, false, true>(grid, a, s);
 }
 
+// the scan of the dense plan
+template <class C> hipError_t launch_dense_cfg(int grid, const ScanArgs &a, hipStream_t s)
+{
+    return a.draw.enabled ? launch_scan_variant<C, false, true, false, false, true>(grid, a, s) : launch_scan_variant<C, false, false, false, false, true>(grid, a, s);
+}
+
+// configurations of these two plans only: the smallest tiles take both (fp8 queries: the dense one), larger ones the whole-store plan
+template <class C> hipError_t launch_unfiltered_cfg(int grid, const ScanArgs &a, hipStream_t s)
+{
+    if (a.dense) {
+        if constexpr (C::TK == 32) return launch_dense_cfg<C>(grid, a, s);
+        return hipErrorInvalidValue;
+    }
+    if constexpr (C::TK == 32 && C::Q8) return hipErrorInvalidValue;
+    else return a.whole_best ? launch_whole_cfg<C>(grid, a, s) : hipErrorInvalidValue;
+}
+
 template <class C> hipError_t launch_scan_cfg(bool sample, int grid, const ScanArgs &a, hipStream_t s)
 {
+    if (a.dense) {
+        if constexpr (C::TQ <= 128) return launch_dense_cfg<C>(grid, a, s);
+        return hipErrorInvalidValue;
+    }
     if (a.whole_best) {
         // (bf16 rows and 65 to 128 queries: tiles of 64 rows, or of 128 on eight wavefronts)
         if constexpr (C::TQ <= 128 && !(C::KT == KB_BF16 && C::TQ == 128 && C::TK == 128)) return launch_whole_cfg<C>(grid, a, s);

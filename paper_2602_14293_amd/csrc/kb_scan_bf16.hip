@@ -12,7 +12,7 @@ hipError_t launch_scan_bf16(int config, bool sample, int grid, const ScanArgs &a
         KB_SCAN_CONFIGS_BF16(X)
 #undef X
 #define X(ID, KT, TK, TQ, WM, WN, RBA, NSTAGE, WGPC) \
-    case ID: return sample || !a.whole_best ? hipErrorInvalidValue : launch_whole_cfg<ScanCfg<KT, TK, TQ, WM, WN, RBA, NSTAGE, WGPC>>(grid, a, s);
+    case ID: return sample ? hipErrorInvalidValue : launch_unfiltered_cfg<ScanCfg<KT, TK, TQ, WM, WN, RBA, NSTAGE, WGPC>>(grid, a, s);
         KB_SCAN_WHOLE_CONFIGS_BF16(X)
 #undef X
     default: return hipErrorInvalidValue;

@@ -17,12 +17,15 @@ template <int CB> struct SmallF32 {
     static_assert(LOADS * (NSTAGE - 2) < 64, "vmcnt is a 6-bit counter");
 };
 
-template <int CB> __global__ __launch_bounds__(64) void kb_small_f32_kernel(ScanArgs p)
+// DENSE: the scan of the dense plan; a workgroup per tile and block of queries, the rows of a tile are neighbours.
+template <int CB, bool DENSE = false> __global__ __launch_bounds__(64) void kb_small_f32_kernel(ScanArgs p)
 {
     typedef SmallF32<CB> C;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void *lds_ptr;
-    const int lane = threadIdx.x, col = lane & 15, h = lane >> 4, tile = blockIdx.x;
+    const int lane = threadIdx.x, col = lane & 15, h = lane >> 4;
+    const int tile = DENSE ? blockIdx.x / p.nqb : blockIdx.x, q0 = DENSE ? (int)(blockIdx.x % p.nqb) * C::TQ : 0;
+    auto row_at = [&](int place) { return DENSE ? (int64_t)tile * C::TK + place : whole_row(tile, (int32_t)p.n_tiles, C::TK, place); };
     const int NC = p.d * 4 / C::RB;
     const uint32_t row_bytes = (uint32_t)p.d * 4;
     // load instruction j of a chunk fills rows 8 j .. 8 j + 7 (keys first, then queries) of 128 bytes, swizzled as in the
@@ -33,10 +36,10 @@ template <int CB> __global__ __launch_bounds__(64) void kb_small_f32_kernel(Scan
         const int r = j * 8 + (lane >> 3), place = j < 2 ? r : r - 16;
         const uint32_t piece = (uint32_t)(((lane & 7) ^ swizzle<8>(place)) * 16);
         if (j < 2) {
-            const int64_t row = whole_row(tile, (int32_t)p.n_tiles, 16, place);
+            const int64_t row = row_at(place);
             src[j] = static_cast<const unsigned char *>(p.keys) + (size_t)(row < p.n_keys ? row : p.n_keys - 1) * row_bytes + piece;
         } else {
-            src[j] = static_cast<const unsigned char *>(p.queries) + (size_t)(place < p.Q ? place : p.Q - 1) * row_bytes + piece;
+            src[j] = static_cast<const unsigned char *>(p.queries) + (size_t)(q0 + place < p.Q ? q0 + place : p.Q - 1) * row_bytes + piece;
         }
     }
     int issued = 0, slot = 0;
@@ -54,14 +57,14 @@ template <int CB> __global__ __launch_bounds__(64) void kb_small_f32_kernel(Scan
     const bool filter = p.qmask != nullptr;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int64_t row = whole_row(tile, (int32_t)p.n_tiles, 16, 4 * h + i);
+        const int64_t row = row_at(4 * h + i);
         live[i] = row < p.n_keys;
         const int64_t r = live[i] ? row : p.n_keys - 1;
         ik[i] = p.inv_norm[r];
         tg[i] = filter ? p.tags[r] : 0ull;
     }
 #pragma unroll
-    for (int b = 0; b < CB; ++b) qm[b] = filter ? p.qmask[16 * b + col < p.Q ? 16 * b + col : p.Q - 1] : 0ull;
+    for (int b = 0; b < CB; ++b) qm[b] = filter ? p.qmask[q0 + 16 * b + col < p.Q ? q0 + 16 * b + col : p.Q - 1] : 0ull;
     asm volatile("" ::: "memory");
     for (int s = 0; s < C::NSTAGE - 1 && s < NC; ++s) issue();
 
@@ -90,6 +93,17 @@ template <int CB> __global__ __launch_bounds__(64) void kb_small_f32_kernel(Scan
     }
 
     // lane (col, h) holds rows 4 h .. 4 h + 3 of query 16 b + col
+    if constexpr (DENSE) {
+#pragma unroll
+        for (int b = 0; b < CB; ++b) {
+            f32x4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = live[i] && !row_removed(ik[i]) && (!filter || (tg[i] & qm[b]) != 0) ? acc[b][i] * ik[i] : -__builtin_inff();
+            const int q = q0 + 16 * b + col;
+            if (q < p.Q) *reinterpret_cast<f32x4 *>(p.dense + (size_t)q * p.dense_stride + tile * C::TK + 4 * h) = v;
+        }
+        return;
+    }
 #pragma unroll
     for (int b = 0; b < CB; ++b) {
         TopThree one[4], t = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), 0u};
@@ -117,10 +131,10 @@ template <int CB> __global__ __launch_bounds__(64) void kb_small_f32_kernel(Scan
     }
 }
 
-template <int CB> hipError_t launch_small_f32(int grid, const ScanArgs &a, hipStream_t s)
+template <int CB, bool DENSE = false> hipError_t launch_small_f32(int grid, const ScanArgs &a, hipStream_t s)
 {
     static_assert(SmallF32<CB>::SMEM_BYTES <= 64 * 1024);
-    hipExtLaunchKernelGGL((&kb_small_f32_kernel<CB>), dim3(grid), dim3(64), SmallF32<CB>::SMEM_BYTES, s, scan_timing.start, scan_timing.stop, 0, a);
+    hipExtLaunchKernelGGL((&kb_small_f32_kernel<CB, DENSE>), dim3(grid), dim3(64), SmallF32<CB>::SMEM_BYTES, s, scan_timing.start, scan_timing.stop, 0, a);
     return hipGetLastError();
 }
 
@@ -132,6 +146,10 @@ hipError_t launch_scan_f32(int config, bool sample, int grid, const ScanArgs &a,
         KB_SCAN_CONFIGS_F32(X)
 #undef X
     case SMALL_F32_CONFIG:
+        if (a.dense) {      // one workgroup per tile of 16 rows and 32 queries (16 if there are no more)
+            if (a.draw.enabled || grid != a.n_tiles * a.nqb) return hipErrorInvalidValue;
+            return a.Q <= 16 ? launch_small_f32<1, true>(grid, a, s) : launch_small_f32<2, true>(grid, a, s);
+        }
         // one workgroup per tile of 16 rows, up to 32 queries
         if (sample || !a.whole_best || a.Q > 32 || grid != a.n_tiles) return hipErrorInvalidValue;
         return a.Q <= 16 ? launch_small_f32<1>(grid, a, s) : launch_small_f32<2>(grid, a, s);
