@@ -254,7 +254,8 @@ kb_status_t kb_check_draw_noise(int64_t *out_dev, void *hip_stream);
 
 /*
  * Diagnostics of the most recent kb_query that used `workspace_dev`: synchronises `hip_stream`, then copies
- * out[0] = candidates that passed the threshold filter (all queries), out[1] = queries resolved by the
+ * out[0] = candidates that passed the threshold filter of the main pass (all queries; a main pass that leaves out the
+ * rows of the sampling pass does not count those), out[1] = queries resolved by the
  * exhaustive per-query path, out[2] = keys scored by the sampling pass, out[3] = workgroups of the scan (a query
  * that took the small-knowledge-base path reports 0, 0, 0 and its workgroups).
  * `out` is host memory, 4 x int64.  Errors: KB_ERR_NULL, KB_ERR_DEVICE.

@@ -2,7 +2,8 @@
 //
 //   kb_normalize : row_norm_kernel            (row L2 norms as a side scale)
 //   kb_query     : scan kernel, sampling pass (kb_scan.hpp)
-//                  threshold_kernel           (k-th best group maximum per query; query norms, counters reset)
+//                  threshold_kernel           (k-th best group maximum per query; query norms, counters reset; what the sample
+//                                              itself adds to the lists where the main pass leaves its rows out)
 //                  [prep_kernel               (query norms, counters reset: when no sampling pass runs)]
 //                  scan kernel, main pass     (kb_scan.hpp; its wavefronts move their records to per-query lists)
 //                  finalize_kernel            (top k of each query's list by radix selection; or the
@@ -106,7 +107,6 @@ constexpr int MAX_CAND_CAP = 8192;     // finalize_kernel likewise
 constexpr int MIN_CAND_CAP = 1024;
 constexpr int FALLBACK_PARTS = 32;    // workgroups that share the rows of a query on the exhaustive path
 constexpr size_t WS_ALIGN = 256;
-constexpr int FP8_PIPELINED_CONFIG = 4;       // fp8 keys with bf16 queries, 64-byte row pieces
 constexpr int FP8_QUERY_CONFIG = 5;    // scan configuration of fp8 keys with fp8 queries (kb_configs.hpp)
 constexpr int FP8_QUERY_WIDE_CONFIG = 20;     // ... with 128-byte row pieces: rows of a multiple of 128 bytes, 512 at least
 constexpr int FP8_QUERY_TILED_CONFIG = 6;     // ... the tiled kernel: 6, 7, 8 for query blocks of 64, 128, 256; every row length
@@ -210,11 +210,11 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
     }
     c.sci = c.ci;
     c.sample_config = c.config;
-    if (c.ci.family == 4 && h->dtype == KB_FP8_E4M3) {       // the fp8 full-line kernel is a main pass only
-        c.sample_config = q8 ? FP8_QUERY_CONFIG : FP8_PIPELINED_CONFIG;
+    if (q8 && c.ci.family == 4) {       // with fp8 queries the full-line kernel is a main pass only
+        c.sample_config = FP8_QUERY_CONFIG;
         if (!scan_config_info(h->dtype, c.sample_config, &c.sci) || c.sci.tq != c.ci.tq || c.sci.tk != c.ci.tk) return false;
     }
-    if (draw && c.ci.family == 4) {     // so is the full-line kernel on keys: the tiled kernel with the same query blocks samples
+    if (draw && c.ci.family == 4) {     // the full-line kernel on keys is a main pass only: the tiled kernel with the same query blocks samples
         c.sample_config = c.ci.tq == 128 ? 2 : 3;
         if (!scan_config_info(h->dtype, c.sample_config, &c.sci) || c.sci.tq != c.ci.tq || c.sci.family != 0) return false;
     }
@@ -230,7 +230,7 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
 // 0 = no sampling pass (every entry is a candidate).  Depends on the row count through nt only, and never falls as
 // nt grows (`floor` switched off).
 constexpr int64_t FREE_SAMPLE_BYTES = 32 << 20;
-int64_t sample_tiles_for(const kb *h, const ConfigInfo &sci, int64_t nt, int32_t Q, int32_t k, bool floor)
+int64_t sample_tiles_for(const kb *h, const ConfigInfo &sci, int64_t nt, int32_t Q, int32_t k, bool whole_rounds, bool floor)
 {
     if (nt < 8) return 0;
     const int64_t kk = k > 8 ? k : 8;
@@ -244,12 +244,22 @@ int64_t sample_tiles_for(const kb *h, const ConfigInfo &sci, int64_t nt, int32_t
         if (free_tiles > by_bytes) free_tiles = by_bytes;
         if (free_tiles > nt / 4) free_tiles = nt / 4;
         if (st < free_tiles) st = free_tiles;
+        // a sample that the main pass leaves out costs nothing as long as both are whole rounds of the compute units (down by a
+        // quarter at most, and not where a round is more than a quarter of the store)
+        if (whole_rounds) {
+            const int64_t rounded = ceil_div(3 * st * nqb, 4 * DEVICE_CUS) * DEVICE_CUS / nqb;
+            if (rounded > st ? rounded <= nt / 4 || !floor : floor) st = rounded;
+        }
     }
     if (st > MAX_SAMPLE_SLOTS / sci.groups_per_tile) st = MAX_SAMPLE_SLOTS / sci.groups_per_tile;
     if (st > nt / 2) st = nt / 2;
     if (floor && st * sci.groups_per_tile < k) st = 0;
     return st;
 }
+
+// Kernels whose main pass leaves the sampled rows out, and those of them whose sample is whole rounds of the compute units.
+bool leaves_sample_out(const Choice &c) { return c.ci.family == 4 && c.sci.family != 3; }
+bool samples_in_rounds(const Choice &c) { return c.ci.family == 4 && c.sci.family == 4; }
 
 int32_t cand_cap_for(int64_t expect, bool sampled)
 {
@@ -261,7 +271,7 @@ int32_t cand_cap_for(int64_t expect, bool sampled)
 
 // Sizes of the workspace arrays.  The layout is a function of these alone and its total grows with each of them.
 struct Sizes {
-    int32_t k, qpad, regions, sample_slots, cand_cap;
+    int32_t k, qpad, regions, sample_slots, more_slots, cand_cap;
     int64_t region_records;     // scan wavefronts * region_cap
     int64_t lgain_rows;
 };
@@ -280,6 +290,7 @@ void lay_out(const Sizes &z, Plan *p)
     p->off_fb_lists = off;    off = align_up(off + sizeof(uint64_t) * (size_t)z.qpad * p->fb_parts * z.k);
     p->off_qmask = off;       off = align_up(off + sizeof(uint64_t) * z.qpad);
     p->off_samp = off;        off = align_up(off + sizeof(uint64_t) * (size_t)z.qpad * (z.sample_slots > 0 ? z.sample_slots : 1));
+    p->off_samp_more = off;   off = align_up(off + sizeof(uint64_t) * (size_t)z.qpad * z.more_slots);
     p->off_regions = off;     off = align_up(off + sizeof(Record) * (size_t)z.region_records);
     p->off_cand = off;        off = align_up(off + sizeof(uint64_t) * (size_t)z.qpad * z.cand_cap);
     p->off_lgain = off;       off = align_up(off + sizeof(float) * (size_t)z.lgain_rows);   // ln(gain), padded past the last tile
@@ -308,18 +319,24 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
     if (n < 1) n = 1;
     const int64_t nt = ceil_div(n, ci.tk), nts = ceil_div(n, sci.tk);     // key tiles of the main pass, of the sampling pass
 
-    const int64_t st = sample_tiles_for(h, sci, nts, Q, k, true);
+    const int64_t st = sample_tiles_for(h, sci, nts, Q, k, samples_in_rounds(c), true);
     p.sample_tk = sci.tk;
     p.sample_tiles = st;
     p.sample_slots = (int32_t)(st * sci.groups_per_tile);
     p.sample_keys = st * sci.tk;
-    const int64_t expect = st > 0 ? ceil_div((int64_t)k * nts, st) : nt * ci.tk;      // candidates per query
+    // Where the full-line kernel runs the main pass, that pass leaves the sampled rows out: see main_row.  (Not where the sample is
+    // whole tiles: the full-line kernel addresses scattered rows in 32 bits, in units of 16 bytes, up to 64 GiB of keys.)
+    const int run_shift = draw ? 2 : 0;
+    const int64_t sampled_runs = p.sample_keys >> run_shift, runs = n >> run_shift;
+    p.once = leaves_sample_out(c) && st > 0 && 2 * sampled_runs < runs && runs >= 3 && !(sci.family == 4 && (uint64_t)n * h->d * key_bytes(h->dtype) >= ((uint64_t)1 << 36));
+    p.main_rows = p.once ? n - p.sample_keys : n;
+    const int64_t expect = st > 0 ? ceil_div((int64_t)k * nts, sample_tiles_for(h, sci, nts, Q, k, false, true)) : nt * ci.tk;      // candidates per query
     p.cand_cap = cand_cap_for(expect, st > 0);
 
     const int wgpc = h->tune_wg_per_cu > 0 ? (int)h->tune_wg_per_cu : ci.wg_per_cu;
-    const int64_t items = nt * p.nqb;
+    const int64_t items = nt * p.nqb, main_items = ceil_div(p.main_rows, ci.tk) * p.nqb;
     const int64_t grid = items < (int64_t)DEVICE_CUS * wgpc ? items : (int64_t)DEVICE_CUS * wgpc;
-    p.grid = (int32_t)grid;
+    p.grid = (int32_t)(main_items < grid ? main_items : grid);
     const int waves = ci.threads / 64;
     p.regions = (int32_t)(grid * waves);
     // Records a scan wavefront collects before it moves them to the per-query lists.  With a sampling pass few pairs
@@ -338,6 +355,7 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
     z.qpad = p.qpad;
     z.regions = p.regions;
     z.sample_slots = p.sample_slots;
+    z.more_slots = leaves_sample_out(c) ? p.sample_slots : 0;
     z.cand_cap = p.cand_cap;
     z.region_records = (int64_t)p.regions * rc;
     z.lgain_rows = draw ? ceil_div(n, 256) * 256 + 256 : 0;      // the weighted random selection only
@@ -465,6 +483,7 @@ void max_into(Sizes &m, const Sizes &z)
     if (z.qpad > m.qpad) m.qpad = z.qpad;
     if (z.regions > m.regions) m.regions = z.regions;
     if (z.sample_slots > m.sample_slots) m.sample_slots = z.sample_slots;
+    if (z.more_slots > m.more_slots) m.more_slots = z.more_slots;
     if (z.cand_cap > m.cand_cap) m.cand_cap = z.cand_cap;
     if (z.region_records > m.region_records) m.region_records = z.region_records;
     if (z.lgain_rows > m.lgain_rows) m.lgain_rows = z.lgain_rows;
@@ -501,7 +520,8 @@ void bound_sizes(const kb *h, const Choice &c, int32_t Q, int32_t k, bool draw, 
     const int64_t at_cap = ceil_div((int64_t)k * cap_nt * sci.groups_per_tile, MAX_SAMPLE_SLOTS);
     if (at_cap > expect) expect = at_cap;
     z.cand_cap = h->tune_sample_keys > 0 ? MAX_CAND_CAP : cand_cap_for(expect, true);
-    z.sample_slots = (int32_t)(sample_tiles_for(h, sci, cap_nt, Q, k, false) * sci.groups_per_tile);
+    z.sample_slots = (int32_t)(sample_tiles_for(h, sci, cap_nt, Q, k, samples_in_rounds(c), false) * sci.groups_per_tile);
+    z.more_slots = leaves_sample_out(c) ? z.sample_slots : 0;
     z.region_records = (int64_t)z.regions * REGION_CAP;
     max_into(m, z);
 }
@@ -844,6 +864,9 @@ __device__ inline void select_topk_desc(uint64_t *buf, int n, int k, SelectScrat
     __syncthreads();
 }
 
+template <int KT, int UNR> __device__ f32x16 score_rows(const void *keys, const void *queries, int d, int64_t my_row, int q);
+constexpr int KT_FP8_Q8 = 3;        // stands for fp8 keys with fp8 queries (one fp8 matrix instruction per 64-byte chunk, as in the scan)
+
 // k-th best group maximum of the sampling pass = a lower bound of the k-th best score (k distinct
 // entries reach it).  Also derives the conservative pre-filter on dot * inv_k used by the main pass:
 // whenever fp32((dot*inv_k) * inv_q) >= s_thr holds, dot*inv_k >= thrp holds (2^-20 relative slack
@@ -865,10 +888,34 @@ struct ThresholdArgs {
     uint32_t *cnt, *flag, *fb_done;
     uint64_t sample_keys;
     int32_t slots, group_shift, k, Q, qpad, d, grid;
+    // where the main pass leaves the sampled rows out:
+    const uint64_t *more;       // ScanArgs::samp_more
+    uint64_t *cand;             // the candidate lists
+    int32_t cand_cap, tile_rows;
+    ScanArgs scan;              // of the sampling pass
 };
-
-template <int QT, bool KEYS> __global__ __launch_bounds__(1024) void threshold_kernel(ThresholdArgs a)
+// A load whose value nobody needs: the line is in the L2 for whoever asks next.
+__device__ inline void touch(const unsigned char *at)
 {
+    uint32_t v = *reinterpret_cast<const volatile uint32_t *>(at);
+    asm volatile("" : : "v"(v));
+}
+constexpr int THRESHOLD_AGAIN = 1024;       // groups that are scored again, a query
+
+// KT: type of the keys (KT_FP8_Q8: with fp8 queries) where the main pass leaves the sampled rows out, -1 otherwise.  The kernel
+// then also lists the sample's own candidates: the best and the second row of a group where they reach the threshold; groups whose
+// bound on the others does too (k^3 / (6 slots^2) of them on a store in no order, one query in a thousand) are scored again
+// with the instruction sequence of the scan, 32 rows a wavefront.
+template <int QT, bool KEYS, int KT, int PER = 2> __global__ __launch_bounds__(1024) void threshold_kernel(ThresholdArgs a)
+{
+    constexpr bool ONCE = KT >= 0;
+    constexpr int SEGS = ONCE ? CAND_SEGMENTS : 1;
+    __shared__ uint32_t sh_seg[SEGS], sh_again, sh_lost;
+    __shared__ uint16_t sh_group[ONCE ? THRESHOLD_AGAIN : 1];
+    if constexpr (ONCE) {
+        if (threadIdx.x < CAND_SEGMENTS) sh_seg[threadIdx.x] = 0;
+        if (threadIdx.x == 0) sh_again = sh_lost = 0;
+    }
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     uint64_t *buf = reinterpret_cast<uint64_t *>(smem_raw);
     const int q = blockIdx.x, tid = threadIdx.x, slots = a.slots, k = a.k;
@@ -878,11 +925,11 @@ template <int QT, bool KEYS> __global__ __launch_bounds__(1024) void threshold_k
     // Everything the kernel reads from global memory is asked for before anything waits: the query's mask word, the
     // first two samples of every thread and (first wavefront) the query row are one memory round trip, not three.
     const int bd = (int)blockDim.x;
-    uint64_t mask_word = 0ull, first0 = 0ull, first1 = 0ull;
+    uint64_t mask_word = 0ull, words[PER];
     if (!KEYS && tid == 0 && a.qmask && q < a.Q) mask_word = a.qmask[q];
     if (KEYS || q < a.Q) {
-        if (tid < slots) first0 = a.samp[sample_slot_index(tid, a.group_shift, a.qpad, q)];
-        if (tid + bd < slots) first1 = a.samp[sample_slot_index(tid + bd, a.group_shift, a.qpad, q)];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) words[u] = tid + u * bd < slots ? a.samp[sample_slot_index(tid + u * bd, a.group_shift, a.qpad, q)] : 0ull;
     }
     if constexpr (!KEYS) {
         if (tid < CAND_SEGMENTS) a.cnt[q * CAND_SEGMENTS + tid] = 0;
@@ -909,9 +956,10 @@ template <int QT, bool KEYS> __global__ __launch_bounds__(1024) void threshold_k
             }
         }
     }
-    if (tid < slots) buf[tid] = first0;
-    if (tid + bd < slots) buf[tid + bd] = first1;
-    for (int i = tid + 2 * bd; i < slots; i += bd) buf[i] = a.samp[sample_slot_index(i, a.group_shift, a.qpad, q)];
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (tid + u * bd < slots) buf[tid + u * bd] = words[u];
+    for (int i = tid + PER * bd; i < slots; i += bd) buf[i] = a.samp[sample_slot_index(i, a.group_shift, a.qpad, q)];
     __syncthreads();
     select_topk_desc(buf, slots, k, sc, tid, bd);
     uint64_t t = k <= slots ? buf[k - 1] : 0ull;
@@ -924,17 +972,92 @@ template <int QT, bool KEYS> __global__ __launch_bounds__(1024) void threshold_k
             t = ((uint64_t)score_to_ordered(s) << 32) | sh_low;
         }
     }
+    float tp = -__builtin_inff();
+    if (KEYS) {
+        // keys are compared as they are: a word at or above t has a key at or above t's key
+        if (t != 0) tp = candidate_score(t);
+    } else if (t != 0 && iq > 0.f) {
+        const float x = candidate_score(t) / iq;
+        tp = x - fabsf(x) * 0x1p-20f - 1e-30f;
+    }
     if (tid == 0) {
-        float tp = -__builtin_inff();
-        if (KEYS) {
-            // keys are compared as they are: a word at or above t has a key at or above t's key
-            if (t != 0) tp = candidate_score(t);
-        } else if (t != 0 && iq > 0.f) {
-            const float x = candidate_score(t) / iq;
-            tp = x - fabsf(x) * 0x1p-20f - 1e-30f;
-        }
         a.thr64[q] = t;
         a.thrp[q] = tp;
+    }
+    if constexpr (ONCE) {
+        const uint32_t seg_cap = (uint32_t)a.cand_cap / CAND_SEGMENTS;
+        uint64_t *list = a.cand + (size_t)q * a.cand_cap;
+        auto append = [&](uint64_t word) {
+            const uint32_t seg = candidate_segment(candidate_index(word)), at = atomicAdd(&sh_seg[seg], 1u);
+            if (at < seg_cap) list[seg * seg_cap + at] = word;
+            else sh_lost = 1u;
+        };
+        // the sample's slot i: its group's lane half holds element e of 32 at this row of the tile
+        auto row_of = [&](int slot, int e) {
+            const int tile = slot >> a.group_shift, group = slot & ((1 << a.group_shift) - 1);
+            const int rl = (group >> 1) * 64 + 4 * (group & 1) + (e >> 4) * 32 + 8 * ((e & 15) >> 2) + (e & 3);
+            return (uint32_t)sample_row<true>(a.scan, sample_tile_run(a.scan, tile, a.tile_rows), tile, a.tile_rows, rl);
+        };
+        // (what is known of a group besides its best is read only where it can reach the threshold: the search tells values apart
+        // but for their low five bits)
+        auto look = [&](int i, uint64_t w) {
+            if (w == 0) return;
+            const float best = candidate_score(w);
+            const uint32_t bits = as_u32(best);
+            if (!(as_f32((int32_t)bits < 0 ? bits & ~31u : bits | 31u) >= tp)) return;
+            if (KEYS ? w >= t : best >= tp) append(KEYS ? w : pack_raw_candidate(best, candidate_index(w)));
+            const uint64_t more = a.more[sample_slot_index(i, a.group_shift, a.qpad, q)];
+            if (more == 0) return;
+            const float second = ordered_to_score((uint32_t)(more >> 32));
+            if (second >= tp) {
+                const uint32_t row = row_of(i, (int)(more & 31u));
+                if (!KEYS) append(pack_raw_candidate(second, row));
+                else if (pack_candidate(second, row) >= t) append(pack_candidate(second, row));
+            }
+            if (others_bound(more) != 0u && ordered_to_score(others_bound(more)) >= tp) {
+                const uint32_t n = atomicAdd(&sh_again, 1u);
+                if (n < THRESHOLD_AGAIN) sh_group[n] = (uint16_t)i;
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < PER; ++u) look(tid + u * bd, words[u]);
+        for (int i = tid + PER * bd; i < slots; i += bd) look(i, a.samp[sample_slot_index(i, a.group_shift, a.qpad, q)]);
+        __syncthreads();
+        const uint32_t again = sh_again;
+        if (again > 0 && again <= THRESHOLD_AGAIN) {
+            const ScanArgs &p = a.scan;
+            const int lane = tid & 63, lrow = lane & 31, half = lane >> 5;
+            const uint64_t qm = p.qmask ? p.qmask[q] : 0ull;
+            // The rows of a group are asked for by all wavefronts before one of them scores it, piece after piece: a call in two has
+            // such a group, and the kernel is as long as its slowest query.
+            for (uint32_t j = 0; j < again && j < 2; ++j) {
+                const unsigned char *at = static_cast<const unsigned char *>(p.keys) + (size_t)row_of(sh_group[j], tid & 31) * ((size_t)a.d * (KT == KB_BF16 ? 2 : 1));
+                for (int b = tid >> 5; b * 128 < a.d * (KT == KB_BF16 ? 2 : 1); b += bd >> 5) touch(at + (size_t)b * 128);
+            }
+            for (uint32_t j = (uint32_t)(tid >> 6); j < again; j += (uint32_t)(bd >> 6)) {
+                const int slot = sh_group[j];
+                const uint32_t row = row_of(slot, lrow);
+                const size_t at = sample_slot_index(slot, a.group_shift, a.qpad, q);
+                const uint32_t known = candidate_index(a.samp[at]), second = row_of(slot, (int)(a.more[at] & 31u));
+                const f32x16 acc = score_rows<ONCE ? KT : 0, KT == KB_FP8_E4M3 ? 4 : 8>(p.keys, a.queries, a.d, row, q);
+                const float dot = select16(acc, lrow & 15);
+                const int64_t mine = __shfl((int)row, 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3), 64);      // whose product lanes 0..15 of each half hold
+                const float ik = p.inv_norm[mine];
+                bool ok = lrow < 16 && !row_removed(ik) && known != (uint32_t)mine && second != (uint32_t)mine;
+                if (p.qmask) ok = ok && (p.tags[mine] & qm) != 0;
+                if (KEYS) {
+                    const float key = draw_key_of(final_score(dot, ik, iq), p.draw, p.draw.first_query + (uint32_t)q, mine);
+                    const uint64_t w = pack_candidate(key, (uint32_t)mine);
+                    if (ok && key > -__builtin_inff() && w >= t) append(w);
+                } else if (ok && dot * ik >= tp) {
+                    append(pack_raw_candidate(dot * ik, (uint32_t)mine));
+                }
+            }
+            __syncthreads();
+        }
+        if (tid < CAND_SEGMENTS) a.cnt[q * CAND_SEGMENTS + tid] = sh_seg[tid] < seg_cap ? sh_seg[tid] : seg_cap;
+        // (the sample's search does not know infinite products: a query without a length goes the exhaustive way, as where every row ties)
+        if (tid == 0 && (sh_lost != 0 || again > THRESHOLD_AGAIN || (!KEYS && !(iq > 0.f)))) a.flag[q] = 1u;
     }
 }
 
@@ -966,8 +1089,6 @@ struct FinalArgs {
     int32_t raw;              // the lists hold dot * inv_k products (plain queries), not finished candidate words
 };
 
-// KT = KT_FP8_Q8 stands for fp8 keys with fp8 queries (one fp8 matrix instruction per 64-byte chunk, as in the scan).
-constexpr int KT_FP8_Q8 = 3;
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 // 32 dot products of one query by one wavefront, accumulated exactly as the scan kernels do: lane (lrow, half) supplies
 // row my_row for lrow and gets, in element i, the product of the row that lane 8 (i / 4) + 4 half + i % 4 supplied
@@ -1297,11 +1418,14 @@ template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whol
     for (int i = tid; i < WHOLE_BINS; i += nt) kth.hist[i] = 0u;
     __syncthreads();
     const float iq = sh_iq;
+    // score that no row behind a group's product exceeds (infinite products, of a query too long for its length to be a number, have
+    // none themselves but stand for finite ones too)
+    auto score_bound = [&](float product) { return __builtin_amdgcn_fmed3f(product, -0x1.fffffep127f, 0x1.fffffep127f) * iq + 0.0f; };
     float lo = __builtin_inff(), hi = NONE;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         if (v[u] > NONE) {
-            v[u] = v[u] * iq + 0.0f;
+            v[u] = score_bound(v[u]);
             lo = __builtin_fminf(lo, v[u]);
             hi = __builtin_fmaxf(hi, v[u]);
         }
@@ -1316,7 +1440,7 @@ template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whol
     auto append = [&](float product, uint32_t row) {
         const float f = product * iq + 0.0f;
         const uint64_t cw = pack_candidate(f, row);
-        if (product > NONE && passes(f) && cw > sh_thr) buf[atomicAdd(&sh_cnt, 1u)] = cw;
+        if (f > NONE && passes(f) && cw > sh_thr) buf[atomicAdd(&sh_cnt, 1u)] = cw;
     };
     // Cuts the `have` words gathered down to the best k and takes the k-th as the threshold (called converged, nobody
     // appending).
@@ -1344,7 +1468,7 @@ template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whol
             append(as_f32(x[0]), row_at(g, x[2] >> 8 & 255u));
             const uint32_t third = x[2] >> 16 & 255u;
             if (third != 0u) append(as_f32(x[1]), row_at(g, third - 1u));
-            if (as_f32(x[1]) > NONE && passes(as_f32(x[1]) * iq + 0.0f)) again[atomicAdd(&sh_again, 1u)] = (uint16_t)g;
+            if (as_f32(x[1]) > NONE && passes(score_bound(as_f32(x[1])))) again[atomicAdd(&sh_again, 1u)] = (uint16_t)g;
         }
         __syncthreads();
         have = sh_cnt;
@@ -1371,7 +1495,7 @@ template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whol
         for (uint32_t j = (uint32_t)tid; j < asked; j += (uint32_t)nt) {
             const uint32_t g = again[j];
             const u32x4 x = pair[g];
-            const float third = as_f32(x[1]), f = third * iq + 0.0f;
+            const float third = as_f32(x[1]), f = score_bound(third);
             const uint32_t place = x[2] >> 16 & 255u;
             uint64_t most = pack_candidate(f, row_at(g, first_place(g)));       // (the group's lowest row)
             if (place != 0u) {          // known: the others' scores are lower, or equal at higher rows unless the rounding hides a difference
@@ -1825,6 +1949,10 @@ template <int KT> hipError_t launch_probe_scan(const dim3 &grid, const FinalArgs
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&probe_scan_kernel<KT>), allowed, probe_scan_lds<KT>()); e != hipSuccess) return e;
     hipLaunchKernelGGL(probe_scan_kernel<KT>, grid, dim3(PROBE_THREADS), probe_scan_lds<KT>(), s, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists);
     return hipGetLastError();
+}
+template <int QT, bool KEYS, int KT> auto threshold_once(int slots) -> void (*)(ThresholdArgs)
+{
+    return slots <= 2048 ? &threshold_kernel<QT, KEYS, KT, 2> : &threshold_kernel<QT, KEYS, KT, 8>;
 }
 template <int KT> auto whole_select(int groups) -> void (*)(WholeSelectArgs)
 {
@@ -2372,6 +2500,11 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         a.row_run_shift = 0;
         a.row_inv_runs = 0.0;
         a.row_ratio = 0.f;
+        a.sample_runs = 1;
+        a.skip_mul = 0;
+        a.skip_inv = 0.0;
+        a.mixed_runs = 0;
+        a.samp_more = nullptr;
         if (p.sample_tiles > 0) {
             // the sample is spread evenly over the knowledge base: a prefix says nothing about later rows when
             // the rows are grouped (by state, by cluster, by age)
@@ -2380,12 +2513,21 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
             // ... row by row where the kernel can gather (the two-phase and register-tile kernels load whole tiles:
             // they take every tile_stride-th tile instead)
             a.row_run_shift = draw ? 2 : 0;
-            a.row_mul = (p.sample_family == 0 || p.sample_family == 3 || p.sample_family == 4) ? scatter_multiplier(kb->n >> a.row_run_shift) : 0;
+            a.sample_runs = kb->n >> a.row_run_shift;
+            if (p.once) {
+                const int64_t sampled = p.sample_keys >> a.row_run_shift, left = a.sample_runs - sampled;
+                a.sample_runs = sampled;
+                a.skip_mul = (uint32_t)ceil_div(sampled << 32, left);
+                a.skip_inv = 4294967296.0 / (double)a.skip_mul;
+                a.mixed_runs = (uint32_t)(sampled + left) & ~255u;
+                a.samp_more = reinterpret_cast<uint64_t *>(ws + p.off_samp_more);
+            }
+            a.row_mul = scatter_multiplier(a.sample_runs);
             // (the full-line kernel addresses scattered rows in 32 bits, in units of 16 bytes: up to 64 GiB of keys)
             if (p.sample_family == 4 && (uint64_t)kb->n * kb->d * key_bytes(kb->dtype) >= ((uint64_t)1 << 36)) a.row_mul = 0;
-            const int64_t runs = (kb->n >> a.row_run_shift) > 0 ? (kb->n >> a.row_run_shift) : 1;
-            a.row_inv_runs = 1.0 / (double)runs;
-            a.row_ratio = (float)((double)a.row_mul / (double)runs);
+            if (a.sample_runs < 1) a.sample_runs = 1;
+            a.row_inv_runs = 1.0 / (double)a.sample_runs;
+            a.row_ratio = (float)((double)a.row_mul / (double)a.sample_runs);
             int64_t sgrid = p.sample_tiles * p.nqb;
             const int64_t smax = (int64_t)DEVICE_CUS * p.sample_wgpc;
             if (sgrid > smax && p.sample_family != 4) sgrid = smax;        // (the full-line kernel samples one item per workgroup)
@@ -2412,17 +2554,24 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
             t.qpad = p.qpad;
             t.d = kb->d;
             t.grid = p.grid;
-            static LdsAllowed thr_allowed[4];
-            const int thr_kind = draw ? 3 : (int)q_dtype;
-            void (*thr_fn)(ThresholdArgs) = draw ? &threshold_kernel<KB_F32, true>
-                                          : q_dtype == KB_F32 ? &threshold_kernel<KB_F32, false>
-                                          : q_dtype == KB_BF16 ? &threshold_kernel<KB_BF16, false> : &threshold_kernel<KB_FP8_E4M3, false>;
+            t.more = a.samp_more;
+            t.cand = cand;
+            t.cand_cap = p.cand_cap;
+            t.tile_rows = p.sample_tk;
+            t.scan = a;
+            static LdsAllowed thr_allowed[12];
+            const int thr_kind = !p.once ? (draw ? 3 : (int)q_dtype) : (draw ? 4 : kb->dtype == KB_BF16 ? 5 : 6) + (p.sample_slots > 2048 ? 3 : 0);
+            void (*thr_fn)(ThresholdArgs) = p.once ? (draw ? threshold_once<KB_F32, true, KB_BF16>(p.sample_slots) : kb->dtype == KB_BF16 ? threshold_once<KB_BF16, false, KB_BF16>(p.sample_slots) : threshold_once<KB_BF16, false, KB_FP8_E4M3>(p.sample_slots))
+                                          : draw ? &threshold_kernel<KB_F32, true, -1>
+                                          : q_dtype == KB_F32 ? &threshold_kernel<KB_F32, false, -1>
+                                          : q_dtype == KB_BF16 ? &threshold_kernel<KB_BF16, false, -1> : &threshold_kernel<KB_FP8_E4M3, false, -1>;
             if (allow_dynamic_lds(reinterpret_cast<const void *>(thr_fn), thr_allowed[thr_kind], MAX_SAMPLE_SLOTS * 8 + sizeof(SelectScratch)) != hipSuccess)
                 return KB_ERR_DEVICE;
             hipLaunchKernelGGL(thr_fn, dim3(draw ? Q : p.qpad), dim3(thr_threads), thr_lds, s, t);
             if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
         }
-        a.n_tiles = ceil_div(kb->n, p.tk);
+        a.n_keys = p.main_rows;
+        a.n_tiles = ceil_div(a.n_keys, p.tk);
         a.tile_stride = 1;
         a.row_mul = 0;
         const bool timed = kb->prof_events && kb->prof_used < kb->prof_max && kb->prof_seen++ % kb->prof_stride == kb->prof_stride / 2;

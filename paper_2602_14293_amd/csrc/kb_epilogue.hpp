@@ -15,6 +15,7 @@ struct EpiSide {               // side data of the item, in LDS
     const uint64_t *thr64;     // [TQ]  candidate words below this cannot be in the result (read by the weighted selection only)
     const uint64_t *qmask;     // [TQ]
     const float *lgain = nullptr;   // [TK]  ln(gain) of the tile's rows (weighted random selection only)
+    const uint32_t *row = nullptr;  // [TK]  rows of the store behind those of the tile (sampling pass of the tiled kernel)
 };
 
 __device__ inline float select16(const f32x16 &a, int i)
@@ -93,7 +94,8 @@ __device__ inline EpiRows load_rows(const EpiSide &sd, int rl0)
 // product of the two maxima.  For stores whose rows have norms of one size (normalised bf16 or f32 rows) the
 // cheap bound is as good; for fp8 codes, whose norms differ by a factor of two from row to row, it lets nine
 // blocks in ten through where two in ten hold a survivor.
-template <bool EXACT>
+// (MAPPED: the main pass may leave rows out, see main_row)
+template <bool EXACT, bool MAPPED>
 __device__ inline void main_block(const f32x16 &a, const EpiRows &rw, float tp, uint64_t qm, uint32_t query, const EpiSide &sd, bool filter,
                                   int64_t row0, const ScanArgs &p, Record *region, uint32_t &wave_cnt, uint32_t region_id)
 {
@@ -127,8 +129,9 @@ __device__ inline void main_block(const f32x16 &a, const EpiRows &rw, float tp, 
         const uint64_t tg = filter ? sd.tag[rl] : 0ull;         // (in flight during the select)
         const float ikv = sd.invk[rl];
         const float dot = select16(a, i);
-        const int64_t row = row0 + rl;
-        bool ok = has && row < p.n_keys && !row_removed(ikv);
+        const int64_t place = row0 + rl;
+        bool ok = has && place < p.n_keys && !row_removed(ikv);
+        const uint32_t row = MAPPED ? main_row(p, (uint32_t)place) : (uint32_t)place;
         if (filter) ok = ok && (tg & qm) != 0;
         // slot in the wave's own record region: running count + rank among the lanes that append (up to 64 of
         // them: the region is emptied first when fewer slots are left)
@@ -137,7 +140,7 @@ __device__ inline void main_block(const f32x16 &a, const EpiRows &rw, float tp, 
         if (ok) {
             const uint32_t pos = wave_cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(okm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)okm, 0u));
             Record rec;
-            rec.cand = pack_raw_candidate(dot * ikv, (uint32_t)row);       // final_score's first product
+            rec.cand = pack_raw_candidate(dot * ikv, row);       // final_score's first product
             rec.query = query;
             rec.pad = 0;
             region[pos] = rec;
@@ -146,7 +149,7 @@ __device__ inline void main_block(const f32x16 &a, const EpiRows &rw, float tp, 
     }
 }
 
-template <int IB, int JB, bool EXACT = false>
+template <int IB, int JB, bool EXACT = false, bool MAPPED = false>
 __device__ inline void main_epilogue(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0,
                                      int half, int64_t row0, int q0, const ScanArgs &p, Record *region, uint32_t &wave_cnt, uint32_t region_id)
 {
@@ -162,7 +165,7 @@ __device__ inline void main_epilogue(const f32x16 (&acc)[IB][JB], const EpiSide 
         const EpiRows rw = load_rows(sd, wave_row0 + ib * 32 + 4 * half);
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb)
-            main_block<EXACT>(acc[ib][jb], rw, thrp[jb], qm[jb], (uint32_t)(q0 + ql0 + jb * 32), sd, filter, row0, p, region, wave_cnt, region_id);
+            main_block<EXACT, MAPPED>(acc[ib][jb], rw, thrp[jb], qm[jb], (uint32_t)(q0 + ql0 + jb * 32), sd, filter, row0, p, region, wave_cnt, region_id);
     }
 }
 
@@ -234,9 +237,10 @@ __device__ inline void sample_block_lean(const f32x16 &a, int rl0, int id0, cons
     }
 }
 
-template <int IB, int JB, bool LEAN = false>
+// store_row: row of the store behind a row of the tile.
+template <int IB, int JB, bool LEAN, class F>
 __device__ inline void sample_epilogue(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0,
-                                       int half, int64_t row0, int q0, const ScanArgs &p, int64_t slot, int64_t tile_run, int tk)
+                                       int half, int64_t row0, int q0, const ScanArgs &p, int64_t slot, F store_row)
 {
     static_assert(IB * 16 <= 32, "element numbers take five bits");
 #pragma unroll
@@ -262,9 +266,103 @@ __device__ inline void sample_epilogue(const f32x16 (&acc)[IB][JB], const EpiSid
             const float ikv = sd.invk[rl];
             // a removed row, or a row past the end of the knowledge base (the repeated last row of a partial tile): no sample
             if (!row_removed(ikv) && row0 + rl < p.n_keys)
-                cw = pack_candidate(dot * ikv, sample_index(p, tile_run, row0, tk, rl));     // dot * inv_k exactly as final_score's first product
+                cw = pack_candidate(dot * ikv, store_row(rl));     // dot * inv_k exactly as final_score's first product
         }
         p.samp[sample_slot_index(slot, p.sample_group_shift, p.qpad, q0 + ql)] = cw;
+    }
+}
+// The same where the main pass leaves the sampled rows out: everything of a group that can reach the threshold has to be known, so
+// the search keeps the best three (floats, as in the whole-store plan's search below, which order negative products too), the
+// first two are recomputed exactly and the third bounds the rest.  Removed rows (dead: bit r is row r of the wave's 64) and, in the
+// tail of a sample that is whole tiles, repeated ones do not take part.  The side data of four rows serves all columns.
+// 2^20 x 1024 bf16 rows, 256 masked queries, a tile of 256 rows for every compute unit: the pass takes 49.6 us, 43.4 with the best
+// of a group alone; the main pass, 1/16 shorter for it, 473 us instead of 499.
+template <int JB, bool FILTER>
+__device__ inline void sample_search(const f32x16 (&acc)[2][JB], const EpiSide &sd, int wave_row0, int half, const uint64_t (&qm)[JB], uint64_t dead, float none,
+                                     float (&m1)[JB], float (&m2)[JB], float (&m3)[JB])
+{
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib) {
+#pragma unroll
+        for (int run = 0; run < 4; ++run) {
+            int rl = wave_row0 + ib * 32 + 4 * half + 8 * run;
+            asm volatile("" : "+v"(rl));        // (side data of all rows at once would take a hundred registers)
+            const f32x4 ik4 = *reinterpret_cast<const f32x4 *>(sd.invk + rl);
+            const float ik[4] = {ik4.x, ik4.y, ik4.z, ik4.w};
+            u32x4 t0 = {}, t1 = {};
+            if constexpr (FILTER) {
+                t0 = *reinterpret_cast<const u32x4 *>(sd.tag + rl);
+                t1 = *reinterpret_cast<const u32x4 *>(sd.tag + rl + 2);
+            }
+            const uint32_t lo[4] = {t0.x, t0.z, t1.x, t1.z}, hi[4] = {t0.y, t0.w, t1.y, t1.w};
+            const uint32_t dead4 = dead != 0 ? (uint32_t)(dead >> (ib * 32 + 8 * run)) >> (4 * half) : 0u;      // (uniform condition)
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb) {
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = acc[ib][jb][4 * run + e] * ik[e];
+                    if constexpr (FILTER) v[e] = ((lo[e] & (uint32_t)qm[jb]) | (hi[e] & (uint32_t)(qm[jb] >> 32))) != 0 ? v[e] : none;
+                }
+                if (dead != 0) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = (dead4 >> e & 1u) != 0 ? none : v[e];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float f = as_f32((as_u32(v[e]) & ~31u) | (uint32_t)(ib * 16 + 4 * run + e));
+                    m3[jb] = __builtin_amdgcn_fmed3f(m2[jb], m3[jb], f);
+                    m2[jb] = __builtin_amdgcn_fmed3f(m1[jb], m2[jb], f);
+                    m1[jb] = __builtin_fmaxf(m1[jb], f);
+                }
+            }
+        }
+    }
+}
+template <int JB>
+__device__ inline void sample_epilogue_more(const f32x16 (&acc)[2][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0, int half, int64_t row0, int q0,
+                                            const ScanArgs &p, int64_t slot, int64_t tile_run, int tk)
+{
+    const float none = as_f32(0xff7fffe0u);        // the lowest finite value but for its low bits
+    float m1[JB], m2[JB], m3[JB];
+    uint64_t qm[JB];
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) {
+        m1[jb] = m2[jb] = m3[jb] = none;
+        qm[jb] = filter ? sd.qmask[ql0 + jb * 32] : 0ull;
+    }
+    uint64_t dead;
+    {
+        const int lane = threadIdx.x & 63;
+        dead = __builtin_amdgcn_ballot_w64(row_removed(sd.invk[wave_row0 + lane]) || row0 + wave_row0 + lane >= p.n_keys);
+    }
+    if (filter) sample_search<JB, true>(acc, sd, wave_row0, half, qm, dead, none, m1, m2, m3);
+    else sample_search<JB, false>(acc, sd, wave_row0, half, qm, dead, none, m1, m2, m3);
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) {
+        const int ql = ql0 + jb * 32;
+        float value[2];
+        int rl[2], place[2];
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            const float m = w == 0 ? m1[jb] : m2[jb];
+            const int e = (int)(as_u32(m) & 31u), i = e & 15;
+            place[w] = e;
+            rl[w] = wave_row0 + (e >> 4) * 32 + 4 * half + 8 * (i >> 2) + (i & 3);
+            const float dot = e < 16 ? select16(acc[0][jb], i) : select16(acc[1][jb], i);
+            value[w] = dot * sd.invk[rl[w]];
+        }
+        if (q0 + ql >= p.Q) continue;
+        const bool any = m1[jb] > none, two = m2[jb] > none;
+        // (the search's order is that of the values but for their low bits: either may be the larger one)
+        const bool swap = two && value[1] > value[0];
+        const size_t at = sample_slot_index(slot, p.sample_group_shift, p.qpad, q0 + ql);
+        p.samp[at] = any ? pack_candidate(swap ? value[1] : value[0], sample_index<true>(p, tile_run, row0, tk, swap ? rl[1] : rl[0])) : 0ull;
+        if (p.samp_more) {
+            const uint32_t b3 = as_u32(m3[jb]);
+            const uint32_t others = m3[jb] > none ? score_to_ordered(as_f32((int32_t)b3 < 0 ? b3 & ~31u : b3 | 31u)) : 0u;
+            p.samp_more[at] = two ? pack_second(swap ? value[0] : value[1], others, (uint32_t)(swap ? place[0] : place[1])) : 0ull;
+        }
     }
 }
 
@@ -615,17 +713,13 @@ __device__ inline float draw_key_of(float score, const DrawArgs &dr, uint32_t qu
 }
 
 // Keys of the 16 elements a lane holds in one block (four runs of four consecutive rows: four generator calls).
-// SAMPLED: the rows are those of a sampling pass (row0 counts sample rows; runs of four map to their place in the
-// knowledge base).
-template <bool SAMPLED>
 __device__ inline void block_keys(const f32x16 &a, const EpiRows &rw, float iq, const ScanArgs &p, uint32_t query, int64_t row0,
-                                  const EpiSide &sd, float (&key)[16], int64_t tile_run = 0, int tk = 0)
+                                  const EpiSide &sd, float (&key)[16])
 {
     const DrawArgs &dr = p.draw;
 #pragma unroll
     for (int run = 0; run < 4; ++run) {
-        const int64_t logical = row0 + rw.rl0 + 8 * run;       // a multiple of 4
-        const int64_t first = SAMPLED ? (int64_t)sample_index(p, tile_run, row0, tk, rw.rl0 + 8 * run) : logical;
+        const int64_t first = row0 + rw.rl0 + 8 * run;         // a multiple of 4
         uint32_t w[4];
         philox4x32_10((uint32_t)(first >> 2), query, dr.seed_lo, dr.seed_hi, w);
         const f32x4 lg = *reinterpret_cast<const f32x4 *>(sd.lgain + rw.rl0 + 8 * run);
@@ -670,6 +764,7 @@ __device__ inline int noise_floor(float xmax, float tp)
 // test is one integer compare on the generator's output.  What passes (the elements whose key can reach the
 // threshold, and as many again) is handled like the survivors of the score pass, each lane walking its own
 // elements, with the exact key and the exact tests.
+template <bool MAPPED>
 __device__ inline void main_block_draw(const f32x16 &a, const EpiRows &rw, float tp, int ql, const EpiSide &sd, bool filter,
                                        int64_t row0, int q0, const ScanArgs &p, Record *region, uint32_t &wave_cnt, uint32_t region_id)
 {
@@ -691,7 +786,8 @@ __device__ inline void main_block_draw(const f32x16 &a, const EpiRows &rw, float
 #pragma unroll
     for (int run = 0; run < 4; ++run) {
         uint32_t w[4];
-        philox4x32_10((uint32_t)((row0 + rw.rl0 + 8 * run) >> 2), query, dr.seed_lo, dr.seed_hi, w);
+        const uint32_t four = (uint32_t)((row0 + rw.rl0 + 8 * run) >> 2);
+        philox4x32_10(MAPPED ? main_run(p, four) : four, query, dr.seed_lo, dr.seed_hi, w);
 #pragma unroll
         for (int e = 0; e < 4; ++e) pass = (pass << 1) | (w[e] > floor_w ? 1u : 0u);       // element i at bit 15 - i
     }
@@ -705,11 +801,12 @@ __device__ inline void main_block_draw(const f32x16 &a, const EpiRows &rw, float
         pass &= ~(1u << b);
         const int i = 15 - b;
         const int rl = rw.rl0 + 8 * (i >> 2) + (i & 3);
-        const int64_t row = row0 + rl;
+        const int64_t place = row0 + rl;
+        const uint32_t row = MAPPED ? main_row(p, (uint32_t)place) : (uint32_t)place;
         const float ik = sd.invk[rl];
         const float kv = draw_key_of(final_score(select16(a, i), ik, iq), sd.lgain[rl], dr, query, row);
-        const uint64_t cw = pack_candidate(kv, (uint32_t)row);
-        bool ok = has && row < p.n_keys && kv > -__builtin_inff() && cw >= t64 && !row_removed(ik);
+        const uint64_t cw = pack_candidate(kv, row);
+        bool ok = has && place < p.n_keys && kv > -__builtin_inff() && cw >= t64 && !row_removed(ik);
         if (filter) ok = ok && (sd.tag[rl] & qm) != 0;
         const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
         if (okm != 0 && wave_cnt + 64 > (uint32_t)p.region_cap) flush_records(p, region, wave_cnt, region_id);
@@ -725,7 +822,7 @@ __device__ inline void main_block_draw(const f32x16 &a, const EpiRows &rw, float
     } while (__builtin_amdgcn_ballot_w64(pass != 0) != 0);
 }
 
-template <int IB, int JB>
+template <int IB, int JB, bool MAPPED = false>
 __device__ inline void main_epilogue_draw(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0,
                                           int half, int64_t row0, int q0, const ScanArgs &p, Record *region, uint32_t &wave_cnt, uint32_t region_id)
 {
@@ -739,7 +836,7 @@ __device__ inline void main_epilogue_draw(const f32x16 (&acc)[IB][JB], const Epi
                 asm volatile("" : "+v"(rl0));
                 rw = load_rows(sd, rl0);
             }
-            main_block_draw(acc[ib][jb], rw, sd.thrp[ql0 + jb * 32], ql0 + jb * 32, sd, filter, row0, q0, p, region, wave_cnt, region_id);
+            main_block_draw<MAPPED>(acc[ib][jb], rw, sd.thrp[ql0 + jb * 32], ql0 + jb * 32, sd, filter, row0, q0, p, region, wave_cnt, region_id);
         }
     }
 }
@@ -758,7 +855,7 @@ __device__ inline void dense_column_draw(const f32x16 (&acc)[IB][JB], const EpiS
         asm volatile("" : "+v"(rl0));       // (see sample_column_draw)
         const EpiRows rw = load_rows(sd, rl0);
         float key[16];
-        block_keys<false>(acc[ib][JBX], rw, iq, p, p.draw.first_query + (uint32_t)(q0 + ql), row0, sd, key);
+        block_keys(acc[ib][JBX], rw, iq, p, p.draw.first_query + (uint32_t)(q0 + ql), row0, sd, key);
 #pragma unroll
         for (int run = 0; run < 4; ++run) {
             float v[4] = {key[4 * run], key[4 * run + 1], key[4 * run + 2], key[4 * run + 3]};
@@ -780,50 +877,62 @@ __device__ inline void dense_epilogue_draw(const f32x16 (&acc)[IB][JB], const Ep
 // live in scratch memory.
 template <int IB, int JB, int JBX>
 __device__ inline void sample_column_draw(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0,
-                                          int half, int64_t row0, int q0, const ScanArgs &p, int64_t slot, int64_t tile_run, int tk)
+                                          int half, int64_t row0, int q0, const ScanArgs &p, int64_t slot)
 {
     const int ql = ql0 + JBX * 32;
     const float iq = sd.invq[ql];
     const uint64_t qm = filter ? sd.qmask[ql] : 0ull;
     const uint32_t query = p.draw.first_query + (uint32_t)(q0 + ql);
-    float best = -__builtin_inff();
-    int best_rl = -1;
+    float best = -__builtin_inff(), second = -__builtin_inff(), third = -__builtin_inff();
+    int best_e = 0, second_e = 0;
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib) {
         // (the row number is opaque per block: otherwise the side data and the scattered-row arithmetic of all the
         // wave's rows, which do not depend on the column, are kept in registers across the columns and spilled)
         int rl0 = wave_row0 + ib * 32 + 4 * half;
         asm volatile("" : "+v"(rl0));
-        const EpiRows rw = load_rows(sd, rl0);
-        float key[16];
-        block_keys<true>(acc[ib][JBX], rw, iq, p, query, row0, sd, key, tile_run, tk);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int rl = rw.rl0 + 8 * (i >> 2) + (i & 3);
-            bool ok = row0 + rl < p.n_keys && key[i] > best && !row_removed(rw.ik[i]);
-            if (filter) ok = ok && (sd.tag[rl] & qm) != 0;
-            if (ok) {
-                best = key[i];
-                best_rl = rl;
+        for (int run = 0; run < 4; ++run) {         // (four rows at a time, one generator call: few registers)
+            int rl = rl0 + 8 * run;
+            asm volatile("" : "+v"(rl), "+v"(best), "+v"(second), "+v"(third), "+v"(best_e), "+v"(second_e));
+            const f32x4 ik4 = *reinterpret_cast<const f32x4 *>(sd.invk + rl), lg4 = *reinterpret_cast<const f32x4 *>(sd.lgain + rl);
+            const float ik[4] = {ik4.x, ik4.y, ik4.z, ik4.w}, lg[4] = {lg4.x, lg4.y, lg4.z, lg4.w};
+            uint32_t w[4];
+            philox4x32_10(sd.row[rl] >> 2, query, p.draw.seed_lo, p.draw.seed_hi, w);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                bool ok = row0 + rl + e < p.n_keys && !row_removed(ik[e]);
+                if (filter) ok = ok && (sd.tag[rl + e] & qm) != 0;
+                const float key = draw_key(final_score(acc[ib][JBX][4 * run + e], ik[e], iq), lg[e], gumbel_of_word(w[e]), p.draw.inv_t);
+                const float f = ok ? key : -__builtin_inff();
+                const int el = ib * 16 + 4 * run + e;
+                third = __builtin_amdgcn_fmed3f(second, third, f);
+                second_e = f > best ? best_e : f > second ? el : second_e;
+                second = __builtin_amdgcn_fmed3f(best, second, f);
+                best_e = f > best ? el : best_e;
+                best = __builtin_fmaxf(best, f);
             }
         }
     }
-    if (q0 + ql < p.Q)
-        p.samp[sample_slot_index(slot, p.sample_group_shift, p.qpad, q0 + ql)] = best_rl >= 0 ? pack_candidate(best, sample_index(p, tile_run, row0, tk, best_rl)) : 0ull;
+    if (q0 + ql < p.Q) {
+        const size_t at = sample_slot_index(slot, p.sample_group_shift, p.qpad, q0 + ql);
+        p.samp[at] = best > -__builtin_inff() ? pack_candidate(best, sd.row[wave_row0 + (best_e >> 4) * 32 + 4 * half + 8 * (best_e >> 2 & 3) + (best_e & 3)]) : 0ull;
+        if (p.samp_more) p.samp_more[at] = second > -__builtin_inff() ? pack_second(second, third > -__builtin_inff() ? score_to_ordered(third) : 0u, (uint32_t)second_e) : 0ull;
+    }
 }
 
 template <int IB, int JB, int... JBX>
 __device__ inline void sample_columns_draw(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0, int half, int64_t row0,
-                                           int q0, const ScanArgs &p, int64_t slot, int64_t tile_run, int tk, std::integer_sequence<int, JBX...>)
+                                           int q0, const ScanArgs &p, int64_t slot, std::integer_sequence<int, JBX...>)
 {
-    (sample_column_draw<IB, JB, JBX>(acc, sd, filter, wave_row0, ql0, half, row0, q0, p, slot, tile_run, tk), ...);
+    (sample_column_draw<IB, JB, JBX>(acc, sd, filter, wave_row0, ql0, half, row0, q0, p, slot), ...);
 }
 
 template <int IB, int JB>
 __device__ inline void sample_epilogue_draw(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0,
-                                            int half, int64_t row0, int q0, const ScanArgs &p, int64_t slot, int64_t tile_run, int tk)
+                                            int half, int64_t row0, int q0, const ScanArgs &p, int64_t slot)
 {
-    sample_columns_draw<IB, JB>(acc, sd, filter, wave_row0, ql0, half, row0, q0, p, slot, tile_run, tk, std::make_integer_sequence<int, JB>{});
+    sample_columns_draw<IB, JB>(acc, sd, filter, wave_row0, ql0, half, row0, q0, p, slot, std::make_integer_sequence<int, JB>{});
 }
 
 }  // namespace kbi

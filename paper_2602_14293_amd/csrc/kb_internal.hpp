@@ -78,6 +78,17 @@ __host__ __device__ inline bool row_removed(float inv_k) { return (as_u32(inv_k)
 // KB_FP8_E4M3 either way, but both operands go to the fp8 matrix instruction as they are stored.
 constexpr int KB_FP8_Q8 = 3;
 
+// Sampling pass whose rows the main pass leaves out: what is known of a group of 32 rows besides its best.  The second best
+// row's value as an ordered score | the upper 27 bits, rounded up, of an ordered score that no other row is above | the second's
+// place, element e of the lane's 32.  0: the group has one row at most.
+__host__ __device__ inline uint64_t pack_second(float value, uint32_t others, uint32_t place)
+{
+    const uint32_t up = others == 0u ? 0u : others > 0xffffffe0u ? 0x07ffffffu : (others + 31u) >> 5;
+    return ((uint64_t)score_to_ordered(value) << 32) | up << 5 | place;
+}
+// ... the bound on the others (0: there are none; a value between two ordered scores is as good as the upper one)
+__host__ __device__ inline uint32_t others_bound(uint64_t second) { return (uint32_t)second & ~31u; }
+
 struct Record {  // one candidate that passed the threshold filter of the scan
     uint64_t cand;
     uint32_t query;
@@ -112,6 +123,9 @@ struct Plan {
     int32_t region_cap;                 // records a scan wavefront collects before it moves them to the lists
     int32_t regions;                    // grid * wavefronts per workgroup
     int32_t cand_cap;                   // candidates per query the final sort can take (power of two)
+    bool once;                              // the main pass leaves out what the sampling pass scored
+    int64_t main_rows;                      // rows of the main pass
+    size_t off_samp_more;
     size_t off_fb_done, off_fb_lists;       // exhaustive path: per-query arrival counters, per-(query, part) partial lists
     int32_t fb_parts;                      // parts the rows are split into when a query takes the exhaustive path
     size_t off_invq, off_thr64, off_thrp, off_cnt, off_flag, off_stats, off_qmask, off_samp, off_regions,
@@ -172,6 +186,7 @@ struct ScanArgs {
     const uint64_t *thr64;    // [qpad] candidate words below this cannot be in the result
     const float *thrp;        // [qpad] conservative pre-filter on dot * inv_k
     uint64_t *samp;           // sampling pass output [sample tiles][qpad][groups per tile]: see sample_slot_index
+    uint64_t *samp_more;      // ... and the group's second best row with a bound on the others (see pack_second); nullptr: not wanted
     Record *regions;          // [grid * waves per workgroup][region_cap]: one private region per wavefront
     uint64_t *cand;           // [qpad][cand_cap] per-query candidate lists, CAND_SEGMENTS segments each
     uint32_t *cnt;            // [qpad][CAND_SEGMENTS] entries claimed in each segment (zero before the launch)
@@ -181,9 +196,13 @@ struct ScanArgs {
     int64_t n_tiles;          // key tiles to scan: logical tile t is rows [t * tile_stride * TK, +TK)
     int32_t tile_stride;      // 1 for the main pass; a sampling pass takes every tile_stride-th tile ...
     uint64_t row_mul;         // ... or, when nonzero, scatters its rows in runs of 2^row_run_shift (see sample_row)
-    double row_inv_runs;      // 1 / (n_keys >> row_run_shift)
-    float row_ratio;          // row_mul / (n_keys >> row_run_shift)
+    int64_t sample_runs;      // runs that the scatter goes over
+    double row_inv_runs;      // 1 / sample_runs
+    float row_ratio;          // row_mul / sample_runs
     int32_t row_run_shift;
+    uint32_t skip_mul;        // the main pass leaves out what the sampling pass scored: see main_row (0: it does not)
+    double skip_inv;          // 2^32 / skip_mul
+    uint32_t mixed_runs;      // runs whose order is mixed (see mixed)
     int32_t d, Q, nqb, qpad, sample_slots, sample_group_shift, region_cap, cand_cap;
     DrawArgs draw;
     int32_t keys_once;        // the launch reads keys that no cache holds and nobody reads again: see stream_keys
@@ -204,13 +223,47 @@ struct ScanArgs {
 // 16-byte load of gains).  Without row_mul the tile is tile_stride tiles further on and rows past the end repeat
 // the last row.
 //
+// Where the main pass leaves the sample out (skip_mul, see main_row), the scatter goes over the runs that are left out instead of
+// all, and run m of those lies at sampled_run(m).  (SKIP: kernels that sample for such a main pass.)
+//
 // The map is linear, so a workgroup maps the first run of its tile once (sample_tile_run: exact 64-bit arithmetic with
 // a quotient estimated in double precision; a 64-bit division would be a software routine of some hundred
 // instructions) and every row of the tile from that (sample_row: the product of a run number below 256 with row_mul
 // has a quotient below 256, which single precision estimates to within one).
+// The division of the store between the two passes: with n_keys >> row_run_shift = U runs, S of them sampled and M = U - S
+// left, the main pass's run m (m <= M, the last one being the rows past the last whole run) is run m + floor(m a / 2^32) of the
+// store with a = skip_mul = ceil(2^32 S / M): the multiple steps over one run whenever the quotient grows, evenly, S times up to M.
+// One multiplication a row, and the rows of a tile stay neighbours.  Stores of 2^20 rows would have every sampled row at the same
+// place of each 32 KiB, in a few of the memory's channels (sampling pass 55 us, 46 with 1,000,003 rows), so both passes count the
+// runs in an order in which each block of 16 is turned by the number of the block.
+__device__ inline uint32_t mixed(const ScanArgs &p, uint32_t run) { return run < p.mixed_runs ? run ^ (run >> 4 & 15u) : run; }
+__device__ inline uint32_t main_run(const ScanArgs &p, uint32_t run) { return mixed(p, run + __umulhi(run, p.skip_mul)); }
+__device__ inline uint32_t main_row(const ScanArgs &p, uint32_t row)
+{
+    const int sh = p.row_run_shift;
+    return main_run(p, row >> sh) << sh | (row & ((1u << sh) - 1u));
+}
+// no row from `row` on is below this (nor in the tile that begins there)
+__device__ inline uint32_t main_base(const ScanArgs &p, uint32_t row)
+{
+    const int sh = p.row_run_shift;
+    const uint32_t run = row >> sh, at = run + __umulhi(run, p.skip_mul);
+    return (p.mixed_runs ? at & ~15u : at) << sh;
+}
+// Run j (0 <= j < S) of those stepped over: it follows the first m whose quotient is j + 1.  (The estimate in double precision is
+// off by one at most.)
+__device__ inline int64_t sampled_run(const ScanArgs &p, int64_t j)
+{
+    const uint32_t want = (uint32_t)j + 1u;
+    const double x = (double)want * p.skip_inv;
+    uint32_t m = x > 1.0 ? (uint32_t)x - 1u : 0u;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) m += __umulhi(m, p.skip_mul) < want ? 1u : 0u;
+    return (int64_t)mixed(p, m + (uint32_t)j);
+}
 __device__ inline int64_t mulmod_runs(const ScanArgs &p, int64_t run)      // (run * row_mul) mod runs, run < runs < 2^31
 {
-    const int64_t runs = p.n_keys >> p.row_run_shift, prod = run * (int64_t)p.row_mul;
+    const int64_t runs = p.sample_runs, prod = run * (int64_t)p.row_mul;
     int64_t r = prod - (int64_t)((double)prod * p.row_inv_runs) * runs;
     r += r < 0 ? runs : 0;
     r -= r >= runs ? runs : 0;
@@ -220,11 +273,11 @@ __device__ inline int64_t sample_tile_run(const ScanArgs &p, int64_t tile, int t
 {
     return p.row_mul ? mulmod_runs(p, (tile * tk) >> p.row_run_shift) : 0;
 }
-__device__ inline int64_t sample_row(const ScanArgs &p, int64_t tile_run, int64_t tile, int tk, int r)     // 0 <= r < tk <= 256
+template <bool SKIP> __device__ inline int64_t sample_row(const ScanArgs &p, int64_t tile_run, int64_t tile, int tk, int r)     // 0 <= r < tk <= 256
 {
     if (p.row_mul) {
         const int sh = p.row_run_shift;
-        const int64_t runs = p.n_keys >> sh;
+        const int64_t runs = p.sample_runs;
         const uint32_t lr = (uint32_t)r >> sh;                                          // run within the tile
         const uint32_t q = (uint32_t)((float)lr * p.row_ratio);                         // floor(lr * row_mul / runs), or one off
         int64_t m = (int64_t)((uint64_t)lr * p.row_mul) - (int64_t)((uint64_t)q * (uint64_t)runs);
@@ -232,6 +285,7 @@ __device__ inline int64_t sample_row(const ScanArgs &p, int64_t tile_run, int64_
         m -= m >= runs ? runs : 0;
         m += tile_run;
         m -= m >= runs ? runs : 0;
+        if (SKIP && p.skip_mul) m = sampled_run(p, m);
         return (m << sh) + (r & ((1 << sh) - 1));
     }
     const int64_t row = tile * p.tile_stride * tk + r;
@@ -240,9 +294,9 @@ __device__ inline int64_t sample_row(const ScanArgs &p, int64_t tile_run, int64_
 // first row number the sampling epilogues count from: logical when the rows are scattered
 __device__ inline int64_t sample_row0(const ScanArgs &p, int64_t tile, int tk) { return p.row_mul ? tile * tk : tile * p.tile_stride * tk; }
 // knowledge-base row of tile-local row rl of a sampling pass whose epilogue counts rows from row0 = sample_row0()
-__device__ inline uint32_t sample_index(const ScanArgs &p, int64_t tile_run, int64_t row0, int tk, int rl)
+template <bool SKIP> __device__ inline uint32_t sample_index(const ScanArgs &p, int64_t tile_run, int64_t row0, int tk, int rl)
 {
-    return (uint32_t)(p.row_mul ? sample_row(p, tile_run, 0, tk, rl) : row0 + rl);
+    return (uint32_t)(p.row_mul ? sample_row<SKIP>(p, tile_run, 0, tk, rl) : row0 + rl);
 }
 
 // Knowledge-base row at place `pos` of a tile of the whole-store plan (>= n_keys: none).  The rows of a tile are not

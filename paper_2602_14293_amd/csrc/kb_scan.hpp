@@ -152,7 +152,10 @@ struct ScanCfg {
     static constexpr int OFF_INVQ = OFF_QMASK + TQ * 8;
     static constexpr int OFF_THRP = OFF_INVQ + TQ * 4;
     static constexpr int OFF_LGAIN = OFF_THRP + TQ * 4;
-    static constexpr int SMEM_BYTES = OFF_LGAIN + TK * 4;
+    // sampling pass: the tile's rows in the place of what it does not use, ln(gain), or with the weighted selection the threshold
+    // words where they are enough
+    static constexpr int OFF_ROW = OFF_LGAIN, OFF_ROW_DRAW = TQ * 8 >= TK * 4 ? OFF_THR64 : OFF_LGAIN + TK * 4;
+    static constexpr int SMEM_BYTES = OFF_LGAIN + TK * 4 + (TQ * 8 >= TK * 4 ? 0 : TK * 4);
     // whole-store plan: the bit map of the tile's dead rows and the waves' exchange take the place of what it does not use
     static constexpr int OFF_DEAD = OFF_INVQ;
     static constexpr int OFF_EXCHANGE = OFF_DEAD + 16;
@@ -213,6 +216,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
     uint64_t *aux_qmask = reinterpret_cast<uint64_t *>(smem + C::OFF_QMASK);
     float *aux_invq = reinterpret_cast<float *>(smem + C::OFF_INVQ);
     float *aux_lgain = reinterpret_cast<float *>(smem + C::OFF_LGAIN);
+    uint32_t *aux_row = reinterpret_cast<uint32_t *>(smem + (DRAW ? C::OFF_ROW_DRAW : C::OFF_ROW));
 
     // items: (tile, qb) with qb fastest
     const int nqb = p.nqb;
@@ -248,7 +252,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
             // (opaque in a sampling pass: the tile-independent part of the scattered-row arithmetic would otherwise be kept
             // per lane and load across the items, in registers that end up spilled)
             if constexpr (SAMPLE) asm volatile("" : "+v"(r));
-            if constexpr (SAMPLE) offA[j] = (uint64_t)sample_row(p, tile_run, ld_tile, TK, r) * key_row_bytes + ldA_piece;
+            if constexpr (SAMPLE) offA[j] = (uint64_t)sample_row<DRAW>(p, tile_run, ld_tile, TK, r) * key_row_bytes + ldA_piece;
             else if constexpr (WHOLE) {
                 const int64_t row = whole_row(ld_tile, (int32_t)p.n_tiles, TK, r);
                 offA[j] = (uint64_t)(row < p.n_keys ? row : p.n_keys - 1) * key_row_bytes + (SAME_SWZ_A ? ldA_piece : (uint32_t)((((wave * 64 + lane) % C::PPRA) ^ swizzle<C::PPRA>(r)) * 16));
@@ -311,6 +315,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
     float my_invk = 0.f, my_invq = 0.f, my_lgain = 0.f;
     uint64_t my_tag = 0, my_thr64 = 0, my_qmask = 0;
     float my_thrp = __builtin_inff();
+    uint32_t my_row = 0;
     const int aux_chunk = NC >= 2 ? NC - 2 : 0;
 
     for (int g = 0; g < total; ++g) {
@@ -331,7 +336,8 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 if constexpr (SAMPLE) {
                     int rl = tid;
                     asm volatile("" : "+v"(rl));
-                    r = sample_row(p, sample_tile_run(p, tile, TK), tile, TK, rl);
+                    r = sample_row<DRAW>(p, sample_tile_run(p, tile, TK), tile, TK, rl);
+                    my_row = (uint32_t)r;
                 }
                 if constexpr (WHOLE) {
                     r = whole_row(tile, (int32_t)p.n_tiles, TK, tid);
@@ -401,25 +407,26 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 aux_invk[tid] = my_invk;
                 aux_tag[tid] = my_tag;
                 if constexpr (DRAW) aux_lgain[tid] = my_lgain;
+                if constexpr (SAMPLE) aux_row[tid] = my_row;
             }
             if (tid < TQ) {
                 aux_qmask[tid] = my_qmask;
                 if constexpr (!WHOLE) {
                     aux_invq[tid] = my_invq;
-                    aux_thr64[tid] = my_thr64;
+                    if constexpr (!SAMPLE) aux_thr64[tid] = my_thr64;
                     reinterpret_cast<float *>(smem + C::OFF_THRP)[tid] = my_thrp;
                 }
             }
             __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0());
             bare_barrier();
             const int64_t row0 = SAMPLE ? sample_row0(p, tile, TK) : tile * tstride * TK;
-            const EpiSide sd{aux_invk, aux_tag, reinterpret_cast<const float *>(smem + C::OFF_THRP), aux_invq, aux_thr64, aux_qmask, aux_lgain};
+            const EpiSide sd{aux_invk, aux_tag, reinterpret_cast<const float *>(smem + C::OFF_THRP), aux_invq, aux_thr64, aux_qmask, aux_lgain, aux_row};
             if (SAMPLE && DRAW)
                 sample_epilogue_draw<IB, JB>(acc, sd, filter, rowA - lrow, rowB, half, row0, qb * TQ, p,
-                                             (int64_t)tile * C::GROUPS_PER_TILE + wm * 2 + half, sample_tile_run(p, tile, TK), TK);
+                                             (int64_t)tile * C::GROUPS_PER_TILE + wm * 2 + half);
             else if (SAMPLE)
                 sample_epilogue<IB, JB, (IB * JB >= 8)>(acc, sd, filter, rowA - lrow, rowB, half, row0, qb * TQ, p,      // (128 accumulators: the search that needs few registers)
-                                        (int64_t)tile * C::GROUPS_PER_TILE + wm * 2 + half, sample_tile_run(p, tile, TK), TK);
+                                        (int64_t)tile * C::GROUPS_PER_TILE + wm * 2 + half, [&](int rl) { return aux_row[rl]; });
             else if constexpr (WHOLE) {
                 const uint64_t *dead_map = reinterpret_cast<const uint64_t *>(smem + C::OFF_DEAD);
                 uint64_t dead = dead_map[wm * IB / 2];              // 64 rows a word

@@ -134,7 +134,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_sp_kernel(ScanArgs p)
             // the tile: computed once per lane and load and kept across the items, those values are spilled and each
             // reload waits for every stream load in flight; r is therefore opaque here and the map is computed per tile)
             if constexpr (SAMPLE) asm volatile("" : "+v"(r));
-            if (SAMPLE && role == 0) off[j] = (Off)((uint64_t)sample_row(p, tile_run, ld_tile, TK, r) * row_bytes + ld_piece);
+            if (SAMPLE && role == 0) off[j] = (Off)((uint64_t)sample_row<false>(p, tile_run, ld_tile, TK, r) * row_bytes + ld_piece);
             else off[j] = (uint32_t)(r < last ? r : last) * row_bytes + ld_piece;
         }
         ld_base = role == 0 ? (SAMPLE ? 0 : (size_t)(ld_tile * tstride) * TK * row_bytes) : (size_t)ld_qb * TQ * row_bytes;
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_sp_kernel(ScanArgs p)
             if constexpr (SAMPLE) {
                 int rl = wave * 64 + lane;
                 asm volatile("" : "+v"(rl));
-                r = sample_row(p, tile_run, ld_tile, TK, rl);
+                r = sample_row<false>(p, tile_run, ld_tile, TK, rl);
             }
             __builtin_amdgcn_global_load_lds((const void *)(p.inv_norm + r), (lds_ptr)(aux + C::AUX_INVK + wave * 256), 4, 0, 0);
         }
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_sp_kernel(ScanArgs p)
             if constexpr (SAMPLE) {
                 int rl = wave * 32 + (lane >> 1);
                 asm volatile("" : "+v"(rl));
-                r = sample_row(p, tile_run, ld_tile, TK, rl);
+                r = sample_row<false>(p, tile_run, ld_tile, TK, rl);
             }
             __builtin_amdgcn_global_load_lds((const void *)(reinterpret_cast<const uint32_t *>(p.tags + r) + (lane & 1)),
                                              (lds_ptr)(aux + C::AUX_TAG + wave * 256), 4, 0, 0);
@@ -290,6 +290,9 @@ __global__ __launch_bounds__(512, 1) void kb_scan_sp_kernel(ScanArgs p)
         // sits in registers the software pipeline needs, gets spilled, and a reload queues behind the stream
         // loads in flight.
         int rowB_e = rowB, half_e = half;
+        tile = __builtin_amdgcn_readfirstlane(tile);
+        qb = __builtin_amdgcn_readfirstlane(qb);
+        par = __builtin_amdgcn_readfirstlane(par);
         asm volatile("" : "+s"(tile), "+s"(qb), "+s"(par), "+v"(rowB_e), "+v"(half_e));
         const int rowB = rowB_e, half = half_e;
         const unsigned char *aux = smem + C::OFF_AUX + par * C::AUX_BYTES, *qaux = smem + C::OFF_QAUX;
@@ -298,8 +301,11 @@ __global__ __launch_bounds__(512, 1) void kb_scan_sp_kernel(ScanArgs p)
                          reinterpret_cast<const uint64_t *>(qaux + C::QAUX_THR64), reinterpret_cast<const uint64_t *>(qaux + C::QAUX_QMASK)};
         const int64_t row0 = SAMPLE ? sample_row0(p, tile, TK) : tile * tstride * TK;
         if (SAMPLE)
-            sample_epilogue<IB, JB, true>(acc, sd, filter, wm * 64, rowB, half, row0, qb * TQ, p,
-                                    (int64_t)tile * C::GROUPS_PER_TILE + wm * 2 + half, sample_tile_run(p, tile, TK), TK);
+        {
+            const int64_t tile_run = sample_tile_run(p, tile, TK);
+            sample_epilogue<IB, JB, true>(acc, sd, filter, wm * 64, rowB, half, row0, qb * TQ, p, (int64_t)tile * C::GROUPS_PER_TILE + wm * 2 + half,
+                                          [&](int rl) { return sample_index<false>(p, tile_run, row0, TK, rl); });
+        }
         else
             main_epilogue<IB, JB, C::KEY_BYTES == 1>(acc, sd, filter, wm * 64, rowB, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
 #pragma unroll

@@ -1,6 +1,6 @@
 // The large-batch scan kernel, full-line version: 256 key rows x 256 queries per work item on eight wavefronts
 // like kb_scan_sp.hpp, but the direct-to-LDS loads fetch 128 bytes of every key row and of every query row at a
-// time (gfx950 only; bf16).
+// time (gfx950 only; bf16, fp8).
 //
 // Why 128-byte rows.  A direct-to-LDS load instruction moves 1 KiB; with 64-byte row pieces it covers half of
 // 16 cache lines and the other halves are asked for again one d-chunk later, with 128-byte pieces it covers 8
@@ -32,6 +32,16 @@
 // With 128-query blocks (the second configuration) a query chunk is one piece, the ring holds seven key pieces and
 // two query pieces (six phases for a key piece to land), and a wave multiplies its 64 rows with 32 queries.
 //
+// fp8 keys with bf16 queries: a 128-byte key piece meets two query chunks of 64 elements (see the two_chunks lambda); 64-byte
+// pieces of the same rows left the matrix cores idle for want of keys (4,194,304 x 768, 1024 queries: call 6.3 -> 5.9 ms).
+//
+// The main pass goes over the rows that the sampling pass has not scored (main_row; the threshold kernel lists the results among
+// the others).  These kernels are limited by the power of the chip: a sixteenth less work is a sixteenth less time, and the sample is
+// made whole rounds of the compute units, so that both passes fill the chip.  Measured, call with the sampled rows scored
+// twice -> once: 2^20 x 1024 bf16, 256 masked queries, k = 32: 562 -> 538 us; 4,194,304 x 768 fp8, 1024 queries, k = 64: 5.93 ->
+// 5.58 ms; 2^20 x 1024 bf16, 256 draws, k = 32: 738 -> 715 us.  Not with fp8 queries: a sampling workgroup takes one item, which the
+// fp8 matrix instruction finishes before the next could be on its way (sampling pass 61 us, the 64-byte-piece kernel 51; call 687 -> 698).
+//
 // Accumulation order over d, lane-to-element mapping and epilogue are those of the other scan kernels, so the
 // scores are bit-identical to theirs.
 #pragma once
@@ -53,6 +63,7 @@ template <int KT_, int TQ_, bool QF8_ = false> struct WideCfg {
     static constexpr int KT = KT_;
     static constexpr bool QF8 = QF8_;                                // fp8 keys AND fp8 queries: the fp8 matrix instruction
     static constexpr int TK = 256, TQ = TQ_, THREADS = 512, NW = 8;
+    static constexpr bool MAPPED = !QF8;                             // the main pass can leave sampled rows out (main_row)
     static constexpr int KEY_BYTES = KeyTraits<KT>::KEY_BYTES, QRY_BYTES = QF8 ? 1 : KeyTraits<KT>::QRY_BYTES;
     static constexpr bool MIX = QRY_BYTES != KEY_BYTES;              // fp8 keys with bf16 queries: a key piece serves two query chunks
     static constexpr int RB = 128;                                   // bytes of a query row per d-chunk, and of a key row per piece
@@ -141,12 +152,14 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
     uint32_t off[2][4];
     auto ld_setup = [&]() {
         int last, base;
+        uint32_t row_base = 0;
         if (role == 0) {
             const int64_t tile_row0 = (int64_t)ld_tile * (SAMPLE ? p.tile_stride : 1) * TK;      // (unless the sample is scattered)
             const int64_t left = p.n_keys - tile_row0;
             last = left < TK ? (int)left - 1 : TK - 1;
             base = 0;
-            ld_src = static_cast<const unsigned char *>(p.keys) + ((SAMPLE && p.row_mul) ? 0 : (size_t)tile_row0 * key_row_bytes);
+            row_base = SAMPLE || !C::MAPPED ? (uint32_t)tile_row0 : main_base(p, (uint32_t)tile_row0);
+            ld_src = static_cast<const unsigned char *>(p.keys) + ((SAMPLE && p.row_mul) ? 0 : (size_t)row_base * key_row_bytes);
         } else {
             last = p.Q - 1 - ld_qb * TQ;
             base = ld_qb * TQ;
@@ -159,7 +172,8 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = h * C::PIECE_ROWS + ld_row + j * 32;
-                if (SAMPLE && role == 0 && p.row_mul) off[h][j] = (uint32_t)(((uint64_t)sample_row(p, tile_run, ld_tile, TK, r) * rb + ld_slot) >> 4);
+                if (SAMPLE && role == 0 && p.row_mul) off[h][j] = (uint32_t)(((uint64_t)sample_row<true>(p, tile_run, ld_tile, TK, r) * rb + ld_slot) >> 4);
+                else if (!SAMPLE && C::MAPPED && role == 0) off[h][j] = (main_row(p, (uint32_t)ld_tile * TK + (uint32_t)(r < last ? r : last)) - row_base) * rb + ld_slot;
                 else off[h][j] = ((uint32_t)(base + (r < last ? r : last)) * rb + ld_slot) >> (role == 0 ? OSH : 0);
             }
     };
@@ -173,13 +187,13 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
         asm volatile("" : "+v"(lane));
         if constexpr (SAMPLE) {
             const int64_t tile_run = sample_tile_run(p, ld_tile, TK);
-            const int64_t r = sample_row(p, tile_run, ld_tile, TK, ridx * 64 + lane);
+            const int64_t r = sample_row<true>(p, tile_run, ld_tile, TK, ridx * 64 + lane);
             __builtin_amdgcn_global_load_lds((const void *)(p.inv_norm + r), (lds_ptr)(aux + C::AUX_INVK + ridx * 256), 4, 0, 0);
             if (filter) {
 #pragma unroll
                 for (int h2 = 0; h2 < 2; ++h2) {
                     const int i = ridx * 2 + h2;
-                    const int64_t rt = sample_row(p, tile_run, ld_tile, TK, i * 32 + (lane >> 1));
+                    const int64_t rt = sample_row<true>(p, tile_run, ld_tile, TK, i * 32 + (lane >> 1));
                     __builtin_amdgcn_global_load_lds((const void *)(reinterpret_cast<const uint32_t *>(p.tags + rt) + (lane & 1)),
                                                      (lds_ptr)(aux + C::AUX_TAG + i * 256), 4, 0, 0);
                 }
@@ -189,23 +203,20 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
         const int64_t row0 = (int64_t)ld_tile * TK;
         const int64_t left = p.n_keys - row0;
         const uint32_t last = left < TK ? (uint32_t)left - 1 : TK - 1;
-        {
-            const uint32_t r = (uint32_t)(ridx * 64 + lane);
-            const unsigned char *g = uniform_address(p.inv_norm + row0);
-            __builtin_amdgcn_global_load_lds((const void *)(g + (r < last ? r : last) * 4u), (lds_ptr)(aux + C::AUX_INVK + ridx * 256), 4, 0, 0);
-        }
-        if constexpr (DRAW) {
-            const uint32_t r = (uint32_t)(ridx * 64 + lane);
-            const unsigned char *g = uniform_address(p.draw.log_gain + row0);
-            __builtin_amdgcn_global_load_lds((const void *)(g + (r < last ? r : last) * 4u), (lds_ptr)(aux + C::AUX_LGAIN + ridx * 256), 4, 0, 0);
-        }
+        const uint32_t base = C::MAPPED ? __builtin_amdgcn_readfirstlane(main_base(p, (uint32_t)row0)) : (uint32_t)row0;
+        auto from_base = [&](uint32_t r) {
+            const uint32_t rr = r < last ? r : last;
+            return C::MAPPED ? main_row(p, (uint32_t)row0 + rr) - base : rr;
+        };
+        const uint32_t mine = from_base((uint32_t)(ridx * 64 + lane)) * 4u;
+        __builtin_amdgcn_global_load_lds((const void *)(uniform_address(p.inv_norm + base) + mine), (lds_ptr)(aux + C::AUX_INVK + ridx * 256), 4, 0, 0);
+        if constexpr (DRAW) __builtin_amdgcn_global_load_lds((const void *)(uniform_address(p.draw.log_gain + base) + mine), (lds_ptr)(aux + C::AUX_LGAIN + ridx * 256), 4, 0, 0);
         if (filter) {
-            const unsigned char *g = uniform_address(p.tags + row0);
+            const unsigned char *g = uniform_address(p.tags + base);
 #pragma unroll
             for (int h2 = 0; h2 < 2; ++h2) {        // tags as dwords: instruction i covers rows [32 i, 32 i + 32)
                 const int i = ridx * 2 + h2;
-                const uint32_t r = (uint32_t)(i * 32 + (lane >> 1));
-                __builtin_amdgcn_global_load_lds((const void *)(g + ((r < last ? r : last) * 8u + (lane & 1) * 4u)),
+                __builtin_amdgcn_global_load_lds((const void *)(g + (from_base((uint32_t)(i * 32 + (lane >> 1))) * 8u + (lane & 1) * 4u)),
                                                  (lds_ptr)(aux + C::AUX_TAG + i * 256), 4, 0, 0);
             }
         }
@@ -335,12 +346,12 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
 #pragma unroll
         for (int rh = 0; rh < 2; ++rh) {
             if constexpr (SAMPLE)       // sampling groups: (piece, wave row, lane half) = 32 rows each
-                sample_epilogue<IB, JB>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p,
+                sample_epilogue_more<JB>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p,
                                         (int64_t)tile * C::GROUPS_PER_TILE + (rh * 2 + wm) * 2 + half, tile_run, TK);
             else if constexpr (DRAW)
-                main_epilogue_draw<IB, JB>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
+                main_epilogue_draw<IB, JB, C::MAPPED>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
             else
-                main_epilogue<IB, JB, C::KEY_BYTES == 1>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
+                main_epilogue<IB, JB, C::KEY_BYTES == 1, C::MAPPED>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
         }
     };
 
@@ -695,7 +706,9 @@ template <class C> hipError_t launch_scan_wide_cfg(bool sample, int grid, const 
 {
     const bool draw = a.draw.enabled != 0;
     if (draw && sample) return hipErrorInvalidValue;                 // keys of the weighted random selection: main pass only
-    if constexpr (C::KEY_BYTES == 1) {      // fp8: the sampling pass runs the 64-byte-piece kernel (fewer registers)
+    if constexpr (C::MIX) {
+        return draw ? hipErrorInvalidValue : sample ? launch_scan_wide_policy<C, true, false>(grid, a, s) : launch_scan_wide_policy<C, false, false>(grid, a, s);
+    } else if constexpr (C::QF8) {      // fp8 queries: the 64-byte-piece kernel samples, several items a workgroup (51 us against 61 on 2,500,001 x 512 rows)
         return sample || draw ? hipErrorInvalidValue : launch_scan_wide_policy<C, false, false>(grid, a, s);
     } else {
         return sample ? launch_scan_wide_policy<C, true, false>(grid, a, s)
