@@ -52,12 +52,18 @@ bool scan_config_info(int key_dtype, int config, ConfigInfo *out)
 #undef X
 #define XS(ID, KT, TQ, NSA, NSB)                                              \
     if (key_dtype == KT && config == ID) {                                    \
-        *out = ConfigInfo{256, TQ, 512, 8, 1, 64 * ((NSA > NSB ? NSA : NSB) + 1), 3}; \
+        *out = ConfigInfo{256, TQ, 512, 8, 1, pipelined_min_row_bytes(NSA > NSB ? NSA : NSB, INTERLEAVED), 3}; \
         return true;                                                          \
     }
-    KB_SCAN_SP_CONFIGS_BF16_IL(XS)
-    KB_SCAN_SP_CONFIGS_FP8(XS)
-    KB_SCAN_SP_CONFIGS_FP8_Q8(XS)
+    {
+        constexpr bool INTERLEAVED = true;
+        KB_SCAN_SP_CONFIGS_BF16_IL(XS)
+        KB_SCAN_SP_CONFIGS_FP8_Q8(XS)
+    }
+    {
+        constexpr bool INTERLEAVED = false;
+        KB_SCAN_SP_CONFIGS_FP8(XS)
+    }
 #undef XS
 #define XW(ID, KT, TQ)                                                        \
     if (key_dtype == KT && config == ID) {                                    \
@@ -86,8 +92,8 @@ int scan_config_for(int key_dtype, int Q, int d, int64_t n)
     if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= 512) return 18;
     // 33 to 128 queries: the full-line kernel once a workgroup has several tiles to stream (its ring takes longer to fill)
     if (key_dtype == KB_BF16 && Q > 32 && d * 2 >= 512 && n >= WIDE128_MIN_ROWS) return 19;
-    if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= 384) return 17;
-    if (key_dtype == KB_FP8_E4M3 && Q > 128 && d >= 256) return d % 128 == 0 ? FP8_WIDE_CONFIG : 4;
+    if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= 256) return 17;
+    if (key_dtype == KB_FP8_E4M3 && Q > 128 && d >= 192) return d >= 256 && d % 128 == 0 ? FP8_WIDE_CONFIG : 4;
     // below that size a query is bound by the latency of its launches: tiles of 64 rows (twice the workgroups, half the
     // chunks each) finish sooner: 62 against 71 us per call on 65,536 rows of 768 bf16 values with 64 queries
     // (and 64 against 70 us with 128 queries)
@@ -108,6 +114,7 @@ constexpr int MIN_CAND_CAP = 1024;
 constexpr int FALLBACK_PARTS = 32;    // workgroups that share the rows of a query on the exhaustive path
 constexpr size_t WS_ALIGN = 256;
 constexpr int FP8_QUERY_CONFIG = 5;    // scan configuration of fp8 keys with fp8 queries (kb_configs.hpp)
+constexpr int FP8_QUERY_SHORT_CONFIG = 27;    // ... rows of 128 and 192 bytes
 constexpr int FP8_QUERY_WIDE_CONFIG = 20;     // ... with 128-byte row pieces: rows of a multiple of 128 bytes, 512 at least
 constexpr int FP8_QUERY_TILED_CONFIG = 6;     // ... the tiled kernel: 6, 7, 8 for query blocks of 64, 128, 256; every row length
 constexpr int FP8_STREAM_CONFIG = 23;         // fp8 keys with bf16 queries: the tiled kernel with whole lines, up to 32 queries
@@ -115,7 +122,7 @@ constexpr int FP8_QUERY_STREAM_CONFIG = 24;   // ... the tiled kernel with whole
 constexpr int FP8_QUERY_SMALL_CONFIG = 25;    // ... with tiles of 32 x 32, the dense plan
 bool is_fp8_query_config(int config)
 {
-    return config == FP8_QUERY_CONFIG || config == FP8_QUERY_STREAM_CONFIG || config == FP8_QUERY_WIDE_CONFIG || (config >= FP8_QUERY_TILED_CONFIG && config <= FP8_QUERY_TILED_CONFIG + 2);
+    return config == FP8_QUERY_CONFIG || config == FP8_QUERY_SHORT_CONFIG || config == FP8_QUERY_STREAM_CONFIG || config == FP8_QUERY_WIDE_CONFIG || (config >= FP8_QUERY_TILED_CONFIG && config <= FP8_QUERY_TILED_CONFIG + 2);
 }
 
 bool is_whole_config(int config) { return (config >= 13 && config <= 15) || config == 21 || config == FP8_QUERY_SMALL_CONFIG; }      // no pipeline with a sampling pass runs them
@@ -185,7 +192,8 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
         if (h->dtype != KB_FP8_E4M3) return false;
         const int generic8 = Q <= 64 ? FP8_QUERY_TILED_CONFIG : Q <= 128 ? FP8_QUERY_TILED_CONFIG + 1 : FP8_QUERY_TILED_CONFIG + 2;
         // large batches: the pipelined kernels (256-query blocks); smaller ones would pad their query columns there
-        c.config = Q <= 128 ? generic8 : (row_bytes % 128 == 0 && row_bytes >= 512) ? FP8_QUERY_WIDE_CONFIG : FP8_QUERY_CONFIG;
+        c.config = Q <= 128 ? generic8 : (row_bytes % 128 == 0 && row_bytes >= 512) ? FP8_QUERY_WIDE_CONFIG
+                                  : row_bytes >= 256 ? FP8_QUERY_CONFIG : FP8_QUERY_SHORT_CONFIG;
         if (Q <= 32 && whole_line_rows && stream_keys(h, n, Q, 1)) c.config = FP8_QUERY_STREAM_CONFIG;
         if (is_fp8_query_config((int)h->tune_config)) c.config = (int)h->tune_config;         // another one can be asked for
         if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;

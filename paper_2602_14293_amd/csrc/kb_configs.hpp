@@ -50,14 +50,23 @@ constexpr int SMALL_F32_CONFIG = 15;
 
 // Software-pipelined configurations (kb_scan_sp.hpp): XS(id, key dtype, TQ, NSA, NSB); 256-row tiles, 512 threads,
 // NSA / NSB = ring depth of key / query chunks in LDS.
-// bf16: the loads are issued between the MFMAs (IL mode)
+// bf16: the loads are issued between the MFMAs (IL mode).  Rows of 256 and 384 bytes (longer ones: the full-line kernel); call on 2^20 rows of
+// 256 bytes, 200 queries, in us: 128, tiled kernel 133; 384 bytes: 170, with a ring of five 175.  (Rows of 128 bytes in rings of three: no gain.)
 #define KB_SCAN_SP_CONFIGS_BF16_IL(XI) \
-    XI(17, KB_BF16, 256, 5, 4)
+    XI(17, KB_BF16, 256, 4, 4)
+// fp8 with bf16 queries: rows of 192 bytes, and those that are no multiple of 128 (192 bytes, 200 queries, per item: 8.0 us, tiled kernel 16.6)
 #define KB_SCAN_SP_CONFIGS_FP8(XS)  \
     XS(4, KB_FP8_E4M3, 256, 3, 3)
-// ... with fp8 queries as well (the fp8 matrix instruction): XQ(id, key dtype, TQ, NSA, NSB)
+// ... with fp8 queries as well (the fp8 matrix instruction): XQ(id, key dtype, TQ, NSA, NSB).  Rings of four take rows of 256 bytes and
+// up, rings of three rows of 128 and 192.  Per item (256 rows x 256 queries) and compute unit, 2^20 rows, 200 queries, in us:
+//   row bytes                 128    192    256    320    384    576    960
+//   tiled kernel             12.4   14.2   16.9   19.6   22.3   29.5   44.1
+//   rings of three            4.6    5.5    6.3    9.0    9.2   14.9   25.4
+//   rings of four              -      -     5.9    7.2    8.2   11.5   19.1
+//   five of keys, four of queries (before)  -  7.5    8.2   11.4   19.3
 #define KB_SCAN_SP_CONFIGS_FP8_Q8(XQ) \
-    XQ(5, KB_FP8_E4M3, 256, 5, 4)
+    XQ(5, KB_FP8_E4M3, 256, 4, 4) \
+    XQ(27, KB_FP8_E4M3, 256, 3, 3)
 
 // Full-line configurations (kb_scan_wide.hpp): XW(id, key dtype, TQ); 256-row tiles, 512 threads, 128-byte row pieces.
 #define KB_SCAN_WIDE_CONFIGS_BF16(XW) \

@@ -363,6 +363,9 @@ hipError_t launch_scan_wide_bf16(int config, bool sample, int grid, const ScanAr
 hipError_t launch_scan_wide_fp8(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_sp_fp8(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 
+// Shortest key row (bytes) of the kernel with a software pipeline of 64-byte pieces and rings of ns chunks: see SPCfg::AUX_COPIES.
+constexpr int pipelined_min_row_bytes(int ns, bool interleaved) { return 64 * (ns == 3 ? (interleaved ? 2 : 3) : interleaved ? ns : ns + 1); }
+
 // Static description of a scan configuration (host side planning).
 struct ConfigInfo {
     int tk, tq, threads, groups_per_tile, wg_per_cu;

@@ -15,8 +15,9 @@
 // (a direct-to-LDS load holds the issuing wave for tens of cycles) or runs an epilogue, and nothing but
 // the one barrier forces the two to move in step.  Iteration g reads chunks g and g+1 only, and its
 // loads overwrite the ring slot of chunk g-1, which nobody touches after barrier g.  A wave arrives at
-// barrier g+1 once its share of chunk g+2 has landed (NS-3 younger chunks still in flight).  Key chunks
-// come from HBM and get a ring of 5, query chunks come from L2 and get 4.
+// barrier g+1 once its share of chunk g+2 has landed (NS-3 younger chunks still in flight).  A ring must not
+// reach past the item after next (pipelined_min_row_bytes): rings of four serve rows from 256 bytes on, and a fifth
+// chunk of keys in flight measured no faster on longer ones (576 bytes 11.5 us an item against 11.4, 960 bytes 19.1 against 19.3).
 //
 // IL mode (256-query blocks of bf16 x bf16 and of fp8 x fp8): no split into compute-first and load-first
 // waves.  Every wave issues its share of the direct-to-LDS loads of chunk g + NS - 1 *between the MFMAs* of
@@ -50,7 +51,11 @@ template <int KT_, int TQ_, int NSA_, int NSB_, bool QF8_ = false, bool IL_ = fa
     static constexpr int A_BYTES = TK * RBA, B_BYTES = TQ * RBB;
     static constexpr int LCA = A_BYTES / 1024 / 4, LCB = B_BYTES / 1024 / 4;   // load instructions per loading wave per chunk
     static constexpr int OFF_B = NSA * A_BYTES;
-    // side data of a key tile, two copies (item parity)
+    // Side data of a key tile, a copy an item in flight.  While the waves are at the epilogue of item i the key stream is at most NS - 1 chunks
+    // (split mode: NS) into what follows, and side data go out with the first chunk of an item: two copies do for rows of NS (NS + 1)
+    // chunks; rings of three get a third one, and the shortest row is that whose query side data, sent off in an item's second
+    // iteration, lands before its epilogue: two chunks (split mode: three).
+    static constexpr int NS_MAX = NSA > NSB ? NSA : NSB, AUX_COPIES = NS_MAX == 3 ? 3 : 2;
     static constexpr int AUX_INVK = 0;                       // float  [TK]
     static constexpr int AUX_TAG = AUX_INVK + TK * 4;        // uint64 [TK]
     static constexpr int AUX_BYTES = AUX_TAG + TK * 8;
@@ -61,10 +66,10 @@ template <int KT_, int TQ_, int NSA_, int NSB_, bool QF8_ = false, bool IL_ = fa
     static constexpr int QAUX_QMASK = QAUX_THR64 + TQ * 8;   // uint64 [TQ]
     static constexpr int QAUX_BYTES = QAUX_QMASK + TQ * 8;
     static constexpr int OFF_AUX = OFF_B + NSB * B_BYTES;
-    static constexpr int OFF_QAUX = OFF_AUX + 2 * AUX_BYTES;
+    static constexpr int OFF_QAUX = OFF_AUX + AUX_COPIES * AUX_BYTES;
     static constexpr int SMEM_BYTES = OFF_QAUX + QAUX_BYTES;
     static constexpr int GROUPS_PER_TILE = 8;                // sampling groups: 4 row blocks x 2 lane halves
-    static constexpr int MIN_ROW_BYTES = RBA * ((NSA > NSB ? NSA : NSB) + 1);   // the side-data buffers alternate safely only then
+    static constexpr int MIN_ROW_BYTES = pipelined_min_row_bytes(NS_MAX, IL);
     static_assert(TQ == 256 || TQ == 128, "query blocks of 256 or 128");
     static_assert((KT == KB_BF16 && BMUL == 1 && !QF8) || (KT == KB_FP8_E4M3 && TQ == 256 && (BMUL == 2 || QF8)), "key types the kernel is written for");
     static_assert(NSA >= 3 && NSA <= 6 && NSB >= 3 && NSB <= 6, "ring depths the waits are written for");
@@ -210,7 +215,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_sp_kernel(ScanArgs p)
         ld_stage = ld_stage + 1 == NS ? 0 : ld_stage + 1;
         if (++ld_c == NC) {
             ld_c = 0;
-            ld_par ^= 1;
+            ld_par = ld_par + 1 == C::AUX_COPIES ? 0 : ld_par + 1;
             ld_tile += step_tile;
             ld_qb += step_qb;
             if (ld_qb >= nqb) {
@@ -239,7 +244,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_sp_kernel(ScanArgs p)
         ld_stage = ld_stage + 1 == NS ? 0 : ld_stage + 1;
         if (++ld_c == NC) {
             ld_c = 0;
-            ld_par ^= 1;
+            ld_par = ld_par + 1 == C::AUX_COPIES ? 0 : ld_par + 1;
             ld_tile += step_tile;
             ld_qb += step_qb;
             if (ld_qb >= nqb) {
@@ -363,7 +368,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_sp_kernel(ScanArgs p)
             e_qb = qb;
             e_par = par;
             c = 0;
-            par ^= 1;
+            par = par + 1 == C::AUX_COPIES ? 0 : par + 1;
             tile += step_tile;
             qb += step_qb;
             if (qb >= nqb) {
@@ -412,7 +417,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_sp_kernel(ScanArgs p)
             e_qb = qb;
             e_par = par;
             c = 0;
-            par ^= 1;
+            par = par + 1 == C::AUX_COPIES ? 0 : par + 1;
             tile += step_tile;
             qb += step_qb;
             if (qb >= nqb) {
