@@ -910,7 +910,7 @@ __device__ inline void touch(const unsigned char *at)
 }
 constexpr int THRESHOLD_AGAIN = 1024;       // groups that are scored again, a query
 
-// KT: type of the keys (KT_FP8_Q8: with fp8 queries) where the main pass leaves the sampled rows out, -1 otherwise.  The kernel
+// KT: type of the keys where the main pass leaves the sampled rows out (never with fp8 queries), -1 otherwise.  The kernel
 // then also lists the sample's own candidates: the best and the second row of a group where they reach the threshold; groups whose
 // bound on the others does too (k^3 / (6 slots^2) of them on a store in no order, one query in a thousand) are scored again
 // with the instruction sequence of the scan, 32 rows a wavefront.
