@@ -101,11 +101,18 @@ kb_status_t kb_normalize(kb_t *kb, void *hip_stream);
  * kb_query_plan_bytes is the host-side planner behind it: the bytes a query of `kind` (0: kb_query, 1:
  * kb_query_sampled, 2: kb_query with KB_FP8_E4M3 queries, 3: kb_query_sampled with them) needs when the knowledge base holds n rows; 0 when the
  * arguments are invalid or the handle does not take that kind of query.  For every n <= capacity it is at most
- * kb_query_workspace_bytes(kb, Q, k).  (A store that is scored whole runs the scan pipeline when given less than this
- * but enough for that.)  No device work.
+ * kb_query_workspace_bytes(kb, Q, k).  No device work.  A call that brings less runs the best of the library's plans that fits, with the
+ * same results, and is refused (KB_ERR_WORKSPACE) when none does.
+ *
+ * kb_query_plan tells which: what such a call does when it brings workspace_bytes, without device work either.  out (host, 4 x
+ * int64): out[0] = 0 the scan pipeline, 1 the whole store in groups of rows, 2 every product of a small store, 3 a small store in
+ * parts; out[1] = bytes of the workspace it uses; out[2] = rows scored by the pipeline's sampling pass; out[3] = rows scored by
+ * the main scan (fewer than n where the results among the sampled rows are taken from the sample).
+ * Errors: KB_ERR_NULL, KB_ERR_INVALID_ARG, KB_ERR_DTYPE (fp8 queries of other keys), KB_ERR_WORKSPACE (the call is refused).
  */
 size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k);
 size_t kb_query_plan_bytes(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32_t kind);
+kb_status_t kb_query_plan(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32_t kind, size_t workspace_bytes, int64_t *out);
 
 /*
  * Retrieval (Section 3: State Selector + top-k of the Optimization Selector).
@@ -131,9 +138,10 @@ kb_status_t kb_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dtype, int3
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical results as
  * kb_query, but the scratch memory is an array of KB_STATIC_SCRATCH_BYTES that is part of the library's device
  * image (one copy per GPU, held until the process ends).  The call allocates and frees nothing; the first call on a
- * device looks the array's address up (make one call before capturing a graph).  A query whose plan needs more than
- * the array holds (kb_query_plan_bytes(kb, kb_size(kb), Q, k, kind) > KB_STATIC_SCRATCH_BYTES: large batches or
- * k on a large knowledge base) returns KB_ERR_WORKSPACE and runs nothing: use kb_query with a workspace then.
+ * device looks the array's address up (make one call before capturing a graph).  A query for which the array is too small
+ * (kb_query_plan(kb, kb_size(kb), Q, k, kind, KB_STATIC_SCRATCH_BYTES, out) says so: large batches or
+ * k on a large knowledge base) returns KB_ERR_WORKSPACE and runs nothing: use kb_query with a workspace then, which may also be
+ * the faster way where kb_query_plan_bytes is more than the array holds.
  * All calls on one GPU share the array, which keeps the last call's contents; every call resets what it needs
  * zeroed.  Calls that overlap on one GPU (different streams, or threads) race: order them on one stream.
  * kb_query_counters on this scratch is not offered.  Errors: as kb_query.

@@ -87,18 +87,27 @@ constexpr int F32_SQUARE_CONFIG = 26;  // f32 rows: tiles of 64 x 64
 constexpr int FP8_WIDE_CONFIG = 22;    // fp8 keys with bf16 queries: the full-line kernel (rows of a multiple of 128 bytes, 256 at least)
 constexpr int64_t WIDE128_MIN_ROWS = 4 * 65536;     // rows from which the 128-query full-line kernel is the faster one (measured: 2^18)
 
-int scan_config_for(int key_dtype, int Q, int d, int64_t n)
+// What a plan gives up for less memory, step by step: a call whose workspace is too small for the fastest plan is served by the
+// first that fits.
+enum Thrift {
+    AMPLE,              // nothing
+    SCORED_TWICE,       // the main pass scores the sampled rows again: no second word per sampled group, no sample in whole rounds
+    LEAST               // ... and the tiled kernel (f32: its 128-row tiles) where another is faster on rows too short for deep rings
+};
+
+int scan_config_for(int key_dtype, int Q, int d, int64_t n, Thrift thrift)
 {
+    const bool least = thrift == LEAST;
     if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= 512) return 18;
     // 33 to 128 queries: the full-line kernel once a workgroup has several tiles to stream (its ring takes longer to fill)
     if (key_dtype == KB_BF16 && Q > 32 && d * 2 >= 512 && n >= WIDE128_MIN_ROWS) return 19;
-    if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= 256) return 17;
-    if (key_dtype == KB_FP8_E4M3 && Q > 128 && d >= 192) return d >= 256 && d % 128 == 0 ? FP8_WIDE_CONFIG : 4;
+    if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= (least ? 384 : 256)) return 17;
+    if (key_dtype == KB_FP8_E4M3 && Q > 128 && d >= (least ? 256 : 192)) return d >= 256 && d % 128 == 0 ? FP8_WIDE_CONFIG : 4;
     // below that size a query is bound by the latency of its launches: tiles of 64 rows (twice the workgroups, half the
     // chunks each) finish sooner: 62 against 71 us per call on 65,536 rows of 768 bf16 values with 64 queries
     // (and 64 against 70 us with 128 queries)
     if (key_dtype == KB_BF16 && Q > 32 && Q <= 128 && n < WIDE128_MIN_ROWS) return Q <= 64 ? 12 : 16;
-    if (key_dtype == KB_F32 && Q > 32 && Q <= 64) return F32_SQUARE_CONFIG;
+    if (key_dtype == KB_F32 && Q > 32 && Q <= 64 && !least) return F32_SQUARE_CONFIG;
     return Q <= 32 ? 1 : Q <= 128 ? 2 : 3;
 }
 
@@ -180,7 +189,7 @@ struct Choice {                 // kernels of a query over n rows
     ConfigInfo sci;
 };
 
-bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choice *out)
+bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Thrift thrift, Choice *out)
 {
     Choice c;
     const int generic = Q <= 32 ? 1 : Q <= 128 ? 2 : 3;        // the tiled kernel: every dtype, every row length
@@ -192,7 +201,7 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
         if (h->dtype != KB_FP8_E4M3) return false;
         const int generic8 = Q <= 64 ? FP8_QUERY_TILED_CONFIG : Q <= 128 ? FP8_QUERY_TILED_CONFIG + 1 : FP8_QUERY_TILED_CONFIG + 2;
         // large batches: the pipelined kernels (256-query blocks); smaller ones would pad their query columns there
-        c.config = Q <= 128 ? generic8 : (row_bytes % 128 == 0 && row_bytes >= 512) ? FP8_QUERY_WIDE_CONFIG
+        c.config = Q <= 128 || (thrift == LEAST && row_bytes < 384) ? generic8 : (row_bytes % 128 == 0 && row_bytes >= 512) ? FP8_QUERY_WIDE_CONFIG
                                   : row_bytes >= 256 ? FP8_QUERY_CONFIG : FP8_QUERY_SHORT_CONFIG;
         if (Q <= 32 && whole_line_rows && stream_keys(h, n, Q, 1)) c.config = FP8_QUERY_STREAM_CONFIG;
         if (is_fp8_query_config((int)h->tune_config)) c.config = (int)h->tune_config;         // another one can be asked for
@@ -204,7 +213,7 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Choic
             if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;
         }
     } else {
-        c.config = h->tune_config > 0 ? (int)h->tune_config : scan_config_for(h->dtype, Q, h->d, n);
+        c.config = h->tune_config > 0 ? (int)h->tune_config : scan_config_for(h->dtype, Q, h->d, n, thrift);
         if (h->tune_config == 0 && h->dtype == KB_FP8_E4M3 && Q <= 32 && whole_line_rows && stream_keys(h, n, Q, 1)) c.config = FP8_STREAM_CONFIG;
         if (!scan_config_info(h->dtype, c.config, &c.ci)) return false;
         // fall back where a (forced) configuration does not apply: the weighted random selection exists in the
@@ -307,8 +316,9 @@ void lay_out(const Sizes &z, Plan *p)
 
 // The plan of a query over n rows with the kernels `c`.  Apart from the ln(gain) array it depends on n through the
 // number of key tiles only, which is what lets kb_query_workspace_bytes bound it over all row counts.
-void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, bool draw, Plan *out, Sizes *sizes)
+void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, bool draw, Thrift thrift, Plan *out, Sizes *sizes)
 {
+    const bool leaves_out = leaves_sample_out(c) && thrift == AMPLE;
     Plan p;
     memset(&p, 0, sizeof p);
     const ConfigInfo &ci = c.ci, &sci = c.sci;
@@ -327,7 +337,7 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
     if (n < 1) n = 1;
     const int64_t nt = ceil_div(n, ci.tk), nts = ceil_div(n, sci.tk);     // key tiles of the main pass, of the sampling pass
 
-    const int64_t st = sample_tiles_for(h, sci, nts, Q, k, samples_in_rounds(c), true);
+    const int64_t st = sample_tiles_for(h, sci, nts, Q, k, samples_in_rounds(c) && leaves_out, true);
     p.sample_tk = sci.tk;
     p.sample_tiles = st;
     p.sample_slots = (int32_t)(st * sci.groups_per_tile);
@@ -336,7 +346,7 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
     // whole tiles: the full-line kernel addresses scattered rows in 32 bits, in units of 16 bytes, up to 64 GiB of keys.)
     const int run_shift = draw ? 2 : 0;
     const int64_t sampled_runs = p.sample_keys >> run_shift, runs = n >> run_shift;
-    p.once = leaves_sample_out(c) && st > 0 && 2 * sampled_runs < runs && runs >= 3 && !(sci.family == 4 && (uint64_t)n * h->d * key_bytes(h->dtype) >= ((uint64_t)1 << 36));
+    p.once = leaves_out && st > 0 && 2 * sampled_runs < runs && runs >= 3 && !(sci.family == 4 && (uint64_t)n * h->d * key_bytes(h->dtype) >= ((uint64_t)1 << 36));
     p.main_rows = p.once ? n - p.sample_keys : n;
     const int64_t expect = st > 0 ? ceil_div((int64_t)k * nts, sample_tiles_for(h, sci, nts, Q, k, false, true)) : nt * ci.tk;      // candidates per query
     p.cand_cap = cand_cap_for(expect, st > 0);
@@ -363,7 +373,7 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
     z.qpad = p.qpad;
     z.regions = p.regions;
     z.sample_slots = p.sample_slots;
-    z.more_slots = leaves_sample_out(c) ? p.sample_slots : 0;
+    z.more_slots = leaves_out ? p.sample_slots : 0;
     z.cand_cap = p.cand_cap;
     z.region_records = (int64_t)p.regions * rc;
     z.lgain_rows = draw ? ceil_div(n, 256) * 256 + 256 : 0;      // the weighted random selection only
@@ -395,14 +405,14 @@ int64_t whole_max_rows(const kb *h, int32_t Q)
 }
 constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
 double cubed(int32_t k) { return (double)k * k * k; }
-bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, WholePlan *out)
+bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, Thrift thrift, WholePlan *out)
 {
     if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
     if (n < 1 || Q > WHOLE_MAX_QUERIES || n > whole_max_rows(h, Q) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
     WholePlan p;
     if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
     else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : n >= 128 * 2 * DEVICE_CUS && h->d >= 512 ? 21 : 16;    // (14: once every resident workgroup gets a tile)
-    else if (h->dtype == KB_F32 && Q > 32) p.config = Q <= 64 || ceil_div(n, 128) * ceil_div(Q, 128) <= DEVICE_CUS ? F32_SQUARE_CONFIG : 2;
+    else if (h->dtype == KB_F32 && Q > 32 && thrift != LEAST) p.config = Q <= 64 || ceil_div(n, 128) * ceil_div(Q, 128) <= DEVICE_CUS ? F32_SQUARE_CONFIG : 2;
     else p.config = Q <= 32 ? 1 : 2;
     if (h->dtype == KB_FP8_E4M3 && Q <= 32 && h->d % 128 == 0 && stream_keys(h, n, Q, 1)) p.config = q8 ? FP8_QUERY_STREAM_CONFIG : FP8_STREAM_CONFIG;
     // tiles of 32 rows while those of 128 would leave compute units without one; f32: of 16 while they run side by side (16,000 x
@@ -477,11 +487,11 @@ bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
 
 // Pure function of (handle settings, row count n, Q, k): which kernels run on what, and where everything lives
 // in the workspace.
-bool make_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, Plan *out)
+bool make_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, Thrift thrift, Plan *out)
 {
     Choice c;
-    if (!choose_kernels(h, n, Q, draw, q8, &c)) return false;
-    plan_for(h, c, n, Q, k, draw, out, nullptr);
+    if (!choose_kernels(h, n, Q, draw, q8, thrift, &c)) return false;
+    plan_for(h, c, n, Q, k, draw, thrift, out, nullptr);
     return true;
 }
 
@@ -518,10 +528,10 @@ void bound_sizes(const kb *h, const Choice &c, int32_t Q, int32_t k, bool draw, 
     Plan p;
     Sizes z;
     for (int64_t n = step; n < h->capacity + step && ceil_div(n, sci.tk) <= EXACT_TILES; n += step) {
-        plan_for(h, c, n, Q, k, draw, &p, &z);
+        plan_for(h, c, n, Q, k, draw, AMPLE, &p, &z);
         max_into(m, z);
     }
-    plan_for(h, c, h->capacity, Q, k, draw, &p, &z);       // the ln(gain) array, and the largest grid
+    plan_for(h, c, h->capacity, Q, k, draw, AMPLE, &p, &z);       // the ln(gain) array, and the largest grid
     max_into(m, z);
     if (cap_nt <= EXACT_TILES) return;
     int64_t expect = 512;
@@ -2346,7 +2356,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     for (int64_t n : ns)
         for (int kind = 0; kind < 4; ++kind) {      // plain, weighted random selection, fp8 queries, both
             Choice c;
-            if (!choose_kernels(kb, n, Q, (kind & 1) != 0, (kind & 2) != 0, &c)) continue;
+            if (!choose_kernels(kb, n, Q, (kind & 1) != 0, (kind & 2) != 0, AMPLE, &c)) continue;
             bound_sizes(kb, c, Q, k, (kind & 1) != 0, m);
             any = true;
         }
@@ -2363,7 +2373,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     for (int64_t n : most)
         for (int q8 = 0; q8 < 2; ++q8) {
             WholePlan wp;
-            if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, &wp)) total = std::max(total, wp.total);
+            if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, AMPLE, &wp)) total = std::max(total, wp.total);
         }
     // the dense plan: grows with the rows
     for (int kind = 0; kind < 4; ++kind) {
@@ -2381,11 +2391,70 @@ size_t kb_query_plan_bytes(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int3
     WholePlan wp;
     DensePlan dp;
     const bool dense = make_dense_plan(kb, n, Q, k, draw, q8, &dp);
-    if (make_whole_plan(kb, n, Q, k, draw, q8, &wp)) return dense && dense_is_better(n, k, wp) ? dp.total : wp.total;
+    if (make_whole_plan(kb, n, Q, k, draw, q8, AMPLE, &wp)) return dense && dense_is_better(n, k, wp) ? dp.total : wp.total;
     if (const int parts = small_path_parts(kb, n, Q, draw); parts && (!q8 || kb->dtype == KB_FP8_E4M3)) return make_small_plan(Q, k, parts).total;         // (with more than that, the call takes the dense plan)
     if (dense) return dp.total;
     Plan p;
-    return make_plan(kb, n, Q, k, (kind & 1) != 0, (kind & 2) != 0, &p) ? p.total : 0;
+    return make_plan(kb, n, Q, k, draw, q8, AMPLE, &p) ? p.total : 0;
+}
+
+namespace {
+
+// What a call does that brings workspace_bytes: the best plan that fits.
+struct Route {
+    enum Kind { PIPELINE = 0, WHOLE = 1, DENSE = 2, PARTS = 3 } kind;
+    Plan pipeline;
+    WholePlan whole;
+    DensePlan dense;
+    SmallPlan small;
+    int parts;
+    size_t bytes;
+};
+kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, size_t workspace_bytes, Route *r)
+{
+    const auto whole_fits = [&](Thrift thrift) { return make_whole_plan(h, n, Q, k, draw, q8, thrift, &r->whole) && r->whole.total <= workspace_bytes; };
+    const bool whole = whole_fits(AMPLE) || whole_fits(LEAST);
+    r->parts = small_path_parts(h, n, Q, draw);
+    if (r->parts) r->small = make_small_plan(Q, k, r->parts);
+    if (!whole && r->parts && workspace_bytes < r->small.total) return KB_ERR_WORKSPACE;
+    const bool dense = make_dense_plan(h, n, Q, k, draw, q8, &r->dense) && r->dense.total <= workspace_bytes;
+    if (dense && !(whole && !dense_is_better(n, k, r->whole))) {
+        r->kind = Route::DENSE;
+        r->bytes = r->dense.total;
+    } else if (whole) {
+        r->kind = Route::WHOLE;
+        r->bytes = r->whole.total;
+    } else if (r->parts) {
+        r->kind = Route::PARTS;
+        r->bytes = r->small.total;
+    } else {
+        for (const Thrift thrift : {AMPLE, SCORED_TWICE, LEAST}) {
+            if (!make_plan(h, n, Q, k, draw, q8, thrift, &r->pipeline)) return KB_ERR_INVALID_ARG;
+            if (r->pipeline.total <= workspace_bytes) break;
+        }
+        r->kind = Route::PIPELINE;
+        r->bytes = r->pipeline.total;
+        if (workspace_bytes < r->bytes) return KB_ERR_WORKSPACE;
+    }
+    return KB_OK;
+}
+
+}  // namespace
+
+kb_status_t kb_query_plan(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32_t kind, size_t workspace_bytes, int64_t *out)
+{
+    if (!kb || !out) return KB_ERR_NULL;
+    if (n < 0 || n > kb->capacity || Q < 1 || k < 1 || k > KB_K_MAX || kind < 0 || kind > 3) return KB_ERR_INVALID_ARG;
+    const bool draw = (kind & 1) != 0, q8 = (kind & 2) != 0;
+    if (q8 && kb->dtype != KB_FP8_E4M3) return KB_ERR_DTYPE;
+    Route r;
+    if (const kb_status_t e = choose_route(kb, n, Q, k, draw, q8, workspace_bytes, &r); e != KB_OK) return e;
+    const bool pipeline = r.kind == Route::PIPELINE;
+    out[0] = r.kind;
+    out[1] = (int64_t)r.bytes;
+    out[2] = pipeline && n > 0 ? r.pipeline.sample_keys : 0;
+    out[3] = pipeline && n > 0 ? r.pipeline.main_rows : n;
+    return KB_OK;
 }
 
 // kb_query and kb_query_sampled: the same pipeline; `gain_dev` != nullptr selects the weighted random selection.
@@ -2421,31 +2490,16 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         ga.blocks = (int)ceil_div(ga.n_padded, 256);
     }
 
-    // (a plan that wants more memory than the call was given is passed over, down to the parts or the pipeline)
-    WholePlan wp;
-    DensePlan dp;
-    const bool whole = make_whole_plan(kb, kb->n, Q, k, draw, q8, &wp) && wp.total <= workspace_bytes;
-    const int parts = small_path_parts(kb, kb->n, Q, draw);
-    if (!whole && parts && workspace_bytes < make_small_plan(Q, k, parts).total) return KB_ERR_WORKSPACE;
-    const bool dense = make_dense_plan(kb, kb->n, Q, k, draw, q8, &dp) && dp.total <= workspace_bytes;
-    if (dense && !(whole && !dense_is_better(kb->n, k, wp)))
-        return launch_dense(kb, dp, queries_dev, q_dtype, Q, qmask_dev, k, dr, ga, indices_out_dev, scores_out_dev, static_cast<unsigned char *>(workspace_dev),
-                            static_cast<hipStream_t>(hip_stream));
-    if (whole)
-        return launch_whole(kb, wp, queries_dev, q8, Q, qmask_dev, k, indices_out_dev, scores_out_dev, static_cast<unsigned char *>(workspace_dev),
-                            static_cast<hipStream_t>(hip_stream));
-    if (parts) {
-        const SmallPlan sp = make_small_plan(Q, k, parts);
-        unsigned char *w = static_cast<unsigned char *>(workspace_dev);
-        return launch_small(kb, queries_dev, q8, Q, qmask_dev, k, parts, reinterpret_cast<uint64_t *>(w + sp.off_lists), reinterpret_cast<uint64_t *>(w),
-                            indices_out_dev, scores_out_dev, static_cast<hipStream_t>(hip_stream));
-    }
-    Plan p;
-    if (!make_plan(kb, kb->n, Q, k, draw, q8, &p)) return KB_ERR_INVALID_ARG;
-    if (workspace_bytes < p.total) return KB_ERR_WORKSPACE;
-
+    Route r;
+    if (const kb_status_t e = choose_route(kb, kb->n, Q, k, draw, q8, workspace_bytes, &r); e != KB_OK) return e;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     unsigned char *ws = static_cast<unsigned char *>(workspace_dev);
+    if (r.kind == Route::DENSE) return launch_dense(kb, r.dense, queries_dev, q_dtype, Q, qmask_dev, k, dr, ga, indices_out_dev, scores_out_dev, ws, s);
+    if (r.kind == Route::WHOLE) return launch_whole(kb, r.whole, queries_dev, q8, Q, qmask_dev, k, indices_out_dev, scores_out_dev, ws, s);
+    if (r.kind == Route::PARTS)
+        return launch_small(kb, queries_dev, q8, Q, qmask_dev, k, r.parts, reinterpret_cast<uint64_t *>(ws + r.small.off_lists), reinterpret_cast<uint64_t *>(ws),
+                            indices_out_dev, scores_out_dev, s);
+    const Plan &p = r.pipeline;
     float *invq = reinterpret_cast<float *>(ws + p.off_invq);
     uint64_t *thr64 = reinterpret_cast<uint64_t *>(ws + p.off_thr64);
     float *thrp = reinterpret_cast<float *>(ws + p.off_thrp);

@@ -50,6 +50,8 @@ def lib() -> ctypes.CDLL:
         L.kb_query_workspace_bytes.argtypes = [vp, i32, i32]
         L.kb_query_plan_bytes.restype = sz
         L.kb_query_plan_bytes.argtypes = [vp, i64, i32, i32, i32]
+        L.kb_query_plan.restype = i32
+        L.kb_query_plan.argtypes = [vp, i64, i32, i32, i32, sz, ctypes.POINTER(i64)]
         L.kb_query.restype = i32
         L.kb_query.argtypes = [vp, vp, i32, i32, vp, i32, vp, vp, vp, sz, vp]
         L.kb_query_static.restype = i32
@@ -258,6 +260,13 @@ class KnowledgeBase:
         _check(lib().kb_compact(self._h, dst._h, _ptr(gain), _ptr(gain_dst), _ptr(index_map), _ptr(ws), ws.numel(), _stream(),
                                 ctypes.byref(live)), "kb_compact")
         return live.value, index_map, None if gain_dst is None else gain_dst[:live.value]
+
+    def plan(self, Q: int, k: int, kind: int = 0, workspace_bytes: Optional[int] = None) -> dict:
+        """kb_query_plan: what a query of the present store does with that much memory (default: all that query() brings)."""
+        out = (ctypes.c_int64 * 4)()
+        have = self.workspace_bytes(Q, k) if workspace_bytes is None else workspace_bytes
+        _check(lib().kb_query_plan(self._h, self.size, Q, k, kind, have, out), "kb_query_plan")
+        return {"plan": ("pipeline", "whole", "dense", "parts")[out[0]], "bytes": out[1], "sampled_rows": out[2], "scanned_rows": out[3]}
 
     def counters(self) -> dict:
         out = (ctypes.c_int64 * 4)()

@@ -298,3 +298,43 @@ def test_append_reports_the_first_index_only_on_success(L):
     assert L.kb_append(h, None, None, None, 3, None, ctypes.byref(first)) == 1 and first.value == -7      # KB_ERR_NULL
     assert L.kb_append(h, FAKE, None, None, 0, None, ctypes.byref(first)) == 0 and first.value == 0       # a no-op reports the size
     L.kb_destroy(h)
+
+
+# type of the keys, d, rows, queries, k, kind, bytes that were enough while no plan kept a second word per sampled group, before short
+# rows and f32 rows had the kernels and tiles they have now
+FORMER_NEEDS = [
+    (kbmod.KB_BF16, 1024, 1 << 20, 256, 64, 0, 25191168), (kbmod.KB_BF16, 768, 1500000, 256, 64, 0, 28812032), (kbmod.KB_BF16, 1024, 2000000, 256, 64, 0, 32809728),
+    (kbmod.KB_FP8_E4M3, 192, 927937, 391, 37, 0, 32359168), (kbmod.KB_FP8_E4M3, 128, 248847, 370, 72, 2, 32850688),
+    (kbmod.KB_FP8_E4M3, 128, 32148, 1191, 47, 2, 32981760), (kbmod.KB_FP8_E4M3, 320, 276650, 7961, 5, 2, 290718464),
+    (kbmod.KB_BF16, 128, 1748891, 424, 36, 0, 41485056), (kbmod.KB_F32, 192, 116098, 34, 1, 0, 1235712), (kbmod.KB_F32, 640, 1929, 116, 3, 0, 75008),
+    (kbmod.KB_F32, 128, 22637, 43, 9, 1, 2857728),
+]
+
+
+@pytest.mark.parametrize("dtype,d,n,Q,k,kind,former", FORMER_NEEDS)
+def test_a_call_that_brings_what_was_once_enough_is_served(L, dtype, d, n, Q, k, kind, former):
+    st, h = _create(L, d=d, dtype=dtype, cap=n, scale=FAKE if dtype == kbmod.KB_FP8_E4M3 else None)
+    out = (ctypes.c_int64 * 4)()
+    for have in (former, 32 << 20):                                                  # kb_query; kb_query_static, whose array has one size
+        if have >= former:
+            assert L.kb_query_plan(h, n, Q, k, kind, have, out) == 0, have
+            assert 0 < out[1] <= have and out[3] <= n
+    told = L.kb_query_plan_bytes(h, n, Q, k, kind)
+    assert told > former                                                             # (else there is nothing to show here)
+    assert L.kb_query_plan(h, n, Q, k, kind, told, out) == 0 and out[1] == told
+    if out[0] == 0 and out[3] < n:                                                   # the fastest plan scores the sampled rows once
+        assert out[3] == n - out[2]
+        assert L.kb_query_plan(h, n, Q, k, kind, told - 1, out) == 0 and out[3] == n and out[2] > 0
+    assert L.kb_query_plan(h, n, Q, k, kind, 256, out) == 7                          # KB_ERR_WORKSPACE
+    L.kb_destroy(h)
+
+
+def test_plan_argument_errors(L):
+    st, h = _create(L, cap=1000)
+    out = (ctypes.c_int64 * 4)()
+    assert L.kb_query_plan(None, 10, 4, 4, 0, 1 << 30, out) == 1 and L.kb_query_plan(h, 10, 4, 4, 0, 1 << 30, None) == 1
+    for n, Q, k, kind in ((-1, 4, 4, 0), (1001, 4, 4, 0), (10, 0, 4, 0), (10, 4, 0, 0), (10, 4, 129, 0), (10, 4, 4, -1), (10, 4, 4, 4)):
+        assert L.kb_query_plan(h, n, Q, k, kind, 1 << 30, out) == 2
+    assert L.kb_query_plan(h, 10, 4, 4, 2, 1 << 30, out) == 3                        # fp8 queries go with fp8 keys only
+    assert L.kb_query_plan(h, 0, 4, 4, 0, 1 << 30, out) == 0 and out[2] == 0 and out[3] == 0
+    L.kb_destroy(h)
