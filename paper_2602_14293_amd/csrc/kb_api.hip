@@ -592,13 +592,17 @@ __device__ inline float wave_sum(float v)
 
 // One wavefront per row: lanes stride over the row's 16-byte pieces, fp32 sum of squares, butterfly
 // reduction, inv = 1/sqrt(sum) or 0 for a zero row.
-template <int DT> __device__ inline float row_inv_norm(const void *base, int64_t row, int row_bytes, int lane)
+__device__ inline float inv_norm_of(float square_sum) { return square_sum > 0.f ? 1.0f / sqrtf(square_sum) : 0.f; }
+template <int DT> __device__ inline float row_square_sum(const void *base, int64_t row, int row_bytes, int lane)
 {
     const u32x4 *p = reinterpret_cast<const u32x4 *>(static_cast<const unsigned char *>(base) + (size_t)row * row_bytes);
     float s = 0.f;
     for (int i = lane; i < row_bytes / 16; i += 64) s += piece_sum_squares<DT>(__builtin_nontemporal_load(p + i));
-    s = wave_sum(s);
-    return s > 0.f ? 1.0f / sqrtf(s) : 0.f;
+    return wave_sum(s);
+}
+template <int DT> __device__ inline float row_inv_norm(const void *base, int64_t row, int row_bytes, int lane)
+{
+    return inv_norm_of(row_square_sum<DT>(base, row, row_bytes, lane));
 }
 
 template <int DT> __global__ __launch_bounds__(256) void row_norm_kernel(const void *keys, int64_t begin, int64_t end, int d, float *inv_norm)
@@ -940,6 +944,7 @@ template <int QT, bool KEYS, int KT, int PER = 2> __global__ __launch_bounds__(1
     SelectScratch *sc = reinterpret_cast<SelectScratch *>(smem_raw + sizeof(uint64_t) * (slots > k ? slots : k));
     __shared__ float sh_iq;
     __shared__ uint32_t sh_low;
+    __shared__ bool sh_endless;         // the query's squared length is past the largest float
     // Everything the kernel reads from global memory is asked for before anything waits: the query's mask word, the
     // first two samples of every thread and (first wavefront) the query row are one memory round trip, not three.
     const int bd = (int)blockDim.x;
@@ -967,10 +972,11 @@ template <int QT, bool KEYS, int KT, int PER = 2> __global__ __launch_bounds__(1
             return;
         }
         if (tid < 64) {
-            const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid);
+            const float square_sum = row_square_sum<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid), inv = inv_norm_of(square_sum);
             if (tid == 0) {
                 a.invq[q] = inv;
                 sh_iq = inv;
+                sh_endless = square_sum == __builtin_inff();
             }
         }
     }
@@ -1074,8 +1080,10 @@ template <int QT, bool KEYS, int KT, int PER = 2> __global__ __launch_bounds__(1
             __syncthreads();
         }
         if (tid < CAND_SEGMENTS) a.cnt[q * CAND_SEGMENTS + tid] = sh_seg[tid] < seg_cap ? sh_seg[tid] : seg_cap;
-        // (the sample's search does not know infinite products: a query without a length goes the exhaustive way, as where every row ties)
-        if (tid == 0 && (sh_lost != 0 || again > THRESHOLD_AGAIN || (!KEYS && !(iq > 0.f)))) a.flag[q] = 1u;
+        // The sample's search does not know infinite products, which only a query of endless length has on finite rows: it goes the
+        // exhaustive way, unless its mask lets nothing through.  (A zero query's products are zeros, one with a NaN has nothing to list.)
+        const bool unknown = !KEYS && sh_endless && (!a.qmask || mask_word != 0);       // (thread 0 holds the mask word)
+        if (tid == 0 && (sh_lost != 0 || again > THRESHOLD_AGAIN || unknown)) a.flag[q] = 1u;
     }
 }
 

@@ -138,3 +138,38 @@ def test_numbers_that_are_none(T, config, N, bits):
     kb.close()
     assert not np.isnan(a[1]).any() and not np.isnan(b[1][5:]).any()
     assert np.array_equal(a[0][5:], b[0][5:]) and np.array_equal(a[1][5:].view(np.uint32), b[1][5:].view(np.uint32))
+
+
+@pytest.mark.parametrize("dtype,config,N,d", [("bf16", 18, 40000 + 1, 256), ("bf16", 19, (1 << 16) + 5, 256), ("fp8", 22, 50000 + 3, 256)])
+def test_queries_without_a_length_stay_on_their_lists(T, dtype, config, N, d):
+    """A batch filled up with zero rows, whose masks let nothing or little through: no such query scores the whole store.  One past the
+    largest length has to, if its mask lets anything through."""
+    Q, k = (100 if config == 19 else 200), 16
+    w = W.clustered(seed=N, N=N, d=d, Q=Q, k=k, centers=32) if dtype == "bf16" else W.compressed(seed=N, N=N, d=d, Q=Q, k=k, centers=32)
+    g = torch.Generator().manual_seed(2)
+    w.tags = torch.ones(N, dtype=torch.int64) << torch.randint(0, 8, (N,), generator=g)
+    few = torch.randperm(N, generator=g)[:20]
+    w.tags[few] = 1 << 62
+    w.qmask = torch.full((Q,), 0x3f, dtype=torch.int64)
+    w.queries[:40] = 0
+    w.qmask[:20] = 0
+    w.qmask[20:40] = 1 << 62
+    w.queries[40:42, 3] = float("nan")
+    w.queries[42, 3] = float("inf")
+    w.queries[43] = 3e38
+    w.qmask[40], w.qmask[41], w.qmask[42:44] = 0, 1 << 62, 0
+    kb = T.build_kb(w)
+    kb.set_tuning("scan_config", config)
+    got = T.gpu_query(kb, w)
+    counters = kb.counters()
+    assert counters["sample_keys"] > 0 and counters["exhaustive_queries"] == 0
+    assert (got[0][:20] == -1).all() and (got[0][40:44] == -1).all()
+    assert np.array_equal(got[0][20:40], np.tile(np.sort(few.numpy())[:k], (20, 1))) and (got[1][20:40] == 0).all()
+    kb.set_tuning("scan_config", 3)
+    ref = T.gpu_query(kb, w)
+    assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1].view(np.uint32), ref[1].view(np.uint32))
+    kb.set_tuning("scan_config", config)
+    w.qmask[42:44] = 1 << 62
+    got = T.gpu_query(kb, w)
+    assert kb.counters()["exhaustive_queries"] == 2 and not np.isnan(got[1]).any()
+    kb.close()
