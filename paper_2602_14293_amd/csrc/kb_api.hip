@@ -262,10 +262,12 @@ int64_t sample_tiles_for(const kb *h, const ConfigInfo &sci, int64_t nt, int32_t
         if (free_tiles > nt / 4) free_tiles = nt / 4;
         if (st < free_tiles) st = free_tiles;
         // a sample that the main pass leaves out costs nothing as long as both are whole rounds of the compute units (down by a
-        // quarter at most, and not where a round is more than a quarter of the store)
+        // quarter at most, with samples enough for k, and not where a round is more than a quarter of the store; the quotient drops the
+        // part of a tile, which of few tiles is much, and with more than 256 query blocks may be all of them)
         if (whole_rounds) {
             const int64_t rounded = ceil_div(3 * st * nqb, 4 * DEVICE_CUS) * DEVICE_CUS / nqb;
-            if (rounded > st ? rounded <= nt / 4 || !floor : floor) st = rounded;
+            const bool down = floor && 4 * rounded >= 3 * st - st / 16 && rounded * sci.groups_per_tile >= k;
+            if (rounded > st ? rounded <= nt / 4 || !floor : down) st = rounded;
         }
     }
     if (st > MAX_SAMPLE_SLOTS / sci.groups_per_tile) st = MAX_SAMPLE_SLOTS / sci.groups_per_tile;

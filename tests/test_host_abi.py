@@ -338,3 +338,19 @@ def test_plan_argument_errors(L):
     assert L.kb_query_plan(h, 10, 4, 4, 2, 1 << 30, out) == 3                        # fp8 queries go with fp8 keys only
     assert L.kb_query_plan(h, 0, 4, 4, 0, 1 << 30, out) == 0 and out[2] == 0 and out[3] == 0
     L.kb_destroy(h)
+
+
+@pytest.mark.parametrize("n,d,k", [(16384, 256, 4), (2048, 256, 1), (10000, 512, 3), (5000, 256, 4)])
+def test_batches_past_256_query_blocks_still_sample(L, n, d, k):
+    # whole rounds of the compute units are less than a tile there; without a sample every row is a candidate, and lists, records and time grow
+    # by a multiple
+    out = (ctypes.c_int64 * 4)()
+    for dtype in (kbmod.KB_BF16, kbmod.KB_FP8_E4M3):
+        st, h = _create(L, d=d, dtype=dtype, cap=n, scale=FAKE if dtype == kbmod.KB_FP8_E4M3 else None)
+        per_query = []
+        for Q in (65000, 65536, 65537, 66000, 90000, 140000):
+            assert L.kb_query_plan(h, n, Q, k, 0, 1 << 60, out) == 0 and out[0] == 0
+            assert out[2] > 0, Q
+            per_query.append(out[1] / Q)
+        assert max(per_query) < 1.1 * min(per_query)
+        L.kb_destroy(h)
