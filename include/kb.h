@@ -106,7 +106,7 @@ kb_status_t kb_normalize(kb_t *kb, void *hip_stream);
  *
  * kb_query_plan tells which: what such a call does when it brings workspace_bytes, without device work either.  out (host, 4 x
  * int64): out[0] = 0 the scan pipeline, 1 the whole store in groups of rows, 2 every product of a small store, 3 a small store in
- * parts; out[1] = bytes of the workspace it uses; out[2] = rows scored by the pipeline's sampling pass; out[3] = rows scored by
+ * parts; out[1] = bytes it needs for that; out[2] = rows scored by the pipeline's sampling pass; out[3] = rows scored by
  * the main scan (fewer than n where the results among the sampled rows are taken from the sample).
  * Errors: KB_ERR_NULL, KB_ERR_INVALID_ARG, KB_ERR_DTYPE (fp8 queries of other keys), KB_ERR_WORKSPACE (the call is refused).
  */

@@ -1926,7 +1926,8 @@ template <int KT> __global__ __launch_bounds__(PROBE_THREADS) void probe_scan_ke
 }
 
 // A small knowledge base, block (s, q): part s of the rows, as above but with fragments loaded to registers.  It takes the
-// calls whose k is large for the number of rows, which the whole-store plan leaves.
+// calls whose k is large for the number of rows, which the whole-store plan leaves, where they bring memory for the lists of
+// the parts but not for the products of the dense plan (1000 x 768 bf16 rows, 8 queries, k = 128: 28 us, the dense plan 16).
 // stats: the diagnostics of a query that took this path: no candidates, no sampling, one workgroup per block.
 template <int KT> __global__ __launch_bounds__(256) void small_scan_kernel(FinalArgs a, uint64_t *lists, uint64_t *stats)
 {
@@ -2173,7 +2174,7 @@ kb_status_t launch_probe(kb *h, const void *queries_dev, bool q8, int32_t Q, con
     return e == hipSuccess ? launch_merge(lists, nprobe * splits, Q, k, indices_out_dev, scores_out_dev, s) : KB_ERR_DEVICE;
 }
 
-// kb_query on a small knowledge base that the whole-store plan leaves (k large for the number of rows): two launches.
+// kb_query on a small knowledge base that the whole-store plan leaves, with too little memory for the dense plan: two launches.
 kb_status_t launch_small(kb *h, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k, int parts, uint64_t *lists,
                          uint64_t *stats, int32_t *indices_out_dev, float *scores_out_dev, hipStream_t s)
 {
@@ -2394,23 +2395,10 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     return total;
 }
 
-size_t kb_query_plan_bytes(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32_t kind)
-{
-    if (!kb || n < 0 || n > kb->capacity || Q < 1 || k < 1 || k > KB_K_MAX || kind < 0 || kind > 3) return 0;
-    const bool draw = (kind & 1) != 0, q8 = (kind & 2) != 0;
-    WholePlan wp;
-    DensePlan dp;
-    const bool dense = make_dense_plan(kb, n, Q, k, draw, q8, &dp);
-    if (make_whole_plan(kb, n, Q, k, draw, q8, AMPLE, &wp)) return dense && dense_is_better(n, k, wp) ? dp.total : wp.total;
-    if (const int parts = small_path_parts(kb, n, Q, draw); parts && (!q8 || kb->dtype == KB_FP8_E4M3)) return make_small_plan(Q, k, parts).total;         // (with more than that, the call takes the dense plan)
-    if (dense) return dp.total;
-    Plan p;
-    return make_plan(kb, n, Q, k, draw, q8, AMPLE, &p) ? p.total : 0;
-}
-
 namespace {
 
 // What a call does that brings workspace_bytes: the best plan that fits.
+// (a store that can be scored in parts takes no call that brings less than their lists, whichever plan it then runs)
 struct Route {
     enum Kind { PIPELINE = 0, WHOLE = 1, DENSE = 2, PARTS = 3 } kind;
     Plan pipeline;
@@ -2430,7 +2418,7 @@ kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw
     const bool dense = make_dense_plan(h, n, Q, k, draw, q8, &r->dense) && r->dense.total <= workspace_bytes;
     if (dense && !(whole && !dense_is_better(n, k, r->whole))) {
         r->kind = Route::DENSE;
-        r->bytes = r->dense.total;
+        r->bytes = !whole && r->parts ? std::max(r->dense.total, r->small.total) : r->dense.total;
     } else if (whole) {
         r->kind = Route::WHOLE;
         r->bytes = r->whole.total;
@@ -2450,6 +2438,15 @@ kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw
 }
 
 }  // namespace
+
+size_t kb_query_plan_bytes(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32_t kind)
+{
+    if (!kb || n < 0 || n > kb->capacity || Q < 1 || k < 1 || k > KB_K_MAX || kind < 0 || kind > 3) return 0;
+    const bool draw = (kind & 1) != 0, q8 = (kind & 2) != 0;
+    if (q8 && kb->dtype != KB_FP8_E4M3) return 0;
+    Route r;
+    return choose_route(kb, n, Q, k, draw, q8, SIZE_MAX, &r) == KB_OK ? r.bytes : 0;
+}
 
 kb_status_t kb_query_plan(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32_t kind, size_t workspace_bytes, int64_t *out)
 {

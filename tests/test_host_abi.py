@@ -246,19 +246,27 @@ def test_workspace_size_bounds_the_plan_of_every_row_count(L, dtype, d, cap, Q, 
 
 
 @pytest.mark.parametrize("dtype,d,n,Q,k", [(kbmod.KB_F32, 64, 128, 1000, 128), (kbmod.KB_BF16, 64, 1, 1, 1), (kbmod.KB_BF16, 128, 500, 200, 16),
-                                           (kbmod.KB_FP8_E4M3, 64, 16384, 16, 128), (kbmod.KB_BF16, 256, 8193, 4, 100)])
-def test_plan_bytes_of_a_small_store_are_its_lists(L, dtype, d, n, Q, k):
-    # too many queries, or k too large for the number of rows, to be selected from groups of rows: one sorted list of k
-    # words per query and part of the rows is all the call keeps, besides the diagnostics
+                                           (kbmod.KB_FP8_E4M3, 64, 16384, 16, 128), (kbmod.KB_BF16, 256, 8193, 4, 100),
+                                           (kbmod.KB_BF16, 768, 1000, 8, 32), (kbmod.KB_F32, 64, 2500, 1, 50)])
+def test_plan_bytes_of_a_small_store_are_those_of_its_fastest_plan(L, dtype, d, n, Q, k):
+    # too many queries, or k too large for the number of rows, to be selected from groups of rows: every product (rows in steps of 128) is
+    # kept besides the diagnostics; a call that brings no more than one sorted list of k words per query and part of the rows is scored in parts
     st, h = _create(L, d=d, dtype=dtype, cap=n, scale=FAKE if dtype == kbmod.KB_FP8_E4M3 else None)
     assert st == 0
-    lists = Q * min(64, -(-n // 128)) * k * 8
+    parts, products = -(-n // 128), Q * -(-n // 128) * 128 * 4
+    lists = Q * min(64, parts) * k * 8
+    out = (ctypes.c_int64 * 4)()
     for kind in (0, 2):
         got = L.kb_query_plan_bytes(h, n, Q, k, kind)
         if kind == 2 and dtype != kbmod.KB_FP8_E4M3:
             assert got == 0                                  # fp8 queries on other keys: not a call the handle takes
             continue
-        assert lists <= got <= lists + 2048 and got <= L.kb_query_workspace_bytes(h, Q, k)
+        most = max(lists, products)
+        assert most <= got <= most + 2048 and got <= L.kb_query_workspace_bytes(h, Q, k)
+        assert L.kb_query_plan(h, n, Q, k, kind, got, out) == 0 and (out[0], out[1]) == (2, got)
+        if lists + 2048 < products:
+            assert L.kb_query_plan(h, n, Q, k, kind, lists + 2048, out) == 0 and out[0] == 3
+        assert L.kb_query_plan(h, n, Q, k, kind, lists - 1, out) == 7                # KB_ERR_WORKSPACE
     L.kb_destroy(h)
 
 
