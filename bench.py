@@ -488,15 +488,16 @@ def run_query_workload(args, torch, kbmod, W, dev, name):
     qps = Q / (ms_per_step * 1e-3)
     key_bytes = N * d * w.keys.element_size()
     # algorithmic bytes of one scan launch: every key row once (+ its fp32 norm, + its 64-bit tag when a
-    # mask is given) and the query block once.  The full-line kernels leave out the rows that the sampling pass has
-    # scored; which kernel ran is not reported, so those rows are counted out of every scan behind a sample.
-    scanned = N - counters["sample_keys"]
+    # mask is given) and the query block once.  Rows whose results were taken from the sampling pass are not read again by the
+    # kernels that leave them out; the plan tells how many rows the main scan went over.
+    plan = kb.plan(Q, k, kind=(1 if args.draw else 0) + (2 if queries.dtype == torch.float8_e4m3fn else 0))
+    scanned = plan["scanned_rows"]
     scan_bytes = scanned * (d * w.keys.element_size() + 4 + (8 if qmask is not None else 0)) + Q * d * queries.element_size()
     scan_ms = scan_ms_total / max(scan_calls, 1)
     achieved = scan_bytes / (scan_ms * 1e-3) / 1e9
     flops = 2.0 * Q * N * d
     scan_flops = 2.0 * Q * scanned * d
-    whole_store = counters["sample_keys"] == 0 and counters["candidates"] == 0
+    whole_store = plan["plan"] != "pipeline"
     result = {
         "metric": "KB top-k queries/sec + key-scan HBM GB/s (% of peak), N=1M d=1024 bf16",
         "value": qps,

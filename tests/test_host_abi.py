@@ -362,3 +362,17 @@ def test_batches_past_256_query_blocks_still_sample(L, n, d, k):
             per_query.append(out[1] / Q)
         assert max(per_query) < 1.1 * min(per_query)
         L.kb_destroy(h)
+
+
+# which main scans leave the sampled rows out: the full-line kernels on bf16 queries
+@pytest.mark.parametrize("dtype,d,n,Q,kind,leaves", [
+    (kbmod.KB_BF16, 1024, 1 << 20, 256, 0, True), (kbmod.KB_BF16, 1024, 1 << 20, 256, 1, True), (kbmod.KB_BF16, 1024, 1 << 20, 100, 0, True),
+    (kbmod.KB_FP8_E4M3, 768, 1 << 22, 1024, 0, True), (kbmod.KB_FP8_E4M3, 512, 2500001, 500, 2, False), (kbmod.KB_FP8_E4M3, 320, 1 << 20, 500, 0, False),
+    (kbmod.KB_FP8_E4M3, 768, 1 << 22, 1024, 1, False), (kbmod.KB_BF16, 128, 1 << 20, 256, 0, False), (kbmod.KB_BF16, 1024, 1 << 20, 20, 0, False),
+    (kbmod.KB_F32, 256, 1 << 20, 256, 0, False)])
+def test_the_plan_tells_the_rows_of_the_main_scan(L, dtype, d, n, Q, kind, leaves):
+    st, h = _create(L, d=d, dtype=dtype, cap=n, scale=FAKE if dtype == kbmod.KB_FP8_E4M3 else None)
+    out = (ctypes.c_int64 * 4)()
+    assert L.kb_query_plan(h, n, Q, 32, kind, 1 << 60, out) == 0
+    assert out[0] == 0 and out[2] > 0 and out[3] == (n - out[2] if leaves else n)
+    L.kb_destroy(h)
