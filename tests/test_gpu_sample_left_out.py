@@ -173,3 +173,15 @@ def test_queries_without_a_length_stay_on_their_lists(T, dtype, config, N, d):
     got = T.gpu_query(kb, w)
     assert kb.counters()["exhaustive_queries"] == 2 and not np.isnan(got[1]).any()
     kb.close()
+
+
+def test_lists_hold_what_a_sample_in_whole_rounds_lets_through(T):
+    """k = 2, a sample rounded down by a fifth: the second best of it scatters by a factor of ten from query to query, and no list runs over."""
+    w = W.clustered(seed=7, N=1284972, d=256, Q=850 * 9, k=2, centers=1254, device="cuda")
+    kb = T.build_kb(w)
+    kb.set_tuning("scan_config", 18)
+    for batch in w.queries.split(850):
+        kb.query(batch.contiguous(), 2)
+        counters = kb.counters()
+        assert counters["sample_keys"] > 0 and counters["exhaustive_queries"] == 0
+    kb.close()
