@@ -316,11 +316,12 @@ void lay_out(const Sizes &z, Plan *p)
     p->total = off;
 }
 
+double cubed(int32_t k) { return (double)k * k * k; }
+
 // The plan of a query over n rows with the kernels `c`.  Apart from the ln(gain) array it depends on n through the
 // number of key tiles only, which is what lets kb_query_workspace_bytes bound it over all row counts.
 void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, bool draw, Thrift thrift, Plan *out, Sizes *sizes)
 {
-    const bool leaves_out = leaves_sample_out(c) && thrift == AMPLE;
     Plan p;
     memset(&p, 0, sizeof p);
     const ConfigInfo &ci = c.ci, &sci = c.sci;
@@ -339,20 +340,40 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
     if (n < 1) n = 1;
     const int64_t nt = ceil_div(n, ci.tk), nts = ceil_div(n, sci.tk);     // key tiles of the main pass, of the sampling pass
 
-    const int64_t st = sample_tiles_for(h, sci, nts, Q, k, samples_in_rounds(c) && leaves_out, true);
+    // Where the full-line kernel runs the main pass, that pass can leave the sampled rows out: see main_row.  (Not where the sample is
+    // whole tiles: the full-line kernel addresses scattered rows in 32 bits, in units of 16 bytes, up to 64 GiB of keys.)  What it
+    // takes costs a call 3 to 10 us, a 50th of the main pass at most; what it gives is whole rounds of the compute units.  Time of the
+    // call with the sampled rows scored twice over this one's, 380 random calls of 17,000 to 1,300,000 rows and 33 to 1200 queries:
+    //   no round saved                  0.91 to 1.06    (97,373 x 256 bf16 rows, 256 queries, 381 items or 286: 55.4 us, 59.9)
+    //   one of 27 rounds and more       0.97 to 1.03
+    //   rows of 256 elements            0.96 to 1.02    (321,757 rows, 742 queries, 15 rounds or 13: 218 us, 223; keys of a draw: 0.99 to 1.36)
+    //   else                            0.99 to 1.15
+    // And k must be small for the groups, or most of them are scored again (k^3 = 31 groups^2: 85 us, 135).
+    // A handle that asks for a configuration gets it with all that belongs to it.
+    const int run_shift = draw ? 2 : 0;
+    const int64_t plain_st = sample_tiles_for(h, sci, nts, Q, k, false, true);
+    int64_t st = sample_tiles_for(h, sci, nts, Q, k, samples_in_rounds(c), true);
+    bool leaves_out = leaves_sample_out(c) && thrift == AMPLE;
+    if (leaves_out && !h->tune_config) {
+        const int64_t round = (int64_t)DEVICE_CUS * ci.wg_per_cu, rounds = ceil_div(nt * p.nqb, round), groups = st * sci.groups_per_tile;
+        const int64_t saved = rounds - ceil_div(ceil_div(n - st * sci.tk, ci.tk) * p.nqb, round);
+        const int64_t per_pair = h->d + (draw ? 256 : 0);       // (a draw's noise takes as long as 256 elements)
+        leaves_out = saved > 0 && 24 * saved >= rounds && per_pair * ci.tq >= 384 * 256 && cubed(k) <= (double)groups * groups;
+    }
+    if (leaves_out) {
+        const int64_t sampled_runs = (st * sci.tk) >> run_shift, runs = n >> run_shift;
+        leaves_out = st > 0 && 2 * sampled_runs < runs && runs >= 3 && !(sci.family == 4 && (uint64_t)n * h->d * key_bytes(h->dtype) >= ((uint64_t)1 << 36));
+    }
+    if (!leaves_out) st = plain_st;
     p.sample_tk = sci.tk;
     p.sample_tiles = st;
     p.sample_slots = (int32_t)(st * sci.groups_per_tile);
     p.sample_keys = st * sci.tk;
-    // Where the full-line kernel runs the main pass, that pass leaves the sampled rows out: see main_row.  (Not where the sample is
-    // whole tiles: the full-line kernel addresses scattered rows in 32 bits, in units of 16 bytes, up to 64 GiB of keys.)
-    const int run_shift = draw ? 2 : 0;
-    const int64_t sampled_runs = p.sample_keys >> run_shift, runs = n >> run_shift;
-    p.once = leaves_out && st > 0 && 2 * sampled_runs < runs && runs >= 3 && !(sci.family == 4 && (uint64_t)n * h->d * key_bytes(h->dtype) >= ((uint64_t)1 << 36));
+    p.once = leaves_out;
     p.main_rows = p.once ? n - p.sample_keys : n;
     // candidates per query.  (Where k is small the k-th best of the sample scatters widely, and lists that were large enough for the sample
     // before it was rounded down run over now and then: 1,284,972 x 256 rows, 850 queries, k = 2, a query in 1000, 6.2 ms for a call of 0.6.)
-    const int64_t expect = st > 0 ? ceil_div((int64_t)k * nts, k < 4 ? st : sample_tiles_for(h, sci, nts, Q, k, false, true)) : nt * ci.tk;
+    const int64_t expect = st > 0 ? ceil_div((int64_t)k * nts, k < 4 ? st : plain_st) : nt * ci.tk;
     p.cand_cap = cand_cap_for(expect, st > 0);
 
     const int wgpc = h->tune_wg_per_cu > 0 ? (int)h->tune_wg_per_cu : ci.wg_per_cu;
@@ -408,7 +429,6 @@ int64_t whole_max_rows(const kb *h, int32_t Q)
     return Q <= 128 ? WHOLE_MAX_ROWS : std::min(WHOLE_MAX_ROWS, pairs / Q);
 }
 constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
-double cubed(int32_t k) { return (double)k * k * k; }
 bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, Thrift thrift, WholePlan *out)
 {
     if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;

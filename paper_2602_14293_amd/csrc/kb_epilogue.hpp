@@ -358,11 +358,9 @@ __device__ inline void sample_epilogue_more(const f32x16 (&acc)[2][JB], const Ep
         const bool swap = two && value[1] > value[0];
         const size_t at = sample_slot_index(slot, p.sample_group_shift, p.qpad, q0 + ql);
         p.samp[at] = any ? pack_candidate(swap ? value[1] : value[0], sample_index<true>(p, tile_run, row0, tk, swap ? rl[1] : rl[0])) : 0ull;
-        if (p.samp_more) {
-            const uint32_t b3 = as_u32(m3[jb]);
-            const uint32_t others = m3[jb] > none ? score_to_ordered(as_f32((int32_t)b3 < 0 ? b3 & ~31u : b3 | 31u)) : 0u;
-            p.samp_more[at] = two ? pack_second(swap ? value[0] : value[1], others, (uint32_t)(swap ? place[0] : place[1])) : 0ull;
-        }
+        const uint32_t b3 = as_u32(m3[jb]);
+        const uint32_t others = m3[jb] > none ? score_to_ordered(as_f32((int32_t)b3 < 0 ? b3 & ~31u : b3 | 31u)) : 0u;
+        p.samp_more[at] = two ? pack_second(swap ? value[0] : value[1], others, (uint32_t)(swap ? place[0] : place[1])) : 0ull;
     }
 }
 

@@ -63,7 +63,7 @@ template <int KT_, int TQ_, bool QF8_ = false> struct WideCfg {
     static constexpr int KT = KT_;
     static constexpr bool QF8 = QF8_;                                // fp8 keys AND fp8 queries: the fp8 matrix instruction
     static constexpr int TK = 256, TQ = TQ_, THREADS = 512, NW = 8;
-    static constexpr bool MAPPED = !QF8;                             // the main pass can leave sampled rows out (main_row)
+    static constexpr bool MAY_PART = !QF8;                           // the main pass can leave sampled rows out (main_row)
     static constexpr int KEY_BYTES = KeyTraits<KT>::KEY_BYTES, QRY_BYTES = QF8 ? 1 : KeyTraits<KT>::QRY_BYTES;
     static constexpr bool MIX = QRY_BYTES != KEY_BYTES;              // fp8 keys with bf16 queries: a key piece serves two query chunks
     static constexpr int RB = 128;                                   // bytes of a query row per d-chunk, and of a key row per piece
@@ -95,7 +95,10 @@ template <int KT_, int TQ_, bool QF8_ = false> struct WideCfg {
     static_assert(SMEM_BYTES <= 160 * 1024, "LDS budget");
 };
 
-template <class C, bool SAMPLE, bool DRAW = false, bool NT = false>
+// APART: the main pass leaves out the rows that the sampling pass scores (the host decides per call).  A variant of its own, as what
+// that takes costs a call that does not do it 3 us: 97,373 x 256 rows, 256 queries 52.5 us, 55.6 with the sampling epilogue
+// that keeps three rows of a group and the main pass's map of the rows switched off by values.
+template <class C, bool SAMPLE, bool DRAW, bool NT, bool APART>
 __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
 {
     static_assert(!DRAW || (!SAMPLE && !C::QF8), "keys of the weighted random selection: main pass, bf16");
@@ -158,7 +161,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
             const int64_t left = p.n_keys - tile_row0;
             last = left < TK ? (int)left - 1 : TK - 1;
             base = 0;
-            row_base = SAMPLE || !C::MAPPED ? (uint32_t)tile_row0 : main_base(p, (uint32_t)tile_row0);
+            row_base = SAMPLE || !APART ? (uint32_t)tile_row0 : main_base(p, (uint32_t)tile_row0);
             ld_src = static_cast<const unsigned char *>(p.keys) + ((SAMPLE && p.row_mul) ? 0 : (size_t)row_base * key_row_bytes);
         } else {
             last = p.Q - 1 - ld_qb * TQ;
@@ -172,8 +175,8 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = h * C::PIECE_ROWS + ld_row + j * 32;
-                if (SAMPLE && role == 0 && p.row_mul) off[h][j] = (uint32_t)(((uint64_t)sample_row<true>(p, tile_run, ld_tile, TK, r) * rb + ld_slot) >> 4);
-                else if (!SAMPLE && C::MAPPED && role == 0) off[h][j] = (main_row(p, (uint32_t)ld_tile * TK + (uint32_t)(r < last ? r : last)) - row_base) * rb + ld_slot;
+                if (SAMPLE && role == 0 && p.row_mul) off[h][j] = (uint32_t)(((uint64_t)sample_row<APART>(p, tile_run, ld_tile, TK, r) * rb + ld_slot) >> 4);
+                else if (!SAMPLE && APART && role == 0) off[h][j] = (main_row(p, (uint32_t)ld_tile * TK + (uint32_t)(r < last ? r : last)) - row_base) * rb + ld_slot;
                 else off[h][j] = ((uint32_t)(base + (r < last ? r : last)) * rb + ld_slot) >> (role == 0 ? OSH : 0);
             }
     };
@@ -187,13 +190,13 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
         asm volatile("" : "+v"(lane));
         if constexpr (SAMPLE) {
             const int64_t tile_run = sample_tile_run(p, ld_tile, TK);
-            const int64_t r = sample_row<true>(p, tile_run, ld_tile, TK, ridx * 64 + lane);
+            const int64_t r = sample_row<APART>(p, tile_run, ld_tile, TK, ridx * 64 + lane);
             __builtin_amdgcn_global_load_lds((const void *)(p.inv_norm + r), (lds_ptr)(aux + C::AUX_INVK + ridx * 256), 4, 0, 0);
             if (filter) {
 #pragma unroll
                 for (int h2 = 0; h2 < 2; ++h2) {
                     const int i = ridx * 2 + h2;
-                    const int64_t rt = sample_row<true>(p, tile_run, ld_tile, TK, i * 32 + (lane >> 1));
+                    const int64_t rt = sample_row<APART>(p, tile_run, ld_tile, TK, i * 32 + (lane >> 1));
                     __builtin_amdgcn_global_load_lds((const void *)(reinterpret_cast<const uint32_t *>(p.tags + rt) + (lane & 1)),
                                                      (lds_ptr)(aux + C::AUX_TAG + i * 256), 4, 0, 0);
                 }
@@ -203,10 +206,10 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
         const int64_t row0 = (int64_t)ld_tile * TK;
         const int64_t left = p.n_keys - row0;
         const uint32_t last = left < TK ? (uint32_t)left - 1 : TK - 1;
-        const uint32_t base = C::MAPPED ? __builtin_amdgcn_readfirstlane(main_base(p, (uint32_t)row0)) : (uint32_t)row0;
+        const uint32_t base = APART ? __builtin_amdgcn_readfirstlane(main_base(p, (uint32_t)row0)) : (uint32_t)row0;
         auto from_base = [&](uint32_t r) {
             const uint32_t rr = r < last ? r : last;
-            return C::MAPPED ? main_row(p, (uint32_t)row0 + rr) - base : rr;
+            return APART ? main_row(p, (uint32_t)row0 + rr) - base : rr;
         };
         const uint32_t mine = from_base((uint32_t)(ridx * 64 + lane)) * 4u;
         __builtin_amdgcn_global_load_lds((const void *)(uniform_address(p.inv_norm + base) + mine), (lds_ptr)(aux + C::AUX_INVK + ridx * 256), 4, 0, 0);
@@ -345,13 +348,17 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
         const int64_t tile_run = SAMPLE ? sample_tile_run(p, tile, TK) : 0;
 #pragma unroll
         for (int rh = 0; rh < 2; ++rh) {
-            if constexpr (SAMPLE)       // sampling groups: (piece, wave row, lane half) = 32 rows each
-                sample_epilogue_more<JB>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p,
-                                        (int64_t)tile * C::GROUPS_PER_TILE + (rh * 2 + wm) * 2 + half, tile_run, TK);
-            else if constexpr (DRAW)
-                main_epilogue_draw<IB, JB, C::MAPPED>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
+            if constexpr (SAMPLE) {     // sampling groups: (piece, wave row, lane half) = 32 rows each
+                const int64_t slot = (int64_t)tile * C::GROUPS_PER_TILE + (rh * 2 + wm) * 2 + half;
+                if constexpr (APART)
+                    sample_epilogue_more<JB>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, slot, tile_run, TK);
+                else
+                    sample_epilogue<IB, JB, false>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, slot,
+                                                   [&](int rl) { return sample_index<false>(p, tile_run, row0, TK, rl); });
+            } else if constexpr (DRAW)
+                main_epilogue_draw<IB, JB, APART>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
             else
-                main_epilogue<IB, JB, C::KEY_BYTES == 1, C::MAPPED>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
+                main_epilogue<IB, JB, C::KEY_BYTES == 1, APART>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
         }
     };
 
@@ -689,17 +696,24 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
     if (!SAMPLE) flush_records(p, my_region, wave_cnt, blockIdx.x * NW + wave);      // what is left in the region
 }
 
-template <class C, bool SAMPLE, bool DRAW, bool NT> hipError_t launch_scan_wide_variant(int grid, const ScanArgs &a, hipStream_t s)
+template <class C, bool SAMPLE, bool DRAW, bool NT, bool APART> hipError_t launch_scan_wide_variant(int grid, const ScanArgs &a, hipStream_t s)
 {
     static LdsAllowed allowed;
-    auto *fn = &kb_scan_wide_kernel<C, SAMPLE, DRAW, NT>;
+    auto *fn = &kb_scan_wide_kernel<C, SAMPLE, DRAW, NT, APART>;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed, C::SMEM_BYTES); e != hipSuccess) return e;
     hipExtLaunchKernelGGL(fn, dim3(grid), dim3(C::THREADS), C::SMEM_BYTES, s, scan_timing.start, scan_timing.stop, 0, a);
     return hipGetLastError();
 }
+template <class C, bool SAMPLE, bool DRAW, bool APART> hipError_t launch_scan_wide_parted(int grid, const ScanArgs &a, hipStream_t s)
+{
+    return a.keys_once ? launch_scan_wide_variant<C, SAMPLE, DRAW, true, APART>(grid, a, s) : launch_scan_wide_variant<C, SAMPLE, DRAW, false, APART>(grid, a, s);
+}
 template <class C, bool SAMPLE, bool DRAW> hipError_t launch_scan_wide_policy(int grid, const ScanArgs &a, hipStream_t s)
 {
-    return a.keys_once ? launch_scan_wide_variant<C, SAMPLE, DRAW, true>(grid, a, s) : launch_scan_wide_variant<C, SAMPLE, DRAW, false>(grid, a, s);
+    if constexpr (C::MAY_PART) {
+        if (SAMPLE ? a.samp_more != nullptr : a.skip_mul != 0) return launch_scan_wide_parted<C, SAMPLE, DRAW, true>(grid, a, s);
+    }
+    return launch_scan_wide_parted<C, SAMPLE, DRAW, false>(grid, a, s);
 }
 
 template <class C> hipError_t launch_scan_wide_cfg(bool sample, int grid, const ScanArgs &a, hipStream_t s)

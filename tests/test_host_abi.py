@@ -376,3 +376,21 @@ def test_the_plan_tells_the_rows_of_the_main_scan(L, dtype, d, n, Q, kind, leave
     assert L.kb_query_plan(h, n, Q, 32, kind, 1 << 60, out) == 0
     assert out[0] == 0 and out[2] > 0 and out[3] == (n - out[2] if leaves else n)
     L.kb_destroy(h)
+
+
+# the sampled rows are left out where that saves the compute units a round, of at most 24, with enough work for every pair, and where k is
+# small for the groups of the sample
+@pytest.mark.parametrize("dtype,d,n,Q,k,kind,leaves", [
+    (kbmod.KB_BF16, 1024, 1 << 20, 256, 32, 0, True), (kbmod.KB_BF16, 512, 194927, 509, 70, 0, True), (kbmod.KB_BF16, 256, 25059, 635, 22, 1, True),
+    (kbmod.KB_BF16, 256, 97373, 256, 20, 0, False), (kbmod.KB_BF16, 1024, 89880, 299, 42, 0, False), (kbmod.KB_BF16, 768, 171198, 256, 77, 0, False),   # no round saved
+    (kbmod.KB_BF16, 1024, 19224, 256, 127, 0, False), (kbmod.KB_FP8_E4M3, 512, 20275, 256, 88, 0, False),                                              # k
+    (kbmod.KB_BF16, 256, 321757, 742, 57, 0, False), (kbmod.KB_BF16, 256, 852694, 117, 32, 0, False),                                                  # short rows
+    (kbmod.KB_BF16, 512, 756664, 1040, 1, 1, False), (kbmod.KB_BF16, 512, 610988, 836, 3, 0, False)])                                                  # one round of many
+def test_sampled_rows_are_left_out_where_that_gains(L, dtype, d, n, Q, k, kind, leaves):
+    st, h = _create(L, d=d, dtype=dtype, cap=n, scale=FAKE if dtype == kbmod.KB_FP8_E4M3 else None)
+    out = (ctypes.c_int64 * 4)()
+    assert L.kb_query_plan(h, n, Q, k, kind, 1 << 60, out) == 0
+    assert out[0] == 0 and out[2] > 0 and (out[3] == n - out[2]) == leaves
+    assert L.kb_set_tuning(h, b"scan_config", 22 if dtype == kbmod.KB_FP8_E4M3 else 18) == 0      # asked for by name: with all that belongs to it
+    assert L.kb_query_plan(h, n, Q, k, kind, 1 << 60, out) == 0 and out[3] == n - out[2]
+    L.kb_destroy(h)
