@@ -442,7 +442,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     // tiles of 32 rows while those of 128 would leave compute units without one; f32: of 16 while they run side by side (16,000 x
     // 768 rows, 20 queries: 40 us, 27 with tiles of 64 x 64; at 8000 rows 25 against 26)
     if (p.config == 1 && n <= WHOLE_SMALL_TILE_ROWS)
-        p.config = h->dtype != KB_F32 ? 13 : Q <= 16 || n <= WHOLE_SMALL_TILE_ROWS / 2 ? SMALL_F32_CONFIG : F32_SQUARE_CONFIG;
+        p.config = h->dtype != KB_F32 ? 13 : Q <= 16 || n <= WHOLE_SMALL_TILE_ROWS / 2 || thrift == LEAST ? SMALL_F32_CONFIG : F32_SQUARE_CONFIG;
     ConfigInfo ci;
     if (!scan_config_info(h->dtype, p.config, &ci)) return false;
     p.tk = ci.tk;
@@ -455,10 +455,20 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     p.group_rows = p.fine ? fine_rows : ci.tk;
     static_assert(WHOLE_MAX_ROWS_FEW / 128 <= WHOLE_MAX_GROUPS && WHOLE_MAX_ROWS / 64 <= WHOLE_MAX_GROUPS, "whole tiles: 128 rows, or 64 with more than 32 queries");
     p.groups = (int32_t)(tiles * (ci.tk / p.group_rows));
-    // Groups with three of a query's k best are scored again, k^3 / 6 / groups^2 of them if rows come in no order.  Time of the
-    // pipeline over this plan's at k^3 / groups^2 of 4 (k = 100, 16,000 rows of 512 elements), 8 to 512 queries: 1.5 to 2.0 with
-    // bf16 rows, 1.1 to 1.9 with fp8, 1.1 to 1.6 with f32; at 8.4 (k = 128) 1.4 to 1.7, 0.8 to 1.8, 0.8 to 1.6.
-    if (cubed(k) > 4.0 * (double)p.groups * p.groups) return false;
+    // Groups with three of a query's k best are scored again, k^3 / 6 / groups^2 of them if rows come in no order, up to k / 2 where
+    // similar rows are neighbours.  That costs a call one step of the selecting workgroups or several, each as long as a row's loads.
+    // Time of the pipeline over this plan's at k^3 / groups^2 of 0.12 to 4, stores of 5000 to 131,072 rows in runs of 4 to 64
+    // similar ones, lowest | tenth | median of some 40 calls each:
+    //                            up to 32 queries                                                  more
+    //   groups of 16 or 32 rows  bf16 768: 1.21 1.25 1.40    1024: 0.96 1.15 1.50    2048: 0.69    256: 0.95 1.12 1.40    768: 0.75
+    //                            fp8 1024: 1.04 1.38 1.80    2048: 0.95 1.39 1.78    4096: 0.88    -
+    //                            f32  256: 1.16 1.31 1.57     512: 0.55 1.02 1.51   1024: 0.61     128: 1.18 1.42 1.90    768: 0.82
+    //   groups of 64 rows        fp8 x 8 256: 0.99 1.06 1.25  768: 0.66 0.81 1.00                  fp8 768: 0.68, f32 768: 0.60
+    //   whole tiles              0.18 to 0.42                                                      0.24 to 0.73
+    // One in fifty queries is the limit where that loses.
+    const size_t row_bytes = (size_t)h->d * key_bytes(h->dtype);
+    const bool cheap = p.group_rows <= 32 && row_bytes <= (Q > 32 ? 512 : h->dtype == KB_F32 ? 1024 : 1536);
+    if (cubed(k) > (cheap ? 4.0 : 0.12) * (double)p.groups * p.groups) return false;
     const int64_t items = tiles * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
     p.grid = (int32_t)(items < most ? items : most);
     p.off_best = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));       // the diagnostics come first, as always
@@ -2433,20 +2443,21 @@ struct Route {
 kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, size_t workspace_bytes, Route *r)
 {
     const auto whole_fits = [&](Thrift thrift) { return make_whole_plan(h, n, Q, k, draw, q8, thrift, &r->whole) && r->whole.total <= workspace_bytes; };
-    const bool whole = whole_fits(AMPLE) || whole_fits(LEAST);
+    const bool whole = whole_fits(AMPLE);
     r->parts = small_path_parts(h, n, Q, draw);
     if (r->parts) r->small = make_small_plan(Q, k, r->parts);
-    if (!whole && r->parts && workspace_bytes < r->small.total) return KB_ERR_WORKSPACE;
-    const bool dense = make_dense_plan(h, n, Q, k, draw, q8, &r->dense) && r->dense.total <= workspace_bytes;
+    const bool lists = !r->parts || workspace_bytes >= r->small.total;
+    const bool dense = (whole || lists) && make_dense_plan(h, n, Q, k, draw, q8, &r->dense) && r->dense.total <= workspace_bytes;
     if (dense && !(whole && !dense_is_better(n, k, r->whole))) {
         r->kind = Route::DENSE;
         r->bytes = !whole && r->parts ? std::max(r->dense.total, r->small.total) : r->dense.total;
-    } else if (whole) {
+    } else if (whole || whole_fits(LEAST)) {
         r->kind = Route::WHOLE;
         r->bytes = r->whole.total;
     } else if (r->parts) {
         r->kind = Route::PARTS;
         r->bytes = r->small.total;
+        if (!lists) return KB_ERR_WORKSPACE;
     } else {
         for (const Thrift thrift : {AMPLE, SCORED_TWICE, LEAST}) {
             if (!make_plan(h, n, Q, k, draw, q8, thrift, &r->pipeline)) return KB_ERR_INVALID_ARG;

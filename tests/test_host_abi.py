@@ -394,3 +394,27 @@ def test_sampled_rows_are_left_out_where_that_gains(L, dtype, d, n, Q, k, kind, 
     assert L.kb_set_tuning(h, b"scan_config", 22 if dtype == kbmod.KB_FP8_E4M3 else 18) == 0      # asked for by name: with all that belongs to it
     assert L.kb_query_plan(h, n, Q, k, kind, 1 << 60, out) == 0 and out[3] == n - out[2]
     L.kb_destroy(h)
+
+
+PLANS = ("pipeline", "whole", "dense", "parts")
+
+
+def _plan_of(L, dtype, d, n, Q, k, kind=0):
+    st, h = _create(L, d=d, dtype=dtype, cap=n, scale=FAKE if dtype == kbmod.KB_FP8_E4M3 else None)
+    out = (ctypes.c_int64 * 4)()
+    assert st == 0 and L.kb_query_plan(h, n, Q, k, kind, 1 << 60, out) == 0
+    L.kb_destroy(h)
+    return PLANS[out[0]]
+
+
+# k large for the groups: stores whose similar rows are neighbours have many groups to score again, which the whole-store plan bears where
+# groups are small and rows short
+@pytest.mark.parametrize("dtype,d,n,Q,k,kind,plan", [
+    (kbmod.KB_BF16, 768, 131072, 30, 128, 0, "whole"), (kbmod.KB_BF16, 256, 65536, 100, 128, 0, "whole"), (kbmod.KB_FP8_E4M3, 1024, 40000, 17, 128, 0, "whole"),
+    (kbmod.KB_F32, 256, 24000, 30, 128, 0, "whole"), (kbmod.KB_F32, 128, 40000, 64, 128, 0, "whole"),
+    (kbmod.KB_BF16, 768, 190000, 8, 128, 0, "pipeline"), (kbmod.KB_F32, 768, 190000, 30, 90, 0, "pipeline"), (kbmod.KB_BF16, 256, 190000, 128, 128, 0, "pipeline"),
+    (kbmod.KB_BF16, 768, 32000, 128, 128, 0, "pipeline"), (kbmod.KB_BF16, 2048, 18000, 32, 90, 0, "pipeline"), (kbmod.KB_F32, 512, 18000, 32, 90, 0, "pipeline"),
+    (kbmod.KB_FP8_E4M3, 768, 48000, 100, 128, 0, "pipeline"), (kbmod.KB_FP8_E4M3, 768, 32000, 8, 90, 2, "pipeline"),
+    (kbmod.KB_F32, 1024, 16000, 17, 36, 0, "dense"), (kbmod.KB_BF16, 768, 190000, 8, 40, 0, "whole")])
+def test_large_k_on_stores_in_groups(L, dtype, d, n, Q, k, kind, plan):
+    assert _plan_of(L, dtype, d, n, Q, k, kind) == plan
