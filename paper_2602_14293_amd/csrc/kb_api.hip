@@ -422,17 +422,27 @@ constexpr int64_t WHOLE_MAX_ROWS_FEW = 5 * 128 * 2 * DEVICE_CUS, WHOLE_MAX_ROWS 
 //   fp8 x 8  65,536 x 512: 1.84 | 1.16    131,072 x 256: 1.73 | 1.23    65,536 x 1024: 1.71 | 0.89   (rows of 256: no pipelined kernel)
 //   f32      65,536 x 1024: 1.14 | 1.16   131,072 x 512: 1.14 | 1.06    131,072 x 1024: 1.02 | 1.05
 constexpr int WHOLE_MAX_QUERIES = 4096;
-int64_t whole_max_rows(const kb *h, int32_t Q)
+// Those are calls whose last block of 128 queries is full; bf16 rows pay for the padding (130,055 x 1024 rows, 129 queries: 0.87), so
+// that it counts.  Where the kernel of the pipeline has the matrix cores' rate and this one has not, long rows lose as well: bf16 | fp8 x 8
+//   2^24 products  2048: 1.09 to 1.12 | 1.53    4096: 0.95 to 1.04 | 1.13    8192: 0.88 to 0.90 | 0.95
+//   2^25 products  1024:      -       | 1.18    2048:      -       | 0.97    4096:      -       | 0.86 to 0.98
+//   10,000,000     2048: 1.27         | 1.46    4096: 1.01         | 1.09    8192: 0.88         | 0.97
+//   2^23 products  8192: 1.16 to 1.52 | 1.47   16384: 1.12         | 1.34
+// (fp8 rows with bf16 queries 1.10 and more at 2^25 products of up to 16,384 elements, f32 1.03 and more)
+int64_t whole_max_rows(const kb *h, int32_t Q, bool q8)
 {
     if (Q <= 32) return WHOLE_MAX_ROWS_FEW;
-    const int64_t pairs = (int64_t)1 << (h->dtype == KB_BF16 ? 24 : h->dtype == KB_F32 ? 26 : 25);
-    return Q <= 128 ? WHOLE_MAX_ROWS : std::min(WHOLE_MAX_ROWS, pairs / Q);
+    if (Q <= 128) return WHOLE_MAX_ROWS;
+    const int64_t columns = h->dtype == KB_BF16 ? ceil_div(Q, 128) * 128 : Q;
+    int64_t pairs = (int64_t)1 << (h->dtype == KB_BF16 ? 24 : h->dtype == KB_F32 ? 26 : 25);
+    if (h->dtype == KB_BF16 || q8) pairs = std::min(pairs, std::max((int64_t)1 << 23, ((int64_t)1 << 35) / h->d));
+    return std::min(WHOLE_MAX_ROWS, pairs / columns);
 }
 constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
 bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, Thrift thrift, WholePlan *out)
 {
     if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
-    if (n < 1 || Q > WHOLE_MAX_QUERIES || n > whole_max_rows(h, Q) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
+    if (n < 1 || Q > WHOLE_MAX_QUERIES || n > whole_max_rows(h, Q, q8) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
     WholePlan p;
     if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
     else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : n >= 128 * 2 * DEVICE_CUS && h->d >= 512 ? 21 : 16;    // (14: once every resident workgroup gets a tile)
@@ -2411,13 +2421,15 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     const int64_t parts = std::min<int64_t>({PROBE_MAX, SMALL_BLOCKS / Q, ceil_div(kb->capacity, 128)});
     if (parts > 0) total = std::max(total, make_small_plan(Q, k, (int)parts).total);
     // the whole-store plan: grows with its groups, so with the rows up to where the groups get coarser and to the most it takes
-    const int64_t whole_rows = std::min(kb->capacity, whole_max_rows(kb, Q));
-    const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, WHOLE_MAX_GROUPS * 32, WHOLE_MAX_GROUPS * 64, whole_rows};
-    for (int64_t n : most)
-        for (int q8 = 0; q8 < 2; ++q8) {
+    for (int q8 = 0; q8 < 2; ++q8) {
+        const int64_t whole_rows = std::min(kb->capacity, whole_max_rows(kb, Q, q8 != 0));
+        const int64_t f32_square = DEVICE_CUS / ceil_div(Q, 128) * 128;        // rows up to which f32 batches past 64 queries have the lower tiles
+        const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, f32_square, WHOLE_MAX_GROUPS * 32, WHOLE_MAX_GROUPS * 64, whole_rows};
+        for (int64_t n : most) {
             WholePlan wp;
             if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, AMPLE, &wp)) total = std::max(total, wp.total);
         }
+    }
     // the dense plan: grows with the rows
     for (int kind = 0; kind < 4; ++kind) {
         DensePlan dp;

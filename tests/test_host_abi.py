@@ -418,3 +418,14 @@ def _plan_of(L, dtype, d, n, Q, k, kind=0):
     (kbmod.KB_F32, 1024, 16000, 17, 36, 0, "dense"), (kbmod.KB_BF16, 768, 190000, 8, 40, 0, "whole")])
 def test_large_k_on_stores_in_groups(L, dtype, d, n, Q, k, kind, plan):
     assert _plan_of(L, dtype, d, n, Q, k, kind) == plan
+
+
+# more than 128 queries: bf16 rows pay for the padding of the last block, long rows for the matrix cores' rate
+@pytest.mark.parametrize("dtype,d,n,Q,kind,plan", [
+    (kbmod.KB_BF16, 1024, 65536, 256, 0, "whole"), (kbmod.KB_BF16, 1024, 65536, 129, 0, "whole"), (kbmod.KB_BF16, 2048, 16384, 1024, 0, "whole"),
+    (kbmod.KB_BF16, 1024, 130055, 129, 0, "pipeline"), (kbmod.KB_BF16, 256, 104857, 160, 0, "pipeline"),
+    (kbmod.KB_BF16, 4096, 65536, 256, 0, "pipeline"), (kbmod.KB_BF16, 8192, 20000, 512, 0, "pipeline"), (kbmod.KB_BF16, 8192, 32768, 256, 0, "whole"),
+    (kbmod.KB_FP8_E4M3, 1024, 131072, 256, 2, "whole"), (kbmod.KB_FP8_E4M3, 2048, 131072, 256, 2, "pipeline"), (kbmod.KB_FP8_E4M3, 4096, 131072, 256, 0, "whole"),
+    (kbmod.KB_F32, 2048, 65536, 1024, 0, "whole")])
+def test_large_batches_scored_whole(L, dtype, d, n, Q, kind, plan):
+    assert _plan_of(L, dtype, d, n, Q, 16, kind) == plan
