@@ -476,6 +476,10 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     //   groups of 64 rows        fp8 x 8 256: 0.99 1.06 1.25  768: 0.66 0.81 1.00                  fp8 768: 0.68, f32 768: 0.60
     //   whole tiles              0.18 to 0.42                                                      0.24 to 0.73
     // One in fifty queries is the limit where that loses.
+    // f32, tiles of 64 rows, too many to be halved into groups: four neighbours share a group.  The pipeline from before had tiles of 128 as this
+    // plan had; now, with 64 in both, time of the pipeline over this plan's, 140,000 x 768 rows and 64 queries in no order | runs of 4 | 32:
+    // k = 16 1.06 | 0.80 | 0.69 (256 elements 1.28 | 1.00 | 0.91), 24 1.07 | 0.71 | 0.64, 40 1.08 | 0.59 | 0.53, 80 1.16 | 0.46 | 0.40
+    if (p.config == F32_SQUARE_CONFIG && !p.fine && k > 16) return false;
     const size_t row_bytes = (size_t)h->d * key_bytes(h->dtype);
     const bool cheap = p.group_rows <= 32 && row_bytes <= (Q > 32 ? 512 : h->dtype == KB_F32 ? 1024 : 1536);
     if (cubed(k) > (cheap ? 4.0 : 0.12) * (double)p.groups * p.groups) return false;
@@ -2463,7 +2467,7 @@ kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw
     if (dense && !(whole && !dense_is_better(n, k, r->whole))) {
         r->kind = Route::DENSE;
         r->bytes = !whole && r->parts ? std::max(r->dense.total, r->small.total) : r->dense.total;
-    } else if (whole || whole_fits(LEAST)) {
+    } else if (whole || (r->parts && whole_fits(LEAST))) {
         r->kind = Route::WHOLE;
         r->bytes = r->whole.total;
     } else if (r->parts) {
@@ -2472,11 +2476,16 @@ kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw
         if (!lists) return KB_ERR_WORKSPACE;
     } else {
         for (const Thrift thrift : {AMPLE, SCORED_TWICE, LEAST}) {
+            r->kind = Route::PIPELINE;
             if (!make_plan(h, n, Q, k, draw, q8, thrift, &r->pipeline)) return KB_ERR_INVALID_ARG;
-            if (r->pipeline.total <= workspace_bytes) break;
+            r->bytes = r->pipeline.total;
+            if (r->bytes <= workspace_bytes) break;
+            if (thrift == AMPLE && whole_fits(LEAST)) {
+                r->kind = Route::WHOLE;
+                r->bytes = r->whole.total;
+                break;
+            }
         }
-        r->kind = Route::PIPELINE;
-        r->bytes = r->pipeline.total;
         if (workspace_bytes < r->bytes) return KB_ERR_WORKSPACE;
     }
     return KB_OK;

@@ -415,7 +415,8 @@ def _plan_of(L, dtype, d, n, Q, k, kind=0):
     (kbmod.KB_BF16, 768, 190000, 8, 128, 0, "pipeline"), (kbmod.KB_F32, 768, 190000, 30, 90, 0, "pipeline"), (kbmod.KB_BF16, 256, 190000, 128, 128, 0, "pipeline"),
     (kbmod.KB_BF16, 768, 32000, 128, 128, 0, "pipeline"), (kbmod.KB_BF16, 2048, 18000, 32, 90, 0, "pipeline"), (kbmod.KB_F32, 512, 18000, 32, 90, 0, "pipeline"),
     (kbmod.KB_FP8_E4M3, 768, 48000, 100, 128, 0, "pipeline"), (kbmod.KB_FP8_E4M3, 768, 32000, 8, 90, 2, "pipeline"),
-    (kbmod.KB_F32, 1024, 16000, 17, 36, 0, "dense"), (kbmod.KB_BF16, 768, 190000, 8, 40, 0, "whole")])
+    (kbmod.KB_F32, 1024, 16000, 17, 36, 0, "dense"), (kbmod.KB_BF16, 768, 190000, 8, 40, 0, "whole"),
+    (kbmod.KB_F32, 768, 140000, 64, 60, 0, "pipeline"), (kbmod.KB_F32, 768, 140000, 64, 16, 0, "whole"), (kbmod.KB_F32, 768, 131072, 64, 60, 0, "whole")])
 def test_large_k_on_stores_in_groups(L, dtype, d, n, Q, k, kind, plan):
     assert _plan_of(L, dtype, d, n, Q, k, kind) == plan
 
