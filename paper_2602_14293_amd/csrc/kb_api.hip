@@ -101,7 +101,7 @@ int scan_config_for(int key_dtype, int Q, int d, int64_t n, Thrift thrift)
     if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= 512) return 18;
     // 33 to 128 queries: the full-line kernel once a workgroup has several tiles to stream (its ring takes longer to fill)
     if (key_dtype == KB_BF16 && Q > 32 && d * 2 >= 512 && n >= WIDE128_MIN_ROWS) return 19;
-    if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= (least ? 384 : 256)) return 17;
+    if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= 384) return 17;      // (rows of 256 bytes: see kb_configs.hpp)
     if (key_dtype == KB_FP8_E4M3 && Q > 128 && d >= (least ? 256 : 192)) return d >= 256 && d % 128 == 0 ? FP8_WIDE_CONFIG : 4;
     // below that size a query is bound by the latency of its launches: tiles of 64 rows (twice the workgroups, half the
     // chunks each) finish sooner: 62 against 71 us per call on 65,536 rows of 768 bf16 values with 64 queries

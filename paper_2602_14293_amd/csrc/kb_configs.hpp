@@ -50,8 +50,9 @@ constexpr int SMALL_F32_CONFIG = 15;
 
 // Software-pipelined configurations (kb_scan_sp.hpp): XS(id, key dtype, TQ, NSA, NSB); 256-row tiles, 512 threads,
 // NSA / NSB = ring depth of key / query chunks in LDS.
-// bf16: the loads are issued between the MFMAs (IL mode).  Rows of 256 and 384 bytes (longer ones: the full-line kernel); call on 2^20 rows of
-// 256 bytes, 200 queries, in us: 128, tiled kernel 133; 384 bytes: 170, with a ring of five 175.  (Rows of 128 bytes in rings of three: no gain.)
+// bf16: the loads are issued between the MFMAs (IL mode).  Rows of 384 bytes (longer ones: the full-line kernel); call on 2^20 rows, 200
+// queries, in us: 170, with a ring of five 175.  Rows of 256 bytes stay with the tiled kernel: 128 against 133 there, but slower on most
+// stores (67,054 rows, 256 queries 50 against 43, 266,059 rows, 200 queries 64 against 59, 1,444,949 rows, 166 queries 194 against 190).
 #define KB_SCAN_SP_CONFIGS_BF16_IL(XI) \
     XI(17, KB_BF16, 256, 4, 4)
 // fp8 with bf16 queries: rows of 192 bytes, and those that are no multiple of 128 (192 bytes, 200 queries, per item: 8.0 us, tiled kernel 16.6)
