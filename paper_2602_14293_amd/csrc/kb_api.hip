@@ -95,6 +95,11 @@ enum Thrift {
     LEAST               // ... and the tiled kernel (f32: its 128-row tiles) where another is faster on rows too short for deep rings
 };
 
+// Rows too short for rings of four: the pipelined kernel's tiles of 256 rows pay once there are enough of them for the compute units.  Time of
+// the tiled kernel's call over that of the pipelined one's: fp8 keys of 192 elements with bf16 queries, 24,134 rows 0.75, 18,106 rows and 945
+// queries 0.88, 33,063 rows 1.00, 39,161 1.15; with fp8 queries 107 items (27,424 rows of 128, 256 queries) 0.96, 130 items 1.2 to 1.3
+constexpr int64_t SHORT_ROWS_MIN_ROWS = 32768, SHORT_ROWS_MIN_ITEMS = 112;
+
 int scan_config_for(int key_dtype, int Q, int d, int64_t n, Thrift thrift)
 {
     const bool least = thrift == LEAST;
@@ -102,7 +107,7 @@ int scan_config_for(int key_dtype, int Q, int d, int64_t n, Thrift thrift)
     // 33 to 128 queries: the full-line kernel once a workgroup has several tiles to stream (its ring takes longer to fill)
     if (key_dtype == KB_BF16 && Q > 32 && d * 2 >= 512 && n >= WIDE128_MIN_ROWS) return 19;
     if (key_dtype == KB_BF16 && Q > 128 && d * 2 >= 384) return 17;      // (rows of 256 bytes: see kb_configs.hpp)
-    if (key_dtype == KB_FP8_E4M3 && Q > 128 && d >= (least ? 256 : 192)) return d >= 256 && d % 128 == 0 ? FP8_WIDE_CONFIG : 4;
+    if (key_dtype == KB_FP8_E4M3 && Q > 128 && d >= (least || n < SHORT_ROWS_MIN_ROWS ? 256 : 192)) return d >= 256 && d % 128 == 0 ? FP8_WIDE_CONFIG : 4;
     // below that size a query is bound by the latency of its launches: tiles of 64 rows (twice the workgroups, half the
     // chunks each) finish sooner: 62 against 71 us per call on 65,536 rows of 768 bf16 values with 64 queries
     // (and 64 against 70 us with 128 queries)
@@ -201,7 +206,8 @@ bool choose_kernels(const kb *h, int64_t n, int32_t Q, bool draw, bool q8, Thrif
         if (h->dtype != KB_FP8_E4M3) return false;
         const int generic8 = Q <= 64 ? FP8_QUERY_TILED_CONFIG : Q <= 128 ? FP8_QUERY_TILED_CONFIG + 1 : FP8_QUERY_TILED_CONFIG + 2;
         // large batches: the pipelined kernels (256-query blocks); smaller ones would pad their query columns there
-        c.config = Q <= 128 || (thrift == LEAST && row_bytes < 384) ? generic8 : (row_bytes % 128 == 0 && row_bytes >= 512) ? FP8_QUERY_WIDE_CONFIG
+        const bool few_items = row_bytes < 256 && ceil_div(n, 256) * ceil_div(Q, 256) < SHORT_ROWS_MIN_ITEMS;
+        c.config = Q <= 128 || few_items || (thrift == LEAST && row_bytes < 384) ? generic8 : (row_bytes % 128 == 0 && row_bytes >= 512) ? FP8_QUERY_WIDE_CONFIG
                                   : row_bytes >= 256 ? FP8_QUERY_CONFIG : FP8_QUERY_SHORT_CONFIG;
         if (Q <= 32 && whole_line_rows && stream_keys(h, n, Q, 1)) c.config = FP8_QUERY_STREAM_CONFIG;
         if (is_fp8_query_config((int)h->tune_config)) c.config = (int)h->tune_config;         // another one can be asked for
@@ -2404,8 +2410,8 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
 {
     if (!kb || Q < 1 || k < 1 || k > KB_K_MAX) return 0;
     // Every combination of kernels a query on this handle can run, each bounded over all row counts.  The choice depends on
-    // the kind of query and, through two limits of which a handle's type and batch meet at most one, on the row count
-    // (WIDE128_MIN_ROWS for bf16 rows, stream_keys for fp8 rows): its two sides are those of 1 and of the capacity.
+    // the kind of query and, through limits of which a handle's type and batch meet at most one for every kind, on the row count
+    // (WIDE128_MIN_ROWS for bf16 rows, stream_keys and SHORT_ROWS_MIN_* for fp8 rows): its two sides are those of 1 and of the capacity.
     Sizes m;
     memset(&m, 0, sizeof m);
     bool any = false;

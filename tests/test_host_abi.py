@@ -444,3 +444,19 @@ def test_rows_of_128_bf16_values_stay_with_the_tiled_kernel(L):
                 rests.add(out[2] % 256)
             assert rests == ({0} if tile == 256 else {0, 128})
             L.kb_destroy(h)
+
+
+@pytest.mark.parametrize("d,Q,kind,few,many", [(192, 256, 0, 24134, 34100), (192, 945, 0, 18106, 39161), (128, 256, 2, 27424, 35933), (192, 200, 2, 20000, 35933)])
+def test_short_fp8_rows_in_small_stores_stay_with_the_tiled_kernel(L, d, Q, kind, few, many):
+    # its tiles of 128 rows show in the row counts of the sample
+    for n, tile in ((few, 128), (many, 256)):
+        st, h = _create(L, d=d, dtype=kbmod.KB_FP8_E4M3, cap=n, scale=FAKE)
+        out = (ctypes.c_int64 * 4)()
+        rests = set()
+        for k in range(60, 129):
+            for m in range(n - 1280, n + 1, 128):
+                assert L.kb_query_plan(h, m, Q, k, kind, 1 << 60, out) == 0
+                if out[0] == 0:
+                    rests.add(out[2] % 256)
+        assert rests == ({0} if tile == 256 else {0, 128})
+        L.kb_destroy(h)
