@@ -102,9 +102,13 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 # A small query is bound by the host, so the stream's handle is asked for directly and pointers are plain integers: 4096 x 256
-# rows, 8 queries take the host 9.9 us a call, 12.8 with a Stream object and a c_void_p for each (10.7 us on the GPU).
+# rows, 8 queries take the host 9.9 us a call, 12.8 with a Stream object and a c_void_p for each (10.7 us on the GPU).  The direct way is not part
+# of torch's public interface: without it the Stream object does.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return _raw_stream(torch.cuda.current_device()) if _raw_stream is not None else torch.cuda.current_stream().cuda_stream
 
 
 def quantize_rows(rows: torch.Tensor, want_scale: bool = True):

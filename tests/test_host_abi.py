@@ -1,10 +1,12 @@
 """CPU-only checks of the C ABI: the library loads, exports what include/kb.h declares, and every
 argument error that is decided on the host comes back as the documented status (no device work)."""
 import ctypes
+import importlib.util
 import os
 import re
 
 import pytest
+import torch
 
 from paper_2602_14293_amd import kb as kbmod
 
@@ -37,6 +39,18 @@ def test_every_declared_symbol_is_exported(L):
             "kb_query_probe_workspace_bytes"} <= names
     for n in names:
         assert hasattr(L, n), f"{n} is declared in kb.h but not exported by libkb.so"
+
+
+def test_stream_handle_without_the_direct_way(monkeypatch):
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    fresh = importlib.util.module_from_spec(importlib.util.find_spec(kbmod.__name__))
+    fresh.__spec__.loader.exec_module(fresh)
+    assert fresh._stream() == 0x1234
 
 
 def test_status_strings(L):
