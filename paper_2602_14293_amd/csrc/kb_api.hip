@@ -282,9 +282,11 @@ int64_t sample_tiles_for(const kb *h, const ConfigInfo &sci, int64_t nt, int32_t
     return st;
 }
 
-// Kernels whose main pass leaves the sampled rows out, and those of them whose sample is whole rounds of the compute units.
-bool leaves_sample_out(const Choice &c) { return c.ci.family == 4 && c.sci.family != 3; }
-bool samples_in_rounds(const Choice &c) { return c.ci.family == 4 && c.sci.family == 4; }
+// Kernels whose main pass can leave the sampled rows out (their sample is then whole rounds of the compute units).  Not the weighted
+// selection, whose sample goes in runs of four neighbours: where a query's best rows are some thousand neighbours every run of theirs makes a
+// group to score again (600,000 x 768 rows in runs of 1000 similar ones, 100 queries, k = 100: 394 us a call, 537 with the rows left out, 117 of
+// them in the threshold kernel; rows in no order 451 and 408; 2^20 x 1024 rows, 256 queries, k = 32 738 and 715).
+bool leaves_sample_out(const Choice &c) { return c.ci.family == 4 && c.sci.family == 4; }
 
 int32_t cand_cap_for(int64_t expect, bool sampled)
 {
@@ -349,27 +351,23 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
     // Where the full-line kernel runs the main pass, that pass can leave the sampled rows out: see main_row.  (Not where the sample is
     // whole tiles: the full-line kernel addresses scattered rows in 32 bits, in units of 16 bytes, up to 64 GiB of keys.)  What it
     // takes costs a call 3 to 10 us, a 50th of the main pass at most; what it gives is whole rounds of the compute units.  Time of the
-    // call with the sampled rows scored twice over this one's, 380 random calls of 17,000 to 1,300,000 rows and 33 to 1200 queries:
-    //   no round saved                  0.91 to 1.06    (97,373 x 256 bf16 rows, 256 queries, 381 items or 286: 55.4 us, 59.9)
-    //   one of 27 rounds and more       0.97 to 1.03
-    //   rows of 256 elements            0.96 to 1.02    (321,757 rows, 742 queries, 15 rounds or 13: 218 us, 223; keys of a draw: 0.99 to 1.36)
-    //   else                            0.99 to 1.15
+    // call with the sampled rows scored twice over this one's, 166 random calls of 17,000 to 1,300,000 rows and 33 to 1200 queries:
+    //   no round saved                       0.83 to 0.98    (97,373 x 256 bf16 rows, 256 queries, 381 items or 286: 52.5 us, 59.9)
+    //   one of 25 rounds and more            0.97 to 1.01
+    //   rows of 256 elements (128 queries    0.96 to 1.05    (321,757 rows, 742 queries, 15 rounds or 13: 218 us, 223)
+    //   a block: of 512)
+    //   else                                 0.99 to 1.15
     // And k must be small for the groups, or most of them are scored again (k^3 = 31 groups^2: 85 us, 135).
     // A handle that asks for a configuration gets it with all that belongs to it.
-    const int run_shift = draw ? 2 : 0;
     const int64_t plain_st = sample_tiles_for(h, sci, nts, Q, k, false, true);
-    int64_t st = sample_tiles_for(h, sci, nts, Q, k, samples_in_rounds(c), true);
+    int64_t st = sample_tiles_for(h, sci, nts, Q, k, leaves_sample_out(c), true);
     bool leaves_out = leaves_sample_out(c) && thrift == AMPLE;
     if (leaves_out && !h->tune_config) {
         const int64_t round = (int64_t)DEVICE_CUS * ci.wg_per_cu, rounds = ceil_div(nt * p.nqb, round), groups = st * sci.groups_per_tile;
         const int64_t saved = rounds - ceil_div(ceil_div(n - st * sci.tk, ci.tk) * p.nqb, round);
-        const int64_t per_pair = h->d + (draw ? 256 : 0);       // (a draw's noise takes as long as 256 elements)
-        leaves_out = saved > 0 && 24 * saved >= rounds && per_pair * ci.tq >= 384 * 256 && cubed(k) <= (double)groups * groups;
+        leaves_out = saved > 0 && 24 * saved >= rounds && h->d * ci.tq >= 384 * 256 && cubed(k) <= (double)groups * groups;
     }
-    if (leaves_out) {
-        const int64_t sampled_runs = (st * sci.tk) >> run_shift, runs = n >> run_shift;
-        leaves_out = st > 0 && 2 * sampled_runs < runs && runs >= 3 && !(sci.family == 4 && (uint64_t)n * h->d * key_bytes(h->dtype) >= ((uint64_t)1 << 36));
-    }
+    if (leaves_out) leaves_out = st > 0 && 2 * st * sci.tk < n && (uint64_t)n * h->d * key_bytes(h->dtype) < ((uint64_t)1 << 36);
     if (!leaves_out) st = plain_st;
     p.sample_tk = sci.tk;
     p.sample_tiles = st;
@@ -592,7 +590,7 @@ void bound_sizes(const kb *h, const Choice &c, int32_t Q, int32_t k, bool draw, 
     const int64_t at_cap = ceil_div((int64_t)k * cap_nt * sci.groups_per_tile, MAX_SAMPLE_SLOTS);
     if (at_cap > expect) expect = at_cap;
     z.cand_cap = h->tune_sample_keys > 0 ? MAX_CAND_CAP : cand_cap_for(expect, true);
-    z.sample_slots = (int32_t)(sample_tiles_for(h, sci, cap_nt, Q, k, samples_in_rounds(c), false) * sci.groups_per_tile);
+    z.sample_slots = (int32_t)(sample_tiles_for(h, sci, cap_nt, Q, k, leaves_sample_out(c), false) * sci.groups_per_tile);
     z.more_slots = leaves_sample_out(c) ? z.sample_slots : 0;
     z.region_records = (int64_t)z.regions * REGION_CAP;
     max_into(m, z);
@@ -978,13 +976,14 @@ __device__ inline void touch(const unsigned char *at)
 }
 constexpr int THRESHOLD_AGAIN = 1024;       // groups that are scored again, a query
 
-// KT: type of the keys where the main pass leaves the sampled rows out (never with fp8 queries), -1 otherwise.  The kernel
+// KT: type of the keys where the main pass leaves the sampled rows out (never with fp8 queries or KEYS), -1 otherwise.  The kernel
 // then also lists the sample's own candidates: the best and the second row of a group where they reach the threshold; groups whose
 // bound on the others does too (k^3 / (6 slots^2) of them on a store in no order, one query in a thousand) are scored again
 // with the instruction sequence of the scan, 32 rows a wavefront.
 template <int QT, bool KEYS, int KT, int PER = 2> __global__ __launch_bounds__(1024) void threshold_kernel(ThresholdArgs a)
 {
     constexpr bool ONCE = KT >= 0;
+    static_assert(!(ONCE && KEYS));
     constexpr int SEGS = ONCE ? CAND_SEGMENTS : 1;
     __shared__ uint32_t sh_seg[SEGS], sh_again, sh_lost;
     __shared__ uint16_t sh_group[ONCE ? THRESHOLD_AGAIN : 1];
@@ -1083,15 +1082,11 @@ template <int QT, bool KEYS, int KT, int PER = 2> __global__ __launch_bounds__(1
             const float best = candidate_score(w);
             const uint32_t bits = as_u32(best);
             if (!(as_f32((int32_t)bits < 0 ? bits & ~31u : bits | 31u) >= tp)) return;
-            if (KEYS ? w >= t : best >= tp) append(KEYS ? w : pack_raw_candidate(best, candidate_index(w)));
+            if (best >= tp) append(pack_raw_candidate(best, candidate_index(w)));
             const uint64_t more = a.more[sample_slot_index(i, a.group_shift, a.qpad, q)];
             if (more == 0) return;
             const float second = ordered_to_score((uint32_t)(more >> 32));
-            if (second >= tp) {
-                const uint32_t row = row_of(i, (int)(more & 31u));
-                if (!KEYS) append(pack_raw_candidate(second, row));
-                else if (pack_candidate(second, row) >= t) append(pack_candidate(second, row));
-            }
+            if (second >= tp) append(pack_raw_candidate(second, row_of(i, (int)(more & 31u))));
             if (others_bound(more) != 0u && ordered_to_score(others_bound(more)) >= tp) {
                 const uint32_t n = atomicAdd(&sh_again, 1u);
                 if (n < THRESHOLD_AGAIN) sh_group[n] = (uint16_t)i;
@@ -1123,20 +1118,14 @@ template <int QT, bool KEYS, int KT, int PER = 2> __global__ __launch_bounds__(1
                 const float ik = p.inv_norm[mine];
                 bool ok = lrow < 16 && !row_removed(ik) && known != (uint32_t)mine && second != (uint32_t)mine;
                 if (p.qmask) ok = ok && (p.tags[mine] & qm) != 0;
-                if (KEYS) {
-                    const float key = draw_key_of(final_score(dot, ik, iq), p.draw, p.draw.first_query + (uint32_t)q, mine);
-                    const uint64_t w = pack_candidate(key, (uint32_t)mine);
-                    if (ok && key > -__builtin_inff() && w >= t) append(w);
-                } else if (ok && dot * ik >= tp) {
-                    append(pack_raw_candidate(dot * ik, (uint32_t)mine));
-                }
+                if (ok && dot * ik >= tp) append(pack_raw_candidate(dot * ik, (uint32_t)mine));
             }
             __syncthreads();
         }
         if (tid < CAND_SEGMENTS) a.cnt[q * CAND_SEGMENTS + tid] = sh_seg[tid] < seg_cap ? sh_seg[tid] : seg_cap;
         // The sample's search does not know infinite products, which only a query of endless length has on finite rows: it goes the
         // exhaustive way, unless its mask lets nothing through.  (A zero query's products are zeros, one with a NaN has nothing to list.)
-        const bool unknown = !KEYS && sh_endless && (!a.qmask || mask_word != 0);       // (thread 0 holds the mask word)
+        const bool unknown = sh_endless && (!a.qmask || mask_word != 0);       // (thread 0 holds the mask word)
         if (tid == 0 && (sh_lost != 0 || again > THRESHOLD_AGAIN || unknown)) a.flag[q] = 1u;
     }
 }
@@ -2031,9 +2020,9 @@ template <int KT> hipError_t launch_probe_scan(const dim3 &grid, const FinalArgs
     hipLaunchKernelGGL(probe_scan_kernel<KT>, grid, dim3(PROBE_THREADS), probe_scan_lds<KT>(), s, f, cluster_offsets_dev, n_clusters, probe_dev, nprobe, splits, lists);
     return hipGetLastError();
 }
-template <int QT, bool KEYS, int KT> auto threshold_once(int slots) -> void (*)(ThresholdArgs)
+template <int KT> auto threshold_once(int slots) -> void (*)(ThresholdArgs)
 {
-    return slots <= 2048 ? &threshold_kernel<QT, KEYS, KT, 2> : &threshold_kernel<QT, KEYS, KT, 8>;
+    return slots <= 2048 ? &threshold_kernel<KB_BF16, false, KT, 2> : &threshold_kernel<KB_BF16, false, KT, 8>;
 }
 template <int KT> auto whole_select(int groups) -> void (*)(WholeSelectArgs)
 {
@@ -2632,7 +2621,7 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         a.sample_runs = 1;
         a.skip_mul = 0;
         a.skip_inv = 0.0;
-        a.mixed_runs = 0;
+        a.mixed_rows = 0;
         a.samp_more = nullptr;
         if (p.sample_tiles > 0) {
             // the sample is spread evenly over the knowledge base: a prefix says nothing about later rows when
@@ -2644,11 +2633,10 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
             a.row_run_shift = draw ? 2 : 0;
             a.sample_runs = kb->n >> a.row_run_shift;
             if (p.once) {
-                const int64_t sampled = p.sample_keys >> a.row_run_shift, left = a.sample_runs - sampled;
-                a.sample_runs = sampled;
-                a.skip_mul = (uint32_t)ceil_div(sampled << 32, left);
+                a.sample_runs = p.sample_keys;
+                a.skip_mul = (uint32_t)ceil_div(p.sample_keys << 32, p.main_rows);
                 a.skip_inv = 4294967296.0 / (double)a.skip_mul;
-                a.mixed_runs = (uint32_t)(sampled + left) & ~255u;
+                a.mixed_rows = (uint32_t)kb->n & ~255u;
                 a.samp_more = reinterpret_cast<uint64_t *>(ws + p.off_samp_more);
             }
             a.row_mul = scatter_multiplier(a.sample_runs);
@@ -2688,9 +2676,9 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
             t.cand_cap = p.cand_cap;
             t.tile_rows = p.sample_tk;
             t.scan = a;
-            static LdsAllowed thr_allowed[12];
-            const int thr_kind = !p.once ? (draw ? 3 : (int)q_dtype) : (draw ? 4 : kb->dtype == KB_BF16 ? 5 : 6) + (p.sample_slots > 2048 ? 3 : 0);
-            void (*thr_fn)(ThresholdArgs) = p.once ? (draw ? threshold_once<KB_F32, true, KB_BF16>(p.sample_slots) : kb->dtype == KB_BF16 ? threshold_once<KB_BF16, false, KB_BF16>(p.sample_slots) : threshold_once<KB_BF16, false, KB_FP8_E4M3>(p.sample_slots))
+            static LdsAllowed thr_allowed[8];
+            const int thr_kind = p.once ? (kb->dtype == KB_BF16 ? 4 : 5) + (p.sample_slots > 2048 ? 2 : 0) : draw ? 3 : (int)q_dtype;
+            void (*thr_fn)(ThresholdArgs) = p.once ? (kb->dtype == KB_BF16 ? threshold_once<KB_BF16>(p.sample_slots) : threshold_once<KB_FP8_E4M3>(p.sample_slots))
                                           : draw ? &threshold_kernel<KB_F32, true, -1>
                                           : q_dtype == KB_F32 ? &threshold_kernel<KB_F32, false, -1>
                                           : q_dtype == KB_BF16 ? &threshold_kernel<KB_BF16, false, -1> : &threshold_kernel<KB_FP8_E4M3, false, -1>;

@@ -762,7 +762,6 @@ __device__ inline int noise_floor(float xmax, float tp)
 // test is one integer compare on the generator's output.  What passes (the elements whose key can reach the
 // threshold, and as many again) is handled like the survivors of the score pass, each lane walking its own
 // elements, with the exact key and the exact tests.
-template <bool MAPPED>
 __device__ inline void main_block_draw(const f32x16 &a, const EpiRows &rw, float tp, int ql, const EpiSide &sd, bool filter,
                                        int64_t row0, int q0, const ScanArgs &p, Record *region, uint32_t &wave_cnt, uint32_t region_id)
 {
@@ -784,8 +783,7 @@ __device__ inline void main_block_draw(const f32x16 &a, const EpiRows &rw, float
 #pragma unroll
     for (int run = 0; run < 4; ++run) {
         uint32_t w[4];
-        const uint32_t four = (uint32_t)((row0 + rw.rl0 + 8 * run) >> 2);
-        philox4x32_10(MAPPED ? main_run(p, four) : four, query, dr.seed_lo, dr.seed_hi, w);
+        philox4x32_10((uint32_t)((row0 + rw.rl0 + 8 * run) >> 2), query, dr.seed_lo, dr.seed_hi, w);
 #pragma unroll
         for (int e = 0; e < 4; ++e) pass = (pass << 1) | (w[e] > floor_w ? 1u : 0u);       // element i at bit 15 - i
     }
@@ -799,12 +797,11 @@ __device__ inline void main_block_draw(const f32x16 &a, const EpiRows &rw, float
         pass &= ~(1u << b);
         const int i = 15 - b;
         const int rl = rw.rl0 + 8 * (i >> 2) + (i & 3);
-        const int64_t place = row0 + rl;
-        const uint32_t row = MAPPED ? main_row(p, (uint32_t)place) : (uint32_t)place;
+        const int64_t row = row0 + rl;
         const float ik = sd.invk[rl];
         const float kv = draw_key_of(final_score(select16(a, i), ik, iq), sd.lgain[rl], dr, query, row);
-        const uint64_t cw = pack_candidate(kv, row);
-        bool ok = has && place < p.n_keys && kv > -__builtin_inff() && cw >= t64 && !row_removed(ik);
+        const uint64_t cw = pack_candidate(kv, (uint32_t)row);
+        bool ok = has && row < p.n_keys && kv > -__builtin_inff() && cw >= t64 && !row_removed(ik);
         if (filter) ok = ok && (sd.tag[rl] & qm) != 0;
         const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
         if (okm != 0 && wave_cnt + 64 > (uint32_t)p.region_cap) flush_records(p, region, wave_cnt, region_id);
@@ -820,7 +817,7 @@ __device__ inline void main_block_draw(const f32x16 &a, const EpiRows &rw, float
     } while (__builtin_amdgcn_ballot_w64(pass != 0) != 0);
 }
 
-template <int IB, int JB, bool MAPPED = false>
+template <int IB, int JB>
 __device__ inline void main_epilogue_draw(const f32x16 (&acc)[IB][JB], const EpiSide &sd, bool filter, int wave_row0, int ql0,
                                           int half, int64_t row0, int q0, const ScanArgs &p, Record *region, uint32_t &wave_cnt, uint32_t region_id)
 {
@@ -834,7 +831,7 @@ __device__ inline void main_epilogue_draw(const f32x16 (&acc)[IB][JB], const Epi
                 asm volatile("" : "+v"(rl0));
                 rw = load_rows(sd, rl0);
             }
-            main_block_draw<MAPPED>(acc[ib][jb], rw, sd.thrp[ql0 + jb * 32], ql0 + jb * 32, sd, filter, row0, q0, p, region, wave_cnt, region_id);
+            main_block_draw(acc[ib][jb], rw, sd.thrp[ql0 + jb * 32], ql0 + jb * 32, sd, filter, row0, q0, p, region, wave_cnt, region_id);
         }
     }
 }
@@ -881,8 +878,8 @@ __device__ inline void sample_column_draw(const f32x16 (&acc)[IB][JB], const Epi
     const float iq = sd.invq[ql];
     const uint64_t qm = filter ? sd.qmask[ql] : 0ull;
     const uint32_t query = p.draw.first_query + (uint32_t)(q0 + ql);
-    float best = -__builtin_inff(), second = -__builtin_inff(), third = -__builtin_inff();
-    int best_e = 0, second_e = 0;
+    float best = -__builtin_inff();
+    int best_e = 0;
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib) {
         // (the row number is opaque per block: otherwise the side data and the scattered-row arithmetic of all the
@@ -892,7 +889,7 @@ __device__ inline void sample_column_draw(const f32x16 (&acc)[IB][JB], const Epi
 #pragma unroll
         for (int run = 0; run < 4; ++run) {         // (four rows at a time, one generator call: few registers)
             int rl = rl0 + 8 * run;
-            asm volatile("" : "+v"(rl), "+v"(best), "+v"(second), "+v"(third), "+v"(best_e), "+v"(second_e));
+            asm volatile("" : "+v"(rl), "+v"(best), "+v"(best_e));
             const f32x4 ik4 = *reinterpret_cast<const f32x4 *>(sd.invk + rl), lg4 = *reinterpret_cast<const f32x4 *>(sd.lgain + rl);
             const float ik[4] = {ik4.x, ik4.y, ik4.z, ik4.w}, lg[4] = {lg4.x, lg4.y, lg4.z, lg4.w};
             uint32_t w[4];
@@ -903,11 +900,7 @@ __device__ inline void sample_column_draw(const f32x16 (&acc)[IB][JB], const Epi
                 if (filter) ok = ok && (sd.tag[rl + e] & qm) != 0;
                 const float key = draw_key(final_score(acc[ib][JBX][4 * run + e], ik[e], iq), lg[e], gumbel_of_word(w[e]), p.draw.inv_t);
                 const float f = ok ? key : -__builtin_inff();
-                const int el = ib * 16 + 4 * run + e;
-                third = __builtin_amdgcn_fmed3f(second, third, f);
-                second_e = f > best ? best_e : f > second ? el : second_e;
-                second = __builtin_amdgcn_fmed3f(best, second, f);
-                best_e = f > best ? el : best_e;
+                best_e = f > best ? ib * 16 + 4 * run + e : best_e;
                 best = __builtin_fmaxf(best, f);
             }
         }
@@ -915,7 +908,6 @@ __device__ inline void sample_column_draw(const f32x16 (&acc)[IB][JB], const Epi
     if (q0 + ql < p.Q) {
         const size_t at = sample_slot_index(slot, p.sample_group_shift, p.qpad, q0 + ql);
         p.samp[at] = best > -__builtin_inff() ? pack_candidate(best, sd.row[wave_row0 + (best_e >> 4) * 32 + 4 * half + 8 * (best_e >> 2 & 3) + (best_e & 3)]) : 0ull;
-        if (p.samp_more) p.samp_more[at] = second > -__builtin_inff() ? pack_second(second, third > -__builtin_inff() ? score_to_ordered(third) : 0u, (uint32_t)second_e) : 0ull;
     }
 }
 

@@ -202,7 +202,7 @@ struct ScanArgs {
     int32_t row_run_shift;
     uint32_t skip_mul;        // the main pass leaves out what the sampling pass scored: see main_row (0: it does not)
     double skip_inv;          // 2^32 / skip_mul
-    uint32_t mixed_runs;      // runs whose order is mixed (see mixed)
+    uint32_t mixed_rows;      // rows whose order is mixed (see mixed)
     int32_t d, Q, nqb, qpad, sample_slots, sample_group_shift, region_cap, cand_cap;
     DrawArgs draw;
     int32_t keys_once;        // the launch reads keys that no cache holds and nobody reads again: see stream_keys
@@ -223,36 +223,26 @@ struct ScanArgs {
 // 16-byte load of gains).  Without row_mul the tile is tile_stride tiles further on and rows past the end repeat
 // the last row.
 //
-// Where the main pass leaves the sample out (skip_mul, see main_row), the scatter goes over the runs that are left out instead of
-// all, and run m of those lies at sampled_run(m).  (SKIP: kernels that sample for such a main pass.)
+// Where the main pass leaves the sample out (skip_mul, see main_row), the scatter goes over the rows that are left out instead of
+// all, and row m of those is sampled_row(m).  (SKIP: kernels that sample for such a main pass, row by row.)
 //
 // The map is linear, so a workgroup maps the first run of its tile once (sample_tile_run: exact 64-bit arithmetic with
 // a quotient estimated in double precision; a 64-bit division would be a software routine of some hundred
 // instructions) and every row of the tile from that (sample_row: the product of a run number below 256 with row_mul
 // has a quotient below 256, which single precision estimates to within one).
-// The division of the store between the two passes: with n_keys >> row_run_shift = U runs, S of them sampled and M = U - S
-// left, the main pass's run m (m <= M, the last one being the rows past the last whole run) is run m + floor(m a / 2^32) of the
-// store with a = skip_mul = ceil(2^32 S / M): the multiple steps over one run whenever the quotient grows, evenly, S times up to M.
+// The division of the store between the two passes: with U rows, S of them sampled and M = U - S left, the main pass's row m (m < M)
+// is row m + floor(m a / 2^32) of the store with a = skip_mul = ceil(2^32 S / M): the multiple steps over one row whenever the quotient
+// grows, evenly, S times up to M.
 // One multiplication a row, and the rows of a tile stay neighbours.  Stores of 2^20 rows would have every sampled row at the same
 // place of each 32 KiB, in a few of the memory's channels (sampling pass 55 us, 46 with 1,000,003 rows), so both passes count the
-// runs in an order in which each block of 16 is turned by the number of the block.
-__device__ inline uint32_t mixed(const ScanArgs &p, uint32_t run) { return run < p.mixed_runs ? run ^ (run >> 4 & 15u) : run; }
-__device__ inline uint32_t main_run(const ScanArgs &p, uint32_t run) { return mixed(p, run + __umulhi(run, p.skip_mul)); }
-__device__ inline uint32_t main_row(const ScanArgs &p, uint32_t row)
-{
-    const int sh = p.row_run_shift;
-    return main_run(p, row >> sh) << sh | (row & ((1u << sh) - 1u));
-}
+// rows in an order in which each block of 16 is turned by the number of the block.
+__device__ inline uint32_t mixed(const ScanArgs &p, uint32_t row) { return row < p.mixed_rows ? row ^ (row >> 4 & 15u) : row; }
+__device__ inline uint32_t main_row(const ScanArgs &p, uint32_t row) { return mixed(p, row + __umulhi(row, p.skip_mul)); }
 // no row from `row` on is below this (nor in the tile that begins there)
-__device__ inline uint32_t main_base(const ScanArgs &p, uint32_t row)
-{
-    const int sh = p.row_run_shift;
-    const uint32_t run = row >> sh, at = run + __umulhi(run, p.skip_mul);
-    return (p.mixed_runs ? at & ~15u : at) << sh;
-}
-// Run j (0 <= j < S) of those stepped over: it follows the first m whose quotient is j + 1.  (The estimate in double precision is
+__device__ inline uint32_t main_base(const ScanArgs &p, uint32_t row) { return (row + __umulhi(row, p.skip_mul)) & ~15u; }
+// Row j (0 <= j < S) of those stepped over: it follows the first m whose quotient is j + 1.  (The estimate in double precision is
 // off by one at most.)
-__device__ inline int64_t sampled_run(const ScanArgs &p, int64_t j)
+__device__ inline int64_t sampled_row(const ScanArgs &p, int64_t j)
 {
     const uint32_t want = (uint32_t)j + 1u;
     const double x = (double)want * p.skip_inv;
@@ -285,7 +275,7 @@ template <bool SKIP> __device__ inline int64_t sample_row(const ScanArgs &p, int
         m -= m >= runs ? runs : 0;
         m += tile_run;
         m -= m >= runs ? runs : 0;
-        if (SKIP && p.skip_mul) m = sampled_run(p, m);
+        if (SKIP) return sampled_row(p, m);
         return (m << sh) + (r & ((1 << sh) - 1));
     }
     const int64_t row = tile * p.tile_stride * tk + r;

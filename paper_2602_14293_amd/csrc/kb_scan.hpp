@@ -252,7 +252,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
             // (opaque in a sampling pass: the tile-independent part of the scattered-row arithmetic would otherwise be kept
             // per lane and load across the items, in registers that end up spilled)
             if constexpr (SAMPLE) asm volatile("" : "+v"(r));
-            if constexpr (SAMPLE) offA[j] = (uint64_t)sample_row<DRAW>(p, tile_run, ld_tile, TK, r) * key_row_bytes + ldA_piece;
+            if constexpr (SAMPLE) offA[j] = (uint64_t)sample_row<false>(p, tile_run, ld_tile, TK, r) * key_row_bytes + ldA_piece;
             else if constexpr (WHOLE) {
                 const int64_t row = whole_row(ld_tile, (int32_t)p.n_tiles, TK, r);
                 offA[j] = (uint64_t)(row < p.n_keys ? row : p.n_keys - 1) * key_row_bytes + (SAME_SWZ_A ? ldA_piece : (uint32_t)((((wave * 64 + lane) % C::PPRA) ^ swizzle<C::PPRA>(r)) * 16));
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 if constexpr (SAMPLE) {
                     int rl = tid;
                     asm volatile("" : "+v"(rl));
-                    r = sample_row<DRAW>(p, sample_tile_run(p, tile, TK), tile, TK, rl);
+                    r = sample_row<false>(p, sample_tile_run(p, tile, TK), tile, TK, rl);
                     my_row = (uint32_t)r;
                 }
                 if constexpr (WHOLE) {

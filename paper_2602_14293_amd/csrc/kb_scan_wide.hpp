@@ -356,7 +356,7 @@ __global__ __launch_bounds__(512, 1) void kb_scan_wide_kernel(ScanArgs p)
                     sample_epilogue<IB, JB, false>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, slot,
                                                    [&](int rl) { return sample_index<false>(p, tile_run, row0, TK, rl); });
             } else if constexpr (DRAW)
-                main_epilogue_draw<IB, JB, APART>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
+                main_epilogue_draw<IB, JB>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
             else
                 main_epilogue<IB, JB, C::KEY_BYTES == 1, APART>(acc[rh], sd, filter, rh * 128 + wm * 64, qrow, half, row0, qb * TQ, p, my_region, wave_cnt, blockIdx.x * NW + wave);
         }
@@ -710,7 +710,7 @@ template <class C, bool SAMPLE, bool DRAW, bool APART> hipError_t launch_scan_wi
 }
 template <class C, bool SAMPLE, bool DRAW> hipError_t launch_scan_wide_policy(int grid, const ScanArgs &a, hipStream_t s)
 {
-    if constexpr (C::MAY_PART) {
+    if constexpr (C::MAY_PART && !DRAW) {
         if (SAMPLE ? a.samp_more != nullptr : a.skip_mul != 0) return launch_scan_wide_parted<C, SAMPLE, DRAW, true>(grid, a, s);
     }
     return launch_scan_wide_parted<C, SAMPLE, DRAW, false>(grid, a, s);

@@ -378,9 +378,9 @@ def test_batches_past_256_query_blocks_still_sample(L, n, d, k):
         L.kb_destroy(h)
 
 
-# which main scans leave the sampled rows out: the full-line kernels on bf16 queries
+# which main scans leave the sampled rows out: the full-line kernels on bf16 queries, but for the weighted selection
 @pytest.mark.parametrize("dtype,d,n,Q,kind,leaves", [
-    (kbmod.KB_BF16, 1024, 1 << 20, 256, 0, True), (kbmod.KB_BF16, 1024, 1 << 20, 256, 1, True), (kbmod.KB_BF16, 1024, 1 << 20, 100, 0, True),
+    (kbmod.KB_BF16, 1024, 1 << 20, 256, 0, True), (kbmod.KB_BF16, 1024, 1 << 20, 256, 1, False), (kbmod.KB_BF16, 1024, 1 << 20, 100, 0, True),
     (kbmod.KB_FP8_E4M3, 768, 1 << 22, 1024, 0, True), (kbmod.KB_FP8_E4M3, 512, 2500001, 500, 2, False), (kbmod.KB_FP8_E4M3, 320, 1 << 20, 500, 0, False),
     (kbmod.KB_FP8_E4M3, 768, 1 << 22, 1024, 1, False), (kbmod.KB_BF16, 128, 1 << 20, 256, 0, False), (kbmod.KB_BF16, 1024, 1 << 20, 20, 0, False),
     (kbmod.KB_F32, 256, 1 << 20, 256, 0, False)])
@@ -395,11 +395,11 @@ def test_the_plan_tells_the_rows_of_the_main_scan(L, dtype, d, n, Q, kind, leave
 # the sampled rows are left out where that saves the compute units a round, of at most 24, with enough work for every pair, and where k is
 # small for the groups of the sample
 @pytest.mark.parametrize("dtype,d,n,Q,k,kind,leaves", [
-    (kbmod.KB_BF16, 1024, 1 << 20, 256, 32, 0, True), (kbmod.KB_BF16, 512, 194927, 509, 70, 0, True), (kbmod.KB_BF16, 256, 25059, 635, 22, 1, True),
+    (kbmod.KB_BF16, 1024, 1 << 20, 256, 32, 0, True), (kbmod.KB_BF16, 512, 194927, 509, 70, 0, True),
     (kbmod.KB_BF16, 256, 97373, 256, 20, 0, False), (kbmod.KB_BF16, 1024, 89880, 299, 42, 0, False), (kbmod.KB_BF16, 768, 171198, 256, 77, 0, False),   # no round saved
     (kbmod.KB_BF16, 1024, 19224, 256, 127, 0, False), (kbmod.KB_FP8_E4M3, 512, 20275, 256, 88, 0, False),                                              # k
     (kbmod.KB_BF16, 256, 321757, 742, 57, 0, False), (kbmod.KB_BF16, 256, 852694, 117, 32, 0, False),                                                  # short rows
-    (kbmod.KB_BF16, 512, 756664, 1040, 1, 1, False), (kbmod.KB_BF16, 512, 610988, 836, 3, 0, False)])                                                  # one round of many
+    (kbmod.KB_BF16, 512, 610988, 836, 3, 0, False)])                                                  # one round of many
 def test_sampled_rows_are_left_out_where_that_gains(L, dtype, d, n, Q, k, kind, leaves):
     st, h = _create(L, d=d, dtype=dtype, cap=n, scale=FAKE if dtype == kbmod.KB_FP8_E4M3 else None)
     out = (ctypes.c_int64 * 4)()
