@@ -275,9 +275,9 @@ kb_status_t kb_query_counters(const kb_t *kb, const void *workspace_dev, int64_t
  *   "sample_keys"   keys scored by the sampling pass (0 = automatic)
  *   "scan_config"   tile configuration of the scan kernel (0 = automatic)
  *   "wg_per_cu"     resident scan workgroups per compute unit (0 = automatic)
- *   "small_path"    1 (default): a knowledge base of up to some hundred thousand rows, queried with up to 128 queries and
- *                   no other knob set, is scored whole by two launches (no sampling pass, no candidate lists); 0: always
- *                   the scan pipeline.  Both produce the same bits.
+ *   "small_path"    1 (default): a knowledge base of up to some hundred thousand rows (fewer with more than 128 queries or a
+ *                   large k), queried with no other knob set, is scored whole by two launches, three with the weighted
+ *                   selection (no sampling pass, no candidate lists); 0: always the scan pipeline.  Both produce the same bits.
  *   "profile_stride" of a kb_profile_begin session, every value-th scan launch is timed: launch value/2 of each run of
  *                   `value` launches (0 or 1: every one).  A timed
  *                   launch costs the stream about 12 us of idle time around it; a stride spreads the timed launches

@@ -35,11 +35,12 @@
 // fp8 keys with bf16 queries: a 128-byte key piece meets two query chunks of 64 elements (see the two_chunks lambda); 64-byte
 // pieces of the same rows left the matrix cores idle for want of keys (4,194,304 x 768, 1024 queries: call 6.3 -> 5.9 ms).
 //
-// The main pass goes over the rows that the sampling pass has not scored (main_row; the threshold kernel lists the results among
-// the others).  These kernels are limited by the power of the chip: a sixteenth less work is a sixteenth less time, and the sample is
-// made whole rounds of the compute units, so that both passes fill the chip.  Measured, call with the sampled rows scored
-// twice -> once: 2^20 x 1024 bf16, 256 masked queries, k = 32: 562 -> 538 us; 4,194,304 x 768 fp8, 1024 queries, k = 64: 5.93 ->
-// 5.58 ms; 2^20 x 1024 bf16, 256 draws, k = 32: 738 -> 715 us.  Not with fp8 queries: a sampling workgroup takes one item, which the
+// Where that saves the compute units a round (the plan's rule), the main pass goes over the rows that the sampling pass has not scored
+// (main_row; the threshold kernel lists the results among the others).  These kernels are limited by the power of the chip: a sixteenth
+// less work is a sixteenth less time, and the sample is made whole rounds of the compute units, so that both passes fill the chip.
+// Measured, call with the sampled rows scored twice -> once: 2^20 x 1024 bf16, 256 masked queries, k = 32: 562 -> 538 us; 4,194,304 x
+// 768 fp8, 1024 queries, k = 64: 5.93 -> 5.58 ms.  Not the weighted selection, whose sample goes in runs of neighbours (see
+// leaves_sample_out), and not with fp8 queries: a sampling workgroup takes one item, which the
 // fp8 matrix instruction finishes before the next could be on its way (sampling pass 61 us, the 64-byte-piece kernel 51; call 687 -> 698).
 //
 // Accumulation order over d, lane-to-element mapping and epilogue are those of the other scan kernels, so the
