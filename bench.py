@@ -35,7 +35,7 @@ DRAW_OPS_PER_PAIR = 36
 # kernel choice and the kernel sources it was taken on: `sources` is scan_sources_digest() at that time, and the
 # figure is reported as null once any of those files has changed.
 SCAN_TRAFFIC = {
-    "filtered": {"fetch_kib": 997918, "fetch_scale": 2.0, "write_kib": 8337, "write_scale": 1.0, "sources": "8694b163d14bb872"},
+    "filtered": {"fetch_kib": 997894, "fetch_scale": 2.0, "write_kib": 8091, "write_scale": 1.0, "sources": "e8bce20ca2fa067c"},
 }
 SCAN_SOURCES = ["kb_scan_wide.hpp", "kb_scan.hpp", "kb_scan_sp.hpp", "kb_epilogue.hpp", "kb_internal.hpp", "kb_configs.hpp"]
 
@@ -497,7 +497,8 @@ def run_query_workload(args, torch, kbmod, W, dev, name):
     achieved = scan_bytes / (scan_ms * 1e-3) / 1e9
     flops = 2.0 * Q * N * d
     scan_flops = 2.0 * Q * scanned * d
-    whole_store = plan["plan"] != "pipeline"
+    scan_kernel = {"whole": "scoring kernel of the whole-store plan", "dense": "scoring kernel of the dense plan",
+                   "parts": "scoring kernel of a store in parts"}.get(plan["plan"], "scan kernel, main pass")
     result = {
         "metric": "KB top-k queries/sec + key-scan HBM GB/s (% of peak), N=1M d=1024 bf16",
         "value": qps,
@@ -519,7 +520,7 @@ def run_query_workload(args, torch, kbmod, W, dev, name):
         "mfma_TFLOPs": flops / (ms_per_step * 1e-3) / 1e12,
         "counters": counters,
         "launch": "hip graph replay" if args.graph else "eager",
-        "roofline": {"bound": "hbm", "kernel": "scoring kernel of the whole-store plan" if whole_store else "scan kernel, main pass",
+        "roofline": {"bound": "hbm", "kernel": scan_kernel,
                      "achieved": achieved, "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS,
                      "traffic": scan_traffic_bytes(name, bool(args.tune) or args.draw),

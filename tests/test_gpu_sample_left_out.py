@@ -70,6 +70,7 @@ def test_the_parts_add_up_to_every_row(T, dtype, config, tiled, N, d, Q, k, shar
 
 @pytest.mark.parametrize("N,Q,k,temperature", [((1 << 16) + 3, 256, 32, 0.02), (1 << 16, 129, 8, 1.0), (2050, 300, 4, 0.1)])
 def test_draws_add_up_too(T, N, Q, k, temperature):
+    """(The weighted selection scores every row in its main pass: the full-line kernel behind the tiled kernel's sample.)"""
     w = W.clustered(seed=N, N=N, d=256, Q=Q, k=k, centers=32)
     _crowded(w, 3, 0.05, N)
     gain = torch.from_numpy(np.random.default_rng(N).uniform(0.25, 4.0, size=N).astype(np.float32)).cuda()
