@@ -17,6 +17,7 @@
 #include "kb_configs.hpp"
 #include "kb_internal.hpp"
 #include "kb_scan.hpp"
+#include "kb_stream.hpp"
 
 using namespace kbi;
 
@@ -417,6 +418,13 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
 // workgroup.  Measured against the pipeline on stores of 256 and 1024 elements a row, masked and not: up to three tiles
 // for every resident workgroup 1.05 to 1.8 times as fast, with up to 32 queries still 1.0 to 1.3 times at five, with more
 // 0.9 to 1.05 times at four; at ten it loses (0.85 to 1.05).
+// With the queries in LDS (kb_stream.hpp) a tile costs less, and rows dealt one by one leave no group to score again where similar rows are
+// neighbours: up to sixteen tiles a wavefront.  Time of the pipeline over this plan's (runs of 1, 4, 16, 64 and 1000 similar rows, k 4 to 96):
+//   400,000 x 256 bf16, 8 queries      1.26 to 1.47 (58 us, 44)      400,000 x 1024, 1 query     1.11 to 1.29 (151 us, 135)
+//   700,000 x 512 bf16, 20 queries     1.10 to 1.39 (138 us, 122)    1,000,003 x 1024, 1 query   1.04 to 1.22 (332 us, 317)
+//   1,000,003 x 256 bf16, 32 queries   1.11 to 1.38 (108 us, 95)     900,000 x 512 fp8, 8        1.10 to 1.35 (100 us, 90)
+//   700,000 x 320 fp8 x 8, 20 queries  1.21 to 1.86 (60 us, 49)
+constexpr int64_t WHOLE_MAX_ROWS_STREAM = (1 << 20) - 1;
 constexpr int64_t WHOLE_MAX_ROWS_FEW = 5 * 128 * 2 * DEVICE_CUS, WHOLE_MAX_ROWS = 3 * 128 * 2 * DEVICE_CUS;     // up to 32 queries; up to 128
 // More than 128 queries: every product costs the epilogue the same, while the pipeline's scan gets better with larger query
 // blocks and pays 30 us of latencies once.  Time of the pipeline over this plan's, k = 16, rows of 256 | 768 elements:
@@ -435,7 +443,7 @@ constexpr int WHOLE_MAX_QUERIES = 4096;
 // (fp8 rows with bf16 queries 1.10 and more at 2^25 products of up to 16,384 elements, f32 1.03 and more)
 int64_t whole_max_rows(const kb *h, int32_t Q, bool q8)
 {
-    if (Q <= 32) return WHOLE_MAX_ROWS_FEW;
+    if (Q <= 32) return h->dtype == KB_F32 ? WHOLE_MAX_ROWS_FEW : WHOLE_MAX_ROWS_STREAM;
     if (Q <= 128) return WHOLE_MAX_ROWS;
     const int64_t columns = h->dtype == KB_BF16 ? ceil_div(Q, 128) * 128 : Q;
     int64_t pairs = (int64_t)1 << (h->dtype == KB_BF16 ? 24 : h->dtype == KB_F32 ? 26 : 25);
@@ -443,11 +451,60 @@ int64_t whole_max_rows(const kb *h, int32_t Q, bool q8)
     return std::min(WHOLE_MAX_ROWS, pairs / columns);
 }
 constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
+// The scan with the queries in LDS (kb_stream.hpp), where they fit beside the rings of four wavefronts and up.
+// `most_groups`: no more groups than that.
+bool make_stream_plan(const kb *h, int64_t n, int32_t Q, bool q8, bool dense, int64_t most_groups, StreamPlan *out)
+{
+    if (h->dtype == KB_F32 || (!dense && Q > 32)) return false;
+    StreamPlan p;
+    const int64_t row_bytes = (int64_t)h->d * key_bytes(h->dtype), pieces = ceil_div(row_bytes, 128);
+    const int64_t query_bytes = row_bytes * (h->dtype == KB_FP8_E4M3 && !q8 ? 2 : 1);
+    const int64_t stride = ceil_div(query_bytes, 256) * 256, resident = std::min<int64_t>(Q, 32) * stride;
+    p.nqb = (int32_t)ceil_div(Q, 32);
+    p.blocks = DEVICE_CUS / p.nqb < 1 ? 1 : DEVICE_CUS / p.nqb;
+    p.tr = dense ? 16 : 32;
+    p.units = (int32_t)ceil_div(n, p.tr);
+    if (p.blocks > p.units) p.blocks = p.units;
+    p.pieces_in_ring = p.tr == 16 ? STREAM_RING_16 : STREAM_RING_32;
+    p.side_slots = (int32_t)(1 + ceil_div(p.pieces_in_ring, pieces));       // (a piece is asked for that many before its turn)
+    for (p.waves_per_block = 8;; --p.waves_per_block) {
+        if (p.waves_per_block < 4) return false;
+        const int64_t lds = resident + (int64_t)p.waves_per_block * (p.pieces_in_ring * p.tr * 128 + p.side_slots * p.tr * 12) + 256;
+        p.lds = (int32_t)lds;
+        if (lds <= STREAM_LDS) break;
+    }
+    p.query_stride = (int32_t)stride;
+    // rows one by one or in runs of four (the store's neighbours then share fewer of a wavefront's 128-byte pieces, at most a group of them
+    // has to be scored again for each run of similar rows): in us, one by one | in runs of four, 700,000 x 128 bf16 rows 53.3 | 48.0 (start of
+    // a group's rescoring 65 to 107), 200,000 x 256 32.0 | 31.1, 60,000 x 768 25.5 | 25.0, 300,000 x 768 84.8 | 84.3, 16,000 x 512 equal.  Stores past
+    // WHOLE_MAX_ROWS_FEW, whose groups are up to 256 rows, take them one by one: 400,000 x 1024 rows in runs of 16, k = 24 251 us in runs of four, 135.
+    p.run_shift = n > WHOLE_MAX_ROWS_FEW || n <= WHOLE_SMALL_TILE_ROWS ? 0 : 2;
+    p.waves = (int32_t)std::min<int64_t>({p.units, (int64_t)p.blocks * p.waves_per_block, most_groups});
+    const int64_t layers = ceil_div(p.units, p.waves), room = dense ? layers : std::max<int64_t>(1, most_groups / p.waves);
+    p.per_group = (int32_t)ceil_div(layers, room);
+    if (!dense && p.per_group * p.tr > 256) return false;
+    *out = p;
+    return true;
+}
+int stream_groups(const StreamPlan &p)
+{
+    const int64_t layers = ceil_div(p.units, p.waves), full = (layers - 1) / p.per_group;       // groups of a wavefront but for the last
+    return (int)(full * p.waves + std::min<int64_t>(p.waves, p.units - full * p.per_group * p.waves));
+}
+
+constexpr size_t WHOLE_OFF_BEST = (sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS) + WS_ALIGN - 1) / WS_ALIGN * WS_ALIGN;       // the diagnostics come first, as always
+size_t whole_bytes(int32_t Q, int32_t groups, size_t *off_pair)
+{
+    *off_pair = WHOLE_OFF_BEST + align_up(sizeof(float) * (size_t)Q * groups);
+    return *off_pair + align_up(sizeof(u32x4) * (size_t)Q * groups);
+}
 bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, Thrift thrift, WholePlan *out)
 {
     if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
     if (n < 1 || Q > WHOLE_MAX_QUERIES || n > whole_max_rows(h, Q, q8) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
     WholePlan p;
+    p.stream = make_stream_plan(h, n, Q, q8, false, thrift == LEAST ? ceil_div(n, 128) : WHOLE_MAX_GROUPS, &p.st);
+    if (!p.stream && Q <= 32 && n > WHOLE_MAX_ROWS_FEW) return false;
     if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
     else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : n >= 128 * 2 * DEVICE_CUS && h->d >= 512 ? 21 : 16;    // (14: once every resident workgroup gets a tile)
     else if (h->dtype == KB_F32 && Q > 32 && thrift != LEAST) p.config = Q <= 64 || ceil_div(n, 128) * ceil_div(Q, 128) <= DEVICE_CUS ? F32_SQUARE_CONFIG : 2;
@@ -469,6 +526,16 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     p.group_rows = p.fine ? fine_rows : ci.tk;
     static_assert(WHOLE_MAX_ROWS_FEW / 128 <= WHOLE_MAX_GROUPS && WHOLE_MAX_ROWS / 64 <= WHOLE_MAX_GROUPS, "whole tiles: 128 rows, or 64 with more than 32 queries");
     p.groups = (int32_t)(tiles * (ci.tk / p.group_rows));
+    p.k_groups = p.groups;
+    if (p.stream) {
+        p.tk = p.st.tr;
+        p.tq = 32;
+        p.nqb = 1;
+        p.fine = 0;
+        p.group_rows = p.st.per_group * p.st.tr;
+        p.groups = stream_groups(p.st);
+        p.k_groups = (int32_t)std::min<int64_t>(p.groups, ceil_div(n, p.st.per_group > 1 ? 128 : q8 ? 64 : 32));
+    }
     // Groups with three of a query's k best are scored again, k^3 / 6 / groups^2 of them if rows come in no order, up to k / 2 where
     // similar rows are neighbours.  That costs a call one step of the selecting workgroups or several, each as long as a row's loads.
     // Time of the pipeline over this plan's at k^3 / groups^2 of 0.12 to 4, stores of 5000 to 131,072 rows in runs of 4 to 64
@@ -485,13 +552,12 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     // k = 16 1.06 | 0.80 | 0.69 (256 elements 1.28 | 1.00 | 0.91), 24 1.07 | 0.71 | 0.64, 40 1.08 | 0.59 | 0.53, 80 1.16 | 0.46 | 0.40
     if (p.config == F32_SQUARE_CONFIG && !p.fine && k > 16) return false;
     const size_t row_bytes = (size_t)h->d * key_bytes(h->dtype);
-    const bool cheap = p.group_rows <= 32 && row_bytes <= (Q > 32 ? 512 : h->dtype == KB_F32 ? 1024 : 1536);
-    if (cubed(k) > (cheap ? 4.0 : 0.12) * (double)p.groups * p.groups) return false;
+    const bool cheap = p.group_rows <= 32 && !(p.stream && q8) && row_bytes <= (Q > 32 ? 512 : h->dtype == KB_F32 ? 1024 : 1536);
+    if (cubed(k) > (cheap ? 4.0 : 0.12) * (double)p.k_groups * p.k_groups) return false;
     const int64_t items = tiles * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
-    p.grid = (int32_t)(items < most ? items : most);
-    p.off_best = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));       // the diagnostics come first, as always
-    p.off_pair = p.off_best + align_up(sizeof(float) * (size_t)Q * p.groups);
-    p.total = p.off_pair + align_up(sizeof(u32x4) * (size_t)Q * p.groups);
+    p.grid = p.stream ? p.st.blocks : (int32_t)(items < most ? items : most);
+    p.off_best = WHOLE_OFF_BEST;
+    p.total = whole_bytes(Q, p.groups, &p.off_pair);
     *out = p;
     return true;
 }
@@ -505,7 +571,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
 // it is level with the pipeline.
 constexpr int64_t DENSE_MAX_PAIRS = (int64_t)1 << 23;
 constexpr int64_t DENSE_FIRST_ROWS = 4096;                 // up to here the dense plan is never the slower one
-bool dense_is_better(int64_t n, int32_t k, const WholePlan &w) { return n <= DENSE_FIRST_ROWS || cubed(k) > 0.5 * (double)w.groups * w.groups; }
+bool dense_is_better(int64_t n, int32_t k, const WholePlan &w) { return n <= DENSE_FIRST_ROWS || cubed(k) > 0.5 * (double)w.k_groups * w.k_groups; }
 bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, DensePlan *out)
 {
     if (h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
@@ -526,6 +592,8 @@ bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     p.nqb = (int32_t)ceil_div(Q, p.tq);
     const int64_t items = ceil_div(n, ci.tk) * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
     p.grid = (int32_t)(items < most || p.config == SMALL_F32_CONFIG ? items : most);
+    p.stream = small && !draw && make_stream_plan(h, n, Q, q8, true, WHOLE_MAX_GROUPS, &p.st);
+    if (p.stream) p.grid = p.st.blocks * p.st.nqb;
     p.stride = (int32_t)(ceil_div(n, 128) * 128);
     p.off_values = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));       // the diagnostics come first, as always
     p.off_invq = p.off_values + align_up(sizeof(float) * (size_t)Q * p.stride);
@@ -1301,6 +1369,7 @@ struct WholeSelectArgs {
     uint64_t *stats;
     int64_t n_keys;
     int32_t k, d, groups, group_rows, tile_rows, tiles, grid;
+    int32_t waves, per_group, run_shift;        // StreamPlan (tiles: its units), where the scan was kb_stream_kernel
 };
 // 256 threads hold the groups: the kernel's length is a dozen barriers, which more wavefronts only make longer (64 queries
 // x 2048 groups: 7.6 us with 256 threads, 8.2 with 1024)
@@ -1452,7 +1521,7 @@ __device__ __forceinline__ void write_best(uint64_t *buf, uint32_t have, int q, 
 }
 
 // PER: groups a thread holds.  (The kernel is a few microseconds long: instructions that a small store skips are fetched all the same.)
-template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_kernel(WholeSelectArgs a)
+template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_kernel(WholeSelectArgs a)
 {
     static_assert(PER * WHOLE_THREADS <= WHOLE_MAX_GROUPS);
     constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
@@ -1503,9 +1572,12 @@ template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whol
     auto passes = [&](float f) { return bound.passes(f); };
 
     // row at a place of the tile of group g (the groups of a tile follow each other)
-    const uint32_t per_tile = (uint32_t)a.tile_rows / (uint32_t)a.group_rows;
-    auto row_at = [&](uint32_t g, uint32_t place) { return (uint32_t)whole_row((int32_t)(g / per_tile), a.tiles, a.tile_rows, (int)place); };
-    auto first_place = [&](uint32_t g) { return g % per_tile * (uint32_t)a.group_rows; };
+    const uint32_t per_tile = STREAM ? 1u : (uint32_t)a.tile_rows / (uint32_t)a.group_rows;
+    auto row_at = [&](uint32_t g, uint32_t place) {
+        if constexpr (STREAM) return (uint32_t)stream_group_row(a.tile_rows, a.tiles, a.waves, a.per_group, a.run_shift, g, place);
+        else return (uint32_t)whole_row((int32_t)(g / per_tile), a.tiles, a.tile_rows, (int)place);
+    };
+    auto first_place = [&](uint32_t g) { return STREAM ? 0u : g % per_tile * (uint32_t)a.group_rows; };
     auto append = [&](float product, uint32_t row) {
         const float f = product * iq + 0.0f;
         const uint64_t cw = pack_candidate(f, row);
@@ -1535,7 +1607,7 @@ template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whol
             const u32x4 x = pair[g];
             append(best[g], row_at(g, x[2] & 255u));
             append(as_f32(x[0]), row_at(g, x[2] >> 8 & 255u));
-            const uint32_t third = x[2] >> 16 & 255u;
+            const uint32_t third = x[2] >> 16 & WHOLE_THIRD;
             if (third != 0u) append(as_f32(x[1]), row_at(g, third - 1u));
             if (as_f32(x[1]) > NONE && passes(score_bound(as_f32(x[1])))) again[atomicAdd(&sh_again, 1u)] = (uint16_t)g;
         }
@@ -1565,7 +1637,7 @@ template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whol
             const uint32_t g = again[j];
             const u32x4 x = pair[g];
             const float third = as_f32(x[1]), f = score_bound(third);
-            const uint32_t place = x[2] >> 16 & 255u;
+            const uint32_t place = x[2] >> 16 & WHOLE_THIRD;
             uint64_t most = pack_candidate(f, row_at(g, first_place(g)));       // (the group's lowest row)
             if (place != 0u) {          // known: the others' scores are lower, or equal at higher rows unless the rounding hides a difference
                 const float below = ordered_to_score(score_to_ordered(third + 0.0f) - ((x[2] & WHOLE_NEAR) != 0u ? 1u : 3u));
@@ -1590,7 +1662,7 @@ template <int KT, int PER> __global__ __launch_bounds__(WHOLE_THREADS) void whol
             const float dot = select16(acc, lrow & 15);
             const uint32_t rel = 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3), place = place0 + rel;
             const int64_t row = row_at(g, place);
-            const bool listed_before = place == (known & 255u) || place == (known >> 8 & 255u) || place + 1u == (known >> 16 & 255u);
+            const bool listed_before = place == (known & 255u) || place == (known >> 8 & 255u) || place + 1u == (known >> 16 & WHOLE_THIRD);
             if (lrow < 16 && in_group + rel < (uint32_t)a.group_rows && row < a.n_keys && !listed_before) {
                 const float ik = a.inv_norm[row];
                 if (!row_removed(ik) && (!a.qmask || (a.tags[row] & qm) != 0)) append(dot * ik, (uint32_t)row);
@@ -2024,9 +2096,14 @@ template <int KT> auto threshold_once(int slots) -> void (*)(ThresholdArgs)
 {
     return slots <= 2048 ? &threshold_kernel<KB_BF16, false, KT, 2> : &threshold_kernel<KB_BF16, false, KT, 8>;
 }
-template <int KT> auto whole_select(int groups) -> void (*)(WholeSelectArgs)
+template <int KT, bool STREAM> auto whole_select(int groups) -> void (*)(WholeSelectArgs)
 {
-    return groups <= 4 * WHOLE_THREADS ? &whole_select_kernel<KT, 4> : groups <= 8 * WHOLE_THREADS ? &whole_select_kernel<KT, 8> : &whole_select_kernel<KT, 16>;
+    return groups <= 4 * WHOLE_THREADS ? &whole_select_kernel<KT, 4, STREAM> : groups <= 8 * WHOLE_THREADS ? &whole_select_kernel<KT, 8, STREAM> : &whole_select_kernel<KT, 16, STREAM>;
+}
+template <bool STREAM> auto whole_select_for(int kt, int groups) -> void (*)(WholeSelectArgs)
+{
+    return kt == KB_F32 ? whole_select<KB_F32, STREAM>(groups) : kt == KB_BF16 ? whole_select<KB_BF16, STREAM>(groups)
+         : kt == KB_FP8_E4M3 ? whole_select<KB_FP8_E4M3, STREAM>(groups) : whole_select<KT_FP8_Q8, STREAM>(groups);
 }
 template <int QT, bool KEYS> void launch_dense_select(const DenseSelectArgs &t, int32_t Q, hipStream_t s)
 {
@@ -2272,6 +2349,31 @@ void launch_prep(const void *queries_dev, kb_dtype_t q_dtype, int32_t Q, int32_t
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(256), 0, s, queries_dev, Q, qpad, d, invq, thr64, thrp, cnt, flag, stats, sample_keys, qmask_dev, qmask_pad, grid, fb_done, ga);
 }
 
+hipError_t launch_stream_scan(const kb *h, const StreamPlan &p, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, float *best, u32x4 *pair, int32_t groups,
+                              bool dense, bool once, hipStream_t s)
+{
+    StreamArgs a;
+    a.keys = h->keys;
+    a.queries = queries_dev;
+    a.inv_norm = h->inv_norm;
+    a.tags = qmask_dev ? h->tags : nullptr;
+    a.qmask = qmask_dev;
+    a.best = best;
+    a.pair = pair;
+    a.n = (int32_t)h->n;
+    a.d = h->d;
+    a.Q = Q;
+    a.units = p.units;
+    a.waves = p.waves;
+    a.per_group = p.per_group;
+    a.groups = groups;
+    a.query_stride = p.query_stride;
+    a.side_slots = p.side_slots;
+    a.blocks = p.blocks;
+    a.run_shift = p.run_shift;
+    return h->dtype == KB_BF16 ? launch_stream_bf16(p, dense, once, a, s) : launch_stream_fp8(p, q8, dense, once, a, s);
+}
+
 // kb_query by the whole-store plan: two launches.
 kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k,
                          int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
@@ -2300,12 +2402,16 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
         scan_timing.start = h->prof_events[2 * h->prof_used];
         scan_timing.stop = h->prof_events[2 * h->prof_used + 1];
     }
-    const hipError_t launched = launch_scan(h->dtype, p.config, 0, false, p.grid, a, s);
+    const hipError_t launched = p.stream ? launch_stream_scan(h, p.st, queries_dev, q8, Q, qmask_dev, a.whole_best, a.whole_pair, p.groups, false, a.keys_once != 0, s)
+                                         : launch_scan(h->dtype, p.config, 0, false, p.grid, a, s);
     scan_timing = ScanTiming();
     if (launched != hipSuccess) return KB_ERR_DEVICE;
     if (timed) ++h->prof_used;
 
     WholeSelectArgs t;
+    t.waves = p.stream ? p.st.waves : 0;
+    t.per_group = p.stream ? p.st.per_group : 1;
+    t.run_shift = p.stream ? p.st.run_shift : 0;
     t.keys = a.keys;
     t.queries = queries_dev;
     t.inv_norm = a.inv_norm;
@@ -2322,11 +2428,10 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     t.groups = p.groups;
     t.group_rows = p.group_rows;
     t.tile_rows = p.tk;
-    t.tiles = (int32_t)a.n_tiles;
+    t.tiles = p.stream ? p.st.units : (int32_t)a.n_tiles;
     t.grid = p.grid;
     const int kt = q8 ? KT_FP8_Q8 : (int)h->dtype;
-    auto *fn = kt == KB_F32 ? whole_select<KB_F32>(p.groups) : kt == KB_BF16 ? whole_select<KB_BF16>(p.groups)
-             : kt == KB_FP8_E4M3 ? whole_select<KB_FP8_E4M3>(p.groups) : whole_select<KT_FP8_Q8>(p.groups);
+    auto *fn = p.stream ? whole_select_for<true>(kt, p.groups) : whole_select_for<false>(kt, p.groups);
     hipLaunchKernelGGL(fn, dim3(Q), dim3(WHOLE_THREADS), 0, s, t);
     return hipGetLastError() == hipSuccess ? KB_OK : KB_ERR_DEVICE;
 }
@@ -2370,7 +2475,8 @@ kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_
         scan_timing.start = h->prof_events[2 * h->prof_used];
         scan_timing.stop = h->prof_events[2 * h->prof_used + 1];
     }
-    const hipError_t launched = launch_scan(h->dtype, p.config, 0, false, p.grid, a, s);
+    const hipError_t launched = p.stream ? launch_stream_scan(h, p.st, queries_dev, q_dtype == KB_FP8_E4M3, Q, qmask_dev, a.dense, nullptr, p.stride, true, false, s)
+                                         : launch_scan(h->dtype, p.config, 0, false, p.grid, a, s);
     scan_timing = ScanTiming();
     if (launched != hipSuccess) return KB_ERR_DEVICE;
     if (timed) ++h->prof_used;
@@ -2420,6 +2526,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     const int64_t parts = std::min<int64_t>({PROBE_MAX, SMALL_BLOCKS / Q, ceil_div(kb->capacity, 128)});
     if (parts > 0) total = std::max(total, make_small_plan(Q, k, (int)parts).total);
     // the whole-store plan: grows with its groups, so with the rows up to where the groups get coarser and to the most it takes
+    size_t unused;
     for (int q8 = 0; q8 < 2; ++q8) {
         const int64_t whole_rows = std::min(kb->capacity, whole_max_rows(kb, Q, q8 != 0));
         const int64_t f32_square = DEVICE_CUS / ceil_div(Q, 128) * 128;        // rows up to which f32 batches past 64 queries have the lower tiles
@@ -2428,6 +2535,8 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
             WholePlan wp;
             if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, AMPLE, &wp)) total = std::max(total, wp.total);
         }
+        // (the scan with the queries in LDS: never more groups than these)
+        if (Q <= 32) total = std::max(total, whole_bytes(Q, (int32_t)std::min<int64_t>(WHOLE_MAX_GROUPS, ceil_div(whole_rows, 16)), &unused));
     }
     // the dense plan: grows with the rows
     for (int kind = 0; kind < 4; ++kind) {

@@ -394,6 +394,17 @@ __device__ inline TopThree other_half(const TopThree &t, int lanes)
     o.rows = (uint32_t)__shfl_xor((int)t.rows, lanes, 64);
     return o;
 }
+// ... of the lane 32 places away, without the round trip through LDS that a shuffle is
+__device__ inline uint32_t across(uint32_t x)
+{
+    typedef uint32_t u32x2_ __attribute__((ext_vector_type(2)));
+    const u32x2_ r = __builtin_amdgcn_permlane32_swap(x, x, false, false);        // {lower half twice, upper half twice}
+    return (threadIdx.x & 32) != 0 ? r.x : r.y;
+}
+__device__ inline TopThree across_halves(const TopThree &t)
+{
+    return TopThree{as_f32(across(as_u32(t.first))), as_f32(across(as_u32(t.second))), as_f32(across(as_u32(t.third))), across(t.rows)};
+}
 // Whether, in some lane, what is not named could be as good as the second row (uniform).
 __device__ inline bool unclear(const TopThree &t)
 {
@@ -426,7 +437,7 @@ template <int TK> __device__ inline TopThree join_in_order(TopThree a, TopThree 
     const bool swap = comes_before(b.first, order(b, 0), a.first, order(a, 0));
     const TopThree x = swap ? b : a, y = swap ? a : b;
     const bool keep = comes_before(x.second, order(x, 1), y.first, order(y, 0));
-    const uint32_t x3 = x.rows >> 16 & 255u;
+    const uint32_t x3 = x.rows >> 16 & WHOLE_THIRD;
     const bool bound = keep && x3 == 0u && x.third >= y.first;
     const bool third_x = keep ? bound || (x3 != 0u && comes_before(x.third, whole_order<TK>(x3 - 1u), y.first, order(y, 0)))
                               : comes_before(x.second, order(x, 1), y.second, order(y, 1));

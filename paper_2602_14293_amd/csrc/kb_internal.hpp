@@ -137,18 +137,28 @@ struct Plan {
 // (the rows of a wave, or of a key tile), the two best products and a bound on all others; one workgroup per query finds the
 // k-th best of the groups' best and takes what reaches it, scoring a group again only when a further row of it might.
 // A group's entry is four words: the second best product; the third best one or a bound on it; the places of these rows
-// in the tile, first | second << 8 | (third + 1) << 16, where 0 means that the third is only a bound; 0.  -inf where there is no row.
+// in the tile (or the group, see StreamPlan), first | second << 8 | (third + 1) << 16, where 0 means that the third is only a bound; 0.  -inf where there is no row.
 //
 // What is not named is strictly worse than the second row if the third is a bound.  Where it could not be told from the
 // second (equal rows, most of all), the scan names the third as well, the rows taken in the order of the result: by
 // product, then by index.  So a group is scored again only if two rows of it are better than the k-th result, which is
 // at most k / 2 groups, however many rows are alike.  One thing is left: products a unit or two in the last place apart
 // can round to equal scores, and then the lower index wins.  WHOLE_NEAR says that such a row may be among those not named.
-constexpr uint32_t WHOLE_NEAR = 1u << 24;
+constexpr uint32_t WHOLE_NEAR = 1u << 25;
+constexpr uint32_t WHOLE_THIRD = 511u;      // ... after the shift: the third's place + 1, of up to 256 rows
 constexpr int WHOLE_MAX_GROUPS = 4096;      // a thread of the selecting workgroup (256) keeps 16 of them
+// The scan with the queries in LDS (kb_stream.hpp): tiles of `tr` rows, dealt to `waves` wavefronts; a group is `per_group` tiles of one of them.
+struct StreamPlan {
+    int32_t tr, pieces_in_ring, waves_per_block, blocks, nqb;       // blocks: per query block
+    int32_t units, waves, per_group, run_shift, side_slots, query_stride;
+    int32_t lds;
+};
 struct WholePlan {
+    bool stream;                        // the first launch is kb_stream_kernel; tk is the tile's rows, config says nothing
+    StreamPlan st;
     int32_t config, tk, tq, nqb, grid;
     int32_t groups, group_rows, fine;
+    int32_t k_groups;                   // groups as the rules for k count them
     size_t off_best, off_pair, total;
 };
 
@@ -157,6 +167,8 @@ struct WholePlan {
 constexpr int DENSE_THREADS = 256;
 constexpr int64_t DENSE_MAX_ROWS = 16384;   // a thread of the selecting workgroup keeps 64 of them
 struct DensePlan {
+    bool stream;
+    StreamPlan st;
     int32_t config, tk, tq, nqb, grid, stride;      // stride: values per query, a multiple of the tile's rows and of what a load of the selection takes
     size_t off_values, off_invq, off_lgain, off_unused, total;      // (off_invq on: the weighted selection only)
 };
@@ -305,8 +317,10 @@ __host__ __device__ inline int64_t whole_row(int32_t tile, int32_t tiles, int tk
     return (((int64_t)j * tiles + t) << shift) + (shift ? pos / per : 0);
 }
 // A number below tk that rises with the row at a place.
+constexpr int NATURAL_ORDER = 256;      // groups whose rows rise with the places
 template <int TK> __host__ __device__ inline uint32_t whole_order(uint32_t place)
 {
+    if (TK == NATURAL_ORDER) return place;
     constexpr int SHIFT = whole_run_shift(TK);
     return ((place << SHIFT) | (place / (uint32_t)(TK >> SHIFT))) & (uint32_t)(TK - 1);
 }
@@ -352,6 +366,9 @@ hipError_t launch_scan_sp_bf16(int config, bool sample, int grid, const ScanArgs
 hipError_t launch_scan_wide_bf16(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_wide_fp8(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_sp_fp8(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
+struct StreamArgs;
+hipError_t launch_stream_bf16(const StreamPlan &p, bool dense, bool once, const StreamArgs &a, hipStream_t s);
+hipError_t launch_stream_fp8(const StreamPlan &p, bool q8, bool dense, bool once, const StreamArgs &a, hipStream_t s);
 
 // Shortest key row (bytes) of the kernel with a software pipeline of 64-byte pieces and rings of ns chunks: see SPCfg::AUX_COPIES.
 constexpr int pipelined_min_row_bytes(int ns, bool interleaved) { return 64 * (ns == 3 ? (interleaved ? 2 : 3) : interleaved ? ns : ns + 1); }

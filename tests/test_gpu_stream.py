@@ -1,0 +1,84 @@
+"""The scan that keeps up to 32 queries in LDS (whole-store and dense plan): the same bits as the scan pipeline at the sizes where its
+tiles, layers and groups change, for every type of keys and queries; the plan with few groups that a call with little memory gets."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import kb_testlib as T
+from paper_2602_14293_amd import kb as kbmod
+from paper_2602_14293_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _store(kind, N, d, Q, k, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    rows = torch.randn((N, d), generator=g, device="cuda")
+    rows[N // 3: N // 3 + min(40, N - N // 3)] = rows[N // 3].clone()                    # neighbours that tie
+    rows[torch.randint(0, N, (min(N, 60),), generator=g, device="cuda")] = rows[N // 2].clone()   # rows far apart that tie
+    if N > 4:
+        rows[N - 2] = 0
+    q = rows[torch.randint(0, N, (Q,), generator=g, device="cuda")] + 0.3 * torch.randn((Q, d), generator=g, device="cuda")
+    if Q > 2:
+        q[1] = rows[N // 3]
+        q[2] = 0
+    q = q.to(torch.float32 if kind == "f32" else torch.bfloat16)
+    scale = None
+    if kind in ("fp8", "q8"):
+        rows, scale = kbmod.quantize_rows(rows)
+        if kind == "q8":
+            q, _ = kbmod.quantize_rows(q)
+    elif kind == "bf16":
+        rows = rows.to(torch.bfloat16)
+    tags, qmask = W.random_bits64(N, 0.3, g, "cuda"), W.random_bits64(Q, 0.3, g, "cuda")
+    code = {"f32": kbmod.KB_F32, "bf16": kbmod.KB_BF16}.get(kind, kbmod.KB_FP8_E4M3)
+    kb = kbmod.KnowledgeBase(d, code, N, tagged=True)
+    kb.append(rows, scale, tags)
+    kb.normalize()
+    if N > 10:
+        kb.remove(torch.randperm(N, generator=g, device="cuda")[: N // 10].to(torch.int32).contiguous())
+    return kb, q.contiguous(), qmask
+
+
+def _same(a, b, what):
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1].view(torch.int32), b[1].view(torch.int32)), what
+
+
+# rows around tiles of 16 and 32, one and two layers of 2048 tiles, one tile of a third layer, groups of two tiles, the last size that is
+# scored whole and the first that is not; one query, a block that is one short, a full one; pieces that end in half a line (fp8)
+@pytest.mark.parametrize("kind,N,d,Q,k", [
+    ("bf16", 1, 64, 1, 1), ("bf16", 15, 64, 3, 8), ("bf16", 17, 128, 32, 20), ("bf16", 4096, 192, 31, 16), ("bf16", 4097, 64, 32, 5),
+    ("bf16", 5000, 1024, 32, 10), ("bf16", 16385, 256, 7, 9), ("bf16", 65535, 64, 32, 12), ("bf16", 65569, 128, 5, 33), ("bf16", 131073, 64, 32, 4),
+    ("bf16", 196700, 64, 9, 10), ("bf16", 327681, 64, 32, 16), ("bf16", (1 << 20) - 1, 64, 3, 90), ("bf16", 1 << 20, 64, 3, 90),
+    ("bf16", 3000, 2048, 30, 7), ("bf16", 40000, 1536, 32, 7), ("bf16", 9000, 4096, 12, 3), ("bf16", 700, 64, 200, 9),
+    ("fp8", 33, 64, 2, 8), ("fp8", 4096, 320, 32, 16), ("fp8", 20000, 64, 32, 8), ("fp8", 70001, 192, 17, 20), ("fp8", 400001, 64, 32, 24), ("fp8", 1000, 960, 100, 3),
+    ("q8", 33, 64, 2, 8), ("q8", 4096, 320, 32, 16), ("q8", 20000, 64, 32, 8), ("q8", 70001, 192, 17, 20), ("q8", 400001, 64, 32, 24), ("q8", 1000, 960, 100, 3)])
+def test_the_bits_of_the_pipeline(kind, N, d, Q, k):
+    kb, q, qmask = _store(kind, N, d, Q, k, seed=N + d)
+    for mask in (None, qmask):
+        kb.set_tuning("small_path", 1)
+        got = kb.query(q, k, mask)
+        kb.set_tuning("small_path", 0)
+        _same(got, kb.query(q, k, mask), f"{kind} N={N} d={d} Q={Q} k={k} masked={mask is not None}")
+    kb.close()
+
+
+# the memory that the plan in groups of 128 rows took is enough for a plan without a sampling pass
+@pytest.mark.parametrize("kind,N,d,Q,k", [("bf16", 200001, 64, 20, 10), ("q8", 9000, 64, 8, 4), ("fp8", 327680, 128, 32, 16), ("bf16", 131073, 1024, 32, 8)])
+def test_few_groups_where_there_is_little_memory(kind, N, d, Q, k):
+    kb, q, qmask = _store(kind, N, d, Q, k, seed=7)
+    want = kb.query(q, k, qmask)
+    have = 768 + sum((Q * -(-N // 128) * b + 255) // 256 * 256 for b in (4, 16))
+    if N <= 16384:
+        have = max(have, 768 + Q * 64 * k * 8 + 256)
+    L, out = kbmod.lib(), (ctypes.c_int64 * 4)()
+    assert L.kb_query_plan(kb._h, N, Q, k, 2 if kind == "q8" else 0, have, out) == 0 and out[0] in (1, 2) and out[1] <= have
+    ws = torch.full((have,), 0xA5, dtype=torch.uint8, device="cuda")
+    oi, os_ = torch.full_like(want[0], -7), torch.full_like(want[1], float("nan"))
+    assert L.kb_query(kb._h, kbmod._ptr(q), kbmod._CODE_OF[q.dtype], Q, kbmod._ptr(qmask), k, kbmod._ptr(oi), kbmod._ptr(os_), kbmod._ptr(ws), have, kbmod._stream()) == 0
+    torch.cuda.synchronize()
+    _same((oi, os_), want, f"{kind} N={N}")
+    kb.close()
