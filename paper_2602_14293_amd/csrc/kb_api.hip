@@ -17,6 +17,7 @@
 #include "kb_configs.hpp"
 #include "kb_internal.hpp"
 #include "kb_scan.hpp"
+#include "kb_norm.hpp"
 #include "kb_stream.hpp"
 
 using namespace kbi;
@@ -443,7 +444,7 @@ constexpr int WHOLE_MAX_QUERIES = 4096;
 // (fp8 rows with bf16 queries 1.10 and more at 2^25 products of up to 16,384 elements, f32 1.03 and more)
 int64_t whole_max_rows(const kb *h, int32_t Q, bool q8)
 {
-    if (Q <= 32) return h->dtype == KB_F32 ? WHOLE_MAX_ROWS_FEW : WHOLE_MAX_ROWS_STREAM;
+    if (Q <= 32) return WHOLE_MAX_ROWS_STREAM;
     if (Q <= 128) return WHOLE_MAX_ROWS;
     const int64_t columns = h->dtype == KB_BF16 ? ceil_div(Q, 128) * 128 : Q;
     int64_t pairs = (int64_t)1 << (h->dtype == KB_BF16 ? 24 : h->dtype == KB_F32 ? 26 : 25);
@@ -451,11 +452,32 @@ int64_t whole_max_rows(const kb *h, int32_t Q, bool q8)
     return std::min(WHOLE_MAX_ROWS, pairs / columns);
 }
 constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
+// Calls on f32 rows whose scan takes two f16 values an element (Mma<KB_F32_SPLIT>).  They select SPLIT_MORE entries more than k by the split
+// products, and the launch that selects orders these by the f32 ones (restate), so that scores don't depend on the path: rows change
+// places only where their scores are within some 1e-6 of each other, and one is missed where more than SPLIT_MORE are that close to the k-th.
+// That takes a call 4 to 5 us (few queries, the rows of k entries in LDS at once; more with k) or 10 (many), and the tiled scan a launch of 2 for
+// the scales, so it is for calls whose scan is long enough.  us a call, f32 instruction | split:
+//   up to 32 queries (kb_stream.hpp, eight wavefronts)     100,000 x 512, Q 12    57.1 | 55.4    300,007 x 384, Q 20   100 | 90.8    300,000 x 768, Q 18    182 | 165
+//     600,000 x 128, Q 16    86.0 | 71.4     1,000,000 x 256, Q 32  208 | 173      under the limits:  50,000 x 896, Q 12   47.9 | 50.2    60,000 x 768, Q 4    47.0 | 51.3
+//     50,000 x 768, Q 32, four wavefronts   45.8 | 58.1      170,000 x 256, k 60   63.8 | 74.5     300,000 x 1024, Q 8, every row on the same few channels   231 | 238
+//   more (tiled kernel)     60,000 x 768, Q 128   113 | 87.5     179,009 x 576, Q 115  247 | 180     150,000 x 256, Q 500  412 | 244     400,000 x 512, Q 200, k 128  1076 | 575
+//     under the limit:       65,000 x 256, Q 64   32.8 | 36.3    33,000 x 1024, Q 64  73.0 | 72.8    16,000 x 256, Q 500  66.3 | 76.8    8000 x 1024, Q 300   82.4 | 95.9
+constexpr int32_t SPLIT_MORE = 4;
+constexpr int RESTATE_LDS = 96 * 1024;
+constexpr int SPLIT_MAX_K_FEW = 32;
+constexpr int64_t SPLIT_MIN_BYTES = 192 << 20, SPLIT_MIN_MULTIPLICATIONS = (int64_t)1 << 32;
+bool split_f32(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw)
+{
+    if (h->dtype != KB_F32 || draw || h->tune_config) return false;
+    if (Q > 32) return n * Q * h->d >= SPLIT_MIN_MULTIPLICATIONS;
+    return k <= SPLIT_MAX_K_FEW && n * h->d * 4 >= SPLIT_MIN_BYTES && h->d < 1024 && (int64_t)(k + SPLIT_MORE + 1) * (h->d + 4) * 4 <= RESTATE_LDS && n <= WHOLE_MAX_ROWS_STREAM &&
+           Q * ceil_div(h->d, 64) * 256 <= 56 * 1024;
+}
 // The scan with the queries in LDS (kb_stream.hpp), where they fit beside the rings of four wavefronts and up.
 // `most_groups`: no more groups than that.
-bool make_stream_plan(const kb *h, int64_t n, int32_t Q, bool q8, bool dense, int64_t most_groups, StreamPlan *out)
+bool make_stream_plan(const kb *h, int64_t n, int32_t Q, bool q8, bool split, bool dense, int64_t most_groups, StreamPlan *out)
 {
-    if (h->dtype == KB_F32 || (!dense && Q > 32)) return false;
+    if ((h->dtype == KB_F32 && (dense || !split)) || (!dense && Q > 32)) return false;
     StreamPlan p;
     const int64_t row_bytes = (int64_t)h->d * key_bytes(h->dtype), pieces = ceil_div(row_bytes, 128);
     const int64_t query_bytes = row_bytes * (h->dtype == KB_FP8_E4M3 && !q8 ? 2 : 1);
@@ -498,12 +520,13 @@ size_t whole_bytes(int32_t Q, int32_t groups, size_t *off_pair)
     *off_pair = WHOLE_OFF_BEST + align_up(sizeof(float) * (size_t)Q * groups);
     return *off_pair + align_up(sizeof(u32x4) * (size_t)Q * groups);
 }
-bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, Thrift thrift, WholePlan *out)
+bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, bool split, Thrift thrift, WholePlan *out)
 {
     if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
     if (n < 1 || Q > WHOLE_MAX_QUERIES || n > whole_max_rows(h, Q, q8) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
+    const int32_t rule_k = split ? std::max(1, k - SPLIT_MORE) : k;
     WholePlan p;
-    p.stream = make_stream_plan(h, n, Q, q8, false, thrift == LEAST ? ceil_div(n, 128) : WHOLE_MAX_GROUPS, &p.st);
+    p.stream = make_stream_plan(h, n, Q, q8, split, false, thrift == LEAST ? ceil_div(n, 128) : WHOLE_MAX_GROUPS, &p.st);
     if (!p.stream && Q <= 32 && n > WHOLE_MAX_ROWS_FEW) return false;
     if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
     else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : n >= 128 * 2 * DEVICE_CUS && h->d >= 512 ? 21 : 16;    // (14: once every resident workgroup gets a tile)
@@ -550,10 +573,10 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     // f32, tiles of 64 rows, too many to be halved into groups: four neighbours share a group.  The pipeline from before had tiles of 128 as this
     // plan had; now, with 64 in both, time of the pipeline over this plan's, 140,000 x 768 rows and 64 queries in no order | runs of 4 | 32:
     // k = 16 1.06 | 0.80 | 0.69 (256 elements 1.28 | 1.00 | 0.91), 24 1.07 | 0.71 | 0.64, 40 1.08 | 0.59 | 0.53, 80 1.16 | 0.46 | 0.40
-    if (p.config == F32_SQUARE_CONFIG && !p.fine && k > 16) return false;
+    if (p.config == F32_SQUARE_CONFIG && !p.fine && rule_k > 16) return false;
     const size_t row_bytes = (size_t)h->d * key_bytes(h->dtype);
     const bool cheap = p.group_rows <= 32 && !(p.stream && q8) && row_bytes <= (Q > 32 ? 512 : h->dtype == KB_F32 ? 1024 : 1536);
-    if (cubed(k) > (cheap ? 4.0 : 0.12) * (double)p.k_groups * p.k_groups) return false;
+    if (cubed(rule_k) > (cheap ? 4.0 : 0.12) * (double)p.k_groups * p.k_groups) return false;
     const int64_t items = tiles * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
     p.grid = p.stream ? p.st.blocks : (int32_t)(items < most ? items : most);
     p.off_best = WHOLE_OFF_BEST;
@@ -572,7 +595,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
 constexpr int64_t DENSE_MAX_PAIRS = (int64_t)1 << 23;
 constexpr int64_t DENSE_FIRST_ROWS = 4096;                 // up to here the dense plan is never the slower one
 bool dense_is_better(int64_t n, int32_t k, const WholePlan &w) { return n <= DENSE_FIRST_ROWS || cubed(k) > 0.5 * (double)w.k_groups * w.k_groups; }
-bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, DensePlan *out)
+bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, bool split, DensePlan *out)
 {
     if (h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
     if (n < 1 || n > DENSE_MAX_ROWS || n * Q > DENSE_MAX_PAIRS || (q8 && h->dtype != KB_FP8_E4M3)) return false;
@@ -582,7 +605,7 @@ bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     const int64_t tiles32 = ceil_div(n, 32) * ceil_div(Q, 32);
     const bool small = tiles32 <= (h->dtype == KB_F32 ? DEVICE_CUS : 2 * DEVICE_CUS);
     if (q8) p.config = small ? FP8_QUERY_SMALL_CONFIG : Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
-    else if (h->dtype == KB_F32) p.config = small && !draw ? SMALL_F32_CONFIG : F32_SQUARE_CONFIG;
+    else if (h->dtype == KB_F32) p.config = small && !draw && !split ? SMALL_F32_CONFIG : F32_SQUARE_CONFIG;
     else if (h->dtype == KB_BF16) p.config = small ? 13 : Q <= 64 ? 12 : 16;
     else p.config = small ? 13 : Q <= 32 ? 1 : 2;
     ConfigInfo ci;
@@ -592,7 +615,7 @@ bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     p.nqb = (int32_t)ceil_div(Q, p.tq);
     const int64_t items = ceil_div(n, ci.tk) * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
     p.grid = (int32_t)(items < most || p.config == SMALL_F32_CONFIG ? items : most);
-    p.stream = small && !draw && make_stream_plan(h, n, Q, q8, true, WHOLE_MAX_GROUPS, &p.st);
+    p.stream = small && !draw && make_stream_plan(h, n, Q, q8, split, true, WHOLE_MAX_GROUPS, &p.st);
     if (p.stream) p.grid = p.st.blocks * p.st.nqb;
     p.stride = (int32_t)(ceil_div(n, 128) * 128);
     p.off_values = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));       // the diagnostics come first, as always
@@ -665,66 +688,8 @@ void bound_sizes(const kb *h, const Choice &c, int32_t Q, int32_t k, bool draw, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// row norms
+// row norms (see kb_norm.hpp)
 // ------------------------------------------------------------------------------------------------
-template <int DT> __device__ inline float piece_sum_squares(u32x4 v);
-template <> __device__ inline float piece_sum_squares<KB_F32>(u32x4 v)
-{
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float x = as_f32(v[e]);
-        s += x * x;
-    }
-    return s;
-}
-template <> __device__ inline float piece_sum_squares<KB_BF16>(u32x4 v)
-{
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float lo = as_f32(v[e] << 16), hi = as_f32(v[e] & 0xffff0000u);
-        s += lo * lo;
-        s += hi * hi;
-    }
-    return s;
-}
-template <> __device__ inline float piece_sum_squares<KB_FP8_E4M3>(u32x4 v)
-{
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const f32x2 a = __builtin_amdgcn_cvt_pk_f32_fp8(v[e], false), b = __builtin_amdgcn_cvt_pk_f32_fp8(v[e], true);
-        s += a.x * a.x;
-        s += a.y * a.y;
-        s += b.x * b.x;
-        s += b.y * b.y;
-    }
-    return s;
-}
-
-__device__ inline float wave_sum(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// One wavefront per row: lanes stride over the row's 16-byte pieces, fp32 sum of squares, butterfly
-// reduction, inv = 1/sqrt(sum) or 0 for a zero row.
-__device__ inline float inv_norm_of(float square_sum) { return square_sum > 0.f ? 1.0f / sqrtf(square_sum) : 0.f; }
-template <int DT> __device__ inline float row_square_sum(const void *base, int64_t row, int row_bytes, int lane)
-{
-    const u32x4 *p = reinterpret_cast<const u32x4 *>(static_cast<const unsigned char *>(base) + (size_t)row * row_bytes);
-    float s = 0.f;
-    for (int i = lane; i < row_bytes / 16; i += 64) s += piece_sum_squares<DT>(__builtin_nontemporal_load(p + i));
-    return wave_sum(s);
-}
-template <int DT> __device__ inline float row_inv_norm(const void *base, int64_t row, int row_bytes, int lane)
-{
-    return inv_norm_of(row_square_sum<DT>(base, row, row_bytes, lane));
-}
-
 template <int DT> __global__ __launch_bounds__(256) void row_norm_kernel(const void *keys, int64_t begin, int64_t end, int d, float *inv_norm)
 {
     const int lane = threadIdx.x & 63;
@@ -1006,7 +971,7 @@ __device__ inline void select_topk_desc(uint64_t *buf, int n, int k, SelectScrat
     __syncthreads();
 }
 
-template <int KT, int UNR> __device__ f32x16 score_rows(const void *keys, const void *queries, int d, int64_t my_row, int q);
+template <int KT, int UNR> __device__ f32x16 score_rows(const void *keys, const void *queries, int d, int64_t my_row, int q, float key_scale = 1.f, float query_scale = 1.f);
 constexpr int KT_FP8_Q8 = 3;        // stands for fp8 keys with fp8 queries (one fp8 matrix instruction per 64-byte chunk, as in the scan)
 
 // k-th best group maximum of the sampling pass = a lower bound of the k-th best score (k distinct
@@ -1093,10 +1058,10 @@ template <int QT, bool KEYS, int KT, int PER = 2> __global__ __launch_bounds__(1
             return;
         }
         if (tid < 64) {
-            const float square_sum = row_square_sum<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid), inv = inv_norm_of(square_sum);
+            const float square_sum = row_square_sum<QT>(a.queries, q, a.d * bytes_of(QT), tid), inv = inv_norm_of(square_sum);
             if (tid == 0) {
                 a.invq[q] = inv;
-                sh_iq = inv;
+                sh_iq = used_inv<QT>(inv);
                 sh_endless = square_sum == __builtin_inff();
             }
         }
@@ -1224,13 +1189,16 @@ struct FinalArgs {
     int32_t fb_parts;
     const uint64_t *thr64;    // [Q] threshold words of the scan
     int32_t raw;              // the lists hold dot * inv_k products (plain queries), not finished candidate words
+    int32_t k_out, more_lds;  // as in WholeSelectArgs
+    int32_t more_at;          // offset of these bytes in the dynamic LDS
 };
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 // 32 dot products of one query by one wavefront, accumulated exactly as the scan kernels do: lane (lrow, half) supplies
 // row my_row for lrow and gets, in element i, the product of the row that lane 8 (i / 4) + 4 half + i % 4 supplied
 // (every column holds the same query).
-template <int KT, int UNR> __device__ inline f32x16 score_rows(const void *keys, const void *queries, int d, int64_t my_row, int q)
+// (split f32: the scales of that row and of the query)
+template <int KT, int UNR> __device__ inline f32x16 score_rows(const void *keys, const void *queries, int d, int64_t my_row, int q, float key_scale, float query_scale)
 {
     constexpr bool Q8 = KT == KT_FP8_Q8;
     constexpr int KTT = Q8 ? (int)KB_FP8_E4M3 : KT;
@@ -1238,14 +1206,34 @@ template <int KT, int UNR> __device__ inline f32x16 score_rows(const void *keys,
     const int half = (threadIdx.x & 63) >> 5;
     const size_t key_row_bytes = (size_t)d * KEY_BYTES;
     const unsigned char *qrow = static_cast<const unsigned char *>(queries) + (size_t)q * d * QRY_BYTES;
-    const int n_groups = (int)(key_row_bytes / (Q8 ? 64 : 32));
+    const int n_groups = (int)(key_row_bytes / (Q8 || KT == KB_F32_SPLIT ? 64 : 32));
     const unsigned char *krow = static_cast<const unsigned char *>(keys) + (size_t)my_row * key_row_bytes + half * 16;
     f32x16 acc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
     // The loads of UNR groups go out before their matrix instructions (the order of the accumulation does not
     // change): one memory round trip per UNR groups instead of one per group.
-    if constexpr (Q8) {
+    if constexpr (KT == KB_F32_SPLIT) {
+        const unsigned char *kp = krow + half * 16, *qp = qrow + half * 32;
+        auto at = [](const unsigned char *base, int g, int piece) { return *reinterpret_cast<const u32x4 *>(base + (size_t)g * 64 + piece * 16); };
+        auto step = [&](const u32x4 &a0, const u32x4 &a1, const u32x4 &b0, const u32x4 &b1) {
+            Mma<KT>::run(acc, Mma<KT>::prepare(a0, a1, key_scale), Mma<KT>::prepare(b0, b1, query_scale));
+        };
+        int g = 0;
+        for (; g + UNR <= n_groups; g += UNR) {
+            u32x4 a0[UNR], a1[UNR], b0[UNR], b1[UNR];
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                a0[u] = at(kp, g + u, 0);
+                a1[u] = at(kp, g + u, 1);
+                b0[u] = at(qp, g + u, 0);
+                b1[u] = at(qp, g + u, 1);
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) step(a0[u], a1[u], b0[u], b1[u]);
+        }
+        for (; g < n_groups; ++g) step(at(kp, g, 0), at(kp, g, 1), at(qp, g, 0), at(qp, g, 1));
+    } else if constexpr (Q8) {
         // one fp8 matrix instruction per 64-byte chunk: lane half h supplies bytes [32h, 32h+32) of its key row
         // and of the query row, the operand layout the scan uses, so both paths give the same bits
         const unsigned char *kp = krow + half * 16;
@@ -1296,6 +1284,7 @@ template <int KT, int UNR> __device__ inline f32x16 score_rows(const void *keys,
     return acc;
 }
 
+template <int KT> __device__ inline float key_scale_of(const float *inv_norm, int64_t row) { return KT == KB_F32_SPLIT ? f32_row_scale(inv_norm[row]) : 1.f; }
 template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, uint64_t *buf, uint32_t *ctl, SelectScratch *sc, int64_t row_begin,
                                                    int64_t row_end, const float *inv_q = nullptr)
 {
@@ -1303,7 +1292,7 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
     const int cap = a.cand_cap;
     const bool filter = a.qmask != nullptr;
     const uint64_t qm = filter ? a.qmask[q] : 0;
-    const float iq = inv_q ? *inv_q : a.invq[q];
+    const float inv = inv_q ? *inv_q : a.invq[q], iq = used_inv<KT>(inv), query_scale = f32_row_scale(inv);
     uint64_t *thr_local = reinterpret_cast<uint64_t *>(ctl + 2);   // ctl[0] = count, ctl[2..3] = threshold word
     if (tid == 0) {
         ctl[0] = 0;
@@ -1313,7 +1302,7 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
     for (int64_t row0 = row_begin; row0 < row_end; row0 += 128) {
         int64_t my_row = row0 + wave * 32 + lrow;
         if (my_row >= row_end) my_row = row_end - 1;
-        const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, my_row, q);    // (16 where a group is two register quadruples, 8 where it is three or four)
+        const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, my_row, q, key_scale_of<KT>(a.inv_norm, my_row), query_scale);    // (16 where a group is two register quadruples, 8 where it is three or four)
         // every column holds the same query; lanes 0..15 of each half own one row each
         float v = acc[0];
 #pragma unroll
@@ -1321,7 +1310,7 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
         if (lrow < 16) {
             const int64_t row = row0 + wave * 32 + 8 * (lrow >> 2) + 4 * half + (lrow & 3);
             if (row < row_end && !row_removed(a.inv_norm[row]) && (!filter || (a.tags[row] & qm) != 0)) {
-                float value = final_score(v, a.inv_norm[row], iq);
+                float value = final_score(v, used_inv<KT>(a.inv_norm[row]), iq);
                 if (a.draw.enabled) value = draw_key_of(value, a.draw, a.draw.first_query + (uint32_t)q, row);
                 const uint64_t cw = pack_candidate(value, (uint32_t)row);
                 if (cw > *thr_local && value > -__builtin_inff()) {
@@ -1369,6 +1358,8 @@ struct WholeSelectArgs {
     uint64_t *stats;
     int64_t n_keys;
     int32_t k, d, groups, group_rows, tile_rows, tiles, grid;
+    int32_t k_out;                      // results wanted, where k is a few more (split f32)
+    int32_t more_lds;                   // bytes of dynamic LDS
     int32_t waves, per_group, run_shift;        // StreamPlan (tiles: its units), where the scan was kb_stream_kernel
 };
 // 256 threads hold the groups: the kernel's length is a dozen barriers, which more wavefronts only make longer (64 queries
@@ -1489,6 +1480,96 @@ template <int PER> __device__ __forceinline__ KthBound bound_kth(const float (&v
     return r;
 }
 
+// Split f32: the scores of the m rows in `words` as every other kernel has them for f32 rows, in place of those that selected them.  A dot
+// product is v_mfma_f32_32x32x2f32's chain (0 4 1 5 2 6 3 7 of every eight elements) on the vector units, which has the same bits;
+// the rows come through LDS a few columns at a time (stage: stage_bytes, 16-byte aligned).  256 threads, converged.
+// So f32 scores don't depend on how many queries or rows a call has, and selecting a few more than k (SPLIT_MORE) leaves their order to these.
+__device__ inline void restate(uint64_t *words, int m, const void *keys, const float *inv_norm, const void *query, int d, float inv_q, float *stage, int stage_bytes)
+{
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int floats = stage_bytes / 4, batch = min(m, floats / 36 - 1);        // rows at a time, so that 32 columns fit (stage_bytes >= 8 KB)
+    float dot = 0.f;
+    for (int r0 = 0; r0 < m; r0 += batch) {
+        const int rows = min(batch, m - r0), room = floats / (rows + 1) - 4;              // floats of a row at a time, four more against bank conflicts
+        const int cols = room >= d ? d : room & ~31, stride = cols + 4;                   // (d is a multiple of 32)
+        for (int c0 = 0; c0 < d; c0 += cols) {
+            const int n = (d - c0 < cols ? d - c0 : cols) / 4;
+            __syncthreads();
+            for (int r = wave; r <= rows; r += 4) {
+                const uint32_t row = r < rows ? candidate_index(words[r0 + r]) : 0u;
+                const float *from = r < rows ? static_cast<const float *>(keys) + (size_t)__builtin_amdgcn_readfirstlane(row) * d : static_cast<const float *>(query);
+                for (int at = 0; at < n; at += 64)
+                    if (at + lane < n) __builtin_amdgcn_global_load_lds((const void *)(from + c0 + 4 * (at + lane)), (lds_ptr)(stage + r * stride + 4 * at), 16, 0, 0);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0070 | 0x0F00);        // vmcnt(0)
+            __syncthreads();
+            if (tid >= r0 && tid < r0 + rows) {
+                const f32x4 *a = reinterpret_cast<const f32x4 *>(stage + (tid - r0) * stride), *b = reinterpret_cast<const f32x4 *>(stage + rows * stride);
+#pragma unroll 4
+                for (int i = 0; i < n; i += 2) {
+                    const f32x4 a0 = a[i], a1 = a[i + 1], b0 = b[i], b1 = b[i + 1];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        dot = __builtin_fmaf(a0[e], b0[e], dot);
+                        dot = __builtin_fmaf(a1[e], b1[e], dot);
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (tid < m) {
+        const uint32_t row = candidate_index(words[tid]);
+        const float value = final_score(dot, inv_norm[row], inv_q);
+        words[tid] = value > -__builtin_inff() ? pack_candidate(value, row) : 0ull;
+    }
+    __syncthreads();
+}
+// LDS for the rows of k entries beside what the selecting kernels have (their buffers of 32 KB, in several rounds, where more queries than
+// compute units would wait for each other)
+int restate_lds(int32_t Q, int32_t k, int32_t d)
+{
+    const int64_t want = ((int64_t)(k + 1) * (d + 4) * 4 + 1023) / 1024 * 1024;
+    return Q > DEVICE_CUS ? 0 : (int)std::min<int64_t>(want, RESTATE_LDS);
+}
+// ... and the best k of them to the query's place in the output
+__device__ inline void write_restated(SelectScratch *sc, int m, int q, int k, int32_t *out_index, float *out_score)
+{
+    const int tid = threadIdx.x;
+    const uint64_t e = tid < m ? sc->sel[tid] : 0ull;
+    int rank = 0;
+#pragma unroll 8
+    for (int j = 0; j < m; ++j) rank += sc->sel[j] > e || (e == 0ull && j < tid);       // (words without a score come last, as nothing)
+    if (tid < m && rank < k) {
+        out_index[(size_t)q * k + rank] = e ? (int32_t)candidate_index(e) : -1;
+        out_score[(size_t)q * k + rank] = e ? candidate_score(e) : -__builtin_inff();
+    }
+    if (tid >= m && tid < k) {
+        out_index[(size_t)q * k + tid] = -1;
+        out_score[(size_t)q * k + tid] = -__builtin_inff();
+    }
+}
+
+// The best k of the `have` words of `buf` go to sc->sel (256 threads, converged); returns how many there are.
+__device__ __forceinline__ int best_to_scratch(uint64_t *buf, uint32_t have, int k, SelectScratch *sc)
+{
+    const int tid = threadIdx.x, m = (int)have < k ? (int)have : k;
+    if (have <= 128u) {
+        const uint64_t e = tid < (int)have ? buf[tid] : 0ull;
+        int rank = 0;
+#pragma unroll 8
+        for (int j = 0; j < (int)have; ++j) rank += buf[j] > e;
+        if (tid < (int)have && rank < k) sc->sel[rank] = e;
+    } else {
+        __syncthreads();
+        select_topk_desc(buf, (int)have, k, sc, tid, WHOLE_THREADS);
+        if (tid < m) sc->sel[tid] = buf[tid];
+    }
+    __syncthreads();
+    return m;
+}
+
 // The best k of the `have` words of `buf`, in order, to a query's place in the output (256 threads, converged).
 __device__ __forceinline__ void write_best(uint64_t *buf, uint32_t have, int q, int k, int32_t *out_index, float *out_score, SelectScratch *sc)
 {
@@ -1524,12 +1605,13 @@ __device__ __forceinline__ void write_best(uint64_t *buf, uint32_t have, int q, 
 template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREADS) void whole_select_kernel(WholeSelectArgs a)
 {
     static_assert(PER * WHOLE_THREADS <= WHOLE_MAX_GROUPS);
-    constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
+    constexpr int QT = queries_of(KT);
+    extern __shared__ __attribute__((aligned(16))) unsigned char more_lds[];        // split f32: see restate_lds
     __shared__ __attribute__((aligned(16))) uint64_t buf[WHOLE_CAP];
     __shared__ KthScratch kth;
     __shared__ uint16_t list[WHOLE_MAX_GROUPS], again[WHOLE_MAX_GROUPS];        // groups that reach the bound; with what is not known of them
     __shared__ SelectScratch sc;
-    __shared__ float sh_iq;
+    __shared__ float sh_iq, sh_scale, sh_inv;
     __shared__ uint32_t sh_cnt, sh_listed, sh_again;
     __shared__ uint64_t sh_thr;
     constexpr int nt = WHOLE_THREADS, nw = nt / 64;
@@ -1546,9 +1628,11 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
     const uint64_t qm = a.qmask ? a.qmask[q] : 0ull;
     if (q == 0 && tid < STAT_WORDS + STAT_PARTIALS) a.stats[tid] = tid == 3 ? (uint64_t)a.grid : 0ull;
     if (tid < 64) {
-        const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid);
+        const float inv = row_inv_norm<QT>(a.queries, q, a.d * bytes_of(QT), tid);
         if (tid == 0) {
-            sh_iq = inv;
+            sh_iq = used_inv<KT>(inv);
+            sh_scale = f32_row_scale(inv);
+            sh_inv = inv;
             sh_cnt = sh_listed = sh_again = 0;
             sh_thr = 0;
         }
@@ -1658,20 +1742,24 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
             const uint32_t g = to_score[t / per], in_group = t % per * 32, place0 = first_place(g) + in_group, known = pair[g][2];
             const int lrow = lane & 31, half = lane >> 5;
             const int64_t at = row_at(g, place0 + lrow), mine = at < a.n_keys ? at : a.n_keys - 1;      // (a place past a group of 16 is some other row)
-            const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, mine, q);
+            const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, mine, q, key_scale_of<KT>(a.inv_norm, mine), sh_scale);
             const float dot = select16(acc, lrow & 15);
             const uint32_t rel = 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3), place = place0 + rel;
             const int64_t row = row_at(g, place);
             const bool listed_before = place == (known & 255u) || place == (known >> 8 & 255u) || place + 1u == (known >> 16 & WHOLE_THIRD);
             if (lrow < 16 && in_group + rel < (uint32_t)a.group_rows && row < a.n_keys && !listed_before) {
-                const float ik = a.inv_norm[row];
+                const float ik = used_inv<KT>(a.inv_norm[row]);
                 if (!row_removed(ik) && (!a.qmask || (a.tags[row] & qm) != 0)) append(dot * ik, (uint32_t)row);
             }
         }
         __syncthreads();
         have = sh_cnt;
     }
-    write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
+    if constexpr (KT == KB_F32_SPLIT) {
+        const int m = best_to_scratch(buf, have, k, &sc);
+        restate(sc.sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, sh_inv, a.more_lds ? reinterpret_cast<float *>(more_lds) : reinterpret_cast<float *>(buf), a.more_lds ? a.more_lds : (int)sizeof buf);
+        write_restated(&sc, m, q, a.k_out, a.out_index, a.out_score);
+    } else write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
 }
 
 // Dense plan, second launch: one workgroup per query selects from the products (KEYS: the keys of the weighted selection)
@@ -1683,16 +1771,20 @@ struct DenseSelectArgs {
     float *out_score;
     uint64_t *stats;
     int32_t k, d, n, stride, grid;
+    const void *keys;           // split f32, as in WholeSelectArgs
+    const float *inv_norm;
+    int32_t k_out, more_lds;
 };
 template <int QT, bool KEYS, int PIECES> __global__ __launch_bounds__(DENSE_THREADS) void dense_select_kernel(DenseSelectArgs a)
 {
     static_assert(DENSE_THREADS == WHOLE_THREADS && PIECES * 4 * DENSE_THREADS <= DENSE_MAX_ROWS);
     constexpr int PER = 4 * PIECES;
     constexpr float NONE = -__builtin_inff();
+    extern __shared__ __attribute__((aligned(16))) unsigned char more_lds[];        // split f32: see restate_lds
     __shared__ __attribute__((aligned(16))) uint64_t buf[WHOLE_CAP];
     __shared__ KthScratch kth;
     __shared__ SelectScratch sc;
-    __shared__ float sh_iq;
+    __shared__ float sh_iq, sh_inv;
     __shared__ uint32_t sh_cnt;
     __shared__ uint64_t sh_thr;
     const int q = blockIdx.x, tid = threadIdx.x, k = a.k;
@@ -1707,8 +1799,11 @@ template <int QT, bool KEYS, int PIECES> __global__ __launch_bounds__(DENSE_THRE
     }
     if (q == 0 && tid < STAT_WORDS + STAT_PARTIALS) a.stats[tid] = tid == 3 ? (uint64_t)a.grid : 0ull;
     if (!KEYS && tid < 64) {
-        const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid);
-        if (tid == 0) sh_iq = inv;
+        const float inv = row_inv_norm<QT>(a.queries, q, a.d * bytes_of(QT), tid);
+        if (tid == 0) {
+            sh_iq = used_inv<QT>(inv);
+            sh_inv = inv;
+        }
     }
     if (tid == 0) {
         sh_cnt = 0;
@@ -1760,7 +1855,11 @@ template <int QT, bool KEYS, int PIECES> __global__ __launch_bounds__(DENSE_THRE
             __syncthreads();
         }
     }
-    write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
+    if constexpr (QT == KB_F32_SPLIT) {
+        const int m = best_to_scratch(buf, have, k, &sc);
+        restate(sc.sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, sh_inv, a.more_lds ? reinterpret_cast<float *>(more_lds) : reinterpret_cast<float *>(buf), a.more_lds ? a.more_lds : (int)sizeof buf);
+        write_restated(&sc, m, q, a.k_out, a.out_index, a.out_score);
+    } else write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
 }
 
 template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalArgs a)
@@ -1823,7 +1922,7 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
         // A plain scan leaves (dot * inv_k, row) of live rows: each candidate is finished here as the scan's exact test
         // would have: the final score from the same three fp32 operations every kernel uses, nothing below the
         // threshold word.  What fails becomes a zero word, which sorts last.
-        const float iq = a.invq[q];
+        const float iq = used_inv<KT>(a.invq[q]);
         const uint64_t t64 = a.raw ? a.thr64[q] : 0ull;
         const uint64_t *lists = a.cand + (size_t)q * a.cand_cap;
         for (uint32_t j0 = tid; j0 < n; j0 += 4 * 256) {
@@ -1853,6 +1952,14 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
         }
         __syncthreads();
         select_topk_desc(buf, (int)n, a.k, sc, tid, 256);
+    }
+    if constexpr (KT == KB_F32_SPLIT) {
+        const uint64_t cw = tid < a.k ? buf[tid] : 0ull;
+        if (tid < a.k) sc->sel[tid] = cw;
+        const int m = __syncthreads_count(cw != 0ull);          // (the words without an entry come last)
+        restate(sc->sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, a.invq[q], reinterpret_cast<float *>(a.more_lds ? smem_raw + a.more_at : smem_raw), a.more_lds ? a.more_lds : a.cand_cap * 8);
+        write_restated(sc, m, q, a.k_out, a.out_index, a.out_score);
+        return;
     }
     if (tid < a.k) {
         const uint64_t cw = tid < a.cand_cap ? buf[tid] : 0ull;
@@ -1960,7 +2067,7 @@ template <int KT> size_t probe_scan_lds() { return (size_t)PROBE_WAVES * ProbeRi
 template <int KT> __global__ __launch_bounds__(PROBE_THREADS) void probe_scan_kernel(FinalArgs a, const int64_t *cluster_offsets, int n_clusters,
                                                                                         const int32_t *probe, int nprobe, int splits, uint64_t *lists)
 {
-    constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
+    constexpr int QT = queries_of(KT);
     constexpr int THREADS = PROBE_THREADS, STEP = 32 * PROBE_WAVES;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     uint64_t *buf = reinterpret_cast<uint64_t *>(smem_raw + PROBE_WAVES * ProbeRing<KT>::BYTES);
@@ -2001,7 +2108,7 @@ template <int KT> __global__ __launch_bounds__(PROBE_THREADS) void probe_scan_ke
         if (wave < PROBE_WAVES && base < end) dot = select16(score_rows_ring<KT>(a.keys, a.queries, a.d, base, end, q, smem_raw + wave * ProbeRing<KT>::BYTES), lrow & 15);
         if (row0 == begin) {
             if (wave == PROBE_WAVES) {
-                const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), lane);
+                const float inv = row_inv_norm<QT>(a.queries, q, a.d * bytes_of(QT), lane);
                 if (lane == 0) inv_q = inv;
             }
             __syncthreads();
@@ -2044,7 +2151,7 @@ template <int KT> __global__ __launch_bounds__(PROBE_THREADS) void probe_scan_ke
 // stats: the diagnostics of a query that took this path: no candidates, no sampling, one workgroup per block.
 template <int KT> __global__ __launch_bounds__(256) void small_scan_kernel(FinalArgs a, uint64_t *lists, uint64_t *stats)
 {
-    constexpr int QT = KT == KB_F32 ? (int)KB_F32 : KT == KT_FP8_Q8 ? (int)KB_FP8_E4M3 : (int)KB_BF16;     // type of the queries
+    constexpr int QT = queries_of(KT);
     __shared__ __attribute__((aligned(16))) uint64_t buf[PROBE_CAP];
     __shared__ uint32_t ctl[4];
     __shared__ SelectScratch sc;
@@ -2059,7 +2166,7 @@ template <int KT> __global__ __launch_bounds__(256) void small_scan_kernel(Final
         return;
     }
     if (tid < 64) {
-        const float inv = row_inv_norm<QT>(a.queries, q, a.d * (QT == KB_F32 ? 4 : QT == KB_BF16 ? 2 : 1), tid);
+        const float inv = row_inv_norm<QT>(a.queries, q, a.d * bytes_of(QT), tid);
         if (tid == 0) inv_q = inv;
     }
     __syncthreads();
@@ -2102,7 +2209,7 @@ template <int KT, bool STREAM> auto whole_select(int groups) -> void (*)(WholeSe
 }
 template <bool STREAM> auto whole_select_for(int kt, int groups) -> void (*)(WholeSelectArgs)
 {
-    return kt == KB_F32 ? whole_select<KB_F32, STREAM>(groups) : kt == KB_BF16 ? whole_select<KB_BF16, STREAM>(groups)
+    return kt == KB_F32 ? whole_select<KB_F32, STREAM>(groups) : kt == KB_F32_SPLIT ? whole_select<KB_F32_SPLIT, STREAM>(groups) : kt == KB_BF16 ? whole_select<KB_BF16, STREAM>(groups)
          : kt == KB_FP8_E4M3 ? whole_select<KB_FP8_E4M3, STREAM>(groups) : whole_select<KT_FP8_Q8, STREAM>(groups);
 }
 template <int QT, bool KEYS> void launch_dense_select(const DenseSelectArgs &t, int32_t Q, hipStream_t s)
@@ -2120,7 +2227,7 @@ hipError_t launch_scan(kb_dtype_t dt, int config, int family, bool sample, int g
         return dt == KB_BF16 ? launch_scan_sp_bf16(config, sample, grid, a, s)
                : dt == KB_FP8_E4M3 ? launch_scan_sp_fp8(config, sample, grid, a, s) : hipErrorInvalidValue;
     switch (dt) {
-    case KB_F32: return launch_scan_f32(config, sample, grid, a, s);
+    case KB_F32: return a.invq_stride ? launch_scan_f32_split(config, sample, grid, a, s) : launch_scan_f32(config, sample, grid, a, s);
     case KB_BF16: return launch_scan_bf16(config, sample, grid, a, s);
     default: return launch_scan_fp8(config, sample, grid, a, s);
     }
@@ -2371,12 +2478,29 @@ hipError_t launch_stream_scan(const kb *h, const StreamPlan &p, const void *quer
     a.side_slots = p.side_slots;
     a.blocks = p.blocks;
     a.run_shift = p.run_shift;
-    return h->dtype == KB_BF16 ? launch_stream_bf16(p, dense, once, a, s) : launch_stream_fp8(p, q8, dense, once, a, s);
+    return h->dtype == KB_F32 ? launch_stream_f32(p, dense, once, a, s) : h->dtype == KB_BF16 ? launch_stream_bf16(p, dense, once, a, s) : launch_stream_fp8(p, q8, dense, once, a, s);
 }
 
-// kb_query by the whole-store plan: two launches.
-kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k,
-                         int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
+// The tiled scan of split f32 rows needs the queries' scales, which come from 1/|q|, and the plans without a sampling pass have no array
+// for them: they lie in the first place of each query's scores until the launch that writes these.
+__global__ __launch_bounds__(256) void query_inv_kernel(const void *queries, int Q, int d, float *out, int stride)
+{
+    const int row = blockIdx.x * 4 + ((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (row >= Q) return;
+    const float inv = row_inv_norm<KB_F32>(queries, row, d * 4, lane);
+    if (lane == 0) out[(size_t)row * stride] = inv;
+}
+hipError_t give_scales(ScanArgs &a, int32_t k, float *scores_out_dev, hipStream_t s)
+{
+    a.invq = scores_out_dev;
+    a.invq_stride = k;
+    hipLaunchKernelGGL(query_inv_kernel, dim3((unsigned)ceil_div(a.Q, 4)), dim3(256), 0, s, a.queries, a.Q, a.d, scores_out_dev, k);
+    return hipGetLastError();
+}
+
+// kb_query by the whole-store plan: two launches (split f32 rows and the tiled scan: three).
+kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k, int32_t k_out,
+                         bool split, int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
 {
     ScanArgs a;
     memset(&a, 0, sizeof a);
@@ -2397,6 +2521,7 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     a.whole_pair = reinterpret_cast<u32x4 *>(ws + p.off_pair);
     a.whole_groups = p.groups;
     a.whole_fine = p.fine;
+    if (split && !p.stream && give_scales(a, k_out, scores_out_dev, s) != hipSuccess) return KB_ERR_DEVICE;
     const bool timed = h->prof_events && h->prof_used < h->prof_max && h->prof_seen++ % h->prof_stride == h->prof_stride / 2;
     if (timed) {
         scan_timing.start = h->prof_events[2 * h->prof_used];
@@ -2424,21 +2549,26 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     t.stats = reinterpret_cast<uint64_t *>(ws);
     t.n_keys = h->n;
     t.k = k;
+    t.k_out = k_out;
     t.d = h->d;
     t.groups = p.groups;
     t.group_rows = p.group_rows;
     t.tile_rows = p.tk;
     t.tiles = p.stream ? p.st.units : (int32_t)a.n_tiles;
     t.grid = p.grid;
-    const int kt = q8 ? KT_FP8_Q8 : (int)h->dtype;
+    const int kt = q8 ? KT_FP8_Q8 : split ? KB_F32_SPLIT : (int)h->dtype;
     auto *fn = p.stream ? whole_select_for<true>(kt, p.groups) : whole_select_for<false>(kt, p.groups);
-    hipLaunchKernelGGL(fn, dim3(Q), dim3(WHOLE_THREADS), 0, s, t);
+    t.more_lds = split ? restate_lds(Q, k, h->d) : 0;
+    static LdsAllowed allowed[6];
+    if (t.more_lds > 0 && allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed[(p.stream ? 3 : 0) + (p.groups <= 4 * WHOLE_THREADS ? 0 : p.groups <= 8 * WHOLE_THREADS ? 1 : 2)], RESTATE_LDS) != hipSuccess)
+        return KB_ERR_DEVICE;
+    hipLaunchKernelGGL(fn, dim3(Q), dim3(WHOLE_THREADS), t.more_lds, s, t);
     return hipGetLastError() == hipSuccess ? KB_OK : KB_ERR_DEVICE;
 }
 
 // kb_query and kb_query_sampled by the dense plan: two launches, three with the weighted selection (its scan needs 1/|q| and ln(gain)).
-kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_dtype_t q_dtype, int32_t Q, const uint64_t *qmask_dev, int32_t k,
-                         DrawArgs dr, GainArgs ga, int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
+kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_dtype_t q_dtype, int32_t Q, const uint64_t *qmask_dev, int32_t k, int32_t k_out,
+                         bool split, DrawArgs dr, GainArgs ga, int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
 {
     ScanArgs a;
     memset(&a, 0, sizeof a);
@@ -2470,6 +2600,7 @@ kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_
                     u32 + (size_t)a.qpad * (CAND_SEGMENTS + 1), ga, s);
         if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
     }
+    if (split && !p.stream && give_scales(a, k_out, scores_out_dev, s) != hipSuccess) return KB_ERR_DEVICE;
     const bool timed = h->prof_events && h->prof_used < h->prof_max && h->prof_seen++ % h->prof_stride == h->prof_stride / 2;
     if (timed) {
         scan_timing.start = h->prof_events[2 * h->prof_used];
@@ -2487,12 +2618,17 @@ kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_
     t.out_index = indices_out_dev;
     t.out_score = scores_out_dev;
     t.stats = stats;
+    t.keys = h->keys;
+    t.inv_norm = h->inv_norm;
+    t.k_out = k_out;
+    t.more_lds = 0;       // (many queries)
     t.k = k;
     t.d = h->d;
     t.n = (int32_t)h->n;
     t.stride = p.stride;
     t.grid = p.grid;
     if (dr.enabled) launch_dense_select<KB_F32, true>(t, Q, s);        // (the keys are finished)
+    else if (split) launch_dense_select<KB_F32_SPLIT, false>(t, Q, s);
     else if (q_dtype == KB_F32) launch_dense_select<KB_F32, false>(t, Q, s);
     else if (q_dtype == KB_BF16) launch_dense_select<KB_BF16, false>(t, Q, s);
     else launch_dense_select<KB_FP8_E4M3, false>(t, Q, s);
@@ -2504,6 +2640,7 @@ kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_
 size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
 {
     if (!kb || Q < 1 || k < 1 || k > KB_K_MAX) return 0;
+    if (kb->dtype == KB_F32) k = std::min(k + SPLIT_MORE, (int32_t)KB_K_MAX);
     // Every combination of kernels a query on this handle can run, each bounded over all row counts.  The choice depends on
     // the kind of query and, through limits of which a handle's type and batch meet at most one for every kind, on the row count
     // (WIDE128_MIN_ROWS for bf16 rows, stream_keys and SHORT_ROWS_MIN_* for fp8 rows): its two sides are those of 1 and of the capacity.
@@ -2533,7 +2670,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
         const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, f32_square, WHOLE_MAX_GROUPS * 32, WHOLE_MAX_GROUPS * 64, whole_rows};
         for (int64_t n : most) {
             WholePlan wp;
-            if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, AMPLE, &wp)) total = std::max(total, wp.total);
+            if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, false, AMPLE, &wp)) total = std::max(total, wp.total);
         }
         // (the scan with the queries in LDS: never more groups than these)
         if (Q <= 32) total = std::max(total, whole_bytes(Q, (int32_t)std::min<int64_t>(WHOLE_MAX_GROUPS, ceil_div(whole_rows, 16)), &unused));
@@ -2541,7 +2678,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     // the dense plan: grows with the rows
     for (int kind = 0; kind < 4; ++kind) {
         DensePlan dp;
-        if (make_dense_plan(kb, std::min({kb->capacity, DENSE_MAX_ROWS, DENSE_MAX_PAIRS / Q}), Q, k, (kind & 1) != 0, (kind & 2) != 0, &dp))
+        if (make_dense_plan(kb, std::min({kb->capacity, DENSE_MAX_ROWS, DENSE_MAX_PAIRS / Q}), Q, k, (kind & 1) != 0, (kind & 2) != 0, false, &dp))
             total = std::max(total, dp.total);
     }
     return total;
@@ -2559,15 +2696,19 @@ struct Route {
     SmallPlan small;
     int parts;
     size_t bytes;
+    bool split;                 // see split_f32
+    int32_t k;                  // entries that are selected
 };
-kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, size_t workspace_bytes, Route *r)
+kb_status_t choose_route_for(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, bool split, size_t workspace_bytes, Route *r)
 {
-    const auto whole_fits = [&](Thrift thrift) { return make_whole_plan(h, n, Q, k, draw, q8, thrift, &r->whole) && r->whole.total <= workspace_bytes; };
+    r->k = k;
+    r->split = split;
+    const auto whole_fits = [&](Thrift thrift) { return make_whole_plan(h, n, Q, k, draw, q8, split, thrift, &r->whole) && r->whole.total <= workspace_bytes; };
     const bool whole = whole_fits(AMPLE);
     r->parts = small_path_parts(h, n, Q, draw);
     if (r->parts) r->small = make_small_plan(Q, k, r->parts);
     const bool lists = !r->parts || workspace_bytes >= r->small.total;
-    const bool dense = (whole || lists) && make_dense_plan(h, n, Q, k, draw, q8, &r->dense) && r->dense.total <= workspace_bytes;
+    const bool dense = (whole || lists) && make_dense_plan(h, n, Q, k, draw, q8, split, &r->dense) && r->dense.total <= workspace_bytes;
     if (dense && !(whole && !dense_is_better(n, k, r->whole))) {
         r->kind = Route::DENSE;
         r->bytes = !whole && r->parts ? std::max(r->dense.total, r->small.total) : r->dense.total;
@@ -2593,6 +2734,13 @@ kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw
         if (workspace_bytes < r->bytes) return KB_ERR_WORKSPACE;
     }
     return KB_OK;
+}
+kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, size_t workspace_bytes, Route *r)
+{
+    // (a call that brings no more than the f32 instruction takes, runs with it)
+    if (split_f32(h, n, Q, k, draw) &&
+        choose_route_for(h, n, Q, std::min(k + SPLIT_MORE, (int32_t)KB_K_MAX), draw, q8, true, workspace_bytes, r) == KB_OK && r->kind != Route::PARTS) return KB_OK;
+    return choose_route_for(h, n, Q, k, draw, q8, false, workspace_bytes, r);
 }
 
 }  // namespace
@@ -2659,8 +2807,8 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     if (const kb_status_t e = choose_route(kb, kb->n, Q, k, draw, q8, workspace_bytes, &r); e != KB_OK) return e;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     unsigned char *ws = static_cast<unsigned char *>(workspace_dev);
-    if (r.kind == Route::DENSE) return launch_dense(kb, r.dense, queries_dev, q_dtype, Q, qmask_dev, k, dr, ga, indices_out_dev, scores_out_dev, ws, s);
-    if (r.kind == Route::WHOLE) return launch_whole(kb, r.whole, queries_dev, q8, Q, qmask_dev, k, indices_out_dev, scores_out_dev, ws, s);
+    if (r.kind == Route::DENSE) return launch_dense(kb, r.dense, queries_dev, q_dtype, Q, qmask_dev, r.k, k, r.split, dr, ga, indices_out_dev, scores_out_dev, ws, s);
+    if (r.kind == Route::WHOLE) return launch_whole(kb, r.whole, queries_dev, q8, Q, qmask_dev, r.k, k, r.split, indices_out_dev, scores_out_dev, ws, s);
     if (r.kind == Route::PARTS)
         return launch_small(kb, queries_dev, q8, Q, qmask_dev, k, r.parts, reinterpret_cast<uint64_t *>(ws + r.small.off_lists), reinterpret_cast<uint64_t *>(ws),
                             indices_out_dev, scores_out_dev, s);
@@ -2681,9 +2829,9 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     dr.log_gain = ga.log_gain = log_gain;
 
     // Query norms and per-call counters: the threshold kernel sets them when there is a sampling pass on scores;
-    // otherwise (no sampling pass, or the weighted random selection, whose sampling pass needs 1/|q|) this launch does.
-    const bool sampled = kb->n > 0 && p.sample_tiles > 0;
-    if (!sampled || draw) {
+    // otherwise (no sampling pass, or the weighted random selection and split f32 rows, whose sampling pass needs 1/|q|) this launch does.
+    const bool sampled = kb->n > 0 && p.sample_tiles > 0, split = r.split;
+    if (!sampled || draw || split) {
         launch_prep(queries_dev, q_dtype, Q, p.qpad, kb->d, invq, thr64, thrp, cnt, flag, stats, (uint64_t)p.sample_keys, qmask_dev, qmask_pad, p.grid, fb_done, ga, s);
         if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
     }
@@ -2697,6 +2845,7 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         a.qmask = qmask_dev;
         a.qmask_pad = qmask_pad;
         a.invq = invq;
+        a.invq_stride = split ? 1 : 0;
         a.thr64 = thr64;
         a.thrp = thrp;
         a.samp = samp;
@@ -2759,7 +2908,7 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
             if (sgrid > smax && p.sample_family != 4) sgrid = smax;        // (the full-line kernel samples one item per workgroup)
             if (launch_scan(kb->dtype, p.sample_config, p.sample_family, true, (int)sgrid, a, s) != hipSuccess) return KB_ERR_DEVICE;
             const int thr_threads = p.sample_slots > 1024 ? 1024 : p.sample_slots > 512 ? 512 : 256;
-            const size_t thr_lds = sizeof(uint64_t) * (p.sample_slots > k ? p.sample_slots : k) + sizeof(SelectScratch);
+            const size_t thr_lds = sizeof(uint64_t) * (p.sample_slots > r.k ? p.sample_slots : r.k) + sizeof(SelectScratch);
             ThresholdArgs t;
             t.samp = samp;
             t.queries = queries_dev;
@@ -2775,7 +2924,7 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
             t.sample_keys = (uint64_t)p.sample_keys;
             t.slots = p.sample_slots;
             t.group_shift = a.sample_group_shift;
-            t.k = k;
+            t.k = r.k;
             t.Q = Q;
             t.qpad = p.qpad;
             t.d = kb->d;
@@ -2785,10 +2934,11 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
             t.cand_cap = p.cand_cap;
             t.tile_rows = p.sample_tk;
             t.scan = a;
-            static LdsAllowed thr_allowed[8];
-            const int thr_kind = p.once ? (kb->dtype == KB_BF16 ? 4 : 5) + (p.sample_slots > 2048 ? 2 : 0) : draw ? 3 : (int)q_dtype;
+            static LdsAllowed thr_allowed[9];
+            const int thr_kind = split ? 8 : p.once ? (kb->dtype == KB_BF16 ? 4 : 5) + (p.sample_slots > 2048 ? 2 : 0) : draw ? 3 : (int)q_dtype;
             void (*thr_fn)(ThresholdArgs) = p.once ? (kb->dtype == KB_BF16 ? threshold_once<KB_BF16>(p.sample_slots) : threshold_once<KB_FP8_E4M3>(p.sample_slots))
                                           : draw ? &threshold_kernel<KB_F32, true, -1>
+                                          : split ? &threshold_kernel<KB_F32_SPLIT, false, -1>
                                           : q_dtype == KB_F32 ? &threshold_kernel<KB_F32, false, -1>
                                           : q_dtype == KB_BF16 ? &threshold_kernel<KB_BF16, false, -1> : &threshold_kernel<KB_FP8_E4M3, false, -1>;
             if (allow_dynamic_lds(reinterpret_cast<const void *>(thr_fn), thr_allowed[thr_kind], MAX_SAMPLE_SLOTS * 8 + sizeof(SelectScratch)) != hipSuccess)
@@ -2826,7 +2976,8 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     f.out_score = scores_out_dev;
     f.n_keys = kb->n;
     f.d = kb->d;
-    f.k = k;
+    f.k = r.k;
+    f.k_out = k;
     f.cand_cap = p.cand_cap;
     f.draw = dr;
     f.fb_done = fb_done;
@@ -2834,15 +2985,20 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     f.fb_parts = p.fb_parts;
     f.thr64 = thr64;
     f.raw = draw ? 0 : 1;
-    const size_t fin_lds = (size_t)p.cand_cap * 8 + 16 + sizeof(SelectScratch);
-    static LdsAllowed fin_allowed[4];
-    const int fin_kind = q8 ? KT_FP8_Q8 : (int)kb->dtype;
-    const void *fin_fn = fin_kind == KB_F32 ? reinterpret_cast<const void *>(&finalize_kernel<KB_F32>)
+    const size_t fin_base = ((size_t)p.cand_cap * 8 + 16 + sizeof(SelectScratch) + 15) / 16 * 16;
+    f.more_at = (int32_t)fin_base;
+    f.more_lds = split ? std::min(restate_lds(Q, r.k, kb->d), (int)(MAX_CAND_CAP * 8 + RESTATE_LDS / 2 - fin_base)) : 0;
+    const size_t fin_lds = fin_base + f.more_lds;
+    static LdsAllowed fin_allowed[5];
+    const int fin_kind = q8 ? KT_FP8_Q8 : split ? KB_F32_SPLIT : (int)kb->dtype;
+    const void *fin_fn = fin_kind == KB_F32_SPLIT ? reinterpret_cast<const void *>(&finalize_kernel<KB_F32_SPLIT>)
+                       : fin_kind == KB_F32 ? reinterpret_cast<const void *>(&finalize_kernel<KB_F32>)
                        : fin_kind == KB_BF16 ? reinterpret_cast<const void *>(&finalize_kernel<KB_BF16>)
                        : fin_kind == KB_FP8_E4M3 ? reinterpret_cast<const void *>(&finalize_kernel<KB_FP8_E4M3>)
                                                  : reinterpret_cast<const void *>(&finalize_kernel<KT_FP8_Q8>);
-    if (allow_dynamic_lds(fin_fn, fin_allowed[fin_kind], MAX_CAND_CAP * 8 + 16 + sizeof(SelectScratch)) != hipSuccess) return KB_ERR_DEVICE;
+    if (allow_dynamic_lds(fin_fn, fin_allowed[fin_kind], MAX_CAND_CAP * 8 + 16 + sizeof(SelectScratch) + (split ? RESTATE_LDS / 2 : 0)) != hipSuccess) return KB_ERR_DEVICE;
     switch (fin_kind) {
+    case KB_F32_SPLIT: hipLaunchKernelGGL(finalize_kernel<KB_F32_SPLIT>, dim3(Q, p.fb_parts), dim3(256), fin_lds, s, f); break;
     case KB_F32: hipLaunchKernelGGL(finalize_kernel<KB_F32>, dim3(Q, p.fb_parts), dim3(256), fin_lds, s, f); break;
     case KB_BF16: hipLaunchKernelGGL(finalize_kernel<KB_BF16>, dim3(Q, p.fb_parts), dim3(256), fin_lds, s, f); break;
     case KB_FP8_E4M3: hipLaunchKernelGGL(finalize_kernel<KB_FP8_E4M3>, dim3(Q, p.fb_parts), dim3(256), fin_lds, s, f); break;

@@ -29,6 +29,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // Bit reinterpretation of scalars passed BY VALUE.  (__builtin_bit_cast applied directly to a vector
@@ -73,6 +74,26 @@ __device__ inline float final_score(float dot, float inv_k, float inv_q) { retur
 // 1/|k| (which is never negative otherwise; a zero row's 0 becomes -0).
 constexpr uint32_t REMOVED_BIT = 0x80000000u;
 __host__ __device__ inline bool row_removed(float inv_k) { return (as_u32(inv_k) & REMOVED_BIT) != 0; }
+
+// Kernel-side name of f32 rows and queries that go to the matrix cores as two f16 values an element (see Mma<KB_F32_SPLIT>): large calls,
+// see split_f32.
+constexpr int KB_F32_SPLIT = 4;
+// They are scaled by a power of two that brings the row's
+// length to [2^7, 2^8]: the largest f16 value is far away, and what is lost below the smallest one is 2^-33 of the length.  The
+// scale comes from 1/|x| alone, so every kernel has the same; a row without a length (zero, or past the largest float) is taken as zeros.
+__host__ __device__ inline float f32_row_scale(float inv)
+{
+    const uint32_t e = as_u32(inv) & 0x7f800000u;
+    return as_f32(e != 0u ? e + (8u << 23) : 0u);
+}
+// 1/|x| of the scaled row: the same digits, so dot products of scaled rows end in the score of the rows as they are.  (The removed bit stays.)
+__host__ __device__ inline float f32_scaled_inv(float inv)
+{
+    const uint32_t u = as_u32(inv);
+    return as_f32((u & 0x7f800000u) != 0u ? (u & 0x807fffffu) | 119u << 23 : u);
+}
+// 1/|x| as the kernels of a key type use it
+template <int KT> __device__ inline float used_inv(float inv) { return KT == KB_F32_SPLIT ? f32_scaled_inv(inv) : inv; }
 
 // Kernel-side name of "fp8 keys with fp8 queries" where a kernel template is selected by key type: the keys are
 // KB_FP8_E4M3 either way, but both operands go to the fp8 matrix instruction as they are stored.
@@ -194,7 +215,8 @@ struct ScanArgs {
     const void *queries;
     const uint64_t *qmask;    // nullptr when no filter is applied
     const uint64_t *qmask_pad; // [qpad] copy of qmask padded with zero words (library workspace)
-    const float *invq;        // [qpad]
+    const float *invq;        // [qpad]; split f32: query q's is invq[q * invq_stride], q < Q
+    int32_t invq_stride;      // 0: f32 rows are not split
     const uint64_t *thr64;    // [qpad] candidate words below this cannot be in the result
     const float *thrp;        // [qpad] conservative pre-filter on dot * inv_k
     uint64_t *samp;           // sampling pass output [sample tiles][qpad][groups per tile]: see sample_slot_index
@@ -360,6 +382,7 @@ extern thread_local ScanTiming scan_timing;
 
 // Launchers, one translation unit per key dtype.  `sample` selects the sampling epilogue.
 hipError_t launch_scan_f32(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
+hipError_t launch_scan_f32_split(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_bf16(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_fp8(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_sp_bf16(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
@@ -367,6 +390,7 @@ hipError_t launch_scan_wide_bf16(int config, bool sample, int grid, const ScanAr
 hipError_t launch_scan_wide_fp8(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_sp_fp8(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 struct StreamArgs;
+hipError_t launch_stream_f32(const StreamPlan &p, bool dense, bool once, const StreamArgs &a, hipStream_t s);
 hipError_t launch_stream_bf16(const StreamPlan &p, bool dense, bool once, const StreamArgs &a, hipStream_t s);
 hipError_t launch_stream_fp8(const StreamPlan &p, bool q8, bool dense, bool once, const StreamArgs &a, hipStream_t s);
 

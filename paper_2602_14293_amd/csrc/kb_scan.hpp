@@ -37,6 +37,7 @@ template <int KT> struct KeyTraits;
 template <> struct KeyTraits<KB_F32> { static constexpr int KEY_BYTES = 4, QRY_BYTES = 4; };
 template <> struct KeyTraits<KB_BF16> { static constexpr int KEY_BYTES = 2, QRY_BYTES = 2; };
 template <> struct KeyTraits<KB_FP8_E4M3> { static constexpr int KEY_BYTES = 1, QRY_BYTES = 2; };
+template <> struct KeyTraits<KB_F32_SPLIT> { static constexpr int KEY_BYTES = 4, QRY_BYTES = 4; };
 template <> struct KeyTraits<KB_FP8_Q8> { static constexpr int KEY_BYTES = 1, QRY_BYTES = 1; };
 
 // One k-group = 32 bytes of a key row: lane half h owns bytes [16h, 16h+16) of it.
@@ -46,6 +47,7 @@ template <> struct KeyTraits<KB_FP8_Q8> { static constexpr int KEY_BYTES = 1, QR
 //         query bytes [32h, +32) of the group's 64 (two 16-byte pieces).
 // fp8 keys with fp8 queries: one k-group = 64 bytes of a key row and of a query row, one 32x32x64 fp8 MFMA; lane half
 // h owns bytes [32h, 32h+32) of either (two 16-byte pieces), the operand layout of every kernel that takes fp8 queries.
+// f32, split: one k-group = 64 bytes as well, 16 elements; three 32x32x16 f16 MFMAs.
 template <int KT> struct Mma;
 
 template <> struct Mma<KB_BF16> {
@@ -66,6 +68,33 @@ template <> struct Mma<KB_F32> {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(as_f32(a[e]), as_f32(b0[e]), acc, 0, 0, 0);
+    }
+};
+
+// f32, split: an element x of a row scaled by s (see f32_row_scale) is h + l, h the f16 value next to it and l the one next to the rest: 23
+// or 24 bits.  The products h h, h l and l h are exact and added up in f32 (l l, 2^-24 of them, is left out): three matrix instructions of
+// 32 clocks for 16 elements, where v_mfma_f32_32x32x2f32 takes eight of 64.  Against 64 bits the scores are closer than with the f32
+// instruction, whose accumulator is rounded five times as often: 2-norm error 1.2e-7 to 3.0e-7 where that has 1.8e-7 to 4.7e-7 (128 to 1024 elements).
+template <> struct Mma<KB_F32_SPLIT> {
+    struct PrepA {
+        f16x8 h, l;
+    };
+    static __device__ inline PrepA prepare(u32x4 first, u32x4 second, float scale)
+    {
+        PrepA p;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float x = as_f32(e < 4 ? first[e & 3] : second[e & 3]);
+            p.h[e] = (_Float16)__builtin_fmaf(x, scale, 0.f);
+            p.l[e] = (_Float16)__builtin_fmaf(x, scale, -(float)p.h[e]);
+        }
+        return p;
+    }
+    static __device__ inline void run(f32x16 &acc, const PrepA &a, const PrepA &b)
+    {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.l, b.h, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h, b.l, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h, b.h, acc, 0, 0, 0);
     }
 };
 
@@ -139,7 +168,8 @@ struct ScanCfg {
     static constexpr int RBB = RBA * BMUL;
     static constexpr int PPRA = RBA / 16, PPRB = RBB / 16;
     static constexpr bool Q8 = KT == KB_FP8_Q8;
-    static constexpr int KG = RBA / (Q8 ? 64 : 32);
+    static constexpr bool PAIRED = Q8 || KT == KB_F32_SPLIT;        // a k-group is 64 bytes of a row
+    static constexpr int KG = RBA / (PAIRED ? 64 : 32);
     static constexpr int NW = WM * WN, THREADS = 64 * NW;
     static constexpr int IB = TK / WM / 32, JB = TQ / WN / 32;
     static constexpr int A_BYTES = TK * RBA, B_BYTES = TQ * RBB, STAGE_BYTES = A_BYTES + B_BYTES;
@@ -196,6 +226,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
 {
     static_assert(!DENSE || !(SAMPLE || WHOLE), "one of the plans");
     constexpr int TK = C::TK, TQ = C::TQ, RBA = C::RBA, RBB = C::RBB, IB = C::IB, JB = C::JB, NW = C::NW;
+    constexpr bool SPLIT = C::KT == KB_F32_SPLIT;
     constexpr int LA = C::NIA / NW, LB = C::NIB / NW;           // load instructions per wave per chunk
     constexpr int RSTEP_A = NW * 64 / C::PPRA, RSTEP_B = NW * 64 / C::PPRB;   // rows between a wave's instructions
     static_assert(C::NIA % NW == 0 && C::NIB % NW == 0, "every wave issues the same number of loads");
@@ -292,8 +323,8 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
     // ---- fragment addresses (bytes inside a stage) ----------------------------------------------
     const int rowA = wm * (TK / C::WM) + lrow;
     const int rowB = wn * (TQ / C::WN) + lrow;
-    const int baseA = C::Q8 ? (rowA * RBA | (((2 * half) ^ swizzle<C::PPRA>(rowA)) << 4)) : (rowA * RBA | ((half ^ swizzle<C::PPRA>(rowA)) << 4));
-    const int baseB = C::BMUL == 1 && !C::Q8 ? (rowB * RBB | ((half ^ swizzle<C::PPRB>(rowB)) << 4))
+    const int baseA = C::PAIRED ? (rowA * RBA | (((2 * half) ^ swizzle<C::PPRA>(rowA)) << 4)) : (rowA * RBA | ((half ^ swizzle<C::PPRA>(rowA)) << 4));
+    const int baseB = C::BMUL == 1 && !C::PAIRED ? (rowB * RBB | ((half ^ swizzle<C::PPRB>(rowB)) << 4))
                                    : (rowB * RBB | (((2 * half) ^ swizzle<C::PPRB>(rowB)) << 4));
 
     f32x16 acc[IB][JB];
@@ -304,6 +335,39 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[ib][jb][i] = 0.f;
 
+    // split f32: the scales of the wave's rows and queries, asked for with the side data of the item before
+    float key_scale[SPLIT ? IB : 1], query_scale[SPLIT ? JB : 1], next_inv_k[SPLIT ? IB : 1], next_inv_q[SPLIT ? JB : 1];
+    auto ask_scales = [&](int t, int q) {
+#pragma unroll
+        for (int ib = 0; ib < IB; ++ib) {
+            const int rl = rowA + ib * 32;
+            int64_t r = t * tstride * TK + rl;
+            if constexpr (SAMPLE) {
+                int at = rl;
+                asm volatile("" : "+v"(at));
+                r = sample_row<false>(p, sample_tile_run(p, t, TK), t, TK, at);
+            }
+            if constexpr (WHOLE) r = whole_row(t, (int32_t)p.n_tiles, TK, rl);
+            next_inv_k[ib] = p.inv_norm[r < p.n_keys ? r : p.n_keys - 1];
+        }
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb) {
+            const int c = q * TQ + rowB + jb * 32;
+            next_inv_q[jb] = p.invq[(size_t)(c < p.Q ? c : p.Q - 1) * p.invq_stride];
+        }
+    };
+    auto take_scales = [&]() {
+#pragma unroll
+        for (int ib = 0; ib < IB; ++ib) key_scale[ib] = f32_row_scale(next_inv_k[ib]);
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb) query_scale[jb] = f32_row_scale(next_inv_q[jb]);
+    };
+    if constexpr (SPLIT) {
+        if (total > 0) {
+            ask_scales(vb / nqb, vb % nqb);
+            take_scales();
+        }
+    }
     if (total > 0) ld_setup();
 #pragma unroll
     for (int s = 0; s < C::NSTAGE - 1; ++s)
@@ -356,19 +420,51 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 }
                 if (filter) my_qmask = p.qmask[q < p.Q ? q : p.Q - 1];
             }
+            if constexpr (SPLIT) {
+                int t = tile + step_tile, q = qb + step_qb;
+                t += q >= nqb ? 1 : 0;
+                q -= q >= nqb ? nqb : 0;
+                ask_scales(t < p.n_tiles ? t : tile, q);
+            }
         }
 
         // ---- contraction over this chunk --------------------------------------------------------
         {
             const unsigned char *sA = smem + stage * C::STAGE_BYTES;
             const unsigned char *sB = sA + C::A_BYTES;
+            if constexpr (SPLIT) {        // all fragments of the chunk first: one round trip to LDS
+                u32x4 ra[C::KG][IB][2], rb[C::KG][JB][2];
+#pragma unroll
+                for (int kg = 0; kg < C::KG; ++kg) {
+#pragma unroll
+                    for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) ra[kg][ib][e] = *reinterpret_cast<const u32x4 *>(sA + ((baseA ^ (kg << 6) ^ (e << 4)) + ib * 32 * RBA));
+#pragma unroll
+                    for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) rb[kg][jb][e] = *reinterpret_cast<const u32x4 *>(sB + ((baseB ^ (kg << 6) ^ (e << 4)) + jb * 32 * RBB));
+                }
+#pragma unroll
+                for (int kg = 0; kg < C::KG; ++kg) {
+                    typename Mma<C::KT>::PrepA a[IB], b[JB];
+#pragma unroll
+                    for (int ib = 0; ib < IB; ++ib) a[ib] = Mma<C::KT>::prepare(ra[kg][ib][0], ra[kg][ib][1], key_scale[ib]);
+#pragma unroll
+                    for (int jb = 0; jb < JB; ++jb) b[jb] = Mma<C::KT>::prepare(rb[kg][jb][0], rb[kg][jb][1], query_scale[jb]);
+#pragma unroll
+                    for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+                        for (int jb = 0; jb < JB; ++jb) Mma<C::KT>::run(acc[ib][jb], a[ib], b[jb]);
+                }
+            } else {
 #pragma unroll
             for (int kg = 0; kg < C::KG; ++kg) {
                 typename Mma<C::KT>::PrepA a[IB];
                 u32x4 b0[JB], b1[JB];
 #pragma unroll
                 for (int ib = 0; ib < IB; ++ib) {
-                    if constexpr (C::Q8) {
+                    if constexpr (C::PAIRED) {
                         a[ib].lo = *reinterpret_cast<const u32x4 *>(sA + ((baseA ^ (kg << 6)) + ib * 32 * RBA));
                         a[ib].hi = *reinterpret_cast<const u32x4 *>(sA + ((baseA ^ (kg << 6) ^ 16) + ib * 32 * RBA));
                     } else {
@@ -378,7 +474,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 }
 #pragma unroll
                 for (int jb = 0; jb < JB; ++jb) {
-                    if (C::BMUL == 1 && !C::Q8) {
+                    if (C::BMUL == 1 && !C::PAIRED) {
                         b0[jb] = *reinterpret_cast<const u32x4 *>(sB + ((baseB ^ (kg << 5)) + jb * 32 * RBB));
                         b1[jb] = b0[jb];
                     } else {
@@ -390,6 +486,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
                     for (int jb = 0; jb < JB; ++jb) Mma<C::KT>::run(acc[ib][jb], a[ib], b0[jb], b1[jb]);
+            }
             }
         }
         stage = stage + 1 == C::NSTAGE ? 0 : stage + 1;
@@ -404,7 +501,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 }
             }
             if (tid < TK) {
-                aux_invk[tid] = my_invk;
+                aux_invk[tid] = used_inv<C::KT>(my_invk);
                 aux_tag[tid] = my_tag;
                 if constexpr (DRAW) aux_lgain[tid] = my_lgain;
                 if constexpr (SAMPLE) aux_row[tid] = my_row;
@@ -412,7 +509,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
             if (tid < TQ) {
                 aux_qmask[tid] = my_qmask;
                 if constexpr (!WHOLE) {
-                    aux_invq[tid] = my_invq;
+                    aux_invq[tid] = used_inv<C::KT>(my_invq);
                     if constexpr (!SAMPLE) aux_thr64[tid] = my_thr64;
                     reinterpret_cast<float *>(smem + C::OFF_THRP)[tid] = my_thrp;
                 }
@@ -456,6 +553,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
                 qb -= nqb;
                 ++tile;
             }
+            if constexpr (SPLIT) take_scales();
         }
     }
 
@@ -493,7 +591,8 @@ template <class C> hipError_t launch_whole_cfg(int grid, const ScanArgs &a, hipS
 // the scan of the dense plan
 template <class C> hipError_t launch_dense_cfg(int grid, const ScanArgs &a, hipStream_t s)
 {
-    return a.draw.enabled ? launch_scan_variant<C, false, true, false, false, true>(grid, a, s) : launch_scan_variant<C, false, false, false, false, true>(grid, a, s);
+    if constexpr (C::KT == KB_F32_SPLIT) return a.draw.enabled ? hipErrorInvalidValue : launch_scan_variant<C, false, false, false, false, true>(grid, a, s);
+    else return a.draw.enabled ? launch_scan_variant<C, false, true, false, false, true>(grid, a, s) : launch_scan_variant<C, false, false, false, false, true>(grid, a, s);
 }
 
 // configurations of these two plans only: the smallest tiles take both (fp8 queries: the dense one), larger ones the whole-store plan
@@ -518,7 +617,9 @@ template <class C> hipError_t launch_scan_cfg(bool sample, int grid, const ScanA
         if constexpr (C::TQ <= 128 && !(C::KT == KB_BF16 && C::TQ == 128 && C::TK == 128)) return launch_whole_cfg<C>(grid, a, s);
         return hipErrorInvalidValue;
     }
-    if (a.draw.enabled) return sample ? launch_scan_policy<C, true, true, false>(grid, a, s) : launch_scan_policy<C, false, true, false>(grid, a, s);
+    if constexpr (C::KT == KB_F32_SPLIT) {
+        if (a.draw.enabled) return hipErrorInvalidValue;       // (see split_f32)
+    } else if (a.draw.enabled) return sample ? launch_scan_policy<C, true, true, false>(grid, a, s) : launch_scan_policy<C, false, true, false>(grid, a, s);
     return sample ? launch_scan_policy<C, true, false, false>(grid, a, s) : launch_scan_policy<C, false, false, false>(grid, a, s);
 }
 

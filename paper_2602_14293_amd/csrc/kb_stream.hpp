@@ -9,6 +9,7 @@
 #pragma once
 #include "kb_epilogue.hpp"
 #include "kb_internal.hpp"
+#include "kb_norm.hpp"
 #include "kb_scan.hpp"
 
 namespace kbi {
@@ -33,7 +34,8 @@ constexpr int STREAM_LDS = 160 * 1024;
 
 template <int KT_, int TR_, int NST_> struct StreamCfg {
     static constexpr int KT = KT_, TR = TR_, NST = NST_;
-    static constexpr bool PAIRED = KT == KB_FP8_Q8;      // a matrix step takes 64 bytes of a row
+    static constexpr bool SPLIT = KT == KB_F32_SPLIT;
+    static constexpr bool PAIRED = KT == KB_FP8_Q8 || SPLIT;     // a matrix step takes 64 bytes of a row
     static constexpr int STEPS = PAIRED ? 2 : 4;
     static constexpr int KEY_BYTES = KeyTraits<KT>::KEY_BYTES, BMUL = KeyTraits<KT>::QRY_BYTES / KEY_BYTES;
     static constexpr int RB = 128, LOADS = TR * RB / 1024, CHUNK = TR * RB;
@@ -77,6 +79,7 @@ template <class C> struct StreamStep {
 template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) void kb_stream_kernel(StreamArgs p)
 {
     constexpr int TR = C::TR, NST = C::NST, LOADS = C::LOADS, RB = C::RB, STEPS = C::STEPS;
+    constexpr bool SPLIT = C::SPLIT;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void *lds_ptr;
     const int tid = threadIdx.x, lane = tid & 63, lrow = lane & 31, half = lane >> 5;
@@ -149,12 +152,14 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
     if (total > 0) issue();
     // ---- queries to LDS: 16-byte pieces, swizzled over 16 of them by the row (whole rows lie a multiple of 256 bytes apart) ----
     {
+        // (a wavefront takes rows of its own)
         const uint32_t qrow = row_bytes * C::BMUL;
-        const int bytes = nq * p.query_stride;
-        for (int o = wave * 1024; o < bytes; o += nw * 1024) {
-            const int at = o + lane * 16, r = at / p.query_stride, piece = ((at - r * p.query_stride) >> 4) ^ (r & 15);
-            if (r < nq && (uint32_t)piece * 16 < qrow)
-                __builtin_amdgcn_global_load_lds((const void *)(static_cast<const unsigned char *>(p.queries) + (size_t)(q0 + r) * qrow + piece * 16), (lds_ptr)(smem + o), 16, 0, 0);
+        for (int r = wave; r < nq; r += nw) {
+            const unsigned char *from = static_cast<const unsigned char *>(p.queries) + (size_t)(q0 + r) * qrow;
+            for (int o = 0; o < p.query_stride; o += 1024) {
+                const uint32_t at = (uint32_t)((o >> 4) + lane) ^ (uint32_t)(r & 15);
+                if (at * 16 < qrow) __builtin_amdgcn_global_load_lds((const void *)(from + at * 16), (lds_ptr)(smem + r * p.query_stride + o), 16, 0, 0);
+            }
         }
     }
     asm volatile("" ::: "memory");
@@ -163,6 +168,24 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
         if (s < total) issue();
     // the queries and the first piece were asked for before the others
     wait_landed<LOADS, NST - 1>(total - 1);
+    if constexpr (SPLIT) {
+        // The queries are kept as the two f16 values of each element, eight of the one and then eight of the other: each wavefront turns
+        // the rows it has asked for.  (Their lengths are summed up as everywhere, piece by piece.)
+        const int pieces = (int)row_bytes / 16;
+        for (int r = wave; r < nq; r += nw) {
+            unsigned char *row = smem + r * p.query_stride;
+            float sum = 0.f;
+            for (int i = lane; i < pieces; i += 64) sum += piece_sum_squares<KB_F32>(*reinterpret_cast<const u32x4 *>(row + ((i ^ (r & 15)) << 4)));
+            const float scale = f32_row_scale(inv_norm_of(wave_sum(sum)));
+            for (int i = 2 * lane; i < pieces; i += 128) {
+                u32x4 *first = reinterpret_cast<u32x4 *>(row + ((i ^ (r & 15)) << 4)), *second = reinterpret_cast<u32x4 *>(row + (((i | 1) ^ (r & 15)) << 4));
+                const typename Mma<KB_F32_SPLIT>::PrepA x = Mma<KB_F32_SPLIT>::prepare(*first, *second, scale);
+                *first = __builtin_bit_cast(u32x4, x.h);
+                *second = __builtin_bit_cast(u32x4, x.l);
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0());
+    }
     bare_barrier();
     if (total == 0) return;
 
@@ -185,9 +208,24 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
         if constexpr (C::PAIRED || C::BMUL == 2) step[k].b[1] = *reinterpret_cast<const u32x4 *>(sQ + (qk ^ qx ^ 16u));
     };
 
+    // split f32: the scale of the lane's row, and the tile's 1/|k| in LDS as the products have them (once the tile's first piece is there)
+    float key_scale = 1.f;
+    auto scale_tile = [&](int at) {
+        if constexpr (SPLIT) {
+            float *inv = reinterpret_cast<float *>(side0 + at * C::SIDE);
+            const float raw = inv[arow];
+            key_scale = f32_row_scale(raw);
+            if (lane < TR) inv[lane] = f32_scaled_inv(raw);
+        }
+    };
     f32x16 acc[1][1];
     auto multiply = [&](int k) {
-        if constexpr (C::PAIRED) {
+        if constexpr (SPLIT) {
+            typename Mma<C::KT>::PrepA b;
+            b.h = __builtin_bit_cast(f16x8, step[k].b[0]);
+            b.l = __builtin_bit_cast(f16x8, step[k].b[1]);
+            Mma<C::KT>::run(acc[0][0], Mma<C::KT>::prepare(step[k].a[0], step[k].a[1], key_scale), b);
+        } else if constexpr (C::PAIRED) {
             typename Mma<C::KT>::PrepA a;
             a.lo = step[k].a[0];
             a.hi = step[k].a[1];
@@ -200,6 +238,7 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
     for (int i = 0; i < 16; ++i) acc[0][0][i] = 0.f;
 #pragma unroll
     for (int k = 0; k < STEPS; ++k) read_step(k, ring, 0u);
+    scale_tile(0);
     TopThree kept = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), 0u};
     int c = 0, layer = 0, in_group = 0, slot = 0, side_slot = 0;
     // Piece g is in registers when its turn comes, the fragments of piece g + 1 follow step by step, and the loads of piece g + NST
@@ -273,6 +312,7 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
             }
         }
         ++layer;
+        if (g + 1 < total) scale_tile(side_slot);
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[0][0][i] = 0.f;
     }
@@ -288,7 +328,9 @@ template <class C, bool DENSE, bool NT> hipError_t launch_stream_variant(const S
 }
 template <int KT> hipError_t launch_stream(const StreamPlan &p, bool dense, bool once, const StreamArgs &a, hipStream_t s)
 {
-    if (dense) return launch_stream_variant<StreamCfg<KT, 16, STREAM_RING_16>, true, false>(p, a, s);
+    if constexpr (KT == KB_F32_SPLIT) {
+        if (dense) return hipErrorInvalidValue;        // (no such plan)
+    } else if (dense) return launch_stream_variant<StreamCfg<KT, 16, STREAM_RING_16>, true, false>(p, a, s);
     if (once) return launch_stream_variant<StreamCfg<KT, 32, STREAM_RING_32>, false, true>(p, a, s);
     return launch_stream_variant<StreamCfg<KT, 32, STREAM_RING_32>, false, false>(p, a, s);
 }

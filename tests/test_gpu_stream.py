@@ -13,7 +13,7 @@ from paper_2602_14293_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-def _store(kind, N, d, Q, k, seed):
+def _store(kind, N, d, Q, k, seed, powers=False):
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
     rows = torch.randn((N, d), generator=g, device="cuda")
@@ -21,10 +21,14 @@ def _store(kind, N, d, Q, k, seed):
     rows[torch.randint(0, N, (min(N, 60),), generator=g, device="cuda")] = rows[N // 2].clone()   # rows far apart that tie
     if N > 4:
         rows[N - 2] = 0
+    if powers:
+        rows *= torch.exp2(torch.randint(-30, 31, (N, 1), generator=g, device="cuda").float())
     q = rows[torch.randint(0, N, (Q,), generator=g, device="cuda")] + 0.3 * torch.randn((Q, d), generator=g, device="cuda")
     if Q > 2:
         q[1] = rows[N // 3]
         q[2] = 0
+    if powers:
+        q *= torch.exp2(torch.randint(-30, 31, (Q, 1), generator=g, device="cuda").float())
     q = q.to(torch.float32 if kind == "f32" else torch.bfloat16)
     scale = None
     if kind in ("fp8", "q8"):
@@ -63,6 +67,25 @@ def test_the_bits_of_the_pipeline(kind, N, d, Q, k):
         got = kb.query(q, k, mask)
         kb.set_tuning("small_path", 0)
         _same(got, kb.query(q, k, mask), f"{kind} N={N} d={d} Q={Q} k={k} masked={mask is not None}")
+    kb.close()
+
+
+# Calls whose scan takes f32 rows as two f16 values an element: the bits of the f32 instruction (a configuration asked for by name keeps to it),
+# from the whole-store plan and from the pipeline.  Just as many rows as few queries take, and the most, the longest rows and the largest k, the largest k and
+# two query blocks of many, every product written, lists of the pipeline; rows whose lengths are powers of two apart.
+@pytest.mark.parametrize("N,d,Q,k,config", [
+    ((1 << 20) - 1, 64, 7, 32, 1), (524300, 96, 32, 20, 1), (78700, 640, 22, 4, 1), (224800, 224, 31, 32, 1), (105000, 480, 9, 32, 1), (51000, 992, 14, 19, 1),
+    (70001, 512, 120, 12, 2), (16400, 1024, 256, 124, 3), (16400, 1024, 256, 128, 3), (40000, 160, 700, 40, 3), (8200, 2048, 257, 9, 3), (400001, 352, 33, 16, 26)])
+def test_split_f32_rows_have_the_bits_of_the_f32_instruction(N, d, Q, k, config):
+    kb, q, qmask = _store("f32", N, d, Q, k, seed=N + d, powers=True)
+    for mask in (None, qmask):
+        kb.set_tuning("small_path", 1)
+        got = kb.query(q, k, mask)
+        kb.set_tuning("small_path", 0)
+        _same(got, kb.query(q, k, mask), f"pipeline N={N} d={d} Q={Q} k={k} masked={mask is not None}")
+        kb.set_tuning("scan_config", config)
+        _same(got, kb.query(q, k, mask), f"f32 instruction N={N} d={d} Q={Q} k={k} masked={mask is not None}")
+        kb.set_tuning("scan_config", 0)
     kb.close()
 
 
