@@ -2725,10 +2725,17 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     memset(&m, 0, sizeof m);
     bool any = false;
     const int64_t ns[2] = {1, kb->capacity};
+    // (the weighted selection first: with the same kernels its plan has everything that the plain one has)
+    Choice seen[8];
+    int n_seen = 0;
     for (int64_t n : ns)
-        for (int kind = 0; kind < 4; ++kind) {      // plain, weighted random selection, fp8 queries, both
+        for (const int kind : {1, 0, 3, 2}) {      // weighted random selection, plain, both with fp8 queries
             Choice c;
             if (!choose_kernels(kb, n, Q, (kind & 1) != 0, (kind & 2) != 0, AMPLE, &c)) continue;
+            bool again = false;
+            for (int i = 0; i < n_seen; ++i) again = again || (seen[i].config == c.config && seen[i].sample_config == c.sample_config);
+            if (again) continue;
+            seen[n_seen++] = c;
             bound_sizes(kb, c, Q, k, (kind & 1) != 0, m);
             any = true;
         }
