@@ -420,11 +420,12 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
 // for every resident workgroup 1.05 to 1.8 times as fast, with up to 32 queries still 1.0 to 1.3 times at five, with more
 // 0.9 to 1.05 times at four; at ten it loses (0.85 to 1.05).
 // With the queries in LDS (kb_stream.hpp) a tile costs less, and rows dealt one by one leave no group to score again where similar rows are
-// neighbours: up to sixteen tiles a wavefront.  Time of the pipeline over this plan's (runs of 1, 4, 16, 64 and 1000 similar rows, k 4 to 96):
+// neighbours: up to sixteen tiles a wavefront, for up to 64 queries (those past 32: two_blocks_stream).  Time of the pipeline over this plan's (runs of 1, 4, 16, 64 and 1000 similar rows, k 4 to 96):
 //   400,000 x 256 bf16, 8 queries      1.26 to 1.47 (58 us, 44)      400,000 x 1024, 1 query     1.11 to 1.29 (151 us, 135)
 //   700,000 x 512 bf16, 20 queries     1.10 to 1.39 (138 us, 122)    1,000,003 x 1024, 1 query   1.04 to 1.22 (332 us, 317)
 //   1,000,003 x 256 bf16, 32 queries   1.11 to 1.38 (108 us, 95)     900,000 x 512 fp8, 8        1.10 to 1.35 (100 us, 90)
-//   700,000 x 320 fp8 x 8, 20 queries  1.21 to 1.86 (60 us, 49)
+//   700,000 x 320 fp8 x 8, 20 queries  1.21 to 1.86 (60 us, 49)     320,000 x 128 bf16, 64         1.33 to 2.10 (47 us, 34)
+//   1,000,003 x 256 bf16, 40 queries   1.16 to 1.50 (115 us, 99)    700,000 x 512 fp8, 48          1.45 to 1.62 (133 us, 91)
 constexpr int64_t WHOLE_MAX_ROWS_STREAM = (1 << 20) - 1;
 constexpr int64_t WHOLE_MAX_ROWS_FEW = 5 * 128 * 2 * DEVICE_CUS, WHOLE_MAX_ROWS = 3 * 128 * 2 * DEVICE_CUS;     // up to 32 queries; up to 128
 // More than 128 queries: every product costs the epilogue the same, while the pipeline's scan gets better with larger query
@@ -444,7 +445,7 @@ constexpr int WHOLE_MAX_QUERIES = 4096;
 // (fp8 rows with bf16 queries 1.10 and more at 2^25 products of up to 16,384 elements, f32 1.03 and more)
 int64_t whole_max_rows(const kb *h, int32_t Q, bool q8)
 {
-    if (Q <= 32) return WHOLE_MAX_ROWS_STREAM;
+    if (Q <= 64) return WHOLE_MAX_ROWS_STREAM;
     if (Q <= 128) return WHOLE_MAX_ROWS;
     const int64_t columns = h->dtype == KB_BF16 ? ceil_div(Q, 128) * 128 : Q;
     int64_t pairs = (int64_t)1 << (h->dtype == KB_BF16 ? 24 : h->dtype == KB_F32 ? 26 : 25);
@@ -475,38 +476,58 @@ bool split_f32(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw)
 }
 // The scan with the queries in LDS (kb_stream.hpp), where they fit beside the rings of four wavefronts and up.
 // `most_groups`: no more groups than that.
+// Batches of 33 to 64 queries (a wavefront multiplies its rows with two blocks of them) against the tiled kernel's plans: the whole-store
+// plan up to WHOLE_MAX_ROWS, the pipeline past it.  us a call, tiled | this:
+//   fp8 rows, bf16 queries   5000 x 256 14.4 | 12.0    17,000 x 768 19.5 | 15.9    90,000 x 512 32.4 | 26.5    131,000 x 768 49.7 | 44.1
+//                            200,000 x 512 60.5 | 36.9    700,000 x 512 135 | 105    1,000,000 x 64 55.0 | 63.2, x 256 109 | 95.1
+//   fp8 rows, fp8 queries    30,000 x 768 15.5 | 17.2    120,000 x 256 19.5 | 20.8    140,000 x 768 43.0 | 36.6    200,000 x 512 50.1 | 34.7
+//                            320,000 x 128 36.3 | 35.1   420,000 x 128 32.3 | 33.7    700,000 x 512 107 | 85.6    1,000,000 x 768 187 | 138, x 64 44.8 | 59.9
+//   bf16                     30,000 x 768 18.8 | 24.1    45,000 x 256 15.8 | 15.5     90,000 x 512 32.8 | 31.4    120,000 x 256 25.9 | 24.0
+//                            131,000 x 768, five wavefronts 56.5 | 57.9               200,000 x 512 69.0 | 52.5    420,000 x 128 51.0 | 39.4    1,000,000 x 256 119 | 109
+// What loses: tiles so few that the tiled kernel has more wavefronts a compute unit; rows so short that the search of the products is what takes the
+// time in stores of many.  (In between tiled fp8 x fp8 scans need no conversions, and the pipeline they give way to begins at 131,072 rows.)
+bool two_blocks_stream(const kb *h, int64_t n, bool q8, int32_t waves_per_block)
+{
+    if (h->dtype == KB_BF16) return n > WHOLE_MAX_ROWS || (n >= 32 * 8 * DEVICE_CUS && waves_per_block >= 7);
+    if (n > WHOLE_MAX_ROWS_FEW && h->d < (q8 ? 256 : 128)) return false;
+    return !q8 || n > WHOLE_MAX_GROUPS * 32;
+}
 bool make_stream_plan(const kb *h, int64_t n, int32_t Q, bool q8, bool split, bool dense, int64_t most_groups, StreamPlan *out)
 {
-    if ((h->dtype == KB_F32 && (dense || !split)) || (!dense && Q > 32)) return false;
+    if ((h->dtype == KB_F32 && (dense || !split || Q > 32)) || (!dense && Q > 64)) return false;
     StreamPlan p;
+    p.tq = dense || Q <= 32 ? 32 : 64;
     const int64_t row_bytes = (int64_t)h->d * key_bytes(h->dtype), pieces = ceil_div(row_bytes, 128);
     const int64_t query_bytes = row_bytes * (h->dtype == KB_FP8_E4M3 && !q8 ? 2 : 1);
-    const int64_t stride = ceil_div(query_bytes, 256) * 256, resident = std::min<int64_t>(Q, 32) * stride;
-    p.nqb = (int32_t)ceil_div(Q, 32);
+    const int64_t stride = ceil_div(query_bytes, 256) * 256, resident = std::min<int64_t>(Q, p.tq) * stride;
+    p.nqb = (int32_t)ceil_div(Q, p.tq);
     p.blocks = DEVICE_CUS / p.nqb < 1 ? 1 : DEVICE_CUS / p.nqb;
     p.tr = dense ? 16 : 32;
     p.units = (int32_t)ceil_div(n, p.tr);
     if (p.blocks > p.units) p.blocks = p.units;
     p.pieces_in_ring = p.tr == 16 ? STREAM_RING_16 : STREAM_RING_32;
     p.side_slots = (int32_t)(1 + ceil_div(p.pieces_in_ring, pieces));       // (a piece is asked for that many before its turn)
-    for (p.waves_per_block = 8;; --p.waves_per_block) {
-        if (p.waves_per_block < 4) return false;
-        const int64_t lds = resident + (int64_t)p.waves_per_block * (p.pieces_in_ring * p.tr * 128 + p.side_slots * p.tr * 12) + 256;
-        p.lds = (int32_t)lds;
-        if (lds <= STREAM_LDS) break;
-    }
     p.query_stride = (int32_t)stride;
     // rows one by one or in runs of four (the store's neighbours then share fewer of a wavefront's 128-byte pieces, at most a group of them
     // has to be scored again for each run of similar rows): in us, one by one | in runs of four, 700,000 x 128 bf16 rows 53.3 | 48.0 (start of
     // a group's rescoring 65 to 107), 200,000 x 256 32.0 | 31.1, 60,000 x 768 25.5 | 25.0, 300,000 x 768 84.8 | 84.3, 16,000 x 512 equal.  Stores past
     // WHOLE_MAX_ROWS_FEW, whose groups are up to 256 rows, take them one by one: 400,000 x 1024 rows in runs of 16, k = 24 251 us in runs of four, 135.
-    p.run_shift = n > WHOLE_MAX_ROWS_FEW || n <= WHOLE_SMALL_TILE_ROWS ? 0 : 2;
-    p.waves = (int32_t)std::min<int64_t>({p.units, (int64_t)p.blocks * p.waves_per_block, most_groups});
-    const int64_t layers = ceil_div(p.units, p.waves), room = dense ? layers : std::max<int64_t>(1, most_groups / p.waves);
-    p.per_group = (int32_t)ceil_div(layers, room);
-    if (!dense && p.per_group * p.tr > 256) return false;
-    *out = p;
-    return true;
+    // Two blocks of queries: past 131,072 rows, whose groups are two tiles or more (Q 50, 200,000 x 512 in runs of 16, k = 32 62 us in
+    // the pipeline, 81 with runs of four, 46 one by one; rows that resemble nobody 47 and 47).
+    p.run_shift = n > (Q <= 32 ? WHOLE_MAX_ROWS_FEW : WHOLE_MAX_GROUPS * 32) || n <= WHOLE_SMALL_TILE_ROWS ? 0 : 2;
+    // (the most wavefronts whose rings have room and whose groups come out at no more than 256 rows)
+    for (p.waves_per_block = 8; p.waves_per_block >= 4; --p.waves_per_block) {
+        const int64_t lds = resident + (int64_t)p.waves_per_block * (p.pieces_in_ring * p.tr * 128 + p.side_slots * p.tr * 12) + 256;
+        if (lds > STREAM_LDS) continue;
+        p.lds = (int32_t)lds;
+        p.waves = (int32_t)std::min<int64_t>({p.units, (int64_t)p.blocks * p.waves_per_block, most_groups});
+        const int64_t layers = ceil_div(p.units, p.waves), room = dense ? layers : std::max<int64_t>(1, most_groups / p.waves);
+        p.per_group = (int32_t)ceil_div(layers, room);
+        if (!dense && p.per_group * p.tr > 256) continue;
+        *out = p;
+        return dense || Q <= 32 || two_blocks_stream(h, n, q8, p.waves_per_block);
+    }
+    return false;
 }
 int stream_groups(const StreamPlan &p)
 {
@@ -527,7 +548,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     const int32_t rule_k = split ? std::max(1, k - SPLIT_MORE) : k;
     WholePlan p;
     p.stream = make_stream_plan(h, n, Q, q8, split, false, thrift == LEAST ? ceil_div(n, 128) : WHOLE_MAX_GROUPS, &p.st);
-    if (!p.stream && Q <= 32 && n > WHOLE_MAX_ROWS_FEW) return false;
+    if (!p.stream && n > (Q <= 32 ? WHOLE_MAX_ROWS_FEW : WHOLE_MAX_ROWS)) return false;
     if (q8) p.config = Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
     else if (h->dtype == KB_BF16) p.config = Q <= 32 ? 1 : Q <= 64 ? (n >= 128 * 2 * DEVICE_CUS ? 14 : 12) : n >= 128 * 2 * DEVICE_CUS && h->d >= 512 ? 21 : 16;    // (14: once every resident workgroup gets a tile)
     else if (h->dtype == KB_F32 && Q > 32 && thrift != LEAST) p.config = Q <= 64 || ceil_div(n, 128) * ceil_div(Q, 128) <= DEVICE_CUS ? F32_SQUARE_CONFIG : 2;
@@ -552,7 +573,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     p.k_groups = p.groups;
     if (p.stream) {
         p.tk = p.st.tr;
-        p.tq = 32;
+        p.tq = p.st.tq;
         p.nqb = 1;
         p.fine = 0;
         p.group_rows = p.st.per_group * p.st.tr;
@@ -2751,7 +2772,9 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     for (int q8 = 0; q8 < 2; ++q8) {
         const int64_t whole_rows = std::min(kb->capacity, whole_max_rows(kb, Q, q8 != 0));
         const int64_t f32_square = DEVICE_CUS / ceil_div(Q, 128) * 128;        // rows up to which f32 batches past 64 queries have the lower tiles
-        const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, f32_square, WHOLE_MAX_GROUPS * 32, WHOLE_MAX_GROUPS * 64, whole_rows};
+        // (7, 6, 5 wavefronts a compute unit: the last rows that those of the scan with the queries in LDS take a tile at a time; then groups of two)
+        const int64_t most[] = {WHOLE_SMALL_TILE_ROWS, f32_square, WHOLE_MAX_GROUPS * 32, WHOLE_MAX_GROUPS * 64, whole_rows,
+                                2 * 7 * DEVICE_CUS * 32, 2 * 6 * DEVICE_CUS * 32, 3 * 5 * DEVICE_CUS * 32};
         for (int64_t n : most) {
             WholePlan wp;
             if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, false, AMPLE, &wp)) total = std::max(total, wp.total);

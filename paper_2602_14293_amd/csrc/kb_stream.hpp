@@ -1,11 +1,16 @@
-// The scan of the whole-store and the dense plan for batches of up to 32 queries (gfx950 only): the queries stay in LDS, every
+// The scan of the whole-store and the dense plan for batches of up to 32 or 64 queries (gfx950 only): the queries stay in LDS, every
 // wavefront streams rows of its own.
 //
 // Such a call reads the rows once and does little with them, so it is as long as the stream of the rows, its start and what
-// interrupts it.  One workgroup a compute unit holds the queries (up to 32, whole rows of them); each of its wavefronts takes tiles
+// interrupts it.  One workgroup a compute unit holds the queries (whole rows of them); each of its wavefronts takes tiles
 // of 16 or 32 rows through a private ring of 128-byte pieces of every row.  No wavefront waits for another once the queries are
 // there, the row's tags and 1/|k| come with the stream, and while one wavefront searches its products the others' loads go on.
 // The tiled kernel meets a barrier every piece, reads the queries again for every tile and joins its wavefronts' groups through LDS.
+// A call with the tiled kernel's plan | with this one, us (bytes of rows over the second: TB/s):
+//   1,000,003 x 1024 bf16 rows, 1 query, masked    322 | 305 (6.7)     200,000 x 512 bf16, 64 queries    69.0 | 52.5 (3.9)
+//   300,007 x 384 f32 rows (split), 20 queries    97.2 | 89.6 (5.1)    200,000 x 512 fp8, 64 queries     60.5 | 36.9 (2.8)
+// What is left: the launches and the selection (about 12 us), the first rows' way in (2), and with many queries or short rows the
+// search of the products, 1 us for 32 rows and 32 queries of each wavefront.
 #pragma once
 #include "kb_epilogue.hpp"
 #include "kb_internal.hpp"
@@ -32,8 +37,9 @@ struct StreamArgs {
 constexpr int STREAM_RING_16 = 4, STREAM_RING_32 = 3;     // pieces in a wavefront's ring, by the rows of a tile
 constexpr int STREAM_LDS = 160 * 1024;
 
-template <int KT_, int TR_, int NST_> struct StreamCfg {
+template <int KT_, int TR_, int NST_, int NQ_> struct StreamCfg {
     static constexpr int KT = KT_, TR = TR_, NST = NST_;
+    static constexpr int NQ = NQ_, TQ = NQ * 32;     // blocks of 32 queries that a wavefront multiplies its rows with
     static constexpr bool SPLIT = KT == KB_F32_SPLIT;
     static constexpr bool PAIRED = KT == KB_FP8_Q8 || SPLIT;     // a matrix step takes 64 bytes of a row
     static constexpr int STEPS = PAIRED ? 2 : 4;
@@ -73,19 +79,19 @@ template <int LOADS, int MOST> __device__ inline void wait_landed(int younger)
 
 // The 16-byte fragments of one matrix step: 32 bytes of a row (fp8 x fp8 and f32: 64).
 template <class C> struct StreamStep {
-    u32x4 a[C::PAIRED ? 2 : 1], b[C::PAIRED || C::BMUL == 2 ? 2 : 1];
+    u32x4 a[C::PAIRED ? 2 : 1], b[C::NQ][C::PAIRED || C::BMUL == 2 ? 2 : 1];
 };
 
 template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) void kb_stream_kernel(StreamArgs p)
 {
-    constexpr int TR = C::TR, NST = C::NST, LOADS = C::LOADS, RB = C::RB, STEPS = C::STEPS;
+    constexpr int TR = C::TR, NST = C::NST, NQ = C::NQ, TQ = C::TQ, LOADS = C::LOADS, RB = C::RB, STEPS = C::STEPS;
     constexpr bool SPLIT = C::SPLIT;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void *lds_ptr;
     const int tid = threadIdx.x, lane = tid & 63, lrow = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)blockDim.x >> 6;
-    const int qb = DENSE ? blockIdx.x / p.blocks : 0, block = DENSE ? blockIdx.x % p.blocks : blockIdx.x, q0 = qb * 32;
-    const int nq = p.Q - q0 < 32 ? p.Q - q0 : 32;
+    const int qb = DENSE ? blockIdx.x / p.blocks : 0, block = DENSE ? blockIdx.x % p.blocks : blockIdx.x, q0 = qb * TQ;
+    const int nq = p.Q - q0 < TQ ? p.Q - q0 : TQ;
     // neighbouring tiles on different compute units of one XCD: their rows' tags and lengths share cache lines
     const int rank = (p.blocks & 7) == 0 ? (block & 7) * (p.blocks >> 3) + (block >> 3) : block;
     const int w = wave * p.blocks + rank;
@@ -95,7 +101,7 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
     const bool odd_tail = C::KEY_BYTES == 1 && (row_bytes & (RB - 1)) != 0;     // the last piece is half a line
     const int total = my_tiles * NC;
     const bool filter = p.qmask != nullptr;
-    const int resident = (p.Q < 32 ? p.Q : 32) * p.query_stride;
+    const int resident = (p.Q < TQ ? p.Q : TQ) * p.query_stride;
 
     // ---- the wavefront's stream ----
     unsigned char *ring = smem + resident + wave * (NST * C::CHUNK);
@@ -189,23 +195,32 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
     bare_barrier();
     if (total == 0) return;
 
-    const int qcol = q0 + lrow < p.Q ? lrow : nq - 1;                    // padding columns repeat the last query
-    uint64_t qm = 0;
-    if (filter) {
-        qm = p.qmask[q0 + qcol];
-        asm volatile("" : "+v"(qm));        // (waited for here, not between the pieces)
+    uint64_t qm[NQ];
+    const unsigned char *sQ[NQ];
+    uint32_t qx[NQ];
+#pragma unroll
+    for (int jb = 0; jb < NQ; ++jb) {
+        const int qcol = q0 + jb * 32 + lrow < p.Q ? jb * 32 + lrow : nq - 1;        // padding columns repeat the last query
+        qm[jb] = 0;
+        if (filter) {
+            qm[jb] = p.qmask[q0 + qcol];
+            asm volatile("" : "+v"(qm[jb]));        // (waited for here, not between the pieces)
+        }
+        sQ[jb] = smem + qcol * p.query_stride;
+        qx[jb] = (uint32_t)(((C::PAIRED || C::BMUL == 2 ? 2 * half : half) ^ (qcol & 15)) << 4);
     }
-    const unsigned char *sQ = smem + qcol * p.query_stride;
     const int arow = lrow & (TR - 1);
-    const uint32_t qx = (uint32_t)(((C::PAIRED || C::BMUL == 2 ? 2 * half : half) ^ (qcol & 15)) << 4);
     const uint32_t ax = (uint32_t)(arow * RB) | (uint32_t)(((C::PAIRED ? 2 * half : half) ^ swizzle<8>(arow)) << 4);
     StreamStep<C> step[STEPS];
     auto read_step = [&](int k, const unsigned char *sA, uint32_t qc) {      // step k of the piece at sA, whose query bytes begin at qc
         const uint32_t ak = (uint32_t)(k * (RB / STEPS)), qk = qc + (uint32_t)(k * (RB / STEPS) * C::BMUL);
         step[k].a[0] = *reinterpret_cast<const u32x4 *>(sA + (ax ^ ak));
         if constexpr (C::PAIRED) step[k].a[1] = *reinterpret_cast<const u32x4 *>(sA + (ax ^ ak ^ 16u));
-        step[k].b[0] = *reinterpret_cast<const u32x4 *>(sQ + (qk ^ qx));
-        if constexpr (C::PAIRED || C::BMUL == 2) step[k].b[1] = *reinterpret_cast<const u32x4 *>(sQ + (qk ^ qx ^ 16u));
+#pragma unroll
+        for (int jb = 0; jb < NQ; ++jb) {
+            step[k].b[jb][0] = *reinterpret_cast<const u32x4 *>(sQ[jb] + (qk ^ qx[jb]));
+            if constexpr (C::PAIRED || C::BMUL == 2) step[k].b[jb][1] = *reinterpret_cast<const u32x4 *>(sQ[jb] + (qk ^ qx[jb] ^ 16u));
+        }
     };
 
     // split f32: the scale of the lane's row, and the tile's 1/|k| in LDS as the products have them (once the tile's first piece is there)
@@ -218,28 +233,36 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
             if (lane < TR) inv[lane] = f32_scaled_inv(raw);
         }
     };
-    f32x16 acc[1][1];
+    f32x16 acc[1][NQ];
     auto multiply = [&](int k) {
-        if constexpr (SPLIT) {
-            typename Mma<C::KT>::PrepA b;
-            b.h = __builtin_bit_cast(f16x8, step[k].b[0]);
-            b.l = __builtin_bit_cast(f16x8, step[k].b[1]);
-            Mma<C::KT>::run(acc[0][0], Mma<C::KT>::prepare(step[k].a[0], step[k].a[1], key_scale), b);
-        } else if constexpr (C::PAIRED) {
-            typename Mma<C::KT>::PrepA a;
-            a.lo = step[k].a[0];
-            a.hi = step[k].a[1];
-            Mma<C::KT>::run(acc[0][0], a, step[k].b[0], step[k].b[1]);
-        } else {
-            Mma<C::KT>::run(acc[0][0], Mma<C::KT>::prepare(step[k].a[0]), step[k].b[0], step[k].b[C::BMUL - 1]);
+#pragma unroll
+        for (int jb = 0; jb < NQ; ++jb) {
+            if constexpr (SPLIT) {
+                typename Mma<C::KT>::PrepA b;
+                b.h = __builtin_bit_cast(f16x8, step[k].b[jb][0]);
+                b.l = __builtin_bit_cast(f16x8, step[k].b[jb][1]);
+                Mma<C::KT>::run(acc[0][jb], Mma<C::KT>::prepare(step[k].a[0], step[k].a[1], key_scale), b);
+            } else if constexpr (C::PAIRED) {
+                typename Mma<C::KT>::PrepA a;
+                a.lo = step[k].a[0];
+                a.hi = step[k].a[1];
+                Mma<C::KT>::run(acc[0][jb], a, step[k].b[jb][0], step[k].b[jb][1]);
+            } else {
+                Mma<C::KT>::run(acc[0][jb], Mma<C::KT>::prepare(step[k].a[0]), step[k].b[jb][0], step[k].b[jb][C::BMUL - 1]);
+            }
         }
     };
+    auto clear = [&]() {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[0][0][i] = 0.f;
+        for (int jb = 0; jb < NQ; ++jb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][jb][i] = 0.f;
+    };
+    clear();
 #pragma unroll
     for (int k = 0; k < STEPS; ++k) read_step(k, ring, 0u);
     scale_tile(0);
-    TopThree kept = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), 0u};
+    TopThree kept[NQ];        // (of the group, once it has a tile)
     int c = 0, layer = 0, in_group = 0, slot = 0, side_slot = 0;
     // Piece g is in registers when its turn comes, the fragments of piece g + 1 follow step by step, and the loads of piece g + NST
     // go into the slot that piece g has left, one after every matrix instruction: none of the three waits for another.
@@ -283,38 +306,41 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
                 f32x4 v;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const bool ok = row0 + rl + e < p.n && !row_removed(ik[e]) && (!filter || (sd.tag[rl + e] & qm) != 0);
+                    const bool ok = row0 + rl + e < p.n && !row_removed(ik[e]) && (!filter || (sd.tag[rl + e] & qm[0]) != 0);
                     v[e] = ok ? acc[0][0][4 * run + e] * ik[e] : -__builtin_inff();
                 }
                 if (q0 + lrow < p.Q) *reinterpret_cast<f32x4 *>(p.best + (size_t)(q0 + lrow) * p.groups + row0 + rl) = v;
             }
         } else {
             const uint32_t dead = (uint32_t)__builtin_amdgcn_ballot_w64(lane >= TR || row_removed(sd.invk[lane & (TR - 1)]) || row_of(layer, lane & (TR - 1)) >= p.n);
-            TopThree t = whole_column<1, 1>(acc, 0, sd, filter, qm, 0, half, dead);
-            t = join(t, across_halves(t));
-            if (__builtin_expect(unclear(t), 0)) {
-                t = whole_column_in_order<NATURAL_ORDER, 1, 1>(acc, 0, sd, filter, qm, 0, half, dead);
-                t = join_in_order<NATURAL_ORDER>(t, across_halves(t));
-            }
-            if (in_group > 0) {
-                const uint32_t place0 = (uint32_t)(in_group * TR);
-                t.rows += place0 | place0 << 8 | ((t.rows >> 16 & WHOLE_THIRD) != 0 ? place0 << 16 : 0u);
-                const TopThree both = join(kept, t);
-                kept = __builtin_expect(unclear(both), 0) ? join_in_order<NATURAL_ORDER>(kept, t) : both;
-            } else kept = t;
-            if (++in_group == p.per_group || g + 1 == total) {
-                if (half == 0 && q0 + lrow < p.Q) {
-                    const size_t at = (size_t)(q0 + lrow) * p.groups + (uint32_t)(layer / p.per_group) * (uint32_t)p.waves + (uint32_t)w;
-                    p.best[at] = kept.first;
-                    p.pair[at] = u32x4{as_u32(kept.second), as_u32(kept.third), kept.rows, 0u};
+            const uint32_t place0 = (uint32_t)(in_group * TR);
+            const bool ends = in_group + 1 == p.per_group || g + 1 == total;
+            const size_t group = (size_t)(layer / p.per_group) * (uint32_t)p.waves + (uint32_t)w;
+#pragma unroll
+            for (int jb = 0; jb < NQ; ++jb) {
+                TopThree t = whole_column<1, NQ>(acc, jb, sd, filter, qm[jb], 0, half, dead);
+                t = join(t, across_halves(t));
+                if (__builtin_expect(unclear(t), 0)) {
+                    t = whole_column_in_order<NATURAL_ORDER, 1, NQ>(acc, jb, sd, filter, qm[jb], 0, half, dead);
+                    t = join_in_order<NATURAL_ORDER>(t, across_halves(t));
                 }
-                in_group = 0;
+                if (in_group > 0) {
+                    t.rows += place0 | place0 << 8 | ((t.rows >> 16 & WHOLE_THIRD) != 0 ? place0 << 16 : 0u);
+                    const TopThree both = join(kept[jb], t);
+                    kept[jb] = __builtin_expect(unclear(both), 0) ? join_in_order<NATURAL_ORDER>(kept[jb], t) : both;
+                } else kept[jb] = t;
+                const int query = q0 + jb * 32 + lrow;
+                if (ends && half == 0 && query < p.Q) {
+                    const size_t at = (size_t)query * p.groups + group;
+                    p.best[at] = kept[jb].first;
+                    p.pair[at] = u32x4{as_u32(kept[jb].second), as_u32(kept[jb].third), kept[jb].rows, 0u};
+                }
             }
+            in_group = ends ? 0 : in_group + 1;
         }
         ++layer;
         if (g + 1 < total) scale_tile(side_slot);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[0][0][i] = 0.f;
+        clear();
     }
 }
 
@@ -329,9 +355,15 @@ template <class C, bool DENSE, bool NT> hipError_t launch_stream_variant(const S
 template <int KT> hipError_t launch_stream(const StreamPlan &p, bool dense, bool once, const StreamArgs &a, hipStream_t s)
 {
     if constexpr (KT == KB_F32_SPLIT) {
-        if (dense) return hipErrorInvalidValue;        // (no such plan)
-    } else if (dense) return launch_stream_variant<StreamCfg<KT, 16, STREAM_RING_16>, true, false>(p, a, s);
-    if (once) return launch_stream_variant<StreamCfg<KT, 32, STREAM_RING_32>, false, true>(p, a, s);
-    return launch_stream_variant<StreamCfg<KT, 32, STREAM_RING_32>, false, false>(p, a, s);
+        if (dense || p.tq != 32) return hipErrorInvalidValue;        // (no such plan)
+    } else {
+        if (dense) return launch_stream_variant<StreamCfg<KT, 16, STREAM_RING_16, 1>, true, false>(p, a, s);
+        if (p.tq == 64) {
+            if (once) return launch_stream_variant<StreamCfg<KT, 32, STREAM_RING_32, 2>, false, true>(p, a, s);
+            return launch_stream_variant<StreamCfg<KT, 32, STREAM_RING_32, 2>, false, false>(p, a, s);
+        }
+    }
+    if (once) return launch_stream_variant<StreamCfg<KT, 32, STREAM_RING_32, 1>, false, true>(p, a, s);
+    return launch_stream_variant<StreamCfg<KT, 32, STREAM_RING_32, 1>, false, false>(p, a, s);
 }
 }  // namespace kbi

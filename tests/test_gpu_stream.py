@@ -1,4 +1,4 @@
-"""The scan that keeps up to 32 queries in LDS (whole-store and dense plan): the same bits as the scan pipeline at the sizes where its
+"""The scan that keeps up to 64 queries in LDS (whole-store and dense plan): the same bits as the scan pipeline at the sizes where its
 tiles, layers and groups change, for every type of keys and queries; the plan with few groups that a call with little memory gets."""
 import ctypes
 
@@ -59,7 +59,11 @@ def _same(a, b, what):
     ("bf16", 196700, 64, 9, 10), ("bf16", 327681, 64, 32, 16), ("bf16", (1 << 20) - 1, 64, 3, 90), ("bf16", 1 << 20, 64, 3, 90),
     ("bf16", 3000, 2048, 30, 7), ("bf16", 40000, 1536, 32, 7), ("bf16", 9000, 4096, 12, 3), ("bf16", 700, 64, 200, 9),
     ("fp8", 33, 64, 2, 8), ("fp8", 4096, 320, 32, 16), ("fp8", 20000, 64, 32, 8), ("fp8", 70001, 192, 17, 20), ("fp8", 400001, 64, 32, 24), ("fp8", 1000, 960, 100, 3),
-    ("q8", 33, 64, 2, 8), ("q8", 4096, 320, 32, 16), ("q8", 20000, 64, 32, 8), ("q8", 70001, 192, 17, 20), ("q8", 400001, 64, 32, 24), ("q8", 1000, 960, 100, 3)])
+    ("q8", 33, 64, 2, 8), ("q8", 4096, 320, 32, 16), ("q8", 20000, 64, 32, 8), ("q8", 70001, 192, 17, 20), ("q8", 400001, 64, 32, 24), ("q8", 1000, 960, 100, 3),
+    # two blocks of queries: one of a single query, one that is short, a full one; both ends of the sizes that take them
+    ("bf16", 65535, 64, 64, 5), ("bf16", 65536, 512, 33, 5), ("bf16", 131073, 64, 47, 9), ("bf16", 196608, 192, 50, 4), ("bf16", 196609, 704, 64, 3), ("bf16", (1 << 20) - 1, 64, 40, 24),
+    ("fp8", 100, 64, 64, 3), ("fp8", 5000, 320, 33, 5), ("fp8", 131073, 64, 63, 9), ("fp8", 30001, 768, 64, 3), ("fp8", 327681, 128, 34, 12), ("fp8", 400001, 704, 64, 30),
+    ("q8", 131072, 64, 63, 9), ("q8", 131073, 64, 63, 9), ("q8", 150001, 1344, 64, 3), ("q8", 400001, 256, 41, 30)])
 def test_the_bits_of_the_pipeline(kind, N, d, Q, k):
     kb, q, qmask = _store(kind, N, d, Q, k, seed=N + d)
     for mask in (None, qmask):
