@@ -508,13 +508,6 @@ bool make_stream_plan(const kb *h, int64_t n, int32_t Q, bool q8, bool split, bo
     p.pieces_in_ring = p.tr == 16 ? STREAM_RING_16 : STREAM_RING_32;
     p.side_slots = (int32_t)(1 + ceil_div(p.pieces_in_ring, pieces));       // (a piece is asked for that many before its turn)
     p.query_stride = (int32_t)stride;
-    // rows one by one or in runs of four (the store's neighbours then share fewer of a wavefront's 128-byte pieces, at most a group of them
-    // has to be scored again for each run of similar rows): in us, one by one | in runs of four, 700,000 x 128 bf16 rows 53.3 | 48.0 (start of
-    // a group's rescoring 65 to 107), 200,000 x 256 32.0 | 31.1, 60,000 x 768 25.5 | 25.0, 300,000 x 768 84.8 | 84.3, 16,000 x 512 equal.  Stores past
-    // WHOLE_MAX_ROWS_FEW, whose groups are up to 256 rows, take them one by one: 400,000 x 1024 rows in runs of 16, k = 24 251 us in runs of four, 135.
-    // Two blocks of queries: past 131,072 rows, whose groups are two tiles or more (Q 50, 200,000 x 512 in runs of 16, k = 32 62 us in
-    // the pipeline, 81 with runs of four, 46 one by one; rows that resemble nobody 47 and 47).
-    p.run_shift = n > (Q <= 32 ? WHOLE_MAX_ROWS_FEW : WHOLE_MAX_GROUPS * 32) || n <= WHOLE_SMALL_TILE_ROWS ? 0 : 2;
     // (the most wavefronts whose rings have room and whose groups come out at no more than 256 rows)
     for (p.waves_per_block = 8; p.waves_per_block >= 4; --p.waves_per_block) {
         const int64_t lds = resident + (int64_t)p.waves_per_block * (p.pieces_in_ring * p.tr * 128 + p.side_slots * p.tr * 12) + 256;
@@ -1419,7 +1412,7 @@ struct WholeSelectArgs {
     int32_t k, d, groups, group_rows, tile_rows, tiles, grid;
     int32_t k_out;                      // results wanted, where k is a few more (split f32)
     int32_t more_lds;                   // bytes of dynamic LDS
-    int32_t waves, per_group, run_shift;        // StreamPlan (tiles: its units), where the scan was kb_stream_kernel
+    int32_t waves, per_group;        // StreamPlan (tiles: its units), where the scan was kb_stream_kernel
 };
 // 256 threads hold the groups: the kernel's length is a dozen barriers, which more wavefronts only make longer (64 queries
 // x 2048 groups: 7.6 us with 256 threads, 8.2 with 1024)
@@ -1717,7 +1710,7 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
     // row at a place of the tile of group g (the groups of a tile follow each other)
     const uint32_t per_tile = STREAM ? 1u : (uint32_t)a.tile_rows / (uint32_t)a.group_rows;
     auto row_at = [&](uint32_t g, uint32_t place) {
-        if constexpr (STREAM) return (uint32_t)stream_group_row(a.tile_rows, a.tiles, a.waves, a.per_group, a.run_shift, g, place);
+        if constexpr (STREAM) return (uint32_t)stream_group_row(a.tile_rows, a.tiles, a.waves, a.per_group, g, place);
         else return (uint32_t)whole_row((int32_t)(g / per_tile), a.tiles, a.tile_rows, (int)place);
     };
     auto first_place = [&](uint32_t g) { return STREAM ? 0u : g % per_tile * (uint32_t)a.group_rows; };
@@ -2575,7 +2568,6 @@ hipError_t launch_stream_scan(const kb *h, const StreamPlan &p, const void *quer
     a.query_stride = p.query_stride;
     a.side_slots = p.side_slots;
     a.blocks = p.blocks;
-    a.run_shift = p.run_shift;
     return h->dtype == KB_F32 ? launch_stream_f32(p, dense, once, a, s) : h->dtype == KB_BF16 ? launch_stream_bf16(p, dense, once, a, s) : launch_stream_fp8(p, q8, dense, once, a, s);
 }
 
@@ -2634,7 +2626,6 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     WholeSelectArgs t;
     t.waves = p.stream ? p.st.waves : 0;
     t.per_group = p.stream ? p.st.per_group : 1;
-    t.run_shift = p.stream ? p.st.run_shift : 0;
     t.keys = a.keys;
     t.queries = queries_dev;
     t.inv_norm = a.inv_norm;

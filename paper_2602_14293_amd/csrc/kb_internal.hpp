@@ -171,7 +171,7 @@ constexpr int WHOLE_MAX_GROUPS = 4096;      // a thread of the selecting workgro
 // The scan with the queries in LDS (kb_stream.hpp): tiles of `tr` rows, dealt to `waves` wavefronts; a group is `per_group` tiles of one of them.
 struct StreamPlan {
     int32_t tr, tq, pieces_in_ring, waves_per_block, blocks, nqb;       // blocks: per query block
-    int32_t units, waves, per_group, run_shift, side_slots, query_stride;
+    int32_t units, waves, per_group, side_slots, query_stride;
     int32_t lds;
 };
 struct WholePlan {

@@ -31,7 +31,6 @@ struct StreamArgs {
     int32_t query_stride;               // bytes from query to query in LDS, a multiple of 256
     int32_t side_slots;                 // tiles whose side data can be in flight or in use
     int32_t blocks;                     // workgroups per query block
-    int32_t run_shift;                  // see stream_row
 };
 
 constexpr int STREAM_RING_16 = 4, STREAM_RING_32 = 3;     // pieces in a wavefront's ring, by the rows of a tile
@@ -50,23 +49,26 @@ template <int KT_, int TR_, int NST_, int NQ_> struct StreamCfg {
 };
 
 // Knowledge-base row at place `pos` of wavefront w's tile in a layer of c tiles (layer jt holds the tiles jt * waves .. of the
-// store's rows from jt * waves * TR on): runs of 2^shift rows dealt to the tiles in turn, so that rows rise with the places of a
-// group.  The distance of a tile's runs is an odd number of them (see whole_row; a few tiles have nothing to gain from it).
+// store's rows from jt * waves * TR on): rows dealt to the tiles one by one, so that rows rise with the places of a group and
+// neighbours, which may be alike, are in groups of their own (three of a query's best in one group cost a rescoring of it).
+// The distance of a tile's rows is odd (see whole_row; a few tiles have nothing to gain from it).
+// Dealt in runs of four, a tile's rows lie closer: 0 to 3 % faster on stores of 17,000 to 330,000 rows in no order (700,000 x 128 bf16 53.3 us
+// one by one, 48.0), and slower by far on stores of similar neighbours: 90,000 x 512, 16 queries, k 32, runs of 16 26.1 us one by one, 47.7;
+// 200,000 x 512 43.9, 79.7; pairs of rows 26.6 and 45.8 (runs of 4: 30.8).
 __host__ __device__ inline int32_t stream_step(int32_t c) { return c <= 64 ? 0 : (c & 1) != 0 ? 2 : 1; }
-__host__ __device__ inline int32_t stream_row(int32_t base, int32_t w, int32_t c, int32_t step, int32_t shift, int pos)
+__host__ __device__ inline int32_t stream_row(int32_t base, int32_t w, int32_t c, int32_t step, int pos)
 {
-    const int j = pos >> shift;              // (< 32)
-    int32_t t = w + j * step;
+    int32_t t = w + pos * step;              // (pos < 32)
     t -= t >= c ? c : 0;
-    return base + ((j * c + t) << shift) + (pos & ((1 << shift) - 1));
+    return base + pos * c + t;
 }
 // Row at a place of a group (past the store's end: none).
-__host__ __device__ inline int64_t stream_group_row(int32_t tr, int32_t units, int32_t waves, int32_t per_group, int32_t shift, uint32_t group, uint32_t place)
+__host__ __device__ inline int64_t stream_group_row(int32_t tr, int32_t units, int32_t waves, int32_t per_group, uint32_t group, uint32_t place)
 {
     const uint32_t first = group / (uint32_t)waves, w = group - first * (uint32_t)waves;
     const int32_t layer = (int32_t)first * per_group + (int32_t)(place >> (tr == 16 ? 4 : 5));
     const int32_t left = units - layer * waves, c = left < waves ? left : waves;
-    return (int32_t)w < c ? stream_row(layer * waves * tr, (int32_t)w, c, stream_step(c), shift, (int)(place & (uint32_t)(tr - 1))) : (int64_t)0x7fffffff;
+    return (int32_t)w < c ? stream_row(layer * waves * tr, (int32_t)w, c, stream_step(c), (int)(place & (uint32_t)(tr - 1))) : (int64_t)0x7fffffff;
 }
 
 // Waits for a piece of a ring behind which `younger` pieces have been asked for, up to MOST of them: it has landed once at most
@@ -113,7 +115,7 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
     auto row_of = [&](int layer, int pos) {
         if constexpr (DENSE) return (layer * p.waves + w) * TR + pos;
         const int left = p.units - layer * p.waves, c = left < p.waves ? left : p.waves;
-        return stream_row(layer * p.waves * TR, w, c, stream_step(c), p.run_shift, pos);
+        return stream_row(layer * p.waves * TR, w, c, stream_step(c), pos);
     };
     auto piece_of = [&](int j) { return (uint32_t)((lane & 7) ^ swizzle<8>(8 * j + (lane >> 3))); };
     // what goes out before the first piece of a tile: the addresses of its rows, their 1/|k| and tags
