@@ -2362,11 +2362,14 @@ kb_status_t kb_append(kb_t *kb, const void *rows_dev, const float *row_scale_dev
     float *scale_to = kb->dtype == KB_FP8_E4M3 && kb->row_scale + kb->n != row_scale_dev ? kb->row_scale + kb->n : nullptr;
     uint64_t *tags_to = kb->tags && kb->tags + kb->n != tags_dev ? kb->tags + kb->n : nullptr;
     const bool rows_move = dst != rows_dev;
-    // One launch where the kernel can reach both sides: memory of this device, as a whole, words at their own alignment.  (The runtime copies the rest, or refuses it.)
+    // One launch instead of two or three copies where the kernel can reach both sides: memory of this device, as a whole, words at their own
+    // alignment.  (The runtime copies the rest, or refuses it.  A single copy stays with it: it takes the host 1 to 2 us less than the checks and
+    // the launch do.  741 x 768 f32 rows appended, normalized and asked about three times: 81 us, 87 with this kernel.)
     auto reached = [](const void *to, const void *from, size_t alignment, size_t bytes) {
         return within_reach(to, alignment, bytes) && within_reach(from, alignment, bytes);
     };
-    const bool direct = (!rows_move || reached(dst, rows_dev, 16, row_bytes * n)) && (!scale_to || reached(scale_to, row_scale_dev, 4, sizeof(float) * n)) &&
+    const bool several = (int)rows_move + (scale_to != nullptr) + (tags_to != nullptr) > 1;
+    const bool direct = several && (!rows_move || reached(dst, rows_dev, 16, row_bytes * n)) && (!scale_to || reached(scale_to, row_scale_dev, 4, sizeof(float) * n)) &&
                         (!tags_to || reached(tags_to, tags_dev, 8, sizeof(uint64_t) * n));
     if (direct) {
         AppendArgs a;
