@@ -8,6 +8,9 @@
 //                  scan kernel, main pass     (kb_scan.hpp; its wavefronts move their records to per-query lists)
 //                  finalize_kernel            (top k of each query's list by radix selection; or the
 //                                              exhaustive per-query scan when a list overflowed)
+//                  or, smaller stores and batches: a scan that keeps the best of every group or every product
+//                  (kb_stream.hpp, kb_scan.hpp), whole_select_kernel or dense_select_kernel
+//   kb_append    : append_kernel              (rows, scales and tags; a single copy by the runtime)
 #include <stdlib.h>
 #include <string.h>
 
