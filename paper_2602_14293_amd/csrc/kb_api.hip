@@ -456,26 +456,38 @@ int64_t whole_max_rows(const kb *h, int32_t Q, bool q8)
     return std::min(WHOLE_MAX_ROWS, pairs / columns);
 }
 constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
-// Calls on f32 rows whose scan takes two f16 values an element (Mma<KB_F32_SPLIT>).  They select SPLIT_MORE entries more than k by the split
-// products, and the launch that selects orders these by the f32 ones (restate), so that scores don't depend on the path: rows change
-// places only where their scores are within some 1e-6 of each other, and one is missed where more than SPLIT_MORE are that close to the k-th.
-// That takes a call 4 to 5 us (few queries, the rows of k entries in LDS at once; more with k) or 10 (many), and the tiled scan a launch of 2 for
-// the scales, so it is for calls whose scan is long enough.  us a call, f32 instruction | split:
-//   up to 32 queries (kb_stream.hpp, eight wavefronts)     100,000 x 512, Q 12    57.1 | 55.4    300,007 x 384, Q 20   100 | 90.8    300,000 x 768, Q 18    182 | 165
-//     600,000 x 128, Q 16    86.0 | 71.4     1,000,000 x 256, Q 32  208 | 173      under the limits:  50,000 x 896, Q 12   47.9 | 50.2    60,000 x 768, Q 4    47.0 | 51.3
-//     50,000 x 768, Q 32, four wavefronts   45.8 | 58.1      170,000 x 256, k 60   63.8 | 74.5     300,000 x 1024, Q 8, every row on the same few channels   231 | 238
-//   more (tiled kernel)     60,000 x 768, Q 128   113 | 87.5     179,009 x 576, Q 115  247 | 180     150,000 x 256, Q 500  412 | 244     400,000 x 512, Q 200, k 128  1076 | 575
-//     under the limit:       65,000 x 256, Q 64   32.8 | 36.3    33,000 x 1024, Q 64  73.0 | 72.8    16,000 x 256, Q 500  66.3 | 76.8    8000 x 1024, Q 300   82.4 | 95.9
-constexpr int32_t SPLIT_MORE = 4;
+// Calls on f32 rows whose scan takes two f16 values an element (Mma<KB_F32_SPLIT>).  They select a few entries more than k by the split
+// products; the launch that selects scores these again by the f32 instruction's chain (restate) and knows from the bound on the difference
+// (split_error) whether another row could belong to the best k.  Where it could, for any query, two more launches do the call's
+// scan and selection with the f32 instruction: they are always there and leave at once otherwise.  So results don't depend on the path.
+// That takes a call some 8 us with few queries (the rows of the selected entries in LDS at once; more with k) and 10 to 15 with many, so it is for
+// calls whose scan is long enough.  us a call, f32 instruction | split:
+//   up to 32 queries (kb_stream.hpp, eight wavefronts)     300,007 x 384, Q 20  97.8 | 93.3    200,000 x 768, Q 16  126 | 119     300,000 x 768, Q 18  181 | 166
+//     past the rows that the tiled kernel's whole-store plan takes   450,000 x 128, Q 32  75.5 | 64.8    600,000 x 128, Q 16  85.3 | 70.7     1,000,000 x 256, Q 32  208 | 176
+//     under the limits   250,000 x 256  62.4 | 65.4   150,000 x 512  63.3 | 65.7   120,000 x 768  77.2 | 79.1   250,000 x 384, k 30  82.0 | 84.3   300,000 x 1024, all rows on the same few channels  231 | 243
+//   up to 64 (tiled kernel, 64 x 64)    400,000 x 512  273 | 260    1,000,000 x 256, Q 48  343 | 324    600,000 x 1024  769 | 724     under the limit  70,000 x 1024  107 | 109    300,000 x 256, k 30  131 | 138
+//   more     60,000 x 768, Q 128   118 | 98.8     179,009 x 576, Q 115  248 | 177     150,000 x 256, Q 500  414 | 248     400,000 x 512, Q 200, k 128  1105 | 594
+//     rows of all selected entries past 400 KB, few keys    20,000 x 1024, Q 300, k 128  395 | 417    30,000 x 1024, Q 512, k 128  410 | 454    50,000 x 768, Q 100, k 128  173 | 171    60,000 x 1024, Q 300, k 128  639 | 589
+// (The instances of 128 x 256 tiles keep 9 and 4 registers in scratch memory.  With 128 x 128 tiles, which keep none, 150,000 x 256 and 500 queries take
+// 260 us, not 240, 400,000 x 512 and 200 702, not 567.)
 constexpr int RESTATE_LDS = 96 * 1024;
-constexpr int SPLIT_MAX_K_FEW = 32;
-constexpr int64_t SPLIT_MIN_BYTES = 192 << 20, SPLIT_MIN_MULTIPLICATIONS = (int64_t)1 << 32;
+constexpr int64_t SPLIT_MIN_MULTIPLICATIONS = (int64_t)1 << 32;
+// Entries that are selected beyond k.  The scores of rows in no order have a deviation of 1 / sqrt(d), and near the k-th best, some five
+// deviations up, the number of rows falls by a factor e every fifth of one: about 5 k sqrt(d) split_error(d) rows are too close to the k-th.  Four
+// times the root of that and three beyond it are not enough for a query in some ten thousand.  More than SPLIT_MAX_SPARE: not split.
+int32_t split_spare(int32_t d, int32_t k)
+{
+    const double close = 5.0 * k * sqrt((double)d) * split_error(d);
+    return (int32_t)std::min(1e6, ceil(close + 4.0 * sqrt(close) + 3.0));
+}
 bool split_f32(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw)
 {
     if (h->dtype != KB_F32 || draw || h->tune_config) return false;
-    if (Q > 32) return n * Q * h->d >= SPLIT_MIN_MULTIPLICATIONS;
-    return k <= SPLIT_MAX_K_FEW && n * h->d * 4 >= SPLIT_MIN_BYTES && h->d < 1024 && (int64_t)(k + SPLIT_MORE + 1) * (h->d + 4) * 4 <= RESTATE_LDS && n <= WHOLE_MAX_ROWS_STREAM &&
-           Q * ceil_div(h->d, 64) * 256 <= 56 * 1024;
+    const int32_t spare = split_spare(h->d, k);
+    if (spare > SPLIT_MAX_SPARE) return false;
+    const int64_t bytes = n * h->d * 4, again_bytes = (int64_t)(k + spare + 1) * (h->d + 4) * 4;
+    if (Q > 32) return n * Q * h->d >= (Q <= 64 ? 2 : 1) * SPLIT_MIN_MULTIPLICATIONS && (again_bytes <= 400 << 10 || n >= 3 << 14);
+    return bytes >= (n > WHOLE_MAX_ROWS_FEW ? 192 : 400) << 20 && k <= 32 && h->d < 1024 && again_bytes <= RESTATE_LDS && n <= WHOLE_MAX_ROWS_STREAM && Q * ceil_div(h->d, 64) * 256 <= 56 * 1024;
 }
 // The scan with the queries in LDS (kb_stream.hpp), where they fit beside the rings of four wavefronts and up.
 // `most_groups`: no more groups than that.
@@ -497,7 +509,7 @@ bool two_blocks_stream(const kb *h, int64_t n, bool q8, int32_t waves_per_block)
 }
 bool make_stream_plan(const kb *h, int64_t n, int32_t Q, bool q8, bool split, bool dense, int64_t most_groups, StreamPlan *out)
 {
-    if ((h->dtype == KB_F32 && (dense || !split || Q > 32)) || (!dense && Q > 64)) return false;
+    if ((h->dtype == KB_F32 && !split) || Q > (split ? 32 : dense ? INT32_MAX : 64)) return false;
     StreamPlan p;
     p.tq = dense || Q <= 32 ? 32 : 64;
     const int64_t row_bytes = (int64_t)h->d * key_bytes(h->dtype), pieces = ceil_div(row_bytes, 128);
@@ -537,11 +549,11 @@ size_t whole_bytes(int32_t Q, int32_t groups, size_t *off_pair)
     *off_pair = WHOLE_OFF_BEST + align_up(sizeof(float) * (size_t)Q * groups);
     return *off_pair + align_up(sizeof(u32x4) * (size_t)Q * groups);
 }
+// (k: entries wanted; split f32 rows select a few more)
 bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, bool split, Thrift thrift, WholePlan *out)
 {
     if (draw || h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
     if (n < 1 || Q > WHOLE_MAX_QUERIES || n > whole_max_rows(h, Q, q8) || (q8 && h->dtype != KB_FP8_E4M3)) return false;
-    const int32_t rule_k = split ? std::max(1, k - SPLIT_MORE) : k;
     WholePlan p;
     p.stream = make_stream_plan(h, n, Q, q8, split, false, thrift == LEAST ? ceil_div(n, 128) : WHOLE_MAX_GROUPS, &p.st);
     if (!p.stream && n > (Q <= 32 ? WHOLE_MAX_ROWS_FEW : WHOLE_MAX_ROWS)) return false;
@@ -590,14 +602,15 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     // f32, tiles of 64 rows, too many to be halved into groups: four neighbours share a group.  The pipeline from before had tiles of 128 as this
     // plan had; now, with 64 in both, time of the pipeline over this plan's, 140,000 x 768 rows and 64 queries in no order | runs of 4 | 32:
     // k = 16 1.06 | 0.80 | 0.69 (256 elements 1.28 | 1.00 | 0.91), 24 1.07 | 0.71 | 0.64, 40 1.08 | 0.59 | 0.53, 80 1.16 | 0.46 | 0.40
-    if (p.config == F32_SQUARE_CONFIG && !p.fine && rule_k > 16) return false;
+    if (p.config == F32_SQUARE_CONFIG && !p.fine && k > 16) return false;
     const size_t row_bytes = (size_t)h->d * key_bytes(h->dtype);
     const bool cheap = p.group_rows <= 32 && !(p.stream && q8) && row_bytes <= (Q > 32 ? 512 : h->dtype == KB_F32 ? 1024 : 1536);
-    if (cubed(rule_k) > (cheap ? 4.0 : 0.12) * (double)p.k_groups * p.k_groups) return false;
+    if (cubed(k) > (cheap ? 4.0 : 0.12) * (double)p.k_groups * p.k_groups) return false;
     const int64_t items = tiles * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
     p.grid = p.stream ? p.st.blocks : (int32_t)(items < most ? items : most);
     p.off_best = WHOLE_OFF_BEST;
-    p.total = whole_bytes(Q, p.groups, &p.off_pair);
+    p.off_invq = whole_bytes(Q, p.groups, &p.off_pair);
+    p.total = p.off_invq + (split && !p.stream ? align_up(sizeof(float) * (size_t)Q) : 0);
     *out = p;
     return true;
 }
@@ -612,7 +625,7 @@ bool make_whole_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
 constexpr int64_t DENSE_MAX_PAIRS = (int64_t)1 << 23;
 constexpr int64_t DENSE_FIRST_ROWS = 4096;                 // up to here the dense plan is never the slower one
 bool dense_is_better(int64_t n, int32_t k, const WholePlan &w) { return n <= DENSE_FIRST_ROWS || cubed(k) > 0.5 * (double)w.k_groups * w.k_groups; }
-bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, bool split, DensePlan *out)
+bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, DensePlan *out)
 {
     if (h->tune_no_small_path || h->tune_config || h->tune_sample_keys || h->tune_wg_per_cu) return false;
     if (n < 1 || n > DENSE_MAX_ROWS || n * Q > DENSE_MAX_PAIRS || (q8 && h->dtype != KB_FP8_E4M3)) return false;
@@ -622,7 +635,7 @@ bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     const int64_t tiles32 = ceil_div(n, 32) * ceil_div(Q, 32);
     const bool small = tiles32 <= (h->dtype == KB_F32 ? DEVICE_CUS : 2 * DEVICE_CUS);
     if (q8) p.config = small ? FP8_QUERY_SMALL_CONFIG : Q <= 64 ? FP8_QUERY_TILED_CONFIG : FP8_QUERY_TILED_CONFIG + 1;
-    else if (h->dtype == KB_F32) p.config = small && !draw && !split ? SMALL_F32_CONFIG : F32_SQUARE_CONFIG;
+    else if (h->dtype == KB_F32) p.config = small && !draw ? SMALL_F32_CONFIG : F32_SQUARE_CONFIG;
     else if (h->dtype == KB_BF16) p.config = small ? 13 : Q <= 64 ? 12 : 16;
     else p.config = small ? 13 : Q <= 32 ? 1 : 2;
     ConfigInfo ci;
@@ -632,7 +645,7 @@ bool make_dense_plan(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bo
     p.nqb = (int32_t)ceil_div(Q, p.tq);
     const int64_t items = ceil_div(n, ci.tk) * p.nqb, most = (int64_t)DEVICE_CUS * ci.wg_per_cu;
     p.grid = (int32_t)(items < most || p.config == SMALL_F32_CONFIG ? items : most);
-    p.stream = small && !draw && make_stream_plan(h, n, Q, q8, split, true, WHOLE_MAX_GROUPS, &p.st);
+    p.stream = small && !draw && make_stream_plan(h, n, Q, q8, false, true, WHOLE_MAX_GROUPS, &p.st);
     if (p.stream) p.grid = p.st.blocks * p.st.nqb;
     p.stride = (int32_t)(ceil_div(n, 128) * 128);
     p.off_values = align_up(sizeof(uint64_t) * (STAT_WORDS + STAT_PARTIALS));       // the diagnostics come first, as always
@@ -797,7 +810,7 @@ template <int QT> __global__ __launch_bounds__(256) void prep_kernel(const void 
         flag[t] = 0;
         qmask_pad[t] = (qmask && t < Q) ? qmask[t] : 0ull;
     }
-    if (t < STAT_WORDS + STAT_PARTIALS) stats[t] = t == 2 ? sample_keys : t == 3 ? (uint64_t)grid : 0ull;
+    if (t <= STAT_GATE) stats[t] = t == 2 ? sample_keys : t == 3 ? (uint64_t)grid : 0ull;
     const int lane = threadIdx.x & 63;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row < qpad) {
@@ -816,8 +829,9 @@ template <int QT> __global__ __launch_bounds__(256) void prep_kernel(const void 
 // data-parallel-primitive moves (a shuffle is an LDS round trip each), the wavefronts exchange their partial
 // results through LDS without atomics, and a pass has two barriers.  Zero words are padding: they are
 // never selected, and if fewer than k words are nonzero the result is zero-padded.
+constexpr int SELECT_MAX = KB_K_MAX + SPLIT_MAX_SPARE;        // entries that a call selects at most
 struct SelectScratch {
-    uint64_t sel[KB_K_MAX];
+    uint64_t sel[SELECT_MAX];
     uint32_t hist[256];
     uint32_t part[16][4];  // per wavefront: its nonzero words, AND and OR of their upper halves
     uint32_t ctl[8];       // 1 selected, 2 digit found, 3 still needed, 4 words in that bin
@@ -1007,7 +1021,7 @@ __device__ inline void select_topk_desc(uint64_t *buf, int n, int k, SelectScrat
         const uint64_t e = buf[i];
         if (e != 0 && shr64(e, shift) >= pref) {
             const uint32_t slot = atomicAdd(&sc->ctl[1], 1u);
-            if (slot < (uint32_t)KB_K_MAX) sc->sel[slot] = e;
+            if (slot < (uint32_t)SELECT_MAX) sc->sel[slot] = e;
         }
     }
     __syncthreads();
@@ -1231,7 +1245,7 @@ struct FinalArgs {
     const uint64_t *qmask;
     const float *invq;
     const uint64_t *cand;
-    const uint32_t *cnt;
+    uint32_t *cnt;
     const uint32_t *flag;
     uint64_t *stats;
     int32_t *out_index;
@@ -1242,7 +1256,9 @@ struct FinalArgs {
     uint32_t *fb_done;        // [Q] arrivals of the parts of an exhaustive scan (zero before the launch)
     uint64_t *fb_lists;       // [Q][fb_parts][k] their partial results
     int32_t fb_parts;
-    const uint64_t *thr64;    // [Q] threshold words of the scan
+    uint64_t *thr64;          // [Q] threshold words of the scan
+    float *thrp;              // ... and the bounds that go with them
+    int32_t again;            // the launch behind one on split f32 rows: the queries that this one left to it, if any
     int32_t raw;              // the lists hold dot * inv_k products (plain queries), not finished candidate words
     int32_t k_out, more_lds;  // as in WholeSelectArgs
     int32_t more_at;          // offset of these bytes in the dynamic LDS
@@ -1347,7 +1363,7 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
     const int cap = a.cand_cap;
     const bool filter = a.qmask != nullptr;
     const uint64_t qm = filter ? a.qmask[q] : 0;
-    const float inv = inv_q ? *inv_q : a.invq[q], iq = used_inv<KT>(inv), query_scale = f32_row_scale(inv);
+    const float iq = inv_q ? *inv_q : a.invq[q];
     uint64_t *thr_local = reinterpret_cast<uint64_t *>(ctl + 2);   // ctl[0] = count, ctl[2..3] = threshold word
     if (tid == 0) {
         ctl[0] = 0;
@@ -1357,7 +1373,7 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
     for (int64_t row0 = row_begin; row0 < row_end; row0 += 128) {
         int64_t my_row = row0 + wave * 32 + lrow;
         if (my_row >= row_end) my_row = row_end - 1;
-        const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, my_row, q, key_scale_of<KT>(a.inv_norm, my_row), query_scale);    // (16 where a group is two register quadruples, 8 where it is three or four)
+        const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, my_row, q);    // (16 where a group is two register quadruples, 8 where it is three or four)
         // every column holds the same query; lanes 0..15 of each half own one row each
         float v = acc[0];
 #pragma unroll
@@ -1365,7 +1381,7 @@ template <int KT> __device__ void exhaustive_query(const FinalArgs &a, int q, ui
         if (lrow < 16) {
             const int64_t row = row0 + wave * 32 + 8 * (lrow >> 2) + 4 * half + (lrow & 3);
             if (row < row_end && !row_removed(a.inv_norm[row]) && (!filter || (a.tags[row] & qm) != 0)) {
-                float value = final_score(v, used_inv<KT>(a.inv_norm[row]), iq);
+                float value = final_score(v, a.inv_norm[row], iq);
                 if (a.draw.enabled) value = draw_key_of(value, a.draw, a.draw.first_query + (uint32_t)q, row);
                 const uint64_t cw = pack_candidate(value, (uint32_t)row);
                 if (cw > *thr_local && value > -__builtin_inff()) {
@@ -1414,6 +1430,7 @@ struct WholeSelectArgs {
     int64_t n_keys;
     int32_t k, d, groups, group_rows, tile_rows, tiles, grid;
     int32_t k_out;                      // results wanted, where k is a few more (split f32)
+    uint64_t *gate;                     // split f32: the word that says whether the f32 instruction is needed; f32: as in ScanArgs
     int32_t more_lds;                   // bytes of dynamic LDS
     int32_t waves, per_group;        // StreamPlan (tiles: its units), where the scan was kb_stream_kernel
 };
@@ -1538,7 +1555,7 @@ template <int PER> __device__ __forceinline__ KthBound bound_kth(const float (&v
 // Split f32: the scores of the m rows in `words` as every other kernel has them for f32 rows, in place of those that selected them.  A dot
 // product is v_mfma_f32_32x32x2f32's chain (0 4 1 5 2 6 3 7 of every eight elements) on the vector units, which has the same bits;
 // the rows come through LDS a few columns at a time (stage: stage_bytes, 16-byte aligned).  256 threads, converged.
-// So f32 scores don't depend on how many queries or rows a call has, and selecting a few more than k (SPLIT_MORE) leaves their order to these.
+// So f32 scores don't depend on how many queries or rows a call has, nor does the order of those selected.
 __device__ inline void restate(uint64_t *words, int m, const void *keys, const float *inv_norm, const void *query, int d, float inv_q, float *stage, int stage_bytes)
 {
     typedef __attribute__((address_space(3))) void *lds_ptr;
@@ -1588,8 +1605,8 @@ int restate_lds(int32_t Q, int32_t k, int32_t d)
     const int64_t want = ((int64_t)(k + 1) * (d + 4) * 4 + 1023) / 1024 * 1024;
     return Q > DEVICE_CUS ? 0 : (int)std::min<int64_t>(want, RESTATE_LDS);
 }
-// ... and the best k of them to the query's place in the output
-__device__ inline void write_restated(SelectScratch *sc, int m, int q, int k, int32_t *out_index, float *out_score)
+// ... and the best k of them to the query's place in the output; *kth: the k-th, zero where there is none (zero before the call, to be read behind a barrier)
+__device__ inline void write_restated(SelectScratch *sc, int m, int q, int k, int32_t *out_index, float *out_score, uint64_t *kth)
 {
     const int tid = threadIdx.x;
     const uint64_t e = tid < m ? sc->sel[tid] : 0ull;
@@ -1599,11 +1616,24 @@ __device__ inline void write_restated(SelectScratch *sc, int m, int q, int k, in
     if (tid < m && rank < k) {
         out_index[(size_t)q * k + rank] = e ? (int32_t)candidate_index(e) : -1;
         out_score[(size_t)q * k + rank] = e ? candidate_score(e) : -__builtin_inff();
+        if (rank == k - 1) *kth = e;
     }
     if (tid >= m && tid < k) {
         out_index[(size_t)q * k + tid] = -1;
         out_score[(size_t)q * k + tid] = -__builtin_inff();
     }
+}
+// Are the k best of the m rows that were scored again the query's results?  They are
+//   if fewer than the `selected` rows asked for were there, as then all that qualify are among them;
+//   if the k-th best f32 score lies above the lowest split score `last` of the selected rows by more than the two can differ: no row that was
+//   not selected has a higher split score, so none has an f32 score that comes near;
+//   if the query is zero: all scores are, and the rows were selected by their index.
+// A query whose length is not a number is left to the f32 instruction.
+__device__ inline bool restated_suffice(int m, int selected, float last, uint64_t kth, float square_sum, int d)
+{
+    if (square_sum == 0.f) return m < selected || kth != 0ull;
+    if (!f32_ordinary(inv_norm_of(square_sum))) return false;
+    return m < selected || (kth != 0ull && candidate_score(kth) > last + split_error(d));
 }
 
 // The best k of the `have` words of `buf` go to sc->sel (256 threads, converged); returns how many there are.
@@ -1666,9 +1696,12 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
     __shared__ KthScratch kth;
     __shared__ uint16_t list[WHOLE_MAX_GROUPS], again[WHOLE_MAX_GROUPS];        // groups that reach the bound; with what is not known of them
     __shared__ SelectScratch sc;
-    __shared__ float sh_iq, sh_scale, sh_inv;
+    __shared__ float sh_iq, sh_square;
     __shared__ uint32_t sh_cnt, sh_listed, sh_again;
-    __shared__ uint64_t sh_thr;
+    __shared__ uint64_t sh_thr, sh_kth;
+    if constexpr (KT == KB_F32) {
+        if (a.gate != nullptr && *a.gate == 0) return;
+    }
     constexpr int nt = WHOLE_THREADS, nw = nt / 64;
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k = a.k, groups = a.groups;
     constexpr float NONE = -__builtin_inff();
@@ -1683,13 +1716,12 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
     const uint64_t qm = a.qmask ? a.qmask[q] : 0ull;
     if (q == 0 && tid < STAT_WORDS + STAT_PARTIALS) a.stats[tid] = tid == 3 ? (uint64_t)a.grid : 0ull;
     if (tid < 64) {
-        const float inv = row_inv_norm<QT>(a.queries, q, a.d * bytes_of(QT), tid);
+        const float square_sum = row_square_sum<QT>(a.queries, q, a.d * bytes_of(QT), tid);
         if (tid == 0) {
-            sh_iq = used_inv<KT>(inv);
-            sh_scale = f32_row_scale(inv);
-            sh_inv = inv;
+            sh_iq = used_inv<KT>(inv_norm_of(square_sum));
+            sh_square = square_sum;
             sh_cnt = sh_listed = sh_again = 0;
-            sh_thr = 0;
+            sh_thr = sh_kth = 0;
         }
     }
     for (int i = tid; i < WHOLE_BINS; i += nt) kth.hist[i] = 0u;
@@ -1797,7 +1829,7 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
             const uint32_t g = to_score[t / per], in_group = t % per * 32, place0 = first_place(g) + in_group, known = pair[g][2];
             const int lrow = lane & 31, half = lane >> 5;
             const int64_t at = row_at(g, place0 + lrow), mine = at < a.n_keys ? at : a.n_keys - 1;      // (a place past a group of 16 is some other row)
-            const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, mine, q, key_scale_of<KT>(a.inv_norm, mine), sh_scale);
+            const f32x16 acc = score_rows<KT, KT == KB_F32 || KT == KB_BF16 ? 16 : 8>(a.keys, a.queries, a.d, mine, q, key_scale_of<KT>(a.inv_norm, mine), KT == KB_F32_SPLIT ? f32_row_scale(inv_norm_of(sh_square)) : 1.f);
             const float dot = select16(acc, lrow & 15);
             const uint32_t rel = 8 * ((lrow & 15) >> 2) + 4 * half + (lrow & 3), place = place0 + rel;
             const int64_t row = row_at(g, place);
@@ -1812,8 +1844,11 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
     }
     if constexpr (KT == KB_F32_SPLIT) {
         const int m = best_to_scratch(buf, have, k, &sc);
-        restate(sc.sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, sh_inv, a.more_lds ? reinterpret_cast<float *>(more_lds) : reinterpret_cast<float *>(buf), a.more_lds ? a.more_lds : (int)sizeof buf);
-        write_restated(&sc, m, q, a.k_out, a.out_index, a.out_score);
+        const float last = m == k ? candidate_score(sc.sel[k - 1]) : NONE;
+        restate(sc.sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, inv_norm_of(sh_square), a.more_lds ? reinterpret_cast<float *>(more_lds) : reinterpret_cast<float *>(buf), a.more_lds ? a.more_lds : (int)sizeof buf);
+        write_restated(&sc, m, q, a.k_out, a.out_index, a.out_score, &sh_kth);
+        __syncthreads();
+        if (tid == 0 && !restated_suffice(m, k, last, sh_kth, sh_square, a.d)) *a.gate = 1;
     } else write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
 }
 
@@ -1826,20 +1861,16 @@ struct DenseSelectArgs {
     float *out_score;
     uint64_t *stats;
     int32_t k, d, n, stride, grid;
-    const void *keys;           // split f32, as in WholeSelectArgs
-    const float *inv_norm;
-    int32_t k_out, more_lds;
 };
 template <int QT, bool KEYS, int PIECES> __global__ __launch_bounds__(DENSE_THREADS) void dense_select_kernel(DenseSelectArgs a)
 {
     static_assert(DENSE_THREADS == WHOLE_THREADS && PIECES * 4 * DENSE_THREADS <= DENSE_MAX_ROWS);
     constexpr int PER = 4 * PIECES;
     constexpr float NONE = -__builtin_inff();
-    extern __shared__ __attribute__((aligned(16))) unsigned char more_lds[];        // split f32: see restate_lds
     __shared__ __attribute__((aligned(16))) uint64_t buf[WHOLE_CAP];
     __shared__ KthScratch kth;
     __shared__ SelectScratch sc;
-    __shared__ float sh_iq, sh_inv;
+    __shared__ float sh_iq;
     __shared__ uint32_t sh_cnt;
     __shared__ uint64_t sh_thr;
     const int q = blockIdx.x, tid = threadIdx.x, k = a.k;
@@ -1855,10 +1886,7 @@ template <int QT, bool KEYS, int PIECES> __global__ __launch_bounds__(DENSE_THRE
     if (q == 0 && tid < STAT_WORDS + STAT_PARTIALS) a.stats[tid] = tid == 3 ? (uint64_t)a.grid : 0ull;
     if (!KEYS && tid < 64) {
         const float inv = row_inv_norm<QT>(a.queries, q, a.d * bytes_of(QT), tid);
-        if (tid == 0) {
-            sh_iq = used_inv<QT>(inv);
-            sh_inv = inv;
-        }
+        if (tid == 0) sh_iq = inv;
     }
     if (tid == 0) {
         sh_cnt = 0;
@@ -1910,11 +1938,7 @@ template <int QT, bool KEYS, int PIECES> __global__ __launch_bounds__(DENSE_THRE
             __syncthreads();
         }
     }
-    if constexpr (QT == KB_F32_SPLIT) {
-        const int m = best_to_scratch(buf, have, k, &sc);
-        restate(sc.sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, sh_inv, a.more_lds ? reinterpret_cast<float *>(more_lds) : reinterpret_cast<float *>(buf), a.more_lds ? a.more_lds : (int)sizeof buf);
-        write_restated(&sc, m, q, a.k_out, a.out_index, a.out_score);
-    } else write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
+    write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
 }
 
 template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalArgs a)
@@ -1924,6 +1948,9 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
     uint32_t *ctl = reinterpret_cast<uint32_t *>(smem_raw + sizeof(uint64_t) * a.cand_cap);
     SelectScratch *sc = reinterpret_cast<SelectScratch *>(smem_raw + sizeof(uint64_t) * a.cand_cap + 16);
     const int q = blockIdx.x, part = blockIdx.y, tid = threadIdx.x;
+    if constexpr (KT == KB_F32) {
+        if (a.again && (a.stats[STAT_GATE] == 0 || (a.flag[q] == 0 && a.thr64[q] == ~0ull))) return;
+    }
     // (the segment counters are asked for together with the flag: one memory round trip instead of two on the path
     // of every query; the parts that turn out to have nothing to do have read 64 bytes in vain)
     uint32_t seg_cnt[CAND_SEGMENTS];
@@ -1940,6 +1967,17 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
     }
     const bool flagged = a.flag[q] != 0 && a.n_keys > 0;
     if (!flagged && part != 0) return;
+    if constexpr (KT == KB_F32_SPLIT) {
+        if (flagged) {          // (the scan behind this launch has nothing to do for this query: the exhaustive one is that of f32 rows)
+            if (tid < CAND_SEGMENTS) a.cnt[(size_t)q * CAND_SEGMENTS + tid] = 0;
+            if (tid == 0) {
+                a.thr64[q] = ~0ull;
+                a.thrp[q] = __builtin_inff();
+                a.stats[STAT_GATE] = 1;
+            }
+            return;
+        }
+    }
     if (flagged) {
         // The grid has fb_parts workgroups per query; for a flagged query each scans its share of the rows and leaves
         // its best k as a sorted list, and the one that arrives last merges the lists.  (One workgroup alone would
@@ -1947,7 +1985,7 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
         const int64_t len = ((a.n_keys + a.fb_parts - 1) / a.fb_parts + 127) / 128 * 128;
         const int64_t begin = (int64_t)part * len, end = begin + len < a.n_keys ? begin + len : a.n_keys;
         uint64_t *mine = a.fb_lists + ((size_t)q * a.fb_parts + part) * a.k;
-        if (begin < end) exhaustive_query<KT>(a, q, buf, ctl, sc, begin, end);
+        if (begin < end) exhaustive_query<KT == KB_F32_SPLIT ? (int)KB_F32 : KT>(a, q, buf, ctl, sc, begin, end);
         if (tid < a.k) mine[tid] = begin < end ? buf[tid] : 0ull;
         __threadfence();                // the list is visible device-wide before the arrival is counted
         __syncthreads();
@@ -2009,11 +2047,31 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
         select_topk_desc(buf, (int)n, a.k, sc, tid, 256);
     }
     if constexpr (KT == KB_F32_SPLIT) {
+        __shared__ float sh_square;
+        __shared__ uint64_t sh_kth;
         const uint64_t cw = tid < a.k ? buf[tid] : 0ull;
         if (tid < a.k) sc->sel[tid] = cw;
+        if (tid < 64) {
+            const float square_sum = row_square_sum<KB_F32>(a.queries, q, a.d * 4, tid);
+            if (tid == 0) {
+                sh_square = square_sum;
+                sh_kth = 0;
+            }
+        }
         const int m = __syncthreads_count(cw != 0ull);          // (the words without an entry come last)
-        restate(sc->sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, a.invq[q], reinterpret_cast<float *>(a.more_lds ? smem_raw + a.more_at : smem_raw), a.more_lds ? a.more_lds : a.cand_cap * 8);
-        write_restated(sc, m, q, a.k_out, a.out_index, a.out_score);
+        const float last = m == a.k ? candidate_score(sc->sel[a.k - 1]) : 0.f, inv = inv_norm_of(sh_square);
+        restate(sc->sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, inv, reinterpret_cast<float *>(a.more_lds ? smem_raw + a.more_at : smem_raw), a.more_lds ? a.more_lds : a.cand_cap * 8);
+        write_restated(sc, m, q, a.k_out, a.out_index, a.out_score, &sh_kth);
+        __syncthreads();
+        if (tid == 0) {
+            // what the scan behind this launch lists: nothing, or what reaches the k-th best f32 word known
+            const bool done = restated_suffice(m, a.k, last, sh_kth, sh_square, a.d);
+            const float x = inv > 0.f && sh_kth != 0ull ? candidate_score(sh_kth) / inv : -__builtin_inff();
+            a.thr64[q] = done ? ~0ull : sh_kth;
+            a.thrp[q] = done ? __builtin_inff() : x - fabsf(x) * 0x1p-20f - 1e-30f;
+            if (!done) a.stats[STAT_GATE] = 1;
+        }
+        if (tid < CAND_SEGMENTS) a.cnt[(size_t)q * CAND_SEGMENTS + tid] = 0;        // (everyone has read them)
         return;
     }
     if (tid < a.k) {
@@ -2282,7 +2340,7 @@ hipError_t launch_scan(kb_dtype_t dt, int config, int family, bool sample, int g
         return dt == KB_BF16 ? launch_scan_sp_bf16(config, sample, grid, a, s)
                : dt == KB_FP8_E4M3 ? launch_scan_sp_fp8(config, sample, grid, a, s) : hipErrorInvalidValue;
     switch (dt) {
-    case KB_F32: return a.invq_stride ? launch_scan_f32_split(config, sample, grid, a, s) : launch_scan_f32(config, sample, grid, a, s);
+    case KB_F32: return a.split ? launch_scan_f32_split(config, sample, grid, a, s) : launch_scan_f32(config, sample, grid, a, s);
     case KB_BF16: return launch_scan_bf16(config, sample, grid, a, s);
     default: return launch_scan_fp8(config, sample, grid, a, s);
     }
@@ -2546,15 +2604,15 @@ void launch_prep(const void *queries_dev, kb_dtype_t q_dtype, int32_t Q, int32_t
                  uint32_t *flag, uint64_t *stats, uint64_t sample_keys, const uint64_t *qmask_dev, uint64_t *qmask_pad, int32_t grid, uint32_t *fb_done,
                  const GainArgs &ga, hipStream_t s)
 {
-    const int n_init = qpad > STAT_WORDS + STAT_PARTIALS ? qpad : STAT_WORDS + STAT_PARTIALS;
+    const int n_init = qpad > STAT_GATE + 1 ? qpad : STAT_GATE + 1;
     const int blocks_rows = (int)ceil_div(qpad, 4), blocks_init = (int)ceil_div(n_init, 256);
     const unsigned blocks = (blocks_rows > blocks_init ? blocks_rows : blocks_init) + ga.blocks;
     auto *fn = q_dtype == KB_F32 ? &prep_kernel<KB_F32> : q_dtype == KB_FP8_E4M3 ? &prep_kernel<KB_FP8_E4M3> : &prep_kernel<KB_BF16>;
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(256), 0, s, queries_dev, Q, qpad, d, invq, thr64, thrp, cnt, flag, stats, sample_keys, qmask_dev, qmask_pad, grid, fb_done, ga);
 }
 
-hipError_t launch_stream_scan(const kb *h, const StreamPlan &p, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, float *best, u32x4 *pair, int32_t groups,
-                              bool dense, bool once, hipStream_t s)
+hipError_t launch_stream_scan(const kb *h, const StreamPlan &p, const void *queries_dev, bool q8, bool split, int32_t Q, const uint64_t *qmask_dev, float *best, u32x4 *pair, int32_t groups,
+                              bool dense, bool once, uint64_t *gate, hipStream_t s)
 {
     StreamArgs a;
     a.keys = h->keys;
@@ -2574,27 +2632,21 @@ hipError_t launch_stream_scan(const kb *h, const StreamPlan &p, const void *quer
     a.query_stride = p.query_stride;
     a.side_slots = p.side_slots;
     a.blocks = p.blocks;
-    return h->dtype == KB_F32 ? launch_stream_f32(p, dense, once, a, s) : h->dtype == KB_BF16 ? launch_stream_bf16(p, dense, once, a, s) : launch_stream_fp8(p, q8, dense, once, a, s);
+    a.gate = gate;
+    return h->dtype == KB_F32 ? launch_stream_f32(p, split, once, a, s) : h->dtype == KB_BF16 ? launch_stream_bf16(p, dense, once, a, s) : launch_stream_fp8(p, q8, dense, once, a, s);
 }
 
-// The tiled scan of split f32 rows needs the queries' scales, which come from 1/|q|, and the plans without a sampling pass have no array
-// for them: they lie in the first place of each query's scores until the launch that writes these.
-__global__ __launch_bounds__(256) void query_inv_kernel(const void *queries, int Q, int d, float *out, int stride)
+// The tiled scan of split f32 rows needs the queries' scales, which come from 1/|q|.  (The gate's word is cleared here: nothing of the call has run.)
+__global__ __launch_bounds__(256) void query_inv_kernel(const void *queries, int Q, int d, float *out, uint64_t *gate)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *gate = 0;
     const int row = blockIdx.x * 4 + ((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= Q) return;
     const float inv = row_inv_norm<KB_F32>(queries, row, d * 4, lane);
-    if (lane == 0) out[(size_t)row * stride] = inv;
-}
-hipError_t give_scales(ScanArgs &a, int32_t k, float *scores_out_dev, hipStream_t s)
-{
-    a.invq = scores_out_dev;
-    a.invq_stride = k;
-    hipLaunchKernelGGL(query_inv_kernel, dim3((unsigned)ceil_div(a.Q, 4)), dim3(256), 0, s, a.queries, a.Q, a.d, scores_out_dev, k);
-    return hipGetLastError();
+    if (lane == 0) out[row] = inv;
 }
 
-// kb_query by the whole-store plan: two launches (split f32 rows and the tiled scan: three).
+// kb_query by the whole-store plan: two launches (split f32 rows: two more that do nothing as a rule, and one before the tiled scan).
 kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, bool q8, int32_t Q, const uint64_t *qmask_dev, int32_t k, int32_t k_out,
                          bool split, int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
 {
@@ -2617,13 +2669,20 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     a.whole_pair = reinterpret_cast<u32x4 *>(ws + p.off_pair);
     a.whole_groups = p.groups;
     a.whole_fine = p.fine;
-    if (split && !p.stream && give_scales(a, k_out, scores_out_dev, s) != hipSuccess) return KB_ERR_DEVICE;
+    uint64_t *gate = reinterpret_cast<uint64_t *>(ws) + STAT_GATE;
+    if (split && !p.stream) {
+        float *invq = reinterpret_cast<float *>(ws + p.off_invq);
+        a.invq = invq;
+        a.split = 1;
+        hipLaunchKernelGGL(query_inv_kernel, dim3((unsigned)ceil_div(Q, 4)), dim3(256), 0, s, queries_dev, Q, h->d, invq, gate);
+        if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
+    }
     const bool timed = h->prof_events && h->prof_used < h->prof_max && h->prof_seen++ % h->prof_stride == h->prof_stride / 2;
     if (timed) {
         scan_timing.start = h->prof_events[2 * h->prof_used];
         scan_timing.stop = h->prof_events[2 * h->prof_used + 1];
     }
-    const hipError_t launched = p.stream ? launch_stream_scan(h, p.st, queries_dev, q8, Q, qmask_dev, a.whole_best, a.whole_pair, p.groups, false, a.keys_once != 0, s)
+    const hipError_t launched = p.stream ? launch_stream_scan(h, p.st, queries_dev, q8, split, Q, qmask_dev, a.whole_best, a.whole_pair, p.groups, false, a.keys_once != 0, split ? gate : nullptr, s)
                                          : launch_scan(h->dtype, p.config, 0, false, p.grid, a, s);
     scan_timing = ScanTiming();
     if (launched != hipSuccess) return KB_ERR_DEVICE;
@@ -2653,17 +2712,30 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     t.grid = p.grid;
     const int kt = q8 ? KT_FP8_Q8 : split ? KB_F32_SPLIT : (int)h->dtype;
     auto *fn = p.stream ? whole_select_for<true>(kt, p.groups) : whole_select_for<false>(kt, p.groups);
+    t.gate = split ? gate : nullptr;
     t.more_lds = split ? restate_lds(Q, k, h->d) : 0;
     static LdsAllowed allowed[6];
     if (t.more_lds > 0 && allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed[(p.stream ? 3 : 0) + (p.groups <= 4 * WHOLE_THREADS ? 0 : p.groups <= 8 * WHOLE_THREADS ? 1 : 2)], RESTATE_LDS) != hipSuccess)
         return KB_ERR_DEVICE;
     hipLaunchKernelGGL(fn, dim3(Q), dim3(WHOLE_THREADS), t.more_lds, s, t);
-    return hipGetLastError() == hipSuccess ? KB_OK : KB_ERR_DEVICE;
+    if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
+    if (split) {        // the same with the f32 instruction, where a query needs it
+        a.split = 0;
+        a.gate = gate;
+        const hipError_t again = p.stream ? launch_stream_scan(h, p.st, queries_dev, q8, false, Q, qmask_dev, a.whole_best, a.whole_pair, p.groups, false, a.keys_once != 0, gate, s)
+                                          : launch_scan(h->dtype, p.config, 0, false, p.grid, a, s);
+        if (again != hipSuccess) return KB_ERR_DEVICE;
+        t.k = k_out;
+        t.more_lds = 0;
+        hipLaunchKernelGGL(p.stream ? whole_select_for<true>(KB_F32, p.groups) : whole_select_for<false>(KB_F32, p.groups), dim3(Q), dim3(WHOLE_THREADS), 0, s, t);
+        if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
+    }
+    return KB_OK;
 }
 
 // kb_query and kb_query_sampled by the dense plan: two launches, three with the weighted selection (its scan needs 1/|q| and ln(gain)).
-kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_dtype_t q_dtype, int32_t Q, const uint64_t *qmask_dev, int32_t k, int32_t k_out,
-                         bool split, DrawArgs dr, GainArgs ga, int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
+kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_dtype_t q_dtype, int32_t Q, const uint64_t *qmask_dev, int32_t k,
+                         DrawArgs dr, GainArgs ga, int32_t *indices_out_dev, float *scores_out_dev, unsigned char *ws, hipStream_t s)
 {
     ScanArgs a;
     memset(&a, 0, sizeof a);
@@ -2695,13 +2767,12 @@ kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_
                     u32 + (size_t)a.qpad * (CAND_SEGMENTS + 1), ga, s);
         if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
     }
-    if (split && !p.stream && give_scales(a, k_out, scores_out_dev, s) != hipSuccess) return KB_ERR_DEVICE;
     const bool timed = h->prof_events && h->prof_used < h->prof_max && h->prof_seen++ % h->prof_stride == h->prof_stride / 2;
     if (timed) {
         scan_timing.start = h->prof_events[2 * h->prof_used];
         scan_timing.stop = h->prof_events[2 * h->prof_used + 1];
     }
-    const hipError_t launched = p.stream ? launch_stream_scan(h, p.st, queries_dev, q_dtype == KB_FP8_E4M3, Q, qmask_dev, a.dense, nullptr, p.stride, true, false, s)
+    const hipError_t launched = p.stream ? launch_stream_scan(h, p.st, queries_dev, q_dtype == KB_FP8_E4M3, false, Q, qmask_dev, a.dense, nullptr, p.stride, true, false, nullptr, s)
                                          : launch_scan(h->dtype, p.config, 0, false, p.grid, a, s);
     scan_timing = ScanTiming();
     if (launched != hipSuccess) return KB_ERR_DEVICE;
@@ -2713,17 +2784,12 @@ kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_
     t.out_index = indices_out_dev;
     t.out_score = scores_out_dev;
     t.stats = stats;
-    t.keys = h->keys;
-    t.inv_norm = h->inv_norm;
-    t.k_out = k_out;
-    t.more_lds = 0;       // (many queries)
     t.k = k;
     t.d = h->d;
     t.n = (int32_t)h->n;
     t.stride = p.stride;
     t.grid = p.grid;
     if (dr.enabled) launch_dense_select<KB_F32, true>(t, Q, s);        // (the keys are finished)
-    else if (split) launch_dense_select<KB_F32_SPLIT, false>(t, Q, s);
     else if (q_dtype == KB_F32) launch_dense_select<KB_F32, false>(t, Q, s);
     else if (q_dtype == KB_BF16) launch_dense_select<KB_BF16, false>(t, Q, s);
     else launch_dense_select<KB_FP8_E4M3, false>(t, Q, s);
@@ -2735,13 +2801,13 @@ kb_status_t launch_dense(kb *h, const DensePlan &p, const void *queries_dev, kb_
 size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
 {
     if (!kb || Q < 1 || k < 1 || k > KB_K_MAX) return 0;
-    if (kb->dtype == KB_F32) k = std::min(k + SPLIT_MORE, (int32_t)KB_K_MAX);
     // Every combination of kernels a query on this handle can run, each bounded over all row counts.  The choice depends on
     // the kind of query and, through limits of which a handle's type and batch meet at most one for every kind, on the row count
     // (WIDE128_MIN_ROWS for bf16 rows, stream_keys and SHORT_ROWS_MIN_* for fp8 rows): its two sides are those of 1 and of the capacity.
     Sizes m;
     memset(&m, 0, sizeof m);
     bool any = false;
+    const int32_t selected = kb->dtype == KB_F32 && split_spare(kb->d, k) <= SPLIT_MAX_SPARE ? k + split_spare(kb->d, k) : k;
     const int64_t ns[2] = {1, kb->capacity};
     // (the weighted selection first: with the same kernels its plan has everything that the plain one has)
     Choice seen[8];
@@ -2754,7 +2820,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
             for (int i = 0; i < n_seen; ++i) again = again || (seen[i].config == c.config && seen[i].sample_config == c.sample_config);
             if (again) continue;
             seen[n_seen++] = c;
-            bound_sizes(kb, c, Q, k, (kind & 1) != 0, m);
+            bound_sizes(kb, c, Q, selected, (kind & 1) != 0, m);
             any = true;
         }
     if (!any) return 0;
@@ -2774,7 +2840,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
                                 2 * 7 * DEVICE_CUS * 32, 2 * 6 * DEVICE_CUS * 32, 3 * 5 * DEVICE_CUS * 32};
         for (int64_t n : most) {
             WholePlan wp;
-            if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, false, AMPLE, &wp)) total = std::max(total, wp.total);
+            if (make_whole_plan(kb, std::min(n, whole_rows), Q, k, false, q8 != 0, false, AMPLE, &wp)) total = std::max(total, wp.total + (kb->dtype == KB_F32 ? align_up(sizeof(float) * (size_t)Q) : 0));
         }
         // (the scan with the queries in LDS: never more groups than these)
         if (Q <= 32) total = std::max(total, whole_bytes(Q, (int32_t)std::min<int64_t>(WHOLE_MAX_GROUPS, ceil_div(whole_rows, 16)), &unused));
@@ -2782,7 +2848,7 @@ size_t kb_query_workspace_bytes(const kb_t *kb, int32_t Q, int32_t k)
     // the dense plan: grows with the rows
     for (int kind = 0; kind < 4; ++kind) {
         DensePlan dp;
-        if (make_dense_plan(kb, std::min({kb->capacity, DENSE_MAX_ROWS, DENSE_MAX_PAIRS / Q}), Q, k, (kind & 1) != 0, (kind & 2) != 0, false, &dp))
+        if (make_dense_plan(kb, std::min({kb->capacity, DENSE_MAX_ROWS, DENSE_MAX_PAIRS / Q}), Q, k, (kind & 1) != 0, (kind & 2) != 0, &dp))
             total = std::max(total, dp.total);
     }
     return total;
@@ -2805,14 +2871,14 @@ struct Route {
 };
 kb_status_t choose_route_for(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, bool split, size_t workspace_bytes, Route *r)
 {
-    r->k = k;
+    r->k = split ? k + split_spare(h->d, k) : k;
     r->split = split;
     const auto whole_fits = [&](Thrift thrift) { return make_whole_plan(h, n, Q, k, draw, q8, split, thrift, &r->whole) && r->whole.total <= workspace_bytes; };
     const bool whole = whole_fits(AMPLE);
     r->parts = small_path_parts(h, n, Q, draw);
     if (r->parts) r->small = make_small_plan(Q, k, r->parts);
     const bool lists = !r->parts || workspace_bytes >= r->small.total;
-    const bool dense = (whole || lists) && make_dense_plan(h, n, Q, k, draw, q8, split, &r->dense) && r->dense.total <= workspace_bytes;
+    const bool dense = !split && (whole || lists) && make_dense_plan(h, n, Q, k, draw, q8, &r->dense) && r->dense.total <= workspace_bytes;
     if (dense && !(whole && !dense_is_better(n, k, r->whole))) {
         r->kind = Route::DENSE;
         r->bytes = !whole && r->parts ? std::max(r->dense.total, r->small.total) : r->dense.total;
@@ -2826,7 +2892,7 @@ kb_status_t choose_route_for(const kb *h, int64_t n, int32_t Q, int32_t k, bool 
     } else {
         for (const Thrift thrift : {AMPLE, SCORED_TWICE, LEAST}) {
             r->kind = Route::PIPELINE;
-            if (!make_plan(h, n, Q, k, draw, q8, thrift, &r->pipeline)) return KB_ERR_INVALID_ARG;
+            if (!make_plan(h, n, Q, r->k, draw, q8, thrift, &r->pipeline)) return KB_ERR_INVALID_ARG;
             r->bytes = r->pipeline.total;
             if (r->bytes <= workspace_bytes) break;
             if (thrift == AMPLE && whole_fits(LEAST)) {
@@ -2841,9 +2907,10 @@ kb_status_t choose_route_for(const kb *h, int64_t n, int32_t Q, int32_t k, bool 
 }
 kb_status_t choose_route(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw, bool q8, size_t workspace_bytes, Route *r)
 {
-    // (a call that brings no more than the f32 instruction takes, runs with it)
-    if (split_f32(h, n, Q, k, draw) &&
-        choose_route_for(h, n, Q, std::min(k + SPLIT_MORE, (int32_t)KB_K_MAX), draw, q8, true, workspace_bytes, r) == KB_OK && r->kind != Route::PARTS) return KB_OK;
+    // (a call that brings no more than the f32 instruction takes, runs with it; so do stores small enough for the dense plan that it is the better one for)
+    if (split_f32(h, n, Q, k, draw) && choose_route_for(h, n, Q, k, draw, q8, true, workspace_bytes, r) == KB_OK &&
+        (r->kind == Route::WHOLE ? Q > 32 ? n > DENSE_MAX_ROWS || !dense_is_better(n, k, r->whole) : r->whole.stream : r->kind == Route::PIPELINE && Q > 32 && n > DENSE_MAX_ROWS))
+        return KB_OK;
     return choose_route_for(h, n, Q, k, draw, q8, false, workspace_bytes, r);
 }
 
@@ -2911,7 +2978,7 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     if (const kb_status_t e = choose_route(kb, kb->n, Q, k, draw, q8, workspace_bytes, &r); e != KB_OK) return e;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     unsigned char *ws = static_cast<unsigned char *>(workspace_dev);
-    if (r.kind == Route::DENSE) return launch_dense(kb, r.dense, queries_dev, q_dtype, Q, qmask_dev, r.k, k, r.split, dr, ga, indices_out_dev, scores_out_dev, ws, s);
+    if (r.kind == Route::DENSE) return launch_dense(kb, r.dense, queries_dev, q_dtype, Q, qmask_dev, k, dr, ga, indices_out_dev, scores_out_dev, ws, s);
     if (r.kind == Route::WHOLE) return launch_whole(kb, r.whole, queries_dev, q8, Q, qmask_dev, r.k, k, r.split, indices_out_dev, scores_out_dev, ws, s);
     if (r.kind == Route::PARTS)
         return launch_small(kb, queries_dev, q8, Q, qmask_dev, k, r.parts, reinterpret_cast<uint64_t *>(ws + r.small.off_lists), reinterpret_cast<uint64_t *>(ws),
@@ -2940,8 +3007,8 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
     }
 
+    ScanArgs a;
     if (kb->n > 0) {
-        ScanArgs a;
         a.keys = kb->keys;
         a.inv_norm = kb->inv_norm;
         a.tags = qmask_dev ? kb->tags : nullptr;
@@ -2949,7 +3016,8 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
         a.qmask = qmask_dev;
         a.qmask_pad = qmask_pad;
         a.invq = invq;
-        a.invq_stride = split ? 1 : 0;
+        a.split = split;
+        a.gate = nullptr;
         a.thr64 = thr64;
         a.thrp = thrp;
         a.samp = samp;
@@ -3088,7 +3156,10 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     f.fb_lists = reinterpret_cast<uint64_t *>(ws + p.off_fb_lists);
     f.fb_parts = p.fb_parts;
     f.thr64 = thr64;
+    f.thrp = thrp;
+    f.again = 0;
     f.raw = draw ? 0 : 1;
+    constexpr size_t FIN_LDS_MAX = ((size_t)MAX_CAND_CAP * 8 + 16 + sizeof(SelectScratch) + 15) / 16 * 16;
     const size_t fin_base = ((size_t)p.cand_cap * 8 + 16 + sizeof(SelectScratch) + 15) / 16 * 16;
     f.more_at = (int32_t)fin_base;
     f.more_lds = split ? std::min(restate_lds(Q, r.k, kb->d), (int)(MAX_CAND_CAP * 8 + RESTATE_LDS / 2 - fin_base)) : 0;
@@ -3100,15 +3171,26 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
                        : fin_kind == KB_BF16 ? reinterpret_cast<const void *>(&finalize_kernel<KB_BF16>)
                        : fin_kind == KB_FP8_E4M3 ? reinterpret_cast<const void *>(&finalize_kernel<KB_FP8_E4M3>)
                                                  : reinterpret_cast<const void *>(&finalize_kernel<KT_FP8_Q8>);
-    if (allow_dynamic_lds(fin_fn, fin_allowed[fin_kind], MAX_CAND_CAP * 8 + 16 + sizeof(SelectScratch) + (split ? RESTATE_LDS / 2 : 0)) != hipSuccess) return KB_ERR_DEVICE;
+    if (allow_dynamic_lds(fin_fn, fin_allowed[fin_kind], FIN_LDS_MAX + (split ? RESTATE_LDS / 2 : 0)) != hipSuccess) return KB_ERR_DEVICE;
     switch (fin_kind) {
-    case KB_F32_SPLIT: hipLaunchKernelGGL(finalize_kernel<KB_F32_SPLIT>, dim3(Q, p.fb_parts), dim3(256), fin_lds, s, f); break;
+    case KB_F32_SPLIT: hipLaunchKernelGGL(finalize_kernel<KB_F32_SPLIT>, dim3(Q), dim3(256), fin_lds, s, f); break;
     case KB_F32: hipLaunchKernelGGL(finalize_kernel<KB_F32>, dim3(Q, p.fb_parts), dim3(256), fin_lds, s, f); break;
     case KB_BF16: hipLaunchKernelGGL(finalize_kernel<KB_BF16>, dim3(Q, p.fb_parts), dim3(256), fin_lds, s, f); break;
     case KB_FP8_E4M3: hipLaunchKernelGGL(finalize_kernel<KB_FP8_E4M3>, dim3(Q, p.fb_parts), dim3(256), fin_lds, s, f); break;
     default: hipLaunchKernelGGL(finalize_kernel<KT_FP8_Q8>, dim3(Q, p.fb_parts), dim3(256), fin_lds, s, f); break;
     }
     if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
+    if (split) {        // the same with the f32 instruction, where a query needs it
+        a.split = 0;
+        a.gate = stats + STAT_GATE;
+        if (launch_scan(kb->dtype, p.config, p.family, false, p.grid, a, s) != hipSuccess) return KB_ERR_DEVICE;
+        f.k = k;
+        f.again = 1;
+        static LdsAllowed again_allowed;
+        if (allow_dynamic_lds(reinterpret_cast<const void *>(&finalize_kernel<KB_F32>), again_allowed, FIN_LDS_MAX) != hipSuccess) return KB_ERR_DEVICE;
+        hipLaunchKernelGGL(finalize_kernel<KB_F32>, dim3(Q, p.fb_parts), dim3(256), fin_base, s, f);
+        if (hipGetLastError() != hipSuccess) return KB_ERR_DEVICE;
+    }
     return KB_OK;
 }
 

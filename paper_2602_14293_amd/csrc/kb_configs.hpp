@@ -20,7 +20,6 @@
     X(26, KB_F32, 64, 64, 2, 2, 128, 4, 2)
 // ... the same for rows that are scored as two f16 values an element
 #define KB_SCAN_CONFIGS_F32_SPLIT(X)                  \
-    X(1, KB_F32_SPLIT, 128, 32, 4, 1, 128, 3, 2)      \
     X(2, KB_F32_SPLIT, 128, 128, 2, 2, 64, 4, 2)      \
     X(3, KB_F32_SPLIT, 128, 256, 2, 2, 64, 3, 2)      \
     X(26, KB_F32_SPLIT, 64, 64, 2, 2, 128, 4, 2)

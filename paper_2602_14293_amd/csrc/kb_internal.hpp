@@ -79,19 +79,29 @@ __host__ __device__ inline bool row_removed(float inv_k) { return (as_u32(inv_k)
 // see split_f32.
 constexpr int KB_F32_SPLIT = 4;
 // They are scaled by a power of two that brings the row's
-// length to [2^7, 2^8]: the largest f16 value is far away, and what is lost below the smallest one is 2^-33 of the length.  The
+// length to [2^7, 2^8]: the largest f16 value is far away, and what is lost below the smallest one is 2^-32 of the length.  The
 // scale comes from 1/|x| alone, so every kernel has the same; a row without a length (zero, or past the largest float) is taken as zeros.
-__host__ __device__ inline float f32_row_scale(float inv)
-{
-    const uint32_t e = as_u32(inv) & 0x7f800000u;
-    return as_f32(e != 0u ? e + (8u << 23) : 0u);
-}
+//
+// These scores only say which rows are scored again by the f32 instruction, and whether those can be all that count (see restated_suffice).
+__host__ __device__ inline bool f32_ordinary(float inv) { return (as_u32(inv) & 0x7f800000u) != 0u; }
+__host__ __device__ inline float f32_row_scale(float inv) { return as_f32(f32_ordinary(inv) ? (as_u32(inv) & 0x7f800000u) + (8u << 23) : 0u); }
 // 1/|x| of the scaled row: the same digits, so dot products of scaled rows end in the score of the rows as they are.  (The removed bit stays.)
 __host__ __device__ inline float f32_scaled_inv(float inv)
 {
     const uint32_t u = as_u32(inv);
-    return as_f32((u & 0x7f800000u) != 0u ? (u & 0x807fffffu) | 119u << 23 : u);
+    return as_f32(f32_ordinary(inv) ? (u & 0x807fffffu) | 119u << 23 : u);
 }
+constexpr int SPLIT_MAX_SPARE = 32;         // entries selected beyond the k wanted (see split_spare)
+// The most by which a row's split score and its f32 score differ, u = 2^-24 and in units of the two lengths' product (which
+// no partial sum exceeds):
+//   the f32 chain: one rounding an element, of at most u each                                               d u
+//   the f16 instruction, three for 16 elements: products are exact, adding one loses at most 2 u              6 d u
+//     (how it rounds is not documented; measured over random operands of any spread, an instruction loses
+//     up to 6.3 u of the magnitudes it adds, where this has 32)
+//   the elements: h + l is within 2^-22 of an element, for both rows, and l l is left out                    12 u
+//   1/|x| are the same; two roundings in each score; 1/|x| is within d u / 4 of the length                     8 u
+// (d u below 2^-9; what is left over is room for the products of these.)
+__host__ __device__ inline float split_error(int d) { return (7.5f * (float)d + 64.f) * 0x1p-24f; }
 // 1/|x| as the kernels of a key type use it
 template <int KT> __device__ inline float used_inv(float inv) { return KT == KB_F32_SPLIT ? f32_scaled_inv(inv) : inv; }
 
@@ -126,6 +136,8 @@ __host__ __device__ inline uint32_t candidate_segment(uint32_t row) { return (ro
 // workgroups), then the candidate count as STAT_PARTIALS partial sums (one hot address would serialise).
 constexpr int STAT_WORDS = 4;
 constexpr int STAT_PARTIALS = 64;
+// ... and a word that is not shown: whether a query of split f32 rows needs the f32 instruction (see restated_suffice).
+constexpr int STAT_GATE = STAT_WORDS + STAT_PARTIALS;
 // Records a scan wavefront collects before it moves them to the per-query lists (it also does so when it ends).
 constexpr int REGION_CAP = 128;
 
@@ -180,7 +192,7 @@ struct WholePlan {
     int32_t config, tk, tq, nqb, grid;
     int32_t groups, group_rows, fine;
     int32_t k_groups;                   // groups as the rules for k count them
-    size_t off_best, off_pair, total;
+    size_t off_best, off_pair, off_invq, total;      // (off_invq: split f32 rows and the tiled kernel)
 };
 
 // The dense plan: a store of some thousand rows.  The tiled scan writes the product (the key, in the weighted selection) of
@@ -215,8 +227,9 @@ struct ScanArgs {
     const void *queries;
     const uint64_t *qmask;    // nullptr when no filter is applied
     const uint64_t *qmask_pad; // [qpad] copy of qmask padded with zero words (library workspace)
-    const float *invq;        // [qpad]; split f32: query q's is invq[q * invq_stride], q < Q
-    int32_t invq_stride;      // 0: f32 rows are not split
+    const float *invq;        // [qpad] (split f32: q < Q)
+    int32_t split;            // f32 rows go to the matrix cores as two f16 values an element
+    const uint64_t *gate;     // f32 rows: the launch does nothing where this word is zero; nullptr: it always runs
     const uint64_t *thr64;    // [qpad] candidate words below this cannot be in the result
     const float *thrp;        // [qpad] conservative pre-filter on dot * inv_k
     uint64_t *samp;           // sampling pass output [sample tiles][qpad][groups per tile]: see sample_slot_index
@@ -390,7 +403,7 @@ hipError_t launch_scan_wide_bf16(int config, bool sample, int grid, const ScanAr
 hipError_t launch_scan_wide_fp8(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_sp_fp8(int config, bool sample, int grid, const ScanArgs &a, hipStream_t s);
 struct StreamArgs;
-hipError_t launch_stream_f32(const StreamPlan &p, bool dense, bool once, const StreamArgs &a, hipStream_t s);
+hipError_t launch_stream_f32(const StreamPlan &p, bool split, bool once, const StreamArgs &a, hipStream_t s);
 hipError_t launch_stream_bf16(const StreamPlan &p, bool dense, bool once, const StreamArgs &a, hipStream_t s);
 hipError_t launch_stream_fp8(const StreamPlan &p, bool q8, bool dense, bool once, const StreamArgs &a, hipStream_t s);
 

@@ -235,6 +235,9 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void *lds_ptr;
 
+    if constexpr (C::KT == KB_F32 && !SAMPLE && !DRAW && !DENSE) {
+        if (p.gate != nullptr && *p.gate == 0) return;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / C::WN, wn = wave % C::WN;
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb) {
             const int c = q * TQ + rowB + jb * 32;
-            next_inv_q[jb] = p.invq[(size_t)(c < p.Q ? c : p.Q - 1) * p.invq_stride];
+            next_inv_q[jb] = p.invq[c < p.Q ? c : p.Q - 1];
         }
     };
     auto take_scales = [&]() {

@@ -31,6 +31,7 @@ struct StreamArgs {
     int32_t query_stride;               // bytes from query to query in LDS, a multiple of 256
     int32_t side_slots;                 // tiles whose side data can be in flight or in use
     int32_t blocks;                     // workgroups per query block
+    uint64_t *gate;                     // f32 rows: as in ScanArgs; split ones: the word to clear
 };
 
 constexpr int STREAM_RING_16 = 4, STREAM_RING_32 = 3;     // pieces in a wavefront's ring, by the rows of a tile
@@ -88,6 +89,12 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
 {
     constexpr int TR = C::TR, NST = C::NST, NQ = C::NQ, TQ = C::TQ, LOADS = C::LOADS, RB = C::RB, STEPS = C::STEPS;
     constexpr bool SPLIT = C::SPLIT;
+    if constexpr (C::KT == KB_F32) {
+        if (*p.gate == 0) return;
+    }
+    if constexpr (SPLIT) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *p.gate = 0;
+    }
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     typedef __attribute__((address_space(3))) void *lds_ptr;
     const int tid = threadIdx.x, lane = tid & 63, lrow = lane & 31, half = lane >> 5;
@@ -356,7 +363,7 @@ template <class C, bool DENSE, bool NT> hipError_t launch_stream_variant(const S
 }
 template <int KT> hipError_t launch_stream(const StreamPlan &p, bool dense, bool once, const StreamArgs &a, hipStream_t s)
 {
-    if constexpr (KT == KB_F32_SPLIT) {
+    if constexpr (KT == KB_F32_SPLIT || KT == KB_F32) {
         if (dense || p.tq != 32) return hipErrorInvalidValue;        // (no such plan)
     } else {
         if (dense) return launch_stream_variant<StreamCfg<KT, 16, STREAM_RING_16, 1>, true, false>(p, a, s);
