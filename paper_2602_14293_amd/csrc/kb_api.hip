@@ -1281,7 +1281,7 @@ template <int KT, int UNR> __device__ inline f32x16 score_rows(const void *keys,
     const unsigned char *krow = static_cast<const unsigned char *>(keys) + (size_t)my_row * key_row_bytes + half * 16;
     f32x16 acc;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    for (int i = 0; i < 16; ++i) acc[i] = KT == KB_F32_SPLIT ? SPLIT_START : 0.f;
     // The loads of UNR groups go out before their matrix instructions (the order of the accumulation does not
     // change): one memory round trip per UNR groups instead of one per group.
     if constexpr (KT == KB_F32_SPLIT) {
@@ -1626,9 +1626,10 @@ __device__ inline void write_restated(SelectScratch *sc, int m, int q, int k, in
 // Are the k best of the m rows that were scored again the query's results?  They are
 //   if fewer than the `selected` rows asked for were there, as then all that qualify are among them;
 //   if the k-th best f32 score lies above the lowest split score `last` of the selected rows by more than the two can differ: no row that was
-//   not selected has a higher split score, so none has an f32 score that comes near;
+//   not selected has a higher split score, so none has an f32 score that comes near (rows of extraordinary length have higher ones than all
+//   others, and a row whose f32 products overflow has no f32 score);
 //   if the query is zero: all scores are, and the rows were selected by their index.
-// A query whose length is not a number is left to the f32 instruction.
+// A query whose length is not ordinary, or not a number, is left to the f32 instruction.
 __device__ inline bool restated_suffice(int m, int selected, float last, uint64_t kth, float square_sum, int d)
 {
     if (square_sum == 0.f) return m < selected || kth != 0ull;

@@ -83,16 +83,26 @@ constexpr int KB_F32_SPLIT = 4;
 // scale comes from 1/|x| alone, so every kernel has the same; a row without a length (zero, or past the largest float) is taken as zeros.
 //
 // These scores only say which rows are scored again by the f32 instruction, and whether those can be all that count (see restated_suffice).
-__host__ __device__ inline bool f32_ordinary(float inv) { return (as_u32(inv) & 0x7f800000u) != 0u; }
+// For that they must be near the f32 ones, which lengths between 2^-48 and 2^62 ensure: no product of two such rows leaves the
+// range of floats, and what falls out of it below is nothing beside the length.  A row of another length has a score above all others
+// instead, so that it is among those that are scored again; a query of another length is left to the f32 instruction.
+__host__ __device__ inline bool f32_ordinary(float inv)
+{
+    const uint32_t e = as_u32(inv) >> 23 & 255u;
+    return e >= 127u - 62u && e <= 127u + 48u;
+}
 __host__ __device__ inline float f32_row_scale(float inv) { return as_f32(f32_ordinary(inv) ? (as_u32(inv) & 0x7f800000u) + (8u << 23) : 0u); }
 // 1/|x| of the scaled row: the same digits, so dot products of scaled rows end in the score of the rows as they are.  (The removed bit stays.)
+// The products of a row without scale are all SPLIT_START, which this takes to 2^107.
 __host__ __device__ inline float f32_scaled_inv(float inv)
 {
-    const uint32_t u = as_u32(inv);
-    return as_f32(f32_ordinary(inv) ? (u & 0x807fffffu) | 119u << 23 : u);
+    const uint32_t u = as_u32(inv), other = (u & 0x7f800000u) != 0u ? (u & 0x80000000u) | 254u << 23 : u;
+    return as_f32(f32_ordinary(inv) ? (u & 0x807fffffu) | 119u << 23 : other);
 }
+// What their sums begin with: 2^-34 of the product of two scaled lengths, so it is far below the rounding of one product.
+constexpr float SPLIT_START = 0x1p-20f;
 constexpr int SPLIT_MAX_SPARE = 32;         // entries selected beyond the k wanted (see split_spare)
-// The most by which a row's split score and its f32 score differ, u = 2^-24 and in units of the two lengths' product (which
+// The most by which a row's split score and its f32 score differ, lengths as above, u = 2^-24 and in units of the two lengths' product (which
 // no partial sum exceeds):
 //   the f32 chain: one rounding an element, of at most u each                                               d u
 //   the f16 instruction, three for 16 elements: products are exact, adding one loses at most 2 u              6 d u

@@ -227,6 +227,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
     static_assert(!DENSE || !(SAMPLE || WHOLE), "one of the plans");
     constexpr int TK = C::TK, TQ = C::TQ, RBA = C::RBA, RBB = C::RBB, IB = C::IB, JB = C::JB, NW = C::NW;
     constexpr bool SPLIT = C::KT == KB_F32_SPLIT;
+    constexpr float START = SPLIT ? SPLIT_START : 0.f;
     constexpr int LA = C::NIA / NW, LB = C::NIB / NW;           // load instructions per wave per chunk
     constexpr int RSTEP_A = NW * 64 / C::PPRA, RSTEP_B = NW * 64 / C::PPRB;   // rows between a wave's instructions
     static_assert(C::NIA % NW == 0 && C::NIB % NW == 0, "every wave issues the same number of loads");
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[ib][jb][i] = 0.f;
+            for (int i = 0; i < 16; ++i) acc[ib][jb][i] = START;
 
     // split f32: the scales of the wave's rows and queries, asked for with the side data of the item before
     float key_scale[SPLIT ? IB : 1], query_scale[SPLIT ? JB : 1], next_inv_k[SPLIT ? IB : 1], next_inv_q[SPLIT ? JB : 1];
@@ -548,7 +549,7 @@ __global__ __launch_bounds__(C::THREADS, C::WGPC) void kb_scan_kernel(ScanArgs p
 #pragma unroll
                 for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[ib][jb][i] = 0.f;
+                    for (int i = 0; i < 16; ++i) acc[ib][jb][i] = START;
             c = 0;
             tile += step_tile;
             qb += step_qb;

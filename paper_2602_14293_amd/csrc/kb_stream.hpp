@@ -265,7 +265,7 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
 #pragma unroll
         for (int jb = 0; jb < NQ; ++jb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[0][jb][i] = 0.f;
+            for (int i = 0; i < 16; ++i) acc[0][jb][i] = SPLIT ? SPLIT_START : 0.f;
     };
     clear();
 #pragma unroll

@@ -83,6 +83,50 @@ def test_close_rows_at_the_last_place_of_a_large_k(N, d, Q, config, k):
     kb.close()
 
 
+# Rows whose squared length is past the largest float: their products are finite or overflow, which leaves no number; queries of that kind, and
+# zero queries and rows.  Few entries qualify, so these are among the ones selected.
+@pytest.mark.parametrize("shape", SHAPES)
+def test_lengths_that_are_no_number(shape):
+    N, d, Q, config = shape
+    rows, q, g = _rows(N, d, Q, 5)
+    rows[::2] *= 1e30
+    rows[1::4] *= -1.0
+    rows[7::500] = 0
+    q[1::4] *= 1e30
+    q[2::8] = 0
+    tags = torch.ones(N, dtype=torch.int64, device="cuda")
+    tags[torch.randperm(N, generator=g, device="cuda")[:30]] = 2
+    qmask = torch.full((Q,), 2, dtype=torch.int64, device="cuda")
+    qmask[::3] = 1
+    kb = _store(rows, tags)
+    for k in (1, 10, 32):
+        got = _check(kb, q, k, config, qmask)
+        assert int((got[0][:3] >= 0).sum()) > 0
+        _check(kb, q, k, config)
+    kb.close()
+
+
+# Lengths at both ends of what counts as ordinary and beyond: rows alone, queries alone, both
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("row_exp,query_exp", [((-74, -40), (0, 0)), ((55, 63), (0, 0)), ((0, 0), (-74, -40)), ((0, 0), (55, 63)), ((-74, 63), (-74, 63))])
+def test_lengths_out_of_the_ordinary(shape, row_exp, query_exp):
+    N, d, Q, config = shape
+    rows, q, g = _rows(N, d, Q, 6)
+
+    def scaled(x, lo, hi, part):
+        x /= x.norm(dim=1, keepdim=True)
+        e = torch.randint(lo, hi + 1, (x.shape[0], 1), generator=g, device="cuda").double()
+        e[torch.rand(e.shape, generator=g, device="cuda") > part] = 0
+        return (x.double() * torch.exp2(e)).float()
+
+    rows, q = scaled(rows, *row_exp, 0.01), scaled(q, *query_exp, 0.5)
+    q[0] = rows[17] / rows[17].norm().clamp_min(1e-38)
+    kb = _store(rows)
+    for k in (1, 10, 32):
+        _check(kb, q, k, config)
+    kb.close()
+
+
 # A call that the f32 instruction has to do again, in a graph: replayed on other queries, some of which need it
 @pytest.mark.parametrize("shape", SHAPES)
 def test_in_a_graph(shape):
