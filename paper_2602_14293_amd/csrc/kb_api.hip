@@ -507,6 +507,34 @@ bool two_blocks_stream(const kb *h, int64_t n, bool q8, int32_t waves_per_block)
     if (n > WHOLE_MAX_ROWS_FEW && h->d < (q8 ? 256 : 128)) return false;
     return !q8 || n > WHOLE_MAX_GROUPS * 32;
 }
+// Up to 32 queries, the whole-store plan: this scan against the plan without it, one store for both.  us a call, without | with:
+//   rows of a multiple of 4 KB: a piece of every row lies on the same few channels, and the wavefronts, which begin together, are at one piece
+//     bf16 x 2048, 1 query    40,000 rows 46.7 | 44.4    60,000 58.8 | 60.6    100,000 89.1 | 98.1    200,000 136 | 196    400,000 310 | 329
+//     bf16 x 4096, 8 queries  40,000 rows 75.7 | 73.9    60,000 94.5 | 124     fp8 x 4096  50,000 62.2 | 60.1    60,000 69.6 | 79.4
+//   rows of 64 bytes in large stores: the search of the products is longer than their stream (8 masked queries)
+//     fp8    150,000 rows: 0.95 of the speed, 260,000: 0.94    340,000 31.5 | 24.9    600,000 35.4 | 33.8    1,000,000 39.6 | 47.2
+//     fp8 x fp8    150,000 rows: 1.18    340,000 29.7 | 24.0    600,000 34.3 | 32.8    1,000,000 40.5 | 45.0
+//   few tiles a compute unit: long rows are a chain of loads of a wavefront's, and where queries are so long that fewer than eight wavefronts have
+//   room, so is a last round of few tiles.  Time without over with it, by tiles a compute unit:
+//     bf16 x 1024 to 1536, 8 masked queries   2.1 1.02    2.3-4 0.94 to 0.99    4.1-5 1.0 to 1.16    more 0.95 to 1.1     (1 query, 20: 0.98 to 1.03 at 2.3-4)
+//     bf16 x 1536, 32 queries, five wavefronts  2-4 0.83 to 0.96    4.1 1.22    4.6 1.12    5.5-8 0.90 to 0.96    8.5-9.4 1.09, 1.04    10-11.6 0.93    12-32 1.0 to 1.12
+//     bf16 x 1024, 32 queries, seven            2-4 0.86 to 0.99    4.1 1.08    4.6-7 0.95 to 1.01    8 0.93    8.5-11 0.97 to 1.03    12-32 1.02 to 1.22
+//     fp8 x 1280, 8 to 32 queries               2-5 1.02 to 1.09    5.5-8 0.94 to 0.98  (x 1024: 0.96 to 1.0, x 2048: 1.0 to 1.1)      more 1.03 to 1.2
+//     fp8 x 1536, 32 queries, five              2-4 0.96 to 1.07    4.1 1.08    4.6 0.99    5.5-7 0.83 to 0.90    8 0.99     8.5-9.4 1.24, 1.14    10-11 0.99    12-32 1.02 to 1.13
+//     fp8 x 2048, 20 queries, six               2-5 1.03 to 1.15    6.2-8 0.94 to 0.96                  8.5-16 1.09 to 1.2
+//   and, of these, the largest stores, where groups of 256 rows leave four or five wavefronts: fp8 1,000,000 x 1024, 32 queries 180 | 196 (bf16 323 | 311).
+// (fp8 x fp8 gains in all of these.)  Elsewhere 0.96 to 1.15; what loses there are masked calls on bf16 rows of 1.5 to 2 KB, 45,000 to 95,000 of them.
+bool one_block_stream(const kb *h, int64_t n, bool q8, const StreamPlan &p)
+{
+    const int64_t row_bytes = (int64_t)h->d * key_bytes(h->dtype), tiles = ceil_div(p.units, DEVICE_CUS), w = p.waves_per_block;
+    if (row_bytes % 4096 == 0 && n > 48 << 10) return false;
+    if (row_bytes == 64 && (n > 640 << 10 || (!q8 && n > WHOLE_MAX_GROUPS * 32 && n <= WHOLE_MAX_ROWS_FEW))) return false;
+    if (q8) return true;
+    if (n > WHOLE_MAX_ROWS_FEW) return h->dtype == KB_BF16 || w == 8 || n <= 896 << 10;
+    if (h->dtype == KB_BF16 && row_bytes >= 2048 && tiles > 2 && tiles <= 4 && (w < 8 || n > 18 << 10)) return false;
+    if (h->dtype == KB_FP8_E4M3 && row_bytes >= 1024 && row_bytes < 2048 && tiles > 5 && tiles <= 8) return false;
+    return w == 8 || (!(tiles > w && tiles <= 8) && !(tiles > 2 * w && tiles <= 12));
+}
 bool make_stream_plan(const kb *h, int64_t n, int32_t Q, bool q8, bool split, bool dense, int64_t most_groups, StreamPlan *out)
 {
     if ((h->dtype == KB_F32 && !split) || Q > (split ? 32 : dense ? INT32_MAX : 64)) return false;
@@ -533,7 +561,7 @@ bool make_stream_plan(const kb *h, int64_t n, int32_t Q, bool q8, bool split, bo
         p.per_group = (int32_t)ceil_div(layers, room);
         if (!dense && p.per_group * p.tr > 256) continue;
         *out = p;
-        return dense || Q <= 32 || two_blocks_stream(h, n, q8, p.waves_per_block);
+        return dense || (Q <= 32 ? one_block_stream(h, n, q8, p) : two_blocks_stream(h, n, q8, p.waves_per_block));
     }
     return false;
 }

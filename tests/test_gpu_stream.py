@@ -109,3 +109,33 @@ def test_few_groups_where_there_is_little_memory(kind, N, d, Q, k):
     torch.cuda.synchronize()
     _same((oi, os_), want, f"{kind} N={N}")
     kb.close()
+
+
+# Where the plan without this scan is the faster one (its workgroups are as many as its tiles up to 512, or there is a sampling pass; this scan has
+# 256), and the sizes beside: rows of a multiple of 4 KB, of 64 bytes in large stores, few tiles a compute unit
+@pytest.mark.parametrize("kind,N,d,Q,workgroups", [
+    ("bf16", 48 << 10, 2048, 8, 256), ("bf16", (48 << 10) + 1, 2048, 8, 385), ("fp8", 60000, 4096, 2, 469), ("q8", 60000, 4096, 2, 469), ("bf16", 60000, 3072, 8, 256),
+    ("fp8", 1 << 17, 64, 8, 256), ("fp8", (1 << 17) + 1, 64, 8, 512), ("fp8", 327681, 64, 8, 256), ("fp8", 700000, 64, 8, None), ("q8", 150000, 64, 8, 256), ("q8", 700000, 64, 8, None),
+    ("bf16", 20000, 1024, 8, 157), ("bf16", 17000, 1024, 8, 256), ("bf16", 17000, 1024, 32, 133), ("bf16", 20000, 768, 8, 256), ("bf16", 33000, 1024, 32, 256),
+    ("bf16", 45000, 1536, 32, 352), ("bf16", 38000, 1536, 32, 256), ("bf16", 92000, 1536, 32, 512), ("bf16", 70000, 1536, 32, 256),
+    ("fp8", 45000, 1280, 8, 352), ("fp8", 40000, 1280, 8, 256), ("q8", 45000, 1280, 8, 256), ("fp8", 917504, 1024, 32, 256), ("fp8", 917505, 1024, 32, None)])
+def test_where_the_queries_in_lds_lose(kind, N, d, Q, workgroups):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    rows, q = torch.randn((N, d), generator=g, device="cuda", dtype=torch.bfloat16), torch.randn((Q, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    scale = None
+    if kind != "bf16":
+        rows, scale = kbmod.quantize_rows(rows)
+        q = kbmod.quantize_rows(q)[0] if kind == "q8" else q
+    kb = kbmod.KnowledgeBase(d, kbmod.KB_BF16 if kind == "bf16" else kbmod.KB_FP8_E4M3, N)
+    kb.append(rows, scale)
+    kb.normalize()
+    got = kb.query(q, 10)
+    said = kb.counters()
+    if workgroups is None:
+        assert said["sample_keys"] > 0
+    else:
+        assert said["sample_keys"] == 0 and said["scan_workgroups"] == workgroups
+    kb.set_tuning("small_path", 0)
+    _same(got, kb.query(q, 10), f"{kind} N={N} d={d} Q={Q}")
+    kb.close()
