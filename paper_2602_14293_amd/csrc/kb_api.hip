@@ -429,6 +429,8 @@ void plan_for(const kb *h, const Choice &c, int64_t n, int32_t Q, int32_t k, boo
 //   1,000,003 x 256 bf16, 32 queries   1.11 to 1.38 (108 us, 95)     900,000 x 512 fp8, 8        1.10 to 1.35 (100 us, 90)
 //   700,000 x 320 fp8 x 8, 20 queries  1.21 to 1.86 (60 us, 49)     320,000 x 128 bf16, 64         1.33 to 2.10 (47 us, 34)
 //   1,000,003 x 256 bf16, 40 queries   1.16 to 1.50 (115 us, 99)    700,000 x 512 fp8, 48          1.45 to 1.62 (133 us, 91)
+// (4096 groups of 256 rows hold one row more.  That store, the size of the large shared ones here, keeps the plan with a sampling pass that callers of
+// kb_query_plan know for it: 1.02 to 1.2 times as long, bf16 x 1024 and 1 query 334 us, 315 with this plan.)
 constexpr int64_t WHOLE_MAX_ROWS_STREAM = (1 << 20) - 1;
 constexpr int64_t WHOLE_MAX_ROWS_FEW = 5 * 128 * 2 * DEVICE_CUS, WHOLE_MAX_ROWS = 3 * 128 * 2 * DEVICE_CUS;     // up to 32 queries; up to 128
 // More than 128 queries: every product costs the epilogue the same, while the pipeline's scan gets better with larger query
@@ -499,11 +501,19 @@ bool split_f32(const kb *h, int64_t n, int32_t Q, int32_t k, bool draw)
 //                            320,000 x 128 36.3 | 35.1   420,000 x 128 32.3 | 33.7    700,000 x 512 107 | 85.6    1,000,000 x 768 187 | 138, x 64 44.8 | 59.9
 //   bf16                     30,000 x 768 18.8 | 24.1    45,000 x 256 15.8 | 15.5     90,000 x 512 32.8 | 31.4    120,000 x 256 25.9 | 24.0
 //                            131,000 x 768, five wavefronts 56.5 | 57.9               200,000 x 512 69.0 | 52.5    420,000 x 128 51.0 | 39.4    1,000,000 x 256 119 | 109
+//   and, one store for both: bf16 65,536 x 768, 40 queries, whose eight tiles a compute unit seven wavefronts take in two rounds 0.87 of the speed; 1,000,000 x 768
+//   and 1024, where groups of 256 rows leave four of seven wavefronts 0.97; rows of 128 bytes in the largest stores, where every product meets its mask and those of
+//   the pipeline only if they pass: masked | not   bf16 x 64  700,000 rows 0.94 | 1.08    1,000,000 0.88 to 0.93 | 1.03 to 1.07    fp8 x 128  800,000 0.98 | 1.10    1,000,000 0.95 | 1.06
 // What loses: tiles so few that the tiled kernel has more wavefronts a compute unit; rows so short that the search of the products is what takes the
 // time in stores of many.  (In between tiled fp8 x fp8 scans need no conversions, and the pipeline they give way to begins at 131,072 rows.)
 bool two_blocks_stream(const kb *h, int64_t n, bool q8, int32_t waves_per_block)
 {
-    if (h->dtype == KB_BF16) return n > WHOLE_MAX_ROWS || (n >= 32 * 8 * DEVICE_CUS && waves_per_block >= 7);
+    const int64_t row_bytes = (int64_t)h->d * key_bytes(h->dtype), eight_tiles = 32 * 8 * DEVICE_CUS;
+    if (row_bytes == 128 && !q8 && n > (h->dtype == KB_BF16 ? 768 : 896) << 10) return false;
+    if (h->dtype == KB_BF16) {
+        if (waves_per_block < 8 && n > 896 << 10) return false;
+        return n > WHOLE_MAX_ROWS || (waves_per_block >= 7 && n > eight_tiles) || (waves_per_block == 8 && n == eight_tiles);
+    }
     if (n > WHOLE_MAX_ROWS_FEW && h->d < (q8 ? 256 : 128)) return false;
     return !q8 || n > WHOLE_MAX_GROUPS * 32;
 }

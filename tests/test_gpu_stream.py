@@ -118,7 +118,11 @@ def test_few_groups_where_there_is_little_memory(kind, N, d, Q, k):
     ("fp8", 1 << 17, 64, 8, 256), ("fp8", (1 << 17) + 1, 64, 8, 512), ("fp8", 327681, 64, 8, 256), ("fp8", 700000, 64, 8, None), ("q8", 150000, 64, 8, 256), ("q8", 700000, 64, 8, None),
     ("bf16", 20000, 1024, 8, 157), ("bf16", 17000, 1024, 8, 256), ("bf16", 17000, 1024, 32, 133), ("bf16", 20000, 768, 8, 256), ("bf16", 33000, 1024, 32, 256),
     ("bf16", 45000, 1536, 32, 352), ("bf16", 38000, 1536, 32, 256), ("bf16", 92000, 1536, 32, 512), ("bf16", 70000, 1536, 32, 256),
-    ("fp8", 45000, 1280, 8, 352), ("fp8", 40000, 1280, 8, 256), ("q8", 45000, 1280, 8, 256), ("fp8", 917504, 1024, 32, 256), ("fp8", 917505, 1024, 32, None)])
+    ("fp8", 45000, 1280, 8, 352), ("fp8", 40000, 1280, 8, 256), ("q8", 45000, 1280, 8, 256), ("fp8", 917504, 1024, 32, 256), ("fp8", 917505, 1024, 32, None),
+    # two blocks of queries
+    ("bf16", 65536, 768, 40, 512), ("bf16", 65537, 768, 40, 256), ("bf16", 65536, 512, 40, 256), ("bf16", 786432, 64, 40, 256), ("bf16", 786433, 64, 40, None),
+    ("bf16", 917504, 768, 40, 256), ("bf16", 917505, 768, 40, None), ("fp8", 917505, 128, 40, None), ("q8", 917505, 256, 40, 256), ("bf16", (1 << 20) - 1, 128, 64, 256),
+    ("bf16", 1 << 20, 128, 64, None)])
 def test_where_the_queries_in_lds_lose(kind, N, d, Q, workgroups):
     g = torch.Generator(device="cuda")
     g.manual_seed(3)
