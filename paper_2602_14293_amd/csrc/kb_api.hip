@@ -2469,7 +2469,8 @@ kb_status_t kb_append(kb_t *kb, const void *rows_dev, const float *row_scale_dev
         return within_reach(to, alignment, bytes) && within_reach(from, alignment, bytes);
     };
     const bool several = (int)rows_move + (scale_to != nullptr) + (tags_to != nullptr) > 1;
-    const bool direct = several && (!rows_move || reached(dst, rows_dev, 16, row_bytes * n)) && (!scale_to || reached(scale_to, row_scale_dev, 4, sizeof(float) * n)) &&
+    // (not with an error of the caller's pending, which the checks and the launch would take for theirs: a copy says itself how it went)
+    const bool direct = several && hipPeekAtLastError() == hipSuccess && (!rows_move || reached(dst, rows_dev, 16, row_bytes * n)) && (!scale_to || reached(scale_to, row_scale_dev, 4, sizeof(float) * n)) &&
                         (!tags_to || reached(tags_to, tags_dev, 8, sizeof(uint64_t) * n));
     if (direct) {
         AppendArgs a;

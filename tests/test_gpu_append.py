@@ -1,4 +1,6 @@
 """kb_append moves rows, scales and tags in one launch where it can read them, and by copies of the runtime where it cannot."""
+import ctypes
+
 import pytest
 import torch
 
@@ -63,4 +65,45 @@ def test_append_in_a_graph(d):
         torch.cuda.synchronize()
         assert bool((kb.keys[:n] == again + 1).all()) and bool((kb.keys[n:] == 0).all())
         assert bool((kb.tags[:n] == again + 11).all()) and bool((kb.tags[n:] == 0).all())
+    kb.close()
+
+
+# the launch takes rows at 16 bytes, scales and tags at their own alignment; rows that lie where they belong already, scales and tags that do not
+@pytest.mark.parametrize("n", [1, 255, 257, 4099])
+@pytest.mark.parametrize("rows_shift,scale_shift,tag_shift,in_place", [(0, 1, 0, False), (0, 3, 1, False), (0, 0, 1, False), (1, 0, 0, False), (0, 0, 0, True), (0, 1, 1, True)])
+def test_each_source_at_its_own_alignment(n, rows_shift, scale_shift, tag_shift, in_place):
+    d = 192
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    kb = kbmod.KnowledgeBase(d, kbmod.KB_FP8_E4M3, 2 * n + 3, tagged=True)
+    for part in range(2):
+        x, s = kbmod.quantize_rows(torch.randn((n, d), generator=g, device="cuda"))
+        t = torch.randint(0, 1 << 62, (n,), generator=g, device="cuda")
+        at = slice(part * n, (part + 1) * n)
+        if in_place:
+            kb.keys[at].view(torch.uint8).copy_(x.view(torch.uint8))
+        rows = kb.keys[at] if in_place else _at(x.view(torch.uint8), rows_shift * 8).view(x.dtype)
+        assert kb.append(rows, _at(s, scale_shift), _at(t, tag_shift)) == part * n
+        torch.cuda.synchronize()
+        assert torch.equal(kb.keys[at].view(torch.uint8), x.view(torch.uint8)) and torch.equal(kb.scale[at], s) and torch.equal(kb.tags[at], t)
+    assert kb.size == 2 * n and bool((kb.tags[2 * n:] == 0).all())
+    kb.close()
+
+
+# an error of the caller's that nobody has asked for yet is not taken for one of the append's, and is still there afterwards
+def test_a_pending_error_of_the_caller():
+    hip = ctypes.CDLL("libamdhip64.so")
+    kb = kbmod.KnowledgeBase(64, kbmod.KB_BF16, 300, tagged=True)
+    x, t = torch.ones((300, 64), dtype=torch.bfloat16, device="cuda"), torch.arange(300, device="cuda")
+    torch.cuda.synchronize()
+    hip.hipGetLastError()
+    pending = hip.hipSetDevice(4096)         # no such device
+    try:
+        assert pending != 0 and hip.hipPeekAtLastError() == pending
+        assert kb.append(x, tags=t) == 0 and kb.size == 300
+        assert hip.hipPeekAtLastError() == pending
+    finally:
+        hip.hipGetLastError()
+    torch.cuda.synchronize()
+    assert torch.equal(kb.keys, x) and torch.equal(kb.tags, t)
     kb.close()
