@@ -1784,7 +1784,7 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
     // row at a place of the tile of group g (the groups of a tile follow each other)
     const uint32_t per_tile = STREAM ? 1u : (uint32_t)a.tile_rows / (uint32_t)a.group_rows;
     auto row_at = [&](uint32_t g, uint32_t place) {
-        if constexpr (STREAM) return (uint32_t)stream_group_row(a.tile_rows, a.tiles, a.waves, a.per_group, g, place);
+        if constexpr (STREAM) return (uint32_t)stream_group_row(a.tiles, a.waves, a.per_group, g, place);
         else return (uint32_t)whole_row((int32_t)(g / per_tile), a.tiles, a.tile_rows, (int)place);
     };
     auto first_place = [&](uint32_t g) { return STREAM ? 0u : g % per_tile * (uint32_t)a.group_rows; };

@@ -595,8 +595,7 @@ template <class C> hipError_t launch_whole_cfg(int grid, const ScanArgs &a, hipS
 // the scan of the dense plan
 template <class C> hipError_t launch_dense_cfg(int grid, const ScanArgs &a, hipStream_t s)
 {
-    if constexpr (C::KT == KB_F32_SPLIT) return a.draw.enabled ? hipErrorInvalidValue : launch_scan_variant<C, false, false, false, false, true>(grid, a, s);
-    else return a.draw.enabled ? launch_scan_variant<C, false, true, false, false, true>(grid, a, s) : launch_scan_variant<C, false, false, false, false, true>(grid, a, s);
+    return a.draw.enabled ? launch_scan_variant<C, false, true, false, false, true>(grid, a, s) : launch_scan_variant<C, false, false, false, false, true>(grid, a, s);
 }
 
 // configurations of these two plans only: the smallest tiles take both (fp8 queries: the dense one), larger ones the whole-store plan
@@ -613,7 +612,7 @@ template <class C> hipError_t launch_unfiltered_cfg(int grid, const ScanArgs &a,
 template <class C> hipError_t launch_scan_cfg(bool sample, int grid, const ScanArgs &a, hipStream_t s)
 {
     if (a.dense) {
-        if constexpr (C::TQ <= 128) return launch_dense_cfg<C>(grid, a, s);
+        if constexpr (C::TQ <= 128 && C::KT != KB_F32_SPLIT) return launch_dense_cfg<C>(grid, a, s);
         return hipErrorInvalidValue;
     }
     if (a.whole_best) {

@@ -64,12 +64,13 @@ __host__ __device__ inline int32_t stream_row(int32_t base, int32_t w, int32_t c
     return base + pos * c + t;
 }
 // Row at a place of a group (past the store's end: none).
-__host__ __device__ inline int64_t stream_group_row(int32_t tr, int32_t units, int32_t waves, int32_t per_group, uint32_t group, uint32_t place)
+constexpr int STREAM_GROUP_TILE = 32;        // rows of a tile where groups are kept
+__host__ __device__ inline int64_t stream_group_row(int32_t units, int32_t waves, int32_t per_group, uint32_t group, uint32_t place)
 {
     const uint32_t first = group / (uint32_t)waves, w = group - first * (uint32_t)waves;
-    const int32_t layer = (int32_t)first * per_group + (int32_t)(place >> (tr == 16 ? 4 : 5));
+    const int32_t layer = (int32_t)first * per_group + (int32_t)(place / (uint32_t)STREAM_GROUP_TILE);
     const int32_t left = units - layer * waves, c = left < waves ? left : waves;
-    return (int32_t)w < c ? stream_row(layer * waves * tr, (int32_t)w, c, stream_step(c), (int)(place & (uint32_t)(tr - 1))) : (int64_t)0x7fffffff;
+    return (int32_t)w < c ? stream_row(layer * waves * STREAM_GROUP_TILE, (int32_t)w, c, stream_step(c), (int)(place % (uint32_t)STREAM_GROUP_TILE)) : (int64_t)0x7fffffff;
 }
 
 // Waits for a piece of a ring behind which `younger` pieces have been asked for, up to MOST of them: it has landed once at most
@@ -89,6 +90,7 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
 {
     constexpr int TR = C::TR, NST = C::NST, NQ = C::NQ, TQ = C::TQ, LOADS = C::LOADS, RB = C::RB, STEPS = C::STEPS;
     constexpr bool SPLIT = C::SPLIT;
+    static_assert(DENSE || TR == STREAM_GROUP_TILE, "groups of whole tiles");
     if constexpr (C::KT == KB_F32) {
         if (*p.gate == 0) return;
     }
@@ -321,7 +323,7 @@ template <class C, bool DENSE, bool NT> __global__ __launch_bounds__(512, 2) voi
                 if (q0 + lrow < p.Q) *reinterpret_cast<f32x4 *>(p.best + (size_t)(q0 + lrow) * p.groups + row0 + rl) = v;
             }
         } else {
-            const uint32_t dead = (uint32_t)__builtin_amdgcn_ballot_w64(lane >= TR || row_removed(sd.invk[lane & (TR - 1)]) || row_of(layer, lane & (TR - 1)) >= p.n);
+            const uint32_t dead = (uint32_t)__builtin_amdgcn_ballot_w64(row_removed(sd.invk[lrow]) || row_of(layer, lrow) >= p.n);
             const uint32_t place0 = (uint32_t)(in_group * TR);
             const bool ends = in_group + 1 == p.per_group || g + 1 == total;
             const size_t group = (size_t)(layer / p.per_group) * (uint32_t)p.waves + (uint32_t)w;
