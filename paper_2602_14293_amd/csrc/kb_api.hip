@@ -460,8 +460,11 @@ int64_t whole_max_rows(const kb *h, int32_t Q, bool q8)
 constexpr int64_t WHOLE_SMALL_TILE_ROWS = 128 * DEVICE_CUS / 2;      // up to 32 queries: tiles of 16 or 32 rows up to here
 // Calls on f32 rows whose scan takes two f16 values an element (Mma<KB_F32_SPLIT>).  They select a few entries more than k by the split
 // products; the launch that selects scores these again by the f32 instruction's chain (restate) and knows from the bound on the difference
-// (split_error) whether another row could belong to the best k.  Where it could, for any query, two more launches do the call's
-// scan and selection with the f32 instruction: they are always there and leave at once otherwise.  So results don't depend on the path.
+// (split_error) whether another row could belong to the best k.  Where it could, it scores all rows again that are near enough, up to some 200.  Where
+// they are more, for any query, two more launches do the call's scan and selection with the f32 instruction: they are always there and
+// leave at once otherwise.  So results don't depend on the path.  us a call, f32 instruction | split, half of the queries near rows that are copies of one:
+//   300,007 x 384, Q 20, k 10    no copies 98 | 93    30 102 | 105    100 99 | 120    1000 105 | 207     60,000 x 768, Q 128, k 16    120 | 90   115 | 98   115 | 114   135 | 244
+//   600,000 x 128, Q 20, k 32    91 | 72    92 | 72    92 | 91    99 | 166    150,000 2256 | 265         400,000 x 512, Q 200, k 32    932 | 473   930 | 467   932 | 486   923 | 1316
 // That takes a call some 8 us with few queries (the rows of the selected entries in LDS at once; more with k) and 10 to 15 with many, so it is for
 // calls whose scan is long enough.  us a call, f32 instruction | split:
 //   up to 32 queries (kb_stream.hpp, eight wavefronts)     300,007 x 384, Q 20  97.8 | 93.3    200,000 x 768, Q 16  126 | 119     300,000 x 768, Q 18  181 | 166
@@ -1636,25 +1639,26 @@ __device__ inline void restate(uint64_t *words, int m, const void *keys, const f
     }
     __syncthreads();
 }
-// LDS for the rows of k entries beside what the selecting kernels have (their buffers of 32 KB, in several rounds, where more queries than
-// compute units would wait for each other)
-int restate_lds(int32_t Q, int32_t k, int32_t d)
-{
-    const int64_t want = ((int64_t)(k + 1) * (d + 4) * 4 + 1023) / 1024 * 1024;
-    return Q > DEVICE_CUS ? 0 : (int)std::min<int64_t>(want, RESTATE_LDS);
-}
-// ... and the best k of them to the query's place in the output; *kth: the k-th, zero where there is none (zero before the call, to be read behind a barrier)
-__device__ inline void write_restated(SelectScratch *sc, int m, int q, int k, int32_t *out_index, float *out_score, uint64_t *kth)
+// LDS for these rows beside what the selecting kernels have (their own buffers, in several rounds, where more queries than compute units would wait
+// for each other)
+int restate_lds(int32_t Q) { return Q > DEVICE_CUS ? 0 : RESTATE_LDS; }
+// ... the place of thread tid's word among them, and the best k of them to the query's place in the output.
+__device__ inline int restated_rank(const uint64_t *words, int m)
 {
     const int tid = threadIdx.x;
-    const uint64_t e = tid < m ? sc->sel[tid] : 0ull;
+    const uint64_t e = tid < m ? words[tid] : 0ull;
     int rank = 0;
 #pragma unroll 8
-    for (int j = 0; j < m; ++j) rank += sc->sel[j] > e || (e == 0ull && j < tid);       // (words without a score come last, as nothing)
+    for (int j = 0; j < m; ++j) rank += words[j] > e || (e == 0ull && j < tid);       // (words without a score come last, as nothing)
+    return rank;
+}
+__device__ inline void write_restated(const uint64_t *words, int m, int rank, int q, int k, int32_t *out_index, float *out_score)
+{
+    const int tid = threadIdx.x;
+    const uint64_t e = tid < m ? words[tid] : 0ull;
     if (tid < m && rank < k) {
         out_index[(size_t)q * k + rank] = e ? (int32_t)candidate_index(e) : -1;
         out_score[(size_t)q * k + rank] = e ? candidate_score(e) : -__builtin_inff();
-        if (rank == k - 1) *kth = e;
     }
     if (tid >= m && tid < k) {
         out_index[(size_t)q * k + tid] = -1;
@@ -1674,6 +1678,9 @@ __device__ inline bool restated_suffice(int m, int selected, float last, uint64_
     if (!f32_ordinary(inv_norm_of(square_sum))) return false;
     return m < selected || (kth != 0ull && candidate_score(kth) > last + split_error(d));
 }
+// Where they are not, the rows whose split score is no further than that below the k-th f32 score are all that count.  If they are known and no
+// more than these, they are scored again as well: a handful of copies of a row take a call 10 us longer and not the f32 instruction's scan.
+constexpr int RESTATE_AGAIN = 256;
 
 // The best k of the `have` words of `buf` go to sc->sel (256 threads, converged); returns how many there are.
 __device__ __forceinline__ int best_to_scratch(uint64_t *buf, uint32_t have, int k, SelectScratch *sc)
@@ -1765,6 +1772,12 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
     }
     for (int i = tid; i < WHOLE_BINS; i += nt) kth.hist[i] = 0u;
     __syncthreads();
+    if constexpr (KT == KB_F32_SPLIT) {        // (all scores of a zero query tie, so every group would be scored again)
+        if (!f32_ordinary(inv_norm_of(sh_square))) {
+            if (tid == 0) *a.gate = 1;
+            return;
+        }
+    }
     const float iq = sh_iq;
     // score that no row behind a group's product exceeds (infinite products, of a query too long for its length to be a number, have
     // none themselves but stand for finite ones too)
@@ -1883,11 +1896,46 @@ template <int KT, int PER, bool STREAM> __global__ __launch_bounds__(WHOLE_THREA
     }
     if constexpr (KT == KB_F32_SPLIT) {
         const int m = best_to_scratch(buf, have, k, &sc);
-        const float last = m == k ? candidate_score(sc.sel[k - 1]) : NONE;
-        restate(sc.sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, inv_norm_of(sh_square), a.more_lds ? reinterpret_cast<float *>(more_lds) : reinterpret_cast<float *>(buf), a.more_lds ? a.more_lds : (int)sizeof buf);
-        write_restated(&sc, m, q, a.k_out, a.out_index, a.out_score, &sh_kth);
+        const float last = m == k ? candidate_score(sc.sel[k - 1]) : NONE, inv = inv_norm_of(sh_square);
+        const float *query = static_cast<const float *>(a.queries) + (size_t)q * a.d;
+        float *stage = a.more_lds ? reinterpret_cast<float *>(more_lds) : reinterpret_cast<float *>(buf + RESTATE_AGAIN);
+        const int stage_bytes = a.more_lds ? a.more_lds : (int)(sizeof buf - sizeof(uint64_t) * RESTATE_AGAIN);
+        restate(sc.sel, m, a.keys, a.inv_norm, query, a.d, inv, stage, stage_bytes);
+        int rank = restated_rank(sc.sel, m);
+        if (tid < m && rank == a.k_out - 1) sh_kth = sc.sel[tid];
         __syncthreads();
-        if (tid == 0 && !restated_suffice(m, k, last, sh_kth, sh_square, a.d)) *a.gate = 1;
+        bool done = restated_suffice(m, k, last, sh_kth, sh_square, a.d);       // (uniform)
+        if (done) {
+            write_restated(sc.sel, m, rank, q, a.k_out, a.out_index, a.out_score);
+        } else if (sh_kth != 0ull) {
+            const float reach = candidate_score(sh_kth) - split_error(a.d);
+            if (tid == 0) sh_cnt = sh_again = 0;
+            __syncthreads();
+            auto put = [&](float product, uint32_t row) {
+                const float f = product * iq + 0.0f;
+                if (!(f >= reach)) return;
+                const uint32_t at = atomicAdd(&sh_cnt, 1u);
+                if (at < (uint32_t)RESTATE_AGAIN) buf[at] = pack_candidate(f, row);
+            };
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                if (!(u < rounds && v[u] >= reach)) continue;
+                const uint32_t g = (uint32_t)(tid + u * nt);
+                const u32x4 x = pair[g];
+                put(best[g], row_at(g, x[2] & 255u));
+                put(as_f32(x[0]), row_at(g, x[2] >> 8 & 255u));
+                if (as_f32(x[1]) > NONE && score_bound(as_f32(x[1])) >= reach) sh_again = 1;        // (a row that is not known may be one of them)
+            }
+            __syncthreads();
+            const uint32_t n = sh_cnt;
+            done = sh_again == 0 && n <= (uint32_t)RESTATE_AGAIN;
+            if (done) {
+                restate(buf, (int)n, a.keys, a.inv_norm, query, a.d, inv, stage, stage_bytes);
+                rank = restated_rank(buf, (int)n);
+                write_restated(buf, (int)n, rank, q, a.k_out, a.out_index, a.out_score);
+            }
+        }
+        if (tid == 0 && !done) *a.gate = 1;
     } else write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
 }
 
@@ -1980,6 +2028,60 @@ template <int QT, bool KEYS, int PIECES> __global__ __launch_bounds__(DENSE_THRE
     write_best(buf, have, q, k, a.out_index, a.out_score, &sc);
 }
 
+// Split f32, a list's rows: buf[0..a.k) are the best by the split products, in order.  best_again(word): the best SELECT_MAX of those
+// that are not below the word, to buf in order.
+template <class AGAIN> __device__ __forceinline__ void finish_split(const FinalArgs &a, int q, uint64_t *buf, SelectScratch *sc, unsigned char *smem_raw, uint64_t t64, AGAIN best_again)
+{
+    __shared__ float sh_square;
+    __shared__ uint64_t sh_kth;
+    const int tid = threadIdx.x;
+    const float *query = static_cast<const float *>(a.queries) + (size_t)q * a.d;
+    float *stage = reinterpret_cast<float *>(a.more_lds ? smem_raw + a.more_at : smem_raw);
+    const int stage_bytes = a.more_lds ? a.more_lds : a.cand_cap * 8;
+    if (tid < 64) {
+        const float square_sum = row_square_sum<KB_F32>(a.queries, q, a.d * 4, tid);
+        if (tid == 0) {
+            sh_square = square_sum;
+            sh_kth = 0;
+        }
+    }
+    int rank = 0;
+    float last = 0.f, inv = 0.f;
+    auto again = [&](int most) {        // scores the best `most` of buf again; returns how many there are
+        const uint64_t cw = tid < most ? buf[tid] : 0ull;
+        if (tid < most) sc->sel[tid] = cw;
+        const int m = __syncthreads_count(cw != 0ull);          // (the words without an entry come last)
+        last = m == most ? candidate_score(sc->sel[most - 1]) : 0.f;
+        inv = inv_norm_of(sh_square);
+        restate(sc->sel, m, a.keys, a.inv_norm, query, a.d, inv, stage, stage_bytes);
+        rank = restated_rank(sc->sel, m);
+        if (tid < m && rank == a.k_out - 1) sh_kth = sc->sel[tid];
+        __syncthreads();
+        return m;
+    };
+    int m = again(a.k);
+    bool done = restated_suffice(m, a.k, last, sh_kth, sh_square, a.d);       // (uniform)
+    if (!done && sh_kth != 0ull && f32_ordinary(inv)) {
+        const float reach = candidate_score(sh_kth) - split_error(a.d);
+        const uint64_t word = (uint64_t)score_to_ordered(reach) << 32;
+        if (word > t64) {       // the list has them all
+            __syncthreads();
+            best_again(word);
+            m = again(SELECT_MAX);
+            done = m < SELECT_MAX;
+        }
+    }
+    if (done) write_restated(sc->sel, m, rank, q, a.k_out, a.out_index, a.out_score);
+    if (tid == 0) {
+        // what the scan behind this launch lists: nothing, or what reaches the k-th best f32 word known
+        const float x = inv > 0.f && sh_kth != 0ull ? candidate_score(sh_kth) / inv : -__builtin_inff();
+        a.thr64[q] = done ? ~0ull : sh_kth;
+        a.thrp[q] = done ? __builtin_inff() : x - fabsf(x) * 0x1p-20f - 1e-30f;
+        if (!done) a.stats[STAT_GATE] = 1;
+    }
+    if (tid < CAND_SEGMENTS) a.cnt[(size_t)q * CAND_SEGMENTS + tid] = 0;        // (everyone has read them)
+}
+
 template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -2017,7 +2119,7 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
             return;
         }
     }
-    if (flagged) {
+    if (KT != KB_F32_SPLIT && flagged) {
         // The grid has fb_parts workgroups per query; for a flagged query each scans its share of the rows and leaves
         // its best k as a sorted list, and the one that arrives last merges the lists.  (One workgroup alone would
         // read the whole knowledge base at the speed of a single compute unit.)
@@ -2057,61 +2159,43 @@ template <int KT> __global__ __launch_bounds__(256) void finalize_kernel(FinalAr
         const float iq = used_inv<KT>(a.invq[q]);
         const uint64_t t64 = a.raw ? a.thr64[q] : 0ull;
         const uint64_t *lists = a.cand + (size_t)q * a.cand_cap;
-        for (uint32_t j0 = tid; j0 < n; j0 += 4 * 256) {
-            uint64_t w[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t j = j0 + u * 256;
-                uint32_t sg = 0, off = 0;
-#pragma unroll
-                for (int s2 = 1; s2 < CAND_SEGMENTS; ++s2) {
-                    const bool past = j >= seg_off[s2];
-                    sg += past ? 1u : 0u;
-                    off = past ? seg_off[s2] : off;
-                }
-                w[u] = j < n ? lists[sg * seg_cap + (j - off)] : 0ull;
-            }
-            if (a.raw) {
+        auto gather = [&](uint64_t least) {
+            for (uint32_t j0 = tid; j0 < n; j0 += 4 * 256) {
+                uint64_t w[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const uint64_t c = pack_candidate(raw_candidate_product(w[u]) * iq + 0.0f, candidate_index(w[u]));
-                    w[u] = (w[u] != 0ull && c >= t64) ? c : 0ull;
-                }
-            }
+                    const uint32_t j = j0 + u * 256;
+                    uint32_t sg = 0, off = 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (j0 + u * 256 < n) buf[j0 + u * 256] = w[u];
-        }
-        __syncthreads();
-        select_topk_desc(buf, (int)n, a.k, sc, tid, 256);
-    }
-    if constexpr (KT == KB_F32_SPLIT) {
-        __shared__ float sh_square;
-        __shared__ uint64_t sh_kth;
-        const uint64_t cw = tid < a.k ? buf[tid] : 0ull;
-        if (tid < a.k) sc->sel[tid] = cw;
-        if (tid < 64) {
-            const float square_sum = row_square_sum<KB_F32>(a.queries, q, a.d * 4, tid);
-            if (tid == 0) {
-                sh_square = square_sum;
-                sh_kth = 0;
+                    for (int s2 = 1; s2 < CAND_SEGMENTS; ++s2) {
+                        const bool past = j >= seg_off[s2];
+                        sg += past ? 1u : 0u;
+                        off = past ? seg_off[s2] : off;
+                    }
+                    w[u] = j < n ? lists[sg * seg_cap + (j - off)] : 0ull;
+                }
+                if (a.raw) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint64_t c = pack_candidate(raw_candidate_product(w[u]) * iq + 0.0f, candidate_index(w[u]));
+                        w[u] = (w[u] != 0ull && c >= least) ? c : 0ull;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (j0 + u * 256 < n) buf[j0 + u * 256] = w[u];
             }
+            __syncthreads();
+        };
+        gather(t64);
+        select_topk_desc(buf, (int)n, a.k, sc, tid, 256);
+        if constexpr (KT == KB_F32_SPLIT) {
+            finish_split(a, q, buf, sc, smem_raw, t64, [&](uint64_t least) {
+                gather(least);
+                select_topk_desc(buf, (int)n, SELECT_MAX, sc, tid, 256);
+            });
+            return;
         }
-        const int m = __syncthreads_count(cw != 0ull);          // (the words without an entry come last)
-        const float last = m == a.k ? candidate_score(sc->sel[a.k - 1]) : 0.f, inv = inv_norm_of(sh_square);
-        restate(sc->sel, m, a.keys, a.inv_norm, static_cast<const float *>(a.queries) + (size_t)q * a.d, a.d, inv, reinterpret_cast<float *>(a.more_lds ? smem_raw + a.more_at : smem_raw), a.more_lds ? a.more_lds : a.cand_cap * 8);
-        write_restated(sc, m, q, a.k_out, a.out_index, a.out_score, &sh_kth);
-        __syncthreads();
-        if (tid == 0) {
-            // what the scan behind this launch lists: nothing, or what reaches the k-th best f32 word known
-            const bool done = restated_suffice(m, a.k, last, sh_kth, sh_square, a.d);
-            const float x = inv > 0.f && sh_kth != 0ull ? candidate_score(sh_kth) / inv : -__builtin_inff();
-            a.thr64[q] = done ? ~0ull : sh_kth;
-            a.thrp[q] = done ? __builtin_inff() : x - fabsf(x) * 0x1p-20f - 1e-30f;
-            if (!done) a.stats[STAT_GATE] = 1;
-        }
-        if (tid < CAND_SEGMENTS) a.cnt[(size_t)q * CAND_SEGMENTS + tid] = 0;        // (everyone has read them)
-        return;
     }
     if (tid < a.k) {
         const uint64_t cw = tid < a.cand_cap ? buf[tid] : 0ull;
@@ -2753,7 +2837,7 @@ kb_status_t launch_whole(kb *h, const WholePlan &p, const void *queries_dev, boo
     const int kt = q8 ? KT_FP8_Q8 : split ? KB_F32_SPLIT : (int)h->dtype;
     auto *fn = p.stream ? whole_select_for<true>(kt, p.groups) : whole_select_for<false>(kt, p.groups);
     t.gate = split ? gate : nullptr;
-    t.more_lds = split ? restate_lds(Q, k, h->d) : 0;
+    t.more_lds = split ? restate_lds(Q) : 0;
     static LdsAllowed allowed[6];
     if (t.more_lds > 0 && allow_dynamic_lds(reinterpret_cast<const void *>(fn), allowed[(p.stream ? 3 : 0) + (p.groups <= 4 * WHOLE_THREADS ? 0 : p.groups <= 8 * WHOLE_THREADS ? 1 : 2)], RESTATE_LDS) != hipSuccess)
         return KB_ERR_DEVICE;
@@ -3202,7 +3286,7 @@ static kb_status_t run_query(kb_t *kb, const void *queries_dev, kb_dtype_t q_dty
     constexpr size_t FIN_LDS_MAX = ((size_t)MAX_CAND_CAP * 8 + 16 + sizeof(SelectScratch) + 15) / 16 * 16;
     const size_t fin_base = ((size_t)p.cand_cap * 8 + 16 + sizeof(SelectScratch) + 15) / 16 * 16;
     f.more_at = (int32_t)fin_base;
-    f.more_lds = split ? std::min(restate_lds(Q, r.k, kb->d), (int)(MAX_CAND_CAP * 8 + RESTATE_LDS / 2 - fin_base)) : 0;
+    f.more_lds = split ? std::min(restate_lds(Q), (int)(MAX_CAND_CAP * 8 + RESTATE_LDS / 2 - fin_base)) : 0;
     const size_t fin_lds = fin_base + f.more_lds;
     static LdsAllowed fin_allowed[5];
     const int fin_kind = q8 ? KT_FP8_Q8 : split ? KB_F32_SPLIT : (int)kb->dtype;

@@ -45,9 +45,9 @@ def test_the_plans_that_are_meant(shape, plan):
     kb.close()
 
 
-# `copies` rows that are one vector but for noise, for half of the queries: a handful that straddle the k-th place, more than are scored again
-# (the f32 instruction decides), copies with no noise at all; noise from where f32 sums tell them apart to where they don't
-@pytest.mark.parametrize("copies,noise", [(8, 1e-6), (24, 1e-5), (60, 1e-7), (60, 1e-6), (60, 1e-4), (60, 1e-3), (3000, 1e-6), (3000, 0.0)])
+# `copies` rows that are one vector but for noise, for half of the queries: a handful that straddle the k-th place, more than the first selection has (all
+# rows as close are scored again), more than that takes (the f32 instruction decides), copies with no noise at all; noise from where f32 sums tell them apart to where they don't
+@pytest.mark.parametrize("copies,noise", [(8, 1e-6), (24, 1e-5), (60, 1e-7), (60, 1e-6), (60, 1e-4), (60, 1e-3), (150, 0.0), (165, 1e-6), (255, 0.0), (258, 0.0), (280, 1e-6), (3000, 1e-6), (3000, 0.0)])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_rows_that_lie_close(shape, copies, noise):
     N, d, Q, config = shape
