@@ -123,7 +123,8 @@ kb_status_t kb_query_plan(const kb_t *kb, int64_t n, int32_t Q, int32_t k, int32
  *   qmask_dev   [Q] uint64, or NULL = no filtering for any query (a zero mask word qualifies nothing)
  *   k           1 .. KB_K_MAX
  *   indices_out_dev [Q, k] int32, scores_out_dev [Q, k] fp32: the result defined at the top of this file,
- *               scores computed as fp32( fp32(dot * inv_norm_i) * inv_norm_q ) with dot accumulated in fp32
+ *               scores computed as fp32( fp32(dot * inv_norm_i) * inv_norm_q ) with dot accumulated in fp32.  Until the call has
+ *               finished on the stream they may hold other values; they overlap no input and not the workspace.
  *   workspace_dev   256-byte aligned, at least kb_query_workspace_bytes(kb, Q, k); contents are scratch
  * Results are bit-identical from run to run.  Finite inputs are the caller's responsibility.
  * Errors: KB_ERR_NULL, KB_ERR_INVALID_ARG, KB_ERR_DTYPE, KB_ERR_NOT_NORMALIZED, KB_ERR_NO_TAGS,
@@ -275,9 +276,10 @@ kb_status_t kb_query_counters(const kb_t *kb, const void *workspace_dev, int64_t
  *   "sample_keys"   keys scored by the sampling pass (0 = automatic)
  *   "scan_config"   tile configuration of the scan kernel (0 = automatic)
  *   "wg_per_cu"     resident scan workgroups per compute unit (0 = automatic)
- *   "small_path"    1 (default): a knowledge base of up to some hundred thousand rows (fewer with more than 128 queries or a
- *                   large k), queried with no other knob set, is scored whole by two launches, three with the weighted
- *                   selection (no sampling pass, no candidate lists); 0: always the scan pipeline.  Both produce the same bits.
+ *   "small_path"    1 (default): a knowledge base of up to some hundred thousand rows (2^20 - 1 with up to 64 queries; fewer with
+ *                   more than 128 queries or a large k), queried with no other knob set, is scored whole by two launches, three with
+ *                   the weighted selection, four or five for large batches or stores of KB_F32 rows (no sampling pass, no candidate
+ *                   lists); 0: always the scan pipeline.  Both produce the same bits.
  *   "profile_stride" of a kb_profile_begin session, every value-th scan launch is timed: launch value/2 of each run of
  *                   `value` launches (0 or 1: every one).  A timed
  *                   launch costs the stream about 12 us of idle time around it; a stride spreads the timed launches

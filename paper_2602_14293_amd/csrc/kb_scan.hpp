@@ -72,7 +72,7 @@ template <> struct Mma<KB_F32> {
 };
 
 // f32, split: an element x of a row scaled by s (see f32_row_scale) is h + l, h the f16 value next to it and l the one next to the rest: 23
-// or 24 bits.  The products h h, h l and l h are exact and added up in f32 (l l, 2^-24 of them, is left out): three matrix instructions of
+// or 24 bits.  The products h h, h l and l h are exact and added up in f32 (l l, 2^-22 of them at most, is left out): three matrix instructions of
 // 32 clocks for 16 elements, where v_mfma_f32_32x32x2f32 takes eight of 64.  Against 64 bits the scores are closer than with the f32
 // instruction, whose accumulator is rounded five times as often: 2-norm error 1.2e-7 to 3.0e-7 where that has 1.8e-7 to 4.7e-7 (128 to 1024 elements).
 template <> struct Mma<KB_F32_SPLIT> {

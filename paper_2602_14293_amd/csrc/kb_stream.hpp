@@ -8,7 +8,7 @@
 // The tiled kernel meets a barrier every piece, reads the queries again for every tile and joins its wavefronts' groups through LDS.
 // A call with the tiled kernel's plan | with this one, us (bytes of rows over the second: TB/s):
 //   1,000,003 x 1024 bf16 rows, 1 query, masked    322 | 305 (6.7)     200,000 x 512 bf16, 64 queries    69.5 | 53.5 (3.8)
-//   300,007 x 384 f32 rows (split), 20 queries     98 | 89 (5.2)    200,000 x 512 fp8, 64 queries     60.5 | 36.9 (2.8)
+//   300,007 x 384 f32 rows (split), 20 queries     98 | 93 (5.0)    200,000 x 512 fp8, 64 queries     60.5 | 36.9 (2.8)
 // What is left: the launches and the selection (about 12 us), the first rows' way in (2), and with many queries or short rows the
 // search of the products, 1 us for 32 rows and 32 queries of each wavefront.
 #pragma once
@@ -53,8 +53,8 @@ template <int KT_, int TR_, int NST_, int NQ_> struct StreamCfg {
 // store's rows from jt * waves * TR on): rows dealt to the tiles one by one, so that rows rise with the places of a group and
 // neighbours, which may be alike, are in groups of their own (three of a query's best in one group cost a rescoring of it).
 // The distance of a tile's rows is odd (see whole_row; a few tiles have nothing to gain from it).
-// Dealt in runs of four, a tile's rows lie closer: 0 to 4 % faster on stores of 17,000 to 330,000 rows in no order (700,000 x 128 bf16 53.3 us
-// one by one, 48.0), and slower by far on stores of similar neighbours: 90,000 x 512, 16 queries, k 32, runs of 16 26.1 us one by one, 47.7;
+// Dealt in runs of four, a tile's rows lie closer: 0 to 4 % faster on stores of 17,000 to 330,000 rows in no order, 11 % on larger ones of short rows (700,000 x 128 bf16
+// 53.3 us one by one, 48.0), and slower by far on stores of similar neighbours: 90,000 x 512, 16 queries, k 32, runs of 16 26.1 us one by one, 47.7;
 // 200,000 x 512 43.9, 79.7; pairs of rows 26.6 and 45.8 (runs of 4: 30.8).
 __host__ __device__ inline int32_t stream_step(int32_t c) { return c <= 64 ? 0 : (c & 1) != 0 ? 2 : 1; }
 __host__ __device__ inline int32_t stream_row(int32_t base, int32_t w, int32_t c, int32_t step, int pos)

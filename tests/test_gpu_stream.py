@@ -2,11 +2,9 @@
 tiles, layers and groups change, for every type of keys and queries; the plan with few groups that a call with little memory gets."""
 import ctypes
 
-import numpy as np
 import pytest
 import torch
 
-import kb_testlib as T
 from paper_2602_14293_amd import kb as kbmod
 from paper_2602_14293_amd import workloads as W
 
