@@ -154,3 +154,36 @@ def test_in_a_graph(shape):
         want = _check(kb, what, 10, config)
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
     kb.close()
+
+
+# Less memory than the plan asks for, down to where the call is refused, and the library's own scratch array: the same results
+@pytest.mark.parametrize("shape", SHAPES)
+def test_with_less_memory(shape):
+    N, d, Q, config = shape
+    rows, q, g = _rows(N, d, Q, 10)
+    at = torch.randperm(N, generator=g, device="cuda")[:60]
+    rows[at] = rows[at[0]].clone() * (1.0 + 1e-6 * torch.randn((60, d), generator=g, device="cuda"))
+    q[: Q // 2] = rows[at[0]] + 0.3 * q[: Q // 2]
+    kb = _store(rows)
+    want = _check(kb, q, 10, config)
+    served = 0
+    have = kb.plan(Q, 10)["bytes"]
+    while have > 0:
+        ws = torch.full((have,), 0xA5, dtype=torch.uint8, device="cuda")
+        index, score = torch.full_like(want[0], -7), torch.full_like(want[1], float("nan"))
+        st = kbmod.lib().kb_query(kb._h, kbmod._ptr(q), kbmod.KB_F32, Q, None, 10, kbmod._ptr(index), kbmod._ptr(score), kbmod._ptr(ws), have, kbmod._stream())
+        if st == 7:                     # KB_ERR_WORKSPACE
+            break
+        torch.cuda.synchronize()
+        assert st == 0 and torch.equal(index, want[0]) and torch.equal(score, want[1]), have
+        served += 1
+        have = min(kb.plan(Q, 10, workspace_bytes=have)["bytes"], have) - 1
+    assert served >= 1
+    index, score = torch.empty_like(want[0]), torch.empty_like(want[1])
+    try:
+        kb.query_static(q, 10, None, index, score)
+    except kbmod.KBError as e:
+        assert e.status == 7
+    else:
+        assert torch.equal(index, want[0]) and torch.equal(score, want[1])
+    kb.close()

@@ -74,10 +74,11 @@ def test_the_bits_of_the_pipeline(kind, N, d, Q, k):
 
 # Calls whose scan takes f32 rows as two f16 values an element: the bits of the f32 instruction (a configuration asked for by name keeps to it),
 # from the whole-store plan and from the pipeline.  Just as many rows as few queries take, and the most, the longest rows and the largest k, the largest k and
-# two query blocks of many, every product written, lists of the pipeline; rows whose lengths are powers of two apart.
+# two query blocks of many, lists of the pipeline; rows whose lengths are powers of two apart.  (The second half: calls under the limits, which keep to the f32 instruction.)
 @pytest.mark.parametrize("N,d,Q,k,config", [
-    ((1 << 20) - 1, 64, 7, 32, 1), (524300, 96, 32, 20, 1), (78700, 640, 22, 4, 1), (224800, 224, 31, 32, 1), (105000, 480, 9, 32, 1), (51000, 992, 14, 19, 1),
-    (70001, 512, 120, 12, 2), (16400, 1024, 256, 124, 3), (16400, 1024, 256, 128, 3), (40000, 160, 700, 40, 3), (8200, 2048, 257, 9, 3), (400001, 352, 33, 16, 26)])
+    ((1 << 20) - 1, 64, 7, 32, 1), (524300, 96, 32, 20, 1), (164000, 640, 22, 4, 1), (327681, 160, 31, 32, 1), (218500, 480, 9, 32, 1), (105800, 992, 14, 14, 1),
+    (70001, 512, 120, 12, 2), (49152, 1024, 128, 124, 2), (49152, 1024, 128, 128, 2), (33000, 512, 256, 128, 3), (40000, 160, 700, 40, 3), (8200, 2048, 257, 9, 3), (400001, 704, 33, 16, 26),
+    (78700, 640, 22, 4, 1), (224800, 224, 31, 32, 1), (105000, 480, 9, 32, 1), (51000, 992, 14, 19, 1), (16400, 1024, 256, 124, 3), (16400, 1024, 256, 128, 3), (400001, 352, 33, 16, 26)])
 def test_split_f32_rows_have_the_bits_of_the_f32_instruction(N, d, Q, k, config):
     kb, q, qmask = _store("f32", N, d, Q, k, seed=N + d, powers=True)
     for mask in (None, qmask):
